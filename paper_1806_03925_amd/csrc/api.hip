@@ -132,9 +132,6 @@ bool make_layout(const gear_config &c, Layout *lay) {
       lay->h[l] = take(&cur, B * lay->out_dim[l] * ab);
       lay->relu_bits[l] = take(&cur, B * lay->out_dim[l] / 8);
       lay->delta[l] = take(&cur, B * lay->out_dim[l] * ab);
-      lay->splitk[l] = gemm_splitk_max(c.mlp_dtype, lay->out_dim[l], lay->in_dim[l], c.max_batch);
-      const size_t pb = (size_t)lay->splitk[l] * wn * sizeof(float);
-      if (pb > max_partial) max_partial = pb;
     }
     if ((size_t)lay->out_dim[l] > max_h) max_h = lay->out_dim[l];
     if ((size_t)lay->in_dim[l] > max_h) max_h = lay->in_dim[l];
@@ -145,18 +142,14 @@ bool make_layout(const gear_config &c, Layout *lay) {
   lay->dx_emb = take(&cur, B * 2 * c.emb_dim * sizeof(float));
   lay->dx_dfv = take(&cur, B * c.dfv_dim * ab);
   {
-    // all hidden layers' partials at once when their products go out as one launch
+    // all hidden layers' partials at once: their products go out as one launch
     TnProblem wp[GEAR_MAX_LAYERS];
     size_t all = 0;
     for (int l = 0; l < L - 1; ++l) {
       wp[l] = TnProblem{nullptr, nullptr, nullptr, lay->out_dim[l], lay->in_dim[l]};
       all += (size_t)lay->in_dim[l] * lay->out_dim[l];
     }
-    // the count of k-ranges grows with the batch, and only batches of a multiple of 32 rows take this
-    // path: the largest such batch bounds what any step needs
-    const size_t pb =
-        (size_t)gemm_tn_batch_splits(c.mlp_dtype, wp, L - 1, c.max_batch / 32 * 32) * all * sizeof(float);
-    if (pb > max_partial) max_partial = pb;
+    max_partial = (size_t)gemm_tn_splits_max(c.mlp_dtype, wp, L - 1, c.max_batch) * all * sizeof(float);
   }
   lay->wgrad_partial = take(&cur, max_partial);
   lay->wgrad_partial_bytes = max_partial;
@@ -484,10 +477,6 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   static const char *const kDgrad[GEAR_MAX_LAYERS] = {"dgrad_gemm_l0", "dgrad_gemm_l1", "dgrad_gemm_l2",
                                                       "dgrad_gemm_l3", "dgrad_gemm_l4", "dgrad_gemm_l5",
                                                       "dgrad_gemm_l6", "dgrad_gemm_l7"};
-  static const char *const kWgrad[GEAR_MAX_LAYERS] = {"wgrad_gemm_l0", "wgrad_gemm_l1", "wgrad_gemm_l2",
-                                                      "wgrad_gemm_l3", "wgrad_gemm_l4", "wgrad_gemm_l5",
-                                                      "wgrad_gemm_l6", "wgrad_gemm_l7"};
-
   GEAR_RUN("begin", launch_begin(status, out->n_ready, out->loss, s));
   if (B == 0) return GEAR_OK;
   int32_t *occ_view = (int32_t *)(ws + lay.occ_view);
@@ -531,24 +520,22 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   }
   // forward
   void *x = ws + lay.x;
-  // the weight-gradient products of the hidden layers, and whether they go out as one launch
+  // the weight-gradient products of the hidden layers
   TnProblem wp[GEAR_MAX_LAYERS];
   int n_wp = 0;
   for (int l = L - 2; l >= 0; --l)
     wp[n_wp++] = TnProblem{ws + lay.delta[l], l == 0 ? x : ws + lay.h[l - 1], nullptr, lay.out_dim[l], lay.in_dim[l]};
-  const int batch_splits = gemm_tn_batch_splits(dt, wp, n_wp, B);
+  const int splits = gemm_tn_splits(dt, wp, n_wp, B);
   GEAR_RUN("gather_pool", launch_gather_pool(*cfg, *b, *t, dfv_cache, x, s));
-  // A hidden layer below the last one also leaves the sign bitmap of its activations when both its
-  // own product and the dgrad product that masks with it run in the kernel that knows bitmaps: the
-  // backward pass then reads one bit per unit instead of the activation.
+  // A bf16 hidden layer below the last one also leaves the sign bitmap of its activations: the backward pass then
+  // reads one bit per unit instead of the activation.
   uint8_t *relu_bits[GEAR_MAX_LAYERS] = {};
-  for (int l = 0; l + 2 < L; ++l)
-    if (gemm_nt_has_bits(dt, lay.in_dim[l]) && gemm_nt_has_bits(dt, lay.out_dim[l + 1]))
-      relu_bits[l] = (uint8_t *)(ws + lay.relu_bits[l]);
+  if (dt == GEAR_BF16)
+    for (int l = 0; l + 2 < L; ++l) relu_bits[l] = (uint8_t *)(ws + lay.relu_bits[l]);
   for (int l = 0; l < L - 1; ++l)
     GEAR_RUN(kFwd[l], launch_gemm_nt(dt, l == 0 ? x : ws + lay.h[l - 1], ws + lay.wc[l], B, lay.out_dim[l],
                                      lay.in_dim[l], EPI_BIAS_RELU, t->mlp_params + lay.b_off[l], nullptr,
-                                     ws + lay.h[l], 0, nullptr, relu_bits[l], status, s));
+                                     ws + lay.h[l], 0, nullptr, relu_bits[l], nullptr, s));
   // The helper stream's launches are issued after the forward pass's: where the host is not ahead of the
   // device (a caller that waits for every step), the gather then starts as soon as the step does, not
   // after the host has issued the grouping's many small launches.
@@ -587,29 +574,22 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
                                               moments_at(mom_mlp, lay.b_off[L - 2]), status, s));
     for (int l = L - 2; l > 0; --l) {
       // bias gradient of layer l - 1: column sums of its delta, left as per-row-tile partials by the
-      // product that made it where that kernel does so, otherwise summed here
+      // product that made it
       const int parts = gemm_nt_colsum_parts(dt, B, lay.in_dim[l], lay.out_dim[l]);
-      if (parts)
-        GEAR_RUN("bias_sgd", launch_partial_sgd(cpart + (size_t)l * lay.colsum_stride, parts, lay.out_dim[l - 1],
-                                                t->mlp_params + lay.b_off[l - 1], opt,
-                                                moments_at(mom_mlp, lay.b_off[l - 1]), status, s));
-      else
-        GEAR_RUN("bias_sgd", launch_colsum_sgd(dt, ws + lay.delta[l - 1], B, lay.out_dim[l - 1], cpart,
-                                               t->mlp_params + lay.b_off[l - 1], opt,
-                                               moments_at(mom_mlp, lay.b_off[l - 1]), status, s));
+      GEAR_RUN("bias_sgd", launch_partial_sgd(cpart + (size_t)l * lay.colsum_stride, parts, lay.out_dim[l - 1],
+                                              t->mlp_params + lay.b_off[l - 1], opt,
+                                              moments_at(mom_mlp, lay.b_off[l - 1]), status, s));
     }
     return GEAR_OK;
   };
   bool embedding_updated = false;
   for (int l = L - 2; l >= 0; --l) {
     if (l > 0) {
-      const int parts = gemm_nt_colsum_parts(dt, B, lay.in_dim[l], lay.out_dim[l]);
       const bool by_bits = relu_bits[l - 1] != nullptr;
       GEAR_RUN(kDgrad[l], launch_gemm_nt(dt, ws + lay.delta[l], ws + lay.wct[l], B, lay.in_dim[l], lay.out_dim[l],
                                          by_bits ? EPI_MASK_BITS : EPI_MASK, nullptr,
                                          by_bits ? (const void *)relu_bits[l - 1] : (const void *)(ws + lay.h[l - 1]),
-                                         ws + lay.delta[l - 1], 0, parts ? cpart + (size_t)l * lay.colsum_stride : nullptr, nullptr,
-                                         status, s));
+                                         ws + lay.delta[l - 1], 0, cpart + (size_t)l * lay.colsum_stride, nullptr, nullptr, s));
     } else {
       // dLoss/dx: the embedding slots stay fp32, the DFV slot is kept in the MLP's operand type.
       // When the product is long enough to hide it, it is made in two parts: the embedding slots
@@ -619,7 +599,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
       const int E2 = 2 * cfg->emb_dim;
       if ((double)B * (F - E2) * lay.out_dim[0] >= kSplitDxMacs) {
         GEAR_RUN("dgrad_gemm_emb", launch_gemm_nt(dt, ws + lay.delta[0], ws + lay.wct[0], B, E2, lay.out_dim[0], EPI_DX,
-                                                  nullptr, dx_dfv, dx_emb, E2, nullptr, nullptr, status, s));
+                                                  nullptr, dx_dfv, dx_emb, E2, nullptr, nullptr, nullptr, s));
         GEAR_HIP(lane.fork());
         {
           hipStream_t s = helper;
@@ -631,10 +611,10 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
         embedding_updated = true;
         GEAR_RUN(kDgrad[0], launch_gemm_nt(dt, ws + lay.delta[0],
                                            ws + lay.wct[0] + (size_t)E2 * lay.out_dim[0] * lay.act_bytes, B, F - E2,
-                                           lay.out_dim[0], EPI_DX, nullptr, dx_dfv, dx_emb, 0, nullptr, nullptr, status, s));
+                                           lay.out_dim[0], EPI_DX, nullptr, dx_dfv, dx_emb, 0, nullptr, nullptr, nullptr, s));
       } else {
         GEAR_RUN(kDgrad[0], launch_gemm_nt(dt, ws + lay.delta[0], ws + lay.wct[0], B, F, lay.out_dim[0], EPI_DX,
-                                           nullptr, dx_dfv, dx_emb, E2, nullptr, nullptr, status, s));
+                                           nullptr, dx_dfv, dx_emb, E2, nullptr, nullptr, nullptr, s));
       }
     }
   }
@@ -658,43 +638,24 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   }
   GEAR_HIP(lane.mark());
   // SGD on the hidden layers' weights: split-K wgrad (the logit layer and all biases are done on the helper stream)
-  bool joined = false;
-  if (batch_splits > 0) {
-    float *next = wpart;
-    for (int i = 0; i < n_wp; ++i) {
-      wp[i].partial = next;
-      next += (size_t)batch_splits * wp[i].M * wp[i].N;
-    }
-    if ((size_t)(next - wpart) * sizeof(float) > lay.wgrad_partial_bytes) return GEAR_ERR_CAPACITY;  // cannot happen: sized for the largest batch
-    GEAR_RUN("wgrad_gemm", launch_gemm_tn_batch(wp, n_wp, B, batch_splits, status, s));
-    SplitkProblem sp[GEAR_MAX_LAYERS];
-    for (int i = 0; i < n_wp; ++i) {
-      const int l = L - 2 - i;
-      sp[i] = SplitkProblem{wp[i].partial, t->mlp_params + lay.w_off[l], moments_at(mom_mlp, lay.w_off[l]),
-                            (int64_t)wp[i].M * wp[i].N};
-    }
-    // The sums of the partials and the SGD change caller state, so the status word has to be final: the
-    // stream waits for the helper's first part (long done by now), not for the bookkeeping.  Their
-    // workgroups get onto the device as the bookkeeping's leave room and are done before it is, so the
-    // step ends with the bookkeeping and the join.
-    GEAR_HIP(lane.wait_checked());
-    GEAR_RUN("splitk_sgd", launch_splitk_sgd_batch(sp, n_wp, batch_splits, opt, status, s));
-    GEAR_HIP(lane.wait(true));
-    joined = true;
-  } else {
-    for (int l = L - 2; l >= 0; --l) {
-      const int splits = gemm_splitk_for(dt, lay.out_dim[l], lay.in_dim[l], B);
-      if ((size_t)splits * lay.out_dim[l] * lay.in_dim[l] * sizeof(float) > lay.wgrad_partial_bytes)
-        return GEAR_ERR_CAPACITY;  // cannot happen: sized for the largest count any batch can ask for
-      GEAR_RUN(kWgrad[l], launch_gemm_tn_splitk(dt, ws + lay.delta[l], l == 0 ? x : ws + lay.h[l - 1], lay.out_dim[l],
-                                                lay.in_dim[l], B, splits, wpart, status, s));
-      if (l == L - 2) GEAR_HIP(lane.wait_checked());
-      GEAR_RUN("splitk_sgd", launch_splitk_sgd(wpart, splits, (int64_t)lay.out_dim[l] * lay.in_dim[l],
-                                               t->mlp_params + lay.w_off[l], opt, moments_at(mom_mlp, lay.w_off[l]),
-                                               status, s));
-    }
+  float *next = wpart;
+  SplitkProblem sp[GEAR_MAX_LAYERS];
+  for (int i = 0; i < n_wp; ++i) {
+    const int l = L - 2 - i;
+    wp[i].partial = next;
+    next += (size_t)splits * wp[i].M * wp[i].N;
+    sp[i] = SplitkProblem{wp[i].partial, t->mlp_params + lay.w_off[l], moments_at(mom_mlp, lay.w_off[l]),
+                          (int64_t)wp[i].M * wp[i].N};
   }
-  if (!joined) GEAR_HIP(lane.wait(true));  // the step ends on the caller's stream
+  if ((size_t)(next - wpart) * sizeof(float) > lay.wgrad_partial_bytes) return GEAR_ERR_CAPACITY;  // cannot happen: sized for the largest batch
+  GEAR_RUN("wgrad_gemm", launch_gemm_tn(dt, wp, n_wp, B, splits, nullptr, s));
+  // The sums of the partials and the SGD change caller state, so the status word has to be final: the
+  // stream waits for the helper's first part (long done by now), not for the bookkeeping.  Their
+  // workgroups get onto the device as the bookkeeping's leave room and are done before it is, so the
+  // step ends with the bookkeeping and the join.
+  GEAR_HIP(lane.wait_checked());
+  GEAR_RUN("splitk_sgd", launch_splitk_sgd(sp, n_wp, splits, opt, status, s));
+  GEAR_HIP(lane.wait(true));  // the step ends on the caller's stream
   if (out->dbg_img_unique && b->nnz > 0)
     GEAR_HIP(hipMemcpyAsync(out->dbg_img_unique, gb.p[2].unique, (size_t)b->nnz * 4, hipMemcpyDeviceToDevice, s));
   if (out->dbg_img_segoff)
@@ -801,11 +762,13 @@ gear_status gear_gemm(int32_t dtype, int32_t form, const void *A, const void *B,
     GEAR_HIP(launch_gemm_nt(dtype, A, B, M, N, K, epilogue, bias, aux, out, 0, nullptr, nullptr, status, s));
   } else if (form == 1) {
     if (M % vec || N % vec || splits < 1 || splits > 64 || !partial) return GEAR_ERR_INVALID;
-    GEAR_HIP(launch_gemm_tn_splitk(dtype, A, B, M, N, K, splits, partial, status, s));
+    const TnProblem one = {A, B, partial, M, N};
+    GEAR_HIP(launch_gemm_tn(dtype, &one, 1, K, splits, status, s));
     GEAR_HIP(launch_fill_zero(out, (size_t)M * N * sizeof(float), s));
     const Optim minus = {-1.0f, 0.0f, 0.0f, 0.0f, 1.0f, 0};   // out = 0 - (-1) * sum of the partials
     const Moments none = {nullptr, nullptr};
-    GEAR_HIP(launch_splitk_sgd(partial, splits, (int64_t)M * N, (float *)out, minus, none, status, s));
+    const SplitkProblem sum = {partial, (float *)out, none, (int64_t)M * N};
+    GEAR_HIP(launch_splitk_sgd(&sum, 1, splits, minus, status, s));
   } else {
     return GEAR_ERR_INVALID;
   }

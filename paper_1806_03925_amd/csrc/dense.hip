@@ -145,11 +145,12 @@ gear_status dense_backward(const gear_dense_config *cfg, const float *raw, float
   // of range leaves the status word set and the weights untouched (both kernels below then stay idle)
   int splits = n_dev ? lay.splits : (n_ready + 255) / 256;
   if (splits > lay.splits) splits = lay.splits;
-  DENSE_HIP(launch_gemm_tn_splitk(GEAR_F32, ready_grads, rows, cfg->dfv_dim, cfg->raw_dim, n_ready, splits, partial,
-                                  status, s, n_dev));
+  const TnProblem dw = {ready_grads, rows, partial, cfg->dfv_dim, cfg->raw_dim};
+  DENSE_HIP(launch_gemm_tn(GEAR_F32, &dw, 1, n_ready, splits, status, s, n_dev));
   const Optim sgd = {lr, 0.0f, 0.0f, 0.0f, 1.0f, 0};
   const Moments none = {nullptr, nullptr};
-  DENSE_HIP(launch_splitk_sgd(partial, splits, (int64_t)cfg->dfv_dim * cfg->raw_dim, wd, sgd, none, status, s));
+  const SplitkProblem sum = {partial, wd, none, (int64_t)cfg->dfv_dim * cfg->raw_dim};
+  DENSE_HIP(launch_splitk_sgd(&sum, 1, splits, sgd, status, s));
   return GEAR_OK;
 }
 }  // namespace

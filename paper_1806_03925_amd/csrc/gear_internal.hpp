@@ -155,7 +155,6 @@ struct Layout {
   int64_t w_off[GEAR_MAX_LAYERS];    // float offsets into mlp_params
   int64_t b_off[GEAR_MAX_LAYERS];
   int64_t n_params;
-  int32_t splitk[GEAR_MAX_LAYERS];   // wgrad split count per layer
   int32_t colsum_chunks;             // row chunks of the column-sum kernels
   size_t act_bytes;                  // sizeof(mlp_dtype)
 
@@ -176,7 +175,7 @@ struct Layout {
 bool make_layout(const gear_config &cfg, Layout *lay);
 bool config_ok(const gear_config &cfg);
 
-constexpr int kColsumRows = 128;     // rows per partial of a column sum
+constexpr int kColsumRows = 64;      // least rows per partial of a column sum
 constexpr int kLossBlocks = 2048;    // most workgroups (and partial sums) of the logit/loss kernel
 
 // ------------------------------------------------------------------------------------------------
@@ -219,34 +218,28 @@ enum GemmEpilogue {
   EPI_MASK_BITS = 4,  // EPI_MASK with aux = the bitmap [M x N/8] an EPI_BIAS_RELU product left in `relu_bits`
 };
 // C[M x N] = A[M x K] * B[N x K]^T, both operands K-contiguous, type `dtype`.
-// relu_bits (EPI_BIAS_RELU only, may be NULL): bit (n % 8) of byte [m][n / 8] = (out[m][n] > 0); only
-// written by the kernel gemm_nt_has_bits() names, which is also the only one that takes EPI_MASK_BITS.
+// relu_bits (bf16 and EPI_BIAS_RELU only, may be NULL): bit (n % 8) of byte [m][n / 8] = (out[m][n] > 0), which is
+// what EPI_MASK_BITS (bf16 only) masks with.  colpart (masked products, may be NULL): [parts x N] column sums of
+// what is stored, per row tile.  status may be NULL (the product then always runs).
 hipError_t launch_gemm_nt(int dtype, const void *A, const void *B, int M, int N, int K, int epilogue,
                           const float *bias, const void *aux, void *out, int split, float *colpart,
                           uint8_t *relu_bits, const int32_t *status, hipStream_t s);
 int gemm_nt_colsum_parts(int dtype, int M, int N, int K);
-bool gemm_nt_has_bits(int dtype, int K);
 // dst[j] -= lr * sum_p partial[p][j], p ascending in a fixed two-level shape
 hipError_t launch_partial_sgd(const float *partial, int P, int H, float *dst, const Optim &opt, const Moments &mom,
                               const int32_t *status, hipStream_t s);
-// partial[z][M x N] = sum over the z-th K range of A[K x M]^T * B[K x N] (operands M-/N-contiguous).
-// k_dev (may be NULL): device word holding the real contraction length, at most K; the split into
-// `splits` ranges is then made on the device.
-hipError_t launch_gemm_tn_splitk(int dtype, const void *A, const void *B, int M, int N, int K, int splits,
-                                 float *partial, const int32_t *status, hipStream_t s, const int32_t *k_dev = nullptr);
-int gemm_splitk_for(int dtype, int M, int N, int K);  // wgrad split count for a [M x N] result contracted over K
-int gemm_splitk_max(int dtype, int M, int N, int K);  // the largest such count over all contraction lengths up to K
-// Several such contractions over the same K rows of bf16 operands in one launch, all with the same
-// number of k-ranges: partial_i[z][M_i x N_i].  gemm_tn_batch_splits gives that number (it looks at
-// M and N only), or 0 if the set has to go through one launch per problem.
+// partial_i[z][M_i x N_i] = sum over the z-th of `splits` ranges of the K rows of A_i[K x M_i]^T * B_i[K x N_i], for
+// all problems in one launch (operands M-/N-contiguous).  k_dev (may be NULL): device word holding the real
+// contraction length, at most K; it is then split into ranges on the device.
 struct TnProblem {
   const void *A, *B;
   float *partial;
   int M, N;
 };
-int gemm_tn_batch_splits(int dtype, const TnProblem *p, int count, int K);
-hipError_t launch_gemm_tn_batch(const TnProblem *p, int count, int K, int splits, const int32_t *status,
-                                hipStream_t s);
+hipError_t launch_gemm_tn(int dtype, const TnProblem *p, int count, int K, int splits, const int32_t *status,
+                          hipStream_t s, const int32_t *k_dev = nullptr);
+int gemm_tn_splits(int dtype, const TnProblem *p, int count, int K);      // ranges to ask for (looks at M and N only)
+int gemm_tn_splits_max(int dtype, const TnProblem *p, int count, int K);  // the most any contraction length up to K asks for
 // w_i <- update(w_i, sum_z partial_i[z]) for the results of such a launch, in one launch
 struct SplitkProblem {
   const float *partial;
@@ -254,10 +247,16 @@ struct SplitkProblem {
   Moments mom;
   int64_t count;
 };
-hipError_t launch_splitk_sgd_batch(const SplitkProblem *p, int count, int splits, const Optim &opt,
-                                   const int32_t *status, hipStream_t s);
-hipError_t launch_splitk_sgd(const float *partial, int splits, int64_t count, float *w, const Optim &opt,
-                             const Moments &mom, const int32_t *status, hipStream_t s);
+hipError_t launch_splitk_sgd(const SplitkProblem *p, int count, int splits, const Optim &opt, const int32_t *status,
+                             hipStream_t s);
+// the same products on tiles of moderate size (gemm_tile.hip)
+hipError_t launch_gemm_nt_tile(int dtype, const void *A, const void *B, int M, int N, int K, int epilogue,
+                               const float *bias, const void *aux, void *out, int split, float *colpart,
+                               uint8_t *relu_bits, const int32_t *status, hipStream_t s);
+int nt_tile_colsum_parts(int dtype, int M, int N);
+hipError_t launch_gemm_tn_tile(int dtype, const TnProblem *p, int count, int K, int splits, const int32_t *status,
+                               hipStream_t s, const int32_t *k_dev);
+int tn_tile_splits(int dtype, const TnProblem *p, int count, int K);
 
 hipError_t launch_logit_loss(int dtype, const void *h, const void *wc_last, const float *bias_last, const float *label,
                              int B, int H, float *logits, float *dz, void *delta, float *partials,
@@ -266,9 +265,6 @@ hipError_t launch_logit_finish(float *partials, int B, int H, float *w_last, flo
                                float *loss, const Optim &opt, const Moments &mom_w_last, const Moments &mom_bias_last,
                                const Moments &mom_bias_hidden, const int32_t *status, hipStream_t s);
 size_t logit_partial_floats(int H);
-
-hipError_t launch_colsum_sgd(int dtype, const void *src, int B, int H, float *partial, float *dst, const Optim &opt,
-                             const Moments &mom, const int32_t *status, hipStream_t s);
 
 hipError_t launch_embedding_update(const gear_config &cfg, const GroupProblem &users, const GroupProblem &urls,
                                    const float *dx_emb, void *user_emb, void *url_emb, float *partials,

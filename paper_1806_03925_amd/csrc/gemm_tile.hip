@@ -1,0 +1,703 @@
+// Matrix products on tiles of moderate size, both operand types, any inner length (Section 3, step 4: the
+// Sparse Part forward and backward).  The large bf16 products have kernels of their own (gemm.hip); what runs
+// here is bound by latency and by how many CUs have a tile at all, not by any peak: a layer of 256 columns over
+// 4096 rows is sixteen tiles of 256 x 256, but 256 tiles of 64 x 64.
+//
+// Operand tiles are copied global -> LDS by DMA into a ring of stages, several stages ahead, so that one memory
+// latency is paid per product and not one per k-tile.  (A register-staged form with one k-tile ahead took 15 us
+// for 4096 x 256 x 320 in fp32, this one 10; the weight gradients of 4096 x (320 -> 256 -> 128) took 63 us in four
+// launches, now 19 in two.)  What lies beyond an operand's inner length is copied from a line of
+// zeros, so no inner length needs padding, and rows beyond the matrix repeat its last row and are not stored.
+#include "gemm_common.hpp"
+
+#include <type_traits>
+
+namespace gear {
+namespace {
+
+__device__ uint4 g_zero_piece;   // sixteen zero bytes, the source of every piece beyond an operand's end
+
+// ---- NT: C = A B^T, a stage is 128 bytes of k per operand row (64 bf16 or 32 fp32) --------------------------
+template <typename T_, int WTM_, int WTN_, int WAVES_M_, int WAVES_N_, int STAGES_> struct NtTile {
+  using T = T_;
+  static constexpr int WTM = WTM_, WTN = WTN_, WAVES_M = WAVES_M_, WAVES_N = WAVES_N_, STAGES = STAGES_;
+  static constexpr int WAVES = WAVES_M * WAVES_N, THREADS = WAVES * kWave;
+  static constexpr int BM = 32 * WTM * WAVES_M, BN = 32 * WTN * WAVES_N;
+  static constexpr int VEC = 16 / (int)sizeof(T), KS = 8 * VEC;
+  static constexpr int STAGE_BYTES = (BM + BN) * 128;
+  static constexpr int DMA_A = BM / 8 / WAVES, DMA_B = BN / 8 / WAVES;   // instructions of a wave per stage
+  static constexpr int PER_STAGE = DMA_A + DMA_B;
+  static_assert(DMA_A * 8 * WAVES == BM && DMA_B * 8 * WAVES == BN, "a DMA instruction copies eight rows");
+  static_assert((STAGES - 1) * PER_STAGE < 64, "outstanding copies are counted in six bits");
+};
+
+template <int N> __device__ __forceinline__ void wait_lgkm() { asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(N) : "memory"); }
+template <typename V> __device__ __forceinline__ void landed(V &r) { asm volatile("" : "+v"(r)); }
+template <int OFF> __device__ __forceinline__ void lds_read16(u32x4_v &dst, uint32_t addr) {
+  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(OFF) : "memory");
+}
+template <int OFF> __device__ __forceinline__ void lds_read4(float &dst, uint32_t addr) {
+  asm volatile("ds_read_b32 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(OFF) : "memory");
+}
+template <int OFF> __device__ __forceinline__ void lds_read_tr(u32x2_v &dst, uint32_t addr) {
+  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(OFF) : "memory");
+}
+
+// One 16-byte piece per lane from global memory to LDS (lane i's goes to dst + 16 i), or zeros where `in` is false.
+// The choice of source is hidden from the compiler, which would otherwise copy under two execution masks in turn.
+__device__ __forceinline__ void copy_piece(const void *src, unsigned char *dst) {
+  __builtin_amdgcn_global_load_lds(src, (lds_ptr_t)dst, 16, 0, 0);
+}
+__device__ __forceinline__ void copy_piece_or_zero(const void *src, bool in, uint64_t zero, unsigned char *dst) {
+  uint64_t at = in ? (uint64_t)(uintptr_t)src : zero;
+  asm volatile("" : "+v"(at));
+  __builtin_amdgcn_global_load_lds((const void *)(uintptr_t)at, (lds_ptr_t)dst, 16, 0, 0);
+}
+__device__ __forceinline__ uint64_t zero_address() {   // fetched once, not before every use
+  uint64_t z = (uint64_t)(uintptr_t)&g_zero_piece;
+  asm volatile("" : "+s"(z));
+  return z;
+}
+
+// wait until at most `stages` later stages of PER copies each are outstanding (0 <= stages <= MAX)
+template <int PER, int MAX> __device__ __forceinline__ void wait_stages(int stages) {
+  if constexpr (MAX == 0) {
+    wait_vm<0>();
+  } else {
+    if (stages >= MAX)
+      wait_vm<PER * MAX>();
+    else
+      wait_stages<PER, MAX - 1>(stages);
+  }
+}
+
+// Operands of one k-step (a quarter of a stage) in registers.  LDS rows are 128 bytes with their eight 16-byte pieces
+// XOR-ed by the row's number modulo 8, so that the 32 rows a read touches spread over all banks; a k-step is two
+// pieces of a row, one for either half-wave: neighbours in bf16 (one product takes all sixteen values), in fp32 one
+// from either half of the row.
+template <typename C> struct Frag {
+  u32x4_v a[C::WTM], b[C::WTN];
+  __device__ __forceinline__ void fetch(uint32_t a_addr, uint32_t b_addr) {
+    static_assert(C::WTM <= 2 && C::WTN <= 2, "tiles of a wave");
+    lds_read16<0>(a[0], a_addr);
+    if constexpr (C::WTM > 1) lds_read16<4096>(a[1], a_addr);
+    lds_read16<0>(b[0], b_addr);
+    if constexpr (C::WTN > 1) lds_read16<4096>(b[1], b_addr);
+  }
+  template <int LATER> __device__ __forceinline__ void wait() {   // at most LATER reads issued after these are outstanding
+    wait_lgkm<LATER>();
+#pragma unroll
+    for (int i = 0; i < C::WTM; ++i) landed(a[i]);
+#pragma unroll
+    for (int j = 0; j < C::WTN; ++j) landed(b[j]);
+  }
+  // bf16 is taken transposed (a lane holds four consecutive columns of a row, see epilogue_patch); fp32 is not (a lane
+  // holds one column, half a wave stores 128 contiguous bytes).  An fp32 product takes two k-values,
+  // k and k + 16 of the stage's 32, k ascending: a fixed order, the same in every shape.
+  // The scheduler may not move products across: it would otherwise put the next wait between them.
+  __device__ __forceinline__ void mma(f32x16_v (&acc)[C::WTM][C::WTN]) const {
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (sizeof(typename C::T) == 2) {
+#pragma unroll
+      for (int i = 0; i < C::WTM; ++i)
+#pragma unroll
+        for (int j = 0; j < C::WTN; ++j) MFMA_BF16_T(acc[i][j], a[i], b[j]);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < C::WTM; ++i)
+#pragma unroll
+          for (int j = 0; j < C::WTN; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[i][e]), __uint_as_float(b[j][e]),
+                                                             acc[i][j], 0, 0, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+};
+
+// The main loop, one form per number of stages.
+//
+// Two stages (bf16): the next stage is copied while this one is multiplied; 64 KB, so two workgroups share a CU and
+// one multiplies while the other waits.
+//
+// More (fp32): an fp32 product keeps the SIMD's vector unit busy as well (measured: every vector instruction between
+// two of them adds its own four cycles, 153 TFLOP/s bare, 110 with four in between), so the loop has as few as it
+// can.  The wait for the next stage and the barrier sit in the middle of a stage, and a k-step's operands are
+// requested one step (256 cycles of products) ahead, also across the border of a stage.
+template <typename C, typename Issue>
+__device__ __forceinline__ void nt_main_loop(f32x16_v (&acc)[C::WTM][C::WTN], uint32_t a_rel, uint32_t b_rel, int nk, Issue issue) {
+  constexpr int S = C::STAGES;
+  constexpr uint32_t STEP = sizeof(typename C::T) == 2 ? 32u : 16u;   // from a k-step's piece to the next one's
+  Frag<C> f[2];
+  if constexpr (S == 2) {
+    constexpr int READS = C::WTM + C::WTN;
+    uint32_t so = 0;
+    for (int t = 0; t < nk; ++t) {
+      wait_vm<0>();      // this wave's share of stage t has landed
+      block_barrier();   // everybody's has, and everybody is done reading stage t - 1
+      if (t + 1 < nk) issue(t + 1, (t + 1) & 1);
+      const uint32_t a = a_rel + so, b = b_rel + so;
+      f[0].fetch(a, b);
+      f[1].fetch(a ^ STEP, b ^ STEP);
+      f[0].template wait<READS>();
+      f[0].mma(acc);
+      f[0].fetch(a ^ (2 * STEP), b ^ (2 * STEP));
+      f[1].template wait<READS>();
+      f[1].mma(acc);
+      f[1].fetch(a ^ (3 * STEP), b ^ (3 * STEP));
+      f[0].template wait<READS>();
+      f[0].mma(acc);
+      f[1].template wait<0>();
+      f[1].mma(acc);
+      so = C::STAGE_BYTES - so;
+    }
+  } else {
+    wait_stages<C::PER_STAGE, S - 2>(nk - 1);
+    block_barrier();
+    f[0].fetch(a_rel, b_rel);
+    f[0].template wait<0>();
+    int stage = 0, fill = S - 1;
+    for (int t = 0; t < nk; ++t) {
+      const int next = stage + 1 == S ? 0 : stage + 1;
+      const uint32_t so = (uint32_t)stage * C::STAGE_BYTES, a = a_rel + so, b = b_rel + so;
+      f[1].fetch(a ^ STEP, b ^ STEP);
+      f[0].mma(acc);
+      f[1].template wait<0>();
+      f[0].fetch(a ^ (2 * STEP), b ^ (2 * STEP));
+      f[1].mma(acc);
+      f[0].template wait<0>();
+      if (t + 1 < nk) {
+        wait_stages<C::PER_STAGE, S - 3>(nk - 2 - t);   // this wave's share of stage t + 1 has landed
+        block_barrier();                                // everybody's has, and everybody is done reading stage t - 1
+        if (t + S - 1 < nk) issue(t + S - 1, fill);
+      }
+      f[1].fetch(a ^ (3 * STEP), b ^ (3 * STEP));
+      f[0].mma(acc);
+      f[1].template wait<0>();
+      // the first step of the next stage; behind the last stage it reads what is left in the ring and is not used
+      f[0].fetch(a_rel + (uint32_t)next * C::STAGE_BYTES, b_rel + (uint32_t)next * C::STAGE_BYTES);
+      f[1].mma(acc);
+      f[0].template wait<0>();
+      stage = next;
+      fill = fill + 1 == S ? 0 : fill + 1;
+    }
+  }
+}
+
+// fp32 results, stored from the accumulator layout: element e of a 32 x 32 tile sits at row
+// 8 (e / 4) + 4 (lane / 32) + e % 4, column lane % 32.  colsum[j] gathers what is stored of column j's tile.
+template <int EPI, typename C, int NB, int NM>
+__device__ __forceinline__ void store_f32(const f32x16_v (&acc)[C::WTM][C::WTN], int m_first, int n_first, int lane, int M,
+                                          int N, const float (&bias)[NB], const float (&mask)[NM][16],
+                                          const float *__restrict__ aux, float *__restrict__ out, int split,
+                                          float (&colsum)[C::WTN]) {
+  const int c = lane & 31, g = lane >> 5;
+  const bool whole = m_first + 32 * C::WTM <= M;   // all rows exist: no test per row
+#pragma unroll
+  for (int j = 0; j < C::WTN; ++j) {
+    const int n = n_first + j * 32 + c;
+    colsum[j] = 0.0f;
+    if (n >= N) continue;
+    // where this column goes: below `split` into out [M x split], the rest into aux [M x (N - split)]
+    float *dst = out + n;
+    int ld = N;
+    if constexpr (EPI == EPI_DX) {
+      dst = n < split ? out + n : const_cast<float *>(aux) + (n - split);
+      ld = n < split ? split : N - split;
+    }
+#pragma unroll
+    for (int i = 0; i < C::WTM; ++i)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int m = m_first + i * 32 + 8 * (e / 4) + 4 * g + (e % 4);
+        float v = acc[i][j][e];
+        if constexpr (EPI == EPI_BIAS_RELU) {
+          v += bias[j];
+          v = v > 0.0f ? v : 0.0f;
+        }
+        if constexpr (EPI == EPI_MASK) v = mask[i * C::WTN + j][e] > 0.0f ? v : 0.0f;
+        if (whole || m < M) {
+          dst[(size_t)m * ld] = v;
+          if constexpr (EPI == EPI_MASK) colsum[j] += v;
+        }
+      }
+  }
+}
+
+template <int EPI, typename C>
+__global__ void __launch_bounds__(C::THREADS)
+k_gemm_nt_tile(const typename C::T *__restrict__ A, const typename C::T *__restrict__ B, int M, int N, int K,
+               const float *__restrict__ bias, const typename C::T *__restrict__ aux, void *__restrict__ out, int split,
+               float *__restrict__ colpart, uint8_t *__restrict__ relu_bits, const int32_t *__restrict__ status) {
+  using T = typename C::T;
+  if (status && *status != 0) return;
+  constexpr bool kBf16 = sizeof(T) == 2;
+  constexpr int kPatchBytes = kBf16 ? C::WAVES * 32 * PATCH_LD * 2 : 0;
+  constexpr int kSumFloats = C::WAVES * 32 * C::WTN;
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[C::STAGES * C::STAGE_BYTES];   // [stage][A rows | B rows]
+  static_assert(kPatchBytes + kSumFloats * 4 <= C::STAGES * C::STAGE_BYTES, "patches and column sums fit");
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / C::WAVES_N, wn = wave % C::WAVES_N;
+  const int n_tiles = (N + C::BN - 1) / C::BN;
+  const int tile = xcd_remap(blockIdx.x, gridDim.x);
+  const int m0 = (tile / n_tiles) * C::BM, n0 = (tile % n_tiles) * C::BN;
+
+  // this lane's piece of the rows it copies: LDS slot lane % 8 of row lane / 8 receives piece (lane % 8) ^ (row % 8)
+  const int piece = (lane & 7) ^ (lane >> 3);
+  const unsigned char *src[C::PER_STAGE];
+#pragma unroll
+  for (int i = 0; i < C::DMA_A; ++i)
+    src[i] = reinterpret_cast<const unsigned char *>(A + (size_t)min(m0 + (i * C::WAVES + wave) * 8 + (lane >> 3), M - 1) * K) + piece * 16;
+#pragma unroll
+  for (int i = 0; i < C::DMA_B; ++i)
+    src[C::DMA_A + i] =
+        reinterpret_cast<const unsigned char *>(B + (size_t)min(n0 + (i * C::WAVES + wave) * 8 + (lane >> 3), N - 1) * K) + piece * 16;
+  // What the epilogue needs from global memory is requested first and arrives while the products run.
+  const int r = lane & 31, g = lane >> 5;
+  const int wave_m0 = m0 + wm * C::WTM * 32, wave_n0 = n0 + wn * C::WTN * 32;
+  float bias_reg[kBf16 ? 1 : C::WTN];
+  if constexpr (EPI == EPI_BIAS_RELU) {
+    if constexpr (kBf16) {
+      static_assert(C::BN <= C::THREADS, "a thread fetches one bias");
+      bias_reg[0] = tid < C::BN && n0 + tid < N ? bias[n0 + tid] : 0.0f;
+    } else {
+#pragma unroll
+      for (int j = 0; j < C::WTN; ++j) bias_reg[j] = wave_n0 + j * 32 + r < N ? bias[wave_n0 + j * 32 + r] : 0.0f;
+    }
+  }
+  uint32_t hbits[C::WTM][4];
+#pragma unroll
+  for (int i = 0; i < C::WTM; ++i)
+#pragma unroll
+    for (int it = 0; it < 4; ++it) hbits[i][it] = 0u;
+  if constexpr (EPI == EPI_MASK_BITS) {
+    const uint8_t *bits = reinterpret_cast<const uint8_t *>(aux);
+    const int n_vec = n0 + wn * WN + (lane & 7) * 8;
+#pragma unroll
+    for (int i = 0; i < C::WTM; ++i)
+#pragma unroll
+      for (int it = 0; it < 4; ++it) {
+        const int m = wave_m0 + i * 32 + it * 8 + (lane >> 3);
+        if (m < M && n_vec < N) hbits[i][it] = bits[(size_t)m * (N >> 3) + (n_vec >> 3)];
+      }
+  }
+  float mask[EPI == EPI_MASK && !kBf16 ? C::WTM * C::WTN : 1][16];
+  if constexpr (EPI == EPI_MASK && !kBf16) {
+#pragma unroll
+    for (int i = 0; i < C::WTM; ++i)
+#pragma unroll
+      for (int j = 0; j < C::WTN; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const int m = wave_m0 + i * 32 + 8 * (e / 4) + 4 * g + (e % 4), n = wave_n0 + j * 32 + r;
+          mask[i * C::WTN + j][e] = aux[(size_t)min(m, M - 1) * N + min(n, N - 1)];
+        }
+  }
+
+  const int nk = (K + C::KS - 1) / C::KS;
+  const uint64_t zero = zero_address();
+  auto issue = [&](int t, int stage) {
+    unsigned char *a = lds + stage * C::STAGE_BYTES + wave * 1024, *b = a + C::BM * 128;
+    if ((t + 1) * C::KS <= K) {
+#pragma unroll
+      for (int i = 0; i < C::PER_STAGE; ++i)
+        copy_piece(src[i] + (size_t)t * 128, i < C::DMA_A ? a + i * C::WAVES * 1024 : b + (i - C::DMA_A) * C::WAVES * 1024);
+    } else {
+      const bool in = t * C::KS + piece * C::VEC < K;   // K is a multiple of a piece
+#pragma unroll
+      for (int i = 0; i < C::PER_STAGE; ++i)
+        copy_piece_or_zero(src[i] + (size_t)t * 128, in, zero,
+                           i < C::DMA_A ? a + i * C::WAVES * 1024 : b + (i - C::DMA_A) * C::WAVES * 1024);
+    }
+  };
+#pragma unroll
+  for (int p = 0; p < C::STAGES - 1; ++p)
+    if (p < nk) issue(p, p);
+
+  f32x16_v acc[C::WTM][C::WTN];
+#pragma unroll
+  for (int i = 0; i < C::WTM; ++i)
+#pragma unroll
+    for (int j = 0; j < C::WTN; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+
+  const uint32_t lds_base = (uint32_t)(uintptr_t)(lds_ptr_t)lds;
+  const uint32_t in_row = (uint32_t)(((kBf16 ? g : 4 * g) ^ (r & 7)) << 4);
+  const uint32_t a_rel = lds_base + (uint32_t)(wm * C::WTM * 32 + r) * 128u + in_row;
+  const uint32_t b_rel = lds_base + (uint32_t)(C::BM + wn * C::WTN * 32 + r) * 128u + in_row;
+  nt_main_loop<C>(acc, a_rel, b_rel, nk, issue);
+
+  if constexpr (kBf16) {
+    static_assert(C::WTN == TN, "the patch epilogue takes wave tiles of 64 columns");
+    __shared__ float s_bias[EPI == EPI_BIAS_RELU ? C::BN : 1];
+    if constexpr (EPI == EPI_BIAS_RELU) {
+      if (tid < C::BN) s_bias[tid] = bias_reg[0];
+    }
+    __syncthreads();   // every wave is done with the operand tiles: they become the output patches
+    float colacc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    epilogue_patch<EPI, C::WTM>(acc, reinterpret_cast<bf16_t *>(lds) + wave * 32 * PATCH_LD, m0, n0, wm, wn, lane, M, N, bias,
+                                aux, out, split, relu_bits, colacc, s_bias, hbits);
+    if constexpr (EPI == EPI_MASK || EPI == EPI_MASK_BITS) {
+      if (colpart) {   // column sums of what was stored, per row tile: lanes, then the waves that share the columns
+        float *s_col = reinterpret_cast<float *>(lds + kPatchBytes);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          float v = colacc[e];
+          v += __shfl_xor(v, 8, kWave);
+          v += __shfl_xor(v, 16, kWave);
+          v += __shfl_xor(v, 32, kWave);
+          if (lane < 8) s_col[wave * WN + lane * 8 + e] = v;
+        }
+        __syncthreads();
+        if (wm == 0 && n0 + wn * WN + lane < N) {
+          float v = s_col[wn * WN + lane];
+#pragma unroll
+          for (int w = 1; w < C::WAVES_M; ++w) v += s_col[(w * C::WAVES_N + wn) * WN + lane];
+          colpart[(size_t)(m0 / C::BM) * N + n0 + wn * WN + lane] = v;
+        }
+      }
+    }
+  } else {
+    // one wait for what was requested ahead, not one before every store
+    if constexpr (EPI == EPI_BIAS_RELU) {
+#pragma unroll
+      for (int j = 0; j < C::WTN; ++j) landed(bias_reg[j]);
+    }
+    if constexpr (EPI == EPI_MASK) {
+#pragma unroll
+      for (int i = 0; i < C::WTM * C::WTN; ++i)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) landed(mask[i][e]);
+    }
+    float colsum[C::WTN];
+    store_f32<EPI, C>(acc, wave_m0, wave_n0, lane, M, N, bias_reg, mask, reinterpret_cast<const float *>(aux), static_cast<float *>(out), split, colsum);
+    if constexpr (EPI == EPI_MASK) {
+      if (colpart) {
+        float *s_col = reinterpret_cast<float *>(lds);
+        __syncthreads();   // the operand tiles are not needed any more
+#pragma unroll
+        for (int j = 0; j < C::WTN; ++j) {
+          const float v = colsum[j] + __shfl_xor(colsum[j], 32, kWave);
+          if (lane < 32) s_col[(wave * C::WTN + j) * 32 + lane] = v;
+        }
+        __syncthreads();
+        for (int k = tid; k < C::BN; k += C::THREADS) {
+          const int w0 = k / (32 * C::WTN), at = k % (32 * C::WTN);
+          float v = s_col[w0 * C::WTN * 32 + at];
+#pragma unroll
+          for (int w = 1; w < C::WAVES_M; ++w) v += s_col[(w * C::WAVES_N + w0) * C::WTN * 32 + at];
+          if (n0 + k < N) colpart[(size_t)(m0 / C::BM) * N + n0 + k] = v;
+        }
+      }
+    }
+  }
+}
+
+// ---- TN: partial[z] = A[rows z]^T B[rows z], a stage is 32 rows of the batch --------------------------------
+template <typename T_, int WTM_, int WTN_, int STAGES_> struct TnTile {
+  using T = T_;
+  static constexpr int WTM = WTM_, WTN = WTN_, STAGES = STAGES_, WAVES = 4, THREADS = 256;   // 2 x 2 waves
+  static constexpr int BM = 64 * WTM, BN = 64 * WTN, KD = 32, ROUND = sizeof(T) == 2 ? 32 : 16;   // rows of a stage; a range is a multiple of ROUND
+  static constexpr int ROW = BM * (int)sizeof(T);                 // bytes of a k-row of either operand
+  static constexpr int PIECES = ROW / 16, ROWS_PER_DMA = 64 / PIECES;
+  static constexpr int OPERAND_BYTES = KD * ROW, STAGE_BYTES = 2 * OPERAND_BYTES;
+  static constexpr int DMA = KD / ROWS_PER_DMA / WAVES;           // instructions of a wave per operand and stage
+  static_assert(BM == BN && PIECES == 16, "256-byte k-rows: a DMA instruction copies four of them");
+};
+
+// fp32: the k-row order in LDS is what v_mfma_f32_32x32x2_f32 wants (half a wave reads 32 neighbouring values).
+// bf16: ds_read_b64_tr_b16 assembles eight k-values of a row per lane (sixteen lanes hand in a 4(k) x 16 block);
+// pieces are XOR-ed by 4 (k % 4), so that the four k-rows a read touches lie in different quarters of the banks.
+template <typename C>
+__device__ __forceinline__ void mma_stage_rows(f32x16_v (&acc)[C::WTM][C::WTN], const uint32_t (&a_addr)[C::WTM],
+                                               const uint32_t (&b_addr)[C::WTN], uint32_t so) {
+  if constexpr (sizeof(typename C::T) == 4) {
+    static_assert(C::WTM == 1 && C::WTN == 1, "one tile per wave in fp32");
+    constexpr int STEPS = C::KD / 2;
+    float a[STEPS], b[STEPS];
+    const uint32_t aa = a_addr[0] + so, bb = b_addr[0] + so;
+#define GEAR_ROW(K)                                   \
+  lds_read4<(K) * 2 * C::ROW>(a[K], aa);              \
+  lds_read4<(K) * 2 * C::ROW>(b[K], bb);
+    GEAR_ROW(0) GEAR_ROW(1) GEAR_ROW(2) GEAR_ROW(3) GEAR_ROW(4) GEAR_ROW(5) GEAR_ROW(6) GEAR_ROW(7)
+    wait_lgkm<8>();
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      landed(a[k]);
+      landed(b[k]);
+      acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[k], b[k], acc[0][0], 0, 0, 0);
+    }
+    GEAR_ROW(8) GEAR_ROW(9) GEAR_ROW(10) GEAR_ROW(11)
+    wait_lgkm<8>();
+#pragma unroll
+    for (int k = 4; k < 8; ++k) {
+      landed(a[k]);
+      landed(b[k]);
+      acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[k], b[k], acc[0][0], 0, 0, 0);
+    }
+    GEAR_ROW(12) GEAR_ROW(13) GEAR_ROW(14) GEAR_ROW(15)
+#undef GEAR_ROW
+    wait_lgkm<8>();
+#pragma unroll
+    for (int k = 8; k < 12; ++k) {
+      landed(a[k]);
+      landed(b[k]);
+      acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[k], b[k], acc[0][0], 0, 0, 0);
+    }
+    wait_lgkm<0>();
+#pragma unroll
+    for (int k = 12; k < 16; ++k) {
+      landed(a[k]);
+      landed(b[k]);
+      acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[k], b[k], acc[0][0], 0, 0, 0);
+    }
+  } else {
+    static_assert(C::WTM == 2 && C::WTN == 2, "2 x 2 tiles per wave in bf16");
+    u32x2_v a[2][2][2], b[2][2][2];   // [k-step][tile][k-rows +0..3 | +4..7 of the lane's eight]
+#define GEAR_TR(KK)                                                      \
+  lds_read_tr<(KK) * 16 * C::ROW>(a[KK][0][0], a_addr[0] + so);          \
+  lds_read_tr<(KK) * 16 * C::ROW + 4 * C::ROW>(a[KK][0][1], a_addr[0] + so); \
+  lds_read_tr<(KK) * 16 * C::ROW>(a[KK][1][0], a_addr[1] + so);          \
+  lds_read_tr<(KK) * 16 * C::ROW + 4 * C::ROW>(a[KK][1][1], a_addr[1] + so); \
+  lds_read_tr<(KK) * 16 * C::ROW>(b[KK][0][0], b_addr[0] + so);          \
+  lds_read_tr<(KK) * 16 * C::ROW + 4 * C::ROW>(b[KK][0][1], b_addr[0] + so); \
+  lds_read_tr<(KK) * 16 * C::ROW>(b[KK][1][0], b_addr[1] + so);          \
+  lds_read_tr<(KK) * 16 * C::ROW + 4 * C::ROW>(b[KK][1][1], b_addr[1] + so);
+    GEAR_TR(0)
+    GEAR_TR(1)
+#undef GEAR_TR
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+      if (kk == 0)
+        wait_lgkm<8>();
+      else
+        wait_lgkm<0>();
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          landed(a[kk][i][h]);
+          landed(b[kk][i][h]);
+        }
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const u32x4_v av = {a[kk][i][0].x, a[kk][i][0].y, a[kk][i][1].x, a[kk][i][1].y};
+          const u32x4_v bv = {b[kk][j][0].x, b[kk][j][0].y, b[kk][j][1].x, b[kk][j][1].y};
+          MFMA_BF16(acc[i][j], av, bv);
+        }
+    }
+  }
+}
+
+struct TnTileArgs {
+  int count, tiles;
+  TnProblem p[GEAR_MAX_LAYERS];
+  int first_tile[GEAR_MAX_LAYERS];
+};
+
+// The grid is k-ranges x (all tiles of all problems).  k_dev (may be NULL): the real inner length, at most K, only
+// known on the device; the ranges are then cut there, and one beyond the end leaves zeros.
+template <typename C>
+__global__ void __launch_bounds__(C::THREADS)
+k_gemm_tn_tile(TnTileArgs args, int K, int splits, const int32_t *__restrict__ status, const int32_t *__restrict__ k_dev) {
+  using T = typename C::T;
+  if (status && *status != 0) return;
+  if (k_dev) K = min(max(*k_dev, 0), K);
+  const int k_chunk = max(((K + splits - 1) / splits + C::ROUND - 1) / C::ROUND * C::ROUND, C::ROUND);
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[C::STAGES * C::STAGE_BYTES];
+  const int work = xcd_remap(blockIdx.x, gridDim.x);
+  const int z = work / args.tiles, tile_all = work % args.tiles;
+  int which = 0;
+  for (int i = 1; i < args.count; ++i)
+    if (tile_all >= args.first_tile[i]) which = i;
+  const TnProblem &q = args.p[which];
+  const int M = q.M, N = q.N, tile = tile_all - args.first_tile[which];
+  const int n_tiles = (N + C::BN - 1) / C::BN;
+  const int m0 = (tile / n_tiles) * C::BM, n0 = (tile % n_tiles) * C::BN;
+  const int k_begin = z * k_chunk, k_end = min(K, k_begin + k_chunk);
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  constexpr int VEC = 16 / (int)sizeof(T);
+  // a DMA instruction copies four k-rows; LDS slot lane % 16 of k-row lane / 16 receives this piece of the row
+  const int krow = lane >> 4;
+  const int piece = sizeof(T) == 2 ? (lane & 15) ^ (4 * krow) : (lane & 15);
+  const T *a_src = static_cast<const T *>(q.A) + min(m0 + piece * VEC, M - VEC);
+  const T *b_src = static_cast<const T *>(q.B) + min(n0 + piece * VEC, N - VEC);
+  const int nk = k_end > k_begin ? (k_end - k_begin + C::KD - 1) / C::KD : 0;
+  const uint64_t zero = zero_address();
+  auto issue = [&](int t, int stage) {
+    unsigned char *a = lds + stage * C::STAGE_BYTES + wave * 1024, *b = a + C::OPERAND_BYTES;
+    const bool full = k_begin + (t + 1) * C::KD <= k_end;
+#pragma unroll
+    for (int i = 0; i < C::DMA; ++i) {
+      const int k = k_begin + t * C::KD + (i * C::WAVES + wave) * C::ROWS_PER_DMA + krow;
+      if (full) {
+        copy_piece(a_src + (size_t)k * M, a + i * C::WAVES * 1024);
+        copy_piece(b_src + (size_t)k * N, b + i * C::WAVES * 1024);
+      } else {
+        copy_piece_or_zero(a_src + (size_t)k * M, k < k_end, zero, a + i * C::WAVES * 1024);
+        copy_piece_or_zero(b_src + (size_t)k * N, k < k_end, zero, b + i * C::WAVES * 1024);
+      }
+    }
+  };
+#pragma unroll
+  for (int p = 0; p < C::STAGES - 1; ++p)
+    if (p < nk) issue(p, p);
+
+  f32x16_v acc[C::WTM][C::WTN];
+#pragma unroll
+  for (int i = 0; i < C::WTM; ++i)
+#pragma unroll
+    for (int j = 0; j < C::WTN; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+
+  const uint32_t lds_base = (uint32_t)(uintptr_t)(lds_ptr_t)lds;
+  uint32_t a_addr[C::WTM], b_addr[C::WTN];
+  if constexpr (sizeof(T) == 4) {
+    const uint32_t at = (uint32_t)(lane >> 5) * C::ROW + (uint32_t)(lane & 31) * 4u;
+    a_addr[0] = lds_base + at + (uint32_t)wm * 128u;
+    b_addr[0] = lds_base + C::OPERAND_BYTES + at + (uint32_t)wn * 128u;
+  } else {
+    const int j = lane & 15, half = (lane >> 4) & 1, g = lane >> 5;
+    const uint32_t at = (uint32_t)(8 * g + (j >> 2)) * C::ROW + 32u * half + 8u * (j & 3);
+#pragma unroll
+    for (int i = 0; i < C::WTM; ++i) a_addr[i] = lds_base + at + (uint32_t)(((wm * C::WTM + i) ^ (j >> 2)) << 6);
+#pragma unroll
+    for (int i = 0; i < C::WTN; ++i)
+      b_addr[i] = lds_base + C::OPERAND_BYTES + at + (uint32_t)(((wn * C::WTN + i) ^ (j >> 2)) << 6);
+  }
+  int stage = 0, fill = C::STAGES - 1;
+  for (int t = 0; t < nk; ++t) {
+    wait_stages<2 * C::DMA, C::STAGES - 2>(nk - 1 - t);
+    block_barrier();
+    if (t + C::STAGES - 1 < nk) issue(t + C::STAGES - 1, fill);
+    mma_stage_rows<C>(acc, a_addr, b_addr, (uint32_t)stage * C::STAGE_BYTES);
+    stage = stage + 1 == C::STAGES ? 0 : stage + 1;
+    fill = fill + 1 == C::STAGES ? 0 : fill + 1;
+  }
+  float *dst = q.partial + (size_t)z * M * N;
+  const int c = lane & 31, g = lane >> 5;
+#pragma unroll
+  for (int i = 0; i < C::WTM; ++i)
+#pragma unroll
+    for (int j = 0; j < C::WTN; ++j) {
+      const int n = n0 + (wn * C::WTN + j) * 32 + c;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int m = m0 + (wm * C::WTM + i) * 32 + 8 * (e / 4) + 4 * g + (e % 4);
+        if (m < M && n < N) dst[(size_t)m * N + n] = acc[i][j][e];
+      }
+    }
+}
+
+// ---- tile shapes -----------------------------------------------------------------------------------------
+using F32Small = NtTile<float, 1, 1, 2, 2, 4>;      //  64 x  64, 64 KB
+using F32Big = NtTile<float, 2, 2, 2, 2, 3>;        // 128 x 128, 96 KB
+using Bf16Small = NtTile<bf16_t, 1, 2, 2, 1, 3>;    //  64 x  64, two waves, 48 KB
+using Bf16Tall = NtTile<bf16_t, 1, 2, 4, 1, 2>;     // 128 x  64, 48 KB
+using Bf16Mid = NtTile<bf16_t, 2, 2, 2, 2, 2>;      // 128 x 128, 64 KB
+using TnF32 = TnTile<float, 1, 1, 4>;               //  64 x  64, 64 KB
+using TnBf16 = TnTile<bf16_t, 2, 2, 4>;             // 128 x 128, 64 KB
+
+long long tiles_of(int M, int N, int bm, int bn) { return (long long)((M + bm - 1) / bm) * ((N + bn - 1) / bn); }
+
+template <int EPI, typename C>
+hipError_t run_nt(const void *A, const void *B, int M, int N, int K, const float *bias, const void *aux, void *out, int split,
+                  float *colpart, uint8_t *relu_bits, const int32_t *status, hipStream_t s) {
+  using T = typename C::T;
+  hipLaunchKernelGGL((k_gemm_nt_tile<EPI, C>), dim3((unsigned)tiles_of(M, N, C::BM, C::BN)), dim3(C::THREADS), 0, s,
+                     (const T *)A, (const T *)B, M, N, K, bias, (const T *)aux, out, split, colpart, relu_bits, status);
+  return hipGetLastError();
+}
+
+template <typename C>
+hipError_t run_nt_any(const void *A, const void *B, int M, int N, int K, int epi, const float *bias, const void *aux, void *out,
+                      int split, float *colpart, uint8_t *relu_bits, const int32_t *status, hipStream_t s) {
+#define GEAR_NT(E) run_nt<E, C>(A, B, M, N, K, bias, aux, out, split, colpart, relu_bits, status, s)
+  switch (epi) {
+    case EPI_BIAS_RELU: return GEAR_NT(EPI_BIAS_RELU);
+    case EPI_MASK: return GEAR_NT(EPI_MASK);
+    case EPI_DX: return GEAR_NT(EPI_DX);
+    case EPI_F32: return GEAR_NT(EPI_F32);
+    case EPI_MASK_BITS:
+      if constexpr (sizeof(typename C::T) == 2) return GEAR_NT(EPI_MASK_BITS);
+  }
+#undef GEAR_NT
+  return hipErrorInvalidValue;
+}
+
+// The shape a product of M x N takes.
+enum NtShape { kSmall, kTall, kWide };   // 64 x 64, 128 x 64 (bf16 only), 128 x 128
+int rows_of(NtShape shape) { return shape == kSmall ? 64 : 128; }
+
+// bf16: two 128 x 128 tiles or three of 128 x 64 fit on a CU.  A 128 x 128 tile moves a quarter fewer bytes for its
+// products (16384 x 512 x 576: 14.2 us against 17.0), as long as whole rounds of them fill the chip; where the last
+// round is mostly empty the half-sized tiles end sooner (16384 x 576 x 512, 640 tiles: 18.8 against 17.6; 10001 x 512
+// x 576, 316 tiles: 13.2 against 12.7).  Below one 128 x 64 tile per CU, 64 x 64 reaches more CUs.
+// fp32: 128 x 128 from one tile per CU on (16384 x 256 x 320: 30.1 us against 31.4), else 64 x 64.
+NtShape nt_shape(int dtype, int M, int N) {
+  const long long big = tiles_of(M, N, 128, 128);
+  if (dtype != GEAR_BF16) return big >= 256 ? kWide : kSmall;
+  const long long tall = tiles_of(M, N, 128, 64);
+  if (tall < 256) return kSmall;
+  return 2 * ((big + 511) / 512) <= (tall + 767) / 768 ? kWide : kTall;
+}
+
+template <typename C>
+hipError_t run_tn(const TnProblem *p, int count, int K, int splits, const int32_t *status, hipStream_t s, const int32_t *k_dev) {
+  TnTileArgs args;
+  args.count = count;
+  args.tiles = 0;
+  for (int i = 0; i < GEAR_MAX_LAYERS; ++i) {
+    args.p[i] = i < count ? p[i] : TnProblem{nullptr, nullptr, nullptr, 0, 0};
+    args.first_tile[i] = args.tiles;
+    if (i < count) args.tiles += (int)tiles_of(p[i].M, p[i].N, C::BM, C::BN);
+  }
+  hipLaunchKernelGGL((k_gemm_tn_tile<C>), dim3((unsigned)(args.tiles * splits)), dim3(C::THREADS), 0, s, args, K, splits, status, k_dev);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+int nt_tile_colsum_parts(int dtype, int M, int N) {
+  const int rows = rows_of(nt_shape(dtype, M, N));
+  return (M + rows - 1) / rows;
+}
+
+hipError_t launch_gemm_nt_tile(int dtype, const void *A, const void *B, int M, int N, int K, int epi, const float *bias,
+                               const void *aux, void *out, int split, float *colpart, uint8_t *relu_bits,
+                               const int32_t *status, hipStream_t s) {
+  const NtShape shape = nt_shape(dtype, M, N);
+#define GEAR_NT(C) run_nt_any<C>(A, B, M, N, K, epi, bias, aux, out, split, colpart, relu_bits, status, s)
+  if (dtype == GEAR_BF16) return shape == kWide ? GEAR_NT(Bf16Mid) : shape == kTall ? GEAR_NT(Bf16Tall) : GEAR_NT(Bf16Small);
+  return shape == kWide ? GEAR_NT(F32Big) : GEAR_NT(F32Small);
+#undef GEAR_NT
+}
+
+// Ranges of the inner length: two workgroups for every CU, as long as each keeps at least 64 rows.
+int tn_tile_splits(int dtype, const TnProblem *p, int count, int K) {
+  long long tiles = 0;
+  const int edge = dtype == GEAR_BF16 ? TnBf16::BM : TnF32::BM;
+  for (int i = 0; i < count; ++i) tiles += tiles_of(p[i].M, p[i].N, edge, edge);
+  long long s = tiles > 0 ? 512 / tiles : 1;
+  if (s > K / 64) s = K / 64;
+  if (s > 64) s = 64;
+  return s < 1 ? 1 : (int)s;
+}
+
+hipError_t launch_gemm_tn_tile(int dtype, const TnProblem *p, int count, int K, int splits, const int32_t *status, hipStream_t s,
+                               const int32_t *k_dev) {
+  return dtype == GEAR_BF16 ? run_tn<TnBf16>(p, count, K, splits, status, s, k_dev)
+                            : run_tn<TnF32>(p, count, K, splits, status, s, k_dev);
+}
+
+}  // namespace gear

@@ -242,42 +242,6 @@ __device__ __forceinline__ void loss_final(const float *__restrict__ loss_partia
   if (threadIdx.x == 0) *loss = v / (float)B;
 }
 
-// partial[chunk][j] = sum over the chunk's rows of src[row][j].  A thread owns one 16-byte piece of
-// the row and every RS-th row of the chunk; the RS row-lanes are then added in order.
-template <typename T>
-__global__ void __launch_bounds__(256)
-k_colsum_partial(const T *__restrict__ src, int B, int H, int rows_per_chunk, float *__restrict__ partial,
-                 const int32_t *__restrict__ status) {
-  if (*status != 0) return;
-  constexpr int VEC = Vec16<T>::N;
-  extern __shared__ float s_part[];  // [RS][cols of this block]
-  const int n_vec = H / VEC;
-  const int vec_here = min(n_vec - (int)blockIdx.x * 256, 256);  // column pieces handled by this block
-  const int RS = 256 / vec_here;                                  // row lanes
-  const int cv = threadIdx.x % vec_here, rl = threadIdx.x / vec_here;
-  const int col = (blockIdx.x * 256 + cv) * VEC;
-  const int r0 = blockIdx.y * rows_per_chunk, r1 = min(B, r0 + rows_per_chunk);
-  float acc[VEC];
-#pragma unroll
-  for (int e = 0; e < VEC; ++e) acc[e] = 0.0f;
-  if (rl < RS) {
-    for (int r = r0 + rl; r < r1; r += RS) {
-      Vec16<T> v;
-      v.v = *reinterpret_cast<const decltype(v.v) *>(src + (size_t)r * H + col);
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) acc[e] += v.get(e);
-    }
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) s_part[(rl * vec_here + cv) * VEC + e] = acc[e];
-  }
-  __syncthreads();
-  for (int j = threadIdx.x; j < vec_here * VEC; j += blockDim.x) {
-    float t = 0.0f;
-    for (int k = 0; k < RS; ++k) t += s_part[k * vec_here * VEC + j];
-    partial[(size_t)blockIdx.y * H + blockIdx.x * 256 * VEC + j] = t;
-  }
-}
-
 // dst[j] -= lr * sum_p partial[p][j].  Eight columns per workgroup and 32 row lanes, each adding
 // every 32nd partial in order (eight loads in flight); then the 32 lanes are added in order.
 __device__ __forceinline__ void partial_sgd(const float *__restrict__ partial, int P, int H, float *__restrict__ dst,
@@ -419,25 +383,6 @@ hipError_t launch_partial_sgd(const float *partial, int P, int H, float *dst, co
                               const int32_t *status, hipStream_t s) {
   if (P <= 0 || H <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_partial_sgd, dim3((H + 7) / 8), dim3(256), 0, s, partial, P, H, dst, opt, mom, status);
-  return hipGetLastError();
-}
-
-// dst[j] -= lr * sum_b src[b][j]   (bias gradient of a hidden layer)
-hipError_t launch_colsum_sgd(int dtype, const void *src, int B, int H, float *partial, float *dst, const Optim &opt,
-                             const Moments &mom, const int32_t *status, hipStream_t s) {
-  if (B <= 0 || H <= 0) return hipSuccess;
-  const int chunks = (B + kColsumRows - 1) / kColsumRows;
-  const int vec = dtype == GEAR_BF16 ? 8 : 4;
-  const int n_vec = H / vec;
-  const dim3 grid((n_vec + 255) / 256, chunks);
-  const size_t smem = 256 * (size_t)vec * sizeof(float);
-  if (dtype == GEAR_BF16)
-    hipLaunchKernelGGL(k_colsum_partial<bf16_t>, grid, dim3(256), smem, s, (const bf16_t *)src, B, H, kColsumRows,
-                       partial, status);
-  else
-    hipLaunchKernelGGL(k_colsum_partial<float>, grid, dim3(256), smem, s, (const float *)src, B, H, kColsumRows,
-                       partial, status);
-  hipLaunchKernelGGL(k_partial_sgd, dim3((H + 7) / 8), dim3(256), 0, s, partial, chunks, H, dst, opt, mom, status);
   return hipGetLastError();
 }
 

@@ -1,0 +1,43 @@
+"""Matrix products at the sizes where a tile shape changes or a tile is cut (gemm_tile.hip), against fp64 products of
+the same operands.  Accumulation is fp32 over at most 1100 terms: 1e-5 of the row's largest element."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def operands(dtype, M, N, K):
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    gen = torch.Generator(device="cuda").manual_seed(M * 31 + N * 7 + K)
+    draw = lambda *s: torch.randn(s, generator=gen, device="cuda").to(td)
+    return draw(M, K), draw(N, K), draw(M, N), torch.randn(N, generator=gen, device="cuda")
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("M,N,K", [
+    (1, 8, 8), (63, 72, 24), (65, 64, 64), (64, 56, 72), (129, 200, 136),    # 64 x 64: one piece, one stage, one over
+    (16385, 128, 40), (16384, 64, 128),                                       # bf16 from 256 tiles of 128 x 64 on
+    (32760, 256, 72), (16390, 256, 32), (65537, 128, 200),                    # 128 x 128, cut in M and in K
+])
+def test_products_at_the_edges_of_tiles(dtype, M, N, K):
+    import paper_1806_03925_amd as g
+    A, B, aux, bias = operands(dtype, M, N, K)
+    ref = A.double() @ B.double().T
+    scale = ref.abs().amax(dim=1, keepdim=True).clamp_min(1e-30)
+    tol = 2.0 ** -8 if dtype == "bf16" else 1e-5            # one rounding of the result to the operand type
+    assert ((g.gear_gemm(A, B, 0, 2).double() - ref).abs() <= 1e-5 * scale).all()
+    want = torch.relu(ref + bias.double())
+    assert ((g.gear_gemm(A, B, 0, 0, bias=bias).double() - want).abs() <= tol * want.abs() + 1e-5 * scale).all()
+    want = torch.where(aux.double() > 0, ref, torch.zeros_like(ref))
+    assert ((g.gear_gemm(A, B, 0, 1, aux=aux).double() - want).abs() <= tol * want.abs() + 1e-5 * scale).all()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("M,N,K,splits", [(8, 8, 1, 1), (72, 136, 31, 3), (64, 128, 33, 64), (320, 72, 1000, 7), (512, 576, 1099, 5)])
+def test_weight_gradients_over_any_number_of_rows(dtype, M, N, K, splits):
+    """K rows of a batch in `splits` ranges, the last cut or empty."""
+    import paper_1806_03925_amd as g
+    A, B, _, _ = operands(dtype, M, N, K)
+    ref = A.double() @ B.double().T
+    out = g.gear_gemm(A.T.contiguous(), B.T.contiguous(), 1, splits=splits)
+    assert ((out.double() - ref).abs() <= 1e-5 * ref.abs().max()).all()
