@@ -73,8 +73,8 @@ template <int PER, int MAX> __device__ __forceinline__ void wait_stages(int stag
 
 // Operands of one k-step (a quarter of a stage) in registers.  LDS rows are 128 bytes with their eight 16-byte pieces
 // XOR-ed by the row's number modulo 8, so that the 32 rows a read touches spread over all banks; a k-step is two
-// pieces of a row, one for either half-wave: neighbours in bf16 (one product takes all sixteen values), in fp32 one
-// from either half of the row.
+// neighbouring pieces of a row, one for either half-wave.  One bf16 product takes all sixteen values as they are; an
+// fp32 product takes two neighbouring k-values, one from either half-wave, so the halves trade values first.
 template <typename C> struct Frag {
   u32x4_v a[C::WTM], b[C::WTN];
   __device__ __forceinline__ void fetch(uint32_t a_addr, uint32_t b_addr) {
@@ -91,11 +91,18 @@ template <typename C> struct Frag {
 #pragma unroll
     for (int j = 0; j < C::WTN; ++j) landed(b[j]);
   }
+  // fp32: the half-waves hold k 0..3 and 4..7 of the step; afterwards registers 0, 2, 1, 3 hold (0, 1), (2, 3), (4, 5),
+  // (6, 7).  Two v_permlane32_swap per operand and step; products then add k in ascending pairs, in every tile shape,
+  // so that a hidden unit next to zero takes the same branch whichever shape its layer's product has.
+  static __device__ __forceinline__ void trade(u32x4_v &v) {
+    const auto lo = __builtin_amdgcn_permlane32_swap(v[0], v[1], false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(v[2], v[3], false, false);
+    v[0] = lo[0], v[1] = lo[1], v[2] = hi[0], v[3] = hi[1];
+  }
   // bf16 is taken transposed (a lane holds four consecutive columns of a row, see epilogue_patch); fp32 is not (a lane
-  // holds one column, half a wave stores 128 contiguous bytes).  An fp32 product takes two k-values,
-  // k and k + 16 of the stage's 32, k ascending: a fixed order, the same in every shape.
+  // holds one column, half a wave stores 128 contiguous bytes).
   // The scheduler may not move products across: it would otherwise put the next wait between them.
-  __device__ __forceinline__ void mma(f32x16_v (&acc)[C::WTM][C::WTN]) const {
+  __device__ __forceinline__ void mma(f32x16_v (&acc)[C::WTM][C::WTN]) {
     __builtin_amdgcn_sched_barrier(0);
     if constexpr (sizeof(typename C::T) == 2) {
 #pragma unroll
@@ -104,13 +111,18 @@ template <typename C> struct Frag {
         for (int j = 0; j < C::WTN; ++j) MFMA_BF16_T(acc[i][j], a[i], b[j]);
     } else {
 #pragma unroll
+      for (int i = 0; i < C::WTM; ++i) trade(a[i]);
+#pragma unroll
+      for (int j = 0; j < C::WTN; ++j) trade(b[j]);
+      constexpr int kAscending[4] = {0, 2, 1, 3};
+#pragma unroll
       for (int e = 0; e < 4; ++e)
 #pragma unroll
         for (int i = 0; i < C::WTM; ++i)
 #pragma unroll
           for (int j = 0; j < C::WTN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[i][e]), __uint_as_float(b[j][e]),
-                                                             acc[i][j], 0, 0, 0);
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[i][kAscending[e]]),
+                                                             __uint_as_float(b[j][kAscending[e]]), acc[i][j], 0, 0, 0);
     }
     __builtin_amdgcn_sched_barrier(0);
   }
@@ -128,7 +140,7 @@ template <typename C> struct Frag {
 template <typename C, typename Issue>
 __device__ __forceinline__ void nt_main_loop(f32x16_v (&acc)[C::WTM][C::WTN], uint32_t a_rel, uint32_t b_rel, int nk, Issue issue) {
   constexpr int S = C::STAGES;
-  constexpr uint32_t STEP = sizeof(typename C::T) == 2 ? 32u : 16u;   // from a k-step's piece to the next one's
+  constexpr uint32_t STEP = 32u;   // from a k-step's piece to the next one's
   Frag<C> f[2];
   if constexpr (S == 2) {
     constexpr int READS = C::WTM + C::WTN;
@@ -326,7 +338,7 @@ k_gemm_nt_tile(const typename C::T *__restrict__ A, const typename C::T *__restr
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
 
   const uint32_t lds_base = (uint32_t)(uintptr_t)(lds_ptr_t)lds;
-  const uint32_t in_row = (uint32_t)(((kBf16 ? g : 4 * g) ^ (r & 7)) << 4);
+  const uint32_t in_row = (uint32_t)((g ^ (r & 7)) << 4);
   const uint32_t a_rel = lds_base + (uint32_t)(wm * C::WTM * 32 + r) * 128u + in_row;
   const uint32_t b_rel = lds_base + (uint32_t)(C::BM + wn * C::WTN * 32 + r) * 128u + in_row;
   nt_main_loop<C>(acc, a_rel, b_rel, nk, issue);

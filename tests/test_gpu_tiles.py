@@ -41,3 +41,13 @@ def test_weight_gradients_over_any_number_of_rows(dtype, M, N, K, splits):
     ref = A.double() @ B.double().T
     out = g.gear_gemm(A.T.contiguous(), B.T.contiguous(), 1, splits=splits)
     assert ((out.double() - ref).abs() <= 1e-5 * ref.abs().max()).all()
+
+
+def test_fp32_bits_do_not_depend_on_the_tile_shape():
+    """Sums run over k in ascending pairs in every shape: the same rows, once in 64 x 64 tiles, once in 128 x 128."""
+    import paper_1806_03925_amd as g
+    for K in (8, 72, 320):
+        A, B, _, bias = operands("f32", 32760, 256, K)
+        big = g.gear_gemm(A, B, 0, 0, bias=bias)
+        small = g.gear_gemm(A[:200].contiguous(), B, 0, 0, bias=bias)
+        assert torch.equal(big[:200], small)
