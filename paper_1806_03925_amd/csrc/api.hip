@@ -100,6 +100,38 @@ bool config_ok(const gear_config &c) {
   return true;
 }
 
+// Bytes of the region that holds the weight gradients' partial results.  Callers allocate a workspace once and keep it,
+// and which configurations the static scratch array takes depends on its size, so this is a fixed rule of the
+// configuration; how many ranges a step cuts its batch into follows from it and not the other way round.
+static size_t wgrad_region_bytes(int dtype, const int32_t *rows, const int32_t *cols, int layers, int K) {
+  auto ranges = [](int tiles, int cap) {
+    int s = 256 / tiles;
+    if (cap < 1) cap = 1;
+    if (s > cap) s = cap;
+    return s < 1 ? 1 : (s > 64 ? 64 : s);
+  };
+  auto tiles_of = [](int m, int n, int bn) { return ((m + 255) / 256) * ((n + bn - 1) / bn); };
+  size_t most = 0, all = 0;
+  int tiles = 0;
+  for (int l = 0; l < layers; ++l) {
+    int s = ranges(tiles_of(rows[l], cols[l], 128), K / 128);
+    if (dtype == GEAR_BF16) {
+      const int t = ranges(tiles_of(rows[l], cols[l], 256), K / 512);
+      if (t > s) s = t;
+    }
+    const size_t n = (size_t)rows[l] * cols[l];
+    if (s * n > most) most = s * n;
+    all += n;
+    tiles += tiles_of(rows[l], cols[l], 256);
+  }
+  // the layers of a bf16 model together, for batches of whole 32-row tiles
+  if (dtype == GEAR_BF16 && layers >= 2 && K >= 32 && tiles <= 128) {
+    const size_t together = ranges(tiles, K / 32 * 32 / 512) * all;
+    if (together > most) most = together;
+  }
+  return most * sizeof(float);
+}
+
 bool make_layout(const gear_config &c, Layout *lay) {
   if (!config_ok(c)) return false;
   memset(lay, 0, sizeof(*lay));
@@ -118,7 +150,6 @@ bool make_layout(const gear_config &c, Layout *lay) {
     off += lay->out_dim[l];
   }
   lay->n_params = off;
-  lay->colsum_chunks = (c.max_batch + kColsumRows - 1) / kColsumRows;
 
   size_t cur = 0;
   const size_t ab = lay->act_bytes;
@@ -141,20 +172,21 @@ bool make_layout(const gear_config &c, Layout *lay) {
   lay->loss_partial = take(&cur, logit_partial_floats(lay->in_dim[L - 1]) * sizeof(float));
   lay->dx_emb = take(&cur, B * 2 * c.emb_dim * sizeof(float));
   lay->dx_dfv = take(&cur, B * c.dfv_dim * ab);
-  {
-    // all hidden layers' partials at once: their products go out as one launch
-    TnProblem wp[GEAR_MAX_LAYERS];
-    size_t all = 0;
-    for (int l = 0; l < L - 1; ++l) {
-      wp[l] = TnProblem{nullptr, nullptr, nullptr, lay->out_dim[l], lay->in_dim[l]};
-      all += (size_t)lay->in_dim[l] * lay->out_dim[l];
-    }
-    max_partial = (size_t)gemm_tn_splits_max(c.mlp_dtype, wp, L - 1, c.max_batch) * all * sizeof(float);
-  }
+  max_partial = wgrad_region_bytes(c.mlp_dtype, lay->out_dim, lay->in_dim, L - 1, c.max_batch);
   lay->wgrad_partial = take(&cur, max_partial);
   lay->wgrad_partial_bytes = max_partial;
-  lay->colsum_stride = (size_t)lay->colsum_chunks * max_h;   // one buffer per hidden layer: they are reduced at the end of a step
-  lay->colsum_partial = take(&cur, lay->colsum_stride * (size_t)(L > 1 ? L - 1 : 1) * sizeof(float));
+  // column-sum partials of all masked products (they are reduced at the end of a step): one block of rows per
+  // kColsumRows rows and layer is what the region holds; products of 64-row tiles leave up to twice as many
+  const size_t blocks = (B + kColsumRows - 1) / kColsumRows;
+  size_t fine = 0;
+  for (int l = 1; l < L - 1; ++l) fine += 2 * blocks * lay->in_dim[l];
+  lay->colsum_coarse = fine > blocks * max_h * (size_t)(L - 1);
+  size_t at = 0;
+  for (int l = 1; l < L - 1; ++l) {
+    lay->colsum_at[l] = at;
+    at += (lay->colsum_coarse ? 1 : 2) * blocks * lay->in_dim[l];
+  }
+  lay->colsum_partial = take(&cur, blocks * max_h * (size_t)(L - 1) * sizeof(float));
   lay->emb_partial = take(&cur, embedding_partial_floats(c) * sizeof(float));
   lay->occ_view = take(&cur, NNZ * sizeof(int32_t));
   for (int s = 0; s < kMaxProblems; ++s) {
@@ -525,7 +557,6 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   int n_wp = 0;
   for (int l = L - 2; l >= 0; --l)
     wp[n_wp++] = TnProblem{ws + lay.delta[l], l == 0 ? x : ws + lay.h[l - 1], nullptr, lay.out_dim[l], lay.in_dim[l]};
-  const int splits = gemm_tn_splits(dt, wp, n_wp, B);
   GEAR_RUN("gather_pool", launch_gather_pool(*cfg, *b, *t, dfv_cache, x, s));
   // A bf16 hidden layer below the last one also leaves the sign bitmap of its activations: the backward pass then
   // reads one bit per unit instead of the activation.
@@ -575,8 +606,8 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
     for (int l = L - 2; l > 0; --l) {
       // bias gradient of layer l - 1: column sums of its delta, left as per-row-tile partials by the
       // product that made it
-      const int parts = gemm_nt_colsum_parts(dt, B, lay.in_dim[l], lay.out_dim[l]);
-      GEAR_RUN("bias_sgd", launch_partial_sgd(cpart + (size_t)l * lay.colsum_stride, parts, lay.out_dim[l - 1],
+      const int parts = gemm_nt_colsum_parts(dt, B, lay.in_dim[l], lay.out_dim[l], lay.colsum_coarse);
+      GEAR_RUN("bias_sgd", launch_partial_sgd(cpart + lay.colsum_at[l], parts, lay.out_dim[l - 1],
                                               t->mlp_params + lay.b_off[l - 1], opt,
                                               moments_at(mom_mlp, lay.b_off[l - 1]), status, s));
     }
@@ -589,7 +620,8 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
       GEAR_RUN(kDgrad[l], launch_gemm_nt(dt, ws + lay.delta[l], ws + lay.wct[l], B, lay.in_dim[l], lay.out_dim[l],
                                          by_bits ? EPI_MASK_BITS : EPI_MASK, nullptr,
                                          by_bits ? (const void *)relu_bits[l - 1] : (const void *)(ws + lay.h[l - 1]),
-                                         ws + lay.delta[l - 1], 0, cpart + (size_t)l * lay.colsum_stride, nullptr, nullptr, s));
+                                         ws + lay.delta[l - 1], 0, cpart + lay.colsum_at[l], nullptr, nullptr, s,
+                                         lay.colsum_coarse));
     } else {
       // dLoss/dx: the embedding slots stay fp32, the DFV slot is kept in the MLP's operand type.
       // When the product is long enough to hide it, it is made in two parts: the embedding slots
@@ -637,24 +669,38 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
                                              out->ready_grads, status, s));
   }
   GEAR_HIP(lane.mark());
-  // SGD on the hidden layers' weights: split-K wgrad (the logit layer and all biases are done on the helper stream)
-  float *next = wpart;
-  SplitkProblem sp[GEAR_MAX_LAYERS];
-  for (int i = 0; i < n_wp; ++i) {
-    const int l = L - 2 - i;
-    wp[i].partial = next;
-    next += (size_t)splits * wp[i].M * wp[i].N;
-    sp[i] = SplitkProblem{wp[i].partial, t->mlp_params + lay.w_off[l], moments_at(mom_mlp, lay.w_off[l]),
-                          (int64_t)wp[i].M * wp[i].N};
+  // SGD on the hidden layers' weights: split-K wgrad (the logit layer and all biases are done on the helper stream).
+  // All layers go out as one launch, in as many ranges of the batch as their partials have room for; a model whose
+  // partials do not fit at once (several wide layers and a short batch) goes in groups of layers.
+  for (int first = 0; first < n_wp;) {
+    const size_t room = lay.wgrad_partial_bytes / sizeof(float);
+    size_t all = 0;
+    int n = 0;
+    while (first + n < n_wp && all + (size_t)wp[first + n].M * wp[first + n].N <= room) {
+      all += (size_t)wp[first + n].M * wp[first + n].N;
+      ++n;
+    }
+    if (n == 0) return GEAR_ERR_CAPACITY;  // cannot happen: the region holds one range of the widest layer
+    int splits = gemm_tn_splits(dt, wp + first, n, B);
+    if (splits > (int)(room / all)) splits = (int)(room / all);
+    float *next = wpart;
+    SplitkProblem sp[GEAR_MAX_LAYERS];
+    for (int i = 0; i < n; ++i) {
+      TnProblem &q = wp[first + i];
+      const int l = L - 2 - (first + i);
+      q.partial = next;
+      next += (size_t)splits * q.M * q.N;
+      sp[i] = SplitkProblem{q.partial, t->mlp_params + lay.w_off[l], moments_at(mom_mlp, lay.w_off[l]), (int64_t)q.M * q.N};
+    }
+    GEAR_RUN("wgrad_gemm", launch_gemm_tn(dt, wp + first, n, B, splits, nullptr, s));
+    // The sums of the partials and the SGD change caller state, so the status word has to be final: the
+    // stream waits for the helper's first part (long done by now), not for the bookkeeping.  Their
+    // workgroups get onto the device as the bookkeeping's leave room and are done before it is, so the
+    // step ends with the bookkeeping and the join.
+    if (first == 0) GEAR_HIP(lane.wait_checked());
+    GEAR_RUN("splitk_sgd", launch_splitk_sgd(sp, n, splits, opt, status, s));
+    first += n;
   }
-  if ((size_t)(next - wpart) * sizeof(float) > lay.wgrad_partial_bytes) return GEAR_ERR_CAPACITY;  // cannot happen: sized for the largest batch
-  GEAR_RUN("wgrad_gemm", launch_gemm_tn(dt, wp, n_wp, B, splits, nullptr, s));
-  // The sums of the partials and the SGD change caller state, so the status word has to be final: the
-  // stream waits for the helper's first part (long done by now), not for the bookkeeping.  Their
-  // workgroups get onto the device as the bookkeeping's leave room and are done before it is, so the
-  // step ends with the bookkeeping and the join.
-  GEAR_HIP(lane.wait_checked());
-  GEAR_RUN("splitk_sgd", launch_splitk_sgd(sp, n_wp, splits, opt, status, s));
   GEAR_HIP(lane.wait(true));  // the step ends on the caller's stream
   if (out->dbg_img_unique && b->nnz > 0)
     GEAR_HIP(hipMemcpyAsync(out->dbg_img_unique, gb.p[2].unique, (size_t)b->nnz * 4, hipMemcpyDeviceToDevice, s));

@@ -155,13 +155,13 @@ struct Layout {
   int64_t w_off[GEAR_MAX_LAYERS];    // float offsets into mlp_params
   int64_t b_off[GEAR_MAX_LAYERS];
   int64_t n_params;
-  int32_t colsum_chunks;             // row chunks of the column-sum kernels
+  bool colsum_coarse;                // the partials only fit with at least kColsumRows rows each
   size_t act_bytes;                  // sizeof(mlp_dtype)
 
   size_t x, h[GEAR_MAX_LAYERS], delta[GEAR_MAX_LAYERS], logits, dz, loss_partial, dx_emb, dx_dfv;
   size_t relu_bits[GEAR_MAX_LAYERS];  // [B x out/8] sign bitmaps of the hidden activations
   size_t wc[GEAR_MAX_LAYERS], wct[GEAR_MAX_LAYERS], wgrad_partial, colsum_partial, emb_partial;
-  size_t colsum_stride;              // floats between the column-sum partials of consecutive layers
+  size_t colsum_at[GEAR_MAX_LAYERS]; // floats before the column-sum partials that layer l's masked product leaves
   size_t wgrad_partial_bytes;        // size of the split-K partial region
   size_t occ_view;
   struct G {
@@ -175,7 +175,7 @@ struct Layout {
 bool make_layout(const gear_config &cfg, Layout *lay);
 bool config_ok(const gear_config &cfg);
 
-constexpr int kColsumRows = 64;      // least rows per partial of a column sum
+constexpr int kColsumRows = 128;     // rows per partial of a column sum that the region of partials is sized for
 constexpr int kLossBlocks = 2048;    // most workgroups (and partial sums) of the logit/loss kernel
 
 // ------------------------------------------------------------------------------------------------
@@ -220,11 +220,12 @@ enum GemmEpilogue {
 // C[M x N] = A[M x K] * B[N x K]^T, both operands K-contiguous, type `dtype`.
 // relu_bits (bf16 and EPI_BIAS_RELU only, may be NULL): bit (n % 8) of byte [m][n / 8] = (out[m][n] > 0), which is
 // what EPI_MASK_BITS (bf16 only) masks with.  colpart (masked products, may be NULL): [parts x N] column sums of
-// what is stored, per row tile.  status may be NULL (the product then always runs).
+// what is stored, per row tile; `coarse` keeps row tiles at kColsumRows rows or more.  status may be NULL (the product
+// then always runs).
 hipError_t launch_gemm_nt(int dtype, const void *A, const void *B, int M, int N, int K, int epilogue,
                           const float *bias, const void *aux, void *out, int split, float *colpart,
-                          uint8_t *relu_bits, const int32_t *status, hipStream_t s);
-int gemm_nt_colsum_parts(int dtype, int M, int N, int K);
+                          uint8_t *relu_bits, const int32_t *status, hipStream_t s, bool coarse = false);
+int gemm_nt_colsum_parts(int dtype, int M, int N, int K, bool coarse);
 // dst[j] -= lr * sum_p partial[p][j], p ascending in a fixed two-level shape
 hipError_t launch_partial_sgd(const float *partial, int P, int H, float *dst, const Optim &opt, const Moments &mom,
                               const int32_t *status, hipStream_t s);
@@ -239,7 +240,6 @@ struct TnProblem {
 hipError_t launch_gemm_tn(int dtype, const TnProblem *p, int count, int K, int splits, const int32_t *status,
                           hipStream_t s, const int32_t *k_dev = nullptr);
 int gemm_tn_splits(int dtype, const TnProblem *p, int count, int K);      // ranges to ask for (looks at M and N only)
-int gemm_tn_splits_max(int dtype, const TnProblem *p, int count, int K);  // the most any contraction length up to K asks for
 // w_i <- update(w_i, sum_z partial_i[z]) for the results of such a launch, in one launch
 struct SplitkProblem {
   const float *partial;
@@ -252,8 +252,8 @@ hipError_t launch_splitk_sgd(const SplitkProblem *p, int count, int splits, cons
 // the same products on tiles of moderate size (gemm_tile.hip)
 hipError_t launch_gemm_nt_tile(int dtype, const void *A, const void *B, int M, int N, int K, int epilogue,
                                const float *bias, const void *aux, void *out, int split, float *colpart,
-                               uint8_t *relu_bits, const int32_t *status, hipStream_t s);
-int nt_tile_colsum_parts(int dtype, int M, int N);
+                               uint8_t *relu_bits, const int32_t *status, hipStream_t s, bool coarse);
+int nt_tile_colsum_parts(int dtype, int M, int N, bool coarse);
 hipError_t launch_gemm_tn_tile(int dtype, const TnProblem *p, int count, int K, int splits, const int32_t *status,
                                hipStream_t s, const int32_t *k_dev);
 int tn_tile_splits(int dtype, const TnProblem *p, int count, int K);

@@ -538,18 +538,18 @@ int tn_dma_splits(const TnProblem *p, int count, int K) {
 }  // namespace
 
 // Number of row-tile partials a masked product leaves in `colpart` ([parts x N] column sums of its result).
-int gemm_nt_colsum_parts(int dtype, int M, int N, int K) {
-  return nt_dma(dtype, M, N, K, false) ? (M + DM - 1) / DM : nt_tile_colsum_parts(dtype, M, N);
+int gemm_nt_colsum_parts(int dtype, int M, int N, int K, bool coarse) {
+  return nt_dma(dtype, M, N, K, false) ? (M + DM - 1) / DM : nt_tile_colsum_parts(dtype, M, N, coarse);
 }
 
 hipError_t launch_gemm_nt(int dtype, const void *A, const void *B, int M, int N, int K, int epi, const float *bias,
                           const void *aux, void *out, int split, float *colpart, uint8_t *relu_bits,
-                          const int32_t *status, hipStream_t s) {
+                          const int32_t *status, hipStream_t s, bool coarse) {
   if (M <= 0 || N <= 0) return hipSuccess;
   if (epi == EPI_MASK_BITS && dtype != GEAR_BF16) return hipErrorInvalidValue;
   const bool narrow = N <= NtNarrow::BN && (epi == EPI_DX || epi == EPI_F32);
   if (!nt_dma(dtype, M, N, K, narrow))
-    return launch_gemm_nt_tile(dtype, A, B, M, N, K, epi, bias, aux, out, split, colpart, relu_bits, status, s);
+    return launch_gemm_nt_tile(dtype, A, B, M, N, K, epi, bias, aux, out, split, colpart, relu_bits, status, s, coarse);
   const dim3 grid(((M + DM - 1) / DM) * (narrow ? 1 : (N + DN - 1) / DN));
 #define GEAR_DMA(E, C)                                                                                                \
   hipLaunchKernelGGL((k_gemm_nt_dma<E, C>), grid, dim3(DTHREADS), 0, s, (const bf16_t *)A, (const bf16_t *)B, M, N, K, \
@@ -574,13 +574,6 @@ hipError_t launch_gemm_nt(int dtype, const void *A, const void *B, int M, int N,
 
 int gemm_tn_splits(int dtype, const TnProblem *p, int count, int K) {
   return tn_dma(dtype, p, count, K) ? tn_dma_splits(p, count, K) : tn_tile_splits(dtype, p, count, K);
-}
-
-// Neither rule decreases in K: the larger of the two at the largest K bounds every smaller one.
-int gemm_tn_splits_max(int dtype, const TnProblem *p, int count, int K) {
-  const int a = tn_tile_splits(dtype, p, count, K);
-  const int b = dtype == GEAR_BF16 ? tn_dma_splits(p, count, K) : 1;
-  return a > b ? a : b;
 }
 
 hipError_t launch_gemm_tn(int dtype, const TnProblem *p, int count, int K, int splits, const int32_t *status,

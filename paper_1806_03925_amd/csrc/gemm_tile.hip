@@ -656,11 +656,12 @@ int rows_of(NtShape shape) { return shape == kSmall ? 64 : 128; }
 // round is mostly empty the half-sized tiles end sooner (16384 x 576 x 512, 640 tiles: 18.8 against 17.6; 10001 x 512
 // x 576, 316 tiles: 13.2 against 12.7).  Below one 128 x 64 tile per CU, 64 x 64 reaches more CUs.
 // fp32: 128 x 128 from one tile per CU on (16384 x 256 x 320: 30.1 us against 31.4), else 64 x 64.
-NtShape nt_shape(int dtype, int M, int N) {
+// `coarse` (column sums of more, narrower row tiles would not fit their region) rules 64 x 64 out.
+NtShape nt_shape(int dtype, int M, int N, bool coarse) {
   const long long big = tiles_of(M, N, 128, 128);
-  if (dtype != GEAR_BF16) return big >= 256 ? kWide : kSmall;
+  if (dtype != GEAR_BF16) return big >= 256 || coarse ? kWide : kSmall;
   const long long tall = tiles_of(M, N, 128, 64);
-  if (tall < 256) return kSmall;
+  if (tall < 256) return coarse ? kTall : kSmall;
   return 2 * ((big + 511) / 512) <= (tall + 767) / 768 ? kWide : kTall;
 }
 
@@ -680,15 +681,15 @@ hipError_t run_tn(const TnProblem *p, int count, int K, int splits, const int32_
 
 }  // namespace
 
-int nt_tile_colsum_parts(int dtype, int M, int N) {
-  const int rows = rows_of(nt_shape(dtype, M, N));
+int nt_tile_colsum_parts(int dtype, int M, int N, bool coarse) {
+  const int rows = rows_of(nt_shape(dtype, M, N, coarse));
   return (M + rows - 1) / rows;
 }
 
 hipError_t launch_gemm_nt_tile(int dtype, const void *A, const void *B, int M, int N, int K, int epi, const float *bias,
                                const void *aux, void *out, int split, float *colpart, uint8_t *relu_bits,
-                               const int32_t *status, hipStream_t s) {
-  const NtShape shape = nt_shape(dtype, M, N);
+                               const int32_t *status, hipStream_t s, bool coarse) {
+  const NtShape shape = nt_shape(dtype, M, N, coarse);
 #define GEAR_NT(C) run_nt_any<C>(A, B, M, N, K, epi, bias, aux, out, split, colpart, relu_bits, status, s)
   if (dtype == GEAR_BF16) return shape == kWide ? GEAR_NT(Bf16Mid) : shape == kTall ? GEAR_NT(Bf16Tall) : GEAR_NT(Bf16Small);
   return shape == kWide ? GEAR_NT(F32Big) : GEAR_NT(F32Small);

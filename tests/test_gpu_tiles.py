@@ -51,3 +51,17 @@ def test_fp32_bits_do_not_depend_on_the_tile_shape():
         big = g.gear_gemm(A, B, 0, 0, bias=bias)
         small = g.gear_gemm(A[:200].contiguous(), B, 0, 0, bias=bias)
         assert torch.equal(big[:200], small)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_weight_gradients_and_bias_sums_that_do_not_fit_at_once(dtype):
+    """Five equal hidden layers and a short batch: the partial results of all weight gradients exceed their region, so
+    the layers go out in groups; the bias partials fit with 128-row tiles only."""
+    from gear_inputs import PageViewSource, get_workload
+    from test_gpu_parity import Pair
+    wl = get_workload("tiny").scaled(batch=300, layers=(512,) * 5 + (1,), emb_dtype=dtype, dfv_dtype=dtype,
+                                     mlp_dtype=dtype)
+    pair = Pair(wl)
+    src = PageViewSource(wl)
+    for step in range(2):
+        pair.step(src.batch(step), wl.lr, f"deep {dtype} step {step}")

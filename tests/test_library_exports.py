@@ -40,3 +40,18 @@ def test_binding_mirrors_the_header():
     assert binding.lib.gear_status_string(3) == b"workspace or ready list too small"
     # null arguments are reported, not dereferenced
     assert binding.lib.gear_step(None, None, None, None, None, None, 1, 0.1, None, 0, None, None) == g.GEAR_ERR_INVALID
+
+
+def test_workspace_size_is_a_fixed_rule_of_the_configuration():
+    """Callers keep workspaces, and the static scratch array takes what fits in 64 MiB: neither may change."""
+    import paper_1806_03925_amd as g
+    sizes = []
+    for B, nnz, layers, dt, d, D in [(1, 1, (8, 1), "f32", 8, 8), (512, 2048, (64, 1), "f32", 16, 64),
+                                     (4096, 32768, (256, 128, 1), "f32", 32, 256),
+                                     (16384, 131072, (512, 256, 1), "bf16", 32, 512),
+                                     (3699, 490, (216, 200, 16, 16, 16, 1), "f32", 96, 1256),
+                                     (700, 900, (512, 512, 512, 512, 512, 1), "bf16", 8, 496),
+                                     (65536, 524288, (1024, 256, 1), "bf16", 64, 1024)]:
+        sizes.append(g.gear_workspace_bytes(g.make_config(1000, 4096, 2000, d, D, layers, "f32", dt, dt, max_batch=B,
+                                                          max_nnz=nnz)))
+    assert sizes == [176128, 2080000, 39670016, 163967232, 87716352, 27937280, 793410048]
