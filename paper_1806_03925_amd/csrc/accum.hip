@@ -10,7 +10,9 @@
 //
 // Work is cut into units of at most M rows (see the plan in group.hip), one workgroup per unit,
 // rows added in arrival order (flat CSR order continuing the earlier steps): no float atomics.
-#include "gear_internal.hpp"
+#include "embedding_common.hpp"
+
+#include <string.h>
 
 namespace gear {
 namespace {
@@ -86,21 +88,47 @@ __device__ __forceinline__ void add_rows(float (&acc)[Cols<GT>::N], const int32_
   }
 }
 
+// Partials of a long run in flight, in the form that shares k_accumulate's registers: more than eight would cost the units
+// their wavefronts (32 in flight: 138 registers; eight: 59).
+constexpr int kSpanInFlight = 8;
+
+// Embedding sums that k_accumulate's first workgroups finish (blocks per table; none without SPANS).
+struct SpanWork {
+  EmbeddingTable table[2];
+  int blocks, d, bf16;
+  Optim opt;
+};
+
 // dx: the DFV slot of dLoss/dx, [B x D].  One workgroup per unit, D / Cols<GT>::N threads.
-template <typename GT>
+template <typename GT, bool SPANS>
 __global__ void __launch_bounds__(256)
 k_accumulate(AccumPlan plan, const GT *__restrict__ dx, int D, float *__restrict__ accum, int M,
-             int32_t *__restrict__ ready_ids, float *__restrict__ ready_grads, const int32_t *__restrict__ status) {
+             int32_t *__restrict__ ready_ids, float *__restrict__ ready_grads, SpanWork spans,
+             const int32_t *__restrict__ status) {
   if (*status != 0) return;
+  int block = blockIdx.x, blocks = gridDim.x;
+  if constexpr (SPANS) {
+    if (block < 2 * spans.blocks) {
+      const int second = block >= spans.blocks ? 1 : 0;
+      const int chunk = (block - second * spans.blocks) * (blockDim.x / kWave) + threadIdx.x / kWave;
+      if (spans.bf16)
+        embedding_span<bf16_t, kSpanInFlight>(spans.table[second], chunk, spans.d, spans.opt);
+      else
+        embedding_span<float, kSpanInFlight>(spans.table[second], chunk, spans.d, spans.opt);
+      return;
+    }
+    block -= 2 * spans.blocks;
+    blocks -= 2 * spans.blocks;
+  }
   constexpr int N = Cols<GT>::N;
   const int n_units = *plan.n_units;
   const int DC = D / N;
   const float fM = (float)M;
-  int u = blockIdx.x;
+  int u = block;
   if (u >= n_units) return;
   UnitDesc d = plan.units[u];
   while (true) {
-    const int u_next = u + gridDim.x;
+    const int u_next = u + blocks;
     UnitDesc d_next = d;
     if (u_next < n_units) d_next = plan.units[u_next];  // in flight while this unit is summed
     float *arow = accum + (size_t)d.image * D;
@@ -150,16 +178,6 @@ k_accumulate(AccumPlan plan, const GT *__restrict__ dx, int D, float *__restrict
   }
 }
 
-// counts[image] += occurrences of the image in this step (Section 1, third point: the number of
-// gradients collected for an image)
-__global__ void __launch_bounds__(256) k_count_update(GroupProblem img, int32_t *__restrict__ counts,
-                                                      const int32_t *__restrict__ status) {
-  if (*status != 0) return;
-  const int n_seg = *img.n_unique;
-  for (int s = blockIdx.x * blockDim.x + threadIdx.x; s < n_seg; s += gridDim.x * blockDim.x)
-    counts[img.unique[s]] += img.segoff[s + 1] - img.segoff[s];
-}
-
 // dfv_cache[ids[r]] = rows[r]; one wavefront per row, 16-byte pieces
 __global__ void __launch_bounds__(256) k_refresh(uint4 *__restrict__ cache, int64_t n_images, int vec_per_row,
                                                  const int32_t *__restrict__ ids, const uint4 *__restrict__ rows,
@@ -179,29 +197,38 @@ __global__ void __launch_bounds__(256) k_refresh(uint4 *__restrict__ cache, int6
 
 }  // namespace
 
+// With `emb` the launch also finishes the embedding update, in workgroups ahead of the units': on a short step that
+// saves a launch of a handful of busy wavefronts (small: 8 us on one stream).
 hipError_t launch_accumulate(const gear_config &cfg, const GroupProblem &img, const AccumPlan &plan,
                              const void *dx_dfv, float *grad_accum, int32_t M, int32_t *ready_ids,
-                             float *ready_grads, const int32_t *status, hipStream_t s) {
-  if (img.n <= 0) return hipSuccess;
+                             float *ready_grads, const EmbeddingFinish *emb, const int32_t *status, hipStream_t s) {
+  if (img.n <= 0 && !emb) return hipSuccess;
   const int D = cfg.dfv_dim;
   const int cols = cfg.mlp_dtype == GEAR_BF16 ? 8 : 4;
   int threads = ((D / cols + 63) / 64) * 64;
   if (threads > 256) threads = 256;
   int blocks = img.n < 32768 ? img.n : 32768;
-  if (cfg.mlp_dtype == GEAR_BF16)
-    hipLaunchKernelGGL(k_accumulate<bf16_t>, dim3(blocks), dim3(threads), 0, s, plan, (const bf16_t *)dx_dfv, D,
-                       grad_accum, M, ready_ids, ready_grads, status);
-  else
-    hipLaunchKernelGGL(k_accumulate<float>, dim3(blocks), dim3(threads), 0, s, plan, (const float *)dx_dfv, D,
-                       grad_accum, M, ready_ids, ready_grads, status);
-  return hipGetLastError();
-}
-
-hipError_t launch_count_update(const GroupProblem &img, int32_t *counts, const int32_t *status, hipStream_t s) {
-  if (img.n <= 0) return hipSuccess;
-  int blocks = (img.n + 255) / 256;
-  if (blocks > 1024) blocks = 1024;
-  hipLaunchKernelGGL(k_count_update, dim3(blocks), dim3(256), 0, s, img, counts, status);
+  SpanWork spans;
+  memset(&spans, 0, sizeof(spans));
+  if (emb) {
+    embedding_tables(cfg, *emb->users, *emb->urls, emb->user_emb, emb->url_emb, emb->partials, emb->mom_user, emb->mom_url,
+                     &spans.table[0], &spans.table[1]);
+    const int chunks = (emb->users->n + kChunk - 1) / kChunk, waves = threads / kWave;   // both lists have one id per view
+    spans.blocks = (chunks + waves - 1) / waves;
+    spans.d = cfg.emb_dim;
+    spans.bf16 = cfg.emb_dtype == GEAR_BF16;
+    spans.opt = emb->opt;
+    blocks += 2 * spans.blocks;
+  }
+#define GEAR_ACC(T, S)                                                                                                     \
+  hipLaunchKernelGGL((k_accumulate<T, S>), dim3(blocks), dim3(threads), 0, s, plan, (const T *)dx_dfv, D, grad_accum, M, \
+                     ready_ids, ready_grads, spans, status)
+  if (cfg.mlp_dtype == GEAR_BF16) {
+    if (emb) GEAR_ACC(bf16_t, true); else GEAR_ACC(bf16_t, false);
+  } else {
+    if (emb) GEAR_ACC(float, true); else GEAR_ACC(float, false);
+  }
+#undef GEAR_ACC
   return hipGetLastError();
 }
 

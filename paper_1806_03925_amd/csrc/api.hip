@@ -25,26 +25,26 @@ int bits_for(int64_t range) {
   return b;
 }
 
-GroupProblem make_problem(const Layout &lay, char *ws, int slot, const int32_t *keys, int n, int64_t range) {
+// `bits`: what the keys have at most
+GroupProblem make_problem(const Layout &lay, char *ws, int slot, const int32_t *keys, int n, int64_t range, int passes, int bits) {
   GroupProblem p;
   memset(&p, 0, sizeof(p));
   p.keys_in = keys;
   p.n = n;
-  p.key_bits = bits_for(range);
-  p.passes = (p.key_bits + kMaxRadixBits - 1) / kMaxRadixBits;
-  p.digit_bits = (p.key_bits + p.passes - 1) / p.passes;
+  p.range = range;
+  p.passes = passes;
+  p.digit_bits = (bits + passes - 1) / passes;
   const Layout::G &g = lay.g[slot];
   for (int i = 0; i < 2; ++i) {
     p.keys[i] = (int32_t *)(ws + g.keys[i]);
     p.vals[i] = (int32_t *)(ws + g.vals[i]);
   }
-  p.block_hist = (int32_t *)(ws + g.block_hist);
+  p.totals = (int32_t *)(ws + g.totals);
+  p.state = (uint32_t *)(ws + g.state);
   p.sorted_keys = p.keys[p.passes & 1];
   p.perm = p.vals[p.passes & 1];
-  p.tile_heads = (int32_t *)(ws + g.tile_heads);
   p.unique = (int32_t *)(ws + g.unique);
   p.segoff = (int32_t *)(ws + g.segoff);
-  p.pos_seg = (int32_t *)(ws + g.pos_seg);
   p.n_unique = (int32_t *)(ws + g.n_unique);
   return p;
 }
@@ -169,7 +169,20 @@ bool make_layout(const gear_config &c, Layout *lay) {
   }
   lay->logits = take(&cur, B * sizeof(float));
   lay->dz = take(&cur, B * sizeof(float));
-  lay->loss_partial = take(&cur, logit_partial_floats(lay->in_dim[L - 1]) * sizeof(float));
+  // The sums of the logit kernel and the digit totals of the sorts share a region: a batch of B views has one row of
+  // sums per 32 views, which leaves most of a region of kLossBlocks rows to the totals of a short batch; a long one has
+  // more tiles, whose share (one row of 512 per tile and list) is enough.
+  const size_t sums = logit_partial_floats(lay->in_dim[L - 1], c.max_batch);
+  size_t pool = logit_partial_floats(lay->in_dim[L - 1], 32 * kLossBlocks);
+  for (int s = 0; s < kMaxProblems; ++s) pool += ((s == 2 ? NNZ : B) + kSortTile - 1) / kSortTile * 512 + 512;
+  lay->loss_partial = take(&cur, pool * sizeof(float));
+  lay->tickets = lay->loss_partial + sums * sizeof(float);
+  size_t room = (pool - sums - kTickets) / kMaxProblems;
+  if (room > (size_t)kStateWords) room = kStateWords;
+  for (int s = 0; s < kMaxProblems; ++s) {
+    lay->g[s].totals = lay->tickets + (kTickets + s * room) * sizeof(float);
+    lay->g[s].total_words = (int32_t)room;
+  }
   lay->dx_emb = take(&cur, B * 2 * c.emb_dim * sizeof(float));
   lay->dx_dfv = take(&cur, B * c.dfv_dim * ab);
   max_partial = wgrad_region_bytes(c.mlp_dtype, lay->out_dim, lay->in_dim, L - 1, c.max_batch);
@@ -197,16 +210,19 @@ bool make_layout(const gear_config &c, Layout *lay) {
       g.keys[i] = take(&cur, n * sizeof(int32_t));
       g.vals[i] = take(&cur, n * sizeof(int32_t));
     }
-    g.block_hist = take(&cur, (tiles + 1) * kMaxRadix * sizeof(int32_t));
-    g.tile_heads = take(&cur, tiles * sizeof(int32_t));
+    // what the tiles of a pass publish (at most 24 KB for each tile but the last) lies where nothing is kept until
+    // the sorts are done
+    if (s < 2) take(&cur, tiles * sizeof(int32_t));
     g.unique = take(&cur, n * sizeof(int32_t));
     g.segoff = take(&cur, (n + 1) * sizeof(int32_t));
-    g.pos_seg = take(&cur, n * sizeof(int32_t));
+    take(&cur, n * sizeof(int32_t));
     g.n_unique = take(&cur, sizeof(int32_t));
+    g.state = g.unique;
   }
   const size_t tiles = (NNZ + kSortTile - 1) / kSortTile;
-  lay->tile_units = take(&cur, tiles * sizeof(int32_t));
-  lay->tile_emits = take(&cur, tiles * sizeof(int32_t));
+  lay->seg_state = take(&cur, tiles * sizeof(int32_t));   // three words a tile
+  take(&cur, tiles * sizeof(int32_t));
+  take(&cur, tiles * sizeof(int32_t));
   lay->units = take(&cur, NNZ * sizeof(UnitDesc));
   lay->row_view = take(&cur, NNZ * sizeof(int32_t));
   lay->row_scale = take(&cur, NNZ * sizeof(float));
@@ -509,19 +525,30 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   static const char *const kDgrad[GEAR_MAX_LAYERS] = {"dgrad_gemm_l0", "dgrad_gemm_l1", "dgrad_gemm_l2",
                                                       "dgrad_gemm_l3", "dgrad_gemm_l4", "dgrad_gemm_l5",
                                                       "dgrad_gemm_l6", "dgrad_gemm_l7"};
-  GEAR_RUN("begin", launch_begin(status, out->n_ready, out->loss, s));
-  if (B == 0) return GEAR_OK;
+  if (B == 0) {
+    GEAR_RUN("begin", launch_begin(status, out->n_ready, out->loss, ZeroList{}, dt, nullptr, 0, s));
+    return GEAR_OK;
+  }
   int32_t *occ_view = (int32_t *)(ws + lay.occ_view);
 
   // grouping of the three id lists and the plan of the per-image accumulation
   GroupBatch gb;
-  gb.count = 3;
-  gb.p[0] = make_problem(lay, ws, 0, b->user_id, B, cfg->n_users);
-  gb.p[1] = make_problem(lay, ws, 1, b->url_id, B, cfg->n_urls);
-  gb.p[2] = make_problem(lay, ws, 2, b->img_id, b->nnz, cfg->n_images);
+  {
+    const int bits[kMaxProblems] = {bits_for(cfg->n_users), bits_for(cfg->n_urls), bits_for(cfg->n_images)};
+    int passes = 1;   // the lists share launches: as many passes for all as the widest ids need
+    for (int i = 0; i < kMaxProblems; ++i) {
+      const int need = radix_passes(bits[i], lay.g[i].total_words, B > b->nnz ? B : b->nnz);
+      if (need > passes) passes = need;
+    }
+    gb.count = kMaxProblems;
+    gb.p[0] = make_problem(lay, ws, 0, b->user_id, B, cfg->n_users, passes, bits[0]);
+    gb.p[1] = make_problem(lay, ws, 1, b->url_id, B, cfg->n_urls, passes, bits[1]);
+    gb.p[2] = make_problem(lay, ws, 2, b->img_id, b->nnz, cfg->n_images, passes, bits[2]);
+    gb.tickets = (int32_t *)(ws + lay.tickets);
+    gb.seg_state = (uint32_t *)(ws + lay.seg_state);
+    if (!out->dbg_img_unique && !out->dbg_img_segoff) gb.p[2].unique = gb.p[2].segoff = nullptr;   // nothing in the step reads them
+  }
   AccumPlan plan;
-  plan.tile_units = (int32_t *)(ws + lay.tile_units);
-  plan.tile_emits = (int32_t *)(ws + lay.tile_emits);
   plan.units = (UnitDesc *)(ws + lay.units);
   plan.row_view = (int32_t *)(ws + lay.row_view);
   plan.row_scale = (float *)(ws + lay.row_scale);
@@ -536,20 +563,18 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   if (!one_stream && !side) return GEAR_ERR_HIP;
   hipStream_t helper = one_stream ? s : side->stream;
   LaneScope lane(side, s);
-  GEAR_HIP(lane.fork());
   {
-    // operand copies of the weights (all layers in one launch), ahead of the gather on the caller's
-    // stream: the first product then needs no event, and behind the gather's many workgroups the
-    // copies would not get onto the device before it ends anyway
-    const float *cw[GEAR_MAX_LAYERS];
-    void *cwc[GEAR_MAX_LAYERS], *cwct[GEAR_MAX_LAYERS];
-    for (int l = 0; l < L; ++l) {
-      cw[l] = t->mlp_params + lay.w_off[l];
-      cwc[l] = ws + lay.wc[l];
-      cwct[l] = ws + lay.wct[l];
-    }
-    GEAR_RUN("cast_weights", launch_cast_weights(L, cw, lay.out_dim, lay.in_dim, dt, cwc, cwct, status, s));
+    // Step outputs and counters cleared and the operand copies of the weights made in one launch ahead of everything:
+    // the first product then needs no event, and behind the gather's many workgroups the copies would not get onto the
+    // device before it ends anyway.
+    CastJob jobs[GEAR_MAX_LAYERS];
+    for (int l = 0; l < L; ++l)
+      jobs[l] = CastJob{t->mlp_params + lay.w_off[l], ws + lay.wc[l], ws + lay.wct[l], lay.out_dim[l], lay.in_dim[l]};
+    ZeroList zero;
+    group_zero_list(gb, &zero);
+    GEAR_RUN("begin", launch_begin(status, out->n_ready, out->loss, zero, dt, jobs, L, s));
   }
+  GEAR_HIP(lane.fork());
   // forward
   void *x = ws + lay.x;
   // the weight-gradient products of the hidden layers
@@ -569,14 +594,12 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
                                      ws + lay.h[l], 0, nullptr, relu_bits[l], nullptr, s));
   // The helper stream's launches are issued after the forward pass's: where the host is not ahead of the
   // device (a caller that waits for every step), the gather then starts as soon as the step does, not
-  // after the host has issued the grouping's many small launches.
+  // after the host has issued the grouping's launches.
   {
     hipStream_t s = helper;  // the launches of this block go to the helper stream
-    GEAR_RUN("validate", launch_validate(*cfg, *b, occ_view, status, s));
-    GEAR_RUN("group_ids", launch_group(gb, status, s));
-    GEAR_RUN("accum_plan", launch_accum_plan(gb.p[2], plan, occ_view, b->img_off, counts, M, out->ready_cap,
-                                             out->n_ready, status, s));
-    GEAR_RUN("count_update", launch_count_update(gb.p[2], counts, status, s));
+    GEAR_RUN("group_ids", launch_group(gb, b->img_off, occ_view, B, b->nnz, status, s));
+    GEAR_RUN("accum_plan", launch_accum_plan(gb, plan, occ_view, b->img_off, counts, M, out->ready_cap, out->n_ready,
+                                             status, s));
   }
   GEAR_HIP(lane.mark_checked());
 
@@ -595,24 +618,26 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   float *dx_emb = (float *)(ws + lay.dx_emb);
   void *dx_dfv = ws + lay.dx_dfv;
   float *cpart = (float *)(ws + lay.colsum_partial), *wpart = (float *)(ws + lay.wgrad_partial);
-  // Small reductions whose results nothing in the step reads (the loss, SGD on the logit layer and on
-  // the biases): they go to the helper stream, ahead of the embedding update.
-  auto small_reductions = [&](hipStream_t s) -> gear_status {
-    GEAR_RUN("logit_sgd", launch_logit_finish((float *)(ws + lay.loss_partial), B, lay.in_dim[L - 1],
-                                              t->mlp_params + lay.w_off[L - 1], t->mlp_params + lay.b_off[L - 1],
-                                              t->mlp_params + lay.b_off[L - 2], out->loss, opt,
-                                              moments_at(mom_mlp, lay.w_off[L - 1]), moments_at(mom_mlp, lay.b_off[L - 1]),
-                                              moments_at(mom_mlp, lay.b_off[L - 2]), status, s));
-    for (int l = L - 2; l > 0; --l) {
-      // bias gradient of layer l - 1: column sums of its delta, left as per-row-tile partials by the
-      // product that made it
-      const int parts = gemm_nt_colsum_parts(dt, B, lay.in_dim[l], lay.out_dim[l], lay.colsum_coarse);
-      GEAR_RUN("bias_sgd", launch_partial_sgd(cpart + lay.colsum_at[l], parts, lay.out_dim[l - 1],
-                                              t->mlp_params + lay.b_off[l - 1], opt,
-                                              moments_at(mom_mlp, lay.b_off[l - 1]), status, s));
-    }
-    return GEAR_OK;
+  EmbeddingFinish emb = {&gb.p[0], &gb.p[1], t->user_emb, t->url_emb, (float *)(ws + lay.emb_partial), opt, mom_user, mom_url};
+  auto embedding_chunks = [&](hipStream_t s) {
+    return launch_embedding_chunks(*cfg, gb.p[0], gb.p[1], b->nnz, plan, dx_emb, t->user_emb, t->url_emb, emb.partials, opt,
+                                   mom_user, mom_url, counts, status, s);
   };
+  // Small sums whose results nothing in the step reads: the loss, the logit layer and the biases (column sums of deltas,
+  // left as per-row-tile partials by the products that made them).
+  ColumnSum columns[kMaxColumnSums];
+  int n_columns = 0;
+  const LogitSums sums = logit_sums((const float *)(ws + lay.loss_partial), B, lay.in_dim[L - 1]);
+  auto column = [&](const float *partial, int parts, int width, int64_t at) {
+    columns[n_columns++] = ColumnSum{partial, t->mlp_params + at, moments_at(mom_mlp, at), parts, width};
+  };
+  column(sums.w, sums.parts, lay.in_dim[L - 1], lay.w_off[L - 1]);
+  column(sums.delta, sums.parts, lay.in_dim[L - 1], lay.b_off[L - 2]);
+  column(sums.bias, sums.parts, 1, lay.b_off[L - 1]);
+  for (int l = L - 2; l > 0; --l)
+    column(cpart + lay.colsum_at[l], gemm_nt_colsum_parts(dt, B, lay.in_dim[l], lay.out_dim[l], lay.colsum_coarse),
+           lay.out_dim[l - 1], lay.b_off[l - 1]);
+  const LossSum loss = {sums.loss, out->loss, sums.parts, B};
   bool embedding_updated = false;
   for (int l = L - 2; l >= 0; --l) {
     if (l > 0) {
@@ -635,10 +660,12 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
         GEAR_HIP(lane.fork());
         {
           hipStream_t s = helper;
-          if (gear_status st = small_reductions(s)) return st;
-          GEAR_RUN("embedding_update",
-                   launch_embedding_update(*cfg, gb.p[0], gb.p[1], dx_emb, t->user_emb, t->url_emb,
-                                           (float *)(ws + lay.emb_partial), opt, mom_user, mom_url, status, s));
+          GEAR_RUN("small_sums", launch_param_update(nullptr, 0, 1, columns, n_columns, loss, opt, status, s));
+          GEAR_RUN("embedding_update", [&]() -> hipError_t {
+            const hipError_t e = embedding_chunks(s);
+            return e != hipSuccess ? e : launch_embedding_spans(*cfg, gb.p[0], gb.p[1], t->user_emb, t->url_emb, emb.partials,
+                                                                opt, mom_user, mom_url, status, s);
+          }());
         }
         embedding_updated = true;
         GEAR_RUN(kDgrad[0], launch_gemm_nt(dt, ws + lay.delta[0],
@@ -659,17 +686,12 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   GEAR_HIP(lane.fork());
   {
     hipStream_t s = helper;
-    if (!embedding_updated) {
-      if (gear_status st = small_reductions(s)) return st;
-      GEAR_RUN("embedding_update",
-               launch_embedding_update(*cfg, gb.p[0], gb.p[1], dx_emb, t->user_emb, t->url_emb,
-                                       (float *)(ws + lay.emb_partial), opt, mom_user, mom_url, status, s));
-    }
-    GEAR_RUN("accumulate", launch_accumulate(*cfg, gb.p[2], plan, dx_dfv, grad_accum, M, out->ready_ids,
-                                             out->ready_grads, status, s));
+    if (!embedding_updated) GEAR_RUN("embedding_update", embedding_chunks(s));
+    GEAR_RUN("accumulate", launch_accumulate(*cfg, gb.p[2], plan, dx_dfv, grad_accum, M, out->ready_ids, out->ready_grads,
+                                             embedding_updated ? nullptr : &emb, status, s));
   }
   GEAR_HIP(lane.mark());
-  // SGD on the hidden layers' weights: split-K wgrad (the logit layer and all biases are done on the helper stream).
+  // SGD on the hidden layers' weights: split-K wgrad.  With the last of them go the small sums, unless they are done.
   // All layers go out as one launch, in as many ranges of the batch as their partials have room for; a model whose
   // partials do not fit at once (several wide layers and a short batch) goes in groups of layers.
   for (int first = 0; first < n_wp;) {
@@ -698,8 +720,10 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
     // workgroups get onto the device as the bookkeeping's leave room and are done before it is, so the
     // step ends with the bookkeeping and the join.
     if (first == 0) GEAR_HIP(lane.wait_checked());
-    GEAR_RUN("splitk_sgd", launch_splitk_sgd(sp, n, splits, opt, status, s));
     first += n;
+    const bool sums_too = first == n_wp && !embedding_updated;   // else the helper stream has done them
+    GEAR_RUN("param_update", launch_param_update(sp, n, splits, columns, sums_too ? n_columns : 0, sums_too ? loss : LossSum{}, opt,
+                                                 status, s));
   }
   GEAR_HIP(lane.wait(true));  // the step ends on the caller's stream
   if (out->dbg_img_unique && b->nnz > 0)
@@ -753,12 +777,19 @@ gear_status gear_group_ids(const gear_config *cfg, const int32_t *keys, int32_t 
   hipStream_t s = (hipStream_t)stream;
   char *ws = (char *)workspace;
   int32_t *status = (int32_t *)(ws + lay.n_units);  // a spare word, cleared below: nothing can fail here
-  GEAR_HIP(launch_fill_zero(status, sizeof(int32_t), s));
   GroupBatch gb;
   gb.count = 1;
-  gb.p[0] = make_problem(lay, ws, 2, keys, n, key_range);
-  gb.p[0].pos_seg = nullptr;
-  GEAR_HIP(launch_group(gb, status, s));
+  const int bits = bits_for(key_range);
+  gb.p[0] = make_problem(lay, ws, 2, keys, n, 0, radix_passes(bits, lay.g[2].total_words, n), bits);
+  gb.tickets = (int32_t *)(ws + lay.tickets);
+  gb.seg_state = (uint32_t *)(ws + lay.seg_state);
+  ZeroList zero;
+  group_zero_list(gb, &zero);
+  zero.p[zero.count] = (uint32_t *)status;
+  zero.words[zero.count++] = 1;
+  GEAR_HIP(launch_clear(zero, s));
+  GEAR_HIP(launch_group(gb, nullptr, nullptr, 0, 0, status, s));
+  GEAR_HIP(launch_segments(gb, status, s));
   if (n > 0) {
     GEAR_HIP(hipMemcpyAsync(unique, gb.p[0].unique, (size_t)n * 4, hipMemcpyDeviceToDevice, s));
     GEAR_HIP(hipMemcpyAsync(perm, gb.p[0].perm, (size_t)n * 4, hipMemcpyDeviceToDevice, s));
@@ -814,7 +845,7 @@ gear_status gear_gemm(int32_t dtype, int32_t form, const void *A, const void *B,
     const Optim minus = {-1.0f, 0.0f, 0.0f, 0.0f, 1.0f, 0};   // out = 0 - (-1) * sum of the partials
     const Moments none = {nullptr, nullptr};
     const SplitkProblem sum = {partial, (float *)out, none, (int64_t)M * N};
-    GEAR_HIP(launch_splitk_sgd(&sum, 1, splits, minus, status, s));
+    GEAR_HIP(launch_param_update(&sum, 1, splits, nullptr, 0, LossSum{}, minus, status, s));
   } else {
     return GEAR_ERR_INVALID;
   }

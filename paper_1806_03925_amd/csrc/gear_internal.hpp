@@ -92,38 +92,71 @@ template <> struct Vec16<bf16_t> {
 
 constexpr int kWave = 64;
 
+// first index of the ascending keys[lo .. hi) whose key is >= key (> key with `after`), hi if there is none;
+// by one wavefront, 64 probes at a time
+__device__ __forceinline__ int wave_search(const int32_t *__restrict__ keys, int lo, int hi, int key, bool after, int lane) {
+  while (lo < hi) {
+    const int step = (hi - lo - 1) / kWave + 1;
+    const int64_t at = (int64_t)lo + (int64_t)lane * step;
+    const int probe = at < hi ? keys[at] : 0;
+    const unsigned long long m = __ballot(at >= hi || (after ? probe > key : probe >= key));
+    const int first = m ? __builtin_ctzll(m) : kWave;
+    const int64_t up = (int64_t)lo + (int64_t)first * step;
+    if (first < kWave && up < hi) hi = (int)up;
+    if (first > 0) lo = (int)min((int64_t)hi, (int64_t)lo + (int64_t)(first - 1) * step + 1);
+  }
+  return lo;
+}
+
 // ------------------------------------------------------------------------------------------------
 // grouping (sort by key + segments) problem descriptors
 // ------------------------------------------------------------------------------------------------
 constexpr int kSortBlock = 256;                       // threads
 constexpr int kSortItems = 8;                         // keys per thread
 constexpr int kSortTile = kSortBlock * kSortItems;    // keys per workgroup
-constexpr int kMaxRadixBits = 9;
-constexpr int kMaxRadix = 1 << kMaxRadixBits;
 constexpr int kMaxProblems = 3;
+constexpr int kMaxPasses = 3;
+constexpr int kMaxDigitBits = 12;
+constexpr int kLongList = 65536;                      // ids from which a launch takes larger tiles (sort_threads)
+// Counts a tile publishes over all passes, at most.  A pass costs a launch and two memory latencies whatever its
+// radix, so a list takes as few passes as its keys allow within this (one up to 12 bits, two up to 22, then three);
+// it is what the regions that hold the counts have room for (24 KB per tile of 2048 keys).
+constexpr int kStateWords = 6144;
+constexpr int kTickets = kMaxProblems * kMaxPasses + 1;   // one per list and pass, the last one for the segments
 
 struct GroupProblem {
   const int32_t *keys_in;  // [n] original keys (read by the first pass)
+  int64_t range;           // keys have to be below this; 0: not checked
   int32_t n;
-  int32_t key_bits;        // significant bits of a key
   int32_t passes;          // radix passes
   int32_t digit_bits;      // bits per pass
   int32_t *keys[2];        // ping-pong key buffers [n]
   int32_t *vals[2];        // ping-pong position buffers [n]
-  int32_t *block_hist;     // [n_tiles x radix] digit counts per tile, then exclusive offsets
+  int32_t *totals;         // [passes][radix] keys of a digit in the whole list
+  uint32_t *state;         // [passes][tiles - 1][radix] what tiles publish for those after them
   int32_t *sorted_keys;    // = keys[passes & 1]
   int32_t *perm;           // = vals[passes & 1]
-  int32_t *tile_heads;     // [n_tiles] number of segment heads per tile
-  int32_t *unique;         // [n]   distinct keys ascending
-  int32_t *segoff;         // [n+1] segment offsets
-  int32_t *pos_seg;        // [n]   segment index of each sorted position (may be NULL)
+  int32_t *unique;         // [n]   distinct keys ascending (NULL: not wanted)
+  int32_t *segoff;         // [n+1] segment offsets (with `unique`)
   int32_t *n_unique;       // [1]
 };
 
 struct GroupBatch {
-  GroupProblem p[kMaxProblems];
+  GroupProblem p[kMaxProblems];   // segments are made of the last one
   int32_t count;
+  int32_t *tickets;               // [kTickets]
+  uint32_t *seg_state;            // [tiles - 1][3] heads, units and emissions, published like `state`
 };
+
+// fewest passes over keys of `bits` bits (twelve-bit digits of the large tiles would take more than 64 KB of LDS)
+inline int radix_passes(int bits, int most_words, int n) {
+  int passes = 1;
+  for (; passes < kMaxPasses; ++passes) {
+    const int digit_bits = (bits + passes - 1) / passes;
+    if (digit_bits <= (n > kLongList ? kMaxDigitBits - 1 : kMaxDigitBits) && (passes << digit_bits) <= most_words) break;
+  }
+  return passes;
+}
 
 // plan of the windowed accumulation over the sorted image occurrences
 struct UnitDesc {         // one workgroup's share of the accumulation (32 bytes)
@@ -132,12 +165,11 @@ struct UnitDesc {         // one workgroup's share of the accumulation (32 bytes
   int32_t slot;           // ready-list slot of the unit's (first) emission
   int32_t s0, s1;         // the image's range of sorted positions
   int32_t phase;          // gradients already collected for the image before this step, modulo M
-  int32_t pad[2];
+  int32_t collected;      // gradients collected for the image after this step
+  int32_t pad;
 };
 
 struct AccumPlan {
-  int32_t *tile_units;   // [n_tiles] unit heads per tile
-  int32_t *tile_emits;   // [n_tiles] completed groups per tile
   UnitDesc *units;       // [nnz]
   int32_t *row_view;     // [nnz] view that owns the occurrence at each sorted position
   float *row_scale;      // [nnz] 1 / (images of that view): backward of the mean
@@ -165,9 +197,10 @@ struct Layout {
   size_t wgrad_partial_bytes;        // size of the split-K partial region
   size_t occ_view;
   struct G {
-    size_t keys[2], vals[2], block_hist, tile_heads, unique, segoff, pos_seg, n_unique;
+    size_t keys[2], vals[2], totals, state, unique, segoff, n_unique;
+    int32_t total_words;             // room for `totals`
   } g[kMaxProblems];
-  size_t tile_units, tile_emits, units, row_view, row_scale, n_units;
+  size_t tickets, seg_state, units, row_view, row_scale, n_units;
   size_t expiry_marks, expiry_tiles;  // gear_expired_ids: byte map over the images, marked bytes per tile
   size_t total;
 };
@@ -185,11 +218,26 @@ hipError_t launch_fill_normal(void *dst, int dtype, int64_t n_elems, uint64_t se
                               float std, hipStream_t s);
 hipError_t launch_fill_zero(void *dst, size_t bytes, hipStream_t s);
 
-hipError_t launch_begin(int32_t *status, int32_t *n_ready, float *loss, hipStream_t s);
-hipError_t launch_validate(const gear_config &cfg, const gear_batch &b, int32_t *occ_view, int32_t *status,
-                           hipStream_t s);
-
-hipError_t launch_group(const GroupBatch &gb, const int32_t *status, hipStream_t s);
+// words that a launch clears on the way
+struct ZeroList {
+  static constexpr int kMax = 2 * kMaxProblems + 3;
+  int count;
+  uint32_t *p[kMax];
+  int64_t words[kMax];
+};
+// launch_begin clears the step's outputs and `zero`, and makes the operand copies of `count` layers' weights
+struct CastJob {
+  const float *w;
+  void *wc, *wct;
+  int rows, cols;
+};
+hipError_t launch_clear(const ZeroList &zero, hipStream_t s);
+hipError_t launch_begin(int32_t *status, int32_t *n_ready, float *loss, const ZeroList &zero, int dtype, const CastJob *jobs,
+                        int count, hipStream_t s);
+void group_zero_list(const GroupBatch &gb, ZeroList *z);
+hipError_t launch_group(const GroupBatch &gb, const int32_t *img_off, int32_t *occ_view, int B, int nnz, int32_t *status,
+                        hipStream_t s);
+hipError_t launch_segments(const GroupBatch &gb, int32_t *status, hipStream_t s);
 // distinct ids of a grouped list whose cache entry is older than `expiry`, ascending
 // words (four images each) of the byte map over all images that the expiry filter marks, and tiles
 // of kSortTile words
@@ -200,15 +248,12 @@ hipError_t launch_expired(const int32_t *image_ids, int n, const int32_t *stamp,
                           int32_t *status, hipStream_t s);
 hipError_t launch_stamp(int32_t *stamp, int64_t n_images, const int32_t *ids, int64_t n, int32_t now, int32_t *status,
                         hipStream_t s, const int32_t *n_dev = nullptr);
-hipError_t launch_accum_plan(const GroupProblem &img, const AccumPlan &plan, const int32_t *occ_view,
-                             const int32_t *img_off, const int32_t *counts, int32_t M, int32_t ready_cap,
-                             int32_t *n_ready, int32_t *status, hipStream_t s);
+hipError_t launch_accum_plan(const GroupBatch &gb, const AccumPlan &plan, const int32_t *occ_view, const int32_t *img_off,
+                             const int32_t *counts, int32_t M, int32_t ready_cap, int32_t *n_ready, int32_t *status,
+                             hipStream_t s);
 
 hipError_t launch_gather_pool(const gear_config &cfg, const gear_batch &b, const gear_tables &t,
                               const void *dfv_cache, void *x, hipStream_t s);
-
-hipError_t launch_cast_weights(int count, const float *const *w, const int *rows, const int *cols, int dtype,
-                               void *const *wc, void *const *wct, const int32_t *status, hipStream_t s);
 
 enum GemmEpilogue {
   EPI_BIAS_RELU = 0,  // out(T)   = max(acc + bias[n], 0)
@@ -226,9 +271,6 @@ hipError_t launch_gemm_nt(int dtype, const void *A, const void *B, int M, int N,
                           const float *bias, const void *aux, void *out, int split, float *colpart,
                           uint8_t *relu_bits, const int32_t *status, hipStream_t s, bool coarse = false);
 int gemm_nt_colsum_parts(int dtype, int M, int N, int K, bool coarse);
-// dst[j] -= lr * sum_p partial[p][j], p ascending in a fixed two-level shape
-hipError_t launch_partial_sgd(const float *partial, int P, int H, float *dst, const Optim &opt, const Moments &mom,
-                              const int32_t *status, hipStream_t s);
 // partial_i[z][M_i x N_i] = sum over the z-th of `splits` ranges of the K rows of A_i[K x M_i]^T * B_i[K x N_i], for
 // all problems in one launch (operands M-/N-contiguous).  k_dev (may be NULL): device word holding the real
 // contraction length, at most K; it is then split into ranges on the device.
@@ -240,15 +282,29 @@ struct TnProblem {
 hipError_t launch_gemm_tn(int dtype, const TnProblem *p, int count, int K, int splits, const int32_t *status,
                           hipStream_t s, const int32_t *k_dev = nullptr);
 int gemm_tn_splits(int dtype, const TnProblem *p, int count, int K);      // ranges to ask for (looks at M and N only)
-// w_i <- update(w_i, sum_z partial_i[z]) for the results of such a launch, in one launch
+// w_i <- update(w_i, sum_z partial_i[z]) for the results of such a launch
 struct SplitkProblem {
   const float *partial;
   float *w;
   Moments mom;
   int64_t count;
 };
-hipError_t launch_splitk_sgd(const SplitkProblem *p, int count, int splits, const Optim &opt, const int32_t *status,
-                             hipStream_t s);
+// dst[j] <- update(dst[j], sum_p partial[p][j]), p < parts and j < width, in a fixed two-level shape
+struct ColumnSum {
+  const float *partial;
+  float *dst;
+  Moments mom;
+  int parts, width;
+};
+struct LossSum {   // *loss = (sum of the partial sums) / B; parts = 0: not wanted
+  const float *partial;
+  float *loss;
+  int parts, B;
+};
+constexpr int kMaxColumnSums = GEAR_MAX_LAYERS + 2;
+// all of that in one launch
+hipError_t launch_param_update(const SplitkProblem *p, int count, int splits, const ColumnSum *c, int n_columns,
+                               const LossSum &loss, const Optim &opt, const int32_t *status, hipStream_t s);
 // the same products on tiles of moderate size (gemm_tile.hip)
 hipError_t launch_gemm_nt_tile(int dtype, const void *A, const void *B, int M, int N, int K, int epilogue,
                                const float *bias, const void *aux, void *out, int split, float *colpart,
@@ -261,21 +317,33 @@ int tn_tile_splits(int dtype, const TnProblem *p, int count, int K);
 hipError_t launch_logit_loss(int dtype, const void *h, const void *wc_last, const float *bias_last, const float *label,
                              int B, int H, float *logits, float *dz, void *delta, float *partials,
                              const int32_t *status, hipStream_t s);
-hipError_t launch_logit_finish(float *partials, int B, int H, float *w_last, float *bias_last, float *bias_hidden,
-                               float *loss, const Optim &opt, const Moments &mom_w_last, const Moments &mom_bias_last,
-                               const Moments &mom_bias_hidden, const int32_t *status, hipStream_t s);
-size_t logit_partial_floats(int H);
+// where launch_logit_loss leaves its sums, one row per workgroup
+struct LogitSums {
+  const float *w, *delta, *bias, *loss;   // [parts x H], [parts x H], [parts], [parts]
+  int parts;
+};
+LogitSums logit_sums(const float *partials, int B, int H);
+size_t logit_partial_floats(int H, int B);
 
-hipError_t launch_embedding_update(const gear_config &cfg, const GroupProblem &users, const GroupProblem &urls,
-                                   const float *dx_emb, void *user_emb, void *url_emb, float *partials,
-                                   const Optim &opt, const Moments &mom_user, const Moments &mom_url,
+hipError_t launch_embedding_chunks(const gear_config &cfg, const GroupProblem &users, const GroupProblem &urls, int nnz,
+                                   const AccumPlan &plan, const float *dx, void *user_emb, void *url_emb, float *partials,
+                                   const Optim &opt, const Moments &mom_user, const Moments &mom_url, int32_t *counts,
                                    const int32_t *status, hipStream_t s);
+hipError_t launch_embedding_spans(const gear_config &cfg, const GroupProblem &users, const GroupProblem &urls, void *user_emb,
+                                  void *url_emb, float *partials, const Optim &opt, const Moments &mom_user,
+                                  const Moments &mom_url, const int32_t *status, hipStream_t s);
 size_t embedding_partial_floats(const gear_config &cfg);
 
+struct EmbeddingFinish {   // what is left of an embedding update after launch_embedding_chunks
+  const GroupProblem *users, *urls;
+  void *user_emb, *url_emb;
+  float *partials;
+  Optim opt;
+  Moments mom_user, mom_url;
+};
 hipError_t launch_accumulate(const gear_config &cfg, const GroupProblem &img, const AccumPlan &plan,
                              const void *dx_dfv, float *grad_accum, int32_t M, int32_t *ready_ids,
-                             float *ready_grads, const int32_t *status, hipStream_t s);
-hipError_t launch_count_update(const GroupProblem &img, int32_t *counts, const int32_t *status, hipStream_t s);
+                             float *ready_grads, const EmbeddingFinish *emb, const int32_t *status, hipStream_t s);
 
 // n_dev (may be NULL): device word holding the real row count, at most n
 hipError_t launch_refresh(int dtype, void *dfv_cache, int64_t n_images, int dim, const int32_t *ids,

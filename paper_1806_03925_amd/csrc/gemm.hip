@@ -457,58 +457,6 @@ k_gemm_tn_dma_batch(TnBatchArgs args, int K, int k_chunk, const int32_t *__restr
               tile - args.first_tile[which], lds);
 }
 
-// W <- update(W, sum_z partial[z]), z ascending; a thread owns four consecutive elements (count is a
-// multiple of 4 because layer widths are multiples of 8) and keeps eight partials in flight
-__device__ __forceinline__ void splitk_sgd_at(const float *__restrict__ partial, int splits, int64_t count,
-                                              float *__restrict__ w, const Optim &opt, const Moments &mom, int64_t i) {
-  if (i >= count) return;
-  float4 g = make_float4(0.f, 0.f, 0.f, 0.f);
-  int z = 0;
-  for (; z + 8 <= splits; z += 8) {
-    float4 v[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) v[k] = *reinterpret_cast<const float4 *>(partial + (size_t)(z + k) * count + i);
-#pragma unroll
-    for (int k = 0; k < 8; ++k) g.x += v[k].x, g.y += v[k].y, g.z += v[k].z, g.w += v[k].w;
-  }
-  for (; z < splits; ++z) {
-    const float4 v = *reinterpret_cast<const float4 *>(partial + (size_t)z * count + i);
-    g.x += v.x, g.y += v.y, g.z += v.z, g.w += v.w;
-  }
-  float4 cur = *reinterpret_cast<float4 *>(w + i);
-  if (!opt.adam) {
-    cur.x -= opt.lr * g.x, cur.y -= opt.lr * g.y, cur.z -= opt.lr * g.z, cur.w -= opt.lr * g.w;
-  } else {
-    float4 m = *reinterpret_cast<float4 *>(mom.m + i), v = *reinterpret_cast<float4 *>(mom.v + i);
-    cur.x = optim_apply(opt, cur.x, g.x, &m.x, &v.x);
-    cur.y = optim_apply(opt, cur.y, g.y, &m.y, &v.y);
-    cur.z = optim_apply(opt, cur.z, g.z, &m.z, &v.z);
-    cur.w = optim_apply(opt, cur.w, g.w, &m.w, &v.w);
-    *reinterpret_cast<float4 *>(mom.m + i) = m;
-    *reinterpret_cast<float4 *>(mom.v + i) = v;
-  }
-  *reinterpret_cast<float4 *>(w + i) = cur;
-}
-
-// one launch for the results of all layers: a workgroup belongs to one of them
-struct SplitkBatchArgs {
-  int count;
-  SplitkProblem p[GEAR_MAX_LAYERS];
-  int first_block[GEAR_MAX_LAYERS];
-};
-
-__global__ void __launch_bounds__(256) k_splitk_sgd_batch(SplitkBatchArgs args, int splits, Optim opt,
-                                                          const int32_t *__restrict__ status) {
-  if (*status != 0) return;
-  int which = 0;
-  for (int i = 1; i < args.count; ++i)
-    if ((int)blockIdx.x >= args.first_block[i]) which = i;
-  const SplitkProblem &q = args.p[which];
-  splitk_sgd_at(q.partial, splits, q.count, q.w, opt, q.mom,
-                ((int64_t)(blockIdx.x - args.first_block[which]) * blockDim.x + threadIdx.x) * 4);
-}
-
-
 // Which of the two bf16 NT kernels a product takes.  The 256 x 256 tiles of the kernel above move the fewest bytes
 // per product, but a CU holds one: below one tile per CU the smaller tiles of gemm_tile.hip win.
 bool nt_dma(int dtype, int M, int N, int K, bool narrow) {
@@ -592,22 +540,6 @@ hipError_t launch_gemm_tn(int dtype, const TnProblem *p, int count, int K, int s
   }
   const int kc = ((((K + splits - 1) / splits) + DK - 1) / DK) * DK;
   hipLaunchKernelGGL(k_gemm_tn_dma_batch, dim3(args.tiles * splits), dim3(DTHREADS), 0, s, args, K, kc, status);
-  return hipGetLastError();
-}
-
-hipError_t launch_splitk_sgd(const SplitkProblem *p, int count, int splits, const Optim &opt, const int32_t *status,
-                             hipStream_t s) {
-  if (count < 1 || count > GEAR_MAX_LAYERS || splits < 1) return hipErrorInvalidValue;
-  SplitkBatchArgs args;
-  args.count = count;
-  int blocks = 0;
-  for (int i = 0; i < GEAR_MAX_LAYERS; ++i) {
-    args.p[i] = i < count ? p[i] : SplitkProblem{nullptr, nullptr, Moments{nullptr, nullptr}, 0};
-    args.first_block[i] = blocks;
-    if (i < count) blocks += (int)((p[i].count / 4 + 255) / 256);
-  }
-  if (blocks == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_splitk_sgd_batch, dim3(blocks), dim3(256), 0, s, args, splits, opt, status);
   return hipGetLastError();
 }
 

@@ -1,50 +1,10 @@
-// The parts of the Sparse-Part MLP that are not matrix products: operand copies of the weights,
-// the logit layer with the loss and its derivative, bias gradients and the logit layer's weight
+// The parts of the Sparse-Part MLP that are not matrix products: the logit layer with the loss and its derivative, bias gradients and the logit layer's weight
 // gradient, each followed by its SGD update (Section 3, step 4: forward to the loss,
 // back-propagation on the Sparse Part, gradients applied to the Sparse Part's parameters).
 #include "gear_internal.hpp"
 
 namespace gear {
 namespace {
-
-// wc = W as MLP operands [rows x cols], wct = its transpose [cols x rows]; both from the fp32 master.
-// One launch serves all layers: a workgroup owns a 32 x 32 tile of one of them.
-struct CastArgs {
-  int count;
-  const float *w[GEAR_MAX_LAYERS];
-  void *wc[GEAR_MAX_LAYERS], *wct[GEAR_MAX_LAYERS];
-  int rows[GEAR_MAX_LAYERS], cols[GEAR_MAX_LAYERS], first_block[GEAR_MAX_LAYERS];
-};
-
-template <typename T>
-__global__ void __launch_bounds__(256) k_cast_weights(CastArgs args, const int32_t *__restrict__ status) {
-  if (*status != 0) return;
-  __shared__ float tile[32][33];
-  int which = 0;
-  for (int i = 1; i < args.count; ++i)
-    if ((int)blockIdx.x >= args.first_block[i]) which = i;
-  const int rows = args.rows[which], cols = args.cols[which];
-  const float *__restrict__ w = args.w[which];
-  T *__restrict__ wc = static_cast<T *>(args.wc[which]);
-  T *__restrict__ wct = static_cast<T *>(args.wct[which]);
-  const int local = blockIdx.x - args.first_block[which], col_tiles = (cols + 31) / 32;
-  const int c0 = (local % col_tiles) * 32, r0 = (local / col_tiles) * 32;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8
-  for (int rr = ty; rr < 32; rr += 8) {
-    const int r = r0 + rr, c = c0 + tx;
-    float v = 0.0f;
-    if (r < rows && c < cols) {
-      v = w[(size_t)r * cols + c];
-      wc[(size_t)r * cols + c] = from_f32<T>(v);
-    }
-    tile[rr][tx] = v;
-  }
-  __syncthreads();
-  for (int cc = ty; cc < 32; cc += 8) {
-    const int c = c0 + cc, r = r0 + tx;
-    if (r < rows && c < cols) wct[(size_t)c * rows + r] = from_f32<T>(tile[tx][cc]);
-  }
-}
 
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
@@ -226,118 +186,23 @@ k_logit_loss(const T *__restrict__ h, const T *__restrict__ w, const float *__re
   }
 }
 
-// loss = (sum of the workgroups' partial sums) / B, by one wavefront, in a fixed shape
-__device__ __forceinline__ void loss_final(const float *__restrict__ loss_partial, int n, int B,
-                                           float *__restrict__ loss) {
-  float part[kLossBlocks / kWave];
-#pragma unroll
-  for (int k = 0; k < kLossBlocks / kWave; ++k) {
-    const int i = threadIdx.x + k * kWave;
-    part[k] = i < n ? loss_partial[i] : 0.0f;
-  }
-  float v = 0.0f;
-#pragma unroll
-  for (int k = 0; k < kLossBlocks / kWave; ++k) v += part[k];
-  v = wave_sum(v);
-  if (threadIdx.x == 0) *loss = v / (float)B;
-}
-
-// dst[j] -= lr * sum_p partial[p][j].  Eight columns per workgroup and 32 row lanes, each adding
-// every 32nd partial in order (eight loads in flight); then the 32 lanes are added in order.
-__device__ __forceinline__ void partial_sgd(const float *__restrict__ partial, int P, int H, float *__restrict__ dst,
-                                            const Optim &opt, const Moments &mom, int block) {
-  __shared__ float s[32][8];
-  const int c = threadIdx.x & 7, g = threadIdx.x >> 3;
-  const int j = block * 8 + c;
-  float acc = 0.0f;
-  if (j < H) {
-    int p = g;
-    for (; p + 32 * 7 < P; p += 32 * 8) {
-      float v[8];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) v[i] = partial[(size_t)(p + 32 * i) * H + j];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) acc += v[i];
-    }
-    for (; p < P; p += 32) acc += partial[(size_t)p * H + j];
-  }
-  s[g][c] = acc;
-  __syncthreads();
-  if (g == 0 && j < H) {
-    float t = 0.0f;
-#pragma unroll
-    for (int k = 0; k < 32; ++k) t += s[k][c];
-    dst[j] = optim_apply(opt, dst[j], t, mom.m + j, mom.v + j);
-  }
-}
-
-__global__ void __launch_bounds__(256) k_partial_sgd(const float *__restrict__ partial, int P, int H,
-                                                     float *__restrict__ dst, Optim opt, Moments mom,
-                                                     const int32_t *__restrict__ status) {
-  if (*status != 0) return;
-  partial_sgd(partial, P, H, dst, opt, mom, blockIdx.x);
-}
-
-// Everything that follows k_logit_loss in one launch; blockIdx.y picks the job: 0 the logit layer's
-// weights, 1 the last hidden layer's bias, 2 the logit bias, 3 the loss.
-__global__ void __launch_bounds__(256)
-k_logit_finish(const float *__restrict__ part_w, const float *__restrict__ part_d, const float *__restrict__ part_b,
-               const float *__restrict__ part_loss, int P, int H, int B, float *__restrict__ w_last,
-               float *__restrict__ bias_hidden, float *__restrict__ bias_last, float *__restrict__ loss, Optim opt,
-               Moments mom_w, Moments mom_bh, Moments mom_bl, const int32_t *__restrict__ status) {
-  if (*status != 0) return;
-  if (blockIdx.y == 0) {
-    partial_sgd(part_w, P, H, w_last, opt, mom_w, blockIdx.x);
-  } else if (blockIdx.y == 1) {
-    partial_sgd(part_d, P, H, bias_hidden, opt, mom_bh, blockIdx.x);
-  } else if (blockIdx.x == 0) {
-    if (blockIdx.y == 2)
-      partial_sgd(part_b, P, 1, bias_last, opt, mom_bl, 0);
-    else if (threadIdx.x < kWave)
-      loss_final(part_loss, P, B, loss);
-  }
-}
-
 }  // namespace
-
-hipError_t launch_cast_weights(int count, const float *const *w, const int *rows, const int *cols, int dtype,
-                               void *const *wc, void *const *wct, const int32_t *status, hipStream_t s) {
-  if (count < 1 || count > GEAR_MAX_LAYERS) return hipErrorInvalidValue;
-  CastArgs args;
-  args.count = count;
-  int blocks = 0;
-  for (int i = 0; i < GEAR_MAX_LAYERS; ++i) {
-    const bool in = i < count;
-    args.w[i] = in ? w[i] : nullptr;
-    args.wc[i] = in ? wc[i] : nullptr;
-    args.wct[i] = in ? wct[i] : nullptr;
-    args.rows[i] = in ? rows[i] : 0;
-    args.cols[i] = in ? cols[i] : 0;
-    args.first_block[i] = blocks;
-    if (in) blocks += ((cols[i] + 31) / 32) * ((rows[i] + 31) / 32);
-  }
-  if (blocks == 0) return hipSuccess;
-  if (dtype == GEAR_BF16)
-    hipLaunchKernelGGL(k_cast_weights<bf16_t>, dim3(blocks), dim3(256), 0, s, args, status);
-  else
-    hipLaunchKernelGGL(k_cast_weights<float>, dim3(blocks), dim3(256), 0, s, args, status);
-  return hipGetLastError();
-}
 
 int logit_blocks(int B) {
   int blocks = (B + 31) / 32;
   return blocks < 1 ? 1 : (blocks > kLossBlocks ? kLossBlocks : blocks);
 }
 
-// Forward logit + loss + delta of the last hidden layer, then SGD on the logit layer's weight and bias.
+// Forward logit + loss + delta of the last hidden layer; leaves the sums that launch_param_update applies.
 hipError_t launch_logit_loss(int dtype, const void *h, const void *wc_last, const float *bias_last, const float *label,
                              int B, int H, float *logits, float *dz, void *delta, float *partials,
                              const int32_t *status, hipStream_t s) {
   if (B <= 0) return hipSuccess;
   const int blocks = logit_blocks(B);
   const int rows_per_block = (B + blocks - 1) / blocks;
-  float *part_w = partials, *part_d = part_w + (size_t)kLossBlocks * H, *part_b = part_d + (size_t)kLossBlocks * H,
-        *part_loss = part_b + kLossBlocks;
+  const LogitSums sums = logit_sums(partials, B, H);
+  float *part_w = partials, *part_d = const_cast<float *>(sums.delta), *part_b = const_cast<float *>(sums.bias),
+        *part_loss = const_cast<float *>(sums.loss);
   // lanes per view and 16-byte pieces per lane, from the width of the last hidden layer
   const int n_vec = H / (dtype == GEAR_BF16 ? 8 : 4);
 #define GEAR_LOGIT(T, NV, G)                                                                                        \
@@ -363,27 +228,12 @@ hipError_t launch_logit_loss(int dtype, const void *h, const void *wc_last, cons
   return hipGetLastError();
 }
 
-// The sums the launch above left in `partials`: the loss, and SGD on the logit layer's weights, its
-// bias and the bias of the last hidden layer.  Nothing later in a step reads what this writes.
-hipError_t launch_logit_finish(float *partials, int B, int H, float *w_last, float *bias_last, float *bias_hidden,
-                               float *loss, const Optim &opt, const Moments &mom_w_last, const Moments &mom_bias_last,
-                               const Moments &mom_bias_hidden, const int32_t *status, hipStream_t s) {
-  if (B <= 0) return hipSuccess;
+LogitSums logit_sums(const float *partials, int B, int H) {
   const int blocks = logit_blocks(B);
-  float *part_w = partials, *part_d = part_w + (size_t)kLossBlocks * H, *part_b = part_d + (size_t)kLossBlocks * H,
-        *part_loss = part_b + kLossBlocks;
-  hipLaunchKernelGGL(k_logit_finish, dim3((H + 7) / 8, 4), dim3(256), 0, s, part_w, part_d, part_b, part_loss, blocks,
-                     H, B, w_last, bias_hidden, bias_last, loss, opt, mom_w_last, mom_bias_hidden, mom_bias_last, status);
-  return hipGetLastError();
+  const float *d = partials + (size_t)blocks * H, *b = d + (size_t)blocks * H;
+  return LogitSums{partials, d, b, b + blocks, blocks};
 }
 
-size_t logit_partial_floats(int H) { return 2 * (size_t)kLossBlocks * H + 2 * (size_t)kLossBlocks; }
-
-hipError_t launch_partial_sgd(const float *partial, int P, int H, float *dst, const Optim &opt, const Moments &mom,
-                              const int32_t *status, hipStream_t s) {
-  if (P <= 0 || H <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_partial_sgd, dim3((H + 7) / 8), dim3(256), 0, s, partial, P, H, dst, opt, mom, status);
-  return hipGetLastError();
-}
+size_t logit_partial_floats(int H, int B) { return 2 * (size_t)logit_blocks(B) * (H + 1); }
 
 }  // namespace gear

@@ -1,61 +1,100 @@
-// Step prologue: reset the per-step outputs and check what only the device can see.
-//
-// A page view is a user id, a URL bucket and a list of image ids (Section 1, Table 1).  Every id
-// later indexes a table, so a bad id must be caught before any kernel dereferences it: the first
-// violation found is written to the status word and every later kernel of the step returns at
-// once when that word is not zero.
+// Step prologue, one launch: reset the per-step outputs, clear the words that the sorts count in, and make the operand
+// copies of the weights.
 #include "gear_internal.hpp"
 
 namespace gear {
 namespace {
 
-__global__ void k_begin(int32_t *status, int32_t *n_ready, float *loss) {
-  if (threadIdx.x == 0) {
+// wc = W as MLP operands [rows x cols], wct = its transpose [cols x rows]; both from the fp32 master.
+// One launch serves all layers: a workgroup owns a 32 x 32 tile of one of them; those behind the tiles clear words.
+struct BeginArgs {
+  int count, cast_blocks;
+  CastJob job[GEAR_MAX_LAYERS];
+  int first_block[GEAR_MAX_LAYERS];
+  ZeroList zero;
+};
+
+__device__ __forceinline__ void clear_words(const ZeroList &zero, int64_t at, int64_t stride) {
+  for (int k = 0; k < zero.count; ++k)
+    for (int64_t i = at; i < zero.words[k]; i += stride) zero.p[k][i] = 0u;
+}
+
+__global__ void __launch_bounds__(256) k_clear(ZeroList zero) {
+  clear_words(zero, (int64_t)blockIdx.x * 256 + threadIdx.x, (int64_t)gridDim.x * 256);
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256) k_begin(BeginArgs args, int32_t *status, int32_t *n_ready, float *loss) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
     *status = 0;
     *n_ready = 0;
     *loss = 0.0f;
   }
-}
-
-__device__ __forceinline__ void flag(int32_t *status, int code) { atomicCAS(status, 0, code); }
-
-// One thread per view (and per occurrence).  Also expands the CSR offsets into occ_view[j] = the
-// view that owns occurrence j, which the accumulation uses to find dLoss/dx of an occurrence.
-__global__ void __launch_bounds__(256) k_validate(int B, int nnz, const int32_t *user_id, const int32_t *url_id,
-                                                  const int32_t *img_off, const int32_t *img_id, int64_t n_users,
-                                                  int64_t n_urls, int64_t n_images, int32_t *occ_view,
-                                                  int32_t *status) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < B) {
-    const int32_t u = user_id[i], v = url_id[i];
-    if (u < 0 || (int64_t)u >= n_users || v < 0 || (int64_t)v >= n_urls) flag(status, GEAR_ERR_RANGE);
-    const int32_t lo = img_off[i], hi = img_off[i + 1];
-    const bool ok = lo >= 0 && lo <= hi && hi <= nnz;
-    if (!ok) flag(status, GEAR_ERR_RANGE);
-    if (i == 0 && lo != 0) flag(status, GEAR_ERR_RANGE);
-    if (i == B - 1 && hi != nnz) flag(status, GEAR_ERR_RANGE);
-    if (ok)
-      for (int j = lo; j < hi; ++j) occ_view[j] = i;
+  if ((int)blockIdx.x >= args.cast_blocks) {
+    clear_words(args.zero, (int64_t)(blockIdx.x - args.cast_blocks) * 256 + threadIdx.x,
+                (int64_t)(gridDim.x - args.cast_blocks) * 256);
+    return;
   }
-  if (i < nnz) {
-    const int32_t g = img_id[i];
-    if (g < 0 || (int64_t)g >= n_images) flag(status, GEAR_ERR_RANGE);
+  __shared__ float tile[32][33];
+  int which = 0;
+  for (int i = 1; i < args.count; ++i)
+    if ((int)blockIdx.x >= args.first_block[i]) which = i;
+  const int rows = args.job[which].rows, cols = args.job[which].cols;
+  const float *__restrict__ w = args.job[which].w;
+  T *__restrict__ wc = static_cast<T *>(args.job[which].wc);
+  T *__restrict__ wct = static_cast<T *>(args.job[which].wct);
+  const int local = blockIdx.x - args.first_block[which], col_tiles = (cols + 31) / 32;
+  const int c0 = (local % col_tiles) * 32, r0 = (local / col_tiles) * 32;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8
+#pragma unroll
+  for (int rr = ty; rr < 32; rr += 8) {
+    const int r = r0 + rr, c = c0 + tx;
+    float v = 0.0f;
+    if (r < rows && c < cols) {
+      v = w[(size_t)r * cols + c];
+      wc[(size_t)r * cols + c] = from_f32<T>(v);
+    }
+    tile[rr][tx] = v;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int cc = ty; cc < 32; cc += 8) {
+    const int c = c0 + cc, r = r0 + tx;
+    if (r < rows && c < cols) wct[(size_t)c * rows + r] = from_f32<T>(tile[tx][cc]);
   }
 }
 
 }  // namespace
 
-hipError_t launch_begin(int32_t *status, int32_t *n_ready, float *loss, hipStream_t s) {
-  hipLaunchKernelGGL(k_begin, dim3(1), dim3(64), 0, s, status, n_ready, loss);
+static int clear_blocks(const ZeroList &zero) {   // four words a thread, then more
+  int64_t words = 0;
+  for (int k = 0; k < zero.count; ++k) words += zero.words[k];
+  const int64_t blocks = (words + 1023) / 1024;
+  return blocks > 256 ? 256 : blocks < 1 ? 1 : (int)blocks;
+}
+
+hipError_t launch_clear(const ZeroList &zero, hipStream_t s) {
+  hipLaunchKernelGGL(k_clear, dim3(clear_blocks(zero)), dim3(256), 0, s, zero);
   return hipGetLastError();
 }
 
-hipError_t launch_validate(const gear_config &cfg, const gear_batch &b, int32_t *occ_view, int32_t *status,
-                           hipStream_t s) {
-  const int n = b.B > b.nnz ? b.B : b.nnz;
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_validate, dim3((n + 255) / 256), dim3(256), 0, s, b.B, b.nnz, b.user_id, b.url_id, b.img_off,
-                     b.img_id, cfg.n_users, cfg.n_urls, cfg.n_images, occ_view, status);
+hipError_t launch_begin(int32_t *status, int32_t *n_ready, float *loss, const ZeroList &zero, int dtype, const CastJob *jobs,
+                        int count, hipStream_t s) {
+  if (count < 0 || count > GEAR_MAX_LAYERS) return hipErrorInvalidValue;
+  BeginArgs args;
+  args.count = count;
+  args.zero = zero;
+  args.cast_blocks = 0;
+  for (int i = 0; i < GEAR_MAX_LAYERS; ++i) {
+    args.job[i] = i < count ? jobs[i] : CastJob{nullptr, nullptr, nullptr, 0, 0};
+    args.first_block[i] = args.cast_blocks;
+    if (i < count) args.cast_blocks += ((jobs[i].cols + 31) / 32) * ((jobs[i].rows + 31) / 32);
+  }
+  const dim3 grid((unsigned)(args.cast_blocks + clear_blocks(zero)));
+  if (dtype == GEAR_BF16)
+    hipLaunchKernelGGL(k_begin<bf16_t>, grid, dim3(256), 0, s, args, status, n_ready, loss);
+  else
+    hipLaunchKernelGGL(k_begin<float>, grid, dim3(256), 0, s, args, status, n_ready, loss);
   return hipGetLastError();
 }
 

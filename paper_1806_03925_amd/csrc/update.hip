@@ -11,25 +11,12 @@
 // those partials in chunk order and writes the row.  No atomics anywhere.
 //
 // A worker is d/4 lanes, each owning one float4 column group of the row.
-#include "gear_internal.hpp"
+#include "embedding_common.hpp"
 
 #include <type_traits>
 
 namespace gear {
 namespace {
-
-constexpr int kChunk = 16;
-
-struct Table {
-  const int32_t *keys;   // sorted ids
-  const int32_t *perm;   // batch position of each sorted position
-  int n;
-  void *rows;            // embedding table
-  int col0;              // first column of this table's slice inside a dx row
-  float *part_first;     // [chunks x d] partial of a run that began in an earlier chunk
-  float *part_last;      // [chunks x d] partial of a run that begins here and goes on
-  Moments mom;           // Adam: fp32 moment tables of the same shape as `rows` (only touched rows move)
-};
 
 // one float4 column group of a row: row <- update(row, g); mrow / vrow are the row's moments (Adam)
 template <typename ET>
@@ -74,10 +61,21 @@ __device__ __forceinline__ void add4(float4 &a, const float4 &b) {
 // level 1: one worker per chunk of sorted positions
 template <typename ET>
 __global__ void __launch_bounds__(256)
-k_embedding_chunks(Table users, Table urls, const float *__restrict__ dx, int F, int d, int lanes_per_worker, Optim opt,
-                   const int32_t *__restrict__ status) {
+k_embedding_chunks(EmbeddingTable users, EmbeddingTable urls, const float *__restrict__ dx, int F, int d, int lanes_per_worker, Optim opt,
+                   AccumPlan plan, int32_t *__restrict__ counts, const int32_t *__restrict__ status) {
   if (*status != 0) return;
-  const Table &t = blockIdx.y == 1 ? urls : users;
+  if (blockIdx.y == 2) {
+    // counts[image] += occurrences of the image in this step (Section 1, third point), by the image's first unit.
+    // Done here and not where the unit is summed: beside a product these scattered words cost nothing, in
+    // k_accumulate, which is bound by memory, 7 us of a step of 65 536 views.
+    const int n = *plan.n_units;
+    for (int u = blockIdx.x * blockDim.x + threadIdx.x; u < n; u += gridDim.x * blockDim.x) {
+      const UnitDesc d = plan.units[u];
+      if (d.q0 == d.s0) counts[d.image] = d.collected;
+    }
+    return;
+  }
+  const EmbeddingTable &t = blockIdx.y == 1 ? urls : users;
   const int tid = blockIdx.x * blockDim.x + threadIdx.x;
   const int chunk = tid / lanes_per_worker, c4 = tid % lanes_per_worker;
   const int q_begin = chunk * kChunk;
@@ -156,54 +154,20 @@ k_embedding_chunks(Table users, Table urls, const float *__restrict__ dx, int F,
     }
 }
 
-constexpr int kSpanInFlight = 32;   // partials of a long run that one lane has in flight
-
-// level 2: one wavefront per chunk; if a border-crossing run starts in this chunk the wave adds
-// the run's partials in chunk order (lane = column) and writes the row
+// level 2 in a launch of its own
 template <typename ET>
 __global__ void __launch_bounds__(256)
-k_embedding_spans(Table users, Table urls, const int32_t *__restrict__ user_pos_seg,
-                  const int32_t *__restrict__ user_segoff, const int32_t *__restrict__ url_pos_seg,
-                  const int32_t *__restrict__ url_segoff, int d, Optim opt, const int32_t *__restrict__ status) {
+k_embedding_spans(EmbeddingTable users, EmbeddingTable urls, int d, Optim opt, const int32_t *__restrict__ status) {
   if (*status != 0) return;
-  const bool second = blockIdx.y == 1;
-  const Table &t = second ? urls : users;
-  const int32_t *pos_seg = second ? url_pos_seg : user_pos_seg;
-  const int32_t *segoff = second ? url_segoff : user_segoff;
-  const int lane = threadIdx.x & 63;
-  const int chunk = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
-  const int q_begin = chunk * kChunk;
-  if (q_begin >= t.n) return;
-  const int q_last = min(t.n, q_begin + kChunk) - 1;
-  if (q_last + 1 >= t.n) return;              // nothing after this chunk
-  const int key = t.keys[q_last];
-  if (t.keys[q_last + 1] != key) return;      // the last run ends inside this chunk
-  const int seg = pos_seg[q_last];
-  const int s0 = segoff[seg], s1 = segoff[seg + 1];
-  if (s0 < q_begin) return;                   // the run began in an earlier chunk: not ours
-  const int k_last = (s1 - 1) / kChunk;
-  for (int c = lane; c < d; c += kWave) {
-    float sum = t.part_last[(size_t)chunk * d + c];
-    int k = chunk + 1;
-    for (; k + kSpanInFlight <= k_last + 1; k += kSpanInFlight) {   // added in order, requested together
-      float v[kSpanInFlight];
-#pragma unroll
-      for (int i = 0; i < kSpanInFlight; ++i) v[i] = t.part_first[(size_t)(k + i) * d + c];
-#pragma unroll
-      for (int i = 0; i < kSpanInFlight; ++i) sum += v[i];
-    }
-    for (; k <= k_last; ++k) sum += t.part_first[(size_t)k * d + c];
-    const size_t at = (size_t)key * d + c;
-    ET *cell = static_cast<ET *>(t.rows) + at;
-    *cell = from_f32<ET>(optim_apply(opt, to_f32<ET>(*cell), sum, t.mom.m + at, t.mom.v + at));
-  }
+  embedding_span<ET, 32>(blockIdx.y == 1 ? urls : users, blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave, d, opt);
 }
 
 }  // namespace
 
-hipError_t launch_embedding_update(const gear_config &cfg, const GroupProblem &users, const GroupProblem &urls,
-                                   const float *dx, void *user_emb, void *url_emb, float *partials,
-                                   const Optim &opt, const Moments &mom_user, const Moments &mom_url,
+// level 1, and the counters of the images; launch_embedding_spans or launch_accumulate finishes the update
+hipError_t launch_embedding_chunks(const gear_config &cfg, const GroupProblem &users, const GroupProblem &urls, int nnz,
+                                   const AccumPlan &plan, const float *dx, void *user_emb, void *url_emb, float *partials,
+                                   const Optim &opt, const Moments &mom_user, const Moments &mom_url, int32_t *counts,
                                    const int32_t *status, hipStream_t s) {
   const int F = 2 * cfg.emb_dim;  // dx holds the two embedding slots of dLoss/dx only
   const int n = users.n > urls.n ? users.n : urls.n;
@@ -212,21 +176,29 @@ hipError_t launch_embedding_update(const gear_config &cfg, const GroupProblem &u
   int lanes = 1;
   while (lanes < d / 4) lanes <<= 1;  // power of two so that workers do not straddle wavefronts
   const int chunks = (n + kChunk - 1) / kChunk;
-  const size_t per = (size_t)((cfg.max_batch + kChunk - 1) / kChunk) * d;
-  Table tu = {users.sorted_keys, users.perm, users.n, user_emb, 0, partials, partials + per, mom_user};
-  Table tl = {urls.sorted_keys, urls.perm, urls.n, url_emb, d, partials + 2 * per, partials + 3 * per, mom_url};
+  EmbeddingTable tu, tl;
+  embedding_tables(cfg, users, urls, user_emb, url_emb, partials, mom_user, mom_url, &tu, &tl);
   const long long threads = (long long)chunks * lanes;
-  const dim3 grid((unsigned)((threads + 255) / 256), 2);
-  const dim3 grid2((chunks + 3) / 4, 2);
-  if (cfg.emb_dtype == GEAR_BF16) {
-    hipLaunchKernelGGL(k_embedding_chunks<bf16_t>, grid, dim3(256), 0, s, tu, tl, dx, F, d, lanes, opt, status);
-    hipLaunchKernelGGL(k_embedding_spans<bf16_t>, grid2, dim3(256), 0, s, tu, tl, users.pos_seg, users.segoff,
-                       urls.pos_seg, urls.segoff, d, opt, status);
-  } else {
-    hipLaunchKernelGGL(k_embedding_chunks<float>, grid, dim3(256), 0, s, tu, tl, dx, F, d, lanes, opt, status);
-    hipLaunchKernelGGL(k_embedding_spans<float>, grid2, dim3(256), 0, s, tu, tl, users.pos_seg, users.segoff,
-                       urls.pos_seg, urls.segoff, d, opt, status);
-  }
+  const dim3 grid((unsigned)((threads + 255) / 256), nnz > 0 ? 3 : 2);
+  if (cfg.emb_dtype == GEAR_BF16)
+    hipLaunchKernelGGL(k_embedding_chunks<bf16_t>, grid, dim3(256), 0, s, tu, tl, dx, F, d, lanes, opt, plan, counts, status);
+  else
+    hipLaunchKernelGGL(k_embedding_chunks<float>, grid, dim3(256), 0, s, tu, tl, dx, F, d, lanes, opt, plan, counts, status);
+  return hipGetLastError();
+}
+
+hipError_t launch_embedding_spans(const gear_config &cfg, const GroupProblem &users, const GroupProblem &urls, void *user_emb,
+                                  void *url_emb, float *partials, const Optim &opt, const Moments &mom_user,
+                                  const Moments &mom_url, const int32_t *status, hipStream_t s) {
+  const int n = users.n > urls.n ? users.n : urls.n;
+  if (n <= 0) return hipSuccess;
+  EmbeddingTable tu, tl;
+  embedding_tables(cfg, users, urls, user_emb, url_emb, partials, mom_user, mom_url, &tu, &tl);
+  const dim3 grid(((n + kChunk - 1) / kChunk + 3) / 4, 2);
+  if (cfg.emb_dtype == GEAR_BF16)
+    hipLaunchKernelGGL(k_embedding_spans<bf16_t>, grid, dim3(256), 0, s, tu, tl, cfg.emb_dim, opt, status);
+  else
+    hipLaunchKernelGGL(k_embedding_spans<float>, grid, dim3(256), 0, s, tu, tl, cfg.emb_dim, opt, status);
   return hipGetLastError();
 }
 
