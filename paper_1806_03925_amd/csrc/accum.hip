@@ -12,8 +12,6 @@
 // rows added in arrival order (flat CSR order continuing the earlier steps): no float atomics.
 #include "embedding_common.hpp"
 
-#include <string.h>
-
 namespace gear {
 namespace {
 
@@ -88,37 +86,56 @@ __device__ __forceinline__ void add_rows(float (&acc)[Cols<GT>::N], const int32_
   }
 }
 
-// Partials of a long run in flight, in the form that shares k_accumulate's registers: more than eight would cost the units
-// their wavefronts (32 in flight: 138 registers; eight: 59).
-constexpr int kSpanInFlight = 8;
-
-// Embedding sums that k_accumulate's first workgroups finish (blocks per table; none without SPANS).
-struct SpanWork {
-  EmbeddingTable table[2];
-  int blocks, d, bf16;
-  Optim opt;
+// What the launch's first workgroups do of the embedding update: nothing (a divided step has it done), its second level
+// (two streams: level 1 and the image counters are the launch before), or level 1 and the counters (one stream: level 2
+// rides with the parameter update).  Level 1 ahead of the units on two streams held their wavefronts down to three a SIMD
+// beside a product that needs the rest (16 384 views: 187 us a step against 180).
+enum EmbRide { kNoRide, kSpans, kChunks };
+struct RideWork {
+  EmbeddingWork w;
+  int blocks, count_blocks, lanes;   // workgroups per table and for the counters; lanes of a worker of level 1
 };
+struct NoWork {};
 
 // dx: the DFV slot of dLoss/dx, [B x D].  One workgroup per unit, D / Cols<GT>::N threads.
-template <typename GT, bool SPANS>
-__global__ void __launch_bounds__(256)
+// kChunks needs 132 registers where the units alone take 44: three wavefronts a SIMD, which still have 72 KB of rows in
+// flight on a CU, as much as a memory latency asks for.  kSpans has eight partials of a long run in flight: 59 (with 32
+// in flight 138).
+template <typename GT, int RIDE>
+__global__ void __launch_bounds__(256, RIDE == kChunks ? 3 : 1)
 k_accumulate(AccumPlan plan, const GT *__restrict__ dx, int D, float *__restrict__ accum, int M,
-             int32_t *__restrict__ ready_ids, float *__restrict__ ready_grads, SpanWork spans,
+             int32_t *__restrict__ ready_ids, float *__restrict__ ready_grads, std::conditional_t<RIDE == kNoRide, NoWork, RideWork> emb,
              const int32_t *__restrict__ status) {
   if (*status != 0) return;
   int block = blockIdx.x, blocks = gridDim.x;
-  if constexpr (SPANS) {
-    if (block < 2 * spans.blocks) {
-      const int second = block >= spans.blocks ? 1 : 0;
-      const int chunk = (block - second * spans.blocks) * (blockDim.x / kWave) + threadIdx.x / kWave;
-      if (spans.bf16)
-        embedding_span<bf16_t, kSpanInFlight>(spans.table[second], chunk, spans.d, spans.opt);
+  if constexpr (RIDE == kSpans) {
+    if (block < 2 * emb.blocks) {
+      const int second = block >= emb.blocks ? 1 : 0;
+      const int chunk = (block - second * emb.blocks) * (blockDim.x / kWave) + threadIdx.x / kWave;
+      if (emb.w.bf16)
+        embedding_span<bf16_t, 8>(emb.w.table[second], chunk, emb.w.d, emb.w.opt);
       else
-        embedding_span<float, kSpanInFlight>(spans.table[second], chunk, spans.d, spans.opt);
+        embedding_span<float, 8>(emb.w.table[second], chunk, emb.w.d, emb.w.opt);
       return;
     }
-    block -= 2 * spans.blocks;
-    blocks -= 2 * spans.blocks;
+    block -= 2 * emb.blocks;
+    blocks -= 2 * emb.blocks;
+  }
+  if constexpr (RIDE == kChunks) {
+    if (block < 2 * emb.blocks) {
+      const int second = block >= emb.blocks ? 1 : 0;
+      const int tid = (block - second * emb.blocks) * blockDim.x + threadIdx.x;
+      if (emb.w.bf16)
+        embedding_chunk<bf16_t, 8>(emb.w.table[second], tid, emb.w.dx, 2 * emb.w.d, emb.w.d, emb.lanes, emb.w.opt);
+      else
+        embedding_chunk<float, 8>(emb.w.table[second], tid, emb.w.dx, 2 * emb.w.d, emb.w.d, emb.lanes, emb.w.opt);
+      return;
+    }
+    block -= 2 * emb.blocks;
+    if (block < emb.count_blocks)
+      return count_images(plan, emb.w.counts, block * blockDim.x + threadIdx.x, emb.count_blocks * blockDim.x);
+    block -= emb.count_blocks;
+    blocks -= 2 * emb.blocks + emb.count_blocks;
   }
   constexpr int N = Cols<GT>::N;
   const int n_units = *plan.n_units;
@@ -197,37 +214,41 @@ __global__ void __launch_bounds__(256) k_refresh(uint4 *__restrict__ cache, int6
 
 }  // namespace
 
-// With `emb` the launch also finishes the embedding update, in workgroups ahead of the units': on a short step that
-// saves a launch of a handful of busy wavefronts (small: 8 us on one stream).
+// emb (may be NULL): level 1 of its update and the counters, or level 2 if `level2`, ride along
 hipError_t launch_accumulate(const gear_config &cfg, const GroupProblem &img, const AccumPlan &plan,
                              const void *dx_dfv, float *grad_accum, int32_t M, int32_t *ready_ids,
-                             float *ready_grads, const EmbeddingFinish *emb, const int32_t *status, hipStream_t s) {
+                             float *ready_grads, const EmbeddingWork *emb, bool level2, const int32_t *status, hipStream_t s) {
   if (img.n <= 0 && !emb) return hipSuccess;
   const int D = cfg.dfv_dim;
   const int cols = cfg.mlp_dtype == GEAR_BF16 ? 8 : 4;
   int threads = ((D / cols + 63) / 64) * 64;
   if (threads > 256) threads = 256;
   int blocks = img.n < 32768 ? img.n : 32768;
-  SpanWork spans;
-  memset(&spans, 0, sizeof(spans));
+  RideWork work;
   if (emb) {
-    embedding_tables(cfg, *emb->users, *emb->urls, emb->user_emb, emb->url_emb, emb->partials, emb->mom_user, emb->mom_url,
-                     &spans.table[0], &spans.table[1]);
-    const int chunks = (emb->users->n + kChunk - 1) / kChunk, waves = threads / kWave;   // both lists have one id per view
-    spans.blocks = (chunks + waves - 1) / waves;
-    spans.d = cfg.emb_dim;
-    spans.bf16 = cfg.emb_dtype == GEAR_BF16;
-    spans.opt = emb->opt;
-    blocks += 2 * spans.blocks;
+    work.w = *emb;
+    work.lanes = level2 ? kWave : embedding_lanes(emb->d);
+    work.blocks = (int)(((long long)embedding_chunks(*emb) * work.lanes + threads - 1) / threads);
+    work.count_blocks = level2 ? 0 : (img.n + 4 * threads - 1) / (4 * threads);
+    if (work.count_blocks > 256) work.count_blocks = 256;
+    blocks += 2 * work.blocks + work.count_blocks;
   }
-#define GEAR_ACC(T, S)                                                                                                     \
-  hipLaunchKernelGGL((k_accumulate<T, S>), dim3(blocks), dim3(threads), 0, s, plan, (const T *)dx_dfv, D, grad_accum, M, \
-                     ready_ids, ready_grads, spans, status)
+#define GEAR_ACC(T, R, EMB)                                                                                                \
+  hipLaunchKernelGGL((k_accumulate<T, R>), dim3(blocks), dim3(threads), 0, s, plan, (const T *)dx_dfv, D, grad_accum, M, \
+                     ready_ids, ready_grads, EMB, status)
+#define GEAR_ACC_T(T)              \
+  if (!emb)                        \
+    GEAR_ACC(T, kNoRide, NoWork{}); \
+  else if (level2)                 \
+    GEAR_ACC(T, kSpans, work);     \
+  else                             \
+    GEAR_ACC(T, kChunks, work)
   if (cfg.mlp_dtype == GEAR_BF16) {
-    if (emb) GEAR_ACC(bf16_t, true); else GEAR_ACC(bf16_t, false);
+    GEAR_ACC_T(bf16_t);
   } else {
-    if (emb) GEAR_ACC(float, true); else GEAR_ACC(float, false);
+    GEAR_ACC_T(float);
   }
+#undef GEAR_ACC_T
 #undef GEAR_ACC
   return hipGetLastError();
 }

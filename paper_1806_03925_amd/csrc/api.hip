@@ -279,6 +279,12 @@ std::mutex g_side_mutex;
 // and event to let the embedding update run beside it (about 10 us of work on the device)
 constexpr double kSplitDxMacs = 5e9;
 
+// Ids of a batch (users, URLs and images) from which a step uses the helper stream.  Its events cost the host 65 us a step
+// and the device four idle gaps; a shorter step has less than that to hide.  On one stream, the grouping carried by other
+// launches, against two streams: 2 300 ids 53 / 99 us, 15 000 82 / 119, 27 000 106 / 128, 63 000 154 / 178 (the slowest host
+// seen), 65 000 143 .. 152 / 144; from there on 89 000 169 / 153, 106 000 187 / 172, 172 000 198 / 182.
+constexpr long long kOneStreamIds = 49152;
+
 // the helper lane of the current device; nullptr when one of its objects cannot be created (nothing
 // half-made is kept: the next call starts over)
 SideLane *side_lane() {
@@ -531,15 +537,26 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   }
   int32_t *occ_view = (int32_t *)(ws + lay.occ_view);
 
+  // On one stream the launches of the forward pass carry the grouping along where they can (gemm_tile.hip); with two, the
+  // helper stream has it.
+  bool moderate = true;
+  for (int l = 0; l < L - 1; ++l) moderate = moderate && gemm_nt_carries(dt, B, lay.out_dim[l], lay.in_dim[l]);
+  const bool one_stream = out->one_stream != 0 || (moderate && (long long)2 * B + b->nnz < kOneStreamIds);
+  const bool carried = one_stream && moderate;
+
   // grouping of the three id lists and the plan of the per-image accumulation
   GroupBatch gb;
   {
     const int bits[kMaxProblems] = {bits_for(cfg->n_users), bits_for(cfg->n_urls), bits_for(cfg->n_images)};
     int passes = 1;   // the lists share launches: as many passes for all as the widest ids need
     for (int i = 0; i < kMaxProblems; ++i) {
-      const int need = radix_passes(bits[i], lay.g[i].total_words, B > b->nnz ? B : b->nnz);
+      const int need = radix_passes(bits[i], lay.g[i].total_words, carried ? kSideDigitBits : kMaxDigitBits);
       if (need > passes) passes = need;
     }
+    // a pass that is carried costs nothing but its length, and narrow digits make it short: as many as find a launch ahead
+    // of the one that takes the segments
+    const int rides = L < kMaxPasses ? L : kMaxPasses;   // the forward products and the logit layer
+    if (carried && passes < rides) passes = rides;
     gb.count = kMaxProblems;
     gb.p[0] = make_problem(lay, ws, 0, b->user_id, B, cfg->n_users, passes, bits[0]);
     gb.p[1] = make_problem(lay, ws, 1, b->url_id, B, cfg->n_urls, passes, bits[1]);
@@ -553,12 +570,12 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   plan.row_view = (int32_t *)(ws + lay.row_view);
   plan.row_scale = (float *)(ws + lay.row_scale);
   plan.n_units = (int32_t *)(ws + lay.n_units);
-  // What depends only on ids and counters runs on the helper stream while the main stream gathers and
-  // runs the forward pass: the check of the ids, the grouping, the accumulation plan and the counter update.  The
+  const PlanArgs plan_args = {plan, occ_view, b->img_off, counts, M, out->ready_cap, out->n_ready};
+  // Not carried: what depends only on ids and counters (the check of the ids, the grouping, the accumulation plan) runs on
+  // the helper stream while the main stream gathers and runs the forward pass.  The
   // main stream waits for it before the first kernel that changes caller state, so the status word
   // is final by then; until then its kernels write the workspace only, and the gather clamps what it
   // uses as an index.
-  const bool one_stream = out->one_stream != 0;
   SideLane *side = one_stream ? nullptr : side_lane();
   if (!one_stream && !side) return GEAR_ERR_HIP;
   hipStream_t helper = one_stream ? s : side->stream;
@@ -574,7 +591,25 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
     group_zero_list(gb, &zero);
     GEAR_RUN("begin", launch_begin(status, out->n_ready, out->loss, zero, dt, jobs, L, s));
   }
-  GEAR_HIP(lane.fork());
+  if (!carried) GEAR_HIP(lane.fork());
+  // Carried: the links of the grouping in order, each taken by the next launch that can.
+  SideTask task;
+  int link = 0;
+  const int links = carried ? group_passes(gb) + 1 : 0;
+  auto passenger = [&]() -> const SideTask * {
+    if (link >= links) return nullptr;
+    task = side_task(gb, plan_args, link++, status);
+    return &task;
+  };
+  auto links_left = [&]() -> gear_status {   // those that found no launch to ride in
+    for (; link < links; ++link)
+      GEAR_RUN("group_ids", link + 1 < links ? launch_radix_pass(gb, link, status, s) : launch_segments(gb, &plan_args, status, s));
+    return GEAR_OK;
+  };
+#define GEAR_BOARD()                                       \
+  do {                                                     \
+    if (link < links && fail_injected()) return GEAR_ERR_HIP; \
+  } while (0)
   // forward
   void *x = ws + lay.x;
   // the weight-gradient products of the hidden layers
@@ -582,35 +617,42 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   int n_wp = 0;
   for (int l = L - 2; l >= 0; --l)
     wp[n_wp++] = TnProblem{ws + lay.delta[l], l == 0 ? x : ws + lay.h[l - 1], nullptr, lay.out_dim[l], lay.in_dim[l]};
-  GEAR_RUN("gather_pool", launch_gather_pool(*cfg, *b, *t, dfv_cache, x, s));
+  {
+    const CheckTask check = check_task(gb, b->img_off, occ_view, B, b->nnz, status);
+    if (carried && fail_injected()) return GEAR_ERR_HIP;
+    GEAR_RUN("gather_pool", launch_gather_pool(*cfg, *b, *t, dfv_cache, x, s, carried ? &check : nullptr));
+  }
   // A bf16 hidden layer below the last one also leaves the sign bitmap of its activations: the backward pass then
   // reads one bit per unit instead of the activation.
   uint8_t *relu_bits[GEAR_MAX_LAYERS] = {};
   if (dt == GEAR_BF16)
     for (int l = 0; l + 2 < L; ++l) relu_bits[l] = (uint8_t *)(ws + lay.relu_bits[l]);
-  for (int l = 0; l < L - 1; ++l)
+  for (int l = 0; l < L - 1; ++l) {
+    GEAR_BOARD();
     GEAR_RUN(kFwd[l], launch_gemm_nt(dt, l == 0 ? x : ws + lay.h[l - 1], ws + lay.wc[l], B, lay.out_dim[l],
                                      lay.in_dim[l], EPI_BIAS_RELU, t->mlp_params + lay.b_off[l], nullptr,
-                                     ws + lay.h[l], 0, nullptr, relu_bits[l], nullptr, s));
+                                     ws + lay.h[l], 0, nullptr, relu_bits[l], nullptr, s, false, passenger()));
+  }
   // The helper stream's launches are issued after the forward pass's: where the host is not ahead of the
   // device (a caller that waits for every step), the gather then starts as soon as the step does, not
   // after the host has issued the grouping's launches.
-  {
+  if (!carried) {
     hipStream_t s = helper;  // the launches of this block go to the helper stream
-    GEAR_RUN("group_ids", launch_group(gb, b->img_off, occ_view, B, b->nnz, status, s));
-    GEAR_RUN("accum_plan", launch_accum_plan(gb, plan, occ_view, b->img_off, counts, M, out->ready_cap, out->n_ready,
-                                             status, s));
+    GEAR_RUN("group_ids", launch_check(gb, b->img_off, occ_view, B, b->nnz, status, s));
+    for (int pass = 0; pass < group_passes(gb); ++pass) GEAR_RUN("group_ids", launch_radix_pass(gb, pass, status, s));
+    GEAR_RUN("accum_plan", launch_segments(gb, &plan_args, status, s));
+    GEAR_HIP(lane.mark_checked());
   }
-  GEAR_HIP(lane.mark_checked());
 
   float *logits = (float *)(ws + lay.logits), *dz = (float *)(ws + lay.dz);
   // Until its first kernel that changes caller state (the first SGD on a hidden layer's weights), the
   // caller's stream writes the workspace only and need not know whether the ids were in range or the
   // ready list fits.  Just before that kernel the stream waits for the helper's first part, so that the
   // status word is final.
+  GEAR_BOARD();
   GEAR_RUN("logit_loss", launch_logit_loss(dt, ws + lay.h[L - 2], ws + lay.wc[L - 1], t->mlp_params + lay.b_off[L - 1],
                                            b->label, B, lay.in_dim[L - 1], logits, dz, ws + lay.delta[L - 2],
-                                           (float *)(ws + lay.loss_partial), status, s));
+                                           (float *)(ws + lay.loss_partial), status, s, passenger()));
 
   // backward through the hidden layers down to dLoss/dx (all from the pre-step operand copies)
   // Each product that makes the delta of a hidden layer also leaves that layer's bias gradient (column
@@ -618,11 +660,8 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   float *dx_emb = (float *)(ws + lay.dx_emb);
   void *dx_dfv = ws + lay.dx_dfv;
   float *cpart = (float *)(ws + lay.colsum_partial), *wpart = (float *)(ws + lay.wgrad_partial);
-  EmbeddingFinish emb = {&gb.p[0], &gb.p[1], t->user_emb, t->url_emb, (float *)(ws + lay.emb_partial), opt, mom_user, mom_url};
-  auto embedding_chunks = [&](hipStream_t s) {
-    return launch_embedding_chunks(*cfg, gb.p[0], gb.p[1], b->nnz, plan, dx_emb, t->user_emb, t->url_emb, emb.partials, opt,
-                                   mom_user, mom_url, counts, status, s);
-  };
+  const EmbeddingWork emb = embedding_work(*cfg, gb.p[0], gb.p[1], dx_emb, t->user_emb, t->url_emb, (float *)(ws + lay.emb_partial),
+                                           opt, mom_user, mom_url, plan, counts);
   // Small sums whose results nothing in the step reads: the loss, the logit layer and the biases (column sums of deltas,
   // left as per-row-tile partials by the products that made them).
   ColumnSum columns[kMaxColumnSums];
@@ -638,7 +677,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
     column(cpart + lay.colsum_at[l], gemm_nt_colsum_parts(dt, B, lay.in_dim[l], lay.out_dim[l], lay.colsum_coarse),
            lay.out_dim[l - 1], lay.b_off[l - 1]);
   const LossSum loss = {sums.loss, out->loss, sums.parts, B};
-  bool embedding_updated = false;
+  bool divided = false;
   for (int l = L - 2; l >= 0; --l) {
     if (l > 0) {
       const bool by_bits = relu_bits[l - 1] != nullptr;
@@ -657,23 +696,24 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
       if ((double)B * (F - E2) * lay.out_dim[0] >= kSplitDxMacs) {
         GEAR_RUN("dgrad_gemm_emb", launch_gemm_nt(dt, ws + lay.delta[0], ws + lay.wct[0], B, E2, lay.out_dim[0], EPI_DX,
                                                   nullptr, dx_dfv, dx_emb, E2, nullptr, nullptr, nullptr, s));
+        if (gear_status st = links_left()) return st;
         GEAR_HIP(lane.fork());
         {
           hipStream_t s = helper;
-          GEAR_RUN("small_sums", launch_param_update(nullptr, 0, 1, columns, n_columns, loss, opt, status, s));
-          GEAR_RUN("embedding_update", [&]() -> hipError_t {
-            const hipError_t e = embedding_chunks(s);
-            return e != hipSuccess ? e : launch_embedding_spans(*cfg, gb.p[0], gb.p[1], t->user_emb, t->url_emb, emb.partials,
-                                                                opt, mom_user, mom_url, status, s);
-          }());
+          GEAR_RUN("small_sums", launch_param_update(nullptr, 0, 1, columns, n_columns, loss, nullptr, opt, status, s));
+          GEAR_RUN("embedding_update", launch_embedding_update(emb, true, status, s));
         }
-        embedding_updated = true;
+        divided = true;
         GEAR_RUN(kDgrad[0], launch_gemm_nt(dt, ws + lay.delta[0],
                                            ws + lay.wct[0] + (size_t)E2 * lay.out_dim[0] * lay.act_bytes, B, F - E2,
                                            lay.out_dim[0], EPI_DX, nullptr, dx_dfv, dx_emb, 0, nullptr, nullptr, nullptr, s));
       } else {
+        const bool takes = gemm_nt_carries(dt, B, F, lay.out_dim[0]);
+        if (takes) GEAR_BOARD();
         GEAR_RUN(kDgrad[0], launch_gemm_nt(dt, ws + lay.delta[0], ws + lay.wct[0], B, F, lay.out_dim[0], EPI_DX,
-                                           nullptr, dx_dfv, dx_emb, E2, nullptr, nullptr, nullptr, s));
+                                           nullptr, dx_dfv, dx_emb, E2, nullptr, nullptr, nullptr, s, false,
+                                           takes ? passenger() : nullptr));
+        if (gear_status st = links_left()) return st;
       }
     }
   }
@@ -686,9 +726,9 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   GEAR_HIP(lane.fork());
   {
     hipStream_t s = helper;
-    if (!embedding_updated) GEAR_RUN("embedding_update", embedding_chunks(s));
+    if (!divided && !one_stream) GEAR_RUN("embedding_update", launch_embedding_update(emb, false, status, s));
     GEAR_RUN("accumulate", launch_accumulate(*cfg, gb.p[2], plan, dx_dfv, grad_accum, M, out->ready_ids, out->ready_grads,
-                                             embedding_updated ? nullptr : &emb, status, s));
+                                             divided ? nullptr : &emb, !one_stream, status, s));
   }
   GEAR_HIP(lane.mark());
   // SGD on the hidden layers' weights: split-K wgrad.  With the last of them go the small sums, unless they are done.
@@ -721,9 +761,9 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
     // step ends with the bookkeeping and the join.
     if (first == 0) GEAR_HIP(lane.wait_checked());
     first += n;
-    const bool sums_too = first == n_wp && !embedding_updated;   // else the helper stream has done them
-    GEAR_RUN("param_update", launch_param_update(sp, n, splits, columns, sums_too ? n_columns : 0, sums_too ? loss : LossSum{}, opt,
-                                                 status, s));
+    const bool sums_too = first == n_wp && !divided;   // else the helper stream has done them
+    GEAR_RUN("param_update", launch_param_update(sp, n, splits, columns, sums_too ? n_columns : 0, sums_too ? loss : LossSum{},
+                                                 sums_too && one_stream ? &emb : nullptr, opt, status, s));
   }
   GEAR_HIP(lane.wait(true));  // the step ends on the caller's stream
   if (out->dbg_img_unique && b->nnz > 0)
@@ -780,7 +820,7 @@ gear_status gear_group_ids(const gear_config *cfg, const int32_t *keys, int32_t 
   GroupBatch gb;
   gb.count = 1;
   const int bits = bits_for(key_range);
-  gb.p[0] = make_problem(lay, ws, 2, keys, n, 0, radix_passes(bits, lay.g[2].total_words, n), bits);
+  gb.p[0] = make_problem(lay, ws, 2, keys, n, 0, radix_passes(bits, lay.g[2].total_words, kMaxDigitBits), bits);
   gb.tickets = (int32_t *)(ws + lay.tickets);
   gb.seg_state = (uint32_t *)(ws + lay.seg_state);
   ZeroList zero;
@@ -788,8 +828,9 @@ gear_status gear_group_ids(const gear_config *cfg, const int32_t *keys, int32_t 
   zero.p[zero.count] = (uint32_t *)status;
   zero.words[zero.count++] = 1;
   GEAR_HIP(launch_clear(zero, s));
-  GEAR_HIP(launch_group(gb, nullptr, nullptr, 0, 0, status, s));
-  GEAR_HIP(launch_segments(gb, status, s));
+  GEAR_HIP(launch_check(gb, nullptr, nullptr, 0, 0, status, s));
+  for (int pass = 0; pass < group_passes(gb); ++pass) GEAR_HIP(launch_radix_pass(gb, pass, status, s));
+  GEAR_HIP(launch_segments(gb, nullptr, status, s));
   if (n > 0) {
     GEAR_HIP(hipMemcpyAsync(unique, gb.p[0].unique, (size_t)n * 4, hipMemcpyDeviceToDevice, s));
     GEAR_HIP(hipMemcpyAsync(perm, gb.p[0].perm, (size_t)n * 4, hipMemcpyDeviceToDevice, s));
@@ -845,7 +886,7 @@ gear_status gear_gemm(int32_t dtype, int32_t form, const void *A, const void *B,
     const Optim minus = {-1.0f, 0.0f, 0.0f, 0.0f, 1.0f, 0};   // out = 0 - (-1) * sum of the partials
     const Moments none = {nullptr, nullptr};
     const SplitkProblem sum = {partial, (float *)out, none, (int64_t)M * N};
-    GEAR_HIP(launch_param_update(&sum, 1, splits, nullptr, 0, LossSum{}, minus, status, s));
+    GEAR_HIP(launch_param_update(&sum, 1, splits, nullptr, 0, LossSum{}, nullptr, minus, status, s));
   } else {
     return GEAR_ERR_INVALID;
   }

@@ -7,7 +7,9 @@
 //
 // One wavefront per page view.  A lane owns 16-byte pieces of the row, so a DFV row is read with
 // fully coalesced 1 KB wave loads, several images in flight; the sum runs in fp32 in CSR order.
-#include "gear_internal.hpp"
+#include "group_device.hpp"
+
+#include <type_traits>
 
 namespace gear {
 namespace {
@@ -18,17 +20,24 @@ __device__ __forceinline__ int64_t clamp_id(int32_t id, int64_t n) {
   return id < 0 ? 0 : ((int64_t)id >= n ? n - 1 : (int64_t)id);
 }
 
-template <typename ET, typename DT, typename XT>
+template <typename ET, typename DT, typename XT, bool CHECK>
 __global__ void __launch_bounds__(256)
 k_gather_pool(int B, int nnz, int d, int D, int64_t n_users, int64_t n_urls, int64_t n_images,
               const int32_t *__restrict__ user_id, const int32_t *__restrict__ url_id,
               const int32_t *__restrict__ img_off, const int32_t *__restrict__ img_id, const ET *__restrict__ user_emb,
-              const ET *__restrict__ url_emb, const DT *__restrict__ dfv, XT *__restrict__ x) {
-  // The ids are being checked on the helper stream while this kernel runs, so it does not trust
+              const ET *__restrict__ url_emb, const DT *__restrict__ dfv, XT *__restrict__ x,
+              std::conditional_t<CHECK, CheckTask, NoTask> check) {
+  int block = blockIdx.x;
+  if constexpr (CHECK) {   // the first workgroups check the ids and count their digits (group_device.hpp)
+    extern __shared__ int hist[];
+    if (block < check.blocks) return check_and_count(check, block, hist);
+    block -= check.blocks;
+  }
+  // The ids are being checked on the helper stream or in this very launch, so the gather does not trust
   // them: every id and offset is clamped into its range before it is used as an index.  If one had
   // to be clamped, the check finds it too and the step stops before anything reads this x.
   const int lane = threadIdx.x & (kWave - 1);
-  const int view = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave));
+  const int view = __builtin_amdgcn_readfirstlane((int)(block * (blockDim.x / kWave) + threadIdx.x / kWave));
   if (view >= B) return;
   const int F = 2 * d + D;
   XT *xrow = x + (size_t)view * F;
@@ -110,29 +119,36 @@ k_gather_pool(int B, int nnz, int d, int D, int64_t n_users, int64_t n_urls, int
 
 template <typename ET, typename DT, typename XT>
 hipError_t run(const gear_config &cfg, const gear_batch &b, const gear_tables &t, const void *dfv, void *x,
-               hipStream_t s) {
-  const int waves = 4;
-  hipLaunchKernelGGL((k_gather_pool<ET, DT, XT>), dim3((b.B + waves - 1) / waves), dim3(waves * kWave), 0, s, b.B, b.nnz,
-                     cfg.emb_dim, cfg.dfv_dim, cfg.n_users, cfg.n_urls, cfg.n_images, b.user_id, b.url_id, b.img_off,
-                     b.img_id, (const ET *)t.user_emb, (const ET *)t.url_emb, (const DT *)dfv, (XT *)x);
+               const CheckTask *check, hipStream_t s) {
+  const int waves = 4, blocks = (b.B + waves - 1) / waves;
+  static_assert(kSortBlock == waves * kWave, "checking workgroups ride along");
+#define GEAR_GATHER(C, EXTRA, LDS, TASK)                                                                                   \
+  hipLaunchKernelGGL((k_gather_pool<ET, DT, XT, C>), dim3(blocks + (EXTRA)), dim3(waves * kWave), LDS, s, b.B, b.nnz,      \
+                     cfg.emb_dim, cfg.dfv_dim, cfg.n_users, cfg.n_urls, cfg.n_images, b.user_id, b.url_id, b.img_off,      \
+                     b.img_id, (const ET *)t.user_emb, (const ET *)t.url_emb, (const DT *)dfv, (XT *)x, TASK)
+  if (check)
+    GEAR_GATHER(true, check->blocks, check_lds_bytes(check->gb), *check);
+  else
+    GEAR_GATHER(false, 0, 0, NoTask{});
+#undef GEAR_GATHER
   return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_gather_pool(const gear_config &cfg, const gear_batch &b, const gear_tables &t, const void *dfv,
-                              void *x, hipStream_t s) {
+                              void *x, hipStream_t s, const CheckTask *check) {
   if (b.B <= 0) return hipSuccess;
   const int key = (cfg.emb_dtype << 2) | (cfg.dfv_dtype << 1) | cfg.mlp_dtype;
   switch (key) {
-    case 0: return run<float, float, float>(cfg, b, t, dfv, x, s);
-    case 1: return run<float, float, bf16_t>(cfg, b, t, dfv, x, s);
-    case 2: return run<float, bf16_t, float>(cfg, b, t, dfv, x, s);
-    case 3: return run<float, bf16_t, bf16_t>(cfg, b, t, dfv, x, s);
-    case 4: return run<bf16_t, float, float>(cfg, b, t, dfv, x, s);
-    case 5: return run<bf16_t, float, bf16_t>(cfg, b, t, dfv, x, s);
-    case 6: return run<bf16_t, bf16_t, float>(cfg, b, t, dfv, x, s);
-    default: return run<bf16_t, bf16_t, bf16_t>(cfg, b, t, dfv, x, s);
+    case 0: return run<float, float, float>(cfg, b, t, dfv, x, check, s);
+    case 1: return run<float, float, bf16_t>(cfg, b, t, dfv, x, check, s);
+    case 2: return run<float, bf16_t, float>(cfg, b, t, dfv, x, check, s);
+    case 3: return run<float, bf16_t, bf16_t>(cfg, b, t, dfv, x, check, s);
+    case 4: return run<bf16_t, float, float>(cfg, b, t, dfv, x, check, s);
+    case 5: return run<bf16_t, float, bf16_t>(cfg, b, t, dfv, x, check, s);
+    case 6: return run<bf16_t, bf16_t, float>(cfg, b, t, dfv, x, check, s);
+    default: return run<bf16_t, bf16_t, bf16_t>(cfg, b, t, dfv, x, check, s);
   }
 }
 

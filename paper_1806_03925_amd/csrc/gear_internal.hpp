@@ -117,7 +117,8 @@ constexpr int kSortTile = kSortBlock * kSortItems;    // keys per workgroup
 constexpr int kMaxProblems = 3;
 constexpr int kMaxPasses = 3;
 constexpr int kMaxDigitBits = 12;
-constexpr int kLongList = 65536;                      // ids from which a launch takes larger tiles (sort_threads)
+constexpr int kSideDigitBits = 11;                    // of passes that other launches carry
+constexpr int kLongList = 65536;                      // ids from which a workgroup of the check takes several tiles
 // Counts a tile publishes over all passes, at most.  A pass costs a launch and two memory latencies whatever its
 // radix, so a list takes as few passes as its keys allow within this (one up to 12 bits, two up to 22, then three);
 // it is what the regions that hold the counts have room for (24 KB per tile of 2048 keys).
@@ -148,12 +149,12 @@ struct GroupBatch {
   uint32_t *seg_state;            // [tiles - 1][3] heads, units and emissions, published like `state`
 };
 
-// fewest passes over keys of `bits` bits (twelve-bit digits of the large tiles would take more than 64 KB of LDS)
-inline int radix_passes(int bits, int most_words, int n) {
+// fewest passes over keys of `bits` bits in digits of up to `widest` bits
+inline int radix_passes(int bits, int most_words, int widest) {
   int passes = 1;
   for (; passes < kMaxPasses; ++passes) {
     const int digit_bits = (bits + passes - 1) / passes;
-    if (digit_bits <= (n > kLongList ? kMaxDigitBits - 1 : kMaxDigitBits) && (passes << digit_bits) <= most_words) break;
+    if (digit_bits <= widest && (passes << digit_bits) <= most_words) break;
   }
   return passes;
 }
@@ -175,6 +176,35 @@ struct AccumPlan {
   float *row_scale;      // [nnz] 1 / (images of that view): backward of the mean
   int32_t *n_units;      // [1]
 };
+
+// ---- tasks of the grouping (group.hip) ----
+struct ViewCheck {
+  const int32_t *img_off;
+  int32_t *occ_view;
+  int32_t B, nnz;   // B = 0: no views to check
+};
+struct CheckTask {
+  GroupBatch gb;
+  ViewCheck views;
+  int blocks, tiles_per_block;
+  int32_t *status;
+};
+struct PlanArgs {
+  AccumPlan plan;
+  const int32_t *occ_view, *img_off, *counts;
+  int32_t M, ready_cap;
+  int32_t *n_ready;
+};
+// one link of the grouping that a launch of the forward pass carries (group_device.hpp)
+struct SideTask {
+  enum Kind { kPass, kSegments };
+  int kind, pass;
+  int blocks;       // workgroups, a multiple of the XCDs' number so that the products' stay on the XCDs they share operands on
+  GroupBatch gb;
+  PlanArgs plan;
+  int32_t *status;
+};
+struct NoTask {};
 
 // ------------------------------------------------------------------------------------------------
 // workspace layout (byte offsets from a 256-byte aligned base)
@@ -235,9 +265,15 @@ hipError_t launch_clear(const ZeroList &zero, hipStream_t s);
 hipError_t launch_begin(int32_t *status, int32_t *n_ready, float *loss, const ZeroList &zero, int dtype, const CastJob *jobs,
                         int count, hipStream_t s);
 void group_zero_list(const GroupBatch &gb, ZeroList *z);
-hipError_t launch_group(const GroupBatch &gb, const int32_t *img_off, int32_t *occ_view, int B, int nnz, int32_t *status,
+CheckTask check_task(const GroupBatch &gb, const int32_t *img_off, int32_t *occ_view, int B, int nnz, int32_t *status);
+int check_lds_bytes(const GroupBatch &gb);
+int group_passes(const GroupBatch &gb);
+SideTask side_task(const GroupBatch &gb, const PlanArgs &plan, int step, int32_t *status);   // step: a pass, or the segments behind them
+int radix_lds_bytes(const GroupBatch &gb);
+hipError_t launch_check(const GroupBatch &gb, const int32_t *img_off, int32_t *occ_view, int B, int nnz, int32_t *status,
                         hipStream_t s);
-hipError_t launch_segments(const GroupBatch &gb, int32_t *status, hipStream_t s);
+hipError_t launch_radix_pass(const GroupBatch &gb, int pass, const int32_t *status, hipStream_t s);
+hipError_t launch_segments(const GroupBatch &gb, const PlanArgs *args, int32_t *status, hipStream_t s);
 // distinct ids of a grouped list whose cache entry is older than `expiry`, ascending
 // words (four images each) of the byte map over all images that the expiry filter marks, and tiles
 // of kSortTile words
@@ -248,12 +284,8 @@ hipError_t launch_expired(const int32_t *image_ids, int n, const int32_t *stamp,
                           int32_t *status, hipStream_t s);
 hipError_t launch_stamp(int32_t *stamp, int64_t n_images, const int32_t *ids, int64_t n, int32_t now, int32_t *status,
                         hipStream_t s, const int32_t *n_dev = nullptr);
-hipError_t launch_accum_plan(const GroupBatch &gb, const AccumPlan &plan, const int32_t *occ_view, const int32_t *img_off,
-                             const int32_t *counts, int32_t M, int32_t ready_cap, int32_t *n_ready, int32_t *status,
-                             hipStream_t s);
-
 hipError_t launch_gather_pool(const gear_config &cfg, const gear_batch &b, const gear_tables &t,
-                              const void *dfv_cache, void *x, hipStream_t s);
+                              const void *dfv_cache, void *x, hipStream_t s, const CheckTask *check = nullptr);
 
 enum GemmEpilogue {
   EPI_BIAS_RELU = 0,  // out(T)   = max(acc + bias[n], 0)
@@ -269,7 +301,9 @@ enum GemmEpilogue {
 // then always runs).
 hipError_t launch_gemm_nt(int dtype, const void *A, const void *B, int M, int N, int K, int epilogue,
                           const float *bias, const void *aux, void *out, int split, float *colpart,
-                          uint8_t *relu_bits, const int32_t *status, hipStream_t s, bool coarse = false);
+                          uint8_t *relu_bits, const int32_t *status, hipStream_t s, bool coarse = false,
+                          const SideTask *side = nullptr);
+bool gemm_nt_carries(int dtype, int M, int N, int K);   // whether a bias + ReLU or dLoss/dx product of this shape takes a SideTask
 int gemm_nt_colsum_parts(int dtype, int M, int N, int K, bool coarse);
 // partial_i[z][M_i x N_i] = sum over the z-th of `splits` ranges of the K rows of A_i[K x M_i]^T * B_i[K x N_i], for
 // all problems in one launch (operands M-/N-contiguous).  k_dev (may be NULL): device word holding the real
@@ -302,13 +336,15 @@ struct LossSum {   // *loss = (sum of the partial sums) / B; parts = 0: not want
   int parts, B;
 };
 constexpr int kMaxColumnSums = GEAR_MAX_LAYERS + 2;
-// all of that in one launch
+// all of that in one launch, and level 2 of an embedding update (may be NULL)
+struct EmbeddingWork;
 hipError_t launch_param_update(const SplitkProblem *p, int count, int splits, const ColumnSum *c, int n_columns,
-                               const LossSum &loss, const Optim &opt, const int32_t *status, hipStream_t s);
+                               const LossSum &loss, const EmbeddingWork *emb, const Optim &opt, const int32_t *status,
+                               hipStream_t s);
 // the same products on tiles of moderate size (gemm_tile.hip)
 hipError_t launch_gemm_nt_tile(int dtype, const void *A, const void *B, int M, int N, int K, int epilogue,
                                const float *bias, const void *aux, void *out, int split, float *colpart,
-                               uint8_t *relu_bits, const int32_t *status, hipStream_t s, bool coarse);
+                               uint8_t *relu_bits, const int32_t *status, hipStream_t s, bool coarse, const SideTask *side);
 int nt_tile_colsum_parts(int dtype, int M, int N, bool coarse);
 hipError_t launch_gemm_tn_tile(int dtype, const TnProblem *p, int count, int K, int splits, const int32_t *status,
                                hipStream_t s, const int32_t *k_dev);
@@ -316,7 +352,7 @@ int tn_tile_splits(int dtype, const TnProblem *p, int count, int K);
 
 hipError_t launch_logit_loss(int dtype, const void *h, const void *wc_last, const float *bias_last, const float *label,
                              int B, int H, float *logits, float *dz, void *delta, float *partials,
-                             const int32_t *status, hipStream_t s);
+                             const int32_t *status, hipStream_t s, const SideTask *side = nullptr);
 // where launch_logit_loss leaves its sums, one row per workgroup
 struct LogitSums {
   const float *w, *delta, *bias, *loss;   // [parts x H], [parts x H], [parts], [parts]
@@ -325,25 +361,35 @@ struct LogitSums {
 LogitSums logit_sums(const float *partials, int B, int H);
 size_t logit_partial_floats(int H, int B);
 
-hipError_t launch_embedding_chunks(const gear_config &cfg, const GroupProblem &users, const GroupProblem &urls, int nnz,
-                                   const AccumPlan &plan, const float *dx, void *user_emb, void *url_emb, float *partials,
-                                   const Optim &opt, const Moments &mom_user, const Moments &mom_url, int32_t *counts,
-                                   const int32_t *status, hipStream_t s);
-hipError_t launch_embedding_spans(const gear_config &cfg, const GroupProblem &users, const GroupProblem &urls, void *user_emb,
-                                  void *url_emb, float *partials, const Optim &opt, const Moments &mom_user,
-                                  const Moments &mom_url, const int32_t *status, hipStream_t s);
+constexpr int kChunk = 16;
+
+struct EmbeddingTable {
+  const int32_t *keys;   // sorted ids
+  const int32_t *perm;   // batch position of each sorted position
+  int n;
+  void *rows;            // embedding table
+  int col0;              // first column of this table's slice inside a dx row
+  float *part_first;     // [chunks x d] partial of a run that began in an earlier chunk
+  float *part_last;      // [chunks x d] partial of a run that begins here and goes on
+  Moments mom;           // Adam: fp32 moment tables of the same shape as `rows` (only touched rows move)
+};
+struct EmbeddingWork {
+  EmbeddingTable table[2];   // users, URLs
+  const float *dx;           // the embedding slots of dLoss/dx, [B x 2 d]
+  int32_t d, bf16;           // width and type of a row
+  Optim opt;
+  AccumPlan plan;            // of the images, for
+  int32_t *counts;           // their counters
+};
+EmbeddingWork embedding_work(const gear_config &cfg, const GroupProblem &users, const GroupProblem &urls, const float *dx,
+                             void *user_emb, void *url_emb, float *partials, const Optim &opt, const Moments &mom_user,
+                             const Moments &mom_url, const AccumPlan &plan, int32_t *counts);
+hipError_t launch_embedding_update(const EmbeddingWork &w, bool both_levels, const int32_t *status, hipStream_t s);
 size_t embedding_partial_floats(const gear_config &cfg);
 
-struct EmbeddingFinish {   // what is left of an embedding update after launch_embedding_chunks
-  const GroupProblem *users, *urls;
-  void *user_emb, *url_emb;
-  float *partials;
-  Optim opt;
-  Moments mom_user, mom_url;
-};
 hipError_t launch_accumulate(const gear_config &cfg, const GroupProblem &img, const AccumPlan &plan,
                              const void *dx_dfv, float *grad_accum, int32_t M, int32_t *ready_ids,
-                             float *ready_grads, const EmbeddingFinish *emb, const int32_t *status, hipStream_t s);
+                             float *ready_grads, const EmbeddingWork *emb, bool level2, const int32_t *status, hipStream_t s);
 
 // n_dev (may be NULL): device word holding the real row count, at most n
 hipError_t launch_refresh(int dtype, void *dfv_cache, int64_t n_images, int dim, const int32_t *ids,

@@ -490,14 +490,17 @@ int gemm_nt_colsum_parts(int dtype, int M, int N, int K, bool coarse) {
   return nt_dma(dtype, M, N, K, false) ? (M + DM - 1) / DM : nt_tile_colsum_parts(dtype, M, N, coarse);
 }
 
+bool gemm_nt_carries(int dtype, int M, int N, int K) { return !nt_dma(dtype, M, N, K, false); }
+
 hipError_t launch_gemm_nt(int dtype, const void *A, const void *B, int M, int N, int K, int epi, const float *bias,
                           const void *aux, void *out, int split, float *colpart, uint8_t *relu_bits,
-                          const int32_t *status, hipStream_t s, bool coarse) {
+                          const int32_t *status, hipStream_t s, bool coarse, const SideTask *side) {
   if (M <= 0 || N <= 0) return hipSuccess;
   if (epi == EPI_MASK_BITS && dtype != GEAR_BF16) return hipErrorInvalidValue;
   const bool narrow = N <= NtNarrow::BN && (epi == EPI_DX || epi == EPI_F32);
   if (!nt_dma(dtype, M, N, K, narrow))
-    return launch_gemm_nt_tile(dtype, A, B, M, N, K, epi, bias, aux, out, split, colpart, relu_bits, status, s, coarse);
+    return launch_gemm_nt_tile(dtype, A, B, M, N, K, epi, bias, aux, out, split, colpart, relu_bits, status, s, coarse, side);
+  if (side) return hipErrorInvalidValue;
   const dim3 grid(((M + DM - 1) / DM) * (narrow ? 1 : (N + DN - 1) / DN));
 #define GEAR_DMA(E, C)                                                                                                \
   hipLaunchKernelGGL((k_gemm_nt_dma<E, C>), grid, dim3(DTHREADS), 0, s, (const bf16_t *)A, (const bf16_t *)B, M, N, K, \

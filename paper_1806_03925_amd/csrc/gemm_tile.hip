@@ -9,6 +9,7 @@
 // launches, now 19 in two.)  What lies beyond an operand's inner length is copied from a line of
 // zeros, so no inner length needs padding, and rows beyond the matrix repeat its last row and are not stored.
 #include "gemm_common.hpp"
+#include "group_device.hpp"
 
 #include <type_traits>
 
@@ -237,11 +238,14 @@ __device__ __forceinline__ void store_f32(const f32x16_v (&acc)[C::WTM][C::WTN],
   }
 }
 
-template <int EPI, typename C>
-__global__ void __launch_bounds__(C::THREADS)
+// SIDE: the first workgroups do a link of the grouping (group_device.hpp); workgroups then have kSortBlock threads, of which
+// the products of a smaller shape leave the rest idle.
+template <int EPI, typename C, bool SIDE = false>
+__global__ void __launch_bounds__(SIDE ? kSortBlock : C::THREADS)
 k_gemm_nt_tile(const typename C::T *__restrict__ A, const typename C::T *__restrict__ B, int M, int N, int K,
                const float *__restrict__ bias, const typename C::T *__restrict__ aux, void *__restrict__ out, int split,
-               float *__restrict__ colpart, uint8_t *__restrict__ relu_bits, const int32_t *__restrict__ status) {
+               float *__restrict__ colpart, uint8_t *__restrict__ relu_bits, const int32_t *__restrict__ status,
+               std::conditional_t<SIDE, SideTask, NoTask> side) {
   using T = typename C::T;
   if (status && *status != 0) return;
   constexpr bool kBf16 = sizeof(T) == 2;
@@ -251,10 +255,18 @@ k_gemm_nt_tile(const typename C::T *__restrict__ A, const typename C::T *__restr
   static_assert(kPatchBytes + kSumFloats * 4 <= C::STAGES * C::STAGE_BYTES, "patches and column sums fit");
 
   const int tid = threadIdx.x, lane = tid & 63;
+  int block = blockIdx.x, blocks = gridDim.x;
+  if constexpr (SIDE) {
+    static_assert(C::THREADS <= kSortBlock && C::STAGES * C::STAGE_BYTES >= 12 << kSideDigitBits, "side work fits");
+    if (block < side.blocks) return side_work(side, block, lds);
+    block -= side.blocks;
+    blocks -= side.blocks;
+    if (tid >= C::THREADS) return;   // a barrier waits for wavefronts that are still there
+  }
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / C::WAVES_N, wn = wave % C::WAVES_N;
   const int n_tiles = (N + C::BN - 1) / C::BN;
-  const int tile = xcd_remap(blockIdx.x, gridDim.x);
+  const int tile = xcd_remap(block, blocks);
   const int m0 = (tile / n_tiles) * C::BM, n0 = (tile % n_tiles) * C::BN;
 
   // this lane's piece of the rows it copies: LDS slot lane % 8 of row lane / 8 receives piece (lane % 8) ^ (row % 8)
@@ -624,17 +636,26 @@ long long tiles_of(int M, int N, int bm, int bn) { return (long long)((M + bm - 
 
 template <int EPI, typename C>
 hipError_t run_nt(const void *A, const void *B, int M, int N, int K, const float *bias, const void *aux, void *out, int split,
-                  float *colpart, uint8_t *relu_bits, const int32_t *status, hipStream_t s) {
+                  float *colpart, uint8_t *relu_bits, const int32_t *status, hipStream_t s, const SideTask *side) {
   using T = typename C::T;
-  hipLaunchKernelGGL((k_gemm_nt_tile<EPI, C>), dim3((unsigned)tiles_of(M, N, C::BM, C::BN)), dim3(C::THREADS), 0, s,
-                     (const T *)A, (const T *)B, M, N, K, bias, (const T *)aux, out, split, colpart, relu_bits, status);
+  const unsigned tiles = (unsigned)tiles_of(M, N, C::BM, C::BN);
+  if constexpr (EPI == EPI_BIAS_RELU || EPI == EPI_DX) {
+    if (side) {
+      hipLaunchKernelGGL((k_gemm_nt_tile<EPI, C, true>), dim3(tiles + side->blocks), dim3(kSortBlock), 0, s, (const T *)A,
+                         (const T *)B, M, N, K, bias, (const T *)aux, out, split, colpart, relu_bits, status, *side);
+      return hipGetLastError();
+    }
+  }
+  if (side) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((k_gemm_nt_tile<EPI, C>), dim3(tiles), dim3(C::THREADS), 0, s, (const T *)A, (const T *)B, M, N, K, bias,
+                     (const T *)aux, out, split, colpart, relu_bits, status, NoTask{});
   return hipGetLastError();
 }
 
 template <typename C>
 hipError_t run_nt_any(const void *A, const void *B, int M, int N, int K, int epi, const float *bias, const void *aux, void *out,
-                      int split, float *colpart, uint8_t *relu_bits, const int32_t *status, hipStream_t s) {
-#define GEAR_NT(E) run_nt<E, C>(A, B, M, N, K, bias, aux, out, split, colpart, relu_bits, status, s)
+                      int split, float *colpart, uint8_t *relu_bits, const int32_t *status, hipStream_t s, const SideTask *side) {
+#define GEAR_NT(E) run_nt<E, C>(A, B, M, N, K, bias, aux, out, split, colpart, relu_bits, status, s, side)
   switch (epi) {
     case EPI_BIAS_RELU: return GEAR_NT(EPI_BIAS_RELU);
     case EPI_MASK: return GEAR_NT(EPI_MASK);
@@ -688,9 +709,9 @@ int nt_tile_colsum_parts(int dtype, int M, int N, bool coarse) {
 
 hipError_t launch_gemm_nt_tile(int dtype, const void *A, const void *B, int M, int N, int K, int epi, const float *bias,
                                const void *aux, void *out, int split, float *colpart, uint8_t *relu_bits,
-                               const int32_t *status, hipStream_t s, bool coarse) {
+                               const int32_t *status, hipStream_t s, bool coarse, const SideTask *side) {
   const NtShape shape = nt_shape(dtype, M, N, coarse);
-#define GEAR_NT(C) run_nt_any<C>(A, B, M, N, K, epi, bias, aux, out, split, colpart, relu_bits, status, s)
+#define GEAR_NT(C) run_nt_any<C>(A, B, M, N, K, epi, bias, aux, out, split, colpart, relu_bits, status, s, side)
   if (dtype == GEAR_BF16) return shape == kWide ? GEAR_NT(Bf16Mid) : shape == kTall ? GEAR_NT(Bf16Tall) : GEAR_NT(Bf16Small);
   return shape == kWide ? GEAR_NT(F32Big) : GEAR_NT(F32Small);
 #undef GEAR_NT

@@ -15,38 +15,10 @@
 //
 // Everything here is integer work whose result does not depend on scheduling: digit counts are
 // integer sums, ranks come from wave ballots in lane order, scans run in a fixed shape.
-#include "gear_internal.hpp"
+#include "group_device.hpp"
 
 namespace gear {
 namespace {
-
-__device__ __forceinline__ int wave_inclusive_scan(int v, int lane) {
-#pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) {
-    const int t = __shfl_up(v, off, kWave);
-    if (lane >= off) v += t;
-  }
-  return v;
-}
-
-// exclusive scan of one int per thread over a workgroup of WAVES wavefronts; *total = sum of all
-template <int WAVES = 4>
-__device__ __forceinline__ int block_exclusive_scan(int v, int *total, int *smem /* >= WAVES ints */) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int inc = wave_inclusive_scan(v, lane);
-  __syncthreads();  // smem may still be read from a previous call
-  if (lane == 63) smem[wave] = inc;
-  __syncthreads();
-  int base = 0, sum = 0;
-#pragma unroll
-  for (int w = 0; w < WAVES; ++w) {
-    const int t = smem[w];
-    if (w < wave) base += t;
-    sum += t;
-  }
-  *total = sum;
-  return base + inc - v;
-}
 
 // sum of tile_vals[0 .. tile) for tile <= 256 * 4, computed by the whole workgroup
 __device__ __forceinline__ int sum_before(const int32_t *tile_vals, int tile, int *smem) {
@@ -55,494 +27,6 @@ __device__ __forceinline__ int sum_before(const int32_t *tile_vals, int tile, in
   int total;
   block_exclusive_scan(v, &total, smem);
   return total;
-}
-
-// ---- words that tiles publish for the tiles after them -------------------------------------------------
-// 0: nothing yet; 1 + c: this tile alone counts c (at most a tile's keys); kPrefix | c: this tile and all before it
-// count c.  A word carries its own value, so no order between stores matters and relaxed accesses do; agent scope,
-// because the tiles run on several XCDs.  Tiles are numbered by a ticket that a workgroup draws when it starts, not by
-// its place in the grid: whoever waits for a word waits for a workgroup that is already running and that publishes its
-// own count before it waits for anybody, so every wait ends whatever else occupies the device.
-constexpr uint32_t kPrefix = 0x80000000u;
-__device__ __forceinline__ void publish(uint32_t *word, uint32_t v) {
-  __hip_atomic_store(word, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ uint32_t published(const uint32_t *word) {
-  return __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ int draw_ticket(int32_t *counter) {
-  return __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// ---- check of the ids and digit counts of all passes ---------------------------------------------------
-// blockIdx.y: an id list, or (one past the lists) the offsets of the views.  A page view is a user id, a URL bucket and
-// a list of image ids (Section 1, Table 1); every id later indexes a table, so a bad id must be caught before any
-// kernel that changes caller state dereferences it: a violation sets the status word and every later kernel of the
-// step returns at once.  Also expands the CSR offsets into occ_view[j] = the view that owns occurrence j.
-__device__ __forceinline__ void flag(int32_t *status, int code) { atomicCAS(status, 0, code); }
-
-struct ViewCheck {
-  const int32_t *img_off;
-  int32_t *occ_view;
-  int32_t B, nnz;   // B = 0: no views to check
-};
-
-__global__ void __launch_bounds__(kSortBlock) k_check_and_count(GroupBatch gb, ViewCheck views, int tiles_per_block,
-                                                                int32_t *status) {
-  if ((int)blockIdx.y == gb.count) {
-    const int i = blockIdx.x * kSortBlock + threadIdx.x;
-    if (i >= views.B) return;
-    const int32_t lo = views.img_off[i], hi = views.img_off[i + 1];
-    const bool ok = lo >= 0 && lo <= hi && hi <= views.nnz;
-    if (!ok || (i == 0 && lo != 0) || (i == views.B - 1 && hi != views.nnz)) flag(status, GEAR_ERR_RANGE);
-    if (ok)
-      for (int j = lo; j < hi; ++j) views.occ_view[j] = i;
-    return;
-  }
-  const GroupProblem &p = gb.p[blockIdx.y];
-  const int64_t begin = (int64_t)blockIdx.x * tiles_per_block * kSortTile;
-  if (begin >= p.n) return;
-  extern __shared__ int hist[];   // [pass][digit]
-  const int radix = 1 << p.digit_bits, words = p.passes << p.digit_bits;
-  for (int d = threadIdx.x; d < words; d += kSortBlock) hist[d] = 0;
-  __syncthreads();
-  const int64_t end = min((int64_t)p.n, begin + (int64_t)tiles_per_block * kSortTile);
-  for (int64_t q0 = begin + threadIdx.x; q0 < end; q0 += kSortTile) {
-    int32_t key[kSortItems];
-#pragma unroll
-    for (int i = 0; i < kSortItems; ++i) key[i] = q0 + i * kSortBlock < end ? p.keys_in[q0 + i * kSortBlock] : 0;
-    bool bad = false;
-#pragma unroll
-    for (int i = 0; i < kSortItems; ++i)
-      if (q0 + i * kSortBlock < end) {
-        bad |= key[i] < 0 || (int64_t)key[i] >= p.range;
-        for (int pass = 0; pass < p.passes; ++pass)
-          atomicAdd(&hist[(pass << p.digit_bits) + ((key[i] >> (pass * p.digit_bits)) & (radix - 1))], 1);
-      }
-    if (bad && p.range > 0) flag(status, GEAR_ERR_RANGE);
-  }
-  __syncthreads();
-  for (int d = threadIdx.x; d < words; d += kSortBlock)
-    if (hist[d]) atomicAdd(&p.totals[d], hist[d]);
-}
-
-// A launch with a long list takes workgroups of 512 threads and tiles of 4096 keys instead of 256 and 2048: a tile looks
-// back at up to all before it, so half as many read a quarter of the words (295 000 keys, nine bits, beside the gather and
-// the first product of a step: 74, 52 and 42 us for the three passes with tiles of 2048, 68, 46 and 43 with 4096).  A
-// short list wants as many CUs on it as it can get.
-int sort_threads(const GroupBatch &gb) {
-  for (int i = 0; i < gb.count; ++i)
-    if (gb.p[i].n > kLongList) return 2 * kSortBlock;
-  return kSortBlock;
-}
-__host__ __device__ inline int radix_tiles(int n, int threads) {
-  return (int)(((int64_t)n + threads * kSortItems - 1) / (threads * kSortItems));
-}
-
-// ---- radix pass: stable scatter ---------------------------------------------------------------------
-// A key's place = start of its digit + keys of that digit in earlier tiles + in earlier waves of the tile + in earlier
-// rounds of the wave + its rank among the wave's keys of the round (ballots, in lane order).  A wavefront owns 512
-// consecutive keys of the tile and counts its digits as it goes, so LDS holds one 16-bit count per wave and digit:
-// 6 KB at nine bits, few enough that a workgroup fits on a CU beside one of the matrix-product kernel.
-// A thread owns DPT consecutive digits of the scans and of the look-back.
-template <int DPT, int THREADS>
-__device__ __forceinline__ void radix_pass(const GroupProblem &p, int pass, int32_t *ticket, bool idle, unsigned char *lds,
-                                           int *scan_smem, int *s_tile) {
-  constexpr int WAVES = THREADS / kWave;
-  const int radix = 1 << p.digit_bits, shift = pass * p.digit_bits;
-  int *digit_off = reinterpret_cast<int *>(lds);                                   // [radix]
-  uint16_t *wave_cnt = reinterpret_cast<uint16_t *>(lds + radix * sizeof(int));    // [wave][radix]
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (tid == 0) *s_tile = draw_ticket(ticket);
-  const int d0 = tid * DPT;
-  const bool owner = d0 < radix;
-  int total[DPT];
-#pragma unroll
-  for (int j = 0; j < DPT; ++j) total[j] = owner && d0 + j < radix ? p.totals[pass * radix + d0 + j] : 0;
-  for (int i = tid; i < WAVES * radix / 2; i += THREADS) reinterpret_cast<uint32_t *>(wave_cnt)[i] = 0u;
-  if (idle) return;
-  __syncthreads();
-  const int tile = *s_tile, n_tiles = radix_tiles(p.n, THREADS);
-  const int64_t first = (int64_t)tile * (THREADS * kSortItems) + wave * (kWave * kSortItems) + lane;
-  const int32_t *keys_in = pass == 0 ? p.keys_in : p.keys[pass & 1];
-  const int32_t *vals_in = p.vals[pass & 1];
-  int32_t key[kSortItems], val[kSortItems], rank[kSortItems];
-#pragma unroll
-  for (int i = 0; i < kSortItems; ++i) {
-    const int64_t q = first + i * kWave;
-    key[i] = q < p.n ? keys_in[q] : 0;
-    val[i] = q < p.n ? (pass == 0 ? (int32_t)q : vals_in[q]) : 0;
-  }
-  uint16_t *mine = wave_cnt + wave * radix;
-#pragma unroll
-  for (int i = 0; i < kSortItems; ++i) {
-    const bool valid = first + i * kWave < p.n;
-    const int digit = (key[i] >> shift) & (radix - 1);
-    unsigned long long peers = __ballot(valid);
-    for (int b = 0; b < p.digit_bits; ++b) {
-      const bool bit = (digit >> b) & 1;
-      const unsigned long long m = __ballot(bit);
-      peers &= bit ? m : ~m;
-    }
-    const int lower = __popcll(peers & ((1ull << lane) - 1ull));
-    const int before = mine[digit];   // the wave's LDS accesses complete in order: all lanes read, then the first of each digit adds
-    __builtin_amdgcn_wave_barrier();
-    if (valid && lower == 0) mine[digit] = (uint16_t)(before + __popcll(peers));
-    __builtin_amdgcn_wave_barrier();
-    rank[i] = before + lower;
-  }
-  __syncthreads();
-  // counts of the tile's digits: published; per wave they become the keys in earlier waves
-  int count[DPT];
-  uint32_t *row = p.state + ((size_t)pass * (n_tiles - 1) + tile) * radix + d0;
-#pragma unroll
-  for (int j = 0; j < DPT; ++j) {
-    count[j] = 0;
-    if (owner && d0 + j < radix) {
-#pragma unroll
-      for (int w = 0; w < WAVES; ++w) {
-        const int c = wave_cnt[w * radix + d0 + j];
-        wave_cnt[w * radix + d0 + j] = (uint16_t)count[j];
-        count[j] += c;
-      }
-      if (tile < n_tiles - 1) publish(row + j, tile == 0 ? kPrefix | (uint32_t)count[j] : 1u + (uint32_t)count[j]);
-    }
-  }
-  int mine_total = 0;
-#pragma unroll
-  for (int j = 0; j < DPT; ++j) mine_total += total[j];
-  int all;
-  int base = block_exclusive_scan<WAVES>(mine_total, &all, scan_smem);
-  // look back, kAhead tiles at a time
-  constexpr int kAhead = DPT >= 8 ? 1 : 16 / DPT;
-  int before[DPT], look[DPT];
-  int open = 0;
-#pragma unroll
-  for (int j = 0; j < DPT; ++j) {
-    before[j] = 0;
-    look[j] = owner && d0 + j < radix ? tile - 1 : -1;
-    open += look[j] >= 0 ? 1 : 0;
-  }
-  while (open > 0) {
-    uint32_t w[DPT][kAhead];
-#pragma unroll
-    for (int j = 0; j < DPT; ++j)
-#pragma unroll
-      for (int a = 0; a < kAhead; ++a)
-        w[j][a] = look[j] - a >= 0 ? published(p.state + ((size_t)pass * (n_tiles - 1) + (look[j] - a)) * radix + d0 + j) : 0u;
-    bool waits = false;
-#pragma unroll
-    for (int j = 0; j < DPT; ++j) {
-      bool go = look[j] >= 0;
-#pragma unroll
-      for (int a = 0; a < kAhead; ++a) {
-        if (go && w[j][a] == 0u) {
-          go = false;
-          waits = true;
-        }
-        if (go) {
-          if (w[j][a] & kPrefix) {
-            before[j] += (int)(w[j][a] & ~kPrefix);
-            look[j] = -1;
-            --open;
-            go = false;
-          } else {
-            before[j] += (int)w[j][a] - 1;
-            --look[j];   // tile 0 publishes a prefix, so this never passes it
-          }
-        }
-      }
-    }
-    if (waits) __builtin_amdgcn_s_sleep(1);
-  }
-#pragma unroll
-  for (int j = 0; j < DPT; ++j)
-    if (owner && d0 + j < radix) {
-      if (tile > 0 && tile < n_tiles - 1) publish(row + j, kPrefix | (uint32_t)(before[j] + count[j]));
-      digit_off[d0 + j] = base + before[j];
-      base += total[j];
-    }
-  __syncthreads();
-  int32_t *keys_out = p.keys[(pass + 1) & 1];
-  int32_t *vals_out = p.vals[(pass + 1) & 1];
-#pragma unroll
-  for (int i = 0; i < kSortItems; ++i) {
-    if (first + i * kWave < p.n) {
-      const int digit = (key[i] >> shift) & (radix - 1);
-      const int pos = digit_off[digit] + mine[digit] + rank[i];
-      keys_out[pos] = key[i];
-      vals_out[pos] = val[i];
-    }
-  }
-}
-
-// Digits of more than nine bits (lists whose keys then take a pass less) need more registers, which would keep the
-// narrow form off the CUs that a product occupies: a form of its own.
-template <bool WIDE, int THREADS>
-__global__ void __launch_bounds__(THREADS) k_radix_pass(GroupBatch gb, int pass, const int32_t *status) {
-  const bool idle = *status != 0;
-  const GroupProblem &p = gb.p[blockIdx.y];
-  if (pass >= p.passes || (int)blockIdx.x >= radix_tiles(p.n, THREADS)) return;
-  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-  __shared__ int scan_smem[8], s_tile;
-  int32_t *ticket = gb.tickets + blockIdx.y * kMaxPasses + pass;
-  const int digits = (1 << p.digit_bits) / THREADS;   // of a thread, at least one
-  if constexpr (WIDE) {
-    if constexpr (THREADS == kSortBlock)
-      if (digits == 16) return radix_pass<16, THREADS>(p, pass, ticket, idle, lds, scan_smem, &s_tile);
-    if (digits == 8) return radix_pass<8, THREADS>(p, pass, ticket, idle, lds, scan_smem, &s_tile);
-    if (digits == 4) return radix_pass<4, THREADS>(p, pass, ticket, idle, lds, scan_smem, &s_tile);
-  }
-  if constexpr (WIDE || THREADS == kSortBlock)
-    if (digits == 2) return radix_pass<2, THREADS>(p, pass, ticket, idle, lds, scan_smem, &s_tile);
-  return radix_pass<1, THREADS>(p, pass, ticket, idle, lds, scan_smem, &s_tile);
-}
-
-// ---- segments of the sorted keys and the plan of the windowed accumulation -------------------------------
-// Section 1, third point: the gradients of one image are collected until M have arrived, then
-// averaged.  With c gradients already collected in earlier steps, the occurrence at in-step rank r
-// has ordinal k = c + r; ordinals kM .. kM+M-1 form one group.  A "unit" is the work of one
-// workgroup: the first (possibly partial, possibly continuing) group of an image together with its
-// unfinished last group, or one complete middle group.  An "emission" is a completed group.
-
-// A thread owns the eight consecutive positions tile0 + 8 t .. + 7.  All loads that do not depend on each other are
-// requested together and none is behind a branch; the chain is ticket -> keys -> counters, start and end of the
-// segments that cross the tile's borders -> flags -> look-back -> descriptors.
-template <bool PLAN>
-__global__ void __launch_bounds__(kSortBlock)
-k_segments(GroupProblem p, AccumPlan plan, uint32_t *state, int32_t *ticket, const int32_t *__restrict__ occ_view,
-           const int32_t *__restrict__ img_off, const int32_t *__restrict__ counts, int M, int ready_cap,
-           int32_t *n_ready, int32_t *status) {
-  const bool idle = *status != 0;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (p.n <= 0) {
-    if (!idle && blockIdx.x == 0 && tid == 0) {
-      *p.n_unique = 0;
-      if (p.segoff) p.segoff[0] = 0;
-      if (PLAN) {
-        *plan.n_units = 0;
-        *n_ready = 0;
-      }
-    }
-    return;
-  }
-  __shared__ int s_tile, s_edge[2], s_last[4], s_first[4];
-  __shared__ unsigned long long s_sum[4];
-  __shared__ int s_base[3];
-  if (tid == 0) s_tile = draw_ticket(ticket);
-  if (idle) return;
-  __syncthreads();
-  const int n = p.n, n_tiles = (n + kSortTile - 1) / kSortTile, tile = s_tile;
-  const int tile0 = tile * kSortTile, tile1 = min(n - tile0, kSortTile) + tile0;
-  const int32_t *__restrict__ sk = p.sorted_keys;
-  const int64_t q0 = (int64_t)tile0 + tid * kSortItems;
-
-  int key[kSortItems];
-  const bool whole = q0 + kSortItems <= n;
-  if (whole) {
-    const int4 a = *reinterpret_cast<const int4 *>(sk + q0), b = *reinterpret_cast<const int4 *>(sk + q0 + 4);
-    key[0] = a.x, key[1] = a.y, key[2] = a.z, key[3] = a.w, key[4] = b.x, key[5] = b.y, key[6] = b.z, key[7] = b.w;
-  } else {
-#pragma unroll
-    for (int i = 0; i < kSortItems; ++i) key[i] = sk[min(q0 + i, (int64_t)n - 1)];
-  }
-  const int key_before = q0 > 0 && q0 < n ? sk[q0 - 1] : -1;
-  int view[kSortItems], far_key[kSortItems], cnt[kSortItems];
-  if constexpr (PLAN) {
-    if (whole) {
-      const int4 a = *reinterpret_cast<const int4 *>(p.perm + q0), b = *reinterpret_cast<const int4 *>(p.perm + q0 + 4);
-      view[0] = a.x, view[1] = a.y, view[2] = a.z, view[3] = a.w, view[4] = b.x, view[5] = b.y, view[6] = b.z, view[7] = b.w;
-    } else {
-#pragma unroll
-      for (int i = 0; i < kSortItems; ++i) view[i] = p.perm[min(q0 + i, (int64_t)n - 1)];
-    }
-#pragma unroll
-    for (int i = 0; i < kSortItems; ++i) far_key[i] = sk[min(q0 + i + M - 1, (int64_t)n - 1)];
-#pragma unroll
-    for (int i = 0; i < kSortItems; ++i) cnt[i] = counts[key[i]];
-#pragma unroll
-    for (int i = 0; i < kSortItems; ++i) view[i] = occ_view[view[i]];
-  }
-  // the segments that the tile's first and last keys belong to may begin before the tile and end behind it
-  if (wave == 0) {
-    const int k = sk[tile0];
-    const int s = tile0 > 0 && sk[tile0 - 1] == k ? wave_search(sk, 0, tile0, k, false, lane) : tile0;
-    if (lane == 0) s_edge[0] = s;
-  } else if (wave == 1) {
-    const int k = sk[tile1 - 1];
-    const int s = tile1 < n && sk[tile1] == k ? wave_search(sk, tile1, n, k, true, lane) : tile1;
-    if (lane == 0) s_edge[1] = s;
-  }
-  bool head[kSortItems];
-#pragma unroll
-  for (int i = 0; i < kSortItems; ++i) head[i] = q0 + i < n && (q0 + i == 0 || key[i] != (i == 0 ? key_before : key[i - 1]));
-
-  // last head at or before each position and first head behind it, over the tile
-  int last = -1, first = INT32_MAX;
-#pragma unroll
-  for (int i = 0; i < kSortItems; ++i)
-    if (head[i]) {
-      last = (int)(q0 + i);
-      if (first == INT32_MAX) first = last;
-    }
-  int run_last = last, run_first = first;   // inclusive scans over the wave, from below and from above
-#pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) {
-    const int a = __shfl_up(run_last, off, kWave), b = __shfl_down(run_first, off, kWave);
-    if (lane >= off) run_last = max(run_last, a);
-    if (lane + off < kWave) run_first = min(run_first, b);
-  }
-  if (lane == 63) s_last[wave] = run_last;
-  if (lane == 0) s_first[wave] = run_first;
-  int seg0 = __shfl_up(run_last, 1, kWave), seg1 = __shfl_down(run_first, 1, kWave);
-  if (lane == 0) seg0 = -1;
-  if (lane == 63) seg1 = INT32_MAX;
-  __syncthreads();
-#pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    if (w < wave) seg0 = max(seg0, s_last[w]);
-    if (w > wave) seg1 = min(seg1, s_first[w]);
-  }
-  if (seg0 < 0) seg0 = s_edge[0];
-  if (seg1 == INT32_MAX) seg1 = s_edge[1];
-
-  // flags; heads, units and emissions are counted together, 21 bits each
-  bool unit[kSortItems], emit[kSortItems];
-  int start[kSortItems];
-  unsigned long long sum = 0;
-#pragma unroll
-  for (int i = 0; i < kSortItems; ++i) {
-    const int64_t q = q0 + i;
-    if (head[i]) seg0 = (int)q;
-    start[i] = seg0;
-    unit[i] = emit[i] = false;
-    if constexpr (PLAN) {
-      if (q < n) {
-        const int ph = (cnt[i] + (int)(q - seg0)) % M;
-        unit[i] = head[i] || (ph == 0 && M <= n - q && far_key[i] == key[i]);
-        emit[i] = ph == M - 1;
-      }
-    }
-    sum += (head[i] ? 1ull : 0ull) + (unit[i] ? 1ull << 21 : 0ull) + (emit[i] ? 1ull << 42 : 0ull);
-  }
-  unsigned long long inc = sum;
-#pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) {
-    const unsigned long long t = __shfl_up(inc, off, kWave);
-    if (lane >= off) inc += t;
-  }
-  if (lane == 63) s_sum[wave] = inc;
-  __syncthreads();
-  unsigned long long below = inc - sum, all = 0;
-#pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    if (w < wave) below += s_sum[w];
-    all += s_sum[w];
-  }
-  constexpr int kMask = (1 << 21) - 1;
-  const int own[3] = {(int)(all & kMask), (int)((all >> 21) & kMask), (int)(all >> 42)};
-  if (tid == 0 && tile < n_tiles - 1)
-#pragma unroll
-    for (int c = 0; c < 3; ++c)
-      publish(state + 3 * (size_t)tile + c, tile == 0 ? kPrefix | (uint32_t)own[c] : 1u + (uint32_t)own[c]);
-
-  if constexpr (PLAN) {
-    // where the occurrence's gradient lives: dLoss/dx of its view, divided by the view's image count
-    float scale[kSortItems];
-#pragma unroll
-    for (int i = 0; i < kSortItems; ++i) scale[i] = 1.0f / (float)(img_off[view[i] + 1] - img_off[view[i]]);
-    if (whole) {
-      *reinterpret_cast<int4 *>(plan.row_view + q0) = make_int4(view[0], view[1], view[2], view[3]);
-      *reinterpret_cast<int4 *>(plan.row_view + q0 + 4) = make_int4(view[4], view[5], view[6], view[7]);
-      *reinterpret_cast<float4 *>(plan.row_scale + q0) = make_float4(scale[0], scale[1], scale[2], scale[3]);
-      *reinterpret_cast<float4 *>(plan.row_scale + q0 + 4) = make_float4(scale[4], scale[5], scale[6], scale[7]);
-    } else {
-#pragma unroll
-      for (int i = 0; i < kSortItems; ++i)
-        if (q0 + i < n) {
-          plan.row_view[q0 + i] = view[i];
-          plan.row_scale[q0 + i] = scale[i];
-        }
-    }
-  }
-
-  if (wave == 0) {
-    // look back 64 tiles at a time; a tile counts once all three of its words are of one kind
-    int before[3] = {0, 0, 0};
-    int look = tile - 1;
-    while (look >= 0) {
-      uint32_t w[3];
-      const int at = look - lane;
-#pragma unroll
-      for (int c = 0; c < 3; ++c) w[c] = at >= 0 ? published(state + 3 * (size_t)at + c) : kPrefix;
-      const bool there = w[0] != 0u && w[1] != 0u && w[2] != 0u;
-      const bool prefix = (w[0] & w[1] & w[2] & kPrefix) != 0u;
-      const bool alone = there && ((w[0] | w[1] | w[2]) & kPrefix) == 0u;
-      // lanes before the first that is not a lone count; that one too if it is a prefix
-      const unsigned long long stop = ~__ballot(alone), pre = __ballot(prefix);
-      const int upto = stop ? __builtin_ctzll(stop) : kWave;
-      const bool done = upto < kWave && ((pre >> upto) & 1ull);
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        int v = lane < upto ? (int)w[c] - 1 : (done && lane == upto ? (int)(w[c] & ~kPrefix) : 0);
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
-        before[c] += v;
-      }
-      if (done) break;
-      look -= upto;
-      if (upto == 0) __builtin_amdgcn_s_sleep(1);
-    }
-    if (lane < 3) {
-      const int b = lane == 0 ? before[0] : lane == 1 ? before[1] : before[2];
-      const int o = lane == 0 ? own[0] : lane == 1 ? own[1] : own[2];
-      s_base[lane] = b;
-      if (tile > 0 && tile < n_tiles - 1) publish(state + 3 * (size_t)tile + lane, kPrefix | (uint32_t)(b + o));
-    }
-  }
-  __syncthreads();
-  int h = s_base[0] + (int)(below & kMask), u = s_base[1] + (int)((below >> 21) & kMask), e = s_base[2] + (int)(below >> 42);
-#pragma unroll
-  for (int i = 0; i < kSortItems; ++i) {
-    const int64_t q = q0 + i;
-    if (head[i] && p.unique) {
-      p.unique[h] = key[i];
-      p.segoff[h] = (int)q;
-    }
-    h += head[i] ? 1 : 0;
-    if constexpr (PLAN) {
-      if (unit[i]) {
-        int end = seg1;   // of the unit's segment: the next head of this thread, or what follows it
-#pragma unroll
-        for (int j = kSortItems - 1; j > i; --j)
-          if (head[j]) end = (int)(q0 + j);
-        UnitDesc d;
-        d.q0 = (int)q;
-        d.image = key[i];
-        d.slot = e;
-        d.s0 = start[i];
-        d.s1 = end;
-        d.phase = cnt[i] % M;
-        d.collected = cnt[i] + (end - start[i]);
-        d.pad = 0;
-        plan.units[u] = d;
-        ++u;
-      }
-      e += emit[i] ? 1 : 0;
-    }
-  }
-  if (tile == n_tiles - 1 && tid == 0) {
-    *p.n_unique = s_base[0] + own[0];
-    if (p.unique) p.segoff[s_base[0] + own[0]] = n;
-    if constexpr (PLAN) {
-      *plan.n_units = s_base[1] + own[1];
-      // a list that does not fit is reported as empty: nobody may read ready_ids past ready_cap.  Every other tile has
-      // read the status word by now: it did so before it published the counts that this one has seen
-      const int emits = s_base[2] + own[2];
-      *n_ready = emits > ready_cap ? 0 : emits;
-      if (emits > ready_cap) atomicCAS(status, 0, GEAR_ERR_CAPACITY);
-    }
-  }
 }
 
 // ---- expiry of cached inference results ------------------------------------------------------------
@@ -662,7 +146,7 @@ hipError_t launch_stamp(int32_t *stamp, int64_t n_images, const int32_t *ids, in
   return hipGetLastError();
 }
 
-// What launch_group and launch_segments count in has to be zero first.
+// What the grouping counts in has to be zero first.
 void group_zero_list(const GroupBatch &gb, ZeroList *z) {
   z->count = 0;
   auto add = [&](void *p, int64_t words) {
@@ -673,63 +157,115 @@ void group_zero_list(const GroupBatch &gb, ZeroList *z) {
     const GroupProblem &p = gb.p[i];
     const int64_t words = (int64_t)p.passes << p.digit_bits;
     add(p.totals, words);
-    add(p.state, (radix_tiles(p.n, sort_threads(gb)) - 1) * words);
+    add(p.state, (radix_tiles(p.n) - 1) * words);
   }
   const GroupProblem &last = gb.p[gb.count - 1];
   add(gb.seg_state, 3 * (((int64_t)last.n + kSortTile - 1) / kSortTile - 1));
 }
 
-// One launch that checks and counts, one per pass.  A workgroup that checks takes one tile of a short list, so that
-// as many CUs as possible work on it, and four tiles of a long one, so that fewer workgroups add to the digits' totals
-// (a list of more than 65 536 ids has 32 tiles and more).
-hipError_t launch_group(const GroupBatch &gb, const int32_t *img_off, int32_t *occ_view, int B, int nnz, int32_t *status,
+// A workgroup that checks takes one tile of a short list, so that as many CUs as possible work on it, and four tiles of a
+// long one, so that fewer workgroups add to the digits' totals (a list of more than 65 536 ids has 32 tiles and more).
+CheckTask check_task(const GroupBatch &gb, const int32_t *img_off, int32_t *occ_view, int B, int nnz, int32_t *status) {
+  CheckTask t;
+  t.gb = gb;
+  t.views = ViewCheck{img_off, occ_view, B, nnz};
+  t.status = status;
+  t.tiles_per_block = 1;
+  for (int i = 0; i < gb.count; ++i)
+    if (gb.p[i].n > kLongList) t.tiles_per_block = 4;
+  t.blocks = (B + kSortBlock - 1) / kSortBlock;
+  for (int i = 0; i < gb.count; ++i)
+    t.blocks += (int)(((int64_t)gb.p[i].n + t.tiles_per_block * kSortTile - 1) / (t.tiles_per_block * kSortTile));
+  return t;
+}
+int check_lds_bytes(const GroupBatch &gb) {
+  int words = 0;
+  for (int i = 0; i < gb.count; ++i)
+    if (gb.p[i].passes << gb.p[i].digit_bits > words) words = gb.p[i].passes << gb.p[i].digit_bits;
+  return words * (int)sizeof(int);
+}
+int group_passes(const GroupBatch &gb) {
+  int passes = 0;
+  for (int i = 0; i < gb.count; ++i)
+    if (gb.p[i].n > 0 && gb.p[i].passes > passes) passes = gb.p[i].passes;
+  return passes;
+}
+static int widest_radix(const GroupBatch &gb) {
+  int radix = 0;
+  for (int i = 0; i < gb.count; ++i)
+    if (1 << gb.p[i].digit_bits > radix) radix = 1 << gb.p[i].digit_bits;
+  return radix;
+}
+int radix_lds_bytes(const GroupBatch &gb) { return (int)(sizeof(int) + kSortBlock / kWave * sizeof(uint16_t)) * widest_radix(gb); }
+
+SideTask side_task(const GroupBatch &gb, const PlanArgs &plan, int step, int32_t *status) {
+  SideTask t;
+  t.kind = step < group_passes(gb) ? SideTask::kPass : SideTask::kSegments;
+  t.pass = step;
+  t.gb = gb;
+  t.plan = plan;
+  t.status = status;
+  t.blocks = 0;
+  if (t.kind == SideTask::kPass)
+    for (int i = 0; i < gb.count; ++i) t.blocks += radix_tiles(gb.p[i].n);
+  else
+    t.blocks = (int)(((int64_t)gb.p[gb.count - 1].n + kSortTile - 1) / kSortTile);
+  t.blocks = (t.blocks + 7) / 8 * 8;
+  if (t.blocks == 0) t.blocks = 8;
+  return t;
+}
+
+namespace {
+__global__ void __launch_bounds__(kSortBlock) k_check_and_count(CheckTask t) {
+  extern __shared__ int hist[];
+  check_and_count(t, blockIdx.x, hist);
+}
+
+// What runs beside the products of a long step has to fit on a CU that one of their workgroups is on: two wavefronts a SIMD
+// of 200 registers leave 112 (gemm.hip).  A workgroup that needs more keeps the next tile of a product waiting: a step of
+// 65 536 views took 991 us with 114 registers here and 123 in k_segments, 985 with 102 and 116, 973 with 102 and 96 (and a
+// dozen spilled).
+template <int BITS>
+__global__ void __launch_bounds__(kSortBlock) k_radix_pass(GroupBatch gb, int pass, const int32_t *status) {
+  const bool idle = *status != 0;
+  if ((int)blockIdx.x >= radix_tiles(gb.p[blockIdx.y].n)) return;
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+  radix_pass_any<BITS, BITS <= 9 ? 4 : 16>(gb, blockIdx.y, pass, idle, lds);
+}
+
+template <bool PLAN>
+__global__ void __launch_bounds__(kSortBlock, 5) k_segments(GroupBatch gb, PlanArgs args, int32_t *status) {
+  segments<PLAN>(gb, args, blockIdx.x, status);
+}
+}  // namespace
+
+hipError_t launch_check(const GroupBatch &gb, const int32_t *img_off, int32_t *occ_view, int B, int nnz, int32_t *status,
                         hipStream_t s) {
-  int max_n = 0, passes = 0, words = 0, radix = 0;
-  for (int i = 0; i < gb.count; ++i) {
-    const GroupProblem &p = gb.p[i];
-    if (p.n <= 0) continue;
-    if (p.n > max_n) max_n = p.n;
-    if (p.passes > passes) passes = p.passes;
-    if (p.passes << p.digit_bits > words) words = p.passes << p.digit_bits;
-    if (1 << p.digit_bits > radix) radix = 1 << p.digit_bits;
-  }
-  const int tiles = (int)(((int64_t)max_n + kSortTile - 1) / kSortTile), per = max_n > kLongList ? 4 : 1;
-  int blocks = (tiles + per - 1) / per;
-  const ViewCheck views = {img_off, occ_view, B, nnz};
-  if (blocks < (B + kSortBlock - 1) / kSortBlock) blocks = (B + kSortBlock - 1) / kSortBlock;
-  if (blocks == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_check_and_count, dim3(blocks, gb.count + (B > 0 ? 1 : 0)), dim3(kSortBlock), words * sizeof(int), s,
-                     gb, views, per, status);
-  const int threads = sort_threads(gb);
-  const dim3 grid(radix_tiles(max_n, threads), gb.count);
-  const unsigned lds = (sizeof(int) + threads / kWave * sizeof(uint16_t)) * radix;
-#define GEAR_PASS(W, T) hipLaunchKernelGGL((k_radix_pass<W, T>), grid, dim3(T), lds, s, gb, pass, status)
-  for (int pass = 0; pass < passes; ++pass) {
-    if (threads == kSortBlock) {
-      if (radix > 512) GEAR_PASS(true, kSortBlock); else GEAR_PASS(false, kSortBlock);
-    } else {
-      if (radix > 512) GEAR_PASS(true, 2 * kSortBlock); else GEAR_PASS(false, 2 * kSortBlock);
-    }
-  }
-#undef GEAR_PASS
+  const CheckTask t = check_task(gb, img_off, occ_view, B, nnz, status);
+  if (t.blocks == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_check_and_count, dim3(t.blocks), dim3(kSortBlock), check_lds_bytes(gb), s, t);
   return hipGetLastError();
 }
 
-hipError_t launch_accum_plan(const GroupBatch &gb, const AccumPlan &plan, const int32_t *occ_view, const int32_t *img_off,
-                             const int32_t *counts, int32_t M, int32_t ready_cap, int32_t *n_ready, int32_t *status,
-                             hipStream_t s) {
-  const GroupProblem &img = gb.p[gb.count - 1];
-  const int tiles = (int)(((int64_t)img.n + kSortTile - 1) / kSortTile);
-  hipLaunchKernelGGL(k_segments<true>, dim3(tiles < 1 ? 1 : tiles), dim3(kSortBlock), 0, s, img, plan, gb.seg_state,
-                     gb.tickets + kTickets - 1, occ_view, img_off, counts, M, ready_cap, n_ready, status);
+hipError_t launch_radix_pass(const GroupBatch &gb, int pass, const int32_t *status, hipStream_t s) {
+  int tiles = 0;
+  for (int i = 0; i < gb.count; ++i)
+    if (radix_tiles(gb.p[i].n) > tiles) tiles = radix_tiles(gb.p[i].n);
+  if (tiles == 0) return hipSuccess;
+  if (widest_radix(gb) > 512)
+    hipLaunchKernelGGL(k_radix_pass<kMaxDigitBits>, dim3(tiles, gb.count), dim3(kSortBlock), radix_lds_bytes(gb), s, gb, pass, status);
+  else
+    hipLaunchKernelGGL(k_radix_pass<9>, dim3(tiles, gb.count), dim3(kSortBlock), radix_lds_bytes(gb), s, gb, pass, status);
   return hipGetLastError();
 }
 
-hipError_t launch_segments(const GroupBatch &gb, int32_t *status, hipStream_t s) {
-  const GroupProblem &p = gb.p[gb.count - 1];
-  const int tiles = (int)(((int64_t)p.n + kSortTile - 1) / kSortTile);
-  hipLaunchKernelGGL(k_segments<false>, dim3(tiles < 1 ? 1 : tiles), dim3(kSortBlock), 0, s, p, AccumPlan{}, gb.seg_state,
-                     gb.tickets + kTickets - 1, nullptr, nullptr, nullptr, 1, 0, nullptr, status);
+// segments of the last list; with `args` also the plan of the accumulation
+hipError_t launch_segments(const GroupBatch &gb, const PlanArgs *args, int32_t *status, hipStream_t s) {
+  const int tiles = (int)(((int64_t)gb.p[gb.count - 1].n + kSortTile - 1) / kSortTile);
+  if (args)
+    hipLaunchKernelGGL(k_segments<true>, dim3(tiles < 1 ? 1 : tiles), dim3(kSortBlock), 0, s, gb, *args, status);
+  else
+    hipLaunchKernelGGL(k_segments<false>, dim3(tiles < 1 ? 1 : tiles), dim3(kSortBlock), 0, s, gb, PlanArgs{}, status);
   return hipGetLastError();
 }
 

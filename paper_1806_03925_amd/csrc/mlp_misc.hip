@@ -1,7 +1,9 @@
 // The parts of the Sparse-Part MLP that are not matrix products: the logit layer with the loss and its derivative, bias gradients and the logit layer's weight
 // gradient, each followed by its SGD update (Section 3, step 4: forward to the loss,
 // back-propagation on the Sparse Part, gradients applied to the Sparse Part's parameters).
-#include "gear_internal.hpp"
+#include "group_device.hpp"
+
+#include <type_traits>
 
 namespace gear {
 namespace {
@@ -66,19 +68,24 @@ template <> struct DeltaPiece<bf16_t> {
   }
 };
 
-template <typename T, int NV, int G>
+template <typename T, int NV, int G, bool SIDE>
 __global__ void __launch_bounds__(256)
 k_logit_loss(const T *__restrict__ h, const T *__restrict__ w, const float *__restrict__ bias,
              const float *__restrict__ label, int B, int H, int rows_per_block, float *__restrict__ logits,
              float *__restrict__ dz_out, T *__restrict__ delta, float *__restrict__ part_w,
              float *__restrict__ part_d, float *__restrict__ part_b, float *__restrict__ part_loss,
-             const int32_t *__restrict__ status) {
-  if (*status != 0) return;
+             const int32_t *__restrict__ status, std::conditional_t<SIDE, SideTask, NoTask> side) {
   constexpr int VEC = Vec16<T>::N;
   constexpr int GROUPS = kWave / G;            // views a wavefront handles side by side
   constexpr int PARTS = 4 * GROUPS;            // partial sums per column in a workgroup
   __shared__ float s_red[4][2];
-  extern __shared__ float s_w[];  // [PARTS][H] weight-gradient sums, then [PARTS][H] delta sums
+  extern __shared__ __attribute__((aligned(16))) float s_w[];  // [PARTS][H] weight-gradient sums, then [PARTS][H] delta sums
+  int block = blockIdx.x;
+  if constexpr (SIDE) {   // the first workgroups do a link of the grouping (group_device.hpp)
+    if (block < side.blocks) return side_work(side, block, reinterpret_cast<unsigned char *>(s_w));
+    block -= side.blocks;
+  }
+  if (*status != 0) return;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int gl = lane & (G - 1), gi = lane / G;
   const int n_vec = H / VEC;
@@ -95,7 +102,7 @@ k_logit_loss(const T *__restrict__ h, const T *__restrict__ w, const float *__re
     for (int e = 0; e < VEC; ++e) gw[i][e] = gd[i][e] = 0.0f;
   }
   float loss_acc = 0.0f, dz_acc = 0.0f;  // partial sums of the views this lane evaluates
-  const int r0 = blockIdx.x * rows_per_block, r1 = min(B, r0 + rows_per_block);
+  const int r0 = block * rows_per_block, r1 = min(B, r0 + rows_per_block);
   constexpr int ROUND = kLogitRows * GROUPS;  // views per wavefront and round
   for (int base = r0 + wave * ROUND; base < r1; base += 4 * ROUND) {
     Vec16<T> hv[kLogitRows][NV];
@@ -177,12 +184,12 @@ k_logit_loss(const T *__restrict__ h, const T *__restrict__ w, const float *__re
       tw += s_w[q * H + j];
       td += s_w[(PARTS + q) * H + j];
     }
-    part_w[(size_t)blockIdx.x * H + j] = tw;
-    part_d[(size_t)blockIdx.x * H + j] = td;
+    part_w[(size_t)block * H + j] = tw;
+    part_d[(size_t)block * H + j] = td;
   }
   if (threadIdx.x == 0) {
-    part_loss[blockIdx.x] = ((s_red[0][0] + s_red[1][0]) + s_red[2][0]) + s_red[3][0];
-    part_b[blockIdx.x] = ((s_red[0][1] + s_red[1][1]) + s_red[2][1]) + s_red[3][1];
+    part_loss[block] = ((s_red[0][0] + s_red[1][0]) + s_red[2][0]) + s_red[3][0];
+    part_b[block] = ((s_red[0][1] + s_red[1][1]) + s_red[2][1]) + s_red[3][1];
   }
 }
 
@@ -196,7 +203,7 @@ int logit_blocks(int B) {
 // Forward logit + loss + delta of the last hidden layer; leaves the sums that launch_param_update applies.
 hipError_t launch_logit_loss(int dtype, const void *h, const void *wc_last, const float *bias_last, const float *label,
                              int B, int H, float *logits, float *dz, void *delta, float *partials,
-                             const int32_t *status, hipStream_t s) {
+                             const int32_t *status, hipStream_t s, const SideTask *side) {
   if (B <= 0) return hipSuccess;
   const int blocks = logit_blocks(B);
   const int rows_per_block = (B + blocks - 1) / blocks;
@@ -205,10 +212,20 @@ hipError_t launch_logit_loss(int dtype, const void *h, const void *wc_last, cons
         *part_loss = const_cast<float *>(sums.loss);
   // lanes per view and 16-byte pieces per lane, from the width of the last hidden layer
   const int n_vec = H / (dtype == GEAR_BF16 ? 8 : 4);
-#define GEAR_LOGIT(T, NV, G)                                                                                        \
-  hipLaunchKernelGGL((k_logit_loss<T, NV, G>), dim3(blocks), dim3(256), 2 * 4 * (kWave / G) * (size_t)H * sizeof(float), \
-                     s, (const T *)h, (const T *)wc_last, bias_last, label, B, H, rows_per_block, logits, dz,       \
-                     (T *)delta, part_w, part_d, part_b, part_loss, status)
+#define GEAR_LOGIT_S(T, NV, G, S, EXTRA, LDS, TASK)                                                                     \
+  hipLaunchKernelGGL((k_logit_loss<T, NV, G, S>), dim3(blocks + (EXTRA)), dim3(256), LDS, s, (const T *)h,              \
+                     (const T *)wc_last, bias_last, label, B, H, rows_per_block, logits, dz, (T *)delta, part_w, part_d, \
+                     part_b, part_loss, status, TASK)
+#define GEAR_LOGIT(T, NV, G)                                                         \
+  do {                                                                               \
+    const size_t lds = 2 * 4 * (kWave / G) * (size_t)H * sizeof(float);              \
+    if (side) {                                                                      \
+      const size_t needs = (size_t)radix_lds_bytes(side->gb);                         \
+      GEAR_LOGIT_S(T, NV, G, true, side->blocks, lds > needs ? lds : needs, *side);  \
+    } else {                                                                         \
+      GEAR_LOGIT_S(T, NV, G, false, 0, lds, NoTask{});                               \
+    }                                                                                \
+  } while (0)
 #define GEAR_LOGIT_T(T)                 \
   if (n_vec <= 32)                      \
     GEAR_LOGIT(T, 1, 32);               \
@@ -225,6 +242,7 @@ hipError_t launch_logit_loss(int dtype, const void *h, const void *wc_last, cons
   }
 #undef GEAR_LOGIT_T
 #undef GEAR_LOGIT
+#undef GEAR_LOGIT_S
   return hipGetLastError();
 }
 

@@ -1,9 +1,10 @@
 // The end of a step's parameter updates (Section 3, step 4), one launch: the weight gradients' partial sums of all hidden
-// layers, the logit layer's weights and bias, the hidden layers' biases, each followed by its update, and the loss.
+// layers, the logit layer's weights and bias, the hidden layers' biases, each followed by its update, and the loss; on a step that does not
+// divide dLoss/dx also the second level of the embedding update (update.hip).
 // They are small and wait for nothing but their partials: bound by a launch's own 4 us, which a launch per bias, one for
 // the logit layer and one for the weights each paid.  (A step of 4096 views on one stream: 150 us with those and the
 // second level of the embedding update in launches of their own, 136 without.)
-#include "gear_internal.hpp"
+#include "embedding_common.hpp"
 
 namespace gear {
 namespace {
@@ -101,10 +102,29 @@ struct ParamArgs {
   int columns_at, loss_at;      // first workgroup of the column sums, and the loss's
   LossSum loss;
 };
+struct SpanWork {
+  EmbeddingWork w;
+  int blocks;                   // workgroups per table, ahead of all others: the longest run is the longest chain
+};
+struct NoSpans {};
 
-__global__ void __launch_bounds__(256) k_param_update(ParamArgs args, Optim opt, const int32_t *__restrict__ status) {
+template <bool SPANS>
+__global__ void __launch_bounds__(256) k_param_update(ParamArgs args, std::conditional_t<SPANS, SpanWork, NoSpans> spans,
+                                                      Optim opt, const int32_t *__restrict__ status) {
   if (*status != 0) return;
-  const int block = blockIdx.x;
+  int block = blockIdx.x;
+  if constexpr (SPANS) {
+    if (block < 2 * spans.blocks) {
+      const int second = block >= spans.blocks ? 1 : 0;
+      const int chunk = (block - second * spans.blocks) * (256 / kWave) + threadIdx.x / kWave;
+      if (spans.w.bf16)
+        embedding_span<bf16_t, 16>(spans.w.table[second], chunk, spans.w.d, spans.w.opt);
+      else
+        embedding_span<float, 16>(spans.w.table[second], chunk, spans.w.d, spans.w.opt);
+      return;
+    }
+    block -= 2 * spans.blocks;
+  }
   if (block >= args.loss_at) {
     if (threadIdx.x < kWave) loss_final(args.loss.partial, args.loss.parts, args.loss.B, args.loss.loss);
   } else if (block >= args.columns_at) {
@@ -126,7 +146,8 @@ __global__ void __launch_bounds__(256) k_param_update(ParamArgs args, Optim opt,
 }  // namespace
 
 hipError_t launch_param_update(const SplitkProblem *p, int count, int splits, const ColumnSum *c, int n_columns,
-                               const LossSum &loss, const Optim &opt, const int32_t *status, hipStream_t s) {
+                               const LossSum &loss, const EmbeddingWork *emb, const Optim &opt, const int32_t *status,
+                               hipStream_t s) {
   if (count < 0 || count > GEAR_MAX_LAYERS || splits < 1 || n_columns < 0 || n_columns > kMaxColumnSums)
     return hipErrorInvalidValue;
   ParamArgs args;
@@ -148,8 +169,15 @@ hipError_t launch_param_update(const SplitkProblem *p, int count, int splits, co
   }
   args.loss_at = blocks;
   if (loss.parts > 0) ++blocks;
+  if (emb) {
+    SpanWork spans;
+    spans.w = *emb;
+    spans.blocks = (embedding_chunks(*emb) + 256 / kWave - 1) / (256 / kWave);
+    hipLaunchKernelGGL(k_param_update<true>, dim3(blocks + 2 * spans.blocks), dim3(256), 0, s, args, spans, opt, status);
+    return hipGetLastError();
+  }
   if (blocks == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_param_update, dim3(blocks), dim3(256), 0, s, args, opt, status);
+  hipLaunchKernelGGL(k_param_update<false>, dim3(blocks), dim3(256), 0, s, args, NoSpans{}, opt, status);
   return hipGetLastError();
 }
 
