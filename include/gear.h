@@ -115,7 +115,7 @@ typedef struct gear_step_out {
   void *profile;
   /* Nonzero: every kernel of the step is launched on the caller's stream, one after another, and
    * the helper stream is not used.  Same results; for timing each kernel alone, or for callers
-   * that want no second stream. */
+   * that want no second stream.  (With zero a step too short to gain from one does so as well.) */
   int32_t one_stream;
 } gear_step_out;
 

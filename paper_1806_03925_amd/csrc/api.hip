@@ -550,7 +550,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
     const int bits[kMaxProblems] = {bits_for(cfg->n_users), bits_for(cfg->n_urls), bits_for(cfg->n_images)};
     int passes = 1;   // the lists share launches: as many passes for all as the widest ids need
     for (int i = 0; i < kMaxProblems; ++i) {
-      const int need = radix_passes(bits[i], lay.g[i].total_words, carried ? kSideDigitBits : kMaxDigitBits);
+      const int need = radix_passes(bits[i], lay.g[i].total_words, carried ? kSideDigitBits : widest_digit(B > b->nnz ? B : b->nnz));
       if (need > passes) passes = need;
     }
     // a pass that is carried costs nothing but its length, and narrow digits make it short: as many as find a launch ahead
@@ -820,7 +820,7 @@ gear_status gear_group_ids(const gear_config *cfg, const int32_t *keys, int32_t 
   GroupBatch gb;
   gb.count = 1;
   const int bits = bits_for(key_range);
-  gb.p[0] = make_problem(lay, ws, 2, keys, n, 0, radix_passes(bits, lay.g[2].total_words, kMaxDigitBits), bits);
+  gb.p[0] = make_problem(lay, ws, 2, keys, n, 0, radix_passes(bits, lay.g[2].total_words, widest_digit(n)), bits);
   gb.tickets = (int32_t *)(ws + lay.tickets);
   gb.seg_state = (uint32_t *)(ws + lay.seg_state);
   ZeroList zero;

@@ -118,7 +118,7 @@ constexpr int kMaxProblems = 3;
 constexpr int kMaxPasses = 3;
 constexpr int kMaxDigitBits = 12;
 constexpr int kSideDigitBits = 11;                    // of passes that other launches carry
-constexpr int kLongList = 65536;                      // ids from which a workgroup of the check takes several tiles
+constexpr int kLongList = 65536;                      // ids from which a workgroup of the check takes several tiles, and a step's products are large
 // Counts a tile publishes over all passes, at most.  A pass costs a launch and two memory latencies whatever its
 // radix, so a list takes as few passes as its keys allow within this (one up to 12 bits, two up to 22, then three);
 // it is what the regions that hold the counts have room for (24 KB per tile of 2048 keys).
@@ -148,6 +148,11 @@ struct GroupBatch {
   int32_t *tickets;               // [kTickets]
   uint32_t *seg_state;            // [tiles - 1][3] heads, units and emissions, published like `state`
 };
+
+// The widest digits a list of n ids is sorted by in launches of their own: a wide digit saves a pass of a short list, but a
+// tile looks back at up to all before it for every digit (139 000 ids, 22 bits: two passes of eleven bits 39 and 43 us
+// beside a product, three of eight bits 12 us each).
+inline int widest_digit(int n) { return n > 16 * kSortTile ? 9 : kMaxDigitBits; }
 
 // fewest passes over keys of `bits` bits in digits of up to `widest` bits
 inline int radix_passes(int bits, int most_words, int widest) {
