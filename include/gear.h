@@ -30,7 +30,9 @@
  * through the return value and nothing is enqueued.  What only the device can
  * see (an id outside its table, offsets that are not a CSR index, a ready list
  * longer than ready_cap) is written to the device word `status`, and the step
- * then leaves every table, accumulator and counter as it was.
+ * then leaves every table, accumulator and counter as it was.  A step writes that
+ * word and never reads it (it keeps its own in the workspace): other calls may
+ * report into the same word while a step runs without disturbing the step.
  */
 #ifndef GEAR_H
 #define GEAR_H

@@ -227,6 +227,7 @@ bool make_layout(const gear_config &c, Layout *lay) {
   lay->row_view = take(&cur, NNZ * sizeof(int32_t));
   lay->row_scale = take(&cur, NNZ * sizeof(float));
   lay->n_units = take(&cur, sizeof(int32_t));
+  lay->failed = lay->n_units + kAlign / 2;   // in the same line of kAlign bytes
   lay->expiry_marks = take(&cur, (size_t)expiry_words(c.n_images) * sizeof(uint32_t));
   lay->expiry_tiles = take(&cur, (size_t)expiry_tiles(c.n_images) * sizeof(int32_t));
   lay->total = cur;
@@ -522,7 +523,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   hipStream_t s = (hipStream_t)stream;
   char *ws = (char *)workspace;
   const int B = b->B, L = lay.L, F = lay.F, dt = cfg->mlp_dtype;
-  int32_t *status = out->status;
+  int32_t *failed = (int32_t *)(ws + lay.failed);   // what the step's kernels look at; out->status is told as well
 
   gear_profile *prof = (gear_profile *)out->profile;
   if (prof) prof->used = 0;
@@ -532,7 +533,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
                                                       "dgrad_gemm_l3", "dgrad_gemm_l4", "dgrad_gemm_l5",
                                                       "dgrad_gemm_l6", "dgrad_gemm_l7"};
   if (B == 0) {
-    GEAR_RUN("begin", launch_begin(status, out->n_ready, out->loss, ZeroList{}, dt, nullptr, 0, s));
+    GEAR_RUN("begin", launch_begin(out->status, failed, out->n_ready, out->loss, ZeroList{}, dt, nullptr, 0, s));
     return GEAR_OK;
   }
   int32_t *occ_view = (int32_t *)(ws + lay.occ_view);
@@ -570,7 +571,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   plan.row_view = (int32_t *)(ws + lay.row_view);
   plan.row_scale = (float *)(ws + lay.row_scale);
   plan.n_units = (int32_t *)(ws + lay.n_units);
-  const PlanArgs plan_args = {plan, occ_view, b->img_off, counts, M, out->ready_cap, out->n_ready};
+  const PlanArgs plan_args = {plan, occ_view, b->img_off, counts, M, out->ready_cap, out->n_ready, out->status};
   // Not carried: what depends only on ids and counters (the check of the ids, the grouping, the accumulation plan) runs on
   // the helper stream while the main stream gathers and runs the forward pass.  The
   // main stream waits for it before the first kernel that changes caller state, so the status word
@@ -589,7 +590,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
       jobs[l] = CastJob{t->mlp_params + lay.w_off[l], ws + lay.wc[l], ws + lay.wct[l], lay.out_dim[l], lay.in_dim[l]};
     ZeroList zero;
     group_zero_list(gb, &zero);
-    GEAR_RUN("begin", launch_begin(status, out->n_ready, out->loss, zero, dt, jobs, L, s));
+    GEAR_RUN("begin", launch_begin(out->status, failed, out->n_ready, out->loss, zero, dt, jobs, L, s));
   }
   if (!carried) GEAR_HIP(lane.fork());
   // Carried: the links of the grouping in order, each taken by the next launch that can.
@@ -598,12 +599,12 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   const int links = carried ? group_passes(gb) + 1 : 0;
   auto passenger = [&]() -> const SideTask * {
     if (link >= links) return nullptr;
-    task = side_task(gb, plan_args, link++, status);
+    task = side_task(gb, plan_args, link++, failed);
     return &task;
   };
   auto links_left = [&]() -> gear_status {   // those that found no launch to ride in
     for (; link < links; ++link)
-      GEAR_RUN("group_ids", link + 1 < links ? launch_radix_pass(gb, link, status, s) : launch_segments(gb, &plan_args, status, s));
+      GEAR_RUN("group_ids", link + 1 < links ? launch_radix_pass(gb, link, failed, s) : launch_segments(gb, &plan_args, failed, s));
     return GEAR_OK;
   };
 #define GEAR_BOARD()                                       \
@@ -618,7 +619,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   for (int l = L - 2; l >= 0; --l)
     wp[n_wp++] = TnProblem{ws + lay.delta[l], l == 0 ? x : ws + lay.h[l - 1], nullptr, lay.out_dim[l], lay.in_dim[l]};
   {
-    const CheckTask check = check_task(gb, b->img_off, occ_view, B, b->nnz, status);
+    const CheckTask check = check_task(gb, b->img_off, occ_view, B, b->nnz, failed, out->status);
     if (carried && fail_injected()) return GEAR_ERR_HIP;
     GEAR_RUN("gather_pool", launch_gather_pool(*cfg, *b, *t, dfv_cache, x, s, carried ? &check : nullptr));
   }
@@ -638,9 +639,9 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   // after the host has issued the grouping's launches.
   if (!carried) {
     hipStream_t s = helper;  // the launches of this block go to the helper stream
-    GEAR_RUN("group_ids", launch_check(gb, b->img_off, occ_view, B, b->nnz, status, s));
-    for (int pass = 0; pass < group_passes(gb); ++pass) GEAR_RUN("group_ids", launch_radix_pass(gb, pass, status, s));
-    GEAR_RUN("accum_plan", launch_segments(gb, &plan_args, status, s));
+    GEAR_RUN("group_ids", launch_check(gb, b->img_off, occ_view, B, b->nnz, failed, out->status, s));
+    for (int pass = 0; pass < group_passes(gb); ++pass) GEAR_RUN("group_ids", launch_radix_pass(gb, pass, failed, s));
+    GEAR_RUN("accum_plan", launch_segments(gb, &plan_args, failed, s));
     GEAR_HIP(lane.mark_checked());
   }
 
@@ -652,7 +653,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   GEAR_BOARD();
   GEAR_RUN("logit_loss", launch_logit_loss(dt, ws + lay.h[L - 2], ws + lay.wc[L - 1], t->mlp_params + lay.b_off[L - 1],
                                            b->label, B, lay.in_dim[L - 1], logits, dz, ws + lay.delta[L - 2],
-                                           (float *)(ws + lay.loss_partial), status, s, passenger()));
+                                           (float *)(ws + lay.loss_partial), failed, s, passenger()));
 
   // backward through the hidden layers down to dLoss/dx (all from the pre-step operand copies)
   // Each product that makes the delta of a hidden layer also leaves that layer's bias gradient (column
@@ -700,8 +701,8 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
         GEAR_HIP(lane.fork());
         {
           hipStream_t s = helper;
-          GEAR_RUN("small_sums", launch_param_update(nullptr, 0, 1, columns, n_columns, loss, nullptr, opt, status, s));
-          GEAR_RUN("embedding_update", launch_embedding_update(emb, true, status, s));
+          GEAR_RUN("small_sums", launch_param_update(nullptr, 0, 1, columns, n_columns, loss, nullptr, opt, failed, s));
+          GEAR_RUN("embedding_update", launch_embedding_update(emb, true, failed, s));
         }
         divided = true;
         GEAR_RUN(kDgrad[0], launch_gemm_nt(dt, ws + lay.delta[0],
@@ -726,9 +727,9 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   GEAR_HIP(lane.fork());
   {
     hipStream_t s = helper;
-    if (!divided && !one_stream) GEAR_RUN("embedding_update", launch_embedding_update(emb, false, status, s));
+    if (!divided && !one_stream) GEAR_RUN("embedding_update", launch_embedding_update(emb, false, failed, s));
     GEAR_RUN("accumulate", launch_accumulate(*cfg, gb.p[2], plan, dx_dfv, grad_accum, M, out->ready_ids, out->ready_grads,
-                                             divided ? nullptr : &emb, !one_stream, status, s));
+                                             divided ? nullptr : &emb, !one_stream, failed, s));
   }
   GEAR_HIP(lane.mark());
   // SGD on the hidden layers' weights: split-K wgrad.  With the last of them go the small sums, unless they are done.
@@ -763,7 +764,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
     first += n;
     const bool sums_too = first == n_wp && !divided;   // else the helper stream has done them
     GEAR_RUN("param_update", launch_param_update(sp, n, splits, columns, sums_too ? n_columns : 0, sums_too ? loss : LossSum{},
-                                                 sums_too && one_stream ? &emb : nullptr, opt, status, s));
+                                                 sums_too && one_stream ? &emb : nullptr, opt, failed, s));
   }
   GEAR_HIP(lane.wait(true));  // the step ends on the caller's stream
   if (out->dbg_img_unique && b->nnz > 0)
@@ -816,7 +817,7 @@ gear_status gear_group_ids(const gear_config *cfg, const int32_t *keys, int32_t 
   if (workspace_bytes < lay.total) return GEAR_ERR_CAPACITY;
   hipStream_t s = (hipStream_t)stream;
   char *ws = (char *)workspace;
-  int32_t *status = (int32_t *)(ws + lay.n_units);  // a spare word, cleared below: nothing can fail here
+  int32_t *failed = (int32_t *)(ws + lay.failed);  // cleared below: nothing can fail here
   GroupBatch gb;
   gb.count = 1;
   const int bits = bits_for(key_range);
@@ -825,12 +826,12 @@ gear_status gear_group_ids(const gear_config *cfg, const int32_t *keys, int32_t 
   gb.seg_state = (uint32_t *)(ws + lay.seg_state);
   ZeroList zero;
   group_zero_list(gb, &zero);
-  zero.p[zero.count] = (uint32_t *)status;
+  zero.p[zero.count] = (uint32_t *)failed;
   zero.words[zero.count++] = 1;
   GEAR_HIP(launch_clear(zero, s));
-  GEAR_HIP(launch_check(gb, nullptr, nullptr, 0, 0, status, s));
-  for (int pass = 0; pass < group_passes(gb); ++pass) GEAR_HIP(launch_radix_pass(gb, pass, status, s));
-  GEAR_HIP(launch_segments(gb, nullptr, status, s));
+  GEAR_HIP(launch_check(gb, nullptr, nullptr, 0, 0, failed, failed, s));
+  for (int pass = 0; pass < group_passes(gb); ++pass) GEAR_HIP(launch_radix_pass(gb, pass, failed, s));
+  GEAR_HIP(launch_segments(gb, nullptr, failed, s));
   if (n > 0) {
     GEAR_HIP(hipMemcpyAsync(unique, gb.p[0].unique, (size_t)n * 4, hipMemcpyDeviceToDevice, s));
     GEAR_HIP(hipMemcpyAsync(perm, gb.p[0].perm, (size_t)n * 4, hipMemcpyDeviceToDevice, s));

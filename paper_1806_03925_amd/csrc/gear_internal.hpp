@@ -183,6 +183,12 @@ struct AccumPlan {
 };
 
 // ---- tasks of the grouping (group.hip) ----
+// What goes wrong in a step is noted twice: in the caller's status word, and in a word of the step's own workspace
+// (`failed`), which is the one that later kernels look at before they do anything.  The caller's may be written by other
+// calls while a step runs (a refresh on another stream reports its ids there), and workgroups of one launch that read it at
+// different times would not agree on whether to work: those that do wait for what the others publish (group_device.hpp).
+// Only launches of the step write `failed`, and a launch that reads it begins after the last one that may set it, but for
+// the tile that finds the ready list too long when all others have read it.
 struct ViewCheck {
   const int32_t *img_off;
   int32_t *occ_view;
@@ -192,13 +198,13 @@ struct CheckTask {
   GroupBatch gb;
   ViewCheck views;
   int blocks, tiles_per_block;
-  int32_t *status;
+  int32_t *failed, *status;
 };
 struct PlanArgs {
   AccumPlan plan;
   const int32_t *occ_view, *img_off, *counts;
   int32_t M, ready_cap;
-  int32_t *n_ready;
+  int32_t *n_ready, *status;
 };
 // one link of the grouping that a launch of the forward pass carries (group_device.hpp)
 struct SideTask {
@@ -207,7 +213,7 @@ struct SideTask {
   int blocks;       // workgroups, a multiple of the XCDs' number so that the products' stay on the XCDs they share operands on
   GroupBatch gb;
   PlanArgs plan;
-  int32_t *status;
+  int32_t *failed;
 };
 struct NoTask {};
 
@@ -230,7 +236,7 @@ struct Layout {
   size_t wc[GEAR_MAX_LAYERS], wct[GEAR_MAX_LAYERS], wgrad_partial, colsum_partial, emb_partial;
   size_t colsum_at[GEAR_MAX_LAYERS]; // floats before the column-sum partials that layer l's masked product leaves
   size_t wgrad_partial_bytes;        // size of the split-K partial region
-  size_t occ_view;
+  size_t occ_view, failed;
   struct G {
     size_t keys[2], vals[2], totals, state, unique, segoff, n_unique;
     int32_t total_words;             // room for `totals`
@@ -267,18 +273,19 @@ struct CastJob {
   int rows, cols;
 };
 hipError_t launch_clear(const ZeroList &zero, hipStream_t s);
-hipError_t launch_begin(int32_t *status, int32_t *n_ready, float *loss, const ZeroList &zero, int dtype, const CastJob *jobs,
+hipError_t launch_begin(int32_t *status, int32_t *failed, int32_t *n_ready, float *loss, const ZeroList &zero, int dtype, const CastJob *jobs,
                         int count, hipStream_t s);
 void group_zero_list(const GroupBatch &gb, ZeroList *z);
-CheckTask check_task(const GroupBatch &gb, const int32_t *img_off, int32_t *occ_view, int B, int nnz, int32_t *status);
+CheckTask check_task(const GroupBatch &gb, const int32_t *img_off, int32_t *occ_view, int B, int nnz, int32_t *failed,
+                     int32_t *status);
 int check_lds_bytes(const GroupBatch &gb);
 int group_passes(const GroupBatch &gb);
-SideTask side_task(const GroupBatch &gb, const PlanArgs &plan, int step, int32_t *status);   // step: a pass, or the segments behind them
+SideTask side_task(const GroupBatch &gb, const PlanArgs &plan, int step, int32_t *failed);   // step: a pass, or the segments behind them
 int radix_lds_bytes(const GroupBatch &gb);
-hipError_t launch_check(const GroupBatch &gb, const int32_t *img_off, int32_t *occ_view, int B, int nnz, int32_t *status,
-                        hipStream_t s);
-hipError_t launch_radix_pass(const GroupBatch &gb, int pass, const int32_t *status, hipStream_t s);
-hipError_t launch_segments(const GroupBatch &gb, const PlanArgs *args, int32_t *status, hipStream_t s);
+hipError_t launch_check(const GroupBatch &gb, const int32_t *img_off, int32_t *occ_view, int B, int nnz, int32_t *failed,
+                        int32_t *status, hipStream_t s);
+hipError_t launch_radix_pass(const GroupBatch &gb, int pass, const int32_t *failed, hipStream_t s);
+hipError_t launch_segments(const GroupBatch &gb, const PlanArgs *args, int32_t *failed, hipStream_t s);
 // distinct ids of a grouped list whose cache entry is older than `expiry`, ascending
 // words (four images each) of the byte map over all images that the expiry filter marks, and tiles
 // of kSortTile words

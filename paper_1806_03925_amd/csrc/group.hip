@@ -165,10 +165,12 @@ void group_zero_list(const GroupBatch &gb, ZeroList *z) {
 
 // A workgroup that checks takes one tile of a short list, so that as many CUs as possible work on it, and four tiles of a
 // long one, so that fewer workgroups add to the digits' totals (a list of more than 65 536 ids has 32 tiles and more).
-CheckTask check_task(const GroupBatch &gb, const int32_t *img_off, int32_t *occ_view, int B, int nnz, int32_t *status) {
+CheckTask check_task(const GroupBatch &gb, const int32_t *img_off, int32_t *occ_view, int B, int nnz, int32_t *failed,
+                     int32_t *status) {
   CheckTask t;
   t.gb = gb;
   t.views = ViewCheck{img_off, occ_view, B, nnz};
+  t.failed = failed;
   t.status = status;
   t.tiles_per_block = 1;
   for (int i = 0; i < gb.count; ++i)
@@ -198,13 +200,13 @@ static int widest_radix(const GroupBatch &gb) {
 }
 int radix_lds_bytes(const GroupBatch &gb) { return (int)(sizeof(int) + kSortBlock / kWave * sizeof(uint16_t)) * widest_radix(gb); }
 
-SideTask side_task(const GroupBatch &gb, const PlanArgs &plan, int step, int32_t *status) {
+SideTask side_task(const GroupBatch &gb, const PlanArgs &plan, int step, int32_t *failed) {
   SideTask t;
   t.kind = step < group_passes(gb) ? SideTask::kPass : SideTask::kSegments;
   t.pass = step;
   t.gb = gb;
   t.plan = plan;
-  t.status = status;
+  t.failed = failed;
   t.blocks = 0;
   if (t.kind == SideTask::kPass)
     for (int i = 0; i < gb.count; ++i) t.blocks += radix_tiles(gb.p[i].n);
@@ -226,51 +228,51 @@ __global__ void __launch_bounds__(kSortBlock) k_check_and_count(CheckTask t) {
 // 65 536 views took 991 us with 114 registers here and 123 in k_segments, 985 with 102 and 116, 973 with 102 and 96 (and a
 // dozen spilled).
 template <int BITS>
-__global__ void __launch_bounds__(kSortBlock) k_radix_pass(GroupBatch gb, int pass, const int32_t *status) {
-  const bool idle = *status != 0;
+__global__ void __launch_bounds__(kSortBlock) k_radix_pass(GroupBatch gb, int pass, const int32_t *failed) {
+  const bool idle = *failed != 0;
   if ((int)blockIdx.x >= radix_tiles(gb.p[blockIdx.y].n)) return;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   radix_pass_any<BITS, BITS <= 9 ? 4 : 16>(gb, blockIdx.y, pass, idle, lds);
 }
 
 template <bool PLAN, bool BESIDE>
-__global__ void __launch_bounds__(kSortBlock, BESIDE ? 5 : 1) k_segments(GroupBatch gb, PlanArgs args, int32_t *status) {
-  segments<PLAN>(gb, args, blockIdx.x, status);
+__global__ void __launch_bounds__(kSortBlock, BESIDE ? 5 : 1) k_segments(GroupBatch gb, PlanArgs args, int32_t *failed) {
+  segments<PLAN>(gb, args, blockIdx.x, failed);
 }
 }  // namespace
 
-hipError_t launch_check(const GroupBatch &gb, const int32_t *img_off, int32_t *occ_view, int B, int nnz, int32_t *status,
-                        hipStream_t s) {
-  const CheckTask t = check_task(gb, img_off, occ_view, B, nnz, status);
+hipError_t launch_check(const GroupBatch &gb, const int32_t *img_off, int32_t *occ_view, int B, int nnz, int32_t *failed,
+                        int32_t *status, hipStream_t s) {
+  const CheckTask t = check_task(gb, img_off, occ_view, B, nnz, failed, status);
   if (t.blocks == 0) return hipSuccess;
   hipLaunchKernelGGL(k_check_and_count, dim3(t.blocks), dim3(kSortBlock), check_lds_bytes(gb), s, t);
   return hipGetLastError();
 }
 
-hipError_t launch_radix_pass(const GroupBatch &gb, int pass, const int32_t *status, hipStream_t s) {
+hipError_t launch_radix_pass(const GroupBatch &gb, int pass, const int32_t *failed, hipStream_t s) {
   int tiles = 0;
   for (int i = 0; i < gb.count; ++i)
     if (radix_tiles(gb.p[i].n) > tiles) tiles = radix_tiles(gb.p[i].n);
   if (tiles == 0) return hipSuccess;
   if (widest_radix(gb) > 512)
-    hipLaunchKernelGGL(k_radix_pass<kMaxDigitBits>, dim3(tiles, gb.count), dim3(kSortBlock), radix_lds_bytes(gb), s, gb, pass, status);
+    hipLaunchKernelGGL(k_radix_pass<kMaxDigitBits>, dim3(tiles, gb.count), dim3(kSortBlock), radix_lds_bytes(gb), s, gb, pass, failed);
   else
-    hipLaunchKernelGGL(k_radix_pass<9>, dim3(tiles, gb.count), dim3(kSortBlock), radix_lds_bytes(gb), s, gb, pass, status);
+    hipLaunchKernelGGL(k_radix_pass<9>, dim3(tiles, gb.count), dim3(kSortBlock), radix_lds_bytes(gb), s, gb, pass, failed);
   return hipGetLastError();
 }
 
 // segments of the last list; with `args` also the plan of the accumulation
-hipError_t launch_segments(const GroupBatch &gb, const PlanArgs *args, int32_t *status, hipStream_t s) {
+hipError_t launch_segments(const GroupBatch &gb, const PlanArgs *args, int32_t *failed, hipStream_t s) {
   const int tiles = (int)(((int64_t)gb.p[gb.count - 1].n + kSortTile - 1) / kSortTile);
   // Beside the large products of a long step: few registers.  A short step has none, and what spills costs it (10 001 views,
   // 45 000 occurrences: 144 us with, 141 without).
   const dim3 grid(tiles < 1 ? 1 : tiles);
   if (!args)
-    hipLaunchKernelGGL((k_segments<false, false>), grid, dim3(kSortBlock), 0, s, gb, PlanArgs{}, status);
+    hipLaunchKernelGGL((k_segments<false, false>), grid, dim3(kSortBlock), 0, s, gb, PlanArgs{}, failed);
   else if (gb.p[gb.count - 1].n > kLongList)
-    hipLaunchKernelGGL((k_segments<true, true>), grid, dim3(kSortBlock), 0, s, gb, *args, status);
+    hipLaunchKernelGGL((k_segments<true, true>), grid, dim3(kSortBlock), 0, s, gb, *args, failed);
   else
-    hipLaunchKernelGGL((k_segments<true, false>), grid, dim3(kSortBlock), 0, s, gb, *args, status);
+    hipLaunchKernelGGL((k_segments<true, false>), grid, dim3(kSortBlock), 0, s, gb, *args, failed);
   return hipGetLastError();
 }
 

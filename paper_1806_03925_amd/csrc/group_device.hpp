@@ -40,7 +40,8 @@ __device__ __forceinline__ int block_exclusive_scan(int v, int *total, int *smem
 // count c.  A word carries its own value, so no order between stores matters and relaxed accesses do; agent scope,
 // because the tiles run on several XCDs.  Tiles are numbered by a ticket that a workgroup draws when it starts, not by
 // its place in the grid: whoever waits for a word waits for a workgroup that is already running and that publishes its
-// own count before it waits for anybody, so every wait ends whatever else occupies the device.
+// own count before it waits for anybody, so every wait ends whatever else occupies the device.  A workgroup that stays idle
+// publishes nothing, so all of a launch have to agree on that: they look at `failed`, which no other call writes.
 constexpr uint32_t kPrefix = 0x80000000u;
 __device__ __forceinline__ void publish(uint32_t *word, uint32_t v) {
   __hip_atomic_store(word, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -57,7 +58,10 @@ __device__ __forceinline__ int draw_ticket(int32_t *counter) {
 // a list of image ids (Section 1, Table 1); every id later indexes a table, so a bad id must be caught before any
 // kernel that changes caller state dereferences it: a violation sets the status word and every later kernel of the
 // step returns at once.  Also expands the CSR offsets into occ_view[j] = the view that owns occurrence j.
-__device__ __forceinline__ void flag(int32_t *status, int code) { atomicCAS(status, 0, code); }
+__device__ __forceinline__ void flag(int32_t *failed, int32_t *status, int code) {
+  atomicCAS(failed, 0, code);
+  atomicCAS(status, 0, code);
+}
 
 // Workgroup `block` of those that check: list by list, then the views.
 __device__ __forceinline__ void check_and_count(const CheckTask &t, int block, int *hist /* [pass][digit] */) {
@@ -74,7 +78,7 @@ __device__ __forceinline__ void check_and_count(const CheckTask &t, int block, i
     if (i >= views.B) return;
     const int32_t lo = views.img_off[i], hi = views.img_off[i + 1];
     const bool ok = lo >= 0 && lo <= hi && hi <= views.nnz;
-    if (!ok || (i == 0 && lo != 0) || (i == views.B - 1 && hi != views.nnz)) flag(t.status, GEAR_ERR_RANGE);
+    if (!ok || (i == 0 && lo != 0) || (i == views.B - 1 && hi != views.nnz)) flag(t.failed, t.status, GEAR_ERR_RANGE);
     if (ok)
       for (int j = lo; j < hi; ++j) views.occ_view[j] = i;
     return;
@@ -97,7 +101,7 @@ __device__ __forceinline__ void check_and_count(const CheckTask &t, int block, i
         for (int pass = 0; pass < p.passes; ++pass)
           atomicAdd(&hist[(pass << p.digit_bits) + ((key[i] >> (pass * p.digit_bits)) & (radix - 1))], 1);
       }
-    if (bad && p.range > 0) flag(t.status, GEAR_ERR_RANGE);
+    if (bad && p.range > 0) flag(t.failed, t.status, GEAR_ERR_RANGE);
   }
   __syncthreads();
   for (int d = threadIdx.x; d < words; d += kSortBlock)
@@ -281,8 +285,8 @@ __device__ __forceinline__ void radix_pass_any(const GroupBatch &gb, int list, i
 // requested together and none is behind a branch; the chain is ticket -> keys -> counters, start and end of the
 // segments that cross the tile's borders -> flags -> look-back -> descriptors.
 template <bool PLAN>
-__device__ __forceinline__ void segments(const GroupBatch &gb, const PlanArgs &args, int block, int32_t *status) {
-  const bool idle = *status != 0;
+__device__ __forceinline__ void segments(const GroupBatch &gb, const PlanArgs &args, int block, int32_t *failed) {
+  const bool idle = *failed != 0;
   const GroupProblem &p = gb.p[gb.count - 1];
   const AccumPlan &plan = args.plan;
   uint32_t *state = gb.seg_state;
@@ -523,10 +527,10 @@ __device__ __forceinline__ void segments(const GroupBatch &gb, const PlanArgs &a
     if constexpr (PLAN) {
       *plan.n_units = s_base[1] + own[1];
       // a list that does not fit is reported as empty: nobody may read ready_ids past ready_cap.  Every other tile has
-      // read the status word by now: it did so before it published the counts that this one has seen
+      // read `failed` by now: it did so before it published the counts that this one has seen
       const int emits = s_base[2] + own[2];
       *args.n_ready = emits > args.ready_cap ? 0 : emits;
-      if (emits > args.ready_cap) atomicCAS(status, 0, GEAR_ERR_CAPACITY);
+      if (emits > args.ready_cap) flag(failed, args.status, GEAR_ERR_CAPACITY);
     }
   }
 }
@@ -540,10 +544,10 @@ __device__ __forceinline__ void segments(const GroupBatch &gb, const PlanArgs &a
 __device__ __forceinline__ void side_work(const SideTask &t, int block, unsigned char *lds) {
   if (t.kind == SideTask::kSegments) {
     const int n = t.gb.p[t.gb.count - 1].n;
-    if (block < max(1, (int)(((int64_t)n + kSortTile - 1) / kSortTile))) segments<true>(t.gb, t.plan, block, t.status);
+    if (block < max(1, (int)(((int64_t)n + kSortTile - 1) / kSortTile))) segments<true>(t.gb, t.plan, block, t.failed);
     return;
   }
-  const bool idle = *t.status != 0;
+  const bool idle = *t.failed != 0;
   for (int list = 0; list < t.gb.count; ++list) {
     const int tiles = radix_tiles(t.gb.p[list].n);
     if (block < tiles) return radix_pass_any<kSideDigitBits, 16>(t.gb, list, t.pass, idle, lds);

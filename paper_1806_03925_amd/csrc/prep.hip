@@ -24,9 +24,10 @@ __global__ void __launch_bounds__(256) k_clear(ZeroList zero) {
 }
 
 template <typename T>
-__global__ void __launch_bounds__(256) k_begin(BeginArgs args, int32_t *status, int32_t *n_ready, float *loss) {
+__global__ void __launch_bounds__(256) k_begin(BeginArgs args, int32_t *status, int32_t *failed, int32_t *n_ready, float *loss) {
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     *status = 0;
+    *failed = 0;
     *n_ready = 0;
     *loss = 0.0f;
   }
@@ -78,7 +79,7 @@ hipError_t launch_clear(const ZeroList &zero, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_begin(int32_t *status, int32_t *n_ready, float *loss, const ZeroList &zero, int dtype, const CastJob *jobs,
+hipError_t launch_begin(int32_t *status, int32_t *failed, int32_t *n_ready, float *loss, const ZeroList &zero, int dtype, const CastJob *jobs,
                         int count, hipStream_t s) {
   if (count < 0 || count > GEAR_MAX_LAYERS) return hipErrorInvalidValue;
   BeginArgs args;
@@ -92,9 +93,9 @@ hipError_t launch_begin(int32_t *status, int32_t *n_ready, float *loss, const Ze
   }
   const dim3 grid((unsigned)(args.cast_blocks + clear_blocks(zero)));
   if (dtype == GEAR_BF16)
-    hipLaunchKernelGGL(k_begin<bf16_t>, grid, dim3(256), 0, s, args, status, n_ready, loss);
+    hipLaunchKernelGGL(k_begin<bf16_t>, grid, dim3(256), 0, s, args, status, failed, n_ready, loss);
   else
-    hipLaunchKernelGGL(k_begin<float>, grid, dim3(256), 0, s, args, status, n_ready, loss);
+    hipLaunchKernelGGL(k_begin<float>, grid, dim3(256), 0, s, args, status, failed, n_ready, loss);
   return hipGetLastError();
 }
 

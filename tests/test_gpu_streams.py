@@ -1,0 +1,60 @@
+"""Steps beside other work on the same device: what other streams do to words and stores that a step shares with them."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def state_of(name, batch, **changes):
+    import paper_1806_03925_amd as g
+    from gear_inputs import PageViewSource, get_workload
+    wl = get_workload(name).scaled(n_users=50_000, n_urls=1 << 15, n_images=4_000, M=4, **changes)
+    st = g.GearState(g.config_for(wl, max_batch=batch))
+    g.gear_init_tables(st)
+    g.gear_fill_normal(st.dfv_cache, wl.n_images, wl.dfv_dim, wl.seed, 3, wl.dfv_std)
+    return wl, st, PageViewSource(wl)
+
+
+def outputs(st):
+    n = int(st.n_ready.item())
+    return [t.clone() for t in (st.loss, st.n_ready, st.ready_ids[:n], st.ready_grads[:n], st.grad_accum, st.counts,
+                                st.user_emb, st.url_emb, st.mlp_params)]
+
+
+@pytest.mark.parametrize("name,batch,changes", [
+    ("tiny", 511, {}),                         # one tile of each list, carried by other launches
+    ("small", 4_096, {}),                      # carried, several tiles that look back
+    ("bf16", 9_001, {}),                       # grouping on the helper stream
+    ("large", 8_192, {"max_images": 40}),      # helper stream, long lists, dLoss/dx in two products
+])
+def test_a_step_does_not_read_the_status_word_that_others_write(name, batch, changes):
+    """Two calls on another stream report bad ids into the step's status word and clear it again, over and over, while the
+    steps run.  Workgroups that wait for one another must not decide by that word whether to work: every step has to end
+    with the bits it gets when it runs alone."""
+    import paper_1806_03925_amd as g
+    results = []
+    for disturbed in (False, True):
+        wl, st, src = state_of(name, batch, **changes)
+        dev = [g.DeviceBatch.from_host(src.batch(t, batch=batch)) for t in range(4)]
+        other = g.GearState(g.make_config(16, 16, 16, 8, 8, (8, 1), max_batch=1, max_nnz=64))
+        other.status = st.status                                   # one word for all that goes on with a cache
+        bad = torch.full((64,), 16, dtype=torch.int32, device="cuda")
+        rows = torch.zeros((64, 8), device="cuda")
+        stamp = torch.zeros(16, dtype=torch.int32, device="cuda")
+        good = torch.zeros(1, dtype=torch.int32, device="cuda")
+        beside = torch.cuda.Stream()
+        torch.cuda.synchronize()
+        for t in range(4):
+            print(f"{name} disturbed {disturbed} step {t}", flush=True)
+            if disturbed:
+                with torch.cuda.stream(beside):
+                    for _ in range(20):
+                        g.gear_refresh_dfv(other, bad, rows)           # sets the word, writes no row
+                        g.gear_expired_ids(other, good, stamp, 0, 1)   # clears it
+            g.gear_step(st, dev[t], wl.M, 0.1)
+        torch.cuda.synchronize()
+        results.append(outputs(st))
+    assert int(results[0][1].item()) > 0
+    for a, b in zip(*results):
+        assert torch.equal(a, b)
