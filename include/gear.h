@@ -12,15 +12,18 @@
  *
  * This library is that per-step work.  All pointers named "device" are device
  * memory owned by the caller; the library allocates no device memory and keeps
- * no state between calls except one helper stream and three events per device,
- * created at the first gear_step (default priority; part of a step runs on it,
- * forked from and joined back into the caller's stream).  Calls enqueue their
- * kernels on the given hipStream_t (passed as void*) and return without
- * synchronising.  Results are valid once the caller has synchronised that
+ * no state between calls except one helper stream and five events per device,
+ * created at the first gear_step that uses them (default priority; part of a long step
+ * runs on the helper stream, forked from and joined back into the caller's stream).
+ * Calls enqueue their kernels on the given hipStream_t (passed as void*) and return
+ * without synchronising.  Results are valid once the caller has synchronised that
  * stream.  The stream must belong to the current device.  The entry points may
  * be called from several host threads; steps issued on one device are enqueued
- * one after the other (a per-device lock is held while a step enqueues) and
- * share the helper stream, so they run in the order they were issued.  Each
+ * one after the other (a per-device lock is held while a step enqueues), and what
+ * they do to counts and grad_accum happens in the order they were issued, also from
+ * different streams: steps with tables of their own may share such a store.  (Steps
+ * with one_stream set, gear_step_static and steps being captured into a graph take no
+ * part in that order: they run in their stream's, or their graph's.)  Each
  * step needs a workspace of its own while it is in flight.  If a call returns
  * GEAR_ERR_HIP part-way through its enqueue, whatever it had put on the helper
  * stream is still joined back into the caller's stream before it returns.
@@ -117,7 +120,8 @@ typedef struct gear_step_out {
   void *profile;
   /* Nonzero: every kernel of the step is launched on the caller's stream, one after another, and
    * the helper stream is not used.  Same results; for timing each kernel alone, or for callers
-   * that want no second stream.  (With zero a step too short to gain from one does so as well.) */
+   * that want no second stream and no event.  (With zero a step too short to gain from the helper
+   * stream does without it as well, and keeps its place in the order of the device's steps.) */
   int32_t one_stream;
 } gear_step_out;
 

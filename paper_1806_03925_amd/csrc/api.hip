@@ -264,13 +264,18 @@ void *static_scratch() {
 }
 }  // namespace
 
-// One helper stream and three events per device, created on first use and kept for the life of the
-// process: the integer grouping of a step runs beside its gather and forward pass.
+// One helper stream and five events per device, created on first use and kept for the life of the
+// process: the integer grouping of a long step runs beside its gather and forward pass.
 namespace {
 struct SideLane {
   hipStream_t stream = nullptr;
-  hipEvent_t fork = nullptr, join = nullptr, checked = nullptr;
+  hipEvent_t fork = nullptr, join = nullptr, join_captured = nullptr, checked = nullptr;
   bool ready = false;
+  // Two programs that step on streams of their own may collect gradients in one store, so what steps do to it has to happen
+  // in the order in which they were issued, whichever form each takes.  Long steps do it on the helper stream; a short one
+  // does it on its caller's, waits for what the last step left, and leaves this event.
+  hipEvent_t done = nullptr;
+  hipEvent_t *last = nullptr;   // what the last step left: `done`, or `join` of a long one (nullptr before the first)
   std::mutex busy;  // held while a step enqueues: two host threads never interleave their forks and joins
 };
 SideLane g_side[64];
@@ -286,22 +291,29 @@ constexpr double kSplitDxMacs = 5e9;
 // seen), 65 000 143 .. 152 / 144; from there on 89 000 169 / 153, 106 000 187 / 172, 172 000 198 / 182.
 constexpr long long kOneStreamIds = 49152;
 
-// the helper lane of the current device; nullptr when one of its objects cannot be created (nothing
-// half-made is kept: the next call starts over)
-SideLane *side_lane() {
+// The lane of the current device, with the helper stream if it is wanted; nullptr when one of its objects cannot be created
+// (nothing half-made is kept: the next call starts over).
+SideLane *side_lane(bool helper) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return nullptr;
   std::lock_guard<std::mutex> lock(g_side_mutex);
   SideLane &l = g_side[dev];
-  if (!l.ready) {
+  // no fence beyond the device: only its streams wait for this event, and the fence was half of its price
+  if (!l.done && hipEventCreateWithFlags(&l.done, hipEventDisableTiming | hipEventDisableSystemFence) != hipSuccess) {
+    l.done = nullptr;
+    return nullptr;
+  }
+  if (helper && !l.ready) {
     hipStream_t stream = nullptr;
-    hipEvent_t fork = nullptr, join = nullptr, checked = nullptr;
+    hipEvent_t fork = nullptr, join = nullptr, join_captured = nullptr, checked = nullptr;
     bool ok = hipStreamCreateWithFlags(&stream, hipStreamNonBlocking) == hipSuccess;
     ok = ok && hipEventCreateWithFlags(&fork, hipEventDisableTiming) == hipSuccess;
     ok = ok && hipEventCreateWithFlags(&join, hipEventDisableTiming) == hipSuccess;
+    ok = ok && hipEventCreateWithFlags(&join_captured, hipEventDisableTiming) == hipSuccess;
     ok = ok && hipEventCreateWithFlags(&checked, hipEventDisableTiming) == hipSuccess;
     if (!ok) {
       if (checked) (void)hipEventDestroy(checked);
+      if (join_captured) (void)hipEventDestroy(join_captured);
       if (join) (void)hipEventDestroy(join);
       if (fork) (void)hipEventDestroy(fork);
       if (stream) (void)hipStreamDestroy(stream);
@@ -310,31 +322,61 @@ SideLane *side_lane() {
     l.stream = stream;
     l.fork = fork;
     l.join = join;
+    l.join_captured = join_captured;
     l.checked = checked;
     l.ready = true;
   }
   return &l;
 }
 
-// A step's use of the helper lane.  Holds the lane for the whole enqueue, so that steps issued from
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
+// A step's use of the lane, with the helper stream or for its place in the order alone.  Holds the lane for the whole
+// enqueue, so that steps issued from
 // several host threads on one device use the lane's events one after the other, and makes sure
 // that whatever was forked to the helper stream is joined back into the caller's stream however the
 // enqueue ends: after an early return (a failed launch) the next call on the caller's stream must
 // not run beside kernels this call left on the helper stream.
 class LaneScope {
  public:
-  LaneScope(SideLane *side, hipStream_t caller) : side_(side), s_(caller) {
-    if (side_) side_->busy.lock();
+  LaneScope(SideLane *lane, bool helper, bool captured, hipStream_t caller)
+      : lane_(lane), side_(helper ? lane : nullptr), s_(caller), captured_(captured),
+        join_(!helper ? nullptr : captured ? lane->join_captured : lane->join) {
+    if (lane_) lane_->busy.lock();
   }
   ~LaneScope() {
-    if (!side_) return;
-    if (forked_ && !joined_) {
-      if (hipEventRecord(side_->join, side_->stream) == hipSuccess) (void)hipStreamWaitEvent(s_, side_->join, 0);
+    if (!lane_) return;
+    if (side_ && forked_ && !joined_) {
+      if (hipEventRecord(join_, side_->stream) == hipSuccess) (void)hipStreamWaitEvent(s_, join_, 0);
     }
-    side_->busy.unlock();
+    if (entered_ && !captured_) {
+      if (side_) {
+        if (forked_) lane_->last = &lane_->join;   // else it ended before it gave the helper anything
+      } else if (hipEventRecord(lane_->done, s_) == hipSuccess) {
+        lane_->last = &lane_->done;
+      }
+    }
+    lane_->busy.unlock();
   }
   LaneScope(const LaneScope &) = delete;
   LaneScope &operator=(const LaneScope &) = delete;
+  // The step takes its place behind the last one.  Of two long steps the helper stream keeps the order by itself; behind or
+  // ahead of a short one it takes an event.  (A short step pays 2 us for leaving one: 49.7 -> 51.8, 78.6 -> 80.5 and 104.9 ->
+  // 106.6 us on the three smallest workloads; left by the step's last kernel itself, hipExtLaunchKernel, it was 0.3 us where
+  // the device is the slower side and 4 us where the host is.)
+  // A step that is being captured has the place its graph is launched in; it leaves the events of the others alone.
+  hipError_t enter() {
+    if (!lane_) return hipSuccess;
+    hipError_t e = hipSuccess;
+    if (!captured_ && lane_->last && !(side_ && lane_->last == &lane_->join)) e = hipStreamWaitEvent(s_, *lane_->last, 0);
+    entered_ = e == hipSuccess;
+    return e;
+  }
   // what the caller's stream has done so far happens before whatever the helper stream is given next
   hipError_t fork() {
     if (!side_) return hipSuccess;
@@ -345,22 +387,24 @@ class LaneScope {
     return hipStreamWaitEvent(side_->stream, side_->fork, 0);
   }
   // marks the point of the helper stream that a later wait() refers to
-  hipError_t mark() { return side_ ? hipEventRecord(side_->join, side_->stream) : hipSuccess; }
+  hipError_t mark() { return side_ ? hipEventRecord(join_, side_->stream) : hipSuccess; }
   // the same for the end of the helper's first part (ids checked, plan made): the status word is final
   hipError_t mark_checked() { return side_ ? hipEventRecord(side_->checked, side_->stream) : hipSuccess; }
   hipError_t wait_checked() { return side_ ? hipStreamWaitEvent(s_, side_->checked, 0) : hipSuccess; }
   // the caller's stream continues after the last mark(); final = nothing is given to the helper after it
   hipError_t wait(bool final) {
     if (!side_) return hipSuccess;
-    hipError_t e = hipStreamWaitEvent(s_, side_->join, 0);
+    hipError_t e = hipStreamWaitEvent(s_, join_, 0);
     if (e == hipSuccess && final) joined_ = true;
     return e;
   }
 
  private:
-  SideLane *side_;
+  SideLane *lane_, *side_;   // side_: the lane if the helper stream is used
   hipStream_t s_;
-  bool forked_ = false, joined_ = false;
+  const bool captured_;
+  const hipEvent_t join_;
+  bool entered_ = false, forked_ = false, joined_ = false;
 };
 }  // namespace
 
@@ -577,10 +621,14 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   // main stream waits for it before the first kernel that changes caller state, so the status word
   // is final by then; until then its kernels write the workspace only, and the gather clamps what it
   // uses as an index.
-  SideLane *side = one_stream ? nullptr : side_lane();
-  if (!one_stream && !side) return GEAR_ERR_HIP;
+  // A caller who asks for one stream gets no event either; a step that is short keeps its place in the order.
+  const bool ordered = out->one_stream == 0, captured = ordered && capturing(s);
+  const bool needs_lane = !one_stream || (ordered && !captured);
+  SideLane *side = needs_lane ? side_lane(!one_stream) : nullptr;
+  if (needs_lane && !side) return GEAR_ERR_HIP;
   hipStream_t helper = one_stream ? s : side->stream;
-  LaneScope lane(side, s);
+  LaneScope lane(side, !one_stream, captured, s);
+  GEAR_HIP(lane.enter());
   {
     // Step outputs and counters cleared and the operand copies of the weights made in one launch ahead of everything:
     // the first product then needs no event, and behind the gather's many workgroups the copies would not get onto the

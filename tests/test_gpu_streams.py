@@ -58,3 +58,78 @@ def test_a_step_does_not_read_the_status_word_that_others_write(name, batch, cha
     assert int(results[0][1].item()) > 0
     for a, b in zip(*results):
         assert torch.equal(a, b)
+
+
+SHORT, LONG = 2_000, 9_001       # views of the bf16 workload: 13 000 ids (one stream), 58 000 (the helper stream)
+
+
+@pytest.mark.parametrize("sizes", [(SHORT, SHORT), (SHORT, LONG), (LONG, SHORT), (SHORT, LONG, SHORT), (LONG, LONG)])
+def test_steps_on_streams_of_their_own_share_a_store_in_the_order_they_were_issued(sizes):
+    """Each step has tables, workspace and stream of its own and all collect gradients in one store.  The first stream is
+    held up ahead of its step, so a step that does not wait for the one issued before it gets there first; which groups of
+    an image close in which step, and every sum, then come out differently."""
+    import paper_1806_03925_amd as g
+    results = []
+    for apart in (False, True):
+        states = [state_of("bf16", n) for n in sizes]
+        store = states[0][1]
+        for _, st, _ in states[1:]:
+            st.grad_accum, st.counts = store.grad_accum, store.counts
+        # another batch for each step, on tables of the same initial values
+        dev = [[g.DeviceBatch.from_host(src.batch(len(sizes) * t + i, batch=n)) for i, (n, (_, _, src)) in enumerate(zip(sizes, states))]
+               for t in range(2)]
+        streams = [torch.cuda.Stream() if apart else torch.cuda.current_stream() for _ in sizes]
+        torch.cuda.synchronize()
+        lists = []
+        for t in range(2):
+            print(f"sizes {sizes} apart {apart} round {t}", flush=True)
+            for i, (wl, st, _) in enumerate(states):
+                with torch.cuda.stream(streams[i]):
+                    if i == 0:
+                        torch.cuda._sleep(3_000_000)
+                    g.gear_step(st, dev[t][i], wl.M, 0.1)
+            torch.cuda.synchronize()
+            for _, st, _ in states:
+                assert int(st.status.item()) == 0
+                n = int(st.n_ready.item())
+                assert n > 0
+                lists += [st.ready_ids[:n].clone(), st.ready_grads[:n].clone()]
+        results.append(lists + [x.clone() for _, st, _ in states for x in (st.grad_accum, st.counts, st.user_emb, st.mlp_params)])
+    for a, b in zip(*results):
+        assert torch.equal(a, b)
+
+
+def test_a_short_step_recorded_into_a_graph_between_steps_on_other_streams():
+    """Recording takes no event from the order of the steps and leaves none: replays, with eager steps on another stream
+    before and between them, give the bits of the same steps issued one after the other."""
+    import paper_1806_03925_amd as g
+    results = []
+    for recorded in (False, True):
+        wl, st, src = state_of("bf16", SHORT)
+        dev = g.DeviceBatch.from_host(src.batch(0, batch=SHORT))
+        wl2, st2, _ = state_of("bf16", LONG)
+        dev2 = g.DeviceBatch.from_host(src.batch(1, batch=LONG))
+        beside = torch.cuda.Stream()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(beside):
+            g.gear_step(st2, dev2, wl2.M, 0.1)
+        g.gear_step(st, dev, wl.M, 0.1)
+        torch.cuda.synchronize()
+        if recorded:
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph):
+                g.gear_step(st, dev, wl.M, 0.1)
+        for _ in range(3):
+            if recorded:
+                graph.replay()
+            else:
+                g.gear_step(st, dev, wl.M, 0.1)
+            with torch.cuda.stream(beside):
+                g.gear_step(st2, dev2, wl2.M, 0.1)
+            torch.cuda.synchronize()
+        g.gear_step(st, dev, wl.M, 0.1)
+        torch.cuda.synchronize()
+        assert int(st.status.item()) == 0 and int(st2.status.item()) == 0
+        results.append(outputs(st) + outputs(st2))
+    for a, b in zip(*results):
+        assert torch.equal(a, b)
