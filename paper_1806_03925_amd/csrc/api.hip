@@ -782,17 +782,19 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   GEAR_HIP(lane.mark());
   // SGD on the hidden layers' weights: split-K wgrad.  With the last of them go the small sums, unless they are done.
   // All layers go out as one launch, in as many ranges of the batch as their partials have room for; a model whose
-  // partials do not fit at once (several wide layers and a short batch) goes in groups of layers.
+  // partials do not fit at once (several wide layers and a short batch), or with more large tiles than fill the device,
+  // goes in groups of layers.
   for (int first = 0; first < n_wp;) {
     const size_t room = lay.wgrad_partial_bytes / sizeof(float);
     size_t all = 0;
     int n = 0;
-    while (first + n < n_wp && all + (size_t)wp[first + n].M * wp[first + n].N <= room) {
+    const TnChoice choice = gemm_tn_choice(dt, wp + first, n_wp - first, B);
+    while (n < choice.layers && all + (size_t)wp[first + n].M * wp[first + n].N <= room) {
       all += (size_t)wp[first + n].M * wp[first + n].N;
       ++n;
     }
     if (n == 0) return GEAR_ERR_CAPACITY;  // cannot happen: the region holds one range of the widest layer
-    int splits = gemm_tn_splits(dt, wp + first, n, B);
+    int splits = gemm_tn_splits(dt, wp + first, n, B, choice.large);
     if (splits > (int)(room / all)) splits = (int)(room / all);
     float *next = wpart;
     SplitkProblem sp[GEAR_MAX_LAYERS];
@@ -803,7 +805,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
       next += (size_t)splits * q.M * q.N;
       sp[i] = SplitkProblem{q.partial, t->mlp_params + lay.w_off[l], moments_at(mom_mlp, lay.w_off[l]), (int64_t)q.M * q.N};
     }
-    GEAR_RUN("wgrad_gemm", launch_gemm_tn(dt, wp + first, n, B, splits, nullptr, s));
+    GEAR_RUN("wgrad_gemm", launch_gemm_tn(dt, wp + first, n, B, splits, choice.large, nullptr, s));
     // The sums of the partials and the SGD change caller state, so the status word has to be final: the
     // stream waits for the helper's first part (long done by now), not for the bookkeeping.  Their
     // workgroups get onto the device as the bookkeeping's leave room and are done before it is, so the
@@ -930,7 +932,7 @@ gear_status gear_gemm(int32_t dtype, int32_t form, const void *A, const void *B,
   } else if (form == 1) {
     if (M % vec || N % vec || splits < 1 || splits > 64 || !partial) return GEAR_ERR_INVALID;
     const TnProblem one = {A, B, partial, M, N};
-    GEAR_HIP(launch_gemm_tn(dtype, &one, 1, K, splits, status, s));
+    GEAR_HIP(launch_gemm_tn(dtype, &one, 1, K, splits, gemm_tn_choice(dtype, &one, 1, K).large, status, s));
     GEAR_HIP(launch_fill_zero(out, (size_t)M * N * sizeof(float), s));
     const Optim minus = {-1.0f, 0.0f, 0.0f, 0.0f, 1.0f, 0};   // out = 0 - (-1) * sum of the partials
     const Moments none = {nullptr, nullptr};

@@ -325,9 +325,16 @@ struct TnProblem {
   float *partial;
   int M, N;
 };
-hipError_t launch_gemm_tn(int dtype, const TnProblem *p, int count, int K, int splits, const int32_t *status,
+// `large`: on 256 x 256 tiles (bf16, K a multiple of 32 and no k_dev), as gemm_tn_choice says.
+hipError_t launch_gemm_tn(int dtype, const TnProblem *p, int count, int K, int splits, bool large, const int32_t *status,
                           hipStream_t s, const int32_t *k_dev = nullptr);
-int gemm_tn_splits(int dtype, const TnProblem *p, int count, int K);      // ranges to ask for (looks at M and N only)
+// how to go about several of them (looks at M and N only): the first `layers` in one launch, on which tiles, in how many ranges
+struct TnChoice {
+  int layers;
+  bool large;
+};
+TnChoice gemm_tn_choice(int dtype, const TnProblem *p, int count, int K);
+int gemm_tn_splits(int dtype, const TnProblem *p, int count, int K, bool large);
 // w_i <- update(w_i, sum_z partial_i[z]) for the results of such a launch
 struct SplitkProblem {
   const float *partial;
@@ -361,6 +368,7 @@ int nt_tile_colsum_parts(int dtype, int M, int N, bool coarse);
 hipError_t launch_gemm_tn_tile(int dtype, const TnProblem *p, int count, int K, int splits, const int32_t *status,
                                hipStream_t s, const int32_t *k_dev);
 int tn_tile_splits(int dtype, const TnProblem *p, int count, int K);
+long long tn_tile_rows(int dtype, const TnProblem *p, int count, int K);   // that a CU walks, two ranges at a time
 
 hipError_t launch_logit_loss(int dtype, const void *h, const void *wc_last, const float *bias_last, const float *label,
                              int B, int H, float *logits, float *dz, void *delta, float *partials,

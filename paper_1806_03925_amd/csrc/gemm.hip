@@ -464,19 +464,10 @@ bool nt_dma(int dtype, int M, int N, int K, bool narrow) {
   return (long long)((M + DM - 1) / DM) * (narrow ? 1 : (N + DN - 1) / DN) >= 256;
 }
 
-// ... and of the weight-gradient kernels: the 256 x 256 tiles need ranges of the batch long enough that their
-// partial results (256 KB a workgroup) do not outweigh the products.
-bool tn_dma(int dtype, const TnProblem *p, int count, int K) {
-  if (dtype != GEAR_BF16 || K % DK != 0 || K < 32768) return false;
-  int tiles = 0;
-  for (int i = 0; i < count; ++i) tiles += ((p[i].M + DM - 1) / DM) * ((p[i].N + DN - 1) / DN);
-  return tiles <= 128;
-}
+int tn_dma_tiles(const TnProblem &p) { return ((p.M + DM - 1) / DM) * ((p.N + DN - 1) / DN); }
 
 // Ranges of the 256 x 256 kernel: one round of the 256 CUs, every range at least 512 rows.
-int tn_dma_splits(const TnProblem *p, int count, int K) {
-  int tiles = 0;
-  for (int i = 0; i < count; ++i) tiles += ((p[i].M + DM - 1) / DM) * ((p[i].N + DN - 1) / DN);
+int tn_dma_splits(int tiles, int K) {
   int s = 256 / tiles;
   if (s > K / 512) s = K / 512;
   if (s > 64) s = 64;
@@ -523,23 +514,53 @@ hipError_t launch_gemm_nt(int dtype, const void *A, const void *B, int M, int N,
   return hipGetLastError();
 }
 
-int gemm_tn_splits(int dtype, const TnProblem *p, int count, int K) {
-  return tn_dma(dtype, p, count, K) ? tn_dma_splits(p, count, K) : tn_tile_splits(dtype, p, count, K);
+// Which weight-gradient kernel the layers take, and how many of them (from the first on) go in one launch.  What either
+// kernel needs follows from the rows of the batch that a CU walks one range after another: 28 ns each on 256 x 256 tiles, a
+// workgroup to a CU, with 14 us for the rest; 18.5 ns on 128 x 128 (gemm_tile.hip), two to a CU, with 4 us; and the larger
+// tiles leave more partials to add up.  Layers go to the larger kernel in groups of up to 128 tiles, so that its ranges
+// fill the CUs.  Products and sums, us, 256 x 256 / 128 x 128: layers 1024-256 (F = 1152) over 12288 rows 62 / 57, 24576
+// 98 / 102, 32736 120 / 133; 2048-1024 over 4096 66 / 79, 16384 165 / 249, 32736 320 / 479; 512-256 (F = 576) over 32736
+// 54 / 50.  From 32768 rows on up to 128 tiles stay on the larger kernel: there the partials and what else is in flight
+// weigh as much as the rows (512-256 over 65536 rows 82 / 92, 320-72 108 / 94, 1024-256 211 / 255).
+TnChoice gemm_tn_choice(int dtype, const TnProblem *p, int count, int K) {
+  if (dtype == GEAR_BF16 && K % DK == 0) {
+    long long cost = 0;   // in half rows of the smaller kernel
+    int first = 0, all = 0;
+    for (int i = 0; i < count;) {
+      int tiles = tn_dma_tiles(p[i]), n = 1;
+      for (; i + n < count && tiles + tn_dma_tiles(p[i + n]) <= 128; ++n) tiles += tn_dma_tiles(p[i + n]);
+      const int splits = tn_dma_splits(tiles, K);
+      cost += 3 * (((long long)tiles * splits + 255) / 256 * ((K + splits - 1) / splits)) + 2200;
+      if (i == 0) first = n;
+      all += tiles;
+      i += n;
+    }
+    if ((K >= 32768 && all <= 128) || cost <= 2 * tn_tile_rows(dtype, p, count, K)) return TnChoice{first, true};
+  }
+  return TnChoice{count, false};
 }
 
-hipError_t launch_gemm_tn(int dtype, const TnProblem *p, int count, int K, int splits, const int32_t *status,
+int gemm_tn_splits(int dtype, const TnProblem *p, int count, int K, bool large) {
+  if (!large) return tn_tile_splits(dtype, p, count, K);
+  int tiles = 0;
+  for (int i = 0; i < count; ++i) tiles += tn_dma_tiles(p[i]);
+  return tn_dma_splits(tiles, K);
+}
+
+hipError_t launch_gemm_tn(int dtype, const TnProblem *p, int count, int K, int splits, bool large, const int32_t *status,
                           hipStream_t s, const int32_t *k_dev) {
   if (count < 1 || count > GEAR_MAX_LAYERS || splits < 1) return hipErrorInvalidValue;
   for (int i = 0; i < count; ++i)
     if (p[i].M < 4 || p[i].N < 4 || !p[i].A || !p[i].B || !p[i].partial) return hipErrorInvalidValue;
-  if (k_dev || !tn_dma(dtype, p, count, K)) return launch_gemm_tn_tile(dtype, p, count, K, splits, status, s, k_dev);
+  if (!large) return launch_gemm_tn_tile(dtype, p, count, K, splits, status, s, k_dev);
+  if (k_dev || dtype != GEAR_BF16 || K % DK != 0) return hipErrorInvalidValue;
   TnBatchArgs args;
   args.count = count;
   args.tiles = 0;
   for (int i = 0; i < GEAR_MAX_LAYERS; ++i) {
     args.p[i] = i < count ? p[i] : TnProblem{nullptr, nullptr, nullptr, 0, 0};
     args.first_tile[i] = args.tiles;
-    if (i < count) args.tiles += ((p[i].M + DM - 1) / DM) * ((p[i].N + DN - 1) / DN);
+    if (i < count) args.tiles += tn_dma_tiles(p[i]);
   }
   const int kc = ((((K + splits - 1) / splits) + DK - 1) / DK) * DK;
   hipLaunchKernelGGL(k_gemm_tn_dma_batch, dim3(args.tiles * splits), dim3(DTHREADS), 0, s, args, K, kc, status);

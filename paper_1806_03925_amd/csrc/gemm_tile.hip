@@ -717,15 +717,25 @@ hipError_t launch_gemm_nt_tile(int dtype, const void *A, const void *B, int M, i
 #undef GEAR_NT
 }
 
-// Ranges of the inner length: two workgroups for every CU, as long as each keeps at least 64 rows.
-int tn_tile_splits(int dtype, const TnProblem *p, int count, int K) {
+static long long tn_tiles(int dtype, const TnProblem *p, int count) {
   long long tiles = 0;
   const int edge = dtype == GEAR_BF16 ? TnBf16::BM : TnF32::BM;
   for (int i = 0; i < count; ++i) tiles += tiles_of(p[i].M, p[i].N, edge, edge);
+  return tiles;
+}
+
+// Ranges of the inner length: two workgroups for every CU, as long as each keeps at least 64 rows.
+int tn_tile_splits(int dtype, const TnProblem *p, int count, int K) {
+  const long long tiles = tn_tiles(dtype, p, count);
   long long s = tiles > 0 ? 512 / tiles : 1;
   if (s > K / 64) s = K / 64;
   if (s > 64) s = 64;
   return s < 1 ? 1 : (int)s;
+}
+
+long long tn_tile_rows(int dtype, const TnProblem *p, int count, int K) {
+  const int splits = tn_tile_splits(dtype, p, count, K);
+  return (tn_tiles(dtype, p, count) * splits + 511) / 512 * ((K + splits - 1) / splits);
 }
 
 hipError_t launch_gemm_tn_tile(int dtype, const TnProblem *p, int count, int K, int splits, const int32_t *status, hipStream_t s,

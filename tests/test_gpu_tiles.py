@@ -13,6 +13,14 @@ def operands(dtype, M, N, K):
     return draw(M, K), draw(N, K), draw(M, N), torch.randn(N, generator=gen, device="cuda")
 
 
+def beside_the_oracle(wl):
+    """The comparison of tests/test_gpu_parity.py, also where these tests run by themselves."""
+    import paper_1806_03925_amd as g
+    import test_gpu_parity as parity
+    parity.g = g
+    return parity.Pair(wl)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("M,N,K", [
     (1, 8, 8), (63, 72, 24), (65, 64, 64), (64, 56, 72), (129, 200, 136),    # 64 x 64: one piece, one stage, one over
@@ -58,10 +66,27 @@ def test_weight_gradients_and_bias_sums_that_do_not_fit_at_once(dtype):
     """Five equal hidden layers and a short batch: the partial results of all weight gradients exceed their region, so
     the layers go out in groups; the bias partials fit with 128-row tiles only."""
     from gear_inputs import PageViewSource, get_workload
-    from test_gpu_parity import Pair
     wl = get_workload("tiny").scaled(batch=300, layers=(512,) * 5 + (1,), emb_dtype=dtype, dfv_dtype=dtype,
                                      mlp_dtype=dtype)
-    pair = Pair(wl)
+    pair = beside_the_oracle(wl)
     src = PageViewSource(wl)
     for step in range(2):
         pair.step(src.batch(step), wl.lr, f"deep {dtype} step {step}")
+
+
+@pytest.mark.parametrize("layers,batch", [
+    ((1024,) * 5 + (1,), 2_304),              # 68 tiles of 256 x 256 in three ranges, from here on faster than 128 x 128
+    ((1024,) * 5 + (1,), 2_272),              # a size below: 128 x 128
+    ((2048, 2048, 2048, 1024, 1), 2_944),     # 168 large tiles: two launches, of 96 and of 72
+])
+def test_weight_gradients_of_many_tiles(layers, batch):
+    """Wide layers take the large tiles below 32 768 rows too, in groups of layers that fill the CUs."""
+    import paper_1806_03925_amd as g
+    from gear_inputs import PageViewSource, get_workload
+    wl = get_workload("tiny").scaled(batch=batch, layers=layers, emb_dtype="bf16", dfv_dtype="bf16", mlp_dtype="bf16")
+    pair = beside_the_oracle(wl)
+    pair.st.profile = g.GearProfile()
+    pair.step(PageViewSource(wl).batch(0), wl.lr, f"{len(layers)} layers, {batch} views")
+    launches = [name for name, _ in pair.st.profile.spans()].count("wgrad_gemm")
+    pair.st.profile.close()
+    assert launches == (2 if layers[0] == 2048 else 1)
