@@ -458,10 +458,20 @@ k_gemm_tn_dma_batch(TnBatchArgs args, int K, int k_chunk, const int32_t *__restr
 }
 
 // Which of the two bf16 NT kernels a product takes.  The 256 x 256 tiles of the kernel above move the fewest bytes
-// per product, but a CU holds one: below one tile per CU the smaller tiles of gemm_tile.hip win.
-bool nt_dma(int dtype, int M, int N, int K, bool narrow) {
+// per product, but a CU holds one: below one tile per CU the smaller tiles of gemm_tile.hip mostly win.
+bool nt_fills(int dtype, int M, int N, int K, bool narrow) {
   if (dtype != GEAR_BF16 || K % DK != 0) return false;
   return (long long)((M + DM - 1) / DM) * (narrow ? 1 : (N + DN - 1) / DN) >= 256;
+}
+// Not so a long product that leaves few CUs out: from about 216 whole tiles on with K >= 512, from 174 on with K >= 1024,
+// a CU's one large tile ends before the two rounds of small ones it would have instead.  (bias + ReLU, us, 256 x 256 /
+// smaller: 20000 x 768 x 1152 37.0 / 47.6, 28672 x 512 x 512 20.2 / 22.4, 24000 x 512 x 1024 31.1 / 33.7, 20000 x 576 x
+// 1024 30.1 / 33.9; on the other side 24000 x 512 x 512 masked 23.3 / 20.7, 20000 x 512 x 1152 33.6 / 31.5, 16384 x 576 x
+// 1152 32.1 / 30.6.  The narrow form has N <= 128 and never as many.)
+bool nt_dma(int dtype, int M, int N, int K, bool narrow) {
+  if (nt_fills(dtype, M, N, K, narrow)) return true;
+  const long long whole = (long long)M * N / (DM * DN);
+  return dtype == GEAR_BF16 && K % DK == 0 && !narrow && ((whole >= 215 && K >= 512) || (whole >= 174 && K >= 1024));
 }
 
 int tn_dma_tiles(const TnProblem &p) { return ((p.M + DM - 1) / DM) * ((p.N + DN - 1) / DN); }
@@ -481,7 +491,7 @@ int gemm_nt_colsum_parts(int dtype, int M, int N, int K, bool coarse) {
   return nt_dma(dtype, M, N, K, false) ? (M + DM - 1) / DM : nt_tile_colsum_parts(dtype, M, N, coarse);
 }
 
-bool gemm_nt_carries(int dtype, int M, int N, int K) { return !nt_dma(dtype, M, N, K, false); }
+bool gemm_nt_carries(int dtype, int M, int N, int K) { return !nt_fills(dtype, M, N, K, false); }
 
 hipError_t launch_gemm_nt(int dtype, const void *A, const void *B, int M, int N, int K, int epi, const float *bias,
                           const void *aux, void *out, int split, float *colpart, uint8_t *relu_bits,
@@ -489,7 +499,7 @@ hipError_t launch_gemm_nt(int dtype, const void *A, const void *B, int M, int N,
   if (M <= 0 || N <= 0) return hipSuccess;
   if (epi == EPI_MASK_BITS && dtype != GEAR_BF16) return hipErrorInvalidValue;
   const bool narrow = N <= NtNarrow::BN && (epi == EPI_DX || epi == EPI_F32);
-  if (!nt_dma(dtype, M, N, K, narrow))
+  if (side ? !nt_fills(dtype, M, N, K, narrow) : !nt_dma(dtype, M, N, K, narrow))
     return launch_gemm_nt_tile(dtype, A, B, M, N, K, epi, bias, aux, out, split, colpart, relu_bits, status, s, coarse, side);
   if (side) return hipErrorInvalidValue;
   const dim3 grid(((M + DM - 1) / DM) * (narrow ? 1 : (N + DN - 1) / DN));

@@ -90,3 +90,18 @@ def test_weight_gradients_of_many_tiles(layers, batch):
     launches = [name for name, _ in pair.st.profile.spans()].count("wgrad_gemm")
     pair.st.profile.close()
     assert launches == (2 if layers[0] == 2048 else 1)
+
+
+@pytest.mark.parametrize("M,N,K", [(20_000, 768, 512), (28_672, 512, 1_056), (20_000, 576, 1_024), (24_001, 512, 1_024)])
+def test_bf16_bits_do_not_depend_on_the_kernel(M, N, K):
+    """Long products that leave a few CUs without a 256 x 256 tile take that kernel, the same rows in a short one do not, and
+    a step's product goes either way depending on whether it carries other work: every epilogue gives the same bits."""
+    import paper_1806_03925_amd as g
+    A, B, aux, bias = operands("bf16", M, N, K)
+    rows = 500
+    a, x = A[:rows].contiguous(), aux[:rows].contiguous()
+    for epilogue, many, few in ((0, dict(bias=bias), dict(bias=bias)), (1, dict(aux=aux), dict(aux=x)), (2, {}, {})):
+        big = g.gear_gemm(A, B, 0, epilogue, **many)
+        assert torch.equal(big[:rows], g.gear_gemm(a, B, 0, epilogue, **few))
+        last = g.gear_gemm(A[-rows:].contiguous(), B, 0, epilogue, **(dict(aux=aux[-rows:].contiguous()) if epilogue == 1 else many))
+        assert torch.equal(big[-rows:], last)
