@@ -526,21 +526,25 @@ hipError_t launch_gemm_nt(int dtype, const void *A, const void *B, int M, int N,
 
 // Which weight-gradient kernel the layers take, and how many of them (from the first on) go in one launch.  What either
 // kernel needs follows from the rows of the batch that a CU walks one range after another: 28 ns each on 256 x 256 tiles, a
-// workgroup to a CU, with 14 us for the rest; 18.5 ns on 128 x 128 (gemm_tile.hip), two to a CU, with 4 us; and the larger
-// tiles leave more partials to add up.  Layers go to the larger kernel in groups of up to 128 tiles, so that its ranges
-// fill the CUs.  Products and sums, us, 256 x 256 / 128 x 128: layers 1024-256 (F = 1152) over 12288 rows 62 / 57, 24576
-// 98 / 102, 32736 120 / 133; 2048-1024 over 4096 66 / 79, 16384 165 / 249, 32736 320 / 479; 512-256 (F = 576) over 32736
-// 54 / 50.  From 32768 rows on up to 128 tiles stay on the larger kernel: there the partials and what else is in flight
-// weigh as much as the rows (512-256 over 65536 rows 82 / 92, 320-72 108 / 94, 1024-256 211 / 255).
+// workgroup to a CU, 18.5 ns on 128 x 128 (gemm_tile.hip), two to a CU; and ahead of them what starting and ending costs,
+// more on the large tiles, which leave more partials.  That shrinks with the length of the batch because the large tiles
+// also move half the bytes, beside an accumulation that is bound by them.  Layers go to the large tiles in groups of up to
+// 128, so that the ranges fill the CUs.
+// Products and sums alone, us, 256 x 256 / 128 x 128: layers 1024-256 (F = 1152) over 12288 rows 62 / 57, 32736 120 / 133;
+// 2048-1024 over 4096 66 / 79, 16384 165 / 249, 32736 320 / 479; 512-256 (F = 576) over 32736 54 / 50.  Whole steps, eight
+// images a view: 1024-256 over 12288 views 254 / 254, 24576 424 / 449; 1024 over 16384 253 / 253, 24576 357 / 373, 32736
+// 416 / 442; 512-512-512 over 20000 289 / 283, 32736 355 / 353; 512-256 over 32736 265 / 263.  From 32768 rows on up to 128
+// tiles are the larger kernel's (512-256 over 65536 views 441 / 445, 1024-256 857 / 953, 320-72 531 / 546; a layer of 256
+// columns 227 / 222).
 TnChoice gemm_tn_choice(int dtype, const TnProblem *p, int count, int K) {
   if (dtype == GEAR_BF16 && K % DK == 0) {
-    long long cost = 0;   // in half rows of the smaller kernel
+    long long cost = min(2200, 20000000 / K);   // in half rows of the smaller kernel, 9 ns; a launch more is 1100
     int first = 0, all = 0;
     for (int i = 0; i < count;) {
       int tiles = tn_dma_tiles(p[i]), n = 1;
       for (; i + n < count && tiles + tn_dma_tiles(p[i + n]) <= 128; ++n) tiles += tn_dma_tiles(p[i + n]);
       const int splits = tn_dma_splits(tiles, K);
-      cost += 3 * (((long long)tiles * splits + 255) / 256 * ((K + splits - 1) / splits)) + 2200;
+      cost += 3 * (((long long)tiles * splits + 255) / 256 * ((K + splits - 1) / splits)) + (i > 0 ? 1100 : 0);
       if (i == 0) first = n;
       all += tiles;
       i += n;

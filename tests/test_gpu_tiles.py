@@ -75,8 +75,8 @@ def test_weight_gradients_and_bias_sums_that_do_not_fit_at_once(dtype):
 
 
 @pytest.mark.parametrize("layers,batch", [
-    ((1024,) * 5 + (1,), 2_304),              # 68 tiles of 256 x 256 in three ranges, from here on faster than 128 x 128
-    ((1024,) * 5 + (1,), 2_272),              # a size below: 128 x 128
+    ((1024,) * 5 + (1,), 2_208),              # 68 tiles of 256 x 256 in three ranges, the shortest batch that takes them
+    ((1024,) * 5 + (1,), 2_176),              # a size below: 128 x 128
     ((2048, 2048, 2048, 1024, 1), 2_944),     # 168 large tiles: two launches, of 96 and of 72
 ])
 def test_weight_gradients_of_many_tiles(layers, batch):
