@@ -290,6 +290,11 @@ constexpr double kSplitDxMacs = 5e9;
 // launches, against two streams: 2 300 ids 53 / 99 us, 15 000 82 / 119, 27 000 106 / 128, 63 000 154 / 178 (the slowest host
 // seen), 65 000 143 .. 152 / 144; from there on 89 000 169 / 153, 106 000 187 / 172, 172 000 198 / 182.
 constexpr long long kOneStreamIds = 49152;
+// ... and the multiply-adds of its forward products, in bf16; four times that of fp32.  Weight gradients that long are worth
+// hiding the accumulation behind however few ids there are.  One stream / two, us, of steps of 12 000 to 48 000 ids: bf16,
+// 5.2e9 126 / 132, 5.9e9 138 / 137, 6.8e9 154 / 149, 7.2e9 169 / 151, 8.9e9 197 / 167, 23e9 311 / 256; fp32, 0.9e9
+// 131 / 129, 1.2e9 148 / 149, 1.4e9 179 / 183, 1.7e9 191 / 183, 2.4e9 225 / 214, 2.9e9 311 / 288.
+constexpr double kOneStreamMacs = 6.8e9;
 
 // The lane of the current device, with the helper stream if it is wanted; nullptr when one of its objects cannot be created
 // (nothing half-made is kept: the next call starts over).
@@ -586,7 +591,10 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   // helper stream has it.
   bool moderate = true;
   for (int l = 0; l < L - 1; ++l) moderate = moderate && gemm_nt_carries(dt, B, lay.out_dim[l], lay.in_dim[l]);
-  const bool one_stream = out->one_stream != 0 || (moderate && (long long)2 * B + b->nnz < kOneStreamIds);
+  double macs = 0.0;
+  for (int l = 0; l < L - 1; ++l) macs += (double)B * lay.in_dim[l] * lay.out_dim[l];
+  const bool is_short = (long long)2 * B + b->nnz < kOneStreamIds && macs * (dt == GEAR_BF16 ? 1 : 4) < kOneStreamMacs;
+  const bool one_stream = out->one_stream != 0 || (moderate && is_short);
   const bool carried = one_stream && moderate;
 
   // grouping of the three id lists and the plan of the per-image accumulation

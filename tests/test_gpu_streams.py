@@ -16,6 +16,42 @@ def state_of(name, batch, **changes):
     return wl, st, PageViewSource(wl)
 
 
+def form_of(st, dev, M):
+    """How a step of this batch is run: the grouping carried by other launches on the caller's stream, or on the helper stream,
+    or there with dLoss/dx in two products."""
+    import paper_1806_03925_amd as g
+    st.profile = g.GearProfile()
+    g.gear_step(st, dev, M, 0.1)
+    torch.cuda.synchronize()
+    names = [name for name, _ in st.profile.spans()]
+    st.profile.close()
+    st.profile = None
+    return "carried" if "accum_plan" not in names else "divided" if "dgrad_gemm_emb" in names else "helper"
+
+
+@pytest.mark.parametrize("batch,changes,form", [
+    (16_383, dict(layers=(128, 1)), "carried"), (16_384, dict(layers=(128, 1)), "helper"),      # 49 152 ids
+    (15_963, {}, "carried"), (15_964, {}, "helper"),                                            # 6.8e9 multiply-adds
+    (11_529, dict(layers=(1024, 1)), "divided"),
+    (2_882, dict(layers=(1024, 1), mlp_dtype="f32"), "carried"), (2_883, dict(layers=(1024, 1), mlp_dtype="f32"), "helper"),
+])
+def test_steps_on_either_side_of_the_line_between_their_forms(batch, changes, form):
+    """One image a view, so three ids.  Each takes the form it should and gives the bits of the other."""
+    import paper_1806_03925_amd as g
+    results = []
+    for one in (False, True):
+        wl, st, src = state_of("bf16", batch, max_images=1, **changes)
+        st.one_stream = one
+        dev = g.DeviceBatch.from_host(src.batch(0, batch=batch))
+        assert form_of(st, dev, wl.M) == ("carried" if one else form)
+        g.gear_step(st, dev, wl.M, 0.1)
+        torch.cuda.synchronize()
+        assert int(st.status.item()) == 0
+        results.append(outputs(st))
+    for a, b in zip(*results):
+        assert torch.equal(a, b)
+
+
 def outputs(st):
     n = int(st.n_ready.item())
     return [t.clone() for t in (st.loss, st.n_ready, st.ready_ids[:n], st.ready_grads[:n], st.grad_accum, st.counts,
