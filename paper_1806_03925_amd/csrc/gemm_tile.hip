@@ -676,11 +676,20 @@ int rows_of(NtShape shape) { return shape == kSmall ? 64 : 128; }
 // products (16384 x 512 x 576: 14.2 us against 17.0), as long as whole rounds of them fill the chip; where the last
 // round is mostly empty the half-sized tiles end sooner (16384 x 576 x 512, 640 tiles: 18.8 against 17.6; 10001 x 512
 // x 576, 316 tiles: 13.2 against 12.7).  Below one 128 x 64 tile per CU, 64 x 64 reaches more CUs.
-// fp32: 128 x 128 from one tile per CU on (16384 x 256 x 320: 30.1 us against 31.4), else 64 x 64.
+// fp32: a CU holds one 128 x 128 tile or two of 64 x 64, and both shapes run at the rate of its matrix unit, so what decides
+// is how full the last round is: 40 us a round of large tiles at K = 512, 10.4 us a half round of small ones and 2 us more
+// to begin with (K = 512, bias + ReLU, us, 128 x 128 / 64 x 64: 16384 x 256 43.3 / 45.5, 16384 x 320 81 / 57, 8192 x 320
+// 42 / 36, 20000 x 384 82 / 86, 24000 x 320 121 / 86, 32768 x 64 43 / 25).
+// dLoss/dx keeps the large tiles from one per CU on: on two streams the grouping is still under way beside it, and two small
+// tiles leave it no room (16384 x 320 with 139 000 ids to group: the product 13 us shorter, the step 2 us longer).
 // `coarse` (column sums of more, narrower row tiles would not fit their region) rules 64 x 64 out.
-NtShape nt_shape(int dtype, int M, int N, bool coarse) {
+NtShape nt_shape(int dtype, int M, int N, bool coarse, bool dx = false) {
   const long long big = tiles_of(M, N, 128, 128);
-  if (dtype != GEAR_BF16) return big >= 256 || coarse ? kWide : kSmall;
+  if (dtype != GEAR_BF16) {
+    const long long rounds = (big + 255) / 256, halves = (tiles_of(M, N, 64, 64) + 255) / 256;
+    if (dx) return big >= 256 ? kWide : kSmall;
+    return coarse || 26 * halves + 5 > 100 * rounds ? kWide : kSmall;
+  }
   const long long tall = tiles_of(M, N, 128, 64);
   if (tall < 256) return coarse ? kTall : kSmall;
   return 2 * ((big + 511) / 512) <= (tall + 767) / 768 ? kWide : kTall;
@@ -710,7 +719,7 @@ int nt_tile_colsum_parts(int dtype, int M, int N, bool coarse) {
 hipError_t launch_gemm_nt_tile(int dtype, const void *A, const void *B, int M, int N, int K, int epi, const float *bias,
                                const void *aux, void *out, int split, float *colpart, uint8_t *relu_bits,
                                const int32_t *status, hipStream_t s, bool coarse, const SideTask *side) {
-  const NtShape shape = nt_shape(dtype, M, N, coarse);
+  const NtShape shape = nt_shape(dtype, M, N, coarse, epi == EPI_DX);
 #define GEAR_NT(C) run_nt_any<C>(A, B, M, N, K, epi, bias, aux, out, split, colpart, relu_bits, status, s, side)
   if (dtype == GEAR_BF16) return shape == kWide ? GEAR_NT(Bf16Mid) : shape == kTall ? GEAR_NT(Bf16Tall) : GEAR_NT(Bf16Small);
   return shape == kWide ? GEAR_NT(F32Big) : GEAR_NT(F32Small);

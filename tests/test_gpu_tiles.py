@@ -26,6 +26,7 @@ def beside_the_oracle(wl):
     (1, 8, 8), (63, 72, 24), (65, 64, 64), (64, 56, 72), (129, 200, 136),    # 64 x 64: one piece, one stage, one over
     (16385, 128, 40), (16384, 64, 128),                                       # bf16 from 256 tiles of 128 x 64 on
     (32760, 256, 72), (16390, 256, 32), (65537, 128, 200),                    # 128 x 128, cut in M and in K
+    (16390, 320, 40), (20000, 384, 40), (20000, 320, 40),                     # fp32 by rounds: 64 x 64, 128 x 128, 64 x 64
 ])
 def test_products_at_the_edges_of_tiles(dtype, M, N, K):
     import paper_1806_03925_amd as g
