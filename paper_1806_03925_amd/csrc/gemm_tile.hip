@@ -200,6 +200,8 @@ __device__ __forceinline__ void nt_main_loop(f32x16_v (&acc)[C::WTM][C::WTN], ui
 
 // fp32 results, stored from the accumulator layout: element e of a 32 x 32 tile sits at row
 // 8 (e / 4) + 4 (lane / 32) + e % 4, column lane % 32.  colsum[j] gathers what is stored of column j's tile.
+// EPI_F32, whose results (the stand-in's rows for a cache, say) are many times its operands, is bound by these stores:
+// 65536 x 1024 x 64 took 133 us on one three-stage tile per CU, 107 on two tiles of two stages, 100 with stores past the L2.
 template <int EPI, typename C, int NB, int NM>
 __device__ __forceinline__ void store_f32(const f32x16_v (&acc)[C::WTM][C::WTN], int m_first, int n_first, int lane, int M,
                                           int N, const float (&bias)[NB], const float (&mask)[NM][16],
@@ -231,7 +233,10 @@ __device__ __forceinline__ void store_f32(const f32x16_v (&acc)[C::WTM][C::WTN],
         }
         if constexpr (EPI == EPI_MASK) v = mask[i * C::WTN + j][e] > 0.0f ? v : 0.0f;
         if (whole || m < M) {
-          dst[(size_t)m * ld] = v;
+          if constexpr (EPI == EPI_F32)
+            __builtin_nontemporal_store(v, &dst[(size_t)m * ld]);
+          else
+            dst[(size_t)m * ld] = v;
           if constexpr (EPI == EPI_MASK) colsum[j] += v;
         }
       }
@@ -626,6 +631,7 @@ k_gemm_tn_tile(TnTileArgs args, int K, int splits, const int32_t *__restrict__ s
 // ---- tile shapes -----------------------------------------------------------------------------------------
 using F32Small = NtTile<float, 1, 1, 2, 2, 4>;      //  64 x  64, 64 KB
 using F32Big = NtTile<float, 2, 2, 2, 2, 3>;        // 128 x 128, 96 KB
+using F32Pair = NtTile<float, 2, 2, 2, 2, 2>;       // 128 x 128, 64 KB: two on a CU, one stores while the other multiplies
 using Bf16Small = NtTile<bf16_t, 1, 2, 2, 1, 3>;    //  64 x  64, two waves, 48 KB
 using Bf16Tall = NtTile<bf16_t, 1, 2, 4, 1, 2>;     // 128 x  64, 48 KB
 using Bf16Mid = NtTile<bf16_t, 2, 2, 2, 2, 2>;      // 128 x 128, 64 KB
@@ -660,7 +666,7 @@ hipError_t run_nt_any(const void *A, const void *B, int M, int N, int K, int epi
     case EPI_BIAS_RELU: return GEAR_NT(EPI_BIAS_RELU);
     case EPI_MASK: return GEAR_NT(EPI_MASK);
     case EPI_DX: return GEAR_NT(EPI_DX);
-    case EPI_F32: return GEAR_NT(EPI_F32);
+    case EPI_F32: return run_nt<EPI_F32, std::conditional_t<std::is_same_v<C, F32Big>, F32Pair, C>>(A, B, M, N, K, bias, aux, out, split, colpart, relu_bits, status, s, side);
     case EPI_MASK_BITS:
       if constexpr (sizeof(typename C::T) == 2) return GEAR_NT(EPI_MASK_BITS);
   }
@@ -682,12 +688,15 @@ int rows_of(NtShape shape) { return shape == kSmall ? 64 : 128; }
 // 42 / 36, 20000 x 384 82 / 86, 24000 x 320 121 / 86, 32768 x 64 43 / 25).
 // dLoss/dx keeps the large tiles from one per CU on: on two streams the grouping is still under way beside it, and two small
 // tiles leave it no room (16384 x 320 with 139 000 ids to group: the product 13 us shorter, the step 2 us longer).
+// EPI_F32 has two large tiles on a CU as well, a half round of them 19 us at K = 256 where one of small ones is 5.3 (16384 x
+// 384 39 / 35, 20000 x 320 39 / 40, 24000 x 576 76 / 78).
 // `coarse` (column sums of more, narrower row tiles would not fit their region) rules 64 x 64 out.
-NtShape nt_shape(int dtype, int M, int N, bool coarse, bool dx = false) {
+NtShape nt_shape(int dtype, int M, int N, bool coarse, int epi = EPI_MASK) {
   const long long big = tiles_of(M, N, 128, 128);
   if (dtype != GEAR_BF16) {
     const long long rounds = (big + 255) / 256, halves = (tiles_of(M, N, 64, 64) + 255) / 256;
-    if (dx) return big >= 256 ? kWide : kSmall;
+    if (epi == EPI_DX) return big >= 256 ? kWide : kSmall;
+    if (epi == EPI_F32) return 29 * halves > 100 * rounds ? kWide : kSmall;
     return coarse || 26 * halves + 5 > 100 * rounds ? kWide : kSmall;
   }
   const long long tall = tiles_of(M, N, 128, 64);
@@ -719,7 +728,7 @@ int nt_tile_colsum_parts(int dtype, int M, int N, bool coarse) {
 hipError_t launch_gemm_nt_tile(int dtype, const void *A, const void *B, int M, int N, int K, int epi, const float *bias,
                                const void *aux, void *out, int split, float *colpart, uint8_t *relu_bits,
                                const int32_t *status, hipStream_t s, bool coarse, const SideTask *side) {
-  const NtShape shape = nt_shape(dtype, M, N, coarse, epi == EPI_DX);
+  const NtShape shape = nt_shape(dtype, M, N, coarse, epi);
 #define GEAR_NT(C) run_nt_any<C>(A, B, M, N, K, epi, bias, aux, out, split, colpart, relu_bits, status, s, side)
   if (dtype == GEAR_BF16) return shape == kWide ? GEAR_NT(Bf16Mid) : shape == kTall ? GEAR_NT(Bf16Tall) : GEAR_NT(Bf16Small);
   return shape == kWide ? GEAR_NT(F32Big) : GEAR_NT(F32Small);
