@@ -608,7 +608,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
     }
     // a pass that is carried costs nothing but its length, and narrow digits make it short: as many as find a launch ahead
     // of the one that takes the segments
-    const int rides = L < kMaxPasses ? L : kMaxPasses;   // the forward products and the logit layer
+    const int rides = L < kMaxRides ? L : kMaxRides;   // the forward products and the logit layer
     if (carried && passes < rides) passes = rides;
     gb.count = kMaxProblems;
     gb.p[0] = make_problem(lay, ws, 0, b->user_id, B, cfg->n_users, passes, bits[0]);

@@ -115,7 +115,8 @@ constexpr int kSortBlock = 256;                       // threads
 constexpr int kSortItems = 8;                         // keys per thread
 constexpr int kSortTile = kSortBlock * kSortItems;    // keys per workgroup
 constexpr int kMaxProblems = 3;
-constexpr int kMaxPasses = 3;
+constexpr int kMaxPasses = 4;
+constexpr int kMaxRides = 3;                          // passes that other launches are asked to carry, if it is up to us
 constexpr int kMaxDigitBits = 12;
 constexpr int kSideDigitBits = 11;                    // of passes that other launches carry
 constexpr int kLongList = 65536;                      // ids from which a workgroup of the check takes several tiles, and a step's products are large
@@ -151,7 +152,8 @@ struct GroupBatch {
 
 // The widest digits a list of n ids is sorted by in launches of their own: a wide digit saves a pass of a short list, but a
 // tile looks back at up to all before it for every digit (139 000 ids, 22 bits: two passes of eleven bits 39 and 43 us
-// beside a product, three of eight bits 12 us each).
+// beside a product, three of eight bits 12 us each; 600 000 ids of 31 bits alone, three of eleven 289 us in all, four of
+// eight 139).
 inline int widest_digit(int n) { return n > 16 * kSortTile ? 9 : kMaxDigitBits; }
 
 // fewest passes over keys of `bits` bits in digits of up to `widest` bits

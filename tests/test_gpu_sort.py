@@ -1,5 +1,5 @@
 """Grouping at the sizes where its shape changes: tiles of 2048 keys, four tiles per counting workgroup beyond 65 536 keys,
-one to three passes of up to twelve bits (kernels for up to nine bits and for more).  Integers: exact."""
+one to four passes of up to twelve bits (kernels for up to nine bits and for more).  Integers: exact."""
 import numpy as np
 import pytest
 import torch
