@@ -16,6 +16,7 @@ import argparse
 import hashlib
 import json
 import os
+import re
 import sys
 import time
 
@@ -124,9 +125,17 @@ MFMA_KERNELS = {k: v[0] for k, v in TRAFFIC_KERNELS.items() if "gemm" in k}
 
 
 def source_hash(files):
+    """Of the files and of every header in CSRC that they include, directly or not: kernel code lives there too."""
+    texts, todo = {}, list(files)
+    while todo:
+        f = todo.pop()
+        if f in texts or not os.path.exists(os.path.join(CSRC, f)):
+            continue
+        texts[f] = open(os.path.join(CSRC, f), "rb").read()
+        todo += re.findall(r'^\s*#\s*include\s+"([^"]+)"', texts[f].decode(), re.M)
     h = hashlib.sha256()
-    for f in sorted(set(files) | {"gear_internal.hpp"}):
-        h.update(open(os.path.join(CSRC, f), "rb").read())
+    for f in sorted(texts):
+        h.update(texts[f])
     return h.hexdigest()[:16]
 
 

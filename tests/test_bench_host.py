@@ -3,10 +3,12 @@ figures are divided by, and the parsing of the rocprofv3 counter files."""
 import csv
 import json
 import os
+import shutil
 import subprocess
 import sys
 
 import numpy as np
+import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 sys.path.insert(0, ROOT)
@@ -108,3 +110,21 @@ def test_mfma_counters_become_occupancy(tmp_path, monkeypatch):
     table = {l.split()[0]: l.split() for l in open(tmp_path / "mfma.txt") if not l.startswith("#")}
     assert float(table["fwd_gemm_l0"][4]) == 0.1 and float(table["fwd_gemm_l1"][4]) == 0.2
     assert float(table["wgrad_gemm"][4]) == 0.6 and table["dgrad_gemm_l0"][1] == "1"
+
+
+@pytest.mark.parametrize("header,spans", [
+    ("gear_internal.hpp", set(bench.TRAFFIC_KERNELS)),
+    ("gemm_common.hpp", {s for s in bench.TRAFFIC_KERNELS if "gemm" in s}),
+    ("group_device.hpp", {"gather_pool"}),
+    ("embedding_common.hpp", {"accumulate", "embedding_update"}),
+])
+def test_a_recorded_figure_goes_stale_with_any_source_of_its_kernel(tmp_path, monkeypatch, header, spans):
+    """Kernel code moves between a .hip file and the headers it includes; a figure is only reported while none of them changed."""
+    here = tmp_path / "csrc"
+    shutil.copytree(bench.CSRC, here)
+    monkeypatch.setattr(bench, "CSRC", str(here))
+    before = {s: bench.source_hash(files) for s, (_, files) in bench.TRAFFIC_KERNELS.items()}
+    with open(here / header, "a") as f:
+        f.write("// changed\n")
+    stale = {s for s, (_, files) in bench.TRAFFIC_KERNELS.items() if bench.source_hash(files) != before[s]}
+    assert stale == spans
