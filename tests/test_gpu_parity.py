@@ -730,14 +730,27 @@ def test_same_step_twice_is_bit_identical():
         assert torch.equal(a, b)
 
 
-@pytest.mark.parametrize("name,batch", [
-    ("bf16", 3000),     # weight gradients layer by layer (the batch is no multiple of 32 rows)
-    ("bf16", 3008),     # all of them in one launch, joined to the helper stream only before their SGD
-    ("large", 8192),    # and dLoss/dx in two products with the embedding update beside the second
+def form_of(st, dev, M, lr):
+    """How a step of this batch is run, read from its launches: the grouping "carried" by other launches on the caller's
+    stream, or on the "helper" stream, or there with dLoss/dx "divided" into two products.  Runs the step."""
+    st.profile = g.GearProfile()
+    g.gear_step(st, dev, M, lr)
+    torch.cuda.synchronize()
+    names = [name for name, _ in st.profile.spans()]
+    st.profile.close()
+    st.profile = None
+    return "carried" if "accum_plan" not in names else "divided" if "dgrad_gemm_emb" in names else "helper"
+
+
+@pytest.mark.parametrize("name,batch,form", [
+    ("bf16", 9_001, "helper"),      # a batch that is no multiple of 32 rows
+    ("bf16", 9_024, "helper"),
+    ("large", 8192, "divided"),     # the embedding update beside the second product of dLoss/dx
 ])
-def test_one_stream_and_two_streams_give_the_same_bits(name, batch):
-    """The step with every kernel on the caller's stream against the step that runs parts of itself
-    on the helper stream: same launches, same order of every sum, so every output bit agrees."""
+def test_one_stream_and_two_streams_give_the_same_bits(name, batch, form):
+    """The step with every kernel on the caller's stream (and the grouping carried by other launches where the products
+    allow it) against the step that runs parts of itself on the helper stream: the same order of every sum, so every
+    output bit agrees."""
     wl = get_workload(name).scaled(n_users=100_000, n_urls=1 << 16, n_images=5_000, M=4)
     outs = []
     for one in (False, True):
@@ -745,7 +758,11 @@ def test_one_stream_and_two_streams_give_the_same_bits(name, batch):
         st.one_stream = one
         src = PageViewSource(wl)
         for step in range(3):
-            g.gear_step(st, g.DeviceBatch.from_host(src.batch(step, batch=batch)), wl.M, 0.5)
+            dev = g.DeviceBatch.from_host(src.batch(step, batch=batch))
+            if step == 0 and not one:
+                assert form_of(st, dev, wl.M, 0.5) == form
+            else:
+                g.gear_step(st, dev, wl.M, 0.5)
         torch.cuda.synchronize()
         assert int(st.status.item()) == 0
         n = int(st.n_ready.item())
@@ -756,15 +773,17 @@ def test_one_stream_and_two_streams_give_the_same_bits(name, batch):
         assert torch.equal(a, b)
 
 
-def test_two_host_threads_stepping_their_own_states_on_one_device():
+@pytest.mark.parametrize("batches,forms", [((8_500, 9_001), ("helper", "helper")), ((1_200, 9_001), ("carried", "helper")),
+                                           ((1_200, 1_504), ("carried", "carried"))])
+def test_two_host_threads_stepping_their_own_states_on_one_device(batches, forms):
     """The entry points may be called from several host threads.  Two threads, each with its own state,
-    workspace and stream, step at the same time; a step forks to and joins from the device's one helper
-    stream with a fixed set of events, so their enqueues must not interleave.  Every thread must end
-    with exactly the bits it gets when it runs alone."""
+    workspace and stream, step at the same time; a long step forks to and joins from the device's one helper
+    stream, and a short one waits for and leaves an event, with a fixed set of events for all, so their enqueues
+    must not interleave.  Every thread must end with exactly the bits it gets when it runs alone."""
     import threading
     wls = [get_workload("small").scaled(n_users=50_000, n_urls=1 << 15, n_images=4_000, M=4),
            get_workload("bf16").scaled(n_users=50_000, n_urls=1 << 15, n_images=4_000, M=4)]
-    batches, steps = [1200, 1504], 6
+    steps = 6
 
     def run(i, stream, out, barrier=None):
         wl = wls[i]
@@ -776,7 +795,10 @@ def test_two_host_threads_stepping_their_own_states_on_one_device():
             if barrier is not None:
                 barrier.wait()
             for t in range(steps):
-                g.gear_step(st, dev[t], wl.M, 0.5)
+                if barrier is None and t == 0:
+                    assert form_of(st, dev[t], wl.M, 0.5) == forms[i]
+                else:
+                    g.gear_step(st, dev[t], wl.M, 0.5)
             stream.synchronize()
             assert int(st.status.item()) == 0
             n = int(st.n_ready.item())
@@ -853,21 +875,30 @@ def test_maximum_batch_and_nnz():
     pair.check_state("max sizes")
 
 
-def _error_path_workload(one_launch):
-    """tiny as it is (fp32, one hidden layer: weight gradients layer by layer, the caller's stream waits
-    for the check of the ids before the loss), or with two bf16 hidden layers (all weight gradients in
-    one launch, the caller's stream joins the helper only before their SGD)."""
-    wl = get_workload("tiny")
-    return wl.scaled(layers=(64, 32, 1), mlp_dtype="bf16") if one_launch else wl
+# What a step that must change nothing goes through: where the violation is found (in a launch that carries the check or
+# the segments, or on the helper stream) and what has to hear of it before it changes anything (the accumulation and the
+# parameter update behind it on the same stream; on two streams the update on the caller's, which waits for the helper's
+# first part, and in a divided step the small sums and the embedding update as well).
+ERROR_PATHS = {
+    "one hidden layer": ("tiny", {}, 512, "carried"),                           # segments with dLoss/dx
+    "two hidden layers": ("tiny", dict(layers=(64, 32, 1), mlp_dtype="bf16"), 512, "carried"),
+    "three hidden layers": ("tiny", dict(layers=(64, 32, 16, 1), mlp_dtype="bf16"), 512, "carried"),   # segments with the logit layer
+    "helper stream": ("bf16", dict(n_users=50_000, n_urls=1 << 15, n_images=4_000), 9_001, "helper"),
+    "divided": ("large", dict(n_users=50_000, n_urls=1 << 15, n_images=4_000), 8_192, "divided"),
+}
 
 
-@pytest.mark.parametrize("one_launch", [False, True])
-def test_bad_ids_are_reported_and_change_nothing(one_launch):
-    wl = _error_path_workload(one_launch)
+def _error_path(path, **changes):
+    name, scaled, batch, form = ERROR_PATHS[path]
+    return get_workload(name).scaled(**scaled).scaled(batch=batch, **changes), form
+
+
+@pytest.mark.parametrize("path", list(ERROR_PATHS))
+def test_bad_ids_are_reported_and_change_nothing(path):
+    wl, form = _error_path(path)
     cfg, st, _ = make_pair(wl)
     src = PageViewSource(wl)
-    g.gear_step(st, g.DeviceBatch.from_host(src.batch(0)), wl.M, wl.lr)
-    torch.cuda.synchronize()
+    assert form_of(st, g.DeviceBatch.from_host(src.batch(0)), wl.M, wl.lr) == form
     before = [t.clone() for t in (st.user_emb, st.url_emb, st.mlp_params, st.grad_accum, st.counts)]
     good = src.batch(1)
     for field, value in (("user_id", wl.n_users), ("url_id", -1), ("img_id", wl.n_images), ("img_off", None)):
@@ -879,6 +910,7 @@ def test_bad_ids_are_reported_and_change_nothing(one_launch):
         g.gear_step(st, g.DeviceBatch.from_host(bad), wl.M, wl.lr)
         torch.cuda.synchronize()
         assert int(st.status.item()) == g.GEAR_ERR_RANGE, field
+        assert int(st.n_ready.item()) == 0, field
         for a, b in zip(before, (st.user_emb, st.url_emb, st.mlp_params, st.grad_accum, st.counts)):
             assert torch.equal(a, b), field
     # the next good step clears the status and runs
@@ -887,30 +919,31 @@ def test_bad_ids_are_reported_and_change_nothing(one_launch):
     assert int(st.status.item()) == 0 and not torch.equal(before[4], st.counts)
 
 
-@pytest.mark.parametrize("one_launch", [False, True])
-def test_ready_list_over_capacity_is_reported_and_changes_nothing(one_launch):
-    wl = _error_path_workload(one_launch).scaled(M=1)
+@pytest.mark.parametrize("path", list(ERROR_PATHS))
+def test_ready_list_over_capacity_is_reported_and_changes_nothing(path):
+    wl, form = _error_path(path, M=1)
     cfg, st, _ = make_pair(wl, ready_cap=100)
-    before = [t.clone() for t in (st.user_emb, st.mlp_params, st.grad_accum, st.counts)]
-    g.gear_step(st, g.DeviceBatch.from_host(PageViewSource(wl).batch(0)), wl.M, wl.lr)   # nnz > 100 emissions
-    torch.cuda.synchronize()
+    before = [t.clone() for t in (st.user_emb, st.url_emb, st.mlp_params, st.grad_accum, st.counts)]
+    assert form_of(st, g.DeviceBatch.from_host(PageViewSource(wl).batch(0)), wl.M, wl.lr) == form   # nnz > 100 emissions
     assert int(st.status.item()) == g.GEAR_ERR_CAPACITY
     assert int(st.n_ready.item()) == 0               # a list that does not fit reads as empty, not as its length
-    for a, b in zip(before, (st.user_emb, st.mlp_params, st.grad_accum, st.counts)):
+    for a, b in zip(before, (st.user_emb, st.url_emb, st.mlp_params, st.grad_accum, st.counts)):
         assert torch.equal(a, b)
 
 
-@pytest.mark.parametrize("name", ["tiny", "large"])
+@pytest.mark.parametrize("name", ["tiny", "bf16", "large"])
 def test_a_step_that_fails_part_way_still_joins_the_helper_stream(name):
     """A launch that fails in the middle of a step's enqueue (forced from the host: the n-th launch is
     not enqueued and the call returns GEAR_ERR_HIP) must leave the caller's stream waiting for whatever
     the call had already put on the helper stream: once the caller's stream has drained, the helper
-    stream has nothing left to run, wherever the step stopped.  A fresh state then steps normally."""
+    stream has nothing left to run, wherever the step stopped.  (tiny is too short to use it: its launches fail one by one
+    on the caller's stream.)  A fresh state then steps normally."""
     wl = get_workload(name)
-    if name == "large":                                # two hidden bf16 layers: dLoss/dx in two products, one wgrad launch
-        wl = wl.scaled(n_users=100_000, n_urls=1 << 16, n_images=5_000, batch=8192)
+    if name != "tiny":                                 # helper stream; with dLoss/dx in two products in the larger one
+        wl = wl.scaled(n_users=100_000, n_urls=1 << 16, n_images=5_000, batch=8192 if name == "large" else 9_001)
     cfg, st, _ = make_pair(wl)
     dev = g.DeviceBatch.from_host(PageViewSource(wl).batch(0))
+    assert form_of(st, dev, wl.M, wl.lr) == {"tiny": "carried", "bf16": "helper", "large": "divided"}[name]
     stream = torch.cuda.current_stream()
     n_fail = 0
     try:
