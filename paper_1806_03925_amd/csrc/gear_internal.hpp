@@ -119,7 +119,7 @@ constexpr int kMaxPasses = 4;
 constexpr int kMaxRides = 3;                          // passes that other launches are asked to carry, if it is up to us
 constexpr int kMaxDigitBits = 12;
 constexpr int kSideDigitBits = 11;                    // of passes that other launches carry
-constexpr int kLongList = 65536;                      // ids from which a workgroup of the check takes several tiles, and a step's products are large
+constexpr int kLongList = 65536;                      // ids from which a workgroup of the check takes several tiles and the segments take few registers
 // Counts a tile publishes over all passes, at most.  A pass costs a launch and two memory latencies whatever its
 // radix, so a list takes as few passes as its keys allow within this (one up to 12 bits, two up to 22, then three);
 // it is what the regions that hold the counts have room for (24 KB per tile of 2048 keys).

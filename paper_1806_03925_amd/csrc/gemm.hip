@@ -5,7 +5,7 @@
 //   dgrad     d_{l-1}  = (d_l W_l) * [a_{l-1} > 0]     NT on the transposed weight copy
 //   wgrad     dW_l     = d_l^T h_{l-1}                  TN, split over the batch, fixed-order sum
 //
-// bf16, K a multiple of 32, at least 256 tiles: one workgroup = 8 wavefronts (2 x 4) on a 256 x 256
+// bf16, K a multiple of 32, about a tile for every CU (nt_dma, gemm_tn_choice): one workgroup = 8 wavefronts (2 x 4) on a 256 x 256
 // block tile, a wavefront owns 128 x 64 as 4 x 2 MFMA 32x32x16 tiles.  Operand tiles of k-depth 32
 // are copied global -> LDS by DMA (global_load_lds_dwordx4) into four stages.  NT form: two k-tiles
 // are copied together while the two before them are multiplied (the halves of a 128-byte line then

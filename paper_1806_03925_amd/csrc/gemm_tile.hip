@@ -686,8 +686,8 @@ int rows_of(NtShape shape) { return shape == kSmall ? 64 : 128; }
 // is how full the last round is: 40 us a round of large tiles at K = 512, 10.4 us a half round of small ones and 2 us more
 // to begin with (K = 512, bias + ReLU, us, 128 x 128 / 64 x 64: 16384 x 256 43.3 / 45.5, 16384 x 320 81 / 57, 8192 x 320
 // 42 / 36, 20000 x 384 82 / 86, 24000 x 320 121 / 86, 32768 x 64 43 / 25).
-// dLoss/dx keeps the large tiles from one per CU on: on two streams the grouping is still under way beside it, and two small
-// tiles leave it no room (16384 x 320 with 139 000 ids to group: the product 13 us shorter, the step 2 us longer).
+// dLoss/dx keeps the large tiles from one per CU on: alone 16384 x 320 x 256 is 13 us shorter on small ones, but a step of two
+// streams (139 000 ids) was 2 us longer with them; what takes the time back is not known.
 // EPI_F32 has two large tiles on a CU as well, a half round of them 19 us at K = 256 where one of small ones is 5.3 (16384 x
 // 384 39 / 35, 20000 x 320 39 / 40, 24000 x 576 76 / 78).
 // `coarse` (column sums of more, narrower row tiles would not fit their region) rules 64 x 64 out.

@@ -1,6 +1,6 @@
-// The parts of the Sparse-Part MLP that are not matrix products: the logit layer with the loss and its derivative, bias gradients and the logit layer's weight
-// gradient, each followed by its SGD update (Section 3, step 4: forward to the loss,
-// back-propagation on the Sparse Part, gradients applied to the Sparse Part's parameters).
+// The part of the Sparse-Part MLP that is not a matrix product (Section 3, step 4: forward to the loss and the first step
+// back): the logit layer with the loss and its derivative, the delta of the last hidden layer, and partial sums of the
+// logit layer's weight gradient, both biases' gradients and the loss.  params.hip adds them up and applies them.
 #include "group_device.hpp"
 
 #include <type_traits>
