@@ -86,6 +86,47 @@ __device__ __forceinline__ void add_rows(float (&acc)[Cols<GT>::N], const int32_
   }
 }
 
+// The same where the sorted order only says which position of the batch comes next (AccumPlan::row_at): a chain of three
+// loads.  The places are fetched two batches of rows ahead and the views one, so that a long group waits for its rows only
+// (one image in most of 17 000 occurrences: a step of 2000 views took 97 us with the loads one after the other).
+template <typename GT>
+__device__ __forceinline__ void add_rows_at(float (&acc)[Cols<GT>::N], const AccumPlan &plan, const GT *__restrict__ col, int D, int qa,
+                                            int qb) {
+  constexpr int N = Cols<GT>::N, R = kRowsInFlight;
+  if (qa >= qb) return;
+  int at[R], view[R];
+  float scale[R];
+#pragma unroll
+  for (int i = 0; i < R; ++i) at[i] = plan.row_at[min(qa + i, qb - 1)];
+#pragma unroll
+  for (int i = 0; i < R; ++i) view[i] = plan.row_view[at[i]], scale[i] = plan.row_scale[at[i]];
+#pragma unroll
+  for (int i = 0; i < R; ++i) at[i] = plan.row_at[min(qa + R + i, qb - 1)];
+  for (int q = qa; q < qb; q += R) {
+    uint4 raw[R];
+    float by[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      raw[i] = *reinterpret_cast<const uint4 *>(col + (size_t)view[i] * D);
+      by[i] = scale[i];
+    }
+    if (q + R < qb) {
+#pragma unroll
+      for (int i = 0; i < R; ++i) view[i] = plan.row_view[at[i]], scale[i] = plan.row_scale[at[i]];
+#pragma unroll
+      for (int i = 0; i < R; ++i) at[i] = plan.row_at[min(q + 2 * R + i, qb - 1)];
+    }
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+      if (q + i < qb) {
+        float v[N];
+        Cols<GT>::widen(raw[i], v);
+#pragma unroll
+        for (int k = 0; k < N; ++k) acc[k] += v[k] * by[i];
+      }
+  }
+}
+
 // What the launch's first workgroups do of the embedding update: nothing (a divided step has it done), its second level
 // (two streams: level 1 and the image counters are the launch before), or level 1 and the counters (one stream: level 2
 // rides with the parameter update).  Level 1 ahead of the units on two streams held their wavefronts down to three a SIMD
@@ -101,7 +142,7 @@ struct NoWork {};
 // kChunks needs 132 registers where the units alone take 44: three wavefronts a SIMD, which still have 72 KB of rows in
 // flight on a CU, as much as a memory latency asks for.  kSpans has eight partials of a long run in flight: 59 (with 32
 // in flight 138).
-template <typename GT, int RIDE>
+template <typename GT, int RIDE, bool AT>
 __global__ void __launch_bounds__(256, RIDE == kChunks ? 3 : 1)
 k_accumulate(AccumPlan plan, const GT *__restrict__ dx, int D, float *__restrict__ accum, int M,
              int32_t *__restrict__ ready_ids, float *__restrict__ ready_grads, std::conditional_t<RIDE == kNoRide, NoWork, RideWork> emb,
@@ -151,6 +192,12 @@ k_accumulate(AccumPlan plan, const GT *__restrict__ dx, int D, float *__restrict
     float *arow = accum + (size_t)d.image * D;
     for (int cg = threadIdx.x; cg < DC; cg += blockDim.x) {
       const GT *col = dx + N * cg;
+      auto add = [&](float (&to)[N], int qa, int qb) {
+        if constexpr (AT)
+          add_rows_at<GT>(to, plan, col, D, qa, qb);
+        else
+          add_rows<GT>(to, plan.row_view, plan.row_scale, col, D, qa, qb);
+      };
       float acc[N];
 #pragma unroll
       for (int k = 0; k < N; ++k) acc[k] = 0.0f;
@@ -159,7 +206,7 @@ k_accumulate(AccumPlan plan, const GT *__restrict__ dx, int D, float *__restrict
         const int p = d.phase;
         const int len0 = min(M - p, d.s1 - d.s0);
         if (p != 0) load_f32<N>(arow + N * cg, acc);
-        add_rows<GT>(acc, plan.row_view, plan.row_scale, col, D, d.s0, d.s0 + len0);
+        add(acc, d.s0, d.s0 + len0);
         const bool complete = (p + len0 == M);
         if (complete) {
           store_div<N>(ready_grads + (size_t)d.slot * D + N * cg, acc, fM);
@@ -179,12 +226,12 @@ k_accumulate(AccumPlan plan, const GT *__restrict__ dx, int D, float *__restrict
           float rest[N];
 #pragma unroll
           for (int k = 0; k < N; ++k) rest[k] = 0.0f;
-          add_rows<GT>(rest, plan.row_view, plan.row_scale, col, D, d.s1 - tail, d.s1);
+          add(rest, d.s1 - tail, d.s1);
           store_f32<N>(arow + N * cg, rest, 1.0f);
         }
       } else {
         // a complete middle group of M rows
-        add_rows<GT>(acc, plan.row_view, plan.row_scale, col, D, d.q0, d.q0 + M);
+        add(acc, d.q0, d.q0 + M);
         store_div<N>(ready_grads + (size_t)d.slot * D + N * cg, acc, fM);
         if (cg == 0) ready_ids[d.slot] = d.image;
       }
@@ -233,16 +280,18 @@ hipError_t launch_accumulate(const gear_config &cfg, const GroupProblem &img, co
     if (work.count_blocks > 256) work.count_blocks = 256;
     blocks += 2 * work.blocks + work.count_blocks;
   }
-#define GEAR_ACC(T, R, EMB)                                                                                                \
-  hipLaunchKernelGGL((k_accumulate<T, R>), dim3(blocks), dim3(threads), 0, s, plan, (const T *)dx_dfv, D, grad_accum, M, \
+#define GEAR_ACC(T, R, AT, EMB)                                                                                            \
+  hipLaunchKernelGGL((k_accumulate<T, R, AT>), dim3(blocks), dim3(threads), 0, s, plan, (const T *)dx_dfv, D, grad_accum, M, \
                      ready_ids, ready_grads, EMB, status)
 #define GEAR_ACC_T(T)              \
   if (!emb)                        \
-    GEAR_ACC(T, kNoRide, NoWork{}); \
+    GEAR_ACC(T, kNoRide, false, NoWork{}); \
   else if (level2)                 \
-    GEAR_ACC(T, kSpans, work);     \
+    GEAR_ACC(T, kSpans, false, work); \
+  else if (plan.row_at)            \
+    GEAR_ACC(T, kChunks, true, work); \
   else                             \
-    GEAR_ACC(T, kChunks, work)
+    GEAR_ACC(T, kChunks, false, work)
   if (cfg.mlp_dtype == GEAR_BF16) {
     GEAR_ACC_T(bf16_t);
   } else {

@@ -1,5 +1,6 @@
 // C ABI of libgear: argument checks, workspace layout and the launch sequence of one step.
 #include "gear_internal.hpp"
+#include "rows.hpp"
 
 #include <math.h>
 #include <string.h>
@@ -17,12 +18,6 @@ size_t take(size_t *cursor, size_t bytes) {
   const size_t at = *cursor;
   *cursor = (at + bytes + kAlign - 1) / kAlign * kAlign;
   return at;
-}
-
-int bits_for(int64_t range) {
-  int b = 1;
-  while (b < 31 && ((int64_t)1 << b) < range) ++b;
-  return b;
 }
 
 // `bits`: what the keys have at most
@@ -183,6 +178,7 @@ bool make_layout(const gear_config &c, Layout *lay) {
     lay->g[s].totals = lay->tickets + (kTickets + s * room) * sizeof(float);
     lay->g[s].total_words = (int32_t)room;
   }
+  lay->pool_bytes = pool * sizeof(float);
   lay->dx_emb = take(&cur, B * 2 * c.emb_dim * sizeof(float));
   lay->dx_dfv = take(&cur, B * c.dfv_dim * ab);
   max_partial = wgrad_region_bytes(c.mlp_dtype, lay->out_dim, lay->in_dim, L - 1, c.max_batch);
@@ -582,7 +578,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
                                                       "dgrad_gemm_l3", "dgrad_gemm_l4", "dgrad_gemm_l5",
                                                       "dgrad_gemm_l6", "dgrad_gemm_l7"};
   if (B == 0) {
-    GEAR_RUN("begin", launch_begin(out->status, failed, out->n_ready, out->loss, ZeroList{}, dt, nullptr, 0, s));
+    GEAR_RUN("begin", launch_begin(out->status, failed, out->n_ready, out->loss, ZeroList{}, dt, nullptr, 0, false, s));
     return GEAR_OK;
   }
   int32_t *occ_view = (int32_t *)(ws + lay.occ_view);
@@ -594,8 +590,11 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   double macs = 0.0;
   for (int l = 0; l < L - 1; ++l) macs += (double)B * lay.in_dim[l] * lay.out_dim[l];
   const bool is_short = (long long)2 * B + b->nnz < kOneStreamIds && macs * (dt == GEAR_BF16 ? 1 : 4) < kOneStreamMacs;
-  const bool one_stream = out->one_stream != 0 || (moderate && is_short);
-  const bool carried = one_stream && moderate;
+  // A short step in blocks of views: the whole network in one launch, with the grouping of the ids beside it (rows.hip).
+  RowsPlan rows;
+  const bool by_rows = is_short && plan_rows(*cfg, lay, B, b->nnz, &rows);
+  const bool one_stream = out->one_stream != 0 || by_rows || (moderate && is_short);
+  const bool carried = one_stream && moderate && !by_rows;
 
   // grouping of the three id lists and the plan of the per-image accumulation
   GroupBatch gb;
@@ -623,6 +622,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   plan.row_view = (int32_t *)(ws + lay.row_view);
   plan.row_scale = (float *)(ws + lay.row_scale);
   plan.n_units = (int32_t *)(ws + lay.n_units);
+  plan.row_at = by_rows ? gb.p[2].perm : nullptr;
   const PlanArgs plan_args = {plan, occ_view, b->img_off, counts, M, out->ready_cap, out->n_ready, out->status};
   // Not carried: what depends only on ids and counters (the check of the ids, the grouping, the accumulation plan) runs on
   // the helper stream while the main stream gathers and runs the forward pass.  The
@@ -642,13 +642,17 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
     // the first product then needs no event, and behind the gather's many workgroups the copies would not get onto the
     // device before it ends anyway.
     CastJob jobs[GEAR_MAX_LAYERS];
-    for (int l = 0; l < L; ++l)
+    const int n_jobs = by_rows ? L - 1 : L;   // the logit layer is one row, which rows.hip takes from the parameters
+    for (int l = 0; l < n_jobs; ++l)
       jobs[l] = CastJob{t->mlp_params + lay.w_off[l], ws + lay.wc[l], ws + lay.wct[l], lay.out_dim[l], lay.in_dim[l]};
     ZeroList zero;
-    group_zero_list(gb, &zero);
-    GEAR_RUN("begin", launch_begin(out->status, failed, out->n_ready, out->loss, zero, dt, jobs, L, s));
+    if (by_rows)
+      local_zero_list(gb, &zero);
+    else
+      group_zero_list(gb, &zero);
+    GEAR_RUN("begin", launch_begin(out->status, failed, out->n_ready, out->loss, zero, dt, jobs, n_jobs, by_rows, s));
   }
-  if (!carried) GEAR_HIP(lane.fork());
+  if (!carried && !by_rows) GEAR_HIP(lane.fork());
   // Carried: the links of the grouping in order, each taken by the next launch that can.
   SideTask task;
   int link = 0;
@@ -674,7 +678,15 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   int n_wp = 0;
   for (int l = L - 2; l >= 0; --l)
     wp[n_wp++] = TnProblem{ws + lay.delta[l], l == 0 ? x : ws + lay.h[l - 1], nullptr, lay.out_dim[l], lay.in_dim[l]};
-  {
+  float *logits = (float *)(ws + lay.logits), *dz = (float *)(ws + lay.dz);
+  float *dx_emb = (float *)(ws + lay.dx_emb);
+  void *dx_dfv = ws + lay.dx_dfv;
+  if (by_rows) {
+    for (int piece = 0; piece < kMaxProblems + 2 * L; ++piece)   // three lists, gather, every layer forward and back but the logit's
+      if (fail_injected()) return GEAR_ERR_HIP;
+    const LocalTask local = local_task(rows, gb, plan_args, failed);
+    GEAR_RUN("view_blocks", launch_rows(*cfg, lay, rows, *b, *t, dfv_cache, ws, local, s));
+  } else {
     const CheckTask check = check_task(gb, b->img_off, occ_view, B, b->nnz, failed, out->status);
     if (carried && fail_injected()) return GEAR_ERR_HIP;
     GEAR_RUN("gather_pool", launch_gather_pool(*cfg, *b, *t, dfv_cache, x, s, carried ? &check : nullptr));
@@ -684,7 +696,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   uint8_t *relu_bits[GEAR_MAX_LAYERS] = {};
   if (dt == GEAR_BF16)
     for (int l = 0; l + 2 < L; ++l) relu_bits[l] = (uint8_t *)(ws + lay.relu_bits[l]);
-  for (int l = 0; l < L - 1; ++l) {
+  for (int l = 0; l < L - 1 && !by_rows; ++l) {
     GEAR_BOARD();
     GEAR_RUN(kFwd[l], launch_gemm_nt(dt, l == 0 ? x : ws + lay.h[l - 1], ws + lay.wc[l], B, lay.out_dim[l],
                                      lay.in_dim[l], EPI_BIAS_RELU, t->mlp_params + lay.b_off[l], nullptr,
@@ -693,7 +705,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   // The helper stream's launches are issued after the forward pass's: where the host is not ahead of the
   // device (a caller that waits for every step), the gather then starts as soon as the step does, not
   // after the host has issued the grouping's launches.
-  if (!carried) {
+  if (!carried && !by_rows) {
     hipStream_t s = helper;  // the launches of this block go to the helper stream
     GEAR_RUN("group_ids", launch_check(gb, b->img_off, occ_view, B, b->nnz, failed, out->status, s));
     for (int pass = 0; pass < group_passes(gb); ++pass) GEAR_RUN("group_ids", launch_radix_pass(gb, pass, failed, s));
@@ -701,29 +713,29 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
     GEAR_HIP(lane.mark_checked());
   }
 
-  float *logits = (float *)(ws + lay.logits), *dz = (float *)(ws + lay.dz);
   // Until its first kernel that changes caller state (the first SGD on a hidden layer's weights), the
   // caller's stream writes the workspace only and need not know whether the ids were in range or the
   // ready list fits.  Just before that kernel the stream waits for the helper's first part, so that the
   // status word is final.
-  GEAR_BOARD();
-  GEAR_RUN("logit_loss", launch_logit_loss(dt, ws + lay.h[L - 2], ws + lay.wc[L - 1], t->mlp_params + lay.b_off[L - 1],
+  if (!by_rows) {
+    GEAR_BOARD();
+    GEAR_RUN("logit_loss", launch_logit_loss(dt, ws + lay.h[L - 2], ws + lay.wc[L - 1], t->mlp_params + lay.b_off[L - 1],
                                            b->label, B, lay.in_dim[L - 1], logits, dz, ws + lay.delta[L - 2],
                                            (float *)(ws + lay.loss_partial), failed, s, passenger()));
+  }
 
   // backward through the hidden layers down to dLoss/dx (all from the pre-step operand copies)
   // Each product that makes the delta of a hidden layer also leaves that layer's bias gradient (column
   // sums of the delta) as per-row-tile partials; they are added in tile order at the end of the step.
-  float *dx_emb = (float *)(ws + lay.dx_emb);
-  void *dx_dfv = ws + lay.dx_dfv;
-  float *cpart = (float *)(ws + lay.colsum_partial), *wpart = (float *)(ws + lay.wgrad_partial);
+  float *cpart = (float *)(ws + (by_rows ? rows.colsum : lay.colsum_partial)), *wpart = (float *)(ws + lay.wgrad_partial);
   const EmbeddingWork emb = embedding_work(*cfg, gb.p[0], gb.p[1], dx_emb, t->user_emb, t->url_emb, (float *)(ws + lay.emb_partial),
                                            opt, mom_user, mom_url, plan, counts);
   // Small sums whose results nothing in the step reads: the loss, the logit layer and the biases (column sums of deltas,
   // left as per-row-tile partials by the products that made them).
   ColumnSum columns[kMaxColumnSums];
   int n_columns = 0;
-  const LogitSums sums = logit_sums((const float *)(ws + lay.loss_partial), B, lay.in_dim[L - 1]);
+  const LogitSums sums = by_rows ? rows_sums(rows, (const float *)(ws + lay.loss_partial), lay.in_dim[L - 1])
+                                 : logit_sums((const float *)(ws + lay.loss_partial), B, lay.in_dim[L - 1]);
   auto column = [&](const float *partial, int parts, int width, int64_t at) {
     columns[n_columns++] = ColumnSum{partial, t->mlp_params + at, moments_at(mom_mlp, at), parts, width};
   };
@@ -731,11 +743,12 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   column(sums.delta, sums.parts, lay.in_dim[L - 1], lay.b_off[L - 2]);
   column(sums.bias, sums.parts, 1, lay.b_off[L - 1]);
   for (int l = L - 2; l > 0; --l)
-    column(cpart + lay.colsum_at[l], gemm_nt_colsum_parts(dt, B, lay.in_dim[l], lay.out_dim[l], lay.colsum_coarse),
+    column(cpart + (by_rows ? rows.colsum_at[l] : lay.colsum_at[l]),
+           by_rows ? rows.blocks : gemm_nt_colsum_parts(dt, B, lay.in_dim[l], lay.out_dim[l], lay.colsum_coarse),
            lay.out_dim[l - 1], lay.b_off[l - 1]);
   const LossSum loss = {sums.loss, out->loss, sums.parts, B};
   bool divided = false;
-  for (int l = L - 2; l >= 0; --l) {
+  for (int l = L - 2; l >= 0 && !by_rows; --l) {
     if (l > 0) {
       const bool by_bits = relu_bits[l - 1] != nullptr;
       GEAR_RUN(kDgrad[l], launch_gemm_nt(dt, ws + lay.delta[l], ws + lay.wct[l], B, lay.in_dim[l], lay.out_dim[l],
@@ -757,7 +770,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
         GEAR_HIP(lane.fork());
         {
           hipStream_t s = helper;
-          GEAR_RUN("small_sums", launch_param_update(nullptr, 0, 1, columns, n_columns, loss, nullptr, opt, failed, s));
+          GEAR_RUN("small_sums", launch_param_update(nullptr, 0, 1, columns, n_columns, loss, nullptr, nullptr, opt, failed, s));
           GEAR_RUN("embedding_update", launch_embedding_update(emb, true, failed, s));
         }
         divided = true;
@@ -822,7 +835,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
     first += n;
     const bool sums_too = first == n_wp && !divided;   // else the helper stream has done them
     GEAR_RUN("param_update", launch_param_update(sp, n, splits, columns, sums_too ? n_columns : 0, sums_too ? loss : LossSum{},
-                                                 sums_too && one_stream ? &emb : nullptr, opt, failed, s));
+                                                 sums_too && one_stream ? &emb : nullptr, by_rows ? out->n_ready : nullptr, opt, failed, s));
   }
   GEAR_HIP(lane.wait(true));  // the step ends on the caller's stream
   if (out->dbg_img_unique && b->nnz > 0)
@@ -945,7 +958,7 @@ gear_status gear_gemm(int32_t dtype, int32_t form, const void *A, const void *B,
     const Optim minus = {-1.0f, 0.0f, 0.0f, 0.0f, 1.0f, 0};   // out = 0 - (-1) * sum of the partials
     const Moments none = {nullptr, nullptr};
     const SplitkProblem sum = {partial, (float *)out, none, (int64_t)M * N};
-    GEAR_HIP(launch_param_update(&sum, 1, splits, nullptr, 0, LossSum{}, nullptr, minus, status, s));
+    GEAR_HIP(launch_param_update(&sum, 1, splits, nullptr, 0, LossSum{}, nullptr, nullptr, minus, status, s));
   } else {
     return GEAR_ERR_INVALID;
   }

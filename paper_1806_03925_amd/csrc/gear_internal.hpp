@@ -156,6 +156,12 @@ struct GroupBatch {
 // eight 139).
 inline int widest_digit(int n) { return n > 16 * kSortTile ? 9 : kMaxDigitBits; }
 
+inline int bits_for(int64_t range) {
+  int b = 1;
+  while (b < 31 && ((int64_t)1 << b) < range) ++b;
+  return b;
+}
+
 // fewest passes over keys of `bits` bits in digits of up to `widest` bits
 inline int radix_passes(int bits, int most_words, int widest) {
   int passes = 1;
@@ -181,6 +187,7 @@ struct AccumPlan {
   UnitDesc *units;       // [nnz]
   int32_t *row_view;     // [nnz] view that owns the occurrence at each sorted position
   float *row_scale;      // [nnz] 1 / (images of that view): backward of the mean
+  const int32_t *row_at; // [nnz] where the two are by position in the batch: that of each sorted one (else NULL)
   int32_t *n_units;      // [1]
 };
 
@@ -218,6 +225,23 @@ struct SideTask {
   int32_t *failed;
 };
 struct NoTask {};
+// the grouping of short lists in LDS (local_group.hpp)
+constexpr int kLocalMost = 20480;                    // ids of a list (62 * 512 at most: a thread's positions are bits of a word)
+struct LocalList {
+  const int32_t *keys_in;
+  int64_t range;
+  int n, bits, parts_log2, value_bits;   // of an id, of the number of parts, of a position
+  int32_t *sorted_keys, *perm;
+  uint32_t *spare;                       // [n]
+};
+struct LocalTask {
+  LocalList list[kMaxProblems];          // segments are made of the last one
+  PlanArgs plan;
+  int32_t *unique, *segoff, *n_unique;   // of the last list; the first two may be NULL
+  uint32_t *state;                       // [parts][3] what the parts of the last list publish
+  int32_t *ticket, *failed;
+  int blocks, room;                      // workgroups; items that LDS has room for
+};
 
 // ------------------------------------------------------------------------------------------------
 // workspace layout (byte offsets from a 256-byte aligned base)
@@ -243,6 +267,7 @@ struct Layout {
     size_t keys[2], vals[2], totals, state, unique, segoff, n_unique;
     int32_t total_words;             // room for `totals`
   } g[kMaxProblems];
+  size_t pool_bytes;                  // of the region of sums that begins at loss_partial
   size_t tickets, seg_state, units, row_view, row_scale, n_units;
   size_t expiry_marks, expiry_tiles;  // gear_expired_ids: byte map over the images, marked bytes per tile
   size_t total;
@@ -276,7 +301,7 @@ struct CastJob {
 };
 hipError_t launch_clear(const ZeroList &zero, hipStream_t s);
 hipError_t launch_begin(int32_t *status, int32_t *failed, int32_t *n_ready, float *loss, const ZeroList &zero, int dtype, const CastJob *jobs,
-                        int count, hipStream_t s);
+                        int count, bool packed, hipStream_t s);
 void group_zero_list(const GroupBatch &gb, ZeroList *z);
 CheckTask check_task(const GroupBatch &gb, const int32_t *img_off, int32_t *occ_view, int B, int nnz, int32_t *failed,
                      int32_t *status);
@@ -357,11 +382,12 @@ struct LossSum {   // *loss = (sum of the partial sums) / B; parts = 0: not want
   int parts, B;
 };
 constexpr int kMaxColumnSums = GEAR_MAX_LAYERS + 2;
-// all of that in one launch, and level 2 of an embedding update (may be NULL)
+// all of that in one launch, and level 2 of an embedding update (may be NULL); n_ready (may be NULL) is cleared if the step
+// has failed
 struct EmbeddingWork;
 hipError_t launch_param_update(const SplitkProblem *p, int count, int splits, const ColumnSum *c, int n_columns,
-                               const LossSum &loss, const EmbeddingWork *emb, const Optim &opt, const int32_t *status,
-                               hipStream_t s);
+                               const LossSum &loss, const EmbeddingWork *emb, int32_t *n_ready, const Optim &opt,
+                               const int32_t *status, hipStream_t s);
 // the same products on tiles of moderate size (gemm_tile.hip)
 hipError_t launch_gemm_nt_tile(int dtype, const void *A, const void *B, int M, int N, int K, int epilogue,
                                const float *bias, const void *aux, void *out, int split, float *colpart,

@@ -101,6 +101,7 @@ struct ParamArgs {
   int first_column_block[kMaxColumnSums];
   int columns_at, loss_at;      // first workgroup of the column sums, and the loss's
   LossSum loss;
+  int32_t *n_ready;             // cleared by a step that has failed: its lists do not know of each other
 };
 struct SpanWork {
   EmbeddingWork w;
@@ -111,7 +112,10 @@ struct NoSpans {};
 template <bool SPANS>
 __global__ void __launch_bounds__(256) k_param_update(ParamArgs args, std::conditional_t<SPANS, SpanWork, NoSpans> spans,
                                                       Optim opt, const int32_t *__restrict__ status) {
-  if (*status != 0) return;
+  if (*status != 0) {
+    if (blockIdx.x == 0 && threadIdx.x == 0 && args.n_ready) *args.n_ready = 0;
+    return;
+  }
   int block = blockIdx.x;
   if constexpr (SPANS) {
     if (block < 2 * spans.blocks) {
@@ -146,8 +150,8 @@ __global__ void __launch_bounds__(256) k_param_update(ParamArgs args, std::condi
 }  // namespace
 
 hipError_t launch_param_update(const SplitkProblem *p, int count, int splits, const ColumnSum *c, int n_columns,
-                               const LossSum &loss, const EmbeddingWork *emb, const Optim &opt, const int32_t *status,
-                               hipStream_t s) {
+                               const LossSum &loss, const EmbeddingWork *emb, int32_t *n_ready, const Optim &opt,
+                               const int32_t *status, hipStream_t s) {
   if (count < 0 || count > GEAR_MAX_LAYERS || splits < 1 || n_columns < 0 || n_columns > kMaxColumnSums)
     return hipErrorInvalidValue;
   ParamArgs args;
@@ -155,6 +159,7 @@ hipError_t launch_param_update(const SplitkProblem *p, int count, int splits, co
   args.n_columns = n_columns;
   args.splits = splits;
   args.loss = loss;
+  args.n_ready = n_ready;
   int blocks = 0;
   for (int i = 0; i < GEAR_MAX_LAYERS; ++i) {
     args.p[i] = i < count ? p[i] : SplitkProblem{nullptr, nullptr, Moments{nullptr, nullptr}, 0};

@@ -5,7 +5,7 @@
 namespace gear {
 namespace {
 
-// wc = W as MLP operands [rows x cols], wct = its transpose [cols x rows]; both from the fp32 master.
+// wc = W as MLP operands [rows x cols], wct = its transpose [cols x rows]; both from the fp32 master, row-major or `packed`.
 // One launch serves all layers: a workgroup owns a 32 x 32 tile of one of them; those behind the tiles clear words.
 struct BeginArgs {
   int count, cast_blocks;
@@ -23,7 +23,33 @@ __global__ void __launch_bounds__(256) k_clear(ZeroList zero) {
   clear_words(zero, (int64_t)blockIdx.x * 256 + threadIdx.x, (int64_t)gridDim.x * 256);
 }
 
-template <typename T>
+// Operand order of rows.hip: all rows' 64 bytes of a k-step lie together, sixteen rows at a time, and of those lane by lane:
+// the 16 bytes of row r at q * rows + r hold k = 32 s + 8 q .. + 7 (bf16) or 16 s + q, + 4, + 8, + 12 (fp32).  What is left of
+// k is a step of fewer q (bf16) or of 8 bytes (fp32).  As many elements as the matrix has.  `row` counts in the operand,
+// get(k) is element (row, k) of the 32 x 32 tile whose first column is k0.
+template <typename T, typename Get>
+__device__ __forceinline__ void put_packed(T *dst, int N, int K, int row, int k0, int piece, Get get) {
+  if (row >= N) return;
+  const int first = row & ~15, rows = min(16, N - first), r = row & 15;
+  if constexpr (sizeof(T) == 2) {   // piece: of four
+    const int k = 8 * piece, s = k0 / 32;
+    if (k0 + k >= K) return;
+    const int pieces = min(4, K / 8 - 4 * s);
+    uint32_t w[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w[e] = (uint32_t)from_f32<T>(get(k + 2 * e)) | ((uint32_t)from_f32<T>(get(k + 2 * e + 1)) << 16);
+    *reinterpret_cast<uint4 *>(dst + (size_t)32 * s * N + ((size_t)first * pieces + piece * rows + r) * 8) = make_uint4(w[0], w[1], w[2], w[3]);
+  } else {                          // piece: of eight
+    const int q = piece & 3, k = 16 * (piece >> 2), s = (k0 + k) / 16;
+    T *step = dst + (size_t)16 * s * N;
+    if (k0 + k + 16 <= K)
+      *reinterpret_cast<float4 *>(step + ((size_t)first * 4 + q * rows + r) * 4) = make_float4(get(k + q), get(k + 4 + q), get(k + 8 + q), get(k + 12 + q));
+    else if (k0 + k < K)
+      *reinterpret_cast<float2 *>(step + ((size_t)first * 4 + q * rows + r) * 2) = make_float2(get(k + q), get(k + 4 + q));
+  }
+}
+
+template <typename T, bool PACKED>
 __global__ void __launch_bounds__(256) k_begin(BeginArgs args, int32_t *status, int32_t *failed, int32_t *n_ready, float *loss) {
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     *status = 0;
@@ -53,11 +79,19 @@ __global__ void __launch_bounds__(256) k_begin(BeginArgs args, int32_t *status, 
     float v = 0.0f;
     if (r < rows && c < cols) {
       v = w[(size_t)r * cols + c];
-      wc[(size_t)r * cols + c] = from_f32<T>(v);
+      if constexpr (!PACKED) wc[(size_t)r * cols + c] = from_f32<T>(v);
     }
     tile[rr][tx] = v;
   }
   __syncthreads();
+  if constexpr (PACKED) {
+    const int at = threadIdx.x & 31, piece = threadIdx.x >> 5;
+    auto of_row = [&](int k) { return tile[at][k]; };
+    auto of_col = [&](int k) { return tile[k][at]; };
+    if (sizeof(T) == 4 || piece < 4) put_packed(wc, rows, cols, r0 + at, c0, piece, of_row);
+    if (sizeof(T) == 4 || piece >= 4) put_packed(wct, cols, rows, c0 + at, r0, sizeof(T) == 4 ? piece : piece - 4, of_col);
+    return;
+  }
 #pragma unroll
   for (int cc = ty; cc < 32; cc += 8) {
     const int c = c0 + cc, r = r0 + tx;
@@ -80,7 +114,7 @@ hipError_t launch_clear(const ZeroList &zero, hipStream_t s) {
 }
 
 hipError_t launch_begin(int32_t *status, int32_t *failed, int32_t *n_ready, float *loss, const ZeroList &zero, int dtype, const CastJob *jobs,
-                        int count, hipStream_t s) {
+                        int count, bool packed, hipStream_t s) {
   if (count < 0 || count > GEAR_MAX_LAYERS) return hipErrorInvalidValue;
   BeginArgs args;
   args.count = count;
@@ -92,10 +126,19 @@ hipError_t launch_begin(int32_t *status, int32_t *failed, int32_t *n_ready, floa
     if (i < count) args.cast_blocks += ((jobs[i].cols + 31) / 32) * ((jobs[i].rows + 31) / 32);
   }
   const dim3 grid((unsigned)(args.cast_blocks + clear_blocks(zero)));
-  if (dtype == GEAR_BF16)
-    hipLaunchKernelGGL(k_begin<bf16_t>, grid, dim3(256), 0, s, args, status, failed, n_ready, loss);
-  else
-    hipLaunchKernelGGL(k_begin<float>, grid, dim3(256), 0, s, args, status, failed, n_ready, loss);
+#define GEAR_BEGIN(T, P) hipLaunchKernelGGL((k_begin<T, P>), grid, dim3(256), 0, s, args, status, failed, n_ready, loss)
+  if (dtype == GEAR_BF16) {
+    if (packed)
+      GEAR_BEGIN(bf16_t, true);
+    else
+      GEAR_BEGIN(bf16_t, false);
+  } else {
+    if (packed)
+      GEAR_BEGIN(float, true);
+    else
+      GEAR_BEGIN(float, false);
+  }
+#undef GEAR_BEGIN
   return hipGetLastError();
 }
 

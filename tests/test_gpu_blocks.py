@@ -1,0 +1,115 @@
+"""Short steps that go in blocks of views, with their ids sorted in LDS (rows.hip, local_group.hpp), beside the oracle: blocks
+that the batch does not fill, widths that no tile and no k-step divides, lists at the borders of what a part or a workgroup
+holds.  The comparison and its bounds are those of tests/test_gpu_parity.py; groupings are compared bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+from test_gpu_tiles import beside_the_oracle
+
+pytestmark = pytest.mark.gpu
+
+
+def wl_of(dtype, batch, layers, d, D, **kw):
+    from gear_inputs import get_workload
+    return get_workload("tiny").scaled(batch=batch, layers=layers, emb_dim=d, dfv_dim=D, emb_dtype=dtype, dfv_dtype=dtype,
+                                       mlp_dtype=dtype, **kw)
+
+
+def in_blocks(pair, batch, what):
+    import paper_1806_03925_amd as g
+    pair.st.profile = g.GearProfile()
+    pair.step(batch, pair.wl.lr, what)
+    names = [name for name, _ in pair.st.profile.spans()]
+    pair.st.profile.close()
+    pair.st.profile = None
+    return "view_blocks" in names
+
+
+@pytest.mark.parametrize("dtype,batch,layers,d,D", [
+    ("f32", 1, (8, 1), 8, 8), ("f32", 15, (24, 1), 8, 24), ("f32", 17, (72, 40, 1), 24, 72), ("f32", 33, (392, 1), 8, 136),
+    ("bf16", 1, (8, 1), 8, 8), ("bf16", 31, (24, 1), 16, 40), ("bf16", 65, (72, 136, 8, 1), 24, 72), ("bf16", 129, (520, 1), 8, 104),
+    ("bf16", 4_096, (40, 24, 1), 8, 40), ("bf16", 4_097, (40, 24, 1), 8, 40),   # 16 views a block, 32
+    ("f32", 300, (64,) * 7 + (1,), 8, 64),
+])
+def test_blocks_at_the_edges_of_tiles(dtype, batch, layers, d, D):
+    from gear_inputs import PageViewSource
+    wl = wl_of(dtype, batch, layers, d, D)
+    pair = beside_the_oracle(wl)
+    src = PageViewSource(wl)
+    for step in range(2):
+        assert in_blocks(pair, src.batch(step), f"{dtype} {batch} {layers} step {step}")
+    pair.check_state(f"{dtype} {batch} {layers}")
+
+
+@pytest.mark.parametrize("n_images,nnz,popular,blocks", [
+    (2_000, 0, 0.0, True), (1, 1_024, 1.0, True),
+    (2_000, 1_024, 0.0, True), (2_000, 1_025, 0.0, True),   # one part, two
+    (3_000_000, 4_099, 0.1, True),                           # as many parts as 32 bits of an item ask for
+    (2_000, 20_480, 0.6, True),                              # a part that LDS holds once
+    (2_000, 20_480, 0.97, True),                             # and one that it does not hold
+    (2_000, 20_481, 0.1, False),                             # too long a list
+])
+def test_lists_at_the_edges_of_parts(n_images, nnz, popular, blocks):
+    """`popular`: the share of the occurrences that are one image, the last of all."""
+    from gear_inputs.pageviews import PageViewBatch
+    B = 2_560
+    wl = wl_of("f32", B, (16, 1), 8, 8, n_images=n_images, max_images=max(1, -(-nnz // B)), M=3)
+    pair = beside_the_oracle(wl)
+    rng = np.random.default_rng(nnz)
+    off = np.sort(rng.integers(0, nnz + 1, B - 1)) if nnz else np.zeros(B - 1, dtype=np.int64)
+    ids = rng.integers(0, wl.n_images, nnz)
+    ids[rng.random(nnz) < popular] = wl.n_images - 1
+    batch = PageViewBatch(user_id=rng.integers(0, wl.n_users, B).astype(np.int32), url_id=rng.integers(0, wl.n_urls, B).astype(np.int32),
+                          img_off=np.concatenate([[0], off, [nnz]]).astype(np.int32), img_id=ids.astype(np.int32),
+                          label=(rng.random(B) < 0.3).astype(np.float32))
+    for step in range(2):
+        assert in_blocks(pair, batch, f"{nnz} ids, {popular} popular, step {step}") == blocks
+    pair.check_state(f"{nnz} ids, {popular} popular")
+
+
+def test_ids_at_any_address():
+    """Ids are read sixteen bytes at a time where their list begins at such an address, one by one elsewhere."""
+    import paper_1806_03925_amd as g
+    from gear_inputs import PageViewSource
+    wl = wl_of("f32", 700, (16, 1), 8, 8)
+    results = []
+    for shift in (0, 1, 3):
+        st = g.GearState(g.config_for(wl))
+        g.gear_init_tables(st)
+        g.gear_fill_normal(st.dfv_cache, wl.n_images, wl.dfv_dim, wl.seed, 3, wl.dfv_std)
+        dev = g.DeviceBatch.from_host(PageViewSource(wl).batch(0))
+        for name in ("user_id", "url_id", "img_id"):
+            ids = getattr(dev, name)
+            moved = torch.empty(ids.numel() + shift, dtype=ids.dtype, device="cuda")[shift:]
+            moved.copy_(ids)
+            setattr(dev, name, moved)
+        g.gear_step(st, dev, wl.M, 0.1)
+        torch.cuda.synchronize()
+        assert int(st.status.item()) == 0
+        results.append([t.clone() for t in (st.loss, st.n_ready, st.grad_accum, st.counts, st.user_emb, st.url_emb, st.mlp_params)])
+    for other in results[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(results[0], other))
+
+
+@pytest.mark.parametrize("what", ["user", "image", "offset"])
+def test_a_bad_id_or_offset_leaves_everything_as_it_was(what):
+    """Whichever workgroup finds it, the others do not know: no table, counter or ready list may show a trace of the step."""
+    import paper_1806_03925_amd as g
+    from gear_inputs import PageViewSource
+    wl = wl_of("f32", 300, (16, 1), 8, 8, M=1)
+    st = g.GearState(g.config_for(wl))
+    g.gear_init_tables(st)
+    batch = PageViewSource(wl).batch(0)
+    if what == "user":
+        batch.user_id[17] = wl.n_users
+    elif what == "image":
+        batch.img_id[-1] = -1
+    else:
+        batch.img_off[100] = batch.img_off[102] + 1
+    before = [t.clone() for t in (st.user_emb, st.url_emb, st.mlp_params, st.grad_accum, st.counts)]
+    g.gear_step(st, g.DeviceBatch.from_host(batch), wl.M, 0.1)
+    torch.cuda.synchronize()
+    assert int(st.status.item()) == g.GEAR_ERR_RANGE and int(st.n_ready.item()) == 0
+    for a, b in zip(before, (st.user_emb, st.url_emb, st.mlp_params, st.grad_accum, st.counts)):
+        assert torch.equal(a, b)
