@@ -11,6 +11,7 @@
 // Work is cut into units of at most M rows (see the plan in group.hip), one workgroup per unit,
 // rows added in arrival order (flat CSR order continuing the earlier steps): no float atomics.
 #include "embedding_common.hpp"
+#include "tn_tile.hpp"
 
 namespace gear {
 namespace {
@@ -127,70 +128,23 @@ __device__ __forceinline__ void add_rows_at(float (&acc)[Cols<GT>::N], const Acc
   }
 }
 
-// What the launch's first workgroups do of the embedding update: nothing (a divided step has it done), its second level
-// (two streams: level 1 and the image counters are the launch before), or level 1 and the counters (one stream: level 2
-// rides with the parameter update).  Level 1 ahead of the units on two streams held their wavefronts down to three a SIMD
-// beside a product that needs the rest (16 384 views: 187 us a step against 180).
-enum EmbRide { kNoRide, kSpans, kChunks };
-struct RideWork {
-  EmbeddingWork w;
-  int blocks, count_blocks, lanes;   // workgroups per table and for the counters; lanes of a worker of level 1
-};
-struct NoWork {};
-
-// dx: the DFV slot of dLoss/dx, [B x D].  One workgroup per unit, D / Cols<GT>::N threads.
-// kChunks needs 132 registers where the units alone take 44: three wavefronts a SIMD, which still have 72 KB of rows in
-// flight on a CU, as much as a memory latency asks for.  kSpans has eight partials of a long run in flight: 59 (with 32
-// in flight 138).
-template <typename GT, int RIDE, bool AT>
-__global__ void __launch_bounds__(256, RIDE == kChunks ? 3 : 1)
-k_accumulate(AccumPlan plan, const GT *__restrict__ dx, int D, float *__restrict__ accum, int M,
-             int32_t *__restrict__ ready_ids, float *__restrict__ ready_grads, std::conditional_t<RIDE == kNoRide, NoWork, RideWork> emb,
-             const int32_t *__restrict__ status) {
-  if (*status != 0) return;
-  int block = blockIdx.x, blocks = gridDim.x;
-  if constexpr (RIDE == kSpans) {
-    if (block < 2 * emb.blocks) {
-      const int second = block >= emb.blocks ? 1 : 0;
-      const int chunk = (block - second * emb.blocks) * (blockDim.x / kWave) + threadIdx.x / kWave;
-      if (emb.w.bf16)
-        embedding_span<bf16_t, 8>(emb.w.table[second], chunk, emb.w.d, emb.w.opt);
-      else
-        embedding_span<float, 8>(emb.w.table[second], chunk, emb.w.d, emb.w.opt);
-      return;
-    }
-    block -= 2 * emb.blocks;
-    blocks -= 2 * emb.blocks;
-  }
-  if constexpr (RIDE == kChunks) {
-    if (block < 2 * emb.blocks) {
-      const int second = block >= emb.blocks ? 1 : 0;
-      const int tid = (block - second * emb.blocks) * blockDim.x + threadIdx.x;
-      if (emb.w.bf16)
-        embedding_chunk<bf16_t, 8>(emb.w.table[second], tid, emb.w.dx, 2 * emb.w.d, emb.w.d, emb.lanes, emb.w.opt);
-      else
-        embedding_chunk<float, 8>(emb.w.table[second], tid, emb.w.dx, 2 * emb.w.d, emb.w.d, emb.lanes, emb.w.opt);
-      return;
-    }
-    block -= 2 * emb.blocks;
-    if (block < emb.count_blocks)
-      return count_images(plan, emb.w.counts, block * blockDim.x + threadIdx.x, emb.count_blocks * blockDim.x);
-    block -= emb.count_blocks;
-    blocks -= 2 * emb.blocks + emb.count_blocks;
-  }
+// The units u, u + stride, ..., one after the other, by `threads` threads of which this is number t.
+template <typename GT, bool AT>
+__device__ __forceinline__ void accumulate_units(const AccumPlan &plan, const GT *__restrict__ dx, int D, float *__restrict__ accum,
+                                                 int M, int32_t *__restrict__ ready_ids, float *__restrict__ ready_grads, int u,
+                                                 int stride, int t, int threads) {
   constexpr int N = Cols<GT>::N;
   const int n_units = *plan.n_units;
   const int DC = D / N;
   const float fM = (float)M;
-  int u = block;
   if (u >= n_units) return;
   UnitDesc d = plan.units[u];
   while (true) {
-    const int u_next = u + blocks;
+    const int u_next = u + stride;
     UnitDesc d_next = d;
     if (u_next < n_units) d_next = plan.units[u_next];  // in flight while this unit is summed
     float *arow = accum + (size_t)d.image * D;
-    for (int cg = threadIdx.x; cg < DC; cg += blockDim.x) {
+    for (int cg = t; cg < DC; cg += threads) {
       const GT *col = dx + N * cg;
       auto add = [&](float (&to)[N], int qa, int qb) {
         if constexpr (AT)
@@ -240,6 +194,99 @@ k_accumulate(AccumPlan plan, const GT *__restrict__ dx, int D, float *__restrict
     u = u_next;
     d = d_next;
   }
+}
+
+// What the launch's first workgroups do of the embedding update: nothing (a divided step has it done), its second level
+// (two streams: level 1 and the image counters are the launch before), or level 1 and the counters (one stream: level 2
+// rides with the parameter update).  Level 1 ahead of the units on two streams held their wavefronts down to three a SIMD
+// beside a product that needs the rest (16 384 views: 187 us a step against 180).
+enum EmbRide { kNoRide, kSpans, kChunks };
+struct RideWork {
+  EmbeddingWork w;
+  int blocks, count_blocks, lanes;   // workgroups per table and for the counters; lanes of a worker of level 1
+};
+struct NoWork {};
+
+// level 1 and the counters, if workgroup `block` is one of theirs
+__device__ __forceinline__ bool chunks_ride(const AccumPlan &plan, const RideWork &emb, int block) {
+  if (block < 2 * emb.blocks) {
+    const int second = block >= emb.blocks ? 1 : 0;
+    const int tid = (block - second * emb.blocks) * blockDim.x + threadIdx.x;
+    if (emb.w.bf16)
+      embedding_chunk<bf16_t, 8>(emb.w.table[second], tid, emb.w.dx, 2 * emb.w.d, emb.w.d, emb.lanes, emb.w.opt);
+    else
+      embedding_chunk<float, 8>(emb.w.table[second], tid, emb.w.dx, 2 * emb.w.d, emb.w.d, emb.lanes, emb.w.opt);
+    return true;
+  }
+  block -= 2 * emb.blocks;
+  if (block >= emb.count_blocks) return false;
+  count_images(plan, emb.w.counts, block * blockDim.x + threadIdx.x, emb.count_blocks * blockDim.x);
+  return true;
+}
+
+// dx: the DFV slot of dLoss/dx, [B x D].  One workgroup per unit, D / Cols<GT>::N threads.
+// kChunks needs 132 registers where the units alone take 44: three wavefronts a SIMD, which still have 72 KB of rows in
+// flight on a CU, as much as a memory latency asks for.  kSpans has eight partials of a long run in flight: 59 (with 32
+// in flight 138).
+template <typename GT, int RIDE, bool AT>
+__global__ void __launch_bounds__(256, RIDE == kChunks ? 3 : 1)
+k_accumulate(AccumPlan plan, const GT *__restrict__ dx, int D, float *__restrict__ accum, int M,
+             int32_t *__restrict__ ready_ids, float *__restrict__ ready_grads, std::conditional_t<RIDE == kNoRide, NoWork, RideWork> emb,
+             const int32_t *__restrict__ status) {
+  if (*status != 0) return;
+  int block = blockIdx.x, blocks = gridDim.x;
+  if constexpr (RIDE == kSpans) {
+    if (block < 2 * emb.blocks) {
+      const int second = block >= emb.blocks ? 1 : 0;
+      const int chunk = (block - second * emb.blocks) * (blockDim.x / kWave) + threadIdx.x / kWave;
+      if (emb.w.bf16)
+        embedding_span<bf16_t, 8>(emb.w.table[second], chunk, emb.w.d, emb.w.opt);
+      else
+        embedding_span<float, 8>(emb.w.table[second], chunk, emb.w.d, emb.w.opt);
+      return;
+    }
+    block -= 2 * emb.blocks;
+    blocks -= 2 * emb.blocks;
+  }
+  if constexpr (RIDE == kChunks) {
+    if (chunks_ride(plan, emb, block)) return;
+    block -= 2 * emb.blocks + emb.count_blocks;
+    blocks -= 2 * emb.blocks + emb.count_blocks;
+  }
+  accumulate_units<GT, AT>(plan, dx, D, accum, M, ready_ids, ready_grads, block, blocks, threadIdx.x, blockDim.x);
+}
+
+// The same beside the weight-gradient products, for a step in blocks of views whose products all go on small tiles: neither
+// needs the other, and a launch less is 4 us of a step of 30 to 90 (512 views fp32 38 / 34 us a step,
+// 4096 85.5 / 80.5, 5000 of one image 67 / 63.5, 1000 bf16 50.7 / 44.3).  The products' workgroups come first, they take longest; with three stages instead of
+// four three workgroups fit on a CU, and the units, of which a workgroup then has several side by side, run between them.
+template <typename GT> struct BesideTile;
+template <> struct BesideTile<float> { using C = TnTile<float, 1, 1, 3>; };
+template <> struct BesideTile<bf16_t> { using C = TnTile<bf16_t, 2, 2, 3>; };
+struct BesideWork {
+  RideWork ride;
+  TnTileArgs tn;
+  int tn_blocks, K, splits;
+  int unit_threads;   // 64, 128 or 256
+};
+template <typename GT>
+__global__ void __launch_bounds__(256, 3)
+k_accumulate_wgrad(AccumPlan plan, const GT *__restrict__ dx, int D, float *__restrict__ accum, int M, int32_t *__restrict__ ready_ids,
+                   float *__restrict__ ready_grads, BesideWork w, const int32_t *__restrict__ status) {
+  using C = typename BesideTile<GT>::C;
+  static_assert(C::THREADS == 256, "one size of workgroup");
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[C::STAGES * C::STAGE_BYTES];
+  int block = blockIdx.x, blocks = gridDim.x;
+  if (block < w.tn_blocks) return tn_tile<C>(w.tn, w.K, w.splits, nullptr, xcd_remap(block, w.tn_blocks), lds);   // into the workspace only
+  if (*status != 0) return;
+  block -= w.tn_blocks;
+  blocks -= w.tn_blocks;
+  if (chunks_ride(plan, w.ride, block)) return;
+  block -= 2 * w.ride.blocks + w.ride.count_blocks;
+  blocks -= 2 * w.ride.blocks + w.ride.count_blocks;
+  const int side = 256 / w.unit_threads, which = __builtin_amdgcn_readfirstlane((int)threadIdx.x / w.unit_threads);
+  accumulate_units<GT, true>(plan, dx, D, accum, M, ready_ids, ready_grads, block * side + which, blocks * side,
+                             (int)threadIdx.x - which * w.unit_threads, w.unit_threads);
 }
 
 // dfv_cache[ids[r]] = rows[r]; one wavefront per row, 16-byte pieces
@@ -299,6 +346,37 @@ hipError_t launch_accumulate(const gear_config &cfg, const GroupProblem &img, co
   }
 #undef GEAR_ACC_T
 #undef GEAR_ACC
+  return hipGetLastError();
+}
+
+hipError_t launch_accumulate_wgrad(const gear_config &cfg, const GroupProblem &img, const AccumPlan &plan, const void *dx_dfv,
+                                   float *grad_accum, int32_t M, int32_t *ready_ids, float *ready_grads, const EmbeddingWork &emb,
+                                   const TnProblem *p, int count, int K, int splits, const int32_t *status, hipStream_t s) {
+  if (count < 1 || count > GEAR_MAX_LAYERS || splits < 1 || !plan.row_at) return hipErrorInvalidValue;
+  const int D = cfg.dfv_dim, threads = 256;
+  BesideWork w;
+  w.ride.w = emb;
+  w.ride.lanes = embedding_lanes(emb.d);
+  w.ride.blocks = (int)(((long long)embedding_chunks(emb) * w.ride.lanes + threads - 1) / threads);
+  w.ride.count_blocks = (img.n + 4 * threads - 1) / (4 * threads);
+  if (w.ride.count_blocks > 256) w.ride.count_blocks = 256;
+  w.K = K;
+  w.splits = splits;
+  const bool bf16 = cfg.mlp_dtype == GEAR_BF16;
+  const int edge = bf16 ? BesideTile<bf16_t>::C::BM : BesideTile<float>::C::BM;
+  w.tn_blocks = tn_tile_args(p, count, edge, &w.tn) * splits;
+  const int pieces = D / (bf16 ? 8 : 4);
+  w.unit_threads = pieces <= 64 ? 64 : pieces <= 128 ? 128 : 256;
+  const int side = threads / w.unit_threads;
+  int units = (img.n + side - 1) / side;
+  if (units > 32768) units = 32768;
+  const dim3 grid((unsigned)(w.tn_blocks + 2 * w.ride.blocks + w.ride.count_blocks + units));
+  if (bf16)
+    hipLaunchKernelGGL(k_accumulate_wgrad<bf16_t>, grid, dim3(threads), 0, s, plan, (const bf16_t *)dx_dfv, D, grad_accum, M, ready_ids,
+                       ready_grads, w, status);
+  else
+    hipLaunchKernelGGL(k_accumulate_wgrad<float>, grid, dim3(threads), 0, s, plan, (const float *)dx_dfv, D, grad_accum, M, ready_ids,
+                       ready_grads, w, status);
   return hipGetLastError();
 }
 

@@ -793,8 +793,13 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   // launched first and, where they can, as one launch of at most one round of workgroups, so that
   // they hold their CUs before the bookkeeping's many small workgroups arrive and fill what is
   // left; a product arriving later would wait until all of those have been placed.
+  // In blocks of views the two are one launch where the products go on small tiles in one group.
+  const TnChoice first_choice = gemm_tn_choice(dt, wp, n_wp, B);
+  size_t all_partials = 0;
+  for (int i = 0; i < n_wp; ++i) all_partials += (size_t)wp[i].M * wp[i].N;
+  const bool beside = by_rows && !first_choice.large && first_choice.layers == n_wp && all_partials * sizeof(float) <= lay.wgrad_partial_bytes;
   GEAR_HIP(lane.fork());
-  {
+  if (!beside) {
     hipStream_t s = helper;
     if (!divided && !one_stream) GEAR_RUN("embedding_update", launch_embedding_update(emb, false, failed, s));
     GEAR_RUN("accumulate", launch_accumulate(*cfg, gb.p[2], plan, dx_dfv, grad_accum, M, out->ready_ids, out->ready_grads,
@@ -816,6 +821,9 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
     }
     if (n == 0) return GEAR_ERR_CAPACITY;  // cannot happen: the region holds one range of the widest layer
     int splits = gemm_tn_splits(dt, wp + first, n, B, choice.large);
+    // Beside the accumulation two thirds as many: the CUs are not theirs alone, and every range is partials to write and to
+    // add (us a step, all / two thirds / half: 4096 views 82.2 / 80.4 / 80.4, 5000 64.3 / 63.5 / 65.4).
+    if (beside) splits = (2 * splits + 2) / 3;
     if (splits > (int)(room / all)) splits = (int)(room / all);
     float *next = wpart;
     SplitkProblem sp[GEAR_MAX_LAYERS];
@@ -826,7 +834,14 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
       next += (size_t)splits * q.M * q.N;
       sp[i] = SplitkProblem{q.partial, t->mlp_params + lay.w_off[l], moments_at(mom_mlp, lay.w_off[l]), (int64_t)q.M * q.N};
     }
-    GEAR_RUN("wgrad_gemm", launch_gemm_tn(dt, wp + first, n, B, splits, choice.large, nullptr, s));
+    if (beside) {
+      for (int piece = 0; piece < 2; ++piece)   // accumulation, embedding update
+        if (fail_injected()) return GEAR_ERR_HIP;
+      GEAR_RUN("accumulate_wgrad", launch_accumulate_wgrad(*cfg, gb.p[2], plan, dx_dfv, grad_accum, M, out->ready_ids, out->ready_grads,
+                                                           emb, wp, n, B, splits, failed, s));
+    } else {
+      GEAR_RUN("wgrad_gemm", launch_gemm_tn(dt, wp + first, n, B, splits, choice.large, nullptr, s));
+    }
     // The sums of the partials and the SGD change caller state, so the status word has to be final: the
     // stream waits for the helper's first part (long done by now), not for the bookkeeping.  Their
     // workgroups get onto the device as the bookkeeping's leave room and are done before it is, so the

@@ -439,6 +439,11 @@ hipError_t launch_accumulate(const gear_config &cfg, const GroupProblem &img, co
                              const void *dx_dfv, float *grad_accum, int32_t M, int32_t *ready_ids,
                              float *ready_grads, const EmbeddingWork *emb, bool level2, const int32_t *status, hipStream_t s);
 
+// with level 1 and the counters, beside `count` weight-gradient products on tiles of moderate size
+hipError_t launch_accumulate_wgrad(const gear_config &cfg, const GroupProblem &img, const AccumPlan &plan, const void *dx_dfv,
+                                   float *grad_accum, int32_t M, int32_t *ready_ids, float *ready_grads, const EmbeddingWork &emb,
+                                   const TnProblem *p, int count, int K, int splits, const int32_t *status, hipStream_t s);
+
 // n_dev (may be NULL): device word holding the real row count, at most n
 hipError_t launch_refresh(int dtype, void *dfv_cache, int64_t n_images, int dim, const int32_t *ids,
                           const void *rows, int64_t n, int32_t *status, hipStream_t s, const int32_t *n_dev = nullptr);
