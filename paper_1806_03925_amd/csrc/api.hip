@@ -179,6 +179,7 @@ bool make_layout(const gear_config &c, Layout *lay) {
     lay->g[s].total_words = (int32_t)room;
   }
   lay->pool_bytes = pool * sizeof(float);
+  lay->pool_rest = lay->tickets + (kTickets + kMaxProblems * room) * sizeof(float);
   lay->dx_emb = take(&cur, B * 2 * c.emb_dim * sizeof(float));
   lay->dx_dfv = take(&cur, B * c.dfv_dim * ab);
   max_partial = wgrad_region_bytes(c.mlp_dtype, lay->out_dim, lay->in_dim, L - 1, c.max_batch);
@@ -345,8 +346,9 @@ bool capturing(hipStream_t s) {
 // not run beside kernels this call left on the helper stream.
 class LaneScope {
  public:
-  LaneScope(SideLane *lane, bool helper, bool captured, hipStream_t caller)
-      : lane_(lane), side_(helper ? lane : nullptr), s_(caller), captured_(captured),
+  // books: what the step does to the store of gradients, it does on the helper stream
+  LaneScope(SideLane *lane, bool helper, bool books, bool captured, hipStream_t caller)
+      : lane_(lane), side_(helper ? lane : nullptr), s_(caller), captured_(captured), books_(helper && books),
         join_(!helper ? nullptr : captured ? lane->join_captured : lane->join) {
     if (lane_) lane_->busy.lock();
   }
@@ -356,7 +358,7 @@ class LaneScope {
       if (hipEventRecord(join_, side_->stream) == hipSuccess) (void)hipStreamWaitEvent(s_, join_, 0);
     }
     if (entered_ && !captured_) {
-      if (side_) {
+      if (books_) {
         if (forked_) lane_->last = &lane_->join;   // else it ended before it gave the helper anything
       } else if (hipEventRecord(lane_->done, s_) == hipSuccess) {
         lane_->last = &lane_->done;
@@ -374,7 +376,7 @@ class LaneScope {
   hipError_t enter() {
     if (!lane_) return hipSuccess;
     hipError_t e = hipSuccess;
-    if (!captured_ && lane_->last && !(side_ && lane_->last == &lane_->join)) e = hipStreamWaitEvent(s_, *lane_->last, 0);
+    if (!captured_ && lane_->last && !(books_ && lane_->last == &lane_->join)) e = hipStreamWaitEvent(s_, *lane_->last, 0);
     entered_ = e == hipSuccess;
     return e;
   }
@@ -403,7 +405,7 @@ class LaneScope {
  private:
   SideLane *lane_, *side_;   // side_: the lane if the helper stream is used
   hipStream_t s_;
-  const bool captured_;
+  const bool captured_, books_;
   const hipEvent_t join_;
   bool entered_ = false, forked_ = false, joined_ = false;
 };
@@ -590,10 +592,24 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   double macs = 0.0;
   for (int l = 0; l < L - 1; ++l) macs += (double)B * lay.in_dim[l] * lay.out_dim[l];
   const bool is_short = (long long)2 * B + b->nnz < kOneStreamIds && macs * (dt == GEAR_BF16 ? 1 : 4) < kOneStreamMacs;
-  // A short step in blocks of views: the whole network in one launch, with the grouping of the ids beside it (rows.hip).
+  // In blocks of views: the whole network in one launch (rows.hip), of a short step with the grouping of the ids in its first
+  // workgroups.  A longer one has the grouping on the other stream, and whichever is the longer chain stays on the caller's
+  // with the bookkeeping behind it, because a wait for the other stream is 10 us on the device: the grouping where there are
+  // many images (us a step, it here / on the helper: 106 000 ids 159.5 / 163, 172 000 181 / 189; 65 000 133 / 127).
   RowsPlan rows;
-  const bool by_rows = is_short && plan_rows(*cfg, lay, B, b->nnz, &rows);
-  const bool one_stream = out->one_stream != 0 || by_rows || (moderate && is_short);
+  const bool long_dx = (double)B * (F - 2 * cfg->emb_dim) * lay.out_dim[0] >= kSplitDxMacs;
+  TnProblem widths[GEAR_MAX_LAYERS];   // of the weight-gradient products
+  size_t all_partials = 0;
+  for (int l = L - 2; l >= 0; --l) {
+    widths[L - 2 - l] = TnProblem{nullptr, nullptr, nullptr, lay.out_dim[l], lay.in_dim[l]};
+    all_partials += (size_t)lay.out_dim[l] * lay.in_dim[l];
+  }
+  const TnChoice first_choice = gemm_tn_choice(dt, widths, L - 1, B);
+  const bool one_group = first_choice.layers == L - 1 && all_partials * sizeof(float) <= lay.wgrad_partial_bytes;
+  const bool by_rows = (is_short || (!long_dx && one_group)) && plan_rows(*cfg, lay, B, b->nnz, is_short, &rows);
+  const bool local_sort = by_rows && is_short;
+  const bool group_here = by_rows && b->nnz > kLongList;
+  const bool one_stream = out->one_stream != 0 || local_sort || (moderate && is_short);
   const bool carried = one_stream && moderate && !by_rows;
 
   // grouping of the three id lists and the plan of the per-image accumulation
@@ -622,7 +638,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   plan.row_view = (int32_t *)(ws + lay.row_view);
   plan.row_scale = (float *)(ws + lay.row_scale);
   plan.n_units = (int32_t *)(ws + lay.n_units);
-  plan.row_at = by_rows ? gb.p[2].perm : nullptr;
+  plan.row_at = local_sort ? gb.p[2].perm : nullptr;
   const PlanArgs plan_args = {plan, occ_view, b->img_off, counts, M, out->ready_cap, out->n_ready, out->status};
   // Not carried: what depends only on ids and counters (the check of the ids, the grouping, the accumulation plan) runs on
   // the helper stream while the main stream gathers and runs the forward pass.  The
@@ -635,7 +651,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   SideLane *side = needs_lane ? side_lane(!one_stream) : nullptr;
   if (needs_lane && !side) return GEAR_ERR_HIP;
   hipStream_t helper = one_stream ? s : side->stream;
-  LaneScope lane(side, !one_stream, captured, s);
+  LaneScope lane(side, !one_stream, !by_rows, captured, s);
   GEAR_HIP(lane.enter());
   {
     // Step outputs and counters cleared and the operand copies of the weights made in one launch ahead of everything:
@@ -646,13 +662,13 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
     for (int l = 0; l < n_jobs; ++l)
       jobs[l] = CastJob{t->mlp_params + lay.w_off[l], ws + lay.wc[l], ws + lay.wct[l], lay.out_dim[l], lay.in_dim[l]};
     ZeroList zero;
-    if (by_rows)
+    if (local_sort)
       local_zero_list(gb, &zero);
     else
       group_zero_list(gb, &zero);
     GEAR_RUN("begin", launch_begin(out->status, failed, out->n_ready, out->loss, zero, dt, jobs, n_jobs, by_rows, s));
   }
-  if (!carried && !by_rows) GEAR_HIP(lane.fork());
+  if (!carried && !local_sort) GEAR_HIP(lane.fork());
   // Carried: the links of the grouping in order, each taken by the next launch that can.
   SideTask task;
   int link = 0;
@@ -684,8 +700,13 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   if (by_rows) {
     for (int piece = 0; piece < kMaxProblems + 2 * L; ++piece)   // three lists, gather, every layer forward and back but the logit's
       if (fail_injected()) return GEAR_ERR_HIP;
-    const LocalTask local = local_task(rows, gb, plan_args, failed);
-    GEAR_RUN("view_blocks", launch_rows(*cfg, lay, rows, *b, *t, dfv_cache, ws, local, s));
+    LocalTask local = {};
+    if (local_sort) local = local_task(rows, gb, plan_args, failed);
+    hipStream_t caller = s;
+    {
+      hipStream_t s = group_here ? helper : caller;
+      GEAR_RUN("view_blocks", launch_rows(*cfg, lay, rows, *b, *t, dfv_cache, ws, local, s));
+    }
   } else {
     const CheckTask check = check_task(gb, b->img_off, occ_view, B, b->nnz, failed, out->status);
     if (carried && fail_injected()) return GEAR_ERR_HIP;
@@ -705,12 +726,12 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   // The helper stream's launches are issued after the forward pass's: where the host is not ahead of the
   // device (a caller that waits for every step), the gather then starts as soon as the step does, not
   // after the host has issued the grouping's launches.
-  if (!carried && !by_rows) {
-    hipStream_t s = helper;  // the launches of this block go to the helper stream
+  if (!carried && !local_sort) {
+    hipStream_t caller = s, s = group_here ? caller : helper;  // the stream of this block's launches
     GEAR_RUN("group_ids", launch_check(gb, b->img_off, occ_view, B, b->nnz, failed, out->status, s));
     for (int pass = 0; pass < group_passes(gb); ++pass) GEAR_RUN("group_ids", launch_radix_pass(gb, pass, failed, s));
-    GEAR_RUN("accum_plan", launch_segments(gb, &plan_args, failed, s));
-    GEAR_HIP(lane.mark_checked());
+    GEAR_RUN(by_rows && one_stream ? "group_ids" : "accum_plan", launch_segments(gb, &plan_args, failed, s));
+    if (!group_here) GEAR_HIP(by_rows ? lane.mark() : lane.mark_checked());
   }
 
   // Until its first kernel that changes caller state (the first SGD on a hidden layer's weights), the
@@ -763,7 +784,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
       // helper stream, beside the larger product that makes the DFV slot.  Every element is computed
       // the same way in both forms.
       const int E2 = 2 * cfg->emb_dim;
-      if ((double)B * (F - E2) * lay.out_dim[0] >= kSplitDxMacs) {
+      if (long_dx) {
         GEAR_RUN("dgrad_gemm_emb", launch_gemm_nt(dt, ws + lay.delta[0], ws + lay.wct[0], B, E2, lay.out_dim[0], EPI_DX,
                                                   nullptr, dx_dfv, dx_emb, E2, nullptr, nullptr, nullptr, s));
         if (gear_status st = links_left()) return st;
@@ -794,18 +815,21 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   // they hold their CUs before the bookkeeping's many small workgroups arrive and fill what is
   // left; a product arriving later would wait until all of those have been placed.
   // In blocks of views the two are one launch where the products go on small tiles in one group.
-  const TnChoice first_choice = gemm_tn_choice(dt, wp, n_wp, B);
-  size_t all_partials = 0;
-  for (int i = 0; i < n_wp; ++i) all_partials += (size_t)wp[i].M * wp[i].N;
-  const bool beside = by_rows && !first_choice.large && first_choice.layers == n_wp && all_partials * sizeof(float) <= lay.wgrad_partial_bytes;
-  GEAR_HIP(lane.fork());
-  if (!beside) {
-    hipStream_t s = helper;
-    if (!divided && !one_stream) GEAR_RUN("embedding_update", launch_embedding_update(emb, false, failed, s));
+  const bool beside = local_sort && !first_choice.large && one_group;
+  // Behind blocks of views the grouping may still be at work: the products fill that time, and the bookkeeping follows them
+  // on the caller's stream.
+  const bool books_here = one_stream || by_rows, books_last = by_rows && !local_sort;
+  if (!by_rows) GEAR_HIP(lane.fork());
+  auto bookkeeping = [&](hipStream_t s) -> gear_status {
+    if (!divided && !books_here) GEAR_RUN("embedding_update", launch_embedding_update(emb, false, failed, s));
     GEAR_RUN("accumulate", launch_accumulate(*cfg, gb.p[2], plan, dx_dfv, grad_accum, M, out->ready_ids, out->ready_grads,
-                                             divided ? nullptr : &emb, !one_stream, failed, s));
+                                             divided ? nullptr : &emb, !books_here, failed, s));
+    return GEAR_OK;
+  };
+  if (!beside && !books_last) {
+    if (gear_status st = bookkeeping(helper)) return st;
+    GEAR_HIP(lane.mark());
   }
-  GEAR_HIP(lane.mark());
   // SGD on the hidden layers' weights: split-K wgrad.  With the last of them go the small sums, unless they are done.
   // All layers go out as one launch, in as many ranges of the batch as their partials have room for; a model whose
   // partials do not fit at once (several wide layers and a short batch), or with more large tiles than fill the device,
@@ -840,19 +864,27 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
       GEAR_RUN("accumulate_wgrad", launch_accumulate_wgrad(*cfg, gb.p[2], plan, dx_dfv, grad_accum, M, out->ready_ids, out->ready_grads,
                                                            emb, wp, n, B, splits, failed, s));
     } else {
+      hipStream_t caller = s;
+      hipStream_t s = group_here ? helper : caller;
       GEAR_RUN("wgrad_gemm", launch_gemm_tn(dt, wp + first, n, B, splits, choice.large, nullptr, s));
     }
     // The sums of the partials and the SGD change caller state, so the status word has to be final: the
     // stream waits for the helper's first part (long done by now), not for the bookkeeping.  Their
     // workgroups get onto the device as the bookkeeping's leave room and are done before it is, so the
     // step ends with the bookkeeping and the join.
-    if (first == 0) GEAR_HIP(lane.wait_checked());
+    if (first == 0 && books_last) {
+      if (group_here) GEAR_HIP(lane.mark());
+      GEAR_HIP(lane.wait(true));
+      if (gear_status st = bookkeeping(s)) return st;
+    } else if (first == 0) {
+      GEAR_HIP(lane.wait_checked());
+    }
     first += n;
     const bool sums_too = first == n_wp && !divided;   // else the helper stream has done them
     GEAR_RUN("param_update", launch_param_update(sp, n, splits, columns, sums_too ? n_columns : 0, sums_too ? loss : LossSum{},
-                                                 sums_too && one_stream ? &emb : nullptr, by_rows ? out->n_ready : nullptr, opt, failed, s));
+                                                 sums_too && books_here ? &emb : nullptr, local_sort ? out->n_ready : nullptr, opt, failed, s));
   }
-  GEAR_HIP(lane.wait(true));  // the step ends on the caller's stream
+  if (!by_rows) GEAR_HIP(lane.wait(true));  // the step ends on the caller's stream
   if (out->dbg_img_unique && b->nnz > 0)
     GEAR_HIP(hipMemcpyAsync(out->dbg_img_unique, gb.p[2].unique, (size_t)b->nnz * 4, hipMemcpyDeviceToDevice, s));
   if (out->dbg_img_segoff)

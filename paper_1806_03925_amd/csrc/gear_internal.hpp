@@ -267,7 +267,7 @@ struct Layout {
     size_t keys[2], vals[2], totals, state, unique, segoff, n_unique;
     int32_t total_words;             // room for `totals`
   } g[kMaxProblems];
-  size_t pool_bytes;                  // of the region of sums that begins at loss_partial
+  size_t pool_bytes, pool_rest;       // the region of sums that begins at loss_partial; what follows its digit totals
   size_t tickets, seg_state, units, row_view, row_scale, n_units;
   size_t expiry_marks, expiry_tiles;  // gear_expired_ids: byte map over the images, marked bytes per tile
   size_t total;

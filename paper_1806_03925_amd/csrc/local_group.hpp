@@ -61,11 +61,13 @@ __device__ __forceinline__ void local_pass(const uint32_t *src, uint32_t *dst, u
   __syncthreads();
   int total = 0;
   if (tid < radix)
-    GEAR_ROLLED for (int w = 0; w < kLocalWaves; ++w) total += count[w * radix + tid];
+#pragma unroll
+    for (int w = 0; w < kLocalWaves; ++w) total += count[w * radix + tid];
   unsigned long long all;
   int base = (int)local_scan((unsigned long long)total, &all, smem);
   if (tid < radix)
-    GEAR_ROLLED for (int w = 0; w < kLocalWaves; ++w) {
+#pragma unroll
+    for (int w = 0; w < kLocalWaves; ++w) {
       const int c = count[w * radix + tid];
       count[w * radix + tid] = (uint16_t)base;   // at most 65 535 items
       base += c;
@@ -117,7 +119,7 @@ __device__ __forceinline__ void local_pass(const uint32_t *src, uint32_t *dst, u
 // Loads go out in batches whose addresses are clamped instead of branched around: the ids are cold.
 __device__ __forceinline__ int local_select(const LocalTask &t, const LocalList &p, int part, uint32_t *items,
                                             unsigned long long *smem, int *below) {
-  constexpr int U = 3;   // quadruples of ids in flight
+  constexpr int U = 5;   // quadruples of ids in flight
   const int tid = threadIdx.x, n = p.n, low_bits = p.bits - p.parts_log2;
   const int per = (n + 4 * kLocalThreads - 1) / (4 * kLocalThreads) * 4, p0 = min(n, tid * per), p1 = min(n, p0 + per);
   const int quads = ((uintptr_t)p.keys_in & 15u) == 0 ? n & ~3 : 0;   // positions that are read four at a time

@@ -1,8 +1,9 @@
 // A block of views taken through the whole Sparse Part in one launch (Section 3, steps 1-4): gather, forward pass, loss
 // and backward pass down to dLoss/dx.  All of it is local to a view except the weights, so a workgroup keeps the
-// activations of its 16 or 32 views in LDS from the gather to dLoss/dx and streams every layer's weights past them, once
+// activations of its 16 to 64 views in LDS from the gather to dLoss/dx and streams every layer's weights past them, once
 // forward and once backward; what the batch sums need (x, h, delta, dLoss/dx) is written to the workspace on the way.  Beside
-// the blocks the first workgroups sort the lists of ids (local_group.hpp).
+// the blocks of a short step the first workgroups sort the lists of ids (local_group.hpp); a longer one sorts them on the
+// other stream.
 //
 // Layer by layer a short step is a chain of eight to twelve dependent launches of 4 to 16 us, each of which pays its ramp,
 // the latency of its first operands and the links of the grouping it carries.  Here the chain is four launches (this one
@@ -230,15 +231,19 @@ __device__ __forceinline__ void rows_layer(const RowsArgs &p, unsigned char *lds
   const int tiles = (N + 15) / 16, least = tiles / kRowsWaves, more = tiles % kRowsWaves;
   const int share = (wave + blockIdx.x / kXcds) % kRowsWaves;
   int count = least + (share < more ? 1 : 0), tile = share * least + min(share, more);
-  constexpr int MOST = 3;   // column tiles at a time: registers
+  constexpr int MOST = MT == 4 ? (EPI == ROWS_FORWARD ? 4 : 5) : 3;   // column tiles at a time: registers
   while (count > 0) {
     const int parts = (count + MOST - 1) / MOST, n = (count + parts - 1) / parts;
     switch (n) {
 #define GEAR_TILES(NT)                                                                                          \
-  case NT: rows_tiles_of<T, MT, NT, EPI>(p, lds, in, out, w, N, K, bias, global, row0, tile, lane); break;
+  case NT:                                                                                                      \
+    if constexpr (NT <= MOST) rows_tiles_of<T, MT, NT, EPI>(p, lds, in, out, w, N, K, bias, global, row0, tile, lane); \
+    break;
       GEAR_TILES(1)
       GEAR_TILES(2)
       GEAR_TILES(3)
+      GEAR_TILES(4)
+      GEAR_TILES(5)
 #undef GEAR_TILES
     }
     tile += n;
@@ -350,12 +355,12 @@ __device__ __forceinline__ void gather_embeddings(const RowsArgs &p, unsigned ch
 
 template <typename T, int R>
 __device__ __forceinline__ void rows_gather(const RowsArgs &p, unsigned char *lds, int32_t *failed, int32_t *status, int row0, int wave, int lane) {
-  constexpr int PER = R / kRowsWaves, VIEWS = 2;
+  constexpr int PER = R / kRowsWaves, VIEWS = R == 64 ? 4 : 2;
   const int first = wave * PER;
   // bounds of the wavefront's lists, clamped like every id: the check of the ids may still be running (gather.hip)
   const int at = min(row0 + first + min(lane, PER), p.B);
   const int raw = p.img_off[at], off = min(max(raw, 0), p.nnz);
-  {   // the check of the offsets
+  if (failed) {   // the check of the offsets, unless it is made elsewhere
     const int next = __shfl_down(raw, 1, kWave), view = row0 + first + lane;
     if (lane < PER && view < p.B && (raw < 0 || raw > next || next > p.nnz || (view == 0 && raw != 0) || (view == p.B - 1 && next != p.nnz)))
       flag(failed, status, GEAR_ERR_RANGE);
@@ -375,7 +380,7 @@ __device__ __forceinline__ void rows_gather(const RowsArgs &p, unsigned char *ld
     }
 #pragma unroll
     for (int u = 0; u < VIEWS; ++u)
-      for (int j = lane; j < n[u]; j += kWave) {
+      for (int j = lane; failed && j < n[u]; j += kWave) {
         p.occ_view[lo[u] + j] = row0 + first + u0 + u;
         p.occ_scale[lo[u] + j] = 1.0f / (float)n[u];
       }
@@ -499,9 +504,11 @@ __device__ __forceinline__ void rows_columns(const RowsArgs &p, unsigned char *l
   }
 }
 
-// The first local.blocks workgroups group the ids.  Two workgroups share a CU (kHalf below), so they have half the registers.
+// The first local.blocks workgroups group the ids.  Two workgroups of up to 32 views share a CU (kHalf below), so they have half
+// the registers; those of 64 have the CU to themselves but for the sorts of a long step, which take 104 to 114 registers
+// beside 191 (group.hip).  In fp32 with 32 views, a form of long steps only, 96 leave room for them too (hotkey 175.5 us a step, with 108 180).
 template <typename T, int MT>
-__global__ void __launch_bounds__(kRowsThreads, 4) k_rows(RowsArgs p, LocalTask local) {
+__global__ void __launch_bounds__(kRowsThreads, MT == 4 ? 2 : MT == 2 && sizeof(T) == 4 ? 5 : 4) k_rows(RowsArgs p, LocalTask local) {
   constexpr int R = 16 * MT;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   if ((int)blockIdx.x < local.blocks) return local_group(local, blockIdx.x, lds);
@@ -585,7 +592,32 @@ long long place_buffers(const Layout &lay, int dtype, int rows, RowsArgs *a) {
 constexpr int kLocalPart = 1024;   // ids of a part, where they are spread evenly (2048: a step of 4096 views 1.5 us longer)
 constexpr int kStateSpan = 96;     // words of three per part, then a ticket
 
-// Which steps go in blocks, and how.  Lines by measurement (us a step; blocks of 16 or 32 views against layer by layer):
+// A step whose ids are sorted in launches of their own (api.hip).  bf16: one workgroup a CU, of 64 views from 12 289 on, where
+// 32 would be two rounds (us a step, blocks / layer by layer, 576 -> 512 -> 256, eight images a view: 9000 views 127 / 139,
+// 12 000 135 / 151, 16 384 159 / 171; three images 138 / 164; 64 views a block at 9000 130, 32 at 16 384 177).  More than
+// 20 480 are several rounds (192 -> 128, 40 000 views: 146 / 137).  fp32: its launches are bound by the matrix unit either way,
+// so what is gained is the launches of small products over many views, in one round of two workgroups a CU (16 384 views of
+// 320 -> 256 175.5 / 180; 12 000 of 96 -> 64 99 / 112; but 5000 of 320 -> 256 129 / 126, 10 000 of 448 -> 384 -> 384 329 / 292).
+bool plan_long(const Layout &lay, int dt, int B, double stream, RowsPlan *plan) {
+  if (dt == GEAR_BF16 ? B > 20480 : B < 12288 || B > 16384 || stream > 1e6) return false;
+  plan->rows = dt == GEAR_BF16 && B > 12288 ? 64 : 32;
+  RowsArgs a;
+  const long long lds = place_buffers(lay, dt, plan->rows, &a);
+  if (lds + 1024 > 160 * 1024) return false;
+  plan->lds = (int)lds;
+  plan->room = 0;
+  plan->blocks = (B + plan->rows - 1) / plan->rows;
+  if (2 * (size_t)plan->blocks * (lay.in_dim[lay.L - 1] + 1) * sizeof(float) > lay.tickets - lay.loss_partial) return false;
+  size_t sums = 0;   // where the layers leave theirs, or behind the digit totals of the sorts
+  for (int l = 1; l < lay.L - 1; ++l) {
+    plan->colsum_at[l] = sums;
+    sums += (size_t)plan->blocks * lay.in_dim[l];
+  }
+  plan->colsum = sums * sizeof(float) <= lay.emb_partial - lay.colsum_partial ? lay.colsum_partial : lay.pool_rest;
+  return plan->colsum == lay.colsum_partial || lay.pool_rest + sums * sizeof(float) <= lay.loss_partial + lay.pool_bytes;
+}
+
+// Which short steps go in blocks, and how.  Lines by measurement (us a step; blocks of 16 or 32 views against layer by layer):
 // - Rows of a block: fp32 16 (1000 views, 448 -> 512 -> 256: 99, of 32 152); bf16 16 up to 4096 views (4000: 80 / 85), where
 //   16 still find a CU for each, then 32, which read the weights half as often (6000: 96 / 89; 12000: 139 / 114).
 // - Every block streams all weights twice, at some 70 GB/s, while the launches of a layer share them: wide layers pay only
@@ -595,7 +627,7 @@ constexpr int kStateSpan = 96;     // words of three per part, then a ticket
 //   20 000 ids in one a CU: 134 against 102).
 // - A list of at most kLocalMost ids, in as many parts as an item's 32 bits ask for: a longer one whose ids are most of them
 //   one image keeps its part's workgroup too long (17 000 ids of Zipf 1.5: 83 / 82; 25 000: 109 / 88).
-bool plan_rows(const gear_config &cfg, const Layout &lay, int B, int nnz, RowsPlan *plan) {
+bool plan_rows(const gear_config &cfg, const Layout &lay, int B, int nnz, bool local, RowsPlan *plan) {
   const int dt = cfg.mlp_dtype, es = (int)dtype_bytes(dt);
   double stream = 0.0;
   for (int l = 0; l < lay.L - 1; ++l) {
@@ -603,6 +635,7 @@ bool plan_rows(const gear_config &cfg, const Layout &lay, int B, int nnz, RowsPl
     stream += 2.0 * es * lay.in_dim[l] * lay.out_dim[l];
   }
   if (lay.F > 4 * kRowsThreads) return false;
+  if (!local) return plan_long(lay, dt, B, stream, plan);
   if (stream > (lay.L - 1) * (1.5e6 + 500.0 * B)) return false;
   // the lists of ids
   const int64_t range[kMaxProblems] = {cfg.n_users, cfg.n_urls, cfg.n_images};
@@ -711,9 +744,11 @@ hipError_t launch_rows(const gear_config &cfg, const Layout &lay, const RowsPlan
   }
   const int rows = plan.rows;
   if (cfg.mlp_dtype == GEAR_BF16) {
+    if (rows == 64) return run_rows<bf16_t, 4>(a, local, plan, s);
     if (rows == 32) return run_rows<bf16_t, 2>(a, local, plan, s);
     if (rows == 16) return run_rows<bf16_t, 1>(a, local, plan, s);
   } else {
+    if (rows == 32) return run_rows<float, 2>(a, local, plan, s);
     if (rows == 16) return run_rows<float, 1>(a, local, plan, s);
   }
   return hipErrorInvalidValue;

@@ -45,7 +45,8 @@ struct RowsPlan {
   size_t colsum;                       // workspace offset of the column sums of the deltas below the last
   size_t colsum_at[GEAR_MAX_LAYERS];   // floats before those that layer l's product leaves
 };
-bool plan_rows(const gear_config &cfg, const Layout &lay, int B, int nnz, RowsPlan *plan);   // false: layer by layer
+// `local`: with the grouping (else the ids are sorted elsewhere).  false: layer by layer.
+bool plan_rows(const gear_config &cfg, const Layout &lay, int B, int nnz, bool local, RowsPlan *plan);
 LogitSums rows_sums(const RowsPlan &plan, const float *partials, int H);
 LocalTask local_task(const RowsPlan &plan, const GroupBatch &gb, const PlanArgs &args, int32_t *failed);
 void local_zero_list(const GroupBatch &gb, ZeroList *z);

@@ -68,6 +68,55 @@ def test_lists_at_the_edges_of_parts(n_images, nnz, popular, blocks):
     pair.check_state(f"{nnz} ids, {popular} popular")
 
 
+@pytest.mark.parametrize("dtype,batch,images", [
+    ("bf16", 12_288, 8), ("bf16", 12_289, 8), ("bf16", 16_384, 8),    # 32 views a block, 64
+    ("bf16", 12_289, 12), ("bf16", 16_384, 12),                       # the grouping on the caller's stream
+    ("f32", 12_287, 8), ("f32", 12_288, 12), ("f32", 16_385, 8),
+])
+def test_long_steps_in_blocks(dtype, batch, images):
+    """Two streams against one, bit for bit; then its first quarter as a step of its own, in smaller blocks or (too many ids)
+    layer by layer: the same logits,
+    and dLoss/dx four times as large, which is exact (a mean over a quarter of the views), as all bits of a view's own
+    results are the same whatever the block.  fp32 also beside the oracle.  (Its bound on what a hidden unit next to zero may
+    move does not hold for bf16 layers as narrow as these over so many views, in blocks or layer by layer.)"""
+    import paper_1806_03925_amd as g
+    from gear_inputs import PageViewSource
+    from gear_inputs.pageviews import PageViewBatch
+    wl = wl_of(dtype, batch, (72, 40, 1), 24, 72, max_images=images)
+    full = PageViewSource(wl).batch(0)
+    blocks = dtype == "bf16" or batch == 12_288
+    if dtype == "f32":
+        assert in_blocks(beside_the_oracle(wl), full, f"{dtype} {batch} {images}") == blocks
+
+    def run(batch, one):
+        st = g.GearState(g.config_for(wl))
+        g.gear_init_tables(st)
+        g.gear_fill_normal(st.dfv_cache, wl.n_images, wl.dfv_dim, wl.seed, 3, wl.dfv_std)
+        st.one_stream = one
+        st.profile = g.GearProfile()
+        g.gear_step(st, g.DeviceBatch.from_host(batch), wl.M, 0.1)
+        torch.cuda.synchronize()
+        assert int(st.status.item()) == 0
+        names = [name for name, _ in st.profile.spans()]
+        st.profile.close()
+        return st, names
+
+    (two, names), (one, _) = run(full, False), run(full, True)
+    assert ("view_blocks" in names) == blocks and "accum_plan" in names
+    n = int(two.n_ready.item())
+    for a, b in zip((two.loss, two.n_ready, two.ready_ids[:n], two.ready_grads[:n], two.grad_accum, two.counts, two.user_emb,
+                     two.url_emb, two.mlp_params),
+                    (one.loss, one.n_ready, one.ready_ids[:n], one.ready_grads[:n], one.grad_accum, one.counts, one.user_emb,
+                     one.url_emb, one.mlp_params)):
+        assert torch.equal(a, b)
+    if batch % 4 == 0:
+        B = batch // 4
+        part, _ = run(PageViewBatch(user_id=full.user_id[:B], url_id=full.url_id[:B], img_off=full.img_off[:B + 1],
+                                        img_id=full.img_id[:full.img_off[B]], label=full.label[:B]), False)
+        assert torch.equal(two.region("logits", batch)[:B], part.region("logits", B))
+        assert torch.equal(4.0 * two.region("dx", batch)[:B].float(), part.region("dx", B).float())
+
+
 def test_ids_at_any_address():
     """Ids are read sixteen bytes at a time where their list begins at such an address, one by one elsewhere."""
     import paper_1806_03925_amd as g
