@@ -448,14 +448,15 @@ __device__ __forceinline__ void rows_logit(const RowsArgs &p, unsigned char *lds
 
 // A thread owns four neighbouring columns and one of `split` parts of the block's rows; the parts are added in order.
 // LOGIT: the delta of the last hidden layer from its activation, sums of delta and of dz h.
-// Otherwise the delta is there and is summed.  Both leave the delta in the workspace.
+// Otherwise the delta is there and is summed.  Both leave the delta in the workspace.  Rows beyond the batch are left out: what
+// the network makes of no view at all may be infinite, and zero times that is not zero.
 template <typename T, int R, bool LOGIT>
 __device__ __forceinline__ void rows_columns(const RowsArgs &p, unsigned char *lds, const RowsBuf &b, int N, T *global, float *part_d,
                                              float *part_w, const float *s_w, const float *s_dz, float *scratch, int row0, int tid) {
   const int owners = N / 4;
   int split = 1;
   while (2 * split <= R && 2 * split * owners <= kRowsThreads) split *= 2;
-  const int part = split > 1 ? tid / owners : 0, rows = R / split, begin = part * rows;
+  const int part = split > 1 ? tid / owners : 0, rows = R / split, begin = part * rows, end = min(begin + rows, p.B - row0);
   for (int c = tid - part * owners; c < owners && part < split; c += kRowsThreads) {
     const int col = 4 * c;
     float gd[4] = {0.f, 0.f, 0.f, 0.f}, gw[4] = {0.f, 0.f, 0.f, 0.f}, w[4];
@@ -463,18 +464,18 @@ __device__ __forceinline__ void rows_columns(const RowsArgs &p, unsigned char *l
 #pragma unroll
       for (int e = 0; e < 4; ++e) w[e] = s_w[col + e];
     }
-    for (int row = begin; row < begin + rows; row += 4) {   // four rows in flight
+    for (int row = begin; row < end; row += 4) {   // four rows in flight
       unsigned char *at = lds + b.at + row * b.stride;
       float v[4][4], dz[4];
 #pragma unroll
       for (int k = 0; k < 4; ++k)
-        if (row + k < begin + rows) {
+        if (row + k < end) {
           lds_get4(at + k * b.stride, col, v[k], T{});
           if constexpr (LOGIT) dz[k] = s_dz[row + k];
         }
 #pragma unroll
       for (int k = 0; k < 4; ++k)
-        if (row + k < begin + rows) {
+        if (row + k < end) {
           if constexpr (LOGIT) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
@@ -486,7 +487,7 @@ __device__ __forceinline__ void rows_columns(const RowsArgs &p, unsigned char *l
           }
 #pragma unroll
           for (int e = 0; e < 4; ++e) gd[e] += v[k][e];
-          if (row0 + row + k < p.B) store4(global + (size_t)(row0 + row + k) * N + col, v[k]);
+          store4(global + (size_t)(row0 + row + k) * N + col, v[k]);
         }
     }
     store4(scratch + part * N + col, gd);

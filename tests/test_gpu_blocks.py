@@ -162,3 +162,30 @@ def test_a_bad_id_or_offset_leaves_everything_as_it_was(what):
     assert int(st.status.item()) == g.GEAR_ERR_RANGE and int(st.n_ready.item()) == 0
     for a, b in zip(before, (st.user_emb, st.url_emb, st.mlp_params, st.grad_accum, st.counts)):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_rows_beyond_the_batch_take_part_in_no_sum(dtype):
+    """A block's last rows have no view.  Here the network overflows on them (its first bias is large, and what cancels it is
+    in every view) and on no view.  The logit layer's gradient against fp64, within the rounding of fp32 sums of 17 terms."""
+    import paper_1806_03925_amd as g
+    from gear_inputs import PageViewSource
+    B = 17
+    wl = wl_of(dtype, B, (8, 8, 1), 8, 8)
+    st = g.GearState(g.config_for(wl))
+    g.gear_init_tables(st)
+    g.gear_fill_normal(st.dfv_cache, wl.n_images, wl.dfv_dim, wl.seed, 3, wl.dfv_std)
+    st.user_emb[:, 0] = 1.0
+    (w0, b0), (w1, _), (w2, _) = (st.layer_params(l) for l in range(3))
+    w0[0] = 0.0
+    w0[0, 0], b0[0] = -2.0 ** 83, 2.0 ** 83   # the unit is off in every view
+    w1[:, 0] = 2.0 ** 66
+    before = w2[0].clone()
+    batch = PageViewSource(wl).batch(0)
+    g.gear_step(st, g.DeviceBatch.from_host(batch), wl.M, 0.5)
+    torch.cuda.synchronize()
+    assert int(st.status.item()) == 0 and torch.isfinite(st.mlp_params).all()
+    h, z = st.region("h1", B).double().cpu(), st.region("logits", B).double().cpu()
+    assert (h > 0).any()
+    grad = ((torch.sigmoid(z) - torch.from_numpy(batch.label)) / B) @ h
+    assert ((before - w2[0]).double().cpu() - 0.5 * grad).abs().max() <= 1e-5 * float(grad.abs().max() + before.abs().max())
