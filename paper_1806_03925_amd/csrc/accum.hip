@@ -11,6 +11,7 @@
 // Work is cut into units of at most M rows (see the plan in group.hip), one workgroup per unit,
 // rows added in arrival order (flat CSR order continuing the earlier steps): no float atomics.
 #include "accum_device.hpp"
+#include "block_sums.hpp"
 
 namespace gear {
 namespace {
@@ -20,10 +21,10 @@ namespace {
 // flight on a CU, as much as a memory latency asks for.  kSpans has eight partials of a long run in flight: 59 (with 32
 // in flight 138).
 template <typename GT, int RIDE, bool AT>
-__global__ void __launch_bounds__(256, RIDE == kChunks ? 3 : 1)
+__global__ void __launch_bounds__(256, RIDE >= kChunks ? 3 : 1)
 k_accumulate(AccumPlan plan, const GT *__restrict__ dx, int D, float *__restrict__ accum, int M,
              int32_t *__restrict__ ready_ids, float *__restrict__ ready_grads, std::conditional_t<RIDE == kNoRide, NoWork, RideWork> emb,
-             const int32_t *__restrict__ status) {
+             std::conditional_t<RIDE == kChunksAndSums, BlockSums, NoWork> sums, const int32_t *__restrict__ status) {
   if (*status != 0) return;
   int block = blockIdx.x, blocks = gridDim.x;
   if constexpr (RIDE == kSpans) {
@@ -39,10 +40,15 @@ k_accumulate(AccumPlan plan, const GT *__restrict__ dx, int D, float *__restrict
     block -= 2 * emb.blocks;
     blocks -= 2 * emb.blocks;
   }
-  if constexpr (RIDE == kChunks) {
+  if constexpr (RIDE >= kChunks) {
     if (chunks_ride(plan, emb, block)) return;
     block -= 2 * emb.blocks + emb.count_blocks;
     blocks -= 2 * emb.blocks + emb.count_blocks;
+  }
+  if constexpr (RIDE == kChunksAndSums) {
+    if (block < emb.sum_blocks) return block_sums<GT>(sums, block * blockDim.x + threadIdx.x);
+    block -= emb.sum_blocks;
+    blocks -= emb.sum_blocks;
   }
   accumulate_units<GT, AT>(plan, dx, D, accum, M, ready_ids, ready_grads, block, blocks, threadIdx.x, blockDim.x);
 }
@@ -69,7 +75,8 @@ __global__ void __launch_bounds__(256) k_refresh(uint4 *__restrict__ cache, int6
 // emb (may be NULL): level 1 of its update and the counters, or level 2 if `level2`, ride along
 hipError_t launch_accumulate(const gear_config &cfg, const GroupProblem &img, const AccumPlan &plan,
                              const void *dx_dfv, float *grad_accum, int32_t M, int32_t *ready_ids,
-                             float *ready_grads, const EmbeddingWork *emb, bool level2, const int32_t *status, hipStream_t s) {
+                             float *ready_grads, const EmbeddingWork *emb, bool level2, const BlockSums *sums, const int32_t *status,
+                             hipStream_t s) {
   if (img.n <= 0 && !emb) return hipSuccess;
   const int D = cfg.dfv_dim;
   const int cols = cfg.mlp_dtype == GEAR_BF16 ? 8 : 4;
@@ -83,20 +90,24 @@ hipError_t launch_accumulate(const gear_config &cfg, const GroupProblem &img, co
     work.blocks = (int)(((long long)embedding_chunks(*emb) * work.lanes + threads - 1) / threads);
     work.count_blocks = level2 ? 0 : (img.n + 4 * threads - 1) / (4 * threads);
     if (work.count_blocks > 256) work.count_blocks = 256;
-    blocks += 2 * work.blocks + work.count_blocks;
+    work.sum_blocks = sums ? (int)((block_sums_threads(*sums) + threads - 1) / threads) : 0;
+    blocks += 2 * work.blocks + work.count_blocks + work.sum_blocks;
   }
-#define GEAR_ACC(T, R, AT, EMB)                                                                                            \
+  if (sums && (!emb || level2 || plan.row_at)) return hipErrorInvalidValue;
+#define GEAR_ACC(T, R, AT, EMB, SUMS)                                                                                            \
   hipLaunchKernelGGL((k_accumulate<T, R, AT>), dim3(blocks), dim3(threads), 0, s, plan, (const T *)dx_dfv, D, grad_accum, M, \
-                     ready_ids, ready_grads, EMB, status)
+                     ready_ids, ready_grads, EMB, SUMS, status)
 #define GEAR_ACC_T(T)              \
   if (!emb)                        \
-    GEAR_ACC(T, kNoRide, false, NoWork{}); \
+    GEAR_ACC(T, kNoRide, false, NoWork{}, NoWork{}); \
   else if (level2)                 \
-    GEAR_ACC(T, kSpans, false, work); \
+    GEAR_ACC(T, kSpans, false, work, NoWork{}); \
+  else if (sums)                   \
+    GEAR_ACC(T, kChunksAndSums, false, work, *sums); \
   else if (plan.row_at)            \
-    GEAR_ACC(T, kChunks, true, work); \
+    GEAR_ACC(T, kChunks, true, work, NoWork{}); \
   else                             \
-    GEAR_ACC(T, kChunks, false, work)
+    GEAR_ACC(T, kChunks, false, work, NoWork{})
   if (cfg.mlp_dtype == GEAR_BF16) {
     GEAR_ACC_T(bf16_t);
   } else {

@@ -191,10 +191,11 @@ __device__ __forceinline__ void accumulate_units(const AccumPlan &plan, const GT
 // (two streams: level 1 and the image counters are the launch before), or level 1 and the counters (one stream: level 2
 // rides with the parameter update).  Level 1 ahead of the units on two streams held their wavefronts down to three a SIMD
 // beside a product that needs the rest (16 384 views: 187 us a step against 180).
-enum EmbRide { kNoRide, kSpans, kChunks };
+enum EmbRide { kNoRide, kSpans, kChunks, kChunksAndSums };   // the last: and the batch sums of the network (block_sums.hpp)
 struct RideWork {
   EmbeddingWork w;
   int blocks, count_blocks, lanes;   // workgroups per table and for the counters; lanes of a worker of level 1
+  int sum_blocks;                    // workgroups of the batch sums
 };
 struct NoWork {};
 

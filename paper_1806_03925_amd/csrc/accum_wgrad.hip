@@ -52,6 +52,7 @@ hipError_t launch_accumulate_wgrad(const gear_config &cfg, const GroupProblem &i
   w.ride.blocks = (int)(((long long)embedding_chunks(emb) * w.ride.lanes + threads - 1) / threads);
   w.ride.count_blocks = (img.n + 4 * threads - 1) / (4 * threads);
   if (w.ride.count_blocks > 256) w.ride.count_blocks = 256;
+  w.ride.sum_blocks = 0;
   w.K = K;
   w.splits = splits;
   const bool bf16 = cfg.mlp_dtype == GEAR_BF16;

@@ -606,7 +606,12 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   }
   const TnChoice first_choice = gemm_tn_choice(dt, widths, L - 1, B);
   const bool one_group = first_choice.layers == L - 1 && all_partials * sizeof(float) <= lay.wgrad_partial_bytes;
-  const bool by_rows = (is_short || (!long_dx && one_group)) && plan_rows(*cfg, lay, B, b->nnz, is_short, &rows);
+  const bool planned = (is_short || (!long_dx && one_group)) && plan_rows(*cfg, lay, B, b->nnz, is_short, &rows);
+  // On one stream nothing runs beside the blocks of a longer step, while the launches of its layers carry the grouping: it goes
+  // layer by layer, with its batch sums in the shape the blocks would leave (block_sums.hpp), so that both forms have the same
+  // bits.  us a step on one stream, layers / blocks, 576 -> 512 -> 256 bf16: 9001 views 134 / 154, 12 288 148 / 165, 16 384 184 / 188;
+  // 192 -> 128, 10 000 views 97 / 110; 96 -> 64 fp32, 16 384 106 / 127.  The sums are 1 to 4 of it.
+  const bool by_rows = planned && (is_short || !out->one_stream), as_rows = planned && !by_rows;
   const bool local_sort = by_rows && is_short;
   const bool group_here = by_rows && b->nnz > kLongList;
   const bool one_stream = out->one_stream != 0 || local_sort || (moderate && is_short);
@@ -748,14 +753,14 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   // backward through the hidden layers down to dLoss/dx (all from the pre-step operand copies)
   // Each product that makes the delta of a hidden layer also leaves that layer's bias gradient (column
   // sums of the delta) as per-row-tile partials; they are added in tile order at the end of the step.
-  float *cpart = (float *)(ws + (by_rows ? rows.colsum : lay.colsum_partial)), *wpart = (float *)(ws + lay.wgrad_partial);
+  float *cpart = (float *)(ws + (planned ? rows.colsum : lay.colsum_partial)), *wpart = (float *)(ws + lay.wgrad_partial);
   const EmbeddingWork emb = embedding_work(*cfg, gb.p[0], gb.p[1], dx_emb, t->user_emb, t->url_emb, (float *)(ws + lay.emb_partial),
                                            opt, mom_user, mom_url, plan, counts);
   // Small sums whose results nothing in the step reads: the loss, the logit layer and the biases (column sums of deltas,
   // left as per-row-tile partials by the products that made them).
   ColumnSum columns[kMaxColumnSums];
   int n_columns = 0;
-  const LogitSums sums = by_rows ? rows_sums(rows, (const float *)(ws + lay.loss_partial), lay.in_dim[L - 1])
+  const LogitSums sums = planned ? rows_sums(rows, (const float *)(ws + lay.loss_partial), lay.in_dim[L - 1])
                                  : logit_sums((const float *)(ws + lay.loss_partial), B, lay.in_dim[L - 1]);
   auto column = [&](const float *partial, int parts, int width, int64_t at) {
     columns[n_columns++] = ColumnSum{partial, t->mlp_params + at, moments_at(mom_mlp, at), parts, width};
@@ -764,8 +769,8 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   column(sums.delta, sums.parts, lay.in_dim[L - 1], lay.b_off[L - 2]);
   column(sums.bias, sums.parts, 1, lay.b_off[L - 1]);
   for (int l = L - 2; l > 0; --l)
-    column(cpart + (by_rows ? rows.colsum_at[l] : lay.colsum_at[l]),
-           by_rows ? rows.blocks : gemm_nt_colsum_parts(dt, B, lay.in_dim[l], lay.out_dim[l], lay.colsum_coarse),
+    column(cpart + (planned ? rows.colsum_at[l] : lay.colsum_at[l]),
+           planned ? rows.blocks : gemm_nt_colsum_parts(dt, B, lay.in_dim[l], lay.out_dim[l], lay.colsum_coarse),
            lay.out_dim[l - 1], lay.b_off[l - 1]);
   const LossSum loss = {sums.loss, out->loss, sums.parts, B};
   bool divided = false;
@@ -775,7 +780,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
       GEAR_RUN(kDgrad[l], launch_gemm_nt(dt, ws + lay.delta[l], ws + lay.wct[l], B, lay.in_dim[l], lay.out_dim[l],
                                          by_bits ? EPI_MASK_BITS : EPI_MASK, nullptr,
                                          by_bits ? (const void *)relu_bits[l - 1] : (const void *)(ws + lay.h[l - 1]),
-                                         ws + lay.delta[l - 1], 0, cpart + lay.colsum_at[l], nullptr, nullptr, s,
+                                         ws + lay.delta[l - 1], 0, as_rows ? nullptr : cpart + lay.colsum_at[l], nullptr, nullptr, s,
                                          lay.colsum_coarse));
     } else {
       // dLoss/dx: the embedding slots stay fp32, the DFV slot is kept in the MLP's operand type.
@@ -822,8 +827,10 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   if (!by_rows) GEAR_HIP(lane.fork());
   auto bookkeeping = [&](hipStream_t s) -> gear_status {
     if (!divided && !books_here) GEAR_RUN("embedding_update", launch_embedding_update(emb, false, failed, s));
+    BlockSums riding;
+    if (as_rows) riding = block_sums_of(rows, lay, *b, ws);
     GEAR_RUN("accumulate", launch_accumulate(*cfg, gb.p[2], plan, dx_dfv, grad_accum, M, out->ready_ids, out->ready_grads,
-                                             divided ? nullptr : &emb, !books_here, failed, s));
+                                             divided ? nullptr : &emb, !books_here, as_rows ? &riding : nullptr, failed, s));
     return GEAR_OK;
   };
   if (!beside && !books_last) {

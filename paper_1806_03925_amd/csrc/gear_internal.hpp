@@ -435,9 +435,24 @@ EmbeddingWork embedding_work(const gear_config &cfg, const GroupProblem &users, 
 hipError_t launch_embedding_update(const EmbeddingWork &w, bool both_levels, const int32_t *status, hipStream_t s);
 size_t embedding_partial_floats(const gear_config &cfg);
 
+// batch sums of a step layer by layer, in the shape in which blocks of views leave them (block_sums.hpp)
+struct BlockSums {
+  struct Columns {
+    const void *delta;   // [B x width]
+    float *part;         // [blocks x width]
+    int width;
+  };
+  int B, rows, blocks, layers;             // rows of a block
+  const float *dz, *logits, *label;
+  const void *h;                           // activations of the last hidden layer, whose delta is layer[0]'s
+  float *part_w, *part_b, *part_loss;
+  Columns layer[GEAR_MAX_LAYERS - 1];
+};
+// `sums` (may be NULL; one stream only) ride along
 hipError_t launch_accumulate(const gear_config &cfg, const GroupProblem &img, const AccumPlan &plan,
                              const void *dx_dfv, float *grad_accum, int32_t M, int32_t *ready_ids,
-                             float *ready_grads, const EmbeddingWork *emb, bool level2, const int32_t *status, hipStream_t s);
+                             float *ready_grads, const EmbeddingWork *emb, bool level2, const BlockSums *sums, const int32_t *status,
+                             hipStream_t s);
 
 // with level 1 and the counters, beside `count` weight-gradient products on tiles of moderate size
 hipError_t launch_accumulate_wgrad(const gear_config &cfg, const GroupProblem &img, const AccumPlan &plan, const void *dx_dfv,

@@ -453,9 +453,7 @@ __device__ __forceinline__ void rows_logit(const RowsArgs &p, unsigned char *lds
 template <typename T, int R, bool LOGIT>
 __device__ __forceinline__ void rows_columns(const RowsArgs &p, unsigned char *lds, const RowsBuf &b, int N, T *global, float *part_d,
                                              float *part_w, const float *s_w, const float *s_dz, float *scratch, int row0, int tid) {
-  const int owners = N / 4;
-  int split = 1;
-  while (2 * split <= R && 2 * split * owners <= kRowsThreads) split *= 2;
+  const int owners = N / 4, split = rows_split(R, owners);
   const int part = split > 1 ? tid / owners : 0, rows = R / split, begin = part * rows, end = min(begin + rows, p.B - row0);
   for (int c = tid - part * owners; c < owners && part < split; c += kRowsThreads) {
     const int col = 4 * c;
@@ -680,6 +678,24 @@ bool plan_rows(const gear_config &cfg, const Layout &lay, int B, int nnz, bool l
 LogitSums rows_sums(const RowsPlan &plan, const float *partials, int H) {
   const float *d = partials + (size_t)plan.blocks * H, *b = d + (size_t)plan.blocks * H;
   return LogitSums{partials, d, b, b + plan.blocks, plan.blocks};
+}
+
+BlockSums block_sums_of(const RowsPlan &plan, const Layout &lay, const gear_batch &b, char *ws) {
+  const LogitSums sums = rows_sums(plan, (const float *)(ws + lay.loss_partial), lay.in_dim[lay.L - 1]);
+  BlockSums w;
+  memset(&w, 0, sizeof(w));
+  w.B = b.B;
+  w.rows = plan.rows;
+  w.blocks = plan.blocks;
+  w.layers = lay.L - 1;
+  w.dz = (const float *)(ws + lay.dz), w.logits = (const float *)(ws + lay.logits), w.label = b.label;
+  w.h = ws + lay.h[lay.L - 2];
+  w.part_w = const_cast<float *>(sums.w), w.part_b = const_cast<float *>(sums.bias), w.part_loss = const_cast<float *>(sums.loss);
+  for (int l = lay.L - 2; l >= 0; --l)
+    w.layer[lay.L - 2 - l] = BlockSums::Columns{ws + lay.delta[l], l == lay.L - 2 ? const_cast<float *>(sums.delta)
+                                                                                 : (float *)(ws + plan.colsum) + plan.colsum_at[l + 1],
+                                                lay.out_dim[l]};
+  return w;
 }
 
 LocalTask local_task(const RowsPlan &plan, const GroupBatch &gb, const PlanArgs &args, int32_t *failed) {

@@ -36,6 +36,13 @@ struct RowsArgs {
   RowsLayer layer[GEAR_MAX_LAYERS - 1];
 };
 
+// parts of a block's rows that a column is added in by as many threads (a power of two), for a quarter of the columns each
+__host__ __device__ inline int rows_split(int rows, int owners) {
+  int split = 1;
+  while (2 * split <= rows && 2 * split * owners <= kRowsThreads) split *= 2;
+  return split;
+}
+
 // How a step goes about it: decided by sizes alone.
 struct RowsPlan {
   int rows, blocks;                    // views of a block; blocks of the batch
@@ -48,6 +55,7 @@ struct RowsPlan {
 // `local`: with the grouping (else the ids are sorted elsewhere).  false: layer by layer.
 bool plan_rows(const gear_config &cfg, const Layout &lay, int B, int nnz, bool local, RowsPlan *plan);
 LogitSums rows_sums(const RowsPlan &plan, const float *partials, int H);
+BlockSums block_sums_of(const RowsPlan &plan, const Layout &lay, const gear_batch &b, char *ws);   // the same sums, from the launches of the layers
 LocalTask local_task(const RowsPlan &plan, const GroupBatch &gb, const PlanArgs &args, int32_t *failed);
 void local_zero_list(const GroupBatch &gb, ZeroList *z);
 hipError_t launch_rows(const gear_config &cfg, const Layout &lay, const RowsPlan &plan, const gear_batch &b, const gear_tables &t,

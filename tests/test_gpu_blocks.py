@@ -117,6 +117,38 @@ def test_long_steps_in_blocks(dtype, batch, images):
         assert torch.equal(4.0 * two.region("dx", batch)[:B].float(), part.region("dx", B).float())
 
 
+@pytest.mark.parametrize("dtype,batch,layers,D", [
+    ("bf16", 9_001, (512, 256, 1), 512), ("bf16", 12_289, (512, 256, 1), 512),   # 32 views a block, 64; the last one not full
+    ("bf16", 12_280, (72, 1), 40), ("bf16", 16_000, (264, 136, 40, 1), 104),
+    ("f32", 16_381, (72, 40, 1), 72),
+])
+def test_on_one_stream_a_long_step_goes_layer_by_layer_with_the_bits_of_blocks(dtype, batch, layers, D):
+    """There the launches of the layers carry the grouping.  All values of a view are the same in both forms; the sums over
+    views are added in the blocks' order in both."""
+    import paper_1806_03925_amd as g
+    from gear_inputs import PageViewSource
+    wl = wl_of(dtype, batch, layers, 32, D, max_images=8, M=4)
+    src = PageViewSource(wl)
+    results = []
+    for one in (False, True):
+        st = g.GearState(g.config_for(wl))
+        g.gear_init_tables(st)
+        g.gear_fill_normal(st.dfv_cache, wl.n_images, wl.dfv_dim, wl.seed, 3, wl.dfv_std)
+        st.one_stream = one
+        for step in range(2):
+            st.profile = g.GearProfile()
+            g.gear_step(st, g.DeviceBatch.from_host(src.batch(step)), wl.M, 0.1)
+            torch.cuda.synchronize()
+            names = [name for name, _ in st.profile.spans()]
+            st.profile.close()
+            assert int(st.status.item()) == 0 and ("view_blocks" in names) != one and ("accum_plan" in names) != one
+        n = int(st.n_ready.item())
+        results.append([t.clone() for t in (st.loss, st.n_ready, st.ready_ids[:n], st.ready_grads[:n], st.grad_accum, st.counts,
+                                            st.user_emb, st.url_emb, st.mlp_params)])
+    for a, b in zip(*results):
+        assert torch.equal(a, b)
+
+
 def test_ids_at_any_address():
     """Ids are read sixteen bytes at a time where their list begins at such an address, one by one elsewhere."""
     import paper_1806_03925_amd as g
