@@ -591,18 +591,39 @@ long long place_buffers(const Layout &lay, int dtype, int rows, RowsArgs *a) {
 constexpr int kLocalPart = 1024;   // ids of a part, where they are spread evenly (2048: a step of 4096 views 1.5 us longer)
 constexpr int kStateSpan = 96;     // words of three per part, then a ticket
 
-// A step whose ids are sorted in launches of their own (api.hip).  bf16: one workgroup a CU, of 64 views from 12 289 on, where
-// 32 would be two rounds (us a step, blocks / layer by layer, 576 -> 512 -> 256, eight images a view: 9000 views 127 / 139,
-// 12 000 135 / 151, 16 384 159 / 171; three images 138 / 164; 64 views a block at 9000 130, 32 at 16 384 177).  More than
-// 20 480 are several rounds (192 -> 128, 40 000 views: 146 / 137).  fp32: its launches are bound by the matrix unit either way,
-// so what is gained is the launches of small products over many views, in one round of two workgroups a CU (16 384 views of
-// 320 -> 256 175.5 / 180; 12 000 of 96 -> 64 99 / 112; but 5000 of 320 -> 256 129 / 126, 10 000 of 448 -> 384 -> 384 329 / 292).
-bool plan_long(const Layout &lay, int dt, int B, double stream, RowsPlan *plan) {
-  if (dt == GEAR_BF16 ? B > 20480 : B < 12288 || B > 16384 || stream > 1e6) return false;
-  plan->rows = dt == GEAR_BF16 && B > 12288 ? 64 : 32;
+// A step whose ids are sorted in launches of their own (api.hip), on two streams.  Lines by measurement (us a step; blocks of
+// views against layer by layer; three images a view unless it says otherwise):
+// - Rows of a block: fp32 32.  bf16 32 to 12 288 views, then 64, one workgroup a CU, where 32 read the weights twice as often
+//   (576 -> 512 -> 256, eight images a view: 64 views a block at 9000 130, 32 at 16 384 177).
+// - One round: a CU holds two blocks of 32 views whose activations leave room, else one, and one of 64 (1024 -> 256 bf16, 80 KB
+//   and so 8192 views, eight images: 6000 131 / 137, 10 000 178 / 169; 576 -> 512 -> 256: 14 000 134 / 150, 16 384 139 / 160,
+//   18 000 180 / 173; 448 -> 384 -> 384: 16 384 132 / 146, 18 000 167 / 156).  A second round of 64-view blocks pays for one narrow
+//   hidden layer (192 -> 128: 20 480 119 / 122, with eight images 125 / 135; 256 -> 128 -> 64 -> 32: 157 / 147; 320 -> 256, 76 KB:
+//   130 / 129; 768 -> 72 -> 40 -> 24 185 / 156), up to 20 480 (40 000: 146 / 137).
+// - bf16: every block streams all weights twice, so wide layers ask for views, as in a short step (832 -> 768 -> 384, 3.7 MB:
+//   2000 views 153 / 135, 4500 148 / 143, 6000 148.5 / 150.5, 8192 156 / 162; 1088 -> 1024, 4.5 MB: 4500 157 / 145; 576 -> 512 ->
+//   256, 1.7 MB: 500 146 / 147, 1000 116 / 127).
+// - A wavefront gathers four views, two at a time, where the gather's launch has one for each: with many images that chain is
+//   the step (192 -> 128: 98 images a view 109 / 136, 200 162 / 155, 600 371 / 220; 576 -> 512 -> 256: 80 135 / 131, 98 146 / 147,
+//   200 205 / 175).
+//   Cached rows of more than a kilobyte are two loads for a lane, one behind the other; eight wavefronts a CU then gather slower than
+//   the gather's launch, and several narrow layers do not make up for it (768 -> 72 -> 40 -> 24: 14 000 views of eight images
+//   164 / 159; 1088 -> 64: 168 / 178).
+// - fp32: products of the layers are bound by the matrix unit either way, so what is gained is their launches, where a full
+//   round takes as long for fewer views: small products from 12 288 views on (96 -> 64: 108 / 119, 16 384 114 / 120; 192 -> 128:
+//   124 / 123 and 129 / 131, with eight images 133 / 139 and 143 / 151), larger ones only next to the full round (320 -> 256:
+//   12 288 162 / 156, 14 000 165 / 163, with eight images 172 / 172 and 177 / 178, 16 384 185 / 188).
+bool plan_long(const Layout &lay, int dt, int B, int nnz, double stream, size_t row_bytes, RowsPlan *plan) {
+  const bool bf16 = dt == GEAR_BF16;
+  if (nnz > 96ll * B) return false;
+  if (bf16 ? stream > 1.5e6 + 420.0 * B : stream > 1e6 || B < (stream > 2e5 ? 14336 : 12288)) return false;
+  plan->rows = bf16 && B > 12288 ? 64 : 32;
   RowsArgs a;
   const long long lds = place_buffers(lay, dt, plan->rows, &a);
   if (lds + 1024 > 160 * 1024) return false;
+  const int round = 256 * plan->rows * (plan->rows == 32 && lds + 1024 <= 80 * 1024 ? 2 : 1);
+  if (plan->rows == 64 && lay.L > 2 && row_bytes > kWave * 16) return false;
+  if (B > round && !(bf16 && plan->rows == 64 && lay.L == 2 && lds <= 64 * 1024 && B <= 20480)) return false;
   plan->lds = (int)lds;
   plan->room = 0;
   plan->blocks = (B + plan->rows - 1) / plan->rows;
@@ -622,6 +643,9 @@ bool plan_long(const Layout &lay, int dt, int B, double stream, RowsPlan *plan) 
 // - Every block streams all weights twice, at some 70 GB/s, while the launches of a layer share them: wide layers pay only
 //   with enough views (bf16, blocks / layers: 1088 -> 1024 -> 512 120 / 104 at 1000 views, 131 / 126 at 3000, 140 / 148 at
 //   4000; 1088 -> 1024 96 / 86 at 1000, 112 / 125 at 4000; 832 -> 768 -> 384 89 / 86 at 500, 97 / 100 at 2000).
+// - Few views with very many images keep few CUs at the gather (16 views, 192 -> 128 bf16: 300 images each 106 / 116, 600 181 /
+//   175; 576 -> 512 -> 256 bf16, 64 views: 150 each 101 / 109, 300 150 / 149, 16 views of 1200 416 / 353; 320 -> 256 fp32, 16
+//   views: 300 102 / 103, 600 180 / 153).
 // - LDS of at most half a CU: the launch then has two workgroups on a CU, and the sorts keep nobody waiting (8000 views of
 //   20 000 ids in one a CU: 134 against 102).
 // - A list of at most kLocalMost ids, in as many parts as an item's 32 bits ask for: a longer one whose ids are most of them
@@ -634,8 +658,9 @@ bool plan_rows(const gear_config &cfg, const Layout &lay, int B, int nnz, bool l
     stream += 2.0 * es * lay.in_dim[l] * lay.out_dim[l];
   }
   if (lay.F > 4 * kRowsThreads) return false;
-  if (!local) return plan_long(lay, dt, B, stream, plan);
+  if (!local) return plan_long(lay, dt, B, nnz, stream, cfg.dfv_dim * dtype_bytes(cfg.dfv_dtype), plan);
   if (stream > (lay.L - 1) * (1.5e6 + 500.0 * B)) return false;
+  if (nnz > 256ll * B) return false;
   // the lists of ids
   const int64_t range[kMaxProblems] = {cfg.n_users, cfg.n_urls, cfg.n_images};
   int most = 0;

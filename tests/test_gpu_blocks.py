@@ -149,6 +149,48 @@ def test_on_one_stream_a_long_step_goes_layer_by_layer_with_the_bits_of_blocks(d
         assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("dtype,batch,each,layers,D,form", [
+    ("bf16", 16_384, 2, (40, 1), 40, "blocks"), ("bf16", 16_385, 2, (40, 1), 40, "blocks"),     # one narrow layer: two rounds
+    ("bf16", 16_384, 2, (72, 40, 1), 40, "blocks"), ("bf16", 16_385, 2, (72, 40, 1), 40, "layers"),
+    ("bf16", 8_192, 5, (256, 1), 960, "blocks"), ("bf16", 8_193, 5, (256, 1), 960, "layers"),   # one workgroup a CU
+    ("bf16", 13_000, 2, (72, 40, 1), 512, "blocks"), ("bf16", 13_000, 2, (72, 40, 1), 520, "layers"),   # a row in two loads
+    ("bf16", 600, 85, (40, 1), 40, "blocks"), ("bf16", 500, 97, (40, 1), 40, "layers"),         # images a view
+    ("bf16", 16, 256, (40, 1), 40, "blocks"), ("bf16", 16, 257, (40, 1), 40, "carried"),        # (ids sorted in LDS, or carried)
+    ("bf16", 2_000, 23, (768, 384, 1), 768, "layers"),                                          # wide layers, few views
+    ("f32", 12_288, 3, (256, 1), 256, "layers"), ("f32", 14_336, 3, (256, 1), 256, "blocks"),
+])
+def test_which_steps_go_in_blocks(dtype, batch, each, layers, D, form):
+    """On either side of each line, with the bits of the same step on one stream."""
+    import paper_1806_03925_amd as g
+    from gear_inputs.pageviews import PageViewBatch
+    wl = wl_of(dtype, batch, layers, 32, D, max_images=each, n_users=1 << 20, n_urls=1 << 12, n_images=2_000, M=4)
+    rng = np.random.default_rng(batch + each)
+    full = g.DeviceBatch.from_host(PageViewBatch(
+        user_id=rng.integers(0, wl.n_users, batch).astype(np.int32), url_id=rng.integers(0, wl.n_urls, batch).astype(np.int32),
+        img_off=(each * np.arange(batch + 1)).astype(np.int32), img_id=rng.integers(0, wl.n_images, batch * each).astype(np.int32),
+        label=(rng.random(batch) < 0.3).astype(np.float32)))
+    results = []
+    for one in (False, True):
+        st = g.GearState(g.config_for(wl))
+        g.gear_init_tables(st)
+        g.gear_fill_normal(st.dfv_cache, wl.n_images, wl.dfv_dim, wl.seed, 3, wl.dfv_std)
+        st.one_stream = one
+        st.profile = g.GearProfile()
+        g.gear_step(st, full, wl.M, 0.1)
+        torch.cuda.synchronize()
+        names = [name for name, _ in st.profile.spans()]
+        st.profile.close()
+        assert int(st.status.item()) == 0
+        if not one:
+            short = 2 * batch + batch * each < 49_152
+            assert ("view_blocks" in names) == (form == "blocks") and ("accum_plan" in names) == (not short)
+        n = int(st.n_ready.item())
+        results.append([t.clone() for t in (st.loss, st.n_ready, st.ready_ids[:n], st.ready_grads[:n], st.grad_accum, st.counts,
+                                            st.user_emb, st.url_emb, st.mlp_params)])
+    for a, b in zip(*results):
+        assert torch.equal(a, b)
+
+
 def test_ids_at_any_address():
     """Ids are read sixteen bytes at a time where their list begins at such an address, one by one elsewhere."""
     import paper_1806_03925_amd as g
