@@ -616,6 +616,9 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   const bool group_here = by_rows && b->nnz > kLongList;
   const bool one_stream = out->one_stream != 0 || local_sort || (moderate && is_short);
   const bool carried = one_stream && moderate && !by_rows;
+  // Blocks of 64 views leave a CU room for sorts by narrow digits only (102 registers against 170, 6 KB of LDS against 24 or 48):
+  // wide ones wait for the blocks to end (16 384 views of two images, 576 -> 512 -> 256 bf16: 159 us a step, narrow 139).
+  const bool beside_rows = by_rows && !local_sort && rows.rows == 64;
 
   // grouping of the three id lists and the plan of the per-image accumulation
   GroupBatch gb;
@@ -623,7 +626,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
     const int bits[kMaxProblems] = {bits_for(cfg->n_users), bits_for(cfg->n_urls), bits_for(cfg->n_images)};
     int passes = 1;   // the lists share launches: as many passes for all as the widest ids need
     for (int i = 0; i < kMaxProblems; ++i) {
-      const int need = radix_passes(bits[i], lay.g[i].total_words, carried ? kSideDigitBits : widest_digit(B > b->nnz ? B : b->nnz));
+      const int need = radix_passes(bits[i], lay.g[i].total_words, carried ? kSideDigitBits : beside_rows ? kBesideDigitBits : widest_digit(B > b->nnz ? B : b->nnz));
       if (need > passes) passes = need;
     }
     // a pass that is carried costs nothing but its length, and narrow digits make it short: as many as find a launch ahead

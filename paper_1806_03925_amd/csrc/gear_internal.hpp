@@ -119,6 +119,7 @@ constexpr int kMaxPasses = 4;
 constexpr int kMaxRides = 3;                          // passes that other launches are asked to carry, if it is up to us
 constexpr int kMaxDigitBits = 12;
 constexpr int kSideDigitBits = 11;                    // of passes that other launches carry
+constexpr int kBesideDigitBits = 9;                   // of passes beside workgroups that fill their CU
 constexpr int kLongList = 65536;                      // ids from which a workgroup of the check takes several tiles and the segments take few registers
 // Counts a tile publishes over all passes, at most.  A pass costs a launch and two memory latencies whatever its
 // radix, so a list takes as few passes as its keys allow within this (one up to 12 bits, two up to 22, then three);

@@ -160,7 +160,8 @@ def test_on_one_stream_a_long_step_goes_layer_by_layer_with_the_bits_of_blocks(d
     ("f32", 12_288, 3, (256, 1), 256, "layers"), ("f32", 14_336, 3, (256, 1), 256, "blocks"),
 ])
 def test_which_steps_go_in_blocks(dtype, batch, each, layers, D, form):
-    """On either side of each line, with the bits of the same step on one stream."""
+    """On either side of each line, with the bits of the same step on one stream.  Sorts beside blocks of 64 views take digits
+    of nine bits."""
     import paper_1806_03925_amd as g
     from gear_inputs.pageviews import PageViewBatch
     wl = wl_of(dtype, batch, layers, 32, D, max_images=each, n_users=1 << 20, n_urls=1 << 12, n_images=2_000, M=4)
@@ -184,6 +185,8 @@ def test_which_steps_go_in_blocks(dtype, batch, each, layers, D, form):
         if not one:
             short = 2 * batch + batch * each < 49_152
             assert ("view_blocks" in names) == (form == "blocks") and ("accum_plan" in names) == (not short)
+            if form == "blocks" and batch > 12_288 and dtype == "bf16":
+                assert names.count("group_ids") == 1 + 3   # the check; 20 bits of a user id
         n = int(st.n_ready.item())
         results.append([t.clone() for t in (st.loss, st.n_ready, st.ready_ids[:n], st.ready_grads[:n], st.grad_accum, st.counts,
                                             st.user_emb, st.url_emb, st.mlp_params)])
