@@ -227,7 +227,7 @@ struct SideTask {
 };
 struct NoTask {};
 // the grouping of short lists in LDS (local_group.hpp)
-constexpr int kLocalMost = 20480;                    // ids of a list (62 * 512 at most: a thread's positions are bits of a word)
+constexpr int kLocalMost = 19200;                    // ids of a list: a part, which may be all of it, fits in half a CU's LDS (rows.hip)
 struct LocalList {
   const int32_t *keys_in;
   int64_t range;

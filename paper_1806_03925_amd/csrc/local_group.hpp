@@ -8,8 +8,8 @@
 //
 // All loops are rolled: a workgroup runs this code once, and what bounded a form with its items in registers, forty times
 // unrolled, was the fetch of instructions (26 us for the two passes over a part of 157 ids, now 4).  The three lists of 4096
-// views (18 000 images) take 44 us beside the rows' 37, of which the longest part, that of the most popular image, needs 14
-// for reading the list, 18 for its passes and 10 for the plan.
+// views (18 400 images) take 38 us beside the rows' 37, of which the longest part, that of the most popular image (2906 ids,
+// 2450 of them that one), needs 8 for reading the list, 14 for sorting and 15 for the plan.
 #pragma once
 
 #include "group_device.hpp"
@@ -44,6 +44,8 @@ __device__ __forceinline__ unsigned long long local_scan(unsigned long long v, u
   return base + inc - v;
 }
 
+__device__ __forceinline__ int lower_lanes(unsigned long long mask, int lane) { return __popcll(mask & ((1ull << lane) - 1ull)); }
+
 // One stable LSD pass from src[0 .. m) to dst: a wavefront owns a contiguous share, counts its digits, and when it knows where
 // each of them begins, ranks and moves its share round by round (ballots, in lane order).
 __device__ __forceinline__ void local_pass(const uint32_t *src, uint32_t *dst, uint16_t *count /* [waves][radix] */, int m, int shift,
@@ -56,7 +58,11 @@ __device__ __forceinline__ void local_pass(const uint32_t *src, uint32_t *dst, u
   __syncthreads();
   GEAR_ROLLED for (int i = begin + lane; i < end; i += kWave) {
     const int digit = (int)(src[i] >> shift) & (radix - 1);
-    atomicAdd(&words[(wave * radix + digit) >> 1], 1u << (16 * (digit & 1)));
+    // lanes that share the first one's digit add as one: of a popular image all would, to one word, one after the other
+    const bool leads = digit == __builtin_amdgcn_readfirstlane(digit);
+    const unsigned long long same = __ballot(leads);
+    if (!leads || lower_lanes(same, lane) == 0)
+      atomicAdd(&words[(wave * radix + digit) >> 1], (leads ? (uint32_t)__popcll(same) : 1u) << (16 * (digit & 1)));
   }
   __syncthreads();
   int total = 0;
@@ -103,7 +109,7 @@ __device__ __forceinline__ void local_pass(const uint32_t *src, uint32_t *dst, u
 #pragma unroll
     for (int k = 0; k < U; ++k) {
       const unsigned long long peers = (unsigned long long)hi[k] << 32 | lo[k];
-      const int lower = __popcll(peers & ((1ull << lane) - 1ull));
+      const int lower = lower_lanes(peers, lane);
       const int at = mine[digit[k]];   // a wavefront's LDS accesses complete in order: all read, then the first of each digit adds
       __builtin_amdgcn_wave_barrier();
       if (valid[k] && lower == 0) mine[digit[k]] = (uint16_t)(at + __popcll(peers));
@@ -114,7 +120,76 @@ __device__ __forceinline__ void local_pass(const uint32_t *src, uint32_t *dst, u
   __syncthreads();
 }
 
-// The part's ids, in order: into items[0 .. m), or into p.spare if LDS has no room for them.  Returns m; *below = ids of the list in lower ranges.
+// A part most of which is one id (a popular image, a user that stands for all unknown ones): those are in order as they are.
+// Their positions go to their place in the list at once, the others are sorted by themselves behind the part's items and put
+// around them; items[0 .. m) is then in order, but for the positions of the popular id, and p.perm is written.  False: no such
+// id, or no room, and nothing has changed.  (us of the sort, 19 000 ids, in passes / like this: 45 % of them one image 19 / 10, 60 % 28 /
+// 11, all 42 / 14.)
+constexpr int kPopularLeast = 2048;   // items of a part (2048 of one image 39.4 us a step so, 41.6 in passes)
+__device__ __forceinline__ bool local_popular(const LocalList &p, uint32_t *items, uint16_t *count, int m, int below, int room,
+                                              unsigned long long *smem) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, vb = p.value_bits;
+  // the most frequent of up to six of 64 items, the same in every wavefront
+  const uint32_t sample = items[(int)((long long)lane * m / kWave)] >> vb;
+  unsigned long long left = ~0ull;
+  uint32_t id = 0u;
+  int votes = 0;
+  GEAR_ROLLED for (int k = 0; k < 6 && left; ++k) {
+    const uint32_t candidate = __shfl(sample, __builtin_ctzll(left), kWave);
+    const unsigned long long same = __ballot(sample == candidate);
+    if (__popcll(same) > votes) votes = __popcll(same), id = candidate;
+    left &= ~same;
+  }
+  if (votes < kWave / 2) return false;
+  const int share = (m + kLocalThreads - 1) / kLocalThreads * kWave, begin = min(m, wave * share), end = min(m, begin + share);
+  int lower = 0, equal = 0;   // of the wavefront's share
+  GEAR_ROLLED for (int i = begin; i < end; i += kWave) {
+    const uint32_t k = i + lane < end ? items[i + lane] >> vb : ~0u;
+    lower += __popcll(__ballot(k < id));
+    equal += __popcll(__ballot(k == id));
+  }
+  unsigned long long all;   // by all threads of a wavefront, of which the first one's counts
+  const unsigned long long before = local_scan(lane == 0 ? (unsigned long long)lower | (unsigned long long)equal << 32 : 0ull, &all, smem);
+  const int n_lower = (int)(uint32_t)all, n_equal = (int)(all >> 32), others = m - n_equal;
+  if (m + others > room) return false;
+  const int equal_before = (int)(__shfl(before, 0, kWave) >> 32);
+  uint32_t *apart = items + m + (begin - equal_before);
+  int32_t *place = p.perm + below + n_lower + equal_before;
+  const uint32_t mask = (1u << vb) - 1u;
+  GEAR_ROLLED for (int i = begin; i < end; i += kWave) {
+    const bool in = i + lane < end;
+    const uint32_t item = in ? items[i + lane] : 0u;
+    const bool is = in && item >> vb == id;
+    const unsigned long long same = __ballot(is), rest = __ballot(in && !is);
+    if (is) place[lower_lanes(same, lane)] = (int)(item & mask);
+    if (in && !is) apart[lower_lanes(rest, lane)] = item;
+    place += __popcll(same);
+    apart += __popcll(rest);
+  }
+  __syncthreads();
+  const int bits = p.bits - p.parts_log2, passes = (bits + kLocalDigitBits - 1) / kLocalDigitBits;
+  int a = m;   // others <= m: they have room below
+  GEAR_ROLLED for (int pass = 0; pass < passes; ++pass) {
+    const int from = pass * bits / passes, to = (pass + 1) * bits / passes;
+    local_pass(items + a, items + (m - a), count, others, vb + from, to - from, smem);
+    a = m - a;
+  }
+  if (a == 0) {
+    GEAR_ROLLED for (int q = tid; q < others; q += kLocalThreads) items[m + q] = items[q];
+    __syncthreads();
+  }
+  GEAR_ROLLED for (int q = tid; q < others; q += kLocalThreads) {
+    const uint32_t item = items[m + q];
+    const int at = q < n_lower ? q : q + n_equal;
+    items[at] = item;
+    p.perm[below + at] = (int)(item & mask);
+  }
+  GEAR_ROLLED for (int q = tid; q < n_equal; q += kLocalThreads) items[n_lower + q] = id << vb;
+  __syncthreads();
+  return true;
+}
+
+// The part's ids, in order, into items[0 .. m).  Returns m; *below = ids of the list in lower ranges.
 // A thread owns `per` consecutive positions, a multiple of four: it counts its own, and writes them when it knows where.
 // Loads go out in batches whose addresses are clamped instead of branched around: the ids are cold.
 __device__ __forceinline__ int local_select(const LocalTask &t, const LocalList &p, int part, uint32_t *items,
@@ -147,15 +222,9 @@ __device__ __forceinline__ int local_select(const LocalTask &t, const LocalList 
   int at = (int)(uint32_t)local_scan((unsigned long long)mine | (unsigned long long)lower << 32, &all, smem);
   const int m = (int)(uint32_t)all;
   *below = (int)(all >> 32);
-  const bool fits = m <= t.room;
-  uint32_t *outside = p.spare + *below;
   auto keep = [&](int32_t key, int q) {
     if ((int)((uint32_t)key >> low_bits) == part) {
-      const uint32_t item = ((uint32_t)key & ((1u << low_bits) - 1u)) << p.value_bits | (uint32_t)q;
-      if (fits)
-        items[at] = item;
-      else
-        outside[at] = item;
+      items[at] = ((uint32_t)key & ((1u << low_bits) - 1u)) << p.value_bits | (uint32_t)q;
       ++at;
     }
   };
@@ -179,7 +248,7 @@ __device__ __forceinline__ int local_select(const LocalTask &t, const LocalList 
 
 // Segments of the part's ids and the plan of the accumulation (group_device.hpp has the rules): a thread owns `per`
 // consecutive positions, at most 64.  cnt: room for the counters of the items' images.
-// FITS: all in LDS; else the counters are fetched once for every segment a thread sees, which then are few.
+// FITS: the counters too are in LDS.
 template <bool FITS>
 __device__ __forceinline__ void local_plan(const LocalTask &t, const LocalList &p, int part, const uint32_t *items, int32_t *cnt, int m,
                                            int below, unsigned long long *smem, int (*edge)[kLocalWaves], int *s_base) {
@@ -190,7 +259,7 @@ __device__ __forceinline__ void local_plan(const LocalTask &t, const LocalList &
   const int high = part << (p.bits - p.parts_log2), mine = min(max(m - p0, 0), per);
 #define GEAR_ID(q) (high | (int)(items[q] >> vb))
   if constexpr (FITS)
-#pragma clang loop unroll_count(2)
+#pragma clang loop unroll_count(8)
     for (int q = tid; q < m; q += kLocalThreads) cnt[q] = args.counts[min((int64_t)GEAR_ID(q), p.range - 1)];
   // heads, bit by bit; last head at or before and first head behind the thread's positions
   unsigned long long heads = 0;
@@ -220,18 +289,33 @@ __device__ __forceinline__ void local_plan(const LocalTask &t, const LocalList &
   }
   if (seg1 == INT32_MAX) seg1 = m;
   unsigned long long units = 0, emits = 0;
-  int seg = seg0, c = 0;
-  GEAR_ROLLED for (int i = 0; i < mine; ++i) {
-    const int q = p0 + i;
-    const bool head = (heads >> i) & 1ull;
-    if (head) seg = q;
-    if constexpr (FITS)
-      c = cnt[q];
-    else if (head || i == 0)
-      c = args.counts[min((int64_t)GEAR_ID(q), p.range - 1)];
-    const int ph = (c + (q - seg)) % M;
-    if (head || (ph == 0 && M <= m - q && items[q + M - 1] >> vb == items[q] >> vb)) units |= 1ull << i;
-    if (ph == M - 1) emits |= 1ull << i;
+  int seg = seg0;
+  // Counters that are not in LDS come four positions at a time, whether it is a head or not: one by one, at the heads, each was
+  // a memory latency (a part of 11 500 ids 25 us here, now 19).
+  constexpr int U = FITS ? 1 : 4;
+  auto counters = [&](int i, int (&c)[U]) {
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      const int q = min(p0 + min(i + k, mine - 1), m - 1);
+      if constexpr (FITS)
+        c[k] = cnt[q];
+      else
+        c[k] = args.counts[min((int64_t)GEAR_ID(q), p.range - 1)];
+    }
+  };
+  GEAR_ROLLED for (int i0 = 0; i0 < mine; i0 += U) {
+    int c[U];
+    counters(i0, c);
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      const int i = i0 + k, q = p0 + i;
+      if (i >= mine) break;
+      const bool head = (heads >> i) & 1ull;
+      if (head) seg = q;
+      const int ph = (c[k] + (q - seg)) % M;
+      if (head || (ph == 0 && M <= m - q && items[q + M - 1] >> vb == items[q] >> vb)) units |= 1ull << i;
+      if (ph == M - 1) emits |= 1ull << i;
+    }
   }
   // heads, units and emissions, 21 bits each
   unsigned long long all;
@@ -260,35 +344,37 @@ __device__ __forceinline__ void local_plan(const LocalTask &t, const LocalList &
   __syncthreads();
   int h = s_base[0] + (int)(before & kMask), u = s_base[1] + (int)((before >> 21) & kMask), e = s_base[2] + (int)(before >> 42);
   seg = seg0;
-  GEAR_ROLLED for (int i = 0; i < mine; ++i) {
-    const int q = p0 + i;
-    const bool head = (heads >> i) & 1ull;
-    if (head) seg = q;
-    if constexpr (FITS)
-      c = cnt[q];
-    else if (head || i == 0)
-      c = args.counts[min((int64_t)GEAR_ID(q), p.range - 1)];
-    if (head && t.unique) {
-      t.unique[h] = GEAR_ID(q);
-      t.segoff[h] = below + q;
+  GEAR_ROLLED for (int i0 = 0; i0 < mine; i0 += U) {
+    int c[U];
+    counters(i0, c);
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      const int i = i0 + k, q = p0 + i;
+      if (i >= mine) break;
+      const bool head = (heads >> i) & 1ull;
+      if (head) seg = q;
+      if (head && t.unique) {
+        t.unique[h] = GEAR_ID(q);
+        t.segoff[h] = below + q;
+      }
+      h += head ? 1 : 0;
+      if ((units >> i) & 1ull) {
+        const unsigned long long behind = i < 63 ? heads >> (i + 1) : 0ull;   // next head of this thread, or what follows it
+        const int end = behind ? q + 1 + __builtin_ctzll(behind) : seg1;
+        UnitDesc d;
+        d.q0 = below + q;
+        d.image = GEAR_ID(q);
+        d.slot = e;
+        d.s0 = below + seg;
+        d.s1 = below + end;
+        d.phase = c[k] % M;
+        d.collected = c[k] + (end - seg);
+        d.pad = 0;
+        plan.units[u] = d;
+        ++u;
+      }
+      e += (emits >> i) & 1ull ? 1 : 0;
     }
-    h += head ? 1 : 0;
-    if ((units >> i) & 1ull) {
-      const unsigned long long behind = i < 63 ? heads >> (i + 1) : 0ull;   // next head of this thread, or what follows it
-      const int end = behind ? q + 1 + __builtin_ctzll(behind) : seg1;
-      UnitDesc d;
-      d.q0 = below + q;
-      d.image = GEAR_ID(q);
-      d.slot = e;
-      d.s0 = below + seg;
-      d.s1 = below + end;
-      d.phase = c % M;
-      d.collected = c + (end - seg);
-      d.pad = 0;
-      plan.units[u] = d;
-      ++u;
-    }
-    e += (emits >> i) & 1ull ? 1 : 0;
   }
   if (part == (1 << p.parts_log2) - 1 && tid == 0) {
     const int n_heads = s_base[0] + (int)(all & kMask), n_emits = s_base[2] + (int)(all >> 42);
@@ -303,48 +389,42 @@ __device__ __forceinline__ void local_plan(const LocalTask &t, const LocalList &
 
 // the part's place in the sorted list, and what hangs on the images
 template <bool FITS>
-__device__ __forceinline__ void local_finish(const LocalTask &t, const LocalList &p, bool last, int part, const uint32_t *sorted,
+__device__ __forceinline__ void local_finish(const LocalTask &t, const LocalList &p, bool last, bool placed, int part, const uint32_t *sorted,
                                              uint32_t *spare, int m, int below, unsigned long long *smem,
                                              int (*edge)[kLocalWaves], int *s_base) {
   const int high = part << (p.bits - p.parts_log2);
   GEAR_ROLLED for (int q = threadIdx.x; q < m; q += kLocalThreads) {
     const uint32_t item = sorted[q];
     if (!last) p.sorted_keys[below + q] = high | (int)(item >> p.value_bits);   // the images' are in the plan
-    p.perm[below + q] = (int)(item & ((1u << p.value_bits) - 1u));
+    if (!placed) p.perm[below + q] = (int)(item & ((1u << p.value_bits) - 1u));
   }
   if (last) local_plan<FITS>(t, p, part, sorted, reinterpret_cast<int32_t *>(spare), m, below, smem, edge, s_base);
 }
 
-// Two sets of the part's items are in LDS, or one is and the other in the workspace, or both are there (a part is that long
-// only where one image is very popular).
-enum LocalPlace { kBothInside, kOneInside, kNoneInside };
-template <int PLACE>
-__device__ __forceinline__ void local_sorted(const LocalTask &t, const LocalList &p, bool last, int part, uint32_t *items, uint16_t *count,
+// Two sets of the part's items are in LDS (INSIDE), or one is and the other in the workspace: a part is that long only where
+// one image is very popular.
+template <bool INSIDE>
+__device__ __forceinline__ void local_sorted(const LocalTask &t, const LocalList &p, bool last, bool placed, int part, uint32_t *items, uint16_t *count,
                                              int m, int below, unsigned long long *smem, int (*edge)[kLocalWaves], int *s_base) {
-  const int bits = p.bits - p.parts_log2, passes = (bits + kLocalDigitBits - 1) / kLocalDigitBits;
-  uint32_t *spare = p.spare + below, *other = reinterpret_cast<uint32_t *>(p.sorted_keys) + below;
+  const int bits = p.bits - p.parts_log2, passes = placed ? 0 : (bits + kLocalDigitBits - 1) / kLocalDigitBits;
+  uint32_t *spare = p.spare + below;
   int a = 0;   // offsets and not pointers that change places: the compiler then knows what is LDS
   GEAR_ROLLED for (int pass = 0; pass < passes; ++pass) {
     const int from = pass * bits / passes, to = (pass + 1) * bits / passes, shift = p.value_bits + from;
-    if constexpr (PLACE == kBothInside) {
+    if constexpr (INSIDE) {
       local_pass(items + a, items + (m - a), count, m, shift, to - from, smem);
       a = m - a;
-    } else if constexpr (PLACE == kOneInside) {
-      local_pass(items, spare, count, m, shift, to - from, smem);
-#pragma clang loop unroll_count(4)
-      for (int q = threadIdx.x; q < m; q += kLocalThreads) items[q] = spare[q];
-      __syncthreads();
     } else {
-      local_pass(spare, other, count, m, shift, to - from, smem);
-#pragma clang loop unroll_count(4)
-      for (int q = threadIdx.x; q < m; q += kLocalThreads) spare[q] = other[q];
+      local_pass(items, spare, count, m, shift, to - from, smem);
+#pragma clang loop unroll_count(8)
+      for (int q = threadIdx.x; q < m; q += kLocalThreads) items[q] = spare[q];
       __syncthreads();
     }
   }
-  if constexpr (PLACE == kBothInside)
-    local_finish<true>(t, p, last, part, items + a, items + (m - a), m, below, smem, edge, s_base);
+  if constexpr (INSIDE)
+    local_finish<true>(t, p, last, placed, part, items + a, items + (m - a), m, below, smem, edge, s_base);
   else
-    local_finish<false>(t, p, last, part, PLACE == kOneInside ? items : spare, nullptr, m, below, smem, edge, s_base);
+    local_finish<false>(t, p, last, placed, part, items, nullptr, m, below, smem, edge, s_base);
 }
 
 // Workgroup `block` of t.blocks, with kLocalThreads threads.  lds: kLocalWaves * kLocalRadix counts and t.room items.
@@ -370,12 +450,11 @@ __device__ __forceinline__ void local_group(const LocalTask &t, int block, unsig
   uint16_t *count = reinterpret_cast<uint16_t *>(lds);
   int below;
   const int m = local_select(t, p, part, items, smem, &below);
+  const bool placed = m >= kPopularLeast && local_popular(p, items, count, m, below, t.room, smem);
   if (2 * m <= t.room)
-    local_sorted<kBothInside>(t, p, last, part, items, count, m, below, smem, edge, s_base);
-  else if (m <= t.room)
-    local_sorted<kOneInside>(t, p, last, part, items, count, m, below, smem, edge, s_base);
+    local_sorted<true>(t, p, last, placed, part, items, count, m, below, smem, edge, s_base);
   else
-    local_sorted<kNoneInside>(t, p, last, part, items, count, m, below, smem, edge, s_base);
+    local_sorted<false>(t, p, last, placed, part, items, count, m, below, smem, edge, s_base);
 }
 
 }  // namespace

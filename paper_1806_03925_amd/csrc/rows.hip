@@ -649,7 +649,8 @@ bool plan_long(const Layout &lay, int dt, int B, int nnz, double stream, size_t 
 // - LDS of at most half a CU: the launch then has two workgroups on a CU, and the sorts keep nobody waiting (8000 views of
 //   20 000 ids in one a CU: 134 against 102).
 // - A list of at most kLocalMost ids, in as many parts as an item's 32 bits ask for: a longer one whose ids are most of them
-//   one image keeps its part's workgroup too long (17 000 ids of Zipf 1.5: 83 / 82; 25 000: 109 / 88).
+//   one image would not fit in its part's LDS (19 000 ids, 96 -> 64 fp32: 30 % of them one image 57 / 74, 60 % 65 / 73, all 76 /
+//   71; 320 -> 256 fp32: 70 / 86, 75 / 86, 87 / 84; Zipf 1.5 80 / 103; 25 000 ids of Zipf 1.5 in an earlier form 109 / 88).
 bool plan_rows(const gear_config &cfg, const Layout &lay, int B, int nnz, bool local, RowsPlan *plan) {
   const int dt = cfg.mlp_dtype, es = (int)dtype_bytes(dt);
   double stream = 0.0;
@@ -682,6 +683,7 @@ bool plan_rows(const gear_config &cfg, const Layout &lay, int B, int nnz, bool l
   long long lds = place_buffers(lay, dt, plan->rows, &a);
   // room for two sets of the longest list's ids, as far as that leaves room for a second workgroup on the CU
   constexpr long long kHalf = 80 * 1024 - 1024;
+  static_assert((kHalf - kLocalWaves * kLocalRadix * 2) / 8 * 2 >= kLocalMost, "a part of any list fits");
   long long sorts = counts + 8 * (long long)most;
   if (sorts > kHalf) sorts = kHalf;
   if (lds < sorts) lds = sorts;

@@ -46,9 +46,10 @@ def test_blocks_at_the_edges_of_tiles(dtype, batch, layers, d, D):
     (2_000, 0, 0.0, True), (1, 1_024, 1.0, True),
     (2_000, 1_024, 0.0, True), (2_000, 1_025, 0.0, True),   # one part, two
     (3_000_000, 4_099, 0.1, True),                           # as many parts as 32 bits of an item ask for
-    (2_000, 20_480, 0.6, True),                              # a part that LDS holds once
-    (2_000, 20_480, 0.97, True),                             # and one that it does not hold
-    (2_000, 20_481, 0.1, False),                             # too long a list
+    (2_000, 19_200, 0.45, True),                             # a part that LDS holds twice
+    (2_000, 19_200, 0.6, True), (2_000, 19_200, 1.0, True),  # and once
+    (70_000, 19_199, 0.97, True),
+    (2_000, 19_201, 0.1, False),                             # too long a list
 ])
 def test_lists_at_the_edges_of_parts(n_images, nnz, popular, blocks):
     """`popular`: the share of the occurrences that are one image, the last of all."""
@@ -66,6 +67,37 @@ def test_lists_at_the_edges_of_parts(n_images, nnz, popular, blocks):
     for step in range(2):
         assert in_blocks(pair, batch, f"{nnz} ids, {popular} popular, step {step}") == blocks
     pair.check_state(f"{nnz} ids, {popular} popular")
+
+
+@pytest.mark.parametrize("n_images,nnz,shares", [
+    (2_000, 19_200, {1_000: 0.6}), (2_000, 19_200, {0: 0.7}),       # one pass over the others
+    (2_000, 9_000, {1_000: 0.6, 999: 0.2, 1_001: 0.2}),             # neighbours on both sides, in the same part
+    (2_000, 19_200, {1_000: 0.55, 1_001: 0.45}),                    # so many that there is no room apart
+    (2_000, 9_000, {1_000: 0.5, 1_001: 0.5}),                       # hardly popular
+    (1 << 16, 19_100, {40_000: 0.9}), (1 << 22, 19_100, {4_000_000: 0.9}),   # two passes, three
+    (2_000, 4_099, {7: 1.0}), (2_000, 2_048, {1_999: 1.0}), (2_000, 2_047, {1_999: 1.0}),   # the smallest part that is looked at
+])
+def test_lists_that_are_mostly_one_id(n_images, nnz, shares):
+    """Parts that set a popular id aside; the same for users, of whom one has most of the views."""
+    from gear_inputs.pageviews import PageViewBatch
+    B = 6_001
+    wl = wl_of("f32", B, (16, 1), 8, 8, n_images=n_images, n_users=5_000, max_images=4, M=7)
+    pair = beside_the_oracle(wl)
+    rng = np.random.default_rng(nnz)
+    for step in range(2):
+        off = np.sort(rng.integers(0, nnz + 1, B - 1))
+        ids = rng.integers(0, wl.n_images, nnz)
+        draw, low = rng.random(nnz), 0.0
+        for image, share in shares.items():
+            ids[(draw >= low) & (draw < low + share)] = image
+            low += share
+        users = rng.integers(0, wl.n_users, B)
+        users[rng.random(B) < 0.9] = 2_500 * step
+        batch = PageViewBatch(user_id=users.astype(np.int32), url_id=rng.integers(0, wl.n_urls, B).astype(np.int32),
+                              img_off=np.concatenate([[0], off, [nnz]]).astype(np.int32), img_id=ids.astype(np.int32),
+                              label=(rng.random(B) < 0.3).astype(np.float32))
+        assert in_blocks(pair, batch, f"{nnz} ids, {shares}, step {step}")
+    pair.check_state(f"{nnz} ids, {shares}")
 
 
 @pytest.mark.parametrize("dtype,batch,images", [
