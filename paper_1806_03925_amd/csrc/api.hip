@@ -373,10 +373,15 @@ class LaneScope {
   // 106.6 us on the three smallest workloads; left by the step's last kernel itself, hipExtLaunchKernel, it was 0.3 us where
   // the device is the slower side and 4 us where the host is.)
   // A step that is being captured has the place its graph is launched in; it leaves the events of the others alone.
-  hipError_t enter() {
+  // `on`: the stream that first looks at the store; what the step gives to its streams before this call, or to others than this
+  // one, runs beside the steps ahead of it (us for a step of each of two programs on streams of their own, with the whole step
+  // behind the other's / so: 16 384 views bf16 334 / 267, 192 -> 128 bf16 244 / 198, 320 -> 256 fp32 361 / 277; 32 768 views of
+  // 1152 -> 1024 -> 256 beside 16 384 of 576 -> 512 -> 256 642 / 602).
+  hipError_t enter(hipStream_t on) {
     if (!lane_) return hipSuccess;
     hipError_t e = hipSuccess;
-    if (!captured_ && lane_->last && !(books_ && lane_->last == &lane_->join)) e = hipStreamWaitEvent(s_, *lane_->last, 0);
+    const bool in_order = side_ && on == side_->stream && lane_->last == &lane_->join;
+    if (!captured_ && lane_->last && !in_order) e = hipStreamWaitEvent(on, *lane_->last, 0);
     entered_ = e == hipSuccess;
     return e;
   }
@@ -660,7 +665,10 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   if (needs_lane && !side) return GEAR_ERR_HIP;
   hipStream_t helper = one_stream ? s : side->stream;
   LaneScope lane(side, !one_stream, !by_rows, captured, s);
-  GEAR_HIP(lane.enter());
+  // Layer by layer on two streams the helper has all that looks at the store.  Blocks whose grouping is on the caller's stream
+  // take their place ahead of its last launch.  The others do at once: ahead of a launch in the middle of the helper's chain the
+  // wait costs a program that is alone 2 us a step.
+  if (!group_here) GEAR_HIP(lane.enter(by_rows ? s : helper));
   {
     // Step outputs and counters cleared and the operand copies of the weights made in one launch ahead of everything:
     // the first product then needs no event, and behind the gather's many workgroups the copies would not get onto the
@@ -738,6 +746,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
     hipStream_t caller = s, s = group_here ? caller : helper;  // the stream of this block's launches
     GEAR_RUN("group_ids", launch_check(gb, b->img_off, occ_view, B, b->nnz, failed, out->status, s));
     for (int pass = 0; pass < group_passes(gb); ++pass) GEAR_RUN("group_ids", launch_radix_pass(gb, pass, failed, s));
+    if (group_here) GEAR_HIP(lane.enter(s));
     GEAR_RUN(by_rows && one_stream ? "group_ids" : "accum_plan", launch_segments(gb, &plan_args, failed, s));
     if (!group_here) GEAR_HIP(by_rows ? lane.mark() : lane.mark_checked());
   }

@@ -96,10 +96,14 @@ def test_a_step_does_not_read_the_status_word_that_others_write(name, batch, cha
         assert torch.equal(a, b)
 
 
-SHORT, LONG = 2_000, 9_001       # views of the bf16 workload: 13 000 ids (one stream), 58 000 (the helper stream)
+# views of the bf16 workload: in blocks on one stream (13 000 ids), with the grouping on the helper stream (58 000) or on the
+# caller's beside blocks on the helper's (105 000), and layer by layer with everything about the store on the helper's
+SHORT, LONG, HERE, LAYERS = 2_000, 9_001, 16_200, 18_001
 
 
-@pytest.mark.parametrize("sizes", [(SHORT, SHORT), (SHORT, LONG), (LONG, SHORT), (SHORT, LONG, SHORT), (LONG, LONG)])
+@pytest.mark.parametrize("sizes", [(SHORT, SHORT), (SHORT, LONG), (LONG, SHORT), (SHORT, LONG, SHORT), (LONG, LONG),
+                                   (HERE, HERE), (SHORT, HERE), (HERE, SHORT), (LONG, HERE), (HERE, LONG), (LAYERS, LAYERS),
+                                   (SHORT, LAYERS), (LAYERS, SHORT), (HERE, LAYERS), (LAYERS, HERE), (LAYERS, HERE, LONG, LAYERS)])
 def test_steps_on_streams_of_their_own_share_a_store_in_the_order_they_were_issued(sizes):
     """Each step has tables, workspace and stream of its own and all collect gradients in one store.  The first stream is
     held up ahead of its step, so a step that does not wait for the one issued before it gets there first; which groups of
