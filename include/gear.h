@@ -326,9 +326,9 @@ int32_t gear_profile_count(const gear_profile *p);
 gear_status gear_profile_span(const gear_profile *p, int32_t i, const char **name, float *ms);
 
 /* Test hooks for the error paths of a step (no device needs to fail for them to be walked).
- * gear_debug_fail_launch(n): on the calling thread, the n-th kernel launch counted from now (n >= 1)
- * is not enqueued and the step returns GEAR_ERR_HIP there, leaving caller state half-updated as any
- * failed launch would; 0 switches it off.  gear_debug_helper_idle(): 1 if the current device's helper
+ * gear_debug_fail_launch(n): on the calling thread, the n-th launch of a step counted from now (n >= 1, as
+ * a profile counts them) is not enqueued and the step returns GEAR_ERR_HIP there, leaving caller state
+ * half-updated as any failed launch would; 0 switches it off.  gear_debug_helper_idle(): 1 if the current device's helper
  * stream has nothing left to run (or was never created), 0 if it is still busy, -1 on a HIP error. */
 void gear_debug_fail_launch(int32_t nth);
 int32_t gear_debug_helper_idle(void);

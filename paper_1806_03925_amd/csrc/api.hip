@@ -699,10 +699,6 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
       GEAR_RUN("group_ids", link + 1 < links ? launch_radix_pass(gb, link, failed, s) : launch_segments(gb, &plan_args, failed, s));
     return GEAR_OK;
   };
-#define GEAR_BOARD()                                       \
-  do {                                                     \
-    if (link < links && fail_injected()) return GEAR_ERR_HIP; \
-  } while (0)
   // forward
   void *x = ws + lay.x;
   // the weight-gradient products of the hidden layers
@@ -714,8 +710,6 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   float *dx_emb = (float *)(ws + lay.dx_emb);
   void *dx_dfv = ws + lay.dx_dfv;
   if (by_rows) {
-    for (int piece = 0; piece < kMaxProblems + 2 * L; ++piece)   // three lists, gather, every layer forward and back but the logit's
-      if (fail_injected()) return GEAR_ERR_HIP;
     LocalTask local = {};
     if (local_sort) local = local_task(rows, gb, plan_args, failed);
     hipStream_t caller = s;
@@ -725,7 +719,6 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
     }
   } else {
     const CheckTask check = check_task(gb, b->img_off, occ_view, B, b->nnz, failed, out->status);
-    if (carried && fail_injected()) return GEAR_ERR_HIP;
     GEAR_RUN("gather_pool", launch_gather_pool(*cfg, *b, *t, dfv_cache, x, s, carried ? &check : nullptr));
   }
   // A bf16 hidden layer below the last one also leaves the sign bitmap of its activations: the backward pass then
@@ -734,7 +727,6 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   if (dt == GEAR_BF16)
     for (int l = 0; l + 2 < L; ++l) relu_bits[l] = (uint8_t *)(ws + lay.relu_bits[l]);
   for (int l = 0; l < L - 1 && !by_rows; ++l) {
-    GEAR_BOARD();
     GEAR_RUN(kFwd[l], launch_gemm_nt(dt, l == 0 ? x : ws + lay.h[l - 1], ws + lay.wc[l], B, lay.out_dim[l],
                                      lay.in_dim[l], EPI_BIAS_RELU, t->mlp_params + lay.b_off[l], nullptr,
                                      ws + lay.h[l], 0, nullptr, relu_bits[l], nullptr, s, false, passenger()));
@@ -756,7 +748,6 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   // ready list fits.  Just before that kernel the stream waits for the helper's first part, so that the
   // status word is final.
   if (!by_rows) {
-    GEAR_BOARD();
     GEAR_RUN("logit_loss", launch_logit_loss(dt, ws + lay.h[L - 2], ws + lay.wc[L - 1], t->mlp_params + lay.b_off[L - 1],
                                            b->label, B, lay.in_dim[L - 1], logits, dz, ws + lay.delta[L - 2],
                                            (float *)(ws + lay.loss_partial), failed, s, passenger()));
@@ -817,7 +808,6 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
                                            lay.out_dim[0], EPI_DX, nullptr, dx_dfv, dx_emb, 0, nullptr, nullptr, nullptr, s));
       } else {
         const bool takes = gemm_nt_carries(dt, B, F, lay.out_dim[0]);
-        if (takes) GEAR_BOARD();
         GEAR_RUN(kDgrad[0], launch_gemm_nt(dt, ws + lay.delta[0], ws + lay.wct[0], B, F, lay.out_dim[0], EPI_DX,
                                            nullptr, dx_dfv, dx_emb, E2, nullptr, nullptr, nullptr, s, false,
                                            takes ? passenger() : nullptr));
@@ -878,8 +868,6 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
       sp[i] = SplitkProblem{q.partial, t->mlp_params + lay.w_off[l], moments_at(mom_mlp, lay.w_off[l]), (int64_t)q.M * q.N};
     }
     if (beside) {
-      for (int piece = 0; piece < 2; ++piece)   // accumulation, embedding update
-        if (fail_injected()) return GEAR_ERR_HIP;
       GEAR_RUN("accumulate_wgrad", launch_accumulate_wgrad(*cfg, gb.p[2], plan, dx_dfv, grad_accum, M, out->ready_ids, out->ready_grads,
                                                            emb, wp, n, B, splits, failed, s));
     } else {
