@@ -696,7 +696,8 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   };
   auto links_left = [&]() -> gear_status {   // those that found no launch to ride in
     for (; link < links; ++link)
-      GEAR_RUN("group_ids", link + 1 < links ? launch_radix_pass(gb, link, failed, s) : launch_segments(gb, &plan_args, failed, s));
+      GEAR_RUN(link + 1 < links ? "group_ids" : "accum_plan",
+               link + 1 < links ? launch_radix_pass(gb, link, failed, s) : launch_segments(gb, &plan_args, failed, s));
     return GEAR_OK;
   };
   // forward
@@ -739,7 +740,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
     GEAR_RUN("group_ids", launch_check(gb, b->img_off, occ_view, B, b->nnz, failed, out->status, s));
     for (int pass = 0; pass < group_passes(gb); ++pass) GEAR_RUN("group_ids", launch_radix_pass(gb, pass, failed, s));
     if (group_here) GEAR_HIP(lane.enter(s));
-    GEAR_RUN(by_rows && one_stream ? "group_ids" : "accum_plan", launch_segments(gb, &plan_args, failed, s));
+    GEAR_RUN("accum_plan", launch_segments(gb, &plan_args, failed, s));
     if (!group_here) GEAR_HIP(by_rows ? lane.mark() : lane.mark_checked());
   }
 

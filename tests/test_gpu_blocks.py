@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 import torch
 
+from step_forms import form_of_launches
 from test_gpu_tiles import beside_the_oracle
 
 pytestmark = pytest.mark.gpu
@@ -173,7 +174,7 @@ def test_on_one_stream_a_long_step_goes_layer_by_layer_with_the_bits_of_blocks(d
             torch.cuda.synchronize()
             names = [name for name, _ in st.profile.spans()]
             st.profile.close()
-            assert int(st.status.item()) == 0 and ("view_blocks" in names) != one and ("accum_plan" in names) != one
+            assert int(st.status.item()) == 0 and form_of_launches(names) == ("carried" if one else "long blocks")
         n = int(st.n_ready.item())
         results.append([t.clone() for t in (st.loss, st.n_ready, st.ready_ids[:n], st.ready_grads[:n], st.grad_accum, st.counts,
                                             st.user_emb, st.url_emb, st.mlp_params)])
@@ -182,14 +183,14 @@ def test_on_one_stream_a_long_step_goes_layer_by_layer_with_the_bits_of_blocks(d
 
 
 @pytest.mark.parametrize("dtype,batch,each,layers,D,form", [
-    ("bf16", 16_384, 2, (40, 1), 40, "blocks"), ("bf16", 16_385, 2, (40, 1), 40, "blocks"),     # one narrow layer: two rounds
-    ("bf16", 16_384, 2, (72, 40, 1), 40, "blocks"), ("bf16", 16_385, 2, (72, 40, 1), 40, "layers"),
-    ("bf16", 8_192, 5, (256, 1), 960, "blocks"), ("bf16", 8_193, 5, (256, 1), 960, "layers"),   # one workgroup a CU
-    ("bf16", 13_000, 2, (72, 40, 1), 512, "blocks"), ("bf16", 13_000, 2, (72, 40, 1), 520, "layers"),   # a row in two loads
-    ("bf16", 600, 85, (40, 1), 40, "blocks"), ("bf16", 500, 97, (40, 1), 40, "layers"),         # images a view
+    ("bf16", 16_384, 2, (40, 1), 40, "long blocks"), ("bf16", 16_385, 2, (40, 1), 40, "long blocks"),     # one narrow layer: two rounds
+    ("bf16", 16_384, 2, (72, 40, 1), 40, "long blocks"), ("bf16", 16_385, 2, (72, 40, 1), 40, "helper"),
+    ("bf16", 8_192, 5, (256, 1), 960, "long blocks"), ("bf16", 8_193, 5, (256, 1), 960, "helper"),   # one workgroup a CU
+    ("bf16", 13_000, 2, (72, 40, 1), 512, "long blocks"), ("bf16", 13_000, 2, (72, 40, 1), 520, "helper"),   # a row in two loads
+    ("bf16", 600, 85, (40, 1), 40, "long blocks"), ("bf16", 500, 97, (40, 1), 40, "helper"),         # images a view
     ("bf16", 16, 256, (40, 1), 40, "blocks"), ("bf16", 16, 257, (40, 1), 40, "carried"),        # (ids sorted in LDS, or carried)
-    ("bf16", 2_000, 23, (768, 384, 1), 768, "layers"),                                          # wide layers, few views
-    ("f32", 12_288, 3, (256, 1), 256, "layers"), ("f32", 14_336, 3, (256, 1), 256, "blocks"),
+    ("bf16", 2_000, 23, (768, 384, 1), 768, "helper"),                                          # wide layers, few views
+    ("f32", 12_288, 3, (256, 1), 256, "helper"), ("f32", 14_336, 3, (256, 1), 256, "long blocks"),
 ])
 def test_which_steps_go_in_blocks(dtype, batch, each, layers, D, form):
     """On either side of each line, with the bits of the same step on one stream.  Sorts beside blocks of 64 views take digits
@@ -215,9 +216,8 @@ def test_which_steps_go_in_blocks(dtype, batch, each, layers, D, form):
         st.profile.close()
         assert int(st.status.item()) == 0
         if not one:
-            short = 2 * batch + batch * each < 49_152
-            assert ("view_blocks" in names) == (form == "blocks") and ("accum_plan" in names) == (not short)
-            if form == "blocks" and batch > 12_288 and dtype == "bf16":
+            assert form_of_launches(names) == form
+            if form == "long blocks" and batch > 12_288 and dtype == "bf16":
                 assert names.count("group_ids") == 1 + 3   # the check; 20 bits of a user id
         n = int(st.n_ready.item())
         results.append([t.clone() for t in (st.loss, st.n_ready, st.ready_ids[:n], st.ready_grads[:n], st.grad_accum, st.counts,

@@ -18,6 +18,7 @@ from oracle.compare import REL, assert_delta_rows_close, assert_rows_close, row_
 from oracle.from_workload import oracle_for
 from oracle.gear_oracle import stable_groups
 from oracle.rounding import round_to
+from step_forms import form_of, launches_of
 
 pytestmark = pytest.mark.gpu
 
@@ -730,21 +731,10 @@ def test_same_step_twice_is_bit_identical():
         assert torch.equal(a, b)
 
 
-def form_of(st, dev, M, lr):
-    """How a step of this batch is run, read from its launches: the grouping "carried" by other launches on the caller's
-    stream, or on the "helper" stream, or there with dLoss/dx "divided" into two products.  Runs the step."""
-    st.profile = g.GearProfile()
-    g.gear_step(st, dev, M, lr)
-    torch.cuda.synchronize()
-    names = [name for name, _ in st.profile.spans()]
-    st.profile.close()
-    st.profile = None
-    return "carried" if "accum_plan" not in names else "divided" if "dgrad_gemm_emb" in names else "helper"
-
-
 @pytest.mark.parametrize("name,batch,form", [
-    ("bf16", 9_001, "helper"),      # a batch that is no multiple of 32 rows
-    ("bf16", 9_024, "helper"),
+    ("bf16", 9_001, "long blocks"),  # a batch that is no multiple of 32 rows
+    ("bf16", 9_024, "long blocks"),
+    ("bf16", 18_001, "helper"),
     ("large", 8192, "divided"),     # the embedding update beside the second product of dLoss/dx
 ])
 def test_one_stream_and_two_streams_give_the_same_bits(name, batch, form):
@@ -773,8 +763,9 @@ def test_one_stream_and_two_streams_give_the_same_bits(name, batch, form):
         assert torch.equal(a, b)
 
 
-@pytest.mark.parametrize("batches,forms", [((8_500, 9_001), ("helper", "helper")), ((1_200, 9_001), ("carried", "helper")),
-                                           ((1_200, 1_504), ("carried", "carried"))])
+@pytest.mark.parametrize("batches,forms", [((8_500, 9_001), ("helper", "long blocks")), ((1_200, 9_001), ("blocks", "long blocks")),
+                                           ((1_200, 1_504), ("blocks", "blocks")), ((4_600, 4_601), ("carried", "carried")),
+                                           ((4_600, 18_001), ("carried", "helper"))])
 def test_two_host_threads_stepping_their_own_states_on_one_device(batches, forms):
     """The entry points may be called from several host threads.  Two threads, each with its own state,
     workspace and stream, step at the same time; a long step forks to and joins from the device's one helper
@@ -875,15 +866,20 @@ def test_maximum_batch_and_nnz():
     pair.check_state("max sizes")
 
 
-# What a step that must change nothing goes through: where the violation is found (in a launch that carries the check or
-# the segments, or on the helper stream) and what has to hear of it before it changes anything (the accumulation and the
-# parameter update behind it on the same stream; on two streams the update on the caller's, which waits for the helper's
-# first part, and in a divided step the small sums and the embedding update as well).
+# What a step that must change nothing goes through: where the violation is found (in the launch that sorts the ids, in one that
+# carries the check or the segments, or on the helper stream) and what has to hear of it before it changes anything (the
+# accumulation and the parameter update behind it on the same stream; on two streams the update on the caller's, which waits for
+# the helper's first part, and in a divided step the small sums and the embedding update as well).
+WIDE = dict(dfv_dim=2_080)   # rows too wide for blocks of views
 ERROR_PATHS = {
-    "one hidden layer": ("tiny", {}, 512, "carried"),                           # segments with dLoss/dx
-    "two hidden layers": ("tiny", dict(layers=(64, 32, 1), mlp_dtype="bf16"), 512, "carried"),
-    "three hidden layers": ("tiny", dict(layers=(64, 32, 16, 1), mlp_dtype="bf16"), 512, "carried"),   # segments with the logit layer
-    "helper stream": ("bf16", dict(n_users=50_000, n_urls=1 << 15, n_images=4_000), 9_001, "helper"),
+    "one hidden layer": ("tiny", {}, 512, "blocks"),
+    "three hidden layers": ("tiny", dict(layers=(64, 32, 16, 1), mlp_dtype="bf16"), 512, "blocks"),
+    "one hidden layer, carried": ("tiny", WIDE, 512, "carried"),                # segments with dLoss/dx
+    "two hidden layers, carried": ("tiny", dict(layers=(64, 32, 1), mlp_dtype="bf16", **WIDE), 512, "carried"),
+    "three hidden layers, carried": ("tiny", dict(layers=(64, 32, 16, 1), mlp_dtype="bf16", **WIDE), 512, "carried"),   # with the logit layer
+    "long blocks": ("bf16", dict(n_users=50_000, n_urls=1 << 15, n_images=4_000), 9_001, "long blocks"),
+    "long blocks, grouping on the caller's stream": ("bf16", dict(n_users=50_000, n_urls=1 << 15, n_images=4_000), 16_200, "long blocks"),
+    "helper stream": ("bf16", dict(n_users=50_000, n_urls=1 << 15, n_images=4_000, layers=(72, 1), **WIDE), 9_001, "helper"),
     "divided": ("large", dict(n_users=50_000, n_urls=1 << 15, n_images=4_000), 8_192, "divided"),
 }
 
@@ -931,7 +927,7 @@ def test_ready_list_over_capacity_is_reported_and_changes_nothing(path):
         assert torch.equal(a, b)
 
 
-@pytest.mark.parametrize("name", ["tiny", "tiny, wide", "bf16", "large"])
+@pytest.mark.parametrize("name", ["tiny", "tiny, wide", "bf16", "bf16, wide", "large"])
 def test_a_step_that_fails_part_way_still_joins_the_helper_stream(name):
     """A launch that fails in the middle of a step's enqueue (forced from the host: the n-th launch is
     not enqueued and the call returns GEAR_ERR_HIP) must leave the caller's stream waiting for whatever
@@ -940,19 +936,15 @@ def test_a_step_that_fails_part_way_still_joins_the_helper_stream(name):
     on the caller's stream, four of blocks, or those of the layers where rows are too wide for that.)  The hook counts the
     launches that there are.  A fresh state then steps normally."""
     wl = get_workload(name.split(",")[0])
-    if "wide" in name:
-        wl = wl.scaled(dfv_dim=2_080)
-    elif name != "tiny":                               # helper stream; with dLoss/dx in two products in the larger one
+    if not name.startswith("tiny"):                    # helper stream; with dLoss/dx in two products in the larger one
         wl = wl.scaled(n_users=100_000, n_urls=1 << 16, n_images=5_000, batch=8192 if name == "large" else 9_001)
+    if "wide" in name:
+        wl = wl.scaled(layers=(72, 1), **WIDE)
     cfg, st, _ = make_pair(wl)
     dev = g.DeviceBatch.from_host(PageViewSource(wl).batch(0))
-    assert form_of(st, dev, wl.M, wl.lr) == {"tiny": "carried", "tiny, wide": "carried", "bf16": "helper", "large": "divided"}[name]
-    st.profile = g.GearProfile()
-    g.gear_step(st, dev, wl.M, wl.lr)
-    torch.cuda.synchronize()
-    launches = len(st.profile.spans())
-    st.profile.close()
-    st.profile = None
+    assert form_of(st, dev, wl.M, wl.lr) == {"tiny": "blocks", "tiny, wide": "carried", "bf16": "long blocks",
+                                             "bf16, wide": "helper", "large": "divided"}[name]
+    launches = len(launches_of(st, dev, wl.M, wl.lr))
     stream = torch.cuda.current_stream()
     n_fail = 0
     try:

@@ -4,6 +4,8 @@ import numpy as np
 import pytest
 import torch
 
+from step_forms import form_of_launches, launches_of
+
 pytestmark = pytest.mark.gpu
 
 
@@ -34,30 +36,33 @@ def test_groups_of_any_length_and_key_width(n, bits):
         assert np.array_equal(perm.cpu().numpy(), rp)
 
 
-@pytest.mark.parametrize("name,layers,batch", [
-    ("bf16", (512, 256, 1), 9_001), ("bf16", (72, 1), 9_001),            # two streams unless told otherwise; two, three passes
-    ("small", (64, 40, 24, 16, 1), 8_500), ("small", (256, 1), 8_500),   # more launches than links, and fewer
-    ("tiny", (64, 1), 1), ("tiny", (64, 1), 511),                        # one tile of each list; too short for the helper
+@pytest.mark.parametrize("name,layers,batch,changes,forms", [      # on one stream; on two, unless the step is short
+    ("bf16", (512, 256, 1), 9_001, {}, ("carried", "long blocks")), ("bf16", (72, 1), 9_001, {}, ("carried", "long blocks")),
+    ("bf16", (72, 40, 1), 9_001, dict(dfv_dim=2_080), ("carried", "helper")),   # two, three passes
+    ("bf16", (40, 1), 18_001, dict(dfv_dim=2_080), ("carried", "helper")),
+    ("small", (64, 40, 24, 16, 1), 8_500, {}, ("carried", "helper")), ("small", (256, 1), 8_500, {}, ("carried", "helper")),   # more launches than links, and fewer
+    ("tiny", (64, 1), 1, {}, ("blocks",)), ("tiny", (64, 1), 511, {}, ("blocks",)),     # one tile of each list; too short for the helper
+    ("tiny", (64, 1), 1, dict(dfv_dim=2_080), ("carried",)), ("tiny", (64, 1), 511, dict(dfv_dim=2_080), ("carried",)),
+    ("tiny", (64, 1), 511, dict(dfv_dim=2_080, mlp_dtype="bf16"), ("carried",)),
+    ("bf16", (512, 256, 1), 4_600, dict(max_images=10), ("carried",)),                  # short, but a list LDS does not hold
 ])
-def test_a_carried_grouping_gives_the_bits_of_one_on_the_helper_stream(name, layers, batch):
+def test_a_carried_grouping_gives_the_bits_of_one_on_the_helper_stream(name, layers, batch, changes, forms):
     """Both against numpy, and where the step is long enough to use the helper stream against each other."""
     import paper_1806_03925_amd as g
     from gear_inputs import PageViewSource, get_workload
-    wl = get_workload(name).scaled(n_users=100_000, n_urls=1 << 22, n_images=9_000, M=4, layers=layers)
+    wl = get_workload(name).scaled(n_users=100_000, n_urls=1 << 22, n_images=9_000, M=4, layers=layers, **changes)
     outs = []
-    for one in (True,) if name == "tiny" else (False, True):
+    for one, form in zip((True, False), forms):
         st = g.GearState(g.config_for(wl, max_batch=batch), debug=True)
         g.gear_init_tables(st)
         g.gear_fill_normal(st.dfv_cache, wl.n_images, wl.dfv_dim, wl.seed, 3, wl.dfv_std)
         st.one_stream = one
         src = PageViewSource(wl)
-        st.profile = g.GearProfile()
         for step in range(2):
             b = g.DeviceBatch.from_host(src.batch(step, batch=batch))
-            g.gear_step(st, b, wl.M, 0.1)
-        torch.cuda.synchronize()
-        assert ("accum_plan" not in [n for n, _ in st.profile.spans()]) == one     # a launch of its own on the helper stream
-        st.profile.close()
+            names = launches_of(st, b, wl.M, 0.1)
+            # the segments by their name where they are a launch of their own: always but in blocks, or where another carries them
+            assert form_of_launches(names) == form and ("accum_plan" in names or form in ("blocks", "carried"))
         assert int(st.status.item()) == 0
         n, m = int(st.n_ready.item()), int(st.dbg[3].item())
         outs.append([t.clone() for t in (st.loss, st.n_ready, st.ready_ids[:n], st.ready_grads[:n], st.grad_accum, st.counts,

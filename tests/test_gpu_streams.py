@@ -3,6 +3,8 @@ import numpy as np
 import pytest
 import torch
 
+from step_forms import form_of
+
 pytestmark = pytest.mark.gpu
 
 
@@ -16,22 +18,10 @@ def state_of(name, batch, **changes):
     return wl, st, PageViewSource(wl)
 
 
-def form_of(st, dev, M):
-    """How a step of this batch is run: the grouping carried by other launches on the caller's stream, or on the helper stream,
-    or there with dLoss/dx in two products."""
-    import paper_1806_03925_amd as g
-    st.profile = g.GearProfile()
-    g.gear_step(st, dev, M, 0.1)
-    torch.cuda.synchronize()
-    names = [name for name, _ in st.profile.spans()]
-    st.profile.close()
-    st.profile = None
-    return "carried" if "accum_plan" not in names else "divided" if "dgrad_gemm_emb" in names else "helper"
-
-
 @pytest.mark.parametrize("batch,changes,form", [
-    (16_383, dict(layers=(128, 1)), "carried"), (16_384, dict(layers=(128, 1)), "helper"),      # 49 152 ids
-    (15_963, {}, "carried"), (15_964, {}, "helper"),                                            # 6.8e9 multiply-adds
+    (16_383, dict(layers=(128, 1)), "blocks"), (16_384, dict(layers=(128, 1)), "long blocks"),                 # 49 152 ids
+    (16_383, dict(layers=(40, 1), dfv_dim=2_080), "carried"), (16_384, dict(layers=(40, 1), dfv_dim=2_080), "helper"),
+    (15_963, {}, "blocks"), (15_964, {}, "long blocks"),                                            # 6.8e9 multiply-adds
     (11_529, dict(layers=(1024, 1)), "divided"),
     (2_882, dict(layers=(1024, 1), mlp_dtype="f32"), "carried"), (2_883, dict(layers=(1024, 1), mlp_dtype="f32"), "helper"),
 ])
@@ -43,7 +33,7 @@ def test_steps_on_either_side_of_the_line_between_their_forms(batch, changes, fo
         wl, st, src = state_of("bf16", batch, max_images=1, **changes)
         st.one_stream = one
         dev = g.DeviceBatch.from_host(src.batch(0, batch=batch))
-        assert form_of(st, dev, wl.M) == ("carried" if one else form)
+        assert form_of(st, dev, wl.M, 0.1) == (form if not one or form == "blocks" else "carried")
         g.gear_step(st, dev, wl.M, 0.1)
         torch.cuda.synchronize()
         assert int(st.status.item()) == 0
@@ -58,13 +48,16 @@ def outputs(st):
                                 st.user_emb, st.url_emb, st.mlp_params)]
 
 
-@pytest.mark.parametrize("name,batch,changes", [
-    ("tiny", 511, {}),                         # one tile of each list, carried by other launches
-    ("small", 4_096, {}),                      # carried, several tiles that look back
-    ("bf16", 9_001, {}),                       # grouping on the helper stream
-    ("large", 8_192, {"max_images": 40}),      # helper stream, long lists, dLoss/dx in two products
+@pytest.mark.parametrize("name,batch,changes,form", [
+    ("tiny", 511, {}, "blocks"), ("small", 4_096, {}, "blocks"),
+    ("tiny", 511, {"dfv_dim": 2_080}, "carried"),                # one tile of each list
+    ("small", 4_096, {"max_images": 12}, "carried"), ("bf16", 4_600, {"max_images": 10}, "carried"),   # several that look back
+    ("bf16", 9_001, {}, "long blocks"),                          # grouping on the helper stream
+    ("bf16", 16_200, {}, "long blocks"),                         # on the caller's, beside blocks
+    ("bf16", 18_001, {}, "helper"),
+    ("large", 8_192, {"max_images": 40}, "divided"),             # helper stream, long lists, dLoss/dx in two products
 ])
-def test_a_step_does_not_read_the_status_word_that_others_write(name, batch, changes):
+def test_a_step_does_not_read_the_status_word_that_others_write(name, batch, changes, form):
     """Two calls on another stream report bad ids into the step's status word and clear it again, over and over, while the
     steps run.  Workgroups that wait for one another must not decide by that word whether to work: every step has to end
     with the bits it gets when it runs alone."""
@@ -81,6 +74,7 @@ def test_a_step_does_not_read_the_status_word_that_others_write(name, batch, cha
         good = torch.zeros(1, dtype=torch.int32, device="cuda")
         beside = torch.cuda.Stream()
         torch.cuda.synchronize()
+        assert form_of(st, dev[0], wl.M, 0.1) == form
         for t in range(4):
             print(f"{name} disturbed {disturbed} step {t}", flush=True)
             if disturbed:
@@ -99,6 +93,7 @@ def test_a_step_does_not_read_the_status_word_that_others_write(name, batch, cha
 # views of the bf16 workload: in blocks on one stream (13 000 ids), with the grouping on the helper stream (58 000) or on the
 # caller's beside blocks on the helper's (105 000), and layer by layer with everything about the store on the helper's
 SHORT, LONG, HERE, LAYERS = 2_000, 9_001, 16_200, 18_001
+FORMS = {SHORT: "blocks", LONG: "long blocks", HERE: "long blocks", LAYERS: "helper"}
 
 
 @pytest.mark.parametrize("sizes", [(SHORT, SHORT), (SHORT, LONG), (LONG, SHORT), (SHORT, LONG, SHORT), (LONG, LONG),
@@ -120,6 +115,7 @@ def test_steps_on_streams_of_their_own_share_a_store_in_the_order_they_were_issu
                for t in range(2)]
         streams = [torch.cuda.Stream() if apart else torch.cuda.current_stream() for _ in sizes]
         torch.cuda.synchronize()
+        assert [form_of(st, d, wl.M, 0.1) for (wl, st, _), d in zip(states, dev[0])] == [FORMS[n] for n in sizes]
         lists = []
         for t in range(2):
             print(f"sizes {sizes} apart {apart} round {t}", flush=True)
