@@ -31,6 +31,7 @@ def in_blocks(pair, batch, what):
     ("f32", 1, (8, 1), 8, 8), ("f32", 15, (24, 1), 8, 24), ("f32", 17, (72, 40, 1), 24, 72), ("f32", 33, (392, 1), 8, 136),
     ("bf16", 1, (8, 1), 8, 8), ("bf16", 31, (24, 1), 16, 40), ("bf16", 65, (72, 136, 8, 1), 24, 72), ("bf16", 129, (520, 1), 8, 104),
     ("bf16", 4_096, (40, 24, 1), 8, 40), ("bf16", 4_097, (40, 24, 1), 8, 40),   # 16 views a block, 32
+    ("bf16", 4_203, (512, 256, 1), 32, 512),                                    # 32, several column tiles to a wavefront
     ("f32", 300, (64,) * 7 + (1,), 8, 64),
 ])
 def test_blocks_at_the_edges_of_tiles(dtype, batch, layers, d, D):
