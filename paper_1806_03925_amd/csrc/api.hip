@@ -283,13 +283,18 @@ std::mutex g_side_mutex;
 constexpr double kSplitDxMacs = 5e9;
 
 // Ids of a batch (users, URLs and images) from which a step uses the helper stream.  Its events cost the host 65 us a step
-// and the device four idle gaps; a shorter step has less than that to hide.  On one stream, the grouping carried by other
-// launches, against two streams: 2 300 ids 53 / 99 us, 15 000 82 / 119, 27 000 106 / 128, 63 000 154 / 178 (the slowest host
-// seen), 65 000 143 .. 152 / 144; from there on 89 000 169 / 153, 106 000 187 / 172, 172 000 198 / 182.
+// and the device four idle gaps; a shorter step has less than that to hide.  Layer by layer, on one stream with the grouping
+// carried by other launches against two streams: 2 300 ids 53 / 99 us, 15 000 82 / 119, 27 000 106 / 128, 63 000 154 / 178 (the
+// slowest host seen), 65 000 143 .. 152 / 144; from there on 89 000 169 / 153, 106 000 187 / 172, 172 000 198 / 182.
+// Steps that go in blocks of views (rows.hip) have other forms on either side.  Their lists of ids in LDS or in launches beside
+// them, one image a view: 16 383 and 16 384 views of 192 -> 128 bf16 68 / 108, 320 -> 256 bf16 75 / 113, 320 -> 256 fp32 137 / 162, so
+// that this line is below where it would be for them alone.  Grouping carried or blocks on two streams: 576 -> 512 -> 256 bf16, 58 000
+// ids 134 / 123, 106 000 184 / 152; narrow networks would carry on (192 -> 128 bf16, 64 000 ids 97 / 110, 106 000 114 / 117; 96 -> 64
+// fp32, 106 000 106 / 119).
 constexpr long long kOneStreamIds = 49152;
 // ... and the multiply-adds of its forward products, in bf16; four times that of fp32.  Weight gradients that long are worth
-// hiding the accumulation behind however few ids there are.  One stream / two, us, of steps of 12 000 to 48 000 ids: bf16,
-// 5.2e9 126 / 132, 5.9e9 138 / 137, 6.8e9 154 / 149, 7.2e9 169 / 151, 8.9e9 197 / 167, 23e9 311 / 256; fp32, 0.9e9
+// hiding the accumulation behind however few ids there are.  Layer by layer, one stream / two, us, of steps of 12 000 to 48 000
+// ids: bf16, 5.2e9 126 / 132, 5.9e9 138 / 137, 6.8e9 154 / 149, 7.2e9 169 / 151, 8.9e9 197 / 167, 23e9 311 / 256; fp32, 0.9e9
 // 131 / 129, 1.2e9 148 / 149, 1.4e9 179 / 183, 1.7e9 191 / 183, 2.4e9 225 / 214, 2.9e9 311 / 288.
 constexpr double kOneStreamMacs = 6.8e9;
 

@@ -120,7 +120,9 @@ constexpr int kMaxRides = 3;                          // passes that other launc
 constexpr int kMaxDigitBits = 12;
 constexpr int kSideDigitBits = 11;                    // of passes that other launches carry
 constexpr int kBesideDigitBits = 9;                   // of passes beside workgroups that fill their CU
-constexpr int kLongList = 65536;                      // ids from which a workgroup of the check takes several tiles and the segments take few registers
+// ids from which a workgroup of the check takes several tiles and the segments take few registers, and images from which the
+// grouping of a step in blocks of views is on the caller's stream and the blocks on the helper's (api.hip)
+constexpr int kLongList = 65536;
 // Counts a tile publishes over all passes, at most.  A pass costs a launch and two memory latencies whatever its
 // radix, so a list takes as few passes as its keys allow within this (one up to 12 bits, two up to 22, then three);
 // it is what the regions that hold the counts have room for (24 KB per tile of 2048 keys).

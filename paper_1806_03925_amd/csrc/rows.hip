@@ -6,10 +6,10 @@
 // other stream.
 //
 // Layer by layer a short step is a chain of eight to twelve dependent launches of 4 to 16 us, each of which pays its ramp,
-// the latency of its first operands and the links of the grouping it carries.  Here the chain is four launches (this one
-// behind the prologue, then accumulation, weight gradients and parameter update): us a step, layer by layer / in blocks,
-// 512 views fp32 52 / 38, 4096 views of 320 -> 256 -> 128 fp32 106 / 85, 5000 of 288 -> 256 fp32 80 / 65, 1000 of 336 ->
-// 320 -> 72 -> 64 bf16 87 / 50.  What bounds it: 4096 views in fp32 take 29 us here, of which the matrix instructions need
+// the latency of its first operands and the links of the grouping it carries.  Here the chain is four launches: the prologue,
+// this one, accumulation beside weight gradients (accum_wgrad.hip) and the parameter update.  us a step, layer by layer / so,
+// 512 views fp32 51 / 31, 4096 views of 320 -> 256 -> 128 fp32 104 / 74, 5000 of 288 -> 256 fp32 79 / 62, 1000 of 336 ->
+// 320 -> 72 -> 64 bf16 86 / 44.  What bounds it: 4096 views in fp32 take 29 us here, of which the matrix instructions need
 // 12 and the gather 4; the rest is the first fetch of each layer's weights (cold in every XCD's L2), the waits between
 // phases and, in the smallest steps, the fetch of instructions (about 0.5 us a KB of code that runs once).
 //
@@ -504,7 +504,7 @@ __device__ __forceinline__ void rows_columns(const RowsArgs &p, unsigned char *l
 }
 
 // The first local.blocks workgroups group the ids.  Two workgroups of up to 32 views share a CU (kHalf below), so they have half
-// the registers; those of 64 have the CU to themselves but for the sorts of a long step, which take 104 to 114 registers
+// the registers; those of 64 have the CU to themselves but for the sorts of a long step, which take 102 to 116 registers
 // beside 191 (group.hip).  In fp32 with 32 views, a form of long steps only, 96 leave room for them too (hotkey 175.5 us a step, with 108 180).
 template <typename T, int MT>
 __global__ void __launch_bounds__(kRowsThreads, MT == 4 ? 2 : MT == 2 && sizeof(T) == 4 ? 5 : 4) k_rows(RowsArgs p, LocalTask local) {

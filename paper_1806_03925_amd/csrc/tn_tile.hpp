@@ -1,5 +1,5 @@
-// Device code of the weight gradients on tiles of moderate size (gemm_tile.hip has the products' own launches, accum.hip
-// carries these beside the accumulation), and the copies, LDS reads and waits that all products on such tiles use.
+// Device code of the weight gradients on tiles of moderate size (gemm_tile.hip has the products' own launches, accum_wgrad.hip
+// has these beside the accumulation), and the copies, LDS reads and waits that all products on such tiles use.
 #pragma once
 
 #include "gemm_common.hpp"
