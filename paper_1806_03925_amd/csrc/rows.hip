@@ -607,8 +607,9 @@ constexpr int kStateSpan = 96;     // words of three per part, then a ticket
 //   the step (192 -> 128: 98 images a view 109 / 136, 200 162 / 155, 600 371 / 220; 576 -> 512 -> 256: 80 135 / 131, 98 146 / 147,
 //   200 205 / 175).
 //   Cached rows of more than a kilobyte are two loads for a lane, one behind the other; eight wavefronts a CU then gather slower than
-//   the gather's launch, and several narrow layers do not make up for it (768 -> 72 -> 40 -> 24: 14 000 views of eight images
-//   164 / 159; 1088 -> 64: 168 / 178).
+//   the gather's launch, and three narrow layers and more do not make up for it (768 -> 72 -> 40 -> 24, eight images: 14 000 views
+//   164 / 159, 16 384 172 / 165; but 704 -> 256 -> 128 166 / 171 and 178 / 181, 1088 -> 64 168 / 178, 576 -> 512 -> 256 with an fp32
+//   cache 166 / 172 and 176 / 188; 640 -> 512 -> 128, which stays, 181 / 175).
 // - fp32: products of the layers are bound by the matrix unit either way, so what is gained is their launches, where a full
 //   round takes as long for fewer views: small products from 12 288 views on (96 -> 64: 108 / 119, 16 384 114 / 120; 192 -> 128:
 //   124 / 123 and 129 / 131, with eight images 133 / 139 and 143 / 151), larger ones only next to the full round (320 -> 256:
@@ -622,7 +623,7 @@ bool plan_long(const Layout &lay, int dt, int B, int nnz, double stream, size_t 
   const long long lds = place_buffers(lay, dt, plan->rows, &a);
   if (lds + 1024 > 160 * 1024) return false;
   const int round = 256 * plan->rows * (plan->rows == 32 && lds + 1024 <= 80 * 1024 ? 2 : 1);
-  if (plan->rows == 64 && lay.L > 2 && row_bytes > kWave * 16) return false;
+  if (plan->rows == 64 && lay.L > 3 && row_bytes > kWave * 16) return false;
   if (B > round && !(bf16 && plan->rows == 64 && lay.L == 2 && lds <= 64 * 1024 && B <= 20480)) return false;
   plan->lds = (int)lds;
   plan->room = 0;

@@ -187,7 +187,8 @@ def test_on_one_stream_a_long_step_goes_layer_by_layer_with_the_bits_of_blocks(d
     ("bf16", 16_384, 2, (40, 1), 40, "long blocks"), ("bf16", 16_385, 2, (40, 1), 40, "long blocks"),     # one narrow layer: two rounds
     ("bf16", 16_384, 2, (72, 40, 1), 40, "long blocks"), ("bf16", 16_385, 2, (72, 40, 1), 40, "helper"),
     ("bf16", 8_192, 5, (256, 1), 960, "long blocks"), ("bf16", 8_193, 5, (256, 1), 960, "helper"),   # one workgroup a CU
-    ("bf16", 13_000, 2, (72, 40, 1), 512, "long blocks"), ("bf16", 13_000, 2, (72, 40, 1), 520, "helper"),   # a row in two loads
+    ("bf16", 13_000, 2, (72, 40, 24, 1), 512, "long blocks"), ("bf16", 13_000, 2, (72, 40, 24, 1), 520, "helper"),   # a row in two loads
+    ("bf16", 13_000, 2, (72, 40, 1), 520, "long blocks"),
     ("bf16", 600, 85, (40, 1), 40, "long blocks"), ("bf16", 500, 97, (40, 1), 40, "helper"),         # images a view
     ("bf16", 16, 256, (40, 1), 40, "blocks"), ("bf16", 16, 257, (40, 1), 40, "carried"),        # (ids sorted in LDS, or carried)
     ("bf16", 2_000, 23, (768, 384, 1), 768, "helper"),                                          # wide layers, few views
