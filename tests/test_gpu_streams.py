@@ -135,14 +135,16 @@ def test_steps_on_streams_of_their_own_share_a_store_in_the_order_they_were_issu
         assert torch.equal(a, b)
 
 
-def test_a_short_step_recorded_into_a_graph_between_steps_on_other_streams():
+@pytest.mark.parametrize("views,one", [(SHORT, False), (LONG, True)])   # in blocks; layer by layer with the sums of blocks
+def test_a_step_on_one_stream_recorded_into_a_graph_between_steps_on_other_streams(views, one):
     """Recording takes no event from the order of the steps and leaves none: replays, with eager steps on another stream
     before and between them, give the bits of the same steps issued one after the other."""
     import paper_1806_03925_amd as g
     results = []
     for recorded in (False, True):
-        wl, st, src = state_of("bf16", SHORT)
-        dev = g.DeviceBatch.from_host(src.batch(0, batch=SHORT))
+        wl, st, src = state_of("bf16", views)
+        st.one_stream = one
+        dev = g.DeviceBatch.from_host(src.batch(0, batch=views))
         wl2, st2, _ = state_of("bf16", LONG)
         dev2 = g.DeviceBatch.from_host(src.batch(1, batch=LONG))
         beside = torch.cuda.Stream()
@@ -167,5 +169,6 @@ def test_a_short_step_recorded_into_a_graph_between_steps_on_other_streams():
         torch.cuda.synchronize()
         assert int(st.status.item()) == 0 and int(st2.status.item()) == 0
         results.append(outputs(st) + outputs(st2))
+        assert form_of(st, dev, wl.M, 0.1) == ("carried" if one else "blocks")
     for a, b in zip(*results):
         assert torch.equal(a, b)
