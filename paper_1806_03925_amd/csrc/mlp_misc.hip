@@ -1,6 +1,8 @@
 // The part of the Sparse-Part MLP that is not a matrix product (Section 3, step 4: forward to the loss and the first step
 // back): the logit layer with the loss and its derivative, the delta of the last hidden layer, and partial sums of the
 // logit layer's weight gradient, both biases' gradients and the loss.  params.hip adds them up and applies them.
+// rows.hip has the same formulas for blocks of views, with other owners of rows and columns: they are changed in both places
+// (a step of either form gives the same logits and deltas bit for bit, which the tests hold together).
 #include "group_device.hpp"
 
 #include <type_traits>
