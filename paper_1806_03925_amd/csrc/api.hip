@@ -314,10 +314,12 @@ SideLane *side_lane(bool helper) {
     hipStream_t stream = nullptr;
     hipEvent_t fork = nullptr, join = nullptr, join_captured = nullptr, checked = nullptr;
     bool ok = hipStreamCreateWithFlags(&stream, hipStreamNonBlocking) == hipSuccess;
-    ok = ok && hipEventCreateWithFlags(&fork, hipEventDisableTiming) == hipSuccess;
+    // Those that only streams of this device wait for go without a fence beyond it, as `done` does (a step of 65 536 views with all
+    // of them so 950 us against 958).  `join` keeps it: without, the helper stream is reported as busy after it has ended.
+    ok = ok && hipEventCreateWithFlags(&fork, hipEventDisableTiming | hipEventDisableSystemFence) == hipSuccess;
     ok = ok && hipEventCreateWithFlags(&join, hipEventDisableTiming) == hipSuccess;
     ok = ok && hipEventCreateWithFlags(&join_captured, hipEventDisableTiming) == hipSuccess;
-    ok = ok && hipEventCreateWithFlags(&checked, hipEventDisableTiming) == hipSuccess;
+    ok = ok && hipEventCreateWithFlags(&checked, hipEventDisableTiming | hipEventDisableSystemFence) == hipSuccess;
     if (!ok) {
       if (checked) (void)hipEventDestroy(checked);
       if (join_captured) (void)hipEventDestroy(join_captured);
