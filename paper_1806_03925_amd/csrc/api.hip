@@ -605,9 +605,11 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   for (int l = 0; l < L - 1; ++l) macs += (double)B * lay.in_dim[l] * lay.out_dim[l];
   const bool is_short = (long long)2 * B + b->nnz < kOneStreamIds && macs * (dt == GEAR_BF16 ? 1 : 4) < kOneStreamMacs;
   // In blocks of views: the whole network in one launch (rows.hip), of a short step with the grouping of the ids in its first
-  // workgroups.  A longer one has the grouping on the other stream, and whichever is the longer chain stays on the caller's
-  // with the bookkeeping behind it, because a wait for the other stream is 10 us on the device: the grouping where there are
-  // many images (us a step, it here / on the helper: 106 000 ids 159.5 / 163, 172 000 181 / 189; 65 000 133 / 127).
+  // workgroups.  A longer one has the grouping on the other stream, by tiles that are counted ahead of every pass
+  // (group_device.hpp), from the start of the step on, so that it is done when the weight gradients are, and the bookkeeping
+  // follows those on the caller's (accumulation beside weight gradients, in one launch or on two streams, took as long as one
+  // behind the other, and the wait for the blocks 10 us more).  us a step, tiles that look back / counted: 16 384 views of 576 ->
+  // 512 -> 256 bf16, 106 000 ids, 157 / 147; of 320 -> 256 fp32, 172 000 ids, 174 / 164.
   RowsPlan rows;
   const bool long_dx = (double)B * (F - 2 * cfg->emb_dim) * lay.out_dim[0] >= kSplitDxMacs;
   TnProblem widths[GEAR_MAX_LAYERS];   // of the weight-gradient products
@@ -618,27 +620,28 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   }
   const TnChoice first_choice = gemm_tn_choice(dt, widths, L - 1, B);
   const bool one_group = first_choice.layers == L - 1 && all_partials * sizeof(float) <= lay.wgrad_partial_bytes;
-  const bool planned = (is_short || (!long_dx && one_group)) && plan_rows(*cfg, lay, B, b->nnz, is_short, &rows);
+  bool planned = (is_short || (!long_dx && one_group)) && plan_rows(*cfg, lay, B, b->nnz, is_short, &rows);
+  const int key_bits[kMaxProblems] = {bits_for(cfg->n_users), bits_for(cfg->n_urls), bits_for(cfg->n_images)};
+  int own_passes[kMaxProblems];   // of a longer step's lists
+  for (int i = 0; planned && !is_short && i < kMaxProblems; ++i) {
+    const bool last = i == kMaxProblems - 1;
+    own_passes[i] = counted_passes(key_bits[i], last ? b->nnz : B, last ? cfg->max_nnz : cfg->max_batch, rows.digit_bits);
+    planned = own_passes[i] > 0;
+  }
   // On one stream nothing runs beside the blocks of a longer step, while the launches of its layers carry the grouping: it goes
   // layer by layer, with its batch sums in the shape the blocks would leave (block_sums.hpp), so that both forms have the same
   // bits.  us a step on one stream, layers / blocks, 576 -> 512 -> 256 bf16: 9001 views 134 / 154, 12 288 148 / 165, 16 384 184 / 188;
   // 192 -> 128, 10 000 views 97 / 110; 96 -> 64 fp32, 16 384 106 / 127.  The sums are 1 to 4 of it.
   const bool by_rows = planned && (is_short || !out->one_stream), as_rows = planned && !by_rows;
-  const bool local_sort = by_rows && is_short;
-  const bool group_here = by_rows && b->nnz > kLongList;
+  const bool local_sort = by_rows && is_short, counted = by_rows && !is_short;
   const bool one_stream = out->one_stream != 0 || local_sort || (moderate && is_short);
   const bool carried = one_stream && moderate && !by_rows;
-  // Blocks of 64 views leave a CU room for sorts by narrow digits only (102 registers against 170, 6 KB of LDS against 24 or 48):
-  // wide ones wait for the blocks to end (16 384 views of two images, 576 -> 512 -> 256 bf16: 159 us a step, narrow 139).
-  const bool beside_rows = by_rows && !local_sort && rows.rows == 64;
-
   // grouping of the three id lists and the plan of the per-image accumulation
   GroupBatch gb;
   {
-    const int bits[kMaxProblems] = {bits_for(cfg->n_users), bits_for(cfg->n_urls), bits_for(cfg->n_images)};
     int passes = 1;   // the lists share launches: as many passes for all as the widest ids need
     for (int i = 0; i < kMaxProblems; ++i) {
-      const int need = radix_passes(bits[i], lay.g[i].total_words, carried ? kSideDigitBits : beside_rows ? kBesideDigitBits : widest_digit(B > b->nnz ? B : b->nnz));
+      const int need = radix_passes(key_bits[i], lay.g[i].total_words, carried ? kSideDigitBits : widest_digit(B > b->nnz ? B : b->nnz));
       if (need > passes) passes = need;
     }
     // a pass that is carried costs nothing but its length, and narrow digits make it short: as many as find a launch ahead
@@ -646,9 +649,9 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
     const int rides = L < kMaxRides ? L : kMaxRides;   // the forward products and the logit layer
     if (carried && passes < rides) passes = rides;
     gb.count = kMaxProblems;
-    gb.p[0] = make_problem(lay, ws, 0, b->user_id, B, cfg->n_users, passes, bits[0]);
-    gb.p[1] = make_problem(lay, ws, 1, b->url_id, B, cfg->n_urls, passes, bits[1]);
-    gb.p[2] = make_problem(lay, ws, 2, b->img_id, b->nnz, cfg->n_images, passes, bits[2]);
+    gb.p[0] = make_problem(lay, ws, 0, b->user_id, B, cfg->n_users, counted ? own_passes[0] : passes, key_bits[0]);
+    gb.p[1] = make_problem(lay, ws, 1, b->url_id, B, cfg->n_urls, counted ? own_passes[1] : passes, key_bits[1]);
+    gb.p[2] = make_problem(lay, ws, 2, b->img_id, b->nnz, cfg->n_images, counted ? own_passes[2] : passes, key_bits[2]);
     gb.tickets = (int32_t *)(ws + lay.tickets);
     gb.seg_state = (uint32_t *)(ws + lay.seg_state);
     if (!out->dbg_img_unique && !out->dbg_img_segoff) gb.p[2].unique = gb.p[2].segoff = nullptr;   // nothing in the step reads them
@@ -672,10 +675,9 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   if (needs_lane && !side) return GEAR_ERR_HIP;
   hipStream_t helper = one_stream ? s : side->stream;
   LaneScope lane(side, !one_stream, !by_rows, captured, s);
-  // Layer by layer on two streams the helper has all that looks at the store.  Blocks whose grouping is on the caller's stream
-  // take their place ahead of its last launch.  The others do at once: ahead of a launch in the middle of the helper's chain the
-  // wait costs a program that is alone 2 us a step.
-  if (!group_here) GEAR_HIP(lane.enter(by_rows ? s : helper));
+  // Layer by layer on two streams the helper has all that looks at the store.  Blocks whose lists are counted take their place
+  // ahead of the launch that first does.
+  if (!counted) GEAR_HIP(lane.enter(by_rows ? s : helper));
   {
     // Step outputs and counters cleared and the operand copies of the weights made in one launch ahead of everything:
     // the first product then needs no event, and behind the gather's many workgroups the copies would not get onto the
@@ -685,13 +687,16 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
     for (int l = 0; l < n_jobs; ++l)
       jobs[l] = CastJob{t->mlp_params + lay.w_off[l], ws + lay.wc[l], ws + lay.wct[l], lay.out_dim[l], lay.in_dim[l]};
     ZeroList zero;
+    zero.count = 0;
     if (local_sort)
       local_zero_list(gb, &zero);
-    else
+    else if (!counted)
       group_zero_list(gb, &zero);
-    GEAR_RUN("begin", launch_begin(out->status, failed, out->n_ready, out->loss, zero, dt, jobs, n_jobs, by_rows, s));
+    // Counted lists need nothing that this launch makes, and their first launch clears the outputs: the helper starts beside it.
+    if (counted) GEAR_HIP(lane.fork());
+    GEAR_RUN("begin", launch_begin(counted ? nullptr : out->status, failed, out->n_ready, out->loss, zero, dt, jobs, n_jobs, by_rows, s));
   }
-  if (!carried && !local_sort) GEAR_HIP(lane.fork());
+  if (!carried && !local_sort && !counted) GEAR_HIP(lane.fork());
   // Carried: the links of the grouping in order, each taken by the next launch that can.
   SideTask task;
   int link = 0;
@@ -720,11 +725,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   if (by_rows) {
     LocalTask local = {};
     if (local_sort) local = local_task(rows, gb, plan_args, failed);
-    hipStream_t caller = s;
-    {
-      hipStream_t s = group_here ? helper : caller;
-      GEAR_RUN("view_blocks", launch_rows(*cfg, lay, rows, *b, *t, dfv_cache, ws, local, s));
-    }
+    GEAR_RUN("view_blocks", launch_rows(*cfg, lay, rows, *b, *t, dfv_cache, ws, local, s));
   } else {
     const CheckTask check = check_task(gb, b->img_off, occ_view, B, b->nnz, failed, out->status);
     GEAR_RUN("gather_pool", launch_gather_pool(*cfg, *b, *t, dfv_cache, x, s, carried ? &check : nullptr));
@@ -743,12 +744,25 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   // device (a caller that waits for every step), the gather then starts as soon as the step does, not
   // after the host has issued the grouping's launches.
   if (!carried && !local_sort) {
-    hipStream_t caller = s, s = group_here ? caller : helper;  // the stream of this block's launches
-    GEAR_RUN("group_ids", launch_check(gb, b->img_off, occ_view, B, b->nnz, failed, out->status, s));
-    for (int pass = 0; pass < group_passes(gb); ++pass) GEAR_RUN("group_ids", launch_radix_pass(gb, pass, failed, s));
-    if (group_here) GEAR_HIP(lane.enter(s));
-    GEAR_RUN("accum_plan", launch_segments(gb, &plan_args, failed, s));
-    if (!group_here) GEAR_HIP(by_rows ? lane.mark() : lane.mark_checked());
+    hipStream_t s = helper;  // the stream of this block's launches
+    if (counted) {
+      const StepOutputs outputs = {out->status, failed, out->n_ready, out->loss};
+      const ViewCheck views = {b->img_off, occ_view, B, b->nnz};
+      const int planned = gb.p[2].n > 0 ? gb.p[2].passes : 1;   // passes that the plan comes behind
+      for (int pass = 0; pass < group_passes(gb); ++pass) {
+        if (pass != planned) GEAR_RUN(pass < 2 ? "group_ids" : "group_rest", launch_count(gb, pass, outputs, views, s));
+        GEAR_RUN(pass < 2 ? "group_ids" : "group_rest", launch_counted_pass(gb, pass, views, plan_args, failed, s));
+        if (pass + 1 == planned) {
+          GEAR_HIP(lane.enter(s));
+          GEAR_RUN("accum_plan", launch_segments_count(gb, plan_args, planned, failed, s));
+        }
+      }
+    } else {
+      GEAR_RUN("group_ids", launch_check(gb, b->img_off, occ_view, B, b->nnz, failed, out->status, s));
+      for (int pass = 0; pass < group_passes(gb); ++pass) GEAR_RUN("group_ids", launch_radix_pass(gb, pass, failed, s));
+      GEAR_RUN("accum_plan", launch_segments(gb, &plan_args, failed, s));
+    }
+    GEAR_HIP(counted ? lane.mark() : lane.mark_checked());
   }
 
   // Until its first kernel that changes caller state (the first SGD on a hidden layer's weights), the
@@ -833,7 +847,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   const bool beside = local_sort && !first_choice.large && one_group;
   // Behind blocks of views the grouping may still be at work: the products fill that time, and the bookkeeping follows them
   // on the caller's stream.
-  const bool books_here = one_stream || by_rows, books_last = by_rows && !local_sort;
+  const bool books_here = one_stream || by_rows;
   if (!by_rows) GEAR_HIP(lane.fork());
   auto bookkeeping = [&](hipStream_t s) -> gear_status {
     if (!divided && !books_here) GEAR_RUN("embedding_update", launch_embedding_update(emb, false, failed, s));
@@ -843,7 +857,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
                                              divided ? nullptr : &emb, !books_here, as_rows ? &riding : nullptr, failed, s));
     return GEAR_OK;
   };
-  if (!beside && !books_last) {
+  if (!beside && !counted) {
     if (gear_status st = bookkeeping(helper)) return st;
     GEAR_HIP(lane.mark());
   }
@@ -879,16 +893,13 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
       GEAR_RUN("accumulate_wgrad", launch_accumulate_wgrad(*cfg, gb.p[2], plan, dx_dfv, grad_accum, M, out->ready_ids, out->ready_grads,
                                                            emb, wp, n, B, splits, failed, s));
     } else {
-      hipStream_t caller = s;
-      hipStream_t s = group_here ? helper : caller;
       GEAR_RUN("wgrad_gemm", launch_gemm_tn(dt, wp + first, n, B, splits, choice.large, nullptr, s));
     }
     // The sums of the partials and the SGD change caller state, so the status word has to be final: the
     // stream waits for the helper's first part (long done by now), not for the bookkeeping.  Their
     // workgroups get onto the device as the bookkeeping's leave room and are done before it is, so the
     // step ends with the bookkeeping and the join.
-    if (first == 0 && books_last) {
-      if (group_here) GEAR_HIP(lane.mark());
+    if (first == 0 && counted) {
       GEAR_HIP(lane.wait(true));
       if (gear_status st = bookkeeping(s)) return st;
     } else if (first == 0) {

@@ -119,7 +119,7 @@ constexpr int kMaxPasses = 4;
 constexpr int kMaxRides = 3;                          // passes that other launches are asked to carry, if it is up to us
 constexpr int kMaxDigitBits = 12;
 constexpr int kSideDigitBits = 11;                    // of passes that other launches carry
-constexpr int kBesideDigitBits = 9;                   // of passes beside workgroups that fill their CU
+constexpr int kCountedDigitBits = 10;                 // of passes whose tiles are counted ahead of them
 // ids from which a workgroup of the check takes several tiles and the segments take few registers, and images from which the
 // grouping of a step in blocks of views is on the caller's stream and the blocks on the helper's (api.hip)
 constexpr int kLongList = 65536;
@@ -138,7 +138,7 @@ struct GroupProblem {
   int32_t *keys[2];        // ping-pong key buffers [n]
   int32_t *vals[2];        // ping-pong position buffers [n]
   int32_t *totals;         // [passes][radix] keys of a digit in the whole list
-  uint32_t *state;         // [passes][tiles - 1][radix] what tiles publish for those after them
+  uint32_t *state;         // [passes][tiles - 1][radix] what tiles publish for those after them; counted: [passes][tiles][radix]
   int32_t *sorted_keys;    // = keys[passes & 1]
   int32_t *perm;           // = vals[passes & 1]
   int32_t *unique;         // [n]   distinct keys ascending (NULL: not wanted)
@@ -303,6 +303,7 @@ struct CastJob {
   int rows, cols;
 };
 hipError_t launch_clear(const ZeroList &zero, hipStream_t s);
+// (status NULL: the outputs are cleared elsewhere)
 hipError_t launch_begin(int32_t *status, int32_t *failed, int32_t *n_ready, float *loss, const ZeroList &zero, int dtype, const CastJob *jobs,
                         int count, bool packed, hipStream_t s);
 void group_zero_list(const GroupBatch &gb, ZeroList *z);
@@ -315,6 +316,17 @@ int radix_lds_bytes(const GroupBatch &gb);
 hipError_t launch_check(const GroupBatch &gb, const int32_t *img_off, int32_t *occ_view, int B, int nnz, int32_t *failed,
                         int32_t *status, hipStream_t s);
 hipError_t launch_radix_pass(const GroupBatch &gb, int pass, const int32_t *failed, hipStream_t s);
+// passes of a list whose tiles are counted, in digits of up to `widest` bits: the fewest whose counts fit where the list's
+// unique ids and their offsets go (of `cap` ids at most); 0: they do not
+int counted_passes(int bits, int n, int cap, int widest);
+int counted_lds_bytes(int digit_bits);
+struct StepOutputs {      // cleared at the start of a step
+  int32_t *status, *failed, *n_ready;
+  float *loss;
+};
+hipError_t launch_count(const GroupBatch &gb, int pass, const StepOutputs &out, const ViewCheck &views, hipStream_t s);   // the first one clears the outputs
+hipError_t launch_counted_pass(const GroupBatch &gb, int pass, const ViewCheck &views, const PlanArgs &args, int32_t *failed, hipStream_t s);
+hipError_t launch_segments_count(const GroupBatch &gb, const PlanArgs &args, int next, int32_t *failed, hipStream_t s);
 hipError_t launch_segments(const GroupBatch &gb, const PlanArgs *args, int32_t *failed, hipStream_t s);
 // distinct ids of a grouped list whose cache entry is older than `expiry`, ascending
 // words (four images each) of the byte map over all images that the expiry filter marks, and tiles

@@ -235,9 +235,78 @@ __global__ void __launch_bounds__(kSortBlock) k_radix_pass(GroupBatch gb, int pa
   radix_pass_any<BITS, BITS <= 9 ? 4 : 16>(gb, blockIdx.y, pass, idle, lds);
 }
 
+// 96 registers in the passes and the segments: five waves' worth, which find a place beside four of a block's 96 on a SIMD whatever
+// was there before (with 128 the first pass waited 40 us for one to end).
+// The first of these launches of a step clears what the segments publish in, and the step's outputs.
+__global__ void __launch_bounds__(kSortBlock) k_count(GroupBatch gb, int pass, StepOutputs out, ViewCheck views) {
+  if ((int)blockIdx.y == gb.count) {
+    // the views of the occurrences; a list that is no list is noted by the next launch, since this one clears the word for it
+    for (int i = blockIdx.x * kSortBlock + threadIdx.x; i < views.B; i += gridDim.x * kSortBlock)
+      if (view_ok(views, i))
+        for (int j = views.img_off[i]; j < views.img_off[i + 1]; ++j) views.occ_view[j] = i;
+    if (blockIdx.x != 0) return;
+    const int words = 3 * (radix_tiles(gb.p[gb.count - 1].n) - 1);
+    for (int i = threadIdx.x; i < words; i += kSortBlock) gb.seg_state[i] = 0u;
+    if (threadIdx.x == 0) {
+      gb.tickets[kTickets - 1] = 0;
+      *out.status = 0;
+      *out.failed = 0;
+      *out.n_ready = 0;
+      *out.loss = 0.0f;
+    }
+    return;
+  }
+  const GroupProblem &p = gb.p[blockIdx.y];
+  if (pass >= p.passes || (int)blockIdx.x >= radix_tiles(p.n)) return;
+  __builtin_amdgcn_s_setprio(3);
+  extern __shared__ int hist[];
+  count_tile(p, pass, blockIdx.x, hist);
+}
+
+__global__ void __launch_bounds__(kSortBlock, 5) k_counted_pass(GroupBatch gb, int pass, ViewCheck views, PlanArgs args, int32_t *failed) {
+  if ((int)blockIdx.y == gb.count) {
+    for (int i = blockIdx.x * kSortBlock + threadIdx.x; i < views.B; i += gridDim.x * kSortBlock)
+      if (!view_ok(views, i)) flag(failed, args.status, GEAR_ERR_RANGE);
+    return;
+  }
+  const GroupProblem &p = gb.p[blockIdx.y];
+  if (pass >= p.passes || (int)blockIdx.x >= radix_tiles(p.n)) return;
+  __builtin_amdgcn_s_setprio(3);
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+  __shared__ int scan_smem[8];
+  const bool last = (int)blockIdx.y == gb.count - 1 && pass == p.passes - 1;
+#define GEAR_COUNTED(DPT)                                                          \
+  if (last)                                                                        \
+    counted_pass<DPT, true>(p, pass, blockIdx.x, args, failed, lds, scan_smem);    \
+  else                                                                             \
+    counted_pass<DPT, false>(p, pass, blockIdx.x, args, failed, lds, scan_smem)
+  if (p.digit_bits == 10) {
+    GEAR_COUNTED(4);
+  } else if (p.digit_bits == 9) {
+    GEAR_COUNTED(2);
+  } else {
+    GEAR_COUNTED(1);
+  }
+#undef GEAR_COUNTED
+}
+
 template <bool PLAN, bool BESIDE>
 __global__ void __launch_bounds__(kSortBlock, BESIDE ? 5 : 1) k_segments(GroupBatch gb, PlanArgs args, int32_t *failed) {
-  segments<PLAN>(gb, args, blockIdx.x, failed);
+  segments<PLAN, true>(gb, args, blockIdx.x, failed);
+}
+
+// behind counted passes, with the counts of the other lists' next pass
+__global__ void __launch_bounds__(kSortBlock, 5) k_segments_count(GroupBatch gb, PlanArgs args, int pass, int32_t *failed) {
+  __builtin_amdgcn_s_setprio(3);
+  if ((int)blockIdx.y == 0) {
+    const int tiles = radix_tiles(gb.p[gb.count - 1].n);
+    if ((int)blockIdx.x < (tiles < 1 ? 1 : tiles)) segments<true, false>(gb, args, blockIdx.x, failed);
+    return;
+  }
+  const GroupProblem &p = gb.p[blockIdx.y - 1];
+  if (pass >= p.passes || (int)blockIdx.x >= radix_tiles(p.n)) return;
+  extern __shared__ int hist[];
+  count_tile(p, pass, blockIdx.x, hist);
 }
 }  // namespace
 
@@ -258,6 +327,54 @@ hipError_t launch_radix_pass(const GroupBatch &gb, int pass, const int32_t *fail
     hipLaunchKernelGGL(k_radix_pass<kMaxDigitBits>, dim3(tiles, gb.count), dim3(kSortBlock), radix_lds_bytes(gb), s, gb, pass, failed);
   else
     hipLaunchKernelGGL(k_radix_pass<9>, dim3(tiles, gb.count), dim3(kSortBlock), radix_lds_bytes(gb), s, gb, pass, failed);
+  return hipGetLastError();
+}
+
+int counted_passes(int bits, int n, int cap, int widest) {
+  const size_t tiles = radix_tiles(n);
+  for (int passes = 1; passes <= kMaxPasses; ++passes) {
+    const int digit_bits = (bits + passes - 1) / passes;
+    if (digit_bits <= widest && (tiles * passes << digit_bits) <= 3 * (size_t)cap) return passes;
+  }
+  return 0;
+}
+int counted_lds_bytes(int digit_bits) { return ((int)(sizeof(int) + kSortBlock / kWave * sizeof(uint16_t)) << digit_bits) + 1280; }
+
+static int most_tiles(const GroupBatch &gb, int pass) {
+  int tiles = 0;
+  for (int i = 0; i < gb.count; ++i)
+    if (pass < gb.p[i].passes && radix_tiles(gb.p[i].n) > tiles) tiles = radix_tiles(gb.p[i].n);
+  return tiles;
+}
+
+hipError_t launch_count(const GroupBatch &gb, int pass, const StepOutputs &out, const ViewCheck &views, hipStream_t s) {
+  for (int i = 0; i < gb.count; ++i)
+    if (gb.p[i].digit_bits > kCountedDigitBits) return hipErrorInvalidValue;   // counted_pass
+  const int tiles = most_tiles(gb, pass);
+  if (tiles == 0 && pass > 0) return hipSuccess;
+  hipLaunchKernelGGL(k_count, dim3(tiles < 1 ? 1 : tiles, gb.count + (pass == 0 ? 1 : 0)), dim3(kSortBlock),
+                     widest_radix(gb) * sizeof(int), s, gb, pass, out, views);
+  return hipGetLastError();
+}
+
+hipError_t launch_counted_pass(const GroupBatch &gb, int pass, const ViewCheck &views, const PlanArgs &args, int32_t *failed, hipStream_t s) {
+  const int tiles = most_tiles(gb, pass);
+  if (tiles == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_counted_pass, dim3(tiles, gb.count + (pass == 0 ? 1 : 0)), dim3(kSortBlock), radix_lds_bytes(gb), s, gb, pass,
+                     views, args, failed);
+  return hipGetLastError();
+}
+
+// the plan of the last list, and the counts of the others' pass `next` where they have one
+hipError_t launch_segments_count(const GroupBatch &gb, const PlanArgs &args, int next, int32_t *failed, hipStream_t s) {
+  int tiles = radix_tiles(gb.p[gb.count - 1].n), others = 0;
+  if (tiles < 1) tiles = 1;
+  for (int i = 0; i + 1 < gb.count; ++i)
+    if (next < gb.p[i].passes) {
+      others = gb.count - 1;
+      if (radix_tiles(gb.p[i].n) > tiles) tiles = radix_tiles(gb.p[i].n);
+    }
+  hipLaunchKernelGGL(k_segments_count, dim3(tiles, 1 + others), dim3(kSortBlock), widest_radix(gb) * sizeof(int), s, gb, args, next, failed);
   return hipGetLastError();
 }
 

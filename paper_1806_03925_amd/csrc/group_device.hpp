@@ -63,6 +63,11 @@ __device__ __forceinline__ void flag(int32_t *failed, int32_t *status, int code)
   atomicCAS(status, 0, code);
 }
 
+__device__ __forceinline__ bool view_ok(const ViewCheck &views, int i) {
+  const int32_t lo = views.img_off[i], hi = views.img_off[i + 1];
+  return lo >= 0 && lo <= hi && hi <= views.nnz && (i > 0 || lo == 0) && (i < views.B - 1 || hi == views.nnz);
+}
+
 // Workgroup `block` of those that check: list by list, then the views.
 __device__ __forceinline__ void check_and_count(const CheckTask &t, int block, int *hist /* [pass][digit] */) {
   const int per = t.tiles_per_block * kSortTile;
@@ -76,11 +81,8 @@ __device__ __forceinline__ void check_and_count(const CheckTask &t, int block, i
     const ViewCheck &views = t.views;
     const int i = block * kSortBlock + threadIdx.x;
     if (i >= views.B) return;
-    const int32_t lo = views.img_off[i], hi = views.img_off[i + 1];
-    const bool ok = lo >= 0 && lo <= hi && hi <= views.nnz;
-    if (!ok || (i == 0 && lo != 0) || (i == views.B - 1 && hi != views.nnz)) flag(t.failed, t.status, GEAR_ERR_RANGE);
-    if (ok)
-      for (int j = lo; j < hi; ++j) views.occ_view[j] = i;
+    if (!view_ok(views, i)) return flag(t.failed, t.status, GEAR_ERR_RANGE);
+    for (int j = views.img_off[i]; j < views.img_off[i + 1]; ++j) views.occ_view[j] = i;
     return;
   }
   const GroupProblem &p = t.gb.p[list];
@@ -274,6 +276,165 @@ __device__ __forceinline__ void radix_pass_any(const GroupBatch &gb, int list, i
   return radix_pass<1, WINDOW>(p, pass, ticket, idle, lds, scan_smem, &s_tile);
 }
 
+// ---- radix pass with counted tiles --------------------------------------------------------------------
+// The same scatter where a launch ahead of it has counted every tile's digits (p.state: [pass][tile][digit]).  A tile adds up
+// the counts of the tiles before it, many loads at once, instead of looking back at words that come past the caches one after
+// the other, and the sort needs no totals.  For what runs beside blocks of views, which is bound by latency: while the blocks
+// gather, a load takes microseconds.  us of the launch alone, 36 tiles of 2048 keys 7 to 9, 68 tiles 9 (looking back 10 and 25),
+// its count 3 to 5; beside the blocks 11 to 16 and 3 to 10 (looking back 13 to 18 and 20 to 57).  Digits of ten bits then cost
+// about what narrow ones do, so ids of 20 bits take two passes.  Counted by adds to the next pass' words while a pass scatters,
+// the most popular ids' words took 20 us of a pass, one add after the other.
+// Waves at the highest priority: blocks of views keep the matrix unit busy, not the others, and wait for nobody here.
+__device__ __forceinline__ void count_tile(const GroupProblem &p, int pass, int tile, int *hist /* [radix] */) {
+  const int radix = 1 << p.digit_bits, shift = pass * p.digit_bits, lane = threadIdx.x & 63;
+  const int32_t *keys = pass == 0 ? p.keys_in : p.keys[pass & 1];
+  const int64_t q0 = (int64_t)tile * kSortTile + threadIdx.x;
+  int32_t key[kSortItems];
+#pragma unroll
+  for (int i = 0; i < kSortItems; ++i) key[i] = q0 + i * kSortBlock < p.n ? keys[q0 + i * kSortBlock] : 0;
+  for (int d = threadIdx.x; d < radix; d += kSortBlock) hist[d] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < kSortItems; ++i) {
+    const bool valid = q0 + i * kSortBlock < p.n;
+    const int digit = (key[i] >> shift) & (radix - 1);
+    // lanes that share the first one's digit add as one: of a popular image all would, to one word, one after the other
+    const bool leads = valid && digit == __builtin_amdgcn_readfirstlane(digit);
+    const unsigned long long same = __ballot(leads);
+    if (valid && (!leads || (same & ((1ull << lane) - 1ull)) == 0ull)) atomicAdd(&hist[digit], leads ? __popcll(same) : 1);
+  }
+  __syncthreads();
+  uint32_t *row = p.state + ((size_t)pass * radix_tiles(p.n) + tile) * radix;
+  for (int d = threadIdx.x; d < radix; d += kSortBlock) row[d] = (uint32_t)hist[d];
+}
+
+// A thread owns DPT consecutive digits: four where there are 1024, two of 512, else one.
+// VIEWS: the images' last pass, which also leaves where each occurrence's gradient lives.
+template <int DPT, bool VIEWS>
+__device__ __forceinline__ void counted_pass(const GroupProblem &p, int pass, int tile, const PlanArgs &args, int32_t *failed,
+                                             unsigned char *lds, int *scan_smem) {
+  constexpr int WAVES = kSortBlock / kWave;
+  const int radix = 1 << p.digit_bits, shift = pass * p.digit_bits;
+  int *digit_off = reinterpret_cast<int *>(lds);                                   // [radix]
+  uint16_t *wave_cnt = reinterpret_cast<uint16_t *>(lds + radix * sizeof(int));    // [wave][radix]
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int d0 = tid * DPT, n_tiles = radix_tiles(p.n);
+  const bool owner = d0 < radix;
+  const int64_t first = (int64_t)tile * kSortTile + wave * (kWave * kSortItems) + lane;
+  const int32_t *keys_in = pass == 0 ? p.keys_in : p.keys[pass & 1];
+  const int32_t *vals_in = p.vals[pass & 1];
+  int32_t key[kSortItems], val[kSortItems], rank[kSortItems];
+#pragma unroll
+  for (int i = 0; i < kSortItems; ++i) {
+    const int64_t q = first + i * kWave;
+    key[i] = q < p.n ? keys_in[q] : 0;
+    val[i] = q < p.n ? (pass == 0 ? (int32_t)q : vals_in[q]) : 0;
+  }
+  for (int i = tid; i < WAVES * radix / 2; i += kSortBlock) reinterpret_cast<uint32_t *>(wave_cnt)[i] = 0u;
+  int view[kSortItems];
+  float scale[kSortItems];
+  if constexpr (VIEWS) {
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < kSortItems; ++i) view[i] = args.occ_view[val[i]];
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  // counts of the tiles before this one and of all
+  int before[DPT] = {}, total[DPT] = {};
+  const uint32_t *rows = p.state + (size_t)pass * n_tiles * radix + d0;
+  if (owner) {
+    constexpr int U = DPT == 4 ? 6 : 12;
+    for (int t0 = 0; t0 < n_tiles; t0 += U) {
+      uint32_t c[U][DPT];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const uint32_t *row = rows + (size_t)min(t0 + u, n_tiles - 1) * radix;
+        if constexpr (DPT == 4) {
+          const uint4 v = *reinterpret_cast<const uint4 *>(row);
+          c[u][0] = v.x, c[u][1] = v.y, c[u][2] = v.z, c[u][3] = v.w;
+        } else if constexpr (DPT == 2) {
+          const uint2 v = *reinterpret_cast<const uint2 *>(row);
+          c[u][0] = v.x, c[u][1] = v.y;
+        } else {
+          c[u][0] = row[0];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int j = 0; j < DPT; ++j) {
+          total[j] += t0 + u < n_tiles ? (int)c[u][j] : 0;
+          before[j] += t0 + u < tile ? (int)c[u][j] : 0;
+        }
+    }
+  }
+  if (pass == 0 && p.range > 0) {
+    bool bad = false;
+#pragma unroll
+    for (int i = 0; i < kSortItems; ++i) bad |= key[i] < 0 || (int64_t)key[i] >= p.range;
+    if (bad) flag(failed, args.status, GEAR_ERR_RANGE);
+  }
+  if constexpr (VIEWS) {
+#pragma unroll
+    for (int i = 0; i < kSortItems; ++i) {
+      const int32_t *off = args.img_off + view[i];
+      scale[i] = (float)(off[1] - off[0]);
+    }
+  }
+  __syncthreads();
+  uint16_t *mine = wave_cnt + wave * radix;
+#pragma unroll
+  for (int i = 0; i < kSortItems; ++i) {
+    const bool valid = first + i * kWave < p.n;
+    const int digit = (key[i] >> shift) & (radix - 1);
+    unsigned long long peers = __ballot(valid);
+    for (int b = 0; b < p.digit_bits; ++b) {
+      const bool bit = (digit >> b) & 1;
+      const unsigned long long m = __ballot(bit);
+      peers &= bit ? m : ~m;
+    }
+    const int lower = __popcll(peers & ((1ull << lane) - 1ull));
+    const int sofar = mine[digit];   // the wave's LDS accesses complete in order: all lanes read, then the first of each digit adds
+    __builtin_amdgcn_wave_barrier();
+    if (valid && lower == 0) mine[digit] = (uint16_t)(sofar + __popcll(peers));
+    __builtin_amdgcn_wave_barrier();
+    rank[i] = sofar + lower;
+  }
+  int mine_total = 0;
+#pragma unroll
+  for (int j = 0; j < DPT; ++j) mine_total += total[j];
+  int all;
+  int base = block_exclusive_scan<WAVES>(mine_total, &all, scan_smem);   // and every wave has counted its digits
+#pragma unroll
+  for (int j = 0; j < DPT; ++j)
+    if (owner) {
+      int count = 0;
+#pragma unroll
+      for (int w = 0; w < WAVES; ++w) {
+        const int c = wave_cnt[w * radix + d0 + j];
+        wave_cnt[w * radix + d0 + j] = (uint16_t)count;
+        count += c;
+      }
+      digit_off[d0 + j] = base + before[j];
+      base += total[j];
+    }
+  __syncthreads();
+  int32_t *keys_out = p.keys[(pass + 1) & 1];
+  int32_t *vals_out = p.vals[(pass + 1) & 1];
+#pragma unroll
+  for (int i = 0; i < kSortItems; ++i)
+    if (first + i * kWave < p.n) {
+      const int digit = (key[i] >> shift) & (radix - 1);
+      const int pos = digit_off[digit] + mine[digit] + rank[i];
+      keys_out[pos] = key[i];
+      vals_out[pos] = val[i];
+      if constexpr (VIEWS) {
+        args.plan.row_view[pos] = view[i];
+        args.plan.row_scale[pos] = 1.0f / scale[i];
+      }
+    }
+}
+
 // ---- segments of the sorted keys and the plan of the windowed accumulation -------------------------------
 // Section 1, third point: the gradients of one image are collected until M have arrived, then
 // averaged.  With c gradients already collected in earlier steps, the occurrence at in-step rank r
@@ -284,7 +445,8 @@ __device__ __forceinline__ void radix_pass_any(const GroupBatch &gb, int list, i
 // A thread owns the eight consecutive positions tile0 + 8 t .. + 7.  All loads that do not depend on each other are
 // requested together and none is behind a branch; the chain is ticket -> keys -> counters, start and end of the
 // segments that cross the tile's borders -> flags -> look-back -> descriptors.
-template <bool PLAN>
+// VIEWS: and where each occurrence's gradient lives, unless the last pass has left that.
+template <bool PLAN, bool VIEWS>
 __device__ __forceinline__ void segments(const GroupBatch &gb, const PlanArgs &args, int block, int32_t *failed) {
   const bool idle = *failed != 0;
   const GroupProblem &p = gb.p[gb.count - 1];
@@ -326,7 +488,7 @@ __device__ __forceinline__ void segments(const GroupBatch &gb, const PlanArgs &a
   }
   const int key_before = q0 > 0 && q0 < n ? sk[q0 - 1] : -1;
   int view[kSortItems], far_key[kSortItems], cnt[kSortItems];
-  if constexpr (PLAN) {
+  if constexpr (PLAN && VIEWS) {
     if (whole) {
       const int4 a = *reinterpret_cast<const int4 *>(p.perm + q0), b = *reinterpret_cast<const int4 *>(p.perm + q0 + 4);
       view[0] = a.x, view[1] = a.y, view[2] = a.z, view[3] = a.w, view[4] = b.x, view[5] = b.y, view[6] = b.z, view[7] = b.w;
@@ -334,12 +496,16 @@ __device__ __forceinline__ void segments(const GroupBatch &gb, const PlanArgs &a
 #pragma unroll
       for (int i = 0; i < kSortItems; ++i) view[i] = p.perm[min(q0 + i, (int64_t)n - 1)];
     }
+  }
+  if constexpr (PLAN) {
 #pragma unroll
     for (int i = 0; i < kSortItems; ++i) far_key[i] = sk[min(q0 + i + M - 1, (int64_t)n - 1)];
     __builtin_amdgcn_sched_barrier(0);   // requests stay in flight, their addresses need not
 #pragma unroll
     for (int i = 0; i < kSortItems; ++i) cnt[i] = counts[key[i]];
     __builtin_amdgcn_sched_barrier(0);
+  }
+  if constexpr (PLAN && VIEWS) {
 #pragma unroll
     for (int i = 0; i < kSortItems; ++i) view[i] = occ_view[view[i]];
     __builtin_amdgcn_sched_barrier(0);
@@ -427,7 +593,7 @@ __device__ __forceinline__ void segments(const GroupBatch &gb, const PlanArgs &a
     for (int c = 0; c < 3; ++c)
       publish(state + 3 * (size_t)tile + c, tile == 0 ? kPrefix | (uint32_t)own[c] : 1u + (uint32_t)own[c]);
 
-  if constexpr (PLAN) {
+  if constexpr (PLAN && VIEWS) {
     // where the occurrence's gradient lives: dLoss/dx of its view, divided by the view's image count
     float scale[kSortItems];
 #pragma unroll
@@ -544,7 +710,7 @@ __device__ __forceinline__ void segments(const GroupBatch &gb, const PlanArgs &a
 __device__ __forceinline__ void side_work(const SideTask &t, int block, unsigned char *lds) {
   if (t.kind == SideTask::kSegments) {
     const int n = t.gb.p[t.gb.count - 1].n;
-    if (block < max(1, (int)(((int64_t)n + kSortTile - 1) / kSortTile))) segments<true>(t.gb, t.plan, block, t.failed);
+    if (block < max(1, (int)(((int64_t)n + kSortTile - 1) / kSortTile))) segments<true, true>(t.gb, t.plan, block, t.failed);
     return;
   }
   const bool idle = *t.failed != 0;

@@ -51,7 +51,7 @@ __device__ __forceinline__ void put_packed(T *dst, int N, int K, int row, int k0
 
 template <typename T, bool PACKED>
 __global__ void __launch_bounds__(256) k_begin(BeginArgs args, int32_t *status, int32_t *failed, int32_t *n_ready, float *loss) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
+  if (blockIdx.x == 0 && threadIdx.x == 0 && status) {
     *status = 0;
     *failed = 0;
     *n_ready = 0;

@@ -627,6 +627,11 @@ bool plan_long(const Layout &lay, int dt, int B, int nnz, double stream, size_t 
   if (B > round && !(bf16 && plan->rows == 64 && lay.L == 2 && lds <= 64 * 1024 && B <= 20480)) return false;
   plan->lds = (int)lds;
   plan->room = 0;
+  // The sorts beside the blocks find a workgroup's LDS free on every CU, or they would wait for a block to end: digits as wide as
+  // fit in what the blocks leave (LDS is given out in pieces of 1280 bytes).
+  const long long block = (lds + 1024 + 1279) / 1280 * 1280, free = 160 * 1024 - block * (plan->rows == 32 && 2 * block <= 160 * 1024 ? 2 : 1);
+  plan->digit_bits = kCountedDigitBits;
+  while (plan->digit_bits > 8 && counted_lds_bytes(plan->digit_bits) > free) --plan->digit_bits;
   plan->blocks = (B + plan->rows - 1) / plan->rows;
   if (2 * (size_t)plan->blocks * (lay.in_dim[lay.L - 1] + 1) * sizeof(float) > lay.tickets - lay.loss_partial) return false;
   size_t sums = 0;   // where the layers leave theirs, or behind the digit totals of the sorts

@@ -47,6 +47,7 @@ __host__ __device__ inline int rows_split(int rows, int owners) {
 struct RowsPlan {
   int rows, blocks;                    // views of a block; blocks of the batch
   int lds, room;                       // bytes of LDS; items of the sorts in them
+  int digit_bits;                      // of the sorts that run beside
   int parts_log2[kMaxProblems];        // of the lists of ids (local_group.hpp)
   int value_bits[kMaxProblems];
   size_t colsum;                       // workspace offset of the column sums of the deltas below the last

@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 import torch
 
-from step_forms import form_of_launches
+from step_forms import form_of_launches, launches_of
 from test_gpu_tiles import beside_the_oracle
 
 pytestmark = pytest.mark.gpu
@@ -224,6 +224,41 @@ def test_which_steps_go_in_blocks(dtype, batch, each, layers, D, form):
         n = int(st.n_ready.item())
         results.append([t.clone() for t in (st.loss, st.n_ready, st.ready_ids[:n], st.ready_grads[:n], st.grad_accum, st.counts,
                                             st.user_emb, st.url_emb, st.mlp_params)])
+    for a, b in zip(*results):
+        assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("dtype,batch,images,n_users,n_urls,n_images", [
+    ("bf16", 16_384, 2, 1, 1 << 10, (1 << 10) + 1),              # digits of one bit, of ten, of six; eight whole tiles
+    ("bf16", 14_337, 3, (1 << 20) + 1, 1 << 20, 1 << 20),        # a tile of one key; three passes beside two
+    ("bf16", 12_289, 4, 1 << 24, 1 << 9, 1 << 24),               # the images last
+    ("bf16", 1_200, 90, 300, 40, 700),                           # lists of one tile, of twenty-seven
+    ("f32", 16_384, 9, 1 << 18, (1 << 18) + 1, 1 << 9),          # digits of nine bits beside two blocks a CU; one pass, two and three
+])
+def test_sorts_of_counted_tiles_give_the_bits_of_those_that_look_back(dtype, batch, images, n_users, n_urls, n_images):
+    """Beside blocks tiles are counted ahead of every pass; on one stream the same lists are sorted by tiles that look back.
+    Half of all ids are one, so that whole tiles are."""
+    import paper_1806_03925_amd as g
+    from gear_inputs import PageViewSource
+    wl = wl_of(dtype, batch, (40, 1), 8, 40, max_images=images, n_users=n_users, n_urls=n_urls, n_images=n_images, M=3)
+    host = PageViewSource(wl).batch(0)
+    rng = np.random.default_rng(batch)
+    for ids in (host.user_id, host.url_id, host.img_id):
+        ids[rng.random(ids.size) < 0.5] = ids.max()
+    results = []
+    for one in (False, True):
+        st = g.GearState(g.config_for(wl), debug=True)
+        g.gear_init_tables(st)
+        g.gear_fill_normal(st.dfv_cache, wl.n_images, wl.dfv_dim, wl.seed, 3, wl.dfv_std)
+        st.one_stream = one
+        for step in range(2):
+            names = launches_of(st, g.DeviceBatch.from_host(host), wl.M, 0.1)
+            assert int(st.status.item()) == 0 and (form_of_launches(names) == "long blocks") == (not one)
+        n = int(st.n_ready.item())
+        results.append([t.clone() for t in (st.loss, st.n_ready, st.ready_ids[:n], st.ready_grads[:n], st.grad_accum, st.counts,
+                                            st.user_emb, st.url_emb, st.mlp_params)])
+    order = np.argsort(host.img_id, kind="stable")
+    assert np.array_equal(st.dbg[2][:host.nnz].cpu().numpy(), order)
     for a, b in zip(*results):
         assert torch.equal(a, b)
 
