@@ -593,8 +593,9 @@ constexpr int kStateSpan = 96;     // words of three per part, then a ticket
 
 // A step whose ids are sorted in launches of their own (api.hip), on two streams.  Lines by measurement (us a step; blocks of
 // views against layer by layer; three images a view unless it says otherwise):
-// - Rows of a block: fp32 32.  bf16 32 to 12 288 views, then 64, one workgroup a CU, where 32 read the weights twice as often
-//   (576 -> 512 -> 256, eight images a view: 64 views a block at 9000 130, 32 at 16 384 177).
+// - Rows of a block: fp32 32.  bf16 32 to 8192 views, then 64, one workgroup a CU, where 32 read the weights twice as often
+//   (576 -> 512 -> 256, eight images a view, of 32 / 64: 9000 125.4 / 122.8, 12 288 135 / 132.5; 384 -> 384 -> 384: 9000 121.8 / 117.9; 640 ->
+//   256 -> 128: 8200 126.6 / 123.7), unless 64 do not fit or gather in two loads (below) and 32 do.
 // - One round: a CU holds two blocks of 32 views whose activations leave room, else one, and one of 64 (1024 -> 256 bf16, 80 KB
 //   and so 8192 views, eight images: 6000 131 / 137, 10 000 178 / 169; 576 -> 512 -> 256: 14 000 134 / 150, 16 384 139 / 160,
 //   18 000 180 / 173; 448 -> 384 -> 384: 16 384 132 / 146, 18 000 167 / 156).  A second round of 64-view blocks pays for one narrow
@@ -618,12 +619,14 @@ bool plan_long(const Layout &lay, int dt, int B, int nnz, double stream, size_t 
   const bool bf16 = dt == GEAR_BF16;
   if (nnz > 96ll * B) return false;
   if (bf16 ? stream > 1.5e6 + 420.0 * B : stream > 1e6 || B < (stream > 2e5 ? 14336 : 12288)) return false;
-  plan->rows = bf16 && B > 12288 ? 64 : 32;
+  const bool two_loads = lay.L > 3 && row_bytes > kWave * 16;
   RowsArgs a;
+  plan->rows = bf16 && B > 8192 ? 64 : 32;
+  if (plan->rows == 64 && B <= 12288 && (two_loads || place_buffers(lay, dt, 64, &a) + 1024 > 160 * 1024)) plan->rows = 32;
   const long long lds = place_buffers(lay, dt, plan->rows, &a);
   if (lds + 1024 > 160 * 1024) return false;
   const int round = 256 * plan->rows * (plan->rows == 32 && lds + 1024 <= 80 * 1024 ? 2 : 1);
-  if (plan->rows == 64 && lay.L > 3 && row_bytes > kWave * 16) return false;
+  if (plan->rows == 64 && two_loads) return false;
   if (B > round && !(bf16 && plan->rows == 64 && lay.L == 2 && lds <= 64 * 1024 && B <= 20480)) return false;
   plan->lds = (int)lds;
   plan->room = 0;
