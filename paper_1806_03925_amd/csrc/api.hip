@@ -596,6 +596,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
     return GEAR_OK;
   }
   int32_t *occ_view = (int32_t *)(ws + lay.occ_view);
+  const int E2 = 2 * cfg->emb_dim;   // columns of the embedding slots
 
   // On one stream the launches of the forward pass carry the grouping along where they can (gemm_tile.hip); with two, the
   // helper stream has it.
@@ -636,6 +637,19 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   const bool local_sort = by_rows && is_short, counted = by_rows && !is_short;
   const bool one_stream = out->one_stream != 0 || local_sort || (moderate && is_short);
   const bool carried = one_stream && moderate && !by_rows;
+  // Layer by layer, weights that are operands of products on the large tiles lie in those tiles' order (gemm.hip): the forward
+  // product's copy, and the transpose but for the rows of the embedding slots where dLoss/dx is made in two products.
+  bool w_tiles[GEAR_MAX_LAYERS] = {};
+  int wt_tiles_from[GEAR_MAX_LAYERS];
+  for (int l = 0; l < L; ++l) wt_tiles_from[l] = INT32_MAX;
+  for (int l = 0; l < L - 1 && !by_rows && !carried; ++l) {
+    const int in = lay.in_dim[l], width = lay.out_dim[l];
+    if (in % 32 || width % 32) continue;
+    w_tiles[l] = gemm_nt_takes_tiles(dt, B, width, in, EPI_BIAS_RELU);
+    const int from = l == 0 && long_dx ? E2 : 0;
+    if (from % 32 == 0 && gemm_nt_takes_tiles(dt, B, in - from, width, l == 0 ? EPI_DX : EPI_MASK_BITS)) wt_tiles_from[l] = from;
+  }
+
   // grouping of the three id lists and the plan of the per-image accumulation
   GroupBatch gb;
   {
@@ -685,7 +699,8 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
     CastJob jobs[GEAR_MAX_LAYERS];
     const int n_jobs = by_rows ? L - 1 : L;   // the logit layer is one row, which rows.hip takes from the parameters
     for (int l = 0; l < n_jobs; ++l)
-      jobs[l] = CastJob{t->mlp_params + lay.w_off[l], ws + lay.wc[l], ws + lay.wct[l], lay.out_dim[l], lay.in_dim[l]};
+      jobs[l] = CastJob{t->mlp_params + lay.w_off[l], ws + lay.wc[l], ws + lay.wct[l], lay.out_dim[l], lay.in_dim[l],
+                        !by_rows && w_tiles[l], by_rows ? INT32_MAX : wt_tiles_from[l]};
     ZeroList zero;
     zero.count = 0;
     if (local_sort)
@@ -738,7 +753,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   for (int l = 0; l < L - 1 && !by_rows; ++l) {
     GEAR_RUN(kFwd[l], launch_gemm_nt(dt, l == 0 ? x : ws + lay.h[l - 1], ws + lay.wc[l], B, lay.out_dim[l],
                                      lay.in_dim[l], EPI_BIAS_RELU, t->mlp_params + lay.b_off[l], nullptr,
-                                     ws + lay.h[l], 0, nullptr, relu_bits[l], nullptr, s, false, passenger()));
+                                     ws + lay.h[l], 0, nullptr, relu_bits[l], nullptr, s, false, passenger(), w_tiles[l]));
   }
   // The helper stream's launches are issued after the forward pass's: where the host is not ahead of the
   // device (a caller that waits for every step), the gather then starts as soon as the step does, not
@@ -806,14 +821,13 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
                                          by_bits ? EPI_MASK_BITS : EPI_MASK, nullptr,
                                          by_bits ? (const void *)relu_bits[l - 1] : (const void *)(ws + lay.h[l - 1]),
                                          ws + lay.delta[l - 1], 0, as_rows ? nullptr : cpart + lay.colsum_at[l], nullptr, nullptr, s,
-                                         lay.colsum_coarse));
+                                         lay.colsum_coarse, nullptr, wt_tiles_from[l] == 0));
     } else {
       // dLoss/dx: the embedding slots stay fp32, the DFV slot is kept in the MLP's operand type.
       // When the product is long enough to hide it, it is made in two parts: the embedding slots
       // first, and as soon as they are there the SGD on the touched embedding rows starts on the
       // helper stream, beside the larger product that makes the DFV slot.  Every element is computed
       // the same way in both forms.
-      const int E2 = 2 * cfg->emb_dim;
       if (long_dx) {
         GEAR_RUN("dgrad_gemm_emb", launch_gemm_nt(dt, ws + lay.delta[0], ws + lay.wct[0], B, E2, lay.out_dim[0], EPI_DX,
                                                   nullptr, dx_dfv, dx_emb, E2, nullptr, nullptr, nullptr, s));
@@ -827,12 +841,13 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
         divided = true;
         GEAR_RUN(kDgrad[0], launch_gemm_nt(dt, ws + lay.delta[0],
                                            ws + lay.wct[0] + (size_t)E2 * lay.out_dim[0] * lay.act_bytes, B, F - E2,
-                                           lay.out_dim[0], EPI_DX, nullptr, dx_dfv, dx_emb, 0, nullptr, nullptr, nullptr, s));
+                                           lay.out_dim[0], EPI_DX, nullptr, dx_dfv, dx_emb, 0, nullptr, nullptr, nullptr, s, false, nullptr,
+                                           wt_tiles_from[0] == E2));
       } else {
         const bool takes = gemm_nt_carries(dt, B, F, lay.out_dim[0]);
         GEAR_RUN(kDgrad[0], launch_gemm_nt(dt, ws + lay.delta[0], ws + lay.wct[0], B, F, lay.out_dim[0], EPI_DX,
                                            nullptr, dx_dfv, dx_emb, E2, nullptr, nullptr, nullptr, s, false,
-                                           takes ? passenger() : nullptr));
+                                           takes ? passenger() : nullptr, wt_tiles_from[0] == 0));
         if (gear_status st = links_left()) return st;
       }
     }

@@ -301,6 +301,10 @@ struct CastJob {
   const float *w;
   void *wc, *wct;
   int rows, cols;
+  // bf16, not `packed`: W in the operand order of the large tiles (gemm.hip), and so its transpose from that row on (a multiple of
+  // 32; INT32_MAX: row-major)
+  bool tiles;
+  int tiles_from;
 };
 hipError_t launch_clear(const ZeroList &zero, hipStream_t s);
 // (status NULL: the outputs are cleared elsewhere)
@@ -356,7 +360,9 @@ enum GemmEpilogue {
 hipError_t launch_gemm_nt(int dtype, const void *A, const void *B, int M, int N, int K, int epilogue,
                           const float *bias, const void *aux, void *out, int split, float *colpart,
                           uint8_t *relu_bits, const int32_t *status, hipStream_t s, bool coarse = false,
-                          const SideTask *side = nullptr);
+                          const SideTask *side = nullptr, bool tiles = false);
+// whether such a product without a SideTask takes B in the operand order of the large tiles (`tiles`)
+bool gemm_nt_takes_tiles(int dtype, int M, int N, int K, int epilogue);
 bool gemm_nt_carries(int dtype, int M, int N, int K);   // whether a bias + ReLU or dLoss/dx product of this shape takes a SideTask
 int gemm_nt_colsum_parts(int dtype, int M, int N, int K, bool coarse);
 // partial_i[z][M_i x N_i] = sum over the z-th of `splits` ranges of the K rows of A_i[K x M_i]^T * B_i[K x N_i], for

@@ -10,7 +10,8 @@
 // are copied global -> LDS by DMA (global_load_lds_dwordx4) into four stages.  NT form: two k-tiles
 // are copied together while the two before them are multiplied (the halves of a 128-byte line then
 // meet in the vector cache), one wait and one s_barrier per pair; LDS rows are [row][32 k] with the
-// four 16-byte k-pieces XOR-swizzled by the row so that ds_read_b128 operand fetches do not conflict.
+// four 16-byte k-pieces XOR-swizzled by the row so that ds_read_b128 operand fetches do not conflict.  The weights of a step
+// come in operand order instead, straight into registers (nt_main_loop_packed).
 // TN form (wgrad): one k-tile per barrier, two in flight; LDS keeps the global [k][row] order and
 // ds_read_b64_tr_b16 assembles the operand.
 // bf16 results leave through a per-wave LDS patch so that every lane stores 16 contiguous bytes.
@@ -42,7 +43,7 @@ struct NtWide {
 struct NtNarrow {
   static constexpr int BN = 128, STAGES = 6, AHEAD = 2, TMW = 2, WAVES_N = 2;
 };
-template <typename C> constexpr int stage_elems() { return A_ELEMS + C::BN * DK; }
+template <typename C, bool PB = false> constexpr int stage_elems() { return A_ELEMS + (PB ? 0 : C::BN * DK); }
 // global_load_lds instructions a wave issues per pair of k-tiles: 16 rows of A twice, 16 rows of B per 128, two k-tiles
 template <typename C> constexpr int dma_per_pair() { return 2 * (2 + C::BN / 128); }
 
@@ -131,6 +132,37 @@ __device__ __forceinline__ void mma_stage(f32x16_v (&acc)[TM][TN], uint32_t a_ad
   MFMA_BF16_T(acc[3][1], r3, s1);
 }
 
+// The same with the B operand in registers: b[k-step][n-tile].
+__device__ __forceinline__ void mma_stage_packed(f32x16_v (&acc)[TM][TN], uint32_t a_addr0, uint32_t a_addr1, const u32x4_v (&b)[2][TN]) {
+  u32x4_v p0, p1, p2, p3, r0, r1, r2, r3;
+  LDS_READ16(p0, a_addr0, 0);
+  LDS_READ16(p1, a_addr0, 2048);
+  LDS_READ16(p2, a_addr0, 4096);
+  LDS_READ16(p3, a_addr0, 6144);
+  LDS_READ16(r0, a_addr1, 0);
+  LDS_READ16(r1, a_addr1, 2048);
+  LDS_READ16(r2, a_addr1, 4096);
+  LDS_READ16(r3, a_addr1, 6144);
+  asm volatile("s_waitcnt lgkmcnt(4)" : "+v"(p0), "+v"(p1), "+v"(p2), "+v"(p3)::"memory");
+  MFMA_BF16_T(acc[0][0], p0, b[0][0]);
+  MFMA_BF16_T(acc[0][1], p0, b[0][1]);
+  MFMA_BF16_T(acc[1][0], p1, b[0][0]);
+  MFMA_BF16_T(acc[1][1], p1, b[0][1]);
+  MFMA_BF16_T(acc[2][0], p2, b[0][0]);
+  MFMA_BF16_T(acc[2][1], p2, b[0][1]);
+  MFMA_BF16_T(acc[3][0], p3, b[0][0]);
+  MFMA_BF16_T(acc[3][1], p3, b[0][1]);
+  asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(r0), "+v"(r1), "+v"(r2), "+v"(r3)::"memory");
+  MFMA_BF16_T(acc[0][0], r0, b[1][0]);
+  MFMA_BF16_T(acc[0][1], r0, b[1][1]);
+  MFMA_BF16_T(acc[1][0], r1, b[1][0]);
+  MFMA_BF16_T(acc[1][1], r1, b[1][1]);
+  MFMA_BF16_T(acc[2][0], r2, b[1][0]);
+  MFMA_BF16_T(acc[2][1], r2, b[1][1]);
+  MFMA_BF16_T(acc[3][0], r3, b[1][0]);
+  MFMA_BF16_T(acc[3][1], r3, b[1][1]);
+}
+
 constexpr int STAGES = 4;                       // of the TN kernel below
 
 // Tiles t and t + 1 (t even) are copied together into stages t % S and (t + 1) % S while the pairs
@@ -166,13 +198,76 @@ __device__ __forceinline__ void nt_main_loop(f32x16_v (&acc)[C::TMW][TN], const 
   }
 }
 
-template <int EPI, typename C = NtWide>
+// B (the weights of a step) in operand order (prep.hip: 1 KB for every 32 rows and 16 k, a lane's sixteen bytes together): a
+// wavefront's operand is one contiguous load into registers and never passes through LDS; the k-tile after next is requested
+// when a k-tile's products are done.  What bounds the form with both operands in LDS is LDS itself: 128 KB pass through it per
+// k-tile, 1024 cycles of its 128 bytes, which is what the k-tile's products take; here it is 80 KB.  Four DMA copies of A and
+// eight loads of B per pair, always issued in that order (past the end the last tile's again): with eight operations outstanding
+// the pair's share of A has landed.  Buffer accesses throughout, which the compiler counts one by one: beside global_load_lds it
+// waits for all of them.  us, through LDS / so: 65 536 x 1024 x 1152 bias + ReLU 173 / 150 (1.03 PFLOP/s), x 1024 x 1024 dLoss/dx
+// 140 / 127, x 1024 x 256 masked 68 / 64.5, x 256 x 1024 42 / 42.5; a step of that network 963 / 939.  Eight stages of A instead
+// of four, two pairs ahead: 156 / 131 / 66.
+template <bool MMA>
+__device__ __forceinline__ void nt_main_loop_packed(f32x16_v (&acc)[TM][TN], const bf16_t *__restrict__ A, const bf16_t *__restrict__ B,
+                                                    const DmaPlan &plan, bf16_t *lds, int nk, int wave, const uint32_t (&a_rel)[2],
+                                                    int m0, int b_row, int M, int N, int K, int lane) {
+  constexpr int SE = stage_elems<NtWide, true>();
+  const auto a_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(A) + (size_t)m0 * K, 0, min(DM, M - m0) * K * 2, 0x00020000);
+  int a_at[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) a_at[i] = (int)(plan.a_off[i] - (size_t)m0 * K) * 2;
+  const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(B), 0, N * K * 2, 0x00020000);   // rows beyond N read as zero
+  int b_at[TN];
+#pragma unroll
+  for (int j = 0; j < TN; ++j) b_at[j] = (b_row / 32 + j) * (K / 16) * 1024 + lane * 16;
+  u32x4_v b[2][2][TN];
+  auto load = [&](u32x4_v (&to)[2][TN], int t) {
+    const int at = min(t, nk - 1) * 2048;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+        if constexpr (MMA) to[ks][j] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, b_at[j], at + ks * 1024, 0);
+    asm volatile("" ::: "memory");
+  };
+  auto copy = [&](int t) {
+    const int k0 = min(t, nk - 1) * DK * 2, k1 = min(t + 1, nk - 1) * DK * 2;
+    bf16_t *s0 = lds + (t & 3) * SE, *s1 = lds + ((t + 1) & 3) * SE;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lds_ptr_t)(s0 + (i * 8 + wave) * 512), 16, a_at[i], k0, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lds_ptr_t)(s1 + (i * 8 + wave) * 512), 16, a_at[i], k1, 0, 0);
+    }
+    asm volatile("" ::: "memory");
+  };
+  copy(0);
+  load(b[0], 0);
+  load(b[1], 1);
+  for (int t = 0; t < nk; t += 2) {
+    if constexpr (MMA)
+      wait_vm<8>();
+    else
+      wait_vm<0>();
+    block_barrier();
+    copy(t + 2);
+    const uint32_t so = (uint32_t)(t & 3) * (2u * SE);
+    if constexpr (MMA) mma_stage_packed(acc, a_rel[0] + so, a_rel[1] + so, b[0]);
+    load(b[0], t + 2);
+    if (t + 1 < nk) {
+      if constexpr (MMA) mma_stage_packed(acc, a_rel[0] + so + 2u * SE, a_rel[1] + so + 2u * SE, b[1]);
+    }
+    load(b[1], t + 3);
+  }
+}
+
+template <int EPI, typename C = NtWide, bool PB = false>
 __global__ void __launch_bounds__(DTHREADS)
 k_gemm_nt_dma(const bf16_t *__restrict__ A, const bf16_t *__restrict__ B, int M, int N, int K,
               const float *__restrict__ bias, const bf16_t *__restrict__ aux, void *__restrict__ out, int split,
               float *__restrict__ colpart, uint8_t *__restrict__ relu_bits, const int32_t *__restrict__ status) {
   if (status && *status != 0) return;
-  __shared__ __attribute__((aligned(1024))) bf16_t lds[C::STAGES * stage_elems<C>()];   // [stage][A tile | B tile]
+  static_assert(!PB || std::is_same_v<C, NtWide>, "the narrow shape reads B through LDS");
+  __shared__ __attribute__((aligned(1024))) bf16_t lds[C::STAGES * stage_elems<C, PB>()];   // [stage][A tile | B tile]
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   constexpr int TMW = C::TMW, WMW = 32 * C::TMW;   // this shape's wave tile: WMW rows x WN columns
@@ -237,13 +332,18 @@ k_gemm_nt_dma(const bf16_t *__restrict__ A, const bf16_t *__restrict__ B, int M,
   // in a tile whose right part lies beyond N, the waves without columns copy tiles and meet the
   // barriers but skip the operand reads and the products
   const bool has_columns = n0 + wn * WN < N;
-  if (has_columns)
+  if constexpr (PB) {
+    if (has_columns)
+      nt_main_loop_packed<true>(acc, A, B, plan, lds, K / DK, wave, a_rel, m0, n0 + wn * WN, M, N, K, lane);
+    else
+      nt_main_loop_packed<false>(acc, A, B, plan, lds, K / DK, wave, a_rel, m0, n0 + wn * WN, M, N, K, lane);
+  } else if (has_columns)
     nt_main_loop<true, C>(acc, A, B, plan, lds, K / DK, wave, a_rel, b_rel);
   else
     nt_main_loop<false, C>(acc, A, B, plan, lds, K / DK, wave, a_rel, b_rel);
   wait_vm<0>();
   block_barrier();  // every wave is done with the operand tiles: the first stages become the output patches
-  static_assert((8 * 32 * PATCH_LD) * 2 + 8 * 64 * 4 <= C::STAGES * stage_elems<C>() * 2, "patches and column sums fit");
+  static_assert((8 * 32 * PATCH_LD) * 2 + 8 * 64 * 4 <= C::STAGES * stage_elems<C, PB>() * 2, "patches and column sums fit");
   bf16_t *patch = lds + wave * 32 * PATCH_LD;
   float colacc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   if (has_columns)
@@ -491,22 +591,37 @@ int gemm_nt_colsum_parts(int dtype, int M, int N, int K, bool coarse) {
   return nt_dma(dtype, M, N, K, false) ? (M + DM - 1) / DM : nt_tile_colsum_parts(dtype, M, N, coarse);
 }
 
+bool gemm_nt_takes_tiles(int dtype, int M, int N, int K, int epi) {
+  const bool narrow = N <= NtNarrow::BN && (epi == EPI_DX || epi == EPI_F32);
+  return !narrow && N % 32 == 0 && (long long)N * K < (1ll << 30) && K < (1 << 21) && nt_dma(dtype, M, N, K, false);
+}
+
 bool gemm_nt_carries(int dtype, int M, int N, int K) { return !nt_fills(dtype, M, N, K, false); }
 
 hipError_t launch_gemm_nt(int dtype, const void *A, const void *B, int M, int N, int K, int epi, const float *bias,
                           const void *aux, void *out, int split, float *colpart, uint8_t *relu_bits,
-                          const int32_t *status, hipStream_t s, bool coarse, const SideTask *side) {
+                          const int32_t *status, hipStream_t s, bool coarse, const SideTask *side, bool tiles) {
   if (M <= 0 || N <= 0) return hipSuccess;
+  if (tiles && (side || !gemm_nt_takes_tiles(dtype, M, N, K, epi))) return hipErrorInvalidValue;
   if (epi == EPI_MASK_BITS && dtype != GEAR_BF16) return hipErrorInvalidValue;
   const bool narrow = N <= NtNarrow::BN && (epi == EPI_DX || epi == EPI_F32);
   if (side ? !nt_fills(dtype, M, N, K, narrow) : !nt_dma(dtype, M, N, K, narrow))
     return launch_gemm_nt_tile(dtype, A, B, M, N, K, epi, bias, aux, out, split, colpart, relu_bits, status, s, coarse, side);
   if (side) return hipErrorInvalidValue;
   const dim3 grid(((M + DM - 1) / DM) * (narrow ? 1 : (N + DN - 1) / DN));
-#define GEAR_DMA(E, C)                                                                                                \
-  hipLaunchKernelGGL((k_gemm_nt_dma<E, C>), grid, dim3(DTHREADS), 0, s, (const bf16_t *)A, (const bf16_t *)B, M, N, K, \
+#define GEAR_DMA(E, ...)                                                                                              \
+  hipLaunchKernelGGL((k_gemm_nt_dma<E, __VA_ARGS__>), grid, dim3(DTHREADS), 0, s, (const bf16_t *)A, (const bf16_t *)B, M, N, K, \
                      bias, (const bf16_t *)aux, out, split, colpart, relu_bits, status)
-  if (epi == EPI_BIAS_RELU)
+  if (tiles) {
+    if (epi == EPI_BIAS_RELU)
+      GEAR_DMA(EPI_BIAS_RELU, NtWide, true);
+    else if (epi == EPI_MASK_BITS)
+      GEAR_DMA(EPI_MASK_BITS, NtWide, true);
+    else if (epi == EPI_DX)
+      GEAR_DMA(EPI_DX, NtWide, true);
+    else
+      return hipErrorInvalidValue;
+  } else if (epi == EPI_BIAS_RELU)
     GEAR_DMA(EPI_BIAS_RELU, NtWide);
   else if (epi == EPI_MASK)
     GEAR_DMA(EPI_MASK, NtWide);

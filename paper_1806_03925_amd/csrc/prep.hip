@@ -49,6 +49,17 @@ __device__ __forceinline__ void put_packed(T *dst, int N, int K, int row, int k0
   }
 }
 
+// Operand order of the large tiles (gemm.hip): 1 KB for every 32 rows and 16 k, of which lane (g, r) has the 16 bytes of row r, k = 8 g .. + 7.
+// `piece`: eight of the 32 k from k0 on.
+template <typename Get>
+__device__ __forceinline__ void put_tiles(bf16_t *dst, int K, int row0, int r, int k0, int piece, Get get) {
+  uint32_t w[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    w[e] = (uint32_t)from_f32<bf16_t>(get(8 * piece + 2 * e)) | ((uint32_t)from_f32<bf16_t>(get(8 * piece + 2 * e + 1)) << 16);
+  *reinterpret_cast<uint4 *>(dst + (size_t)row0 * K + (k0 / 16 + piece / 2) * 512 + ((piece & 1) * 32 + r) * 8) = make_uint4(w[0], w[1], w[2], w[3]);
+}
+
 template <typename T, bool PACKED>
 __global__ void __launch_bounds__(256) k_begin(BeginArgs args, int32_t *status, int32_t *failed, int32_t *n_ready, float *loss) {
   if (blockIdx.x == 0 && threadIdx.x == 0 && status) {
@@ -72,6 +83,7 @@ __global__ void __launch_bounds__(256) k_begin(BeginArgs args, int32_t *status, 
   T *__restrict__ wct = static_cast<T *>(args.job[which].wct);
   const int local = blockIdx.x - args.first_block[which], col_tiles = (cols + 31) / 32;
   const int c0 = (local % col_tiles) * 32, r0 = (local / col_tiles) * 32;
+  const bool tiles = !PACKED && args.job[which].tiles, tiles_t = !PACKED && c0 >= args.job[which].tiles_from;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8
 #pragma unroll
   for (int rr = ty; rr < 32; rr += 8) {
@@ -79,7 +91,8 @@ __global__ void __launch_bounds__(256) k_begin(BeginArgs args, int32_t *status, 
     float v = 0.0f;
     if (r < rows && c < cols) {
       v = w[(size_t)r * cols + c];
-      if constexpr (!PACKED) wc[(size_t)r * cols + c] = from_f32<T>(v);
+      if constexpr (!PACKED)
+        if (!tiles) wc[(size_t)r * cols + c] = from_f32<T>(v);
     }
     tile[rr][tx] = v;
   }
@@ -92,6 +105,12 @@ __global__ void __launch_bounds__(256) k_begin(BeginArgs args, int32_t *status, 
     if (sizeof(T) == 4 || piece >= 4) put_packed(wct, cols, rows, c0 + at, r0, sizeof(T) == 4 ? piece : piece - 4, of_col);
     return;
   }
+  if constexpr (sizeof(T) == 2) {   // whole 32 x 32 tiles: the host asks for them of such matrices alone
+    const int piece = ty & 3;
+    if (tiles && ty < 4) put_tiles(wc, cols, r0, tx, c0, piece, [&](int k) { return tile[tx][k]; });
+    if (tiles_t && ty >= 4) put_tiles(wct, rows, c0, tx, r0, piece, [&](int k) { return tile[k][tx]; });
+  }
+  if (tiles_t) return;
 #pragma unroll
   for (int cc = ty; cc < 32; cc += 8) {
     const int c = c0 + cc, r = r0 + tx;
@@ -121,7 +140,10 @@ hipError_t launch_begin(int32_t *status, int32_t *failed, int32_t *n_ready, floa
   args.zero = zero;
   args.cast_blocks = 0;
   for (int i = 0; i < GEAR_MAX_LAYERS; ++i) {
-    args.job[i] = i < count ? jobs[i] : CastJob{nullptr, nullptr, nullptr, 0, 0};
+    args.job[i] = i < count ? jobs[i] : CastJob{nullptr, nullptr, nullptr, 0, 0, false, INT32_MAX};
+    if (!packed && i < count && (jobs[i].tiles || jobs[i].tiles_from < jobs[i].cols) &&
+        (dtype != GEAR_BF16 || jobs[i].rows % 32 || jobs[i].cols % 32 || (jobs[i].tiles_from < jobs[i].cols && jobs[i].tiles_from % 32)))
+      return hipErrorInvalidValue;
     args.first_block[i] = args.cast_blocks;
     if (i < count) args.cast_blocks += ((jobs[i].cols + 31) / 32) * ((jobs[i].rows + 31) / 32);
   }

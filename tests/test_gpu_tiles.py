@@ -106,3 +106,35 @@ def test_bf16_bits_do_not_depend_on_the_kernel(M, N, K):
         assert torch.equal(big[:rows], g.gear_gemm(a, B, 0, epilogue, **few))
         last = g.gear_gemm(A[-rows:].contiguous(), B, 0, epilogue, **(dict(aux=aux[-rows:].contiguous()) if epilogue == 1 else many))
         assert torch.equal(big[-rows:], last)
+
+
+@pytest.mark.parametrize("batch,layers,d,D", [
+    (65_540, (96, 32, 1), 16, 160),   # one, three and six k-tiles; 32, 96 and 192 columns; four rows in the last tile
+    (33_028, (288, 1), 16, 224),      # column tiles of 256 and 32
+    (65_536, (288, 1), 16, 288),      # dLoss/dx in two products, the transpose in tile order from row 32 on
+])
+def test_weights_in_the_order_of_large_tiles(batch, layers, d, D):
+    """The first quarter of the views as a step of its own takes other kernels, with weights in other orders: the same logits, and
+    dLoss/dx four times as large, which is exact (a mean over a quarter of the views)."""
+    import paper_1806_03925_amd as g
+    from gear_inputs import PageViewSource, get_workload
+    from gear_inputs.pageviews import PageViewBatch
+    wl = get_workload("tiny").scaled(batch=batch, layers=layers, emb_dim=d, dfv_dim=D, emb_dtype="bf16", dfv_dtype="bf16",
+                                     mlp_dtype="bf16", max_images=1)
+    full = PageViewSource(wl).batch(0)
+    B = batch // 4
+
+    def run(host):
+        st = g.GearState(g.config_for(wl))
+        g.gear_init_tables(st)
+        g.gear_fill_normal(st.dfv_cache, wl.n_images, wl.dfv_dim, wl.seed, 3, wl.dfv_std)
+        g.gear_step(st, g.DeviceBatch.from_host(host), wl.M, 0.1)
+        torch.cuda.synchronize()
+        assert int(st.status.item()) == 0
+        return st
+
+    whole = run(full)
+    part = run(PageViewBatch(user_id=full.user_id[:B], url_id=full.url_id[:B], img_off=full.img_off[:B + 1],
+                             img_id=full.img_id[:full.img_off[B]], label=full.label[:B]))
+    assert torch.equal(whole.region("logits", batch)[:B], part.region("logits", B))
+    assert torch.equal(4.0 * whole.region("dx", batch)[:B].float(), part.region("dx", B).float())
