@@ -116,8 +116,8 @@ TRAFFIC_KERNELS = {
     "fwd_gemm_l0": ([("k_gemm_nt_dma<0,", 2, 0)], ["gemm.hip"]),
     "fwd_gemm_l1": ([("k_gemm_nt_dma<0,", 2, 1)], ["gemm.hip"]),
     "dgrad_gemm_l1": ([("k_gemm_nt_dma<4,", 1, 0)], ["gemm.hip"]),   # masked by the sign bitmap
-    "dgrad_gemm_emb": ([("k_gemm_nt_dma<3, %sNtNarrow>" % _NS, 1, 0)], ["gemm.hip"]),   # the narrow tile shape
-    "dgrad_gemm_l0": ([("k_gemm_nt_dma<3, %sNtWide>" % _NS, 1, 0)], ["gemm.hip"]),
+    "dgrad_gemm_emb": ([("k_gemm_nt_dma<3, %sNtNarrow" % _NS, 1, 0)], ["gemm.hip"]),   # the narrow tile shape
+    "dgrad_gemm_l0": ([("k_gemm_nt_dma<3, %sNtWide" % _NS, 1, 0)], ["gemm.hip"]),
     "wgrad_gemm": ([("k_gemm_tn_dma_batch", 1, 0)], ["gemm.hip"]),
 }
 # launches whose matrix-pipe occupancy is reported (same part notation)

@@ -120,8 +120,7 @@ constexpr int kMaxRides = 3;                          // passes that other launc
 constexpr int kMaxDigitBits = 12;
 constexpr int kSideDigitBits = 11;                    // of passes that other launches carry
 constexpr int kCountedDigitBits = 10;                 // of passes whose tiles are counted ahead of them
-// ids from which a workgroup of the check takes several tiles and the segments take few registers, and images from which the
-// grouping of a step in blocks of views is on the caller's stream and the blocks on the helper's (api.hip)
+// ids from which a workgroup of the check takes several tiles and the segments take few registers
 constexpr int kLongList = 65536;
 // Counts a tile publishes over all passes, at most.  A pass costs a launch and two memory latencies whatever its
 // radix, so a list takes as few passes as its keys allow within this (one up to 12 bits, two up to 22, then three);

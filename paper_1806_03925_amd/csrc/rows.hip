@@ -504,7 +504,7 @@ __device__ __forceinline__ void rows_columns(const RowsArgs &p, unsigned char *l
 }
 
 // The first local.blocks workgroups group the ids.  Two workgroups of up to 32 views share a CU (kHalf below), so they have half
-// the registers; those of 64 have the CU to themselves but for the sorts of a long step, which take 102 to 116 registers
+// the registers; those of 64 have the CU to themselves but for the sorts of a long step, which take 96 registers
 // beside 191 (group.hip).  In fp32 with 32 views, a form of long steps only, 96 leave room for them too (hotkey 175.5 us a step, with 108 180).
 template <typename T, int MT>
 __global__ void __launch_bounds__(kRowsThreads, MT == 4 ? 2 : MT == 2 && sizeof(T) == 4 ? 5 : 4) k_rows(RowsArgs p, LocalTask local) {
