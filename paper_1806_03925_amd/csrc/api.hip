@@ -634,7 +634,11 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   // bits.  us a step on one stream, layers / blocks, 576 -> 512 -> 256 bf16: 9001 views 134 / 154, 12 288 148 / 165, 16 384 184 / 188;
   // 192 -> 128, 10 000 views 97 / 110; 96 -> 64 fp32, 16 384 106 / 127.  The sums are 1 to 4 of it.
   const bool by_rows = planned && (is_short || !out->one_stream), as_rows = planned && !by_rows;
-  const bool local_sort = by_rows && is_short, counted = by_rows && !is_short;
+  const bool local_sort = by_rows && is_short, long_rows = by_rows && !is_short;
+  // Every tile reads the counts of all, so very long lists go back to tiles that look back, and so do long ones of few views, whose
+  // blocks leave CUs idle (us a step, tiles that look back / counted, 576 -> 512 -> 256 bf16: 254 000 images of 16 384 views 227 / 220;
+  // 192 -> 128: 290 000 of 20 000 187.5 / 191.5, 795 000 of 16 384 278 / 355, 61 000 of 2000 112 / 119).
+  const bool counted = long_rows && b->nnz <= 128 * kSortTile && b->nnz <= 24ll * B;
   const bool one_stream = out->one_stream != 0 || local_sort || (moderate && is_short);
   const bool carried = one_stream && moderate && !by_rows;
   // Layer by layer, weights that are operands of products on the large tiles lie in those tiles' order (gemm.hip): the forward
@@ -655,7 +659,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   {
     int passes = 1;   // the lists share launches: as many passes for all as the widest ids need
     for (int i = 0; i < kMaxProblems; ++i) {
-      const int need = radix_passes(key_bits[i], lay.g[i].total_words, carried ? kSideDigitBits : widest_digit(B > b->nnz ? B : b->nnz));
+      const int need = radix_passes(key_bits[i], lay.g[i].total_words, carried ? kSideDigitBits : long_rows ? 9 : widest_digit(B > b->nnz ? B : b->nnz));
       if (need > passes) passes = need;
     }
     // a pass that is carried costs nothing but its length, and narrow digits make it short: as many as find a launch ahead
@@ -777,7 +781,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
       for (int pass = 0; pass < group_passes(gb); ++pass) GEAR_RUN("group_ids", launch_radix_pass(gb, pass, failed, s));
       GEAR_RUN("accum_plan", launch_segments(gb, &plan_args, failed, s));
     }
-    GEAR_HIP(counted ? lane.mark() : lane.mark_checked());
+    GEAR_HIP(long_rows ? lane.mark() : lane.mark_checked());
   }
 
   // Until its first kernel that changes caller state (the first SGD on a hidden layer's weights), the
@@ -872,7 +876,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
                                              divided ? nullptr : &emb, !books_here, as_rows ? &riding : nullptr, failed, s));
     return GEAR_OK;
   };
-  if (!beside && !counted) {
+  if (!beside && !long_rows) {
     if (gear_status st = bookkeeping(helper)) return st;
     GEAR_HIP(lane.mark());
   }
@@ -914,7 +918,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
     // stream waits for the helper's first part (long done by now), not for the bookkeeping.  Their
     // workgroups get onto the device as the bookkeeping's leave room and are done before it is, so the
     // step ends with the bookkeeping and the join.
-    if (first == 0 && counted) {
+    if (first == 0 && long_rows) {
       GEAR_HIP(lane.wait(true));
       if (gear_status st = bookkeeping(s)) return st;
     } else if (first == 0) {
