@@ -275,11 +275,11 @@ __global__ void __launch_bounds__(kSortBlock, 5) k_counted_pass(GroupBatch gb, i
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   __shared__ int scan_smem[8];
   const bool last = (int)blockIdx.y == gb.count - 1 && pass == p.passes - 1;
-#define GEAR_COUNTED(DPT)                                                          \
-  if (last)                                                                        \
-    counted_pass<DPT, true>(p, pass, blockIdx.x, args, failed, lds, scan_smem);    \
-  else                                                                             \
-    counted_pass<DPT, false>(p, pass, blockIdx.x, args, failed, lds, scan_smem)
+#define GEAR_COUNTED(DPT)                                                                  \
+  if (last)                                                                                \
+    counted_pass<DPT, true>(p, pass, blockIdx.x, views.B, args, failed, lds, scan_smem);   \
+  else                                                                                     \
+    counted_pass<DPT, false>(p, pass, blockIdx.x, views.B, args, failed, lds, scan_smem)
   if (p.digit_bits == 10) {
     GEAR_COUNTED(4);
   } else if (p.digit_bits == 9) {

@@ -311,7 +311,7 @@ __device__ __forceinline__ void count_tile(const GroupProblem &p, int pass, int 
 // A thread owns DPT consecutive digits: four where there are 1024, two of 512, else one.
 // VIEWS: the images' last pass, which also leaves where each occurrence's gradient lives.
 template <int DPT, bool VIEWS>
-__device__ __forceinline__ void counted_pass(const GroupProblem &p, int pass, int tile, const PlanArgs &args, int32_t *failed,
+__device__ __forceinline__ void counted_pass(const GroupProblem &p, int pass, int tile, int n_views, const PlanArgs &args, int32_t *failed,
                                              unsigned char *lds, int *scan_smem) {
   constexpr int WAVES = kSortBlock / kWave;
   const int radix = 1 << p.digit_bits, shift = pass * p.digit_bits;
@@ -377,6 +377,9 @@ __device__ __forceinline__ void counted_pass(const GroupProblem &p, int pass, in
   if constexpr (VIEWS) {
 #pragma unroll
     for (int i = 0; i < kSortItems; ++i) {
+      // Where the offsets are no CSR index, which a workgroup of this very launch may be the one to find, an occurrence can be
+      // without a view, and its word has whatever was there before: it must not become an address.
+      view[i] = (int)min((uint32_t)view[i], (uint32_t)n_views - 1u);
       const int32_t *off = args.img_off + view[i];
       scale[i] = (float)(off[1] - off[0]);
     }

@@ -310,6 +310,53 @@ def test_a_bad_id_or_offset_leaves_everything_as_it_was(what):
         assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("n_images", [1 << 10, 4_000])   # sorted in one pass, in the launch that checks the offsets, and in two
+@pytest.mark.parametrize("what", ["ends short", "begins late", "negative", "beyond"])
+def test_occurrences_that_no_view_owns(n_images, what):
+    """Offsets that are no CSR index leave words of the workspace as they were: whatever those hold, the step reports it and no
+    table, counter or ready list shows a trace; the next step has the bits of one on a state of its own."""
+    import paper_1806_03925_amd as g
+    from gear_inputs import PageViewSource
+    wl = wl_of("bf16", 9_001, (72, 40, 1), 24, 72, max_images=8, n_images=n_images, M=2)
+    good, bad = PageViewSource(wl).batch(0), PageViewSource(wl).batch(0)
+    if what == "ends short":
+        bad.img_off[:] = np.minimum(bad.img_off, bad.nnz - 5)
+    elif what == "begins late":
+        bad.img_off[:] = np.maximum(bad.img_off, 5)
+    else:
+        bad.img_off[4_000] = -7 if what == "negative" else bad.nnz + 7
+
+    def state():
+        st = g.GearState(g.config_for(wl))
+        g.gear_init_tables(st)
+        g.gear_fill_normal(st.dfv_cache, wl.n_images, wl.dfv_dim, wl.seed, 3, wl.dfv_std)
+        return st
+
+    def results(st):
+        n = int(st.n_ready.item())
+        return [t.clone() for t in (st.user_emb, st.url_emb, st.mlp_params, st.grad_accum, st.counts, st.loss, st.ready_ids[:n],
+                                    st.ready_grads[:n])]
+
+    fresh = state()
+    assert form_of_launches(launches_of(fresh, g.DeviceBatch.from_host(good), wl.M, 0.1)) == "long blocks"
+    assert int(fresh.status.item()) == 0 and int(fresh.n_ready.item()) > 0
+    for fill in (0x7f, 0xff):
+        st = state()
+        st.workspace.fill_(fill)
+        before = results(st)[:5]
+        print(f"{n_images} images, {what}, words of {fill:#x}", flush=True)
+        g.gear_step(st, g.DeviceBatch.from_host(bad), wl.M, 0.1)
+        torch.cuda.synchronize()
+        assert int(st.status.item()) == g.GEAR_ERR_RANGE and int(st.n_ready.item()) == 0
+        for a, b in zip(before, results(st)):
+            assert torch.equal(a, b)
+        g.gear_step(st, g.DeviceBatch.from_host(good), wl.M, 0.1)
+        torch.cuda.synchronize()
+        assert int(st.status.item()) == 0
+        for a, b in zip(results(st), results(fresh)):
+            assert torch.equal(a, b)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_rows_beyond_the_batch_take_part_in_no_sum(dtype):
     """A block's last rows have no view.  Here the network overflows on them (its first bias is large, and what cancels it is
