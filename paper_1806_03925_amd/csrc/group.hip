@@ -241,9 +241,11 @@ __global__ void __launch_bounds__(kSortBlock) k_radix_pass(GroupBatch gb, int pa
 __global__ void __launch_bounds__(kSortBlock) k_count(GroupBatch gb, int pass, StepOutputs out, ViewCheck views) {
   if ((int)blockIdx.y == gb.count) {
     // the views of the occurrences; a list that is no list is noted by the next launch, since this one clears the word for it
-    for (int i = blockIdx.x * kSortBlock + threadIdx.x; i < views.B; i += gridDim.x * kSortBlock)
-      if (view_ok(views, i))
-        for (int j = views.img_off[i]; j < views.img_off[i + 1]; ++j) views.occ_view[j] = i;
+    for (int i = blockIdx.x * kSortBlock + threadIdx.x; i < views.B; i += gridDim.x * kSortBlock) {
+      int32_t lo, hi;
+      if (view_ok(views, i, lo, hi))
+        for (int j = lo; j < hi; ++j) views.occ_view[j] = i;
+    }
     if (blockIdx.x != 0) return;
     const int words = 3 * (radix_tiles(gb.p[gb.count - 1].n) - 1);
     for (int i = threadIdx.x; i < words; i += kSortBlock) gb.seg_state[i] = 0u;
@@ -265,8 +267,9 @@ __global__ void __launch_bounds__(kSortBlock) k_count(GroupBatch gb, int pass, S
 
 __global__ void __launch_bounds__(kSortBlock, 5) k_counted_pass(GroupBatch gb, int pass, ViewCheck views, PlanArgs args, int32_t *failed) {
   if ((int)blockIdx.y == gb.count) {
+    int32_t lo, hi;
     for (int i = blockIdx.x * kSortBlock + threadIdx.x; i < views.B; i += gridDim.x * kSortBlock)
-      if (!view_ok(views, i)) flag(failed, args.status, GEAR_ERR_RANGE);
+      if (!view_ok(views, i, lo, hi)) flag(failed, args.status, GEAR_ERR_RANGE);
     return;
   }
   const GroupProblem &p = gb.p[blockIdx.y];

@@ -63,8 +63,10 @@ __device__ __forceinline__ void flag(int32_t *failed, int32_t *status, int code)
   atomicCAS(status, 0, code);
 }
 
-__device__ __forceinline__ bool view_ok(const ViewCheck &views, int i) {
-  const int32_t lo = views.img_off[i], hi = views.img_off[i + 1];
+// The bounds come by value: read again in a loop that writes occ_view, which for all the compiler knows may be the offsets, they
+// are a load for every occurrence.
+__device__ __forceinline__ bool view_ok(const ViewCheck &views, int i, int32_t &lo, int32_t &hi) {
+  lo = views.img_off[i], hi = views.img_off[i + 1];
   return lo >= 0 && lo <= hi && hi <= views.nnz && (i > 0 || lo == 0) && (i < views.B - 1 || hi == views.nnz);
 }
 
@@ -81,8 +83,9 @@ __device__ __forceinline__ void check_and_count(const CheckTask &t, int block, i
     const ViewCheck &views = t.views;
     const int i = block * kSortBlock + threadIdx.x;
     if (i >= views.B) return;
-    if (!view_ok(views, i)) return flag(t.failed, t.status, GEAR_ERR_RANGE);
-    for (int j = views.img_off[i]; j < views.img_off[i + 1]; ++j) views.occ_view[j] = i;
+    int32_t lo, hi;
+    if (!view_ok(views, i, lo, hi)) return flag(t.failed, t.status, GEAR_ERR_RANGE);
+    for (int j = lo; j < hi; ++j) views.occ_view[j] = i;
     return;
   }
   const GroupProblem &p = t.gb.p[list];
