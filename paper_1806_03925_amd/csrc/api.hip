@@ -621,13 +621,14 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   }
   const TnChoice first_choice = gemm_tn_choice(dt, widths, L - 1, B);
   const bool one_group = first_choice.layers == L - 1 && all_partials * sizeof(float) <= lay.wgrad_partial_bytes;
-  bool planned = (is_short || (!long_dx && one_group)) && plan_rows(*cfg, lay, B, b->nnz, is_short, &rows);
+  const bool planned = (is_short || (!long_dx && one_group)) && plan_rows(*cfg, lay, B, b->nnz, is_short, &rows);
   const int key_bits[kMaxProblems] = {bits_for(cfg->n_users), bits_for(cfg->n_urls), bits_for(cfg->n_images)};
-  int own_passes[kMaxProblems];   // of a longer step's lists
+  int own_passes[kMaxProblems];   // of a longer step's lists, where their tiles' counts have room: hardly any image, and they have not
+  bool fit = true;
   for (int i = 0; planned && !is_short && i < kMaxProblems; ++i) {
     const bool last = i == kMaxProblems - 1;
     own_passes[i] = counted_passes(key_bits[i], last ? b->nnz : B, last ? cfg->max_nnz : cfg->max_batch, rows.digit_bits);
-    planned = own_passes[i] > 0;
+    fit = fit && own_passes[i] > 0;
   }
   // On one stream nothing runs beside the blocks of a longer step, while the launches of its layers carry the grouping: it goes
   // layer by layer, with its batch sums in the shape the blocks would leave (block_sums.hpp), so that both forms have the same
@@ -638,7 +639,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   // Every tile reads the counts of all, so very long lists go back to tiles that look back, and so do long ones of few views, whose
   // blocks leave CUs idle (us a step, tiles that look back / counted, 576 -> 512 -> 256 bf16: 254 000 images of 16 384 views 227 / 220;
   // 192 -> 128: 290 000 of 20 000 187.5 / 191.5, 795 000 of 16 384 278 / 355, 61 000 of 2000 112 / 119).
-  const bool counted = long_rows && b->nnz <= 128 * kSortTile && b->nnz <= 24ll * B;
+  const bool counted = long_rows && fit && b->nnz <= 128 * kSortTile && b->nnz <= 24ll * B;
   const bool one_stream = out->one_stream != 0 || local_sort || (moderate && is_short);
   const bool carried = one_stream && moderate && !by_rows;
   // Layer by layer, weights that are operands of products on the large tiles lie in those tiles' order (gemm.hip): the forward

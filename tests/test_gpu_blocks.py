@@ -263,6 +263,36 @@ def test_sorts_of_counted_tiles_give_the_bits_of_those_that_look_back(dtype, bat
         assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("nnz", [0, 1, 32, 64])   # images of 20 bits: four passes of 32 digits take 43 ids' room
+def test_blocks_of_hardly_any_image(nnz):
+    """The counts of a list lie where its groups go, which is too little where a batch may have hardly any image; the step goes in
+    blocks all the same, with the bits of one stream."""
+    import paper_1806_03925_amd as g
+    from gear_inputs.pageviews import PageViewBatch
+    B = 16_000
+    wl = wl_of("bf16", B, (512, 256, 1), 32, 512, n_images=1 << 20, M=2)
+    rng = np.random.default_rng(nnz)
+    dev = g.DeviceBatch.from_host(PageViewBatch(
+        user_id=rng.integers(0, wl.n_users, B).astype(np.int32), url_id=rng.integers(0, wl.n_urls, B).astype(np.int32),
+        img_off=np.minimum(np.arange(B + 1), nnz).astype(np.int32), img_id=rng.choice([3, 1 << 19, (1 << 20) - 1], nnz).astype(np.int32),
+        label=(rng.random(B) < 0.3).astype(np.float32)))
+    results = []
+    for one in (False, True):
+        st = g.GearState(g.config_for(wl, max_nnz=max(nnz, 1)))
+        g.gear_init_tables(st)
+        st.dfv_cache.zero_()
+        st.dfv_cache[[3, 1 << 19, (1 << 20) - 1]] = torch.arange(1.0, 4.0, device="cuda").reshape(3, 1).to(st.dfv_cache.dtype)
+        st.one_stream = one
+        for _ in range(2):
+            names = launches_of(st, dev, wl.M, 0.1)
+            assert int(st.status.item()) == 0 and (form_of_launches(names) == "long blocks") == (not one)
+        n = int(st.n_ready.item())
+        results.append([t.clone() for t in (st.loss, st.n_ready, st.ready_ids[:n], st.ready_grads[:n], st.counts, st.user_emb, st.url_emb,
+                                            st.mlp_params)] + [st.grad_accum[[3, 1 << 19, (1 << 20) - 1]].clone()])
+    for a, b in zip(*results):
+        assert torch.equal(a, b)
+
+
 def test_ids_at_any_address():
     """Ids are read sixteen bytes at a time where their list begins at such an address, one by one elsewhere."""
     import paper_1806_03925_amd as g
