@@ -636,10 +636,11 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   // 192 -> 128, 10 000 views 97 / 110; 96 -> 64 fp32, 16 384 106 / 127.  The sums are 1 to 4 of it.
   const bool by_rows = planned && (is_short || !out->one_stream), as_rows = planned && !by_rows;
   const bool local_sort = by_rows && is_short, long_rows = by_rows && !is_short;
-  // Every tile reads the counts of all, so very long lists go back to tiles that look back, and so do long ones of few views, whose
-  // blocks leave CUs idle (us a step, tiles that look back / counted, 576 -> 512 -> 256 bf16: 254 000 images of 16 384 views 227 / 220;
-  // 192 -> 128: 290 000 of 20 000 187.5 / 191.5, 795 000 of 16 384 278 / 355, 61 000 of 2000 112 / 119).
-  const bool counted = long_rows && fit && b->nnz <= 128 * kSortTile && b->nnz <= 24ll * B;
+  // Every tile reads the counts of all, so very long lists go back to tiles that look back (us a step, look back / counted, of
+  // 64-view blocks: 576 -> 512 -> 256 bf16, 327 000 images of 16 384 views 221 / 229; 192 -> 128, 290 000 of 20 000 167 / 170, 785 000 of
+  // 16 384 262 / 317.  Below: 239 000 of 8000 149 / 137, 158 000 of 4000 views of 576 -> 512 -> 256 152 / 155, 59 000 of 2000 99 / 93, 54 000 of
+  // 1200 99 / 100).
+  const bool counted = long_rows && fit && b->nnz <= 128 * kSortTile;
   const bool one_stream = out->one_stream != 0 || local_sort || (moderate && is_short);
   const bool carried = one_stream && moderate && !by_rows;
   // Layer by layer, weights that are operands of products on the large tiles lie in those tiles' order (gemm.hip): the forward
@@ -768,13 +769,13 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
     if (counted) {
       const StepOutputs outputs = {out->status, failed, out->n_ready, out->loss};
       const ViewCheck views = {b->img_off, occ_view, B, b->nnz};
-      const int planned = gb.p[2].n > 0 ? gb.p[2].passes : 1;   // passes that the plan comes behind
+      const int plan_behind = gb.p[2].n > 0 ? gb.p[2].passes : 1;   // how many passes the plan comes behind
       for (int pass = 0; pass < group_passes(gb); ++pass) {
-        if (pass != planned) GEAR_RUN(pass < 2 ? "group_ids" : "group_rest", launch_count(gb, pass, outputs, views, s));
-        GEAR_RUN(pass < 2 ? "group_ids" : "group_rest", launch_counted_pass(gb, pass, views, plan_args, failed, s));
-        if (pass + 1 == planned) {
+        if (pass != plan_behind) GEAR_RUN("group_count", launch_count(gb, pass, outputs, views, s));
+        GEAR_RUN("group_ids", launch_counted_pass(gb, pass, views, plan_args, failed, s));
+        if (pass + 1 == plan_behind) {
           GEAR_HIP(lane.enter(s));
-          GEAR_RUN("accum_plan", launch_segments_count(gb, plan_args, planned, failed, s));
+          GEAR_RUN("accum_plan", launch_segments_count(gb, plan_args, plan_behind, failed, s));
         }
       }
     } else {

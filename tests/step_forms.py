@@ -25,6 +25,11 @@ def form_of_launches(names):
     return "divided" if "dgrad_gemm_emb" in names else "helper"
 
 
+def counted(names):
+    """Whether the lists beside blocks were sorted by tiles that are counted ahead of every pass."""
+    return "group_count" in names
+
+
 def form_of(st, dev, M, lr):
     """Runs the step."""
     return form_of_launches(launches_of(st, dev, M, lr))

@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 import torch
 
-from step_forms import form_of_launches, launches_of
+from step_forms import counted, form_of_launches, launches_of
 from test_gpu_tiles import beside_the_oracle
 
 pytestmark = pytest.mark.gpu
@@ -188,7 +188,7 @@ def test_on_one_stream_a_long_step_goes_layer_by_layer_with_the_bits_of_blocks(d
     ("bf16", 16_384, 2, (72, 40, 1), 40, "long blocks"), ("bf16", 16_385, 2, (72, 40, 1), 40, "helper"),
     ("bf16", 8_192, 5, (256, 1), 960, "long blocks"), ("bf16", 8_193, 5, (256, 1), 960, "helper"),   # one workgroup a CU
     ("bf16", 13_000, 2, (72, 40, 24, 1), 512, "long blocks"), ("bf16", 13_000, 2, (72, 40, 24, 1), 520, "helper"),   # a row in two loads
-    ("bf16", 13_000, 2, (72, 40, 1), 520, "long blocks"),
+    ("bf16", 13_000, 2, (72, 40, 1), 520, "long blocks"), ("bf16", 13_000, 2, (72, 1), 1_024, "long blocks"),
     ("bf16", 600, 85, (40, 1), 40, "long blocks"), ("bf16", 500, 97, (40, 1), 40, "helper"),         # images a view
     ("bf16", 16, 256, (40, 1), 40, "blocks"), ("bf16", 16, 257, (40, 1), 40, "carried"),        # (ids sorted in LDS, or carried)
     ("bf16", 2_000, 23, (768, 384, 1), 768, "helper"),                                          # wide layers, few views
@@ -196,7 +196,7 @@ def test_on_one_stream_a_long_step_goes_layer_by_layer_with_the_bits_of_blocks(d
 ])
 def test_which_steps_go_in_blocks(dtype, batch, each, layers, D, form):
     """On either side of each line, with the bits of the same step on one stream.  Sorts beside blocks of 64 views take digits
-    of nine bits."""
+    as wide as the blocks leave LDS for."""
     import paper_1806_03925_amd as g
     from gear_inputs.pageviews import PageViewBatch
     wl = wl_of(dtype, batch, layers, 32, D, max_images=each, n_users=1 << 20, n_urls=1 << 12, n_images=2_000, M=4)
@@ -220,7 +220,8 @@ def test_which_steps_go_in_blocks(dtype, batch, each, layers, D, form):
         if not one:
             assert form_of_launches(names) == form
             if form == "long blocks" and batch > 12_288 and dtype == "bf16":
-                assert names.count("group_ids") == 1 + 3   # the check; 20 bits of a user id
+                # 20 bits of a user id: ten and ten, but of nine at most beside blocks of 151 KB
+                assert counted(names) and names.count("group_ids") == (3 if D == 1_024 else 2)
         n = int(st.n_ready.item())
         results.append([t.clone() for t in (st.loss, st.n_ready, st.ready_ids[:n], st.ready_grads[:n], st.grad_accum, st.counts,
                                             st.user_emb, st.url_emb, st.mlp_params)])
@@ -253,7 +254,8 @@ def test_sorts_of_counted_tiles_give_the_bits_of_those_that_look_back(dtype, bat
         st.one_stream = one
         for step in range(2):
             names = launches_of(st, g.DeviceBatch.from_host(host), wl.M, 0.1)
-            assert int(st.status.item()) == 0 and (form_of_launches(names) == "long blocks") == (not one)
+            assert int(st.status.item()) == 0 and form_of_launches(names) == ("carried" if one else "long blocks")
+            assert counted(names) == (not one)
         n = int(st.n_ready.item())
         results.append([t.clone() for t in (st.loss, st.n_ready, st.ready_ids[:n], st.ready_grads[:n], st.grad_accum, st.counts,
                                             st.user_emb, st.url_emb, st.mlp_params)])
@@ -286,6 +288,7 @@ def test_blocks_of_hardly_any_image(nnz):
         for _ in range(2):
             names = launches_of(st, dev, wl.M, 0.1)
             assert int(st.status.item()) == 0 and (form_of_launches(names) == "long blocks") == (not one)
+            assert counted(names) == (not one and nnz in (0, 64))   # of no image, one workgroup
         n = int(st.n_ready.item())
         results.append([t.clone() for t in (st.loss, st.n_ready, st.ready_ids[:n], st.ready_grads[:n], st.counts, st.user_emb, st.url_emb,
                                             st.mlp_params)] + [st.grad_accum[[3, 1 << 19, (1 << 20) - 1]].clone()])
@@ -368,7 +371,7 @@ def test_occurrences_that_no_view_owns(n_images, what):
                                     st.ready_grads[:n])]
 
     fresh = state()
-    assert form_of_launches(launches_of(fresh, g.DeviceBatch.from_host(good), wl.M, 0.1)) == "long blocks"
+    assert counted(launches_of(fresh, g.DeviceBatch.from_host(good), wl.M, 0.1))
     assert int(fresh.status.item()) == 0 and int(fresh.n_ready.item()) > 0
     for fill in (0x7f, 0xff):
         st = state()
