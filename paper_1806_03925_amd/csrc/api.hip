@@ -640,7 +640,11 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   // 64-view blocks: 576 -> 512 -> 256 bf16, 327 000 images of 16 384 views 221 / 229; 192 -> 128, 290 000 of 20 000 167 / 170, 785 000 of
   // 16 384 262 / 317.  Below: 239 000 of 8000 149 / 137, 158 000 of 4000 views of 576 -> 512 -> 256 152 / 155, 59 000 of 2000 99 / 93, 54 000 of
   // 1200 99 / 100).
-  const bool counted = long_rows && fit && b->nnz <= 128 * kSortTile;
+  const bool very_long = b->nnz > 128 * kSortTile, counted = long_rows && fit && !very_long;
+  // Very long lists beside blocks of 32 views, which leave less of a CU, are on the caller's stream, so that their sorts start ahead
+  // of the blocks, which go to the helper's with the weight gradients (us a step, on the helper's / on the caller's: 16 384 views of 20
+  // images, 320 -> 256 fp32 209 / 193, 8000 of 40, 192 -> 128 bf16 164 / 151; but blocks of 64, 16 384 of 20, 576 -> 512 -> 256 221 / 230).
+  const bool group_here = long_rows && very_long && rows.rows == 32;
   const bool one_stream = out->one_stream != 0 || local_sort || (moderate && is_short);
   const bool carried = one_stream && moderate && !by_rows;
   // Layer by layer, weights that are operands of products on the large tiles lie in those tiles' order (gemm.hip): the forward
@@ -661,7 +665,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   {
     int passes = 1;   // the lists share launches: as many passes for all as the widest ids need
     for (int i = 0; i < kMaxProblems; ++i) {
-      const int need = radix_passes(key_bits[i], lay.g[i].total_words, carried ? kSideDigitBits : long_rows ? 9 : widest_digit(B > b->nnz ? B : b->nnz));
+      const int need = radix_passes(key_bits[i], lay.g[i].total_words, carried ? kSideDigitBits : long_rows && rows.rows == 64 ? kBesideDigitBits : widest_digit(B > b->nnz ? B : b->nnz));
       if (need > passes) passes = need;
     }
     // a pass that is carried costs nothing but its length, and narrow digits make it short: as many as find a launch ahead
@@ -695,9 +699,10 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   if (needs_lane && !side) return GEAR_ERR_HIP;
   hipStream_t helper = one_stream ? s : side->stream;
   LaneScope lane(side, !one_stream, !by_rows, captured, s);
-  // Layer by layer on two streams the helper has all that looks at the store.  Blocks whose lists are counted take their place
-  // ahead of the launch that first does.
-  if (!counted) GEAR_HIP(lane.enter(by_rows ? s : helper));
+  // Layer by layer on two streams the helper has all that looks at the store.  Blocks take their place ahead of the launch that
+  // first does, and run beside the step of another program until then (us for a step of each of two programs, at once / so, 290 000
+  // images of 20 000 views, 192 -> 128 bf16, 344 / 257; 319 000 of 8000 351 / 229; LaneScope::enter).
+  if (!long_rows) GEAR_HIP(lane.enter(helper));
   {
     // Step outputs and counters cleared and the operand copies of the weights made in one launch ahead of everything:
     // the first product then needs no event, and behind the gather's many workgroups the copies would not get onto the
@@ -746,7 +751,11 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   if (by_rows) {
     LocalTask local = {};
     if (local_sort) local = local_task(rows, gb, plan_args, failed);
-    GEAR_RUN("view_blocks", launch_rows(*cfg, lay, rows, *b, *t, dfv_cache, ws, local, s));
+    hipStream_t caller = s;
+    {
+      hipStream_t s = group_here ? helper : caller;
+      GEAR_RUN("view_blocks", launch_rows(*cfg, lay, rows, *b, *t, dfv_cache, ws, local, s));
+    }
   } else {
     const CheckTask check = check_task(gb, b->img_off, occ_view, B, b->nnz, failed, out->status);
     GEAR_RUN("gather_pool", launch_gather_pool(*cfg, *b, *t, dfv_cache, x, s, carried ? &check : nullptr));
@@ -765,7 +774,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   // device (a caller that waits for every step), the gather then starts as soon as the step does, not
   // after the host has issued the grouping's launches.
   if (!carried && !local_sort) {
-    hipStream_t s = helper;  // the stream of this block's launches
+    hipStream_t caller = s, s = group_here ? caller : helper;  // the stream of this block's launches
     if (counted) {
       const StepOutputs outputs = {out->status, failed, out->n_ready, out->loss};
       const ViewCheck views = {b->img_off, occ_view, B, b->nnz};
@@ -781,9 +790,10 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
     } else {
       GEAR_RUN("group_ids", launch_check(gb, b->img_off, occ_view, B, b->nnz, failed, out->status, s));
       for (int pass = 0; pass < group_passes(gb); ++pass) GEAR_RUN("group_ids", launch_radix_pass(gb, pass, failed, s));
+      if (long_rows) GEAR_HIP(lane.enter(s));
       GEAR_RUN("accum_plan", launch_segments(gb, &plan_args, failed, s));
     }
-    GEAR_HIP(long_rows ? lane.mark() : lane.mark_checked());
+    if (!group_here) GEAR_HIP(long_rows ? lane.mark() : lane.mark_checked());
   }
 
   // Until its first kernel that changes caller state (the first SGD on a hidden layer's weights), the
@@ -914,6 +924,8 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
       GEAR_RUN("accumulate_wgrad", launch_accumulate_wgrad(*cfg, gb.p[2], plan, dx_dfv, grad_accum, M, out->ready_ids, out->ready_grads,
                                                            emb, wp, n, B, splits, failed, s));
     } else {
+      hipStream_t caller = s;
+      hipStream_t s = group_here ? helper : caller;
       GEAR_RUN("wgrad_gemm", launch_gemm_tn(dt, wp + first, n, B, splits, choice.large, nullptr, s));
     }
     // The sums of the partials and the SGD change caller state, so the status word has to be final: the
@@ -921,6 +933,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
     // workgroups get onto the device as the bookkeeping's leave room and are done before it is, so the
     // step ends with the bookkeeping and the join.
     if (first == 0 && long_rows) {
+      if (group_here) GEAR_HIP(lane.mark());
       GEAR_HIP(lane.wait(true));
       if (gear_status st = bookkeeping(s)) return st;
     } else if (first == 0) {

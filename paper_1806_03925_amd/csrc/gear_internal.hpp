@@ -119,6 +119,7 @@ constexpr int kMaxPasses = 4;
 constexpr int kMaxRides = 3;                          // passes that other launches are asked to carry, if it is up to us
 constexpr int kMaxDigitBits = 12;
 constexpr int kSideDigitBits = 11;                    // of passes that other launches carry
+constexpr int kBesideDigitBits = 9;                   // of passes that look back beside workgroups that fill their CU
 constexpr int kCountedDigitBits = 10;                 // of passes whose tiles are counted ahead of them
 // ids from which a workgroup of the check takes several tiles and the segments take few registers
 constexpr int kLongList = 65536;

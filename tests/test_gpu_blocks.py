@@ -104,7 +104,7 @@ def test_lists_that_are_mostly_one_id(n_images, nnz, shares):
 
 @pytest.mark.parametrize("dtype,batch,images", [
     ("bf16", 12_288, 8), ("bf16", 12_289, 8), ("bf16", 16_384, 8),    # 32 views a block, 64
-    ("bf16", 12_289, 12), ("bf16", 16_384, 12),                       # the grouping on the caller's stream
+    ("bf16", 12_289, 12), ("bf16", 16_384, 12),                       # more ids
     ("f32", 12_287, 8), ("f32", 12_288, 12), ("f32", 16_385, 8),
 ])
 def test_long_steps_in_blocks(dtype, batch, images):
@@ -263,6 +263,39 @@ def test_sorts_of_counted_tiles_give_the_bits_of_those_that_look_back(dtype, bat
     assert np.array_equal(st.dbg[2][:host.nnz].cpu().numpy(), order)
     for a, b in zip(*results):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("dtype,batch,layers", [("bf16", 16_384, (40, 1)), ("bf16", 4_096, (40, 1)), ("f32", 16_384, (72, 40, 1))])
+def test_very_long_lists_go_back_to_tiles_that_look_back(dtype, batch, layers):
+    """262 144 images and one more: in counted tiles, and in tiles that look back on the helper stream (64 views a block) or on the
+    caller's (32); with the bits of one stream."""
+    import paper_1806_03925_amd as g
+    from gear_inputs.pageviews import PageViewBatch
+    rng = np.random.default_rng(batch)
+    for nnz in (262_144, 262_145):
+        each = 262_144 // batch
+        wl = wl_of(dtype, batch, layers, 8, 40, max_images=each + 1, n_users=3_000, n_urls=70_000, n_images=30_000, M=7)
+        off = each * np.arange(batch + 1)
+        off[-1] = nnz
+        dev = g.DeviceBatch.from_host(PageViewBatch(
+            user_id=rng.integers(0, wl.n_users, batch).astype(np.int32), url_id=rng.integers(0, wl.n_urls, batch).astype(np.int32),
+            img_off=off.astype(np.int32), img_id=rng.integers(0, wl.n_images, nnz).astype(np.int32),
+            label=(rng.random(batch) < 0.3).astype(np.float32)))
+        results = []
+        for one in (False, True):
+            st = g.GearState(g.config_for(wl))
+            g.gear_init_tables(st)
+            g.gear_fill_normal(st.dfv_cache, wl.n_images, wl.dfv_dim, wl.seed, 3, wl.dfv_std)
+            st.one_stream = one
+            for _ in range(2):
+                names = launches_of(st, dev, wl.M, 0.1)
+                assert int(st.status.item()) == 0 and (form_of_launches(names) == "long blocks") == (not one)
+                assert counted(names) == (not one and nnz == 262_144)
+            n = int(st.n_ready.item())
+            results.append([t.clone() for t in (st.loss, st.n_ready, st.ready_ids[:n], st.ready_grads[:n], st.grad_accum, st.counts,
+                                                st.user_emb, st.url_emb, st.mlp_params)])
+        for a, b in zip(*results):
+            assert torch.equal(a, b)
 
 
 @pytest.mark.parametrize("nnz", [0, 1, 32, 64])   # images of 20 bits: four passes of 32 digits take 43 ids' room

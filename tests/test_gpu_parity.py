@@ -878,7 +878,8 @@ ERROR_PATHS = {
     "two hidden layers, carried": ("tiny", dict(layers=(64, 32, 1), mlp_dtype="bf16", **WIDE), 512, "carried"),
     "three hidden layers, carried": ("tiny", dict(layers=(64, 32, 16, 1), mlp_dtype="bf16", **WIDE), 512, "carried"),   # with the logit layer
     "long blocks": ("bf16", dict(n_users=50_000, n_urls=1 << 15, n_images=4_000), 9_001, "long blocks"),
-    "long blocks, grouping on the caller's stream": ("bf16", dict(n_users=50_000, n_urls=1 << 15, n_images=4_000), 16_200, "long blocks"),
+    "long blocks, tiles that look back": ("bf16", dict(n_users=50_000, n_urls=1 << 15, n_images=4_000, max_images=40), 16_200, "long blocks"),
+    "long blocks, grouping on the caller's stream": ("bf16", dict(n_users=50_000, n_urls=1 << 15, n_images=4_000, max_images=80), 8_000, "long blocks"),
     "helper stream": ("bf16", dict(n_users=50_000, n_urls=1 << 15, n_images=4_000, layers=(72, 1), **WIDE), 9_001, "helper"),
     "divided": ("large", dict(n_users=50_000, n_urls=1 << 15, n_images=4_000), 8_192, "divided"),
 }
@@ -927,7 +928,7 @@ def test_ready_list_over_capacity_is_reported_and_changes_nothing(path):
         assert torch.equal(a, b)
 
 
-@pytest.mark.parametrize("name", ["tiny", "tiny, wide", "bf16", "bf16, wide", "large"])
+@pytest.mark.parametrize("name", ["tiny", "tiny, wide", "bf16", "bf16, many images", "bf16, wide", "large"])
 def test_a_step_that_fails_part_way_still_joins_the_helper_stream(name):
     """A launch that fails in the middle of a step's enqueue (forced from the host: the n-th launch is
     not enqueued and the call returns GEAR_ERR_HIP) must leave the caller's stream waiting for whatever
@@ -940,9 +941,11 @@ def test_a_step_that_fails_part_way_still_joins_the_helper_stream(name):
         wl = wl.scaled(n_users=100_000, n_urls=1 << 16, n_images=5_000, batch=8192 if name == "large" else 9_001)
     if "wide" in name:
         wl = wl.scaled(layers=(72, 1), **WIDE)
+    if "many" in name:                                 # blocks and weight gradients there, the grouping on the caller's stream
+        wl = wl.scaled(batch=8_000, max_images=80)
     cfg, st, _ = make_pair(wl)
     dev = g.DeviceBatch.from_host(PageViewSource(wl).batch(0))
-    assert form_of(st, dev, wl.M, wl.lr) == {"tiny": "blocks", "tiny, wide": "carried", "bf16": "long blocks",
+    assert form_of(st, dev, wl.M, wl.lr) == {"tiny": "blocks", "tiny, wide": "carried", "bf16": "long blocks", "bf16, many images": "long blocks",
                                              "bf16, wide": "helper", "large": "divided"}[name]
     launches = len(launches_of(st, dev, wl.M, wl.lr))
     stream = torch.cuda.current_stream()

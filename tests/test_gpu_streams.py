@@ -52,8 +52,9 @@ def outputs(st):
     ("tiny", 511, {}, "blocks"), ("small", 4_096, {}, "blocks"),
     ("tiny", 511, {"dfv_dim": 2_080}, "carried"),                # one tile of each list
     ("small", 4_096, {"max_images": 12}, "carried"), ("bf16", 4_600, {"max_images": 10}, "carried"),   # several that look back
-    ("bf16", 9_001, {}, "long blocks"),                          # grouping on the helper stream
-    ("bf16", 16_200, {}, "long blocks"),                         # on the caller's, beside blocks
+    ("bf16", 9_001, {}, "long blocks"),                          # lists in counted tiles
+    ("bf16", 16_200, {"max_images": 40}, "long blocks"),         # in tiles that look back
+    ("bf16", 8_000, {"max_images": 80}, "long blocks"),          # on the caller's stream, beside blocks
     ("bf16", 18_001, {}, "helper"),
     ("large", 8_192, {"max_images": 40}, "divided"),             # helper stream, long lists, dLoss/dx in two products
 ])
@@ -90,15 +91,18 @@ def test_a_step_does_not_read_the_status_word_that_others_write(name, batch, cha
         assert torch.equal(a, b)
 
 
-# views of the bf16 workload: in blocks on one stream (13 000 ids), with the grouping on the helper stream (58 000) or on the
-# caller's beside blocks on the helper's (105 000), and layer by layer with everything about the store on the helper's
-SHORT, LONG, HERE, LAYERS = 2_000, 9_001, 16_200, 18_001
-FORMS = {SHORT: "blocks", LONG: "long blocks", HERE: "long blocks", LAYERS: "helper"}
+# views of the bf16 workload: in blocks on one stream (13 000 ids), with the grouping on the helper stream, in counted tiles (58 000)
+# or in tiles that look back (365 000), or on the caller's beside blocks on the helper's (340 000), and layer by layer with everything about
+# the store on the helper's
+SHORT, LONG, BACK, HERE, LAYERS = 2_000, 9_001, 16_200, 8_000, 18_001
+FORMS = {SHORT: "blocks", LONG: "long blocks", BACK: "long blocks", HERE: "long blocks", LAYERS: "helper"}
+IMAGES = {BACK: dict(max_images=40), HERE: dict(max_images=80)}
 
 
 @pytest.mark.parametrize("sizes", [(SHORT, SHORT), (SHORT, LONG), (LONG, SHORT), (SHORT, LONG, SHORT), (LONG, LONG),
                                    (HERE, HERE), (SHORT, HERE), (HERE, SHORT), (LONG, HERE), (HERE, LONG), (LAYERS, LAYERS),
-                                   (SHORT, LAYERS), (LAYERS, SHORT), (HERE, LAYERS), (LAYERS, HERE), (LAYERS, HERE, LONG, LAYERS)])
+                                   (SHORT, LAYERS), (LAYERS, SHORT), (HERE, LAYERS), (LAYERS, HERE), (LAYERS, HERE, LONG, LAYERS),
+                                   (BACK, BACK), (BACK, SHORT), (LONG, BACK), (BACK, LAYERS), (LAYERS, BACK), (HERE, BACK, HERE)])
 def test_steps_on_streams_of_their_own_share_a_store_in_the_order_they_were_issued(sizes):
     """Each step has tables, workspace and stream of its own and all collect gradients in one store.  The first stream is
     held up ahead of its step, so a step that does not wait for the one issued before it gets there first; which groups of
@@ -106,7 +110,7 @@ def test_steps_on_streams_of_their_own_share_a_store_in_the_order_they_were_issu
     import paper_1806_03925_amd as g
     results = []
     for apart in (False, True):
-        states = [state_of("bf16", n) for n in sizes]
+        states = [state_of("bf16", n, **IMAGES.get(n, {})) for n in sizes]
         store = states[0][1]
         for _, st, _ in states[1:]:
             st.grad_accum, st.counts = store.grad_accum, store.counts
@@ -135,18 +139,19 @@ def test_steps_on_streams_of_their_own_share_a_store_in_the_order_they_were_issu
         assert torch.equal(a, b)
 
 
-@pytest.mark.parametrize("views,one", [(SHORT, False), (LONG, True)])   # in blocks; layer by layer with the sums of blocks
-def test_a_step_on_one_stream_recorded_into_a_graph_between_steps_on_other_streams(views, one):
+# on one stream, in blocks and layer by layer with the sums of blocks; on two, the fork to the helper ahead of all launches and behind the first
+@pytest.mark.parametrize("views,one", [(SHORT, False), (LONG, True), (LONG, False), (BACK, False), (HERE, False)])
+def test_a_step_recorded_into_a_graph_between_steps_on_other_streams(views, one):
     """Recording takes no event from the order of the steps and leaves none: replays, with eager steps on another stream
     before and between them, give the bits of the same steps issued one after the other."""
     import paper_1806_03925_amd as g
     results = []
     for recorded in (False, True):
-        wl, st, src = state_of("bf16", views)
+        wl, st, src = state_of("bf16", views, **IMAGES.get(views, {}))
         st.one_stream = one
         dev = g.DeviceBatch.from_host(src.batch(0, batch=views))
-        wl2, st2, _ = state_of("bf16", LONG)
-        dev2 = g.DeviceBatch.from_host(src.batch(1, batch=LONG))
+        wl2, st2, src2 = state_of("bf16", LONG)
+        dev2 = g.DeviceBatch.from_host(src2.batch(1, batch=LONG))
         beside = torch.cuda.Stream()
         torch.cuda.synchronize()
         with torch.cuda.stream(beside):
@@ -169,6 +174,6 @@ def test_a_step_on_one_stream_recorded_into_a_graph_between_steps_on_other_strea
         torch.cuda.synchronize()
         assert int(st.status.item()) == 0 and int(st2.status.item()) == 0
         results.append(outputs(st) + outputs(st2))
-        assert form_of(st, dev, wl.M, 0.1) == ("carried" if one else "blocks")
+        assert form_of(st, dev, wl.M, 0.1) == ("carried" if one else FORMS[views])
     for a, b in zip(*results):
         assert torch.equal(a, b)
