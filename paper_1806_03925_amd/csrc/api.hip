@@ -610,7 +610,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   // (group_device.hpp), from the start of the step on, so that it is done when the weight gradients are, and the bookkeeping
   // follows those on the caller's (accumulation beside weight gradients, in one launch or on two streams, took as long as one
   // behind the other, and the wait for the blocks 10 us more).  us a step, tiles that look back / counted: 16 384 views of 576 ->
-  // 512 -> 256 bf16, 106 000 ids, 157 / 147; of 320 -> 256 fp32, 172 000 ids, 174 / 164.
+  // 512 -> 256 bf16, 106 000 ids, 170 / 158; of 320 -> 256 fp32, 172 000 ids, 178 / 166.
   RowsPlan rows;
   const bool long_dx = (double)B * (F - 2 * cfg->emb_dim) * lay.out_dim[0] >= kSplitDxMacs;
   TnProblem widths[GEAR_MAX_LAYERS];   // of the weight-gradient products
@@ -711,7 +711,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
     const int n_jobs = by_rows ? L - 1 : L;   // the logit layer is one row, which rows.hip takes from the parameters
     for (int l = 0; l < n_jobs; ++l)
       jobs[l] = CastJob{t->mlp_params + lay.w_off[l], ws + lay.wc[l], ws + lay.wct[l], lay.out_dim[l], lay.in_dim[l],
-                        !by_rows && w_tiles[l], by_rows ? INT32_MAX : wt_tiles_from[l]};
+                        w_tiles[l], wt_tiles_from[l]};
     ZeroList zero;
     zero.count = 0;
     if (local_sort)

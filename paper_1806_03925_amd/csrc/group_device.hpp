@@ -284,9 +284,9 @@ __device__ __forceinline__ void radix_pass_any(const GroupBatch &gb, int list, i
 // the counts of the tiles before it, many loads at once, instead of looking back at words that come past the caches one after
 // the other, and the sort needs no totals.  For what runs beside blocks of views, which is bound by latency: while the blocks
 // gather, a load takes microseconds.  us of the launch alone, 36 tiles of 2048 keys 7 to 9, 68 tiles 9 (looking back 10 and 25),
-// its count 3 to 5; beside the blocks 11 to 16 and 3 to 10 (looking back 13 to 18 and 20 to 57).  Digits of ten bits then cost
-// about what narrow ones do, so ids of 20 bits take two passes.  Counted by adds to the next pass' words while a pass scatters,
-// the most popular ids' words took 20 us of a pass, one add after the other.
+// its count 3 to 5; in a step, of 106 000 ids 10 to 16 and its count 2.5, of 172 000 6 to 29 and 2.5 to 6 (looking back 13 to 18 and
+// 20 to 57).  Digits of ten bits then cost about what narrow ones do, so ids of 20 bits take two passes.  Counted by adds to the next
+// pass' words while a pass scatters, the most popular ids' words took 20 us of a pass, one add after the other.
 // Waves at the highest priority: blocks of views keep the matrix unit busy, not the others, and wait for nobody here.
 __device__ __forceinline__ void count_tile(const GroupProblem &p, int pass, int tile, int *hist /* [radix] */) {
   const int radix = 1 << p.digit_bits, shift = pass * p.digit_bits, lane = threadIdx.x & 63;
