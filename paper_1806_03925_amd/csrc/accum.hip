@@ -76,8 +76,8 @@ __global__ void __launch_bounds__(256) k_refresh(uint4 *__restrict__ cache, int6
 hipError_t launch_accumulate(const gear_config &cfg, const GroupProblem &img, const AccumPlan &plan,
                              const void *dx_dfv, float *grad_accum, int32_t M, int32_t *ready_ids,
                              float *ready_grads, const EmbeddingWork *emb, bool level2, const BlockSums *sums, const int32_t *status,
-                             hipStream_t s) {
-  if (img.n <= 0 && !emb) return hipSuccess;
+                             hipStream_t s, hipEvent_t stop) {
+  if (img.n <= 0 && !emb) return leave(stop, s);
   const int D = cfg.dfv_dim;
   const int cols = cfg.mlp_dtype == GEAR_BF16 ? 8 : 4;
   int threads = ((D / cols + 63) / 64) * 64;
@@ -95,8 +95,8 @@ hipError_t launch_accumulate(const gear_config &cfg, const GroupProblem &img, co
   }
   if (sums && (!emb || level2 || plan.row_at)) return hipErrorInvalidValue;
 #define GEAR_ACC(T, R, AT, EMB, SUMS)                                                                                            \
-  hipLaunchKernelGGL((k_accumulate<T, R, AT>), dim3(blocks), dim3(threads), 0, s, plan, (const T *)dx_dfv, D, grad_accum, M, \
-                     ready_ids, ready_grads, EMB, SUMS, status)
+  launch_leaving(stop, k_accumulate<T, R, AT>, dim3(blocks), threads, 0, s, plan, (const T *)dx_dfv, D, grad_accum, M, ready_ids, \
+                 ready_grads, EMB, SUMS, status)
 #define GEAR_ACC_T(T)              \
   if (!emb)                        \
     GEAR_ACC(T, kNoRide, false, NoWork{}, NoWork{}); \

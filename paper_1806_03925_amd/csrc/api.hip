@@ -367,7 +367,7 @@ class LaneScope {
     if (entered_ && !captured_) {
       if (books_) {
         if (forked_) lane_->last = &lane_->join;   // else it ended before it gave the helper anything
-      } else if (hipEventRecord(lane_->done, s_) == hipSuccess) {
+      } else if (done_left_ || hipEventRecord(lane_->done, s_) == hipSuccess) {
         lane_->last = &lane_->done;
       }
     }
@@ -376,9 +376,8 @@ class LaneScope {
   LaneScope(const LaneScope &) = delete;
   LaneScope &operator=(const LaneScope &) = delete;
   // The step takes its place behind the last one.  Of two long steps the helper stream keeps the order by itself; behind or
-  // ahead of a short one it takes an event.  (A short step pays 2 us for leaving one: 49.7 -> 51.8, 78.6 -> 80.5 and 104.9 ->
-  // 106.6 us on the three smallest workloads; left by the step's last kernel itself, hipExtLaunchKernel, it was 0.3 us where
-  // the device is the slower side and 4 us where the host is.)
+  // ahead of a short one it takes an event.  (A short step pays 2 us for one recorded behind it: 49.7 -> 51.8, 78.6 -> 80.5 and
+  // 104.9 -> 106.6 us on the three smallest workloads in an earlier form; 0.3 us left by its last launch itself, done_by.)
   // A step that is being captured has the place its graph is launched in; it leaves the events of the others alone.
   // `on`: the stream that first looks at the store; what the step gives to its streams before this call, or to others than this
   // one, runs beside the steps ahead of it (us for a step of each of two programs on streams of their own, with the whole step
@@ -392,19 +391,29 @@ class LaneScope {
     entered_ = e == hipSuccess;
     return e;
   }
+  // The launches that an event is to come behind leave it themselves where they can: what follows on the stream then waits for no
+  // event's packet (us between the ends of a launch and the start of the next one on its stream, with the packet / without: 8 to 10 / 3;
+  // from a launch on one stream to one on the other that waits for it 10 to 12 / 6 to 8; a step of 512 views 31.3 / 30.1, of 16 384
+  // bf16 159 / 154, the counts of its first passes in the prologue included).  Not while they are being captured.  `left`: the launch
+  // ahead was given the event.
+  hipEvent_t fork_by() const { return side_ && !captured_ ? side_->fork : nullptr; }
+  hipEvent_t mark_by() const { return side_ && !captured_ ? join_ : nullptr; }
+  hipEvent_t mark_checked_by() const { return side_ && !captured_ ? side_->checked : nullptr; }
+  hipEvent_t done_by() const { return lane_ && !captured_ && !books_ ? lane_->done : nullptr; }
+  void done_left() { done_left_ = done_by() != nullptr; }   // it was the step's last launch
   // what the caller's stream has done so far happens before whatever the helper stream is given next
-  hipError_t fork() {
+  hipError_t fork(bool left) {
     if (!side_) return hipSuccess;
-    hipError_t e = hipEventRecord(side_->fork, s_);
-    if (e != hipSuccess) return e;
+    if (!left || captured_)
+      if (hipError_t e = hipEventRecord(side_->fork, s_)) return e;
     forked_ = true;
     joined_ = false;
     return hipStreamWaitEvent(side_->stream, side_->fork, 0);
   }
   // marks the point of the helper stream that a later wait() refers to
-  hipError_t mark() { return side_ ? hipEventRecord(join_, side_->stream) : hipSuccess; }
+  hipError_t mark(bool left) { return side_ && (!left || captured_) ? hipEventRecord(join_, side_->stream) : hipSuccess; }
   // the same for the end of the helper's first part (ids checked, plan made): the status word is final
-  hipError_t mark_checked() { return side_ ? hipEventRecord(side_->checked, side_->stream) : hipSuccess; }
+  hipError_t mark_checked(bool left) { return side_ && (!left || captured_) ? hipEventRecord(side_->checked, side_->stream) : hipSuccess; }
   hipError_t wait_checked() { return side_ ? hipStreamWaitEvent(s_, side_->checked, 0) : hipSuccess; }
   // the caller's stream continues after the last mark(); final = nothing is given to the helper after it
   hipError_t wait(bool final) {
@@ -419,7 +428,7 @@ class LaneScope {
   hipStream_t s_;
   const bool captured_, books_;
   const hipEvent_t join_;
-  bool entered_ = false, forked_ = false, joined_ = false;
+  bool entered_ = false, forked_ = false, joined_ = false, done_left_ = false;
 };
 }  // namespace
 
@@ -592,7 +601,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
                                                       "dgrad_gemm_l3", "dgrad_gemm_l4", "dgrad_gemm_l5",
                                                       "dgrad_gemm_l6", "dgrad_gemm_l7"};
   if (B == 0) {
-    GEAR_RUN("begin", launch_begin(out->status, failed, out->n_ready, out->loss, ZeroList{}, dt, nullptr, 0, false, s));
+    GEAR_RUN("begin", launch_begin(out->status, failed, out->n_ready, out->loss, ZeroList{}, dt, nullptr, 0, false, nullptr, s, nullptr));
     return GEAR_OK;
   }
   int32_t *occ_view = (int32_t *)(ws + lay.occ_view);
@@ -703,6 +712,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   // first does, and run beside the step of another program until then (us for a step of each of two programs, at once / so, 290 000
   // images of 20 000 views, 192 -> 128 bf16, 344 / 257; 319 000 of 8000 351 / 229; LaneScope::enter).
   if (!long_rows) GEAR_HIP(lane.enter(helper));
+  const ViewCheck views = {b->img_off, occ_view, B, b->nnz};
   {
     // Step outputs and counters cleared and the operand copies of the weights made in one launch ahead of everything:
     // the first product then needs no event, and behind the gather's many workgroups the copies would not get onto the
@@ -716,13 +726,16 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
     zero.count = 0;
     if (local_sort)
       local_zero_list(gb, &zero);
-    else if (!counted)
+    else if (counted)
+      counted_zero_list(gb, &zero);
+    else
       group_zero_list(gb, &zero);
-    // Counted lists need nothing that this launch makes, and their first launch clears the outputs: the helper starts beside it.
-    if (counted) GEAR_HIP(lane.fork());
-    GEAR_RUN("begin", launch_begin(counted ? nullptr : out->status, failed, out->n_ready, out->loss, zero, dt, jobs, n_jobs, by_rows, s));
+    FirstCounts first;
+    if (counted) first = first_counts(gb, views);
+    GEAR_RUN(counted ? "group_count" : "begin",
+             launch_begin(out->status, failed, out->n_ready, out->loss, zero, dt, jobs, n_jobs, by_rows, counted ? &first : nullptr, s, lane.fork_by()));
   }
-  if (!carried && !local_sort && !counted) GEAR_HIP(lane.fork());
+  if (!carried && !local_sort) GEAR_HIP(lane.fork(true));
   // Carried: the links of the grouping in order, each taken by the next launch that can.
   SideTask task;
   int link = 0;
@@ -775,25 +788,24 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   // after the host has issued the grouping's launches.
   if (!carried && !local_sort) {
     hipStream_t caller = s, s = group_here ? caller : helper;  // the stream of this block's launches
+    const hipEvent_t end = group_here ? nullptr : long_rows ? lane.mark_by() : lane.mark_checked_by();   // left by the last of them
     if (counted) {
-      const StepOutputs outputs = {out->status, failed, out->n_ready, out->loss};
-      const ViewCheck views = {b->img_off, occ_view, B, b->nnz};
-      const int plan_behind = gb.p[2].n > 0 ? gb.p[2].passes : 1;   // how many passes the plan comes behind
-      for (int pass = 0; pass < group_passes(gb); ++pass) {
-        if (pass != plan_behind) GEAR_RUN("group_count", launch_count(gb, pass, outputs, views, s));
-        GEAR_RUN("group_ids", launch_counted_pass(gb, pass, views, plan_args, failed, s));
+      const int passes = group_passes(gb), plan_behind = gb.p[2].n > 0 ? gb.p[2].passes : 1;   // how many passes the plan comes behind
+      for (int pass = 0; pass < passes; ++pass) {
+        if (pass > 0 && pass != plan_behind) GEAR_RUN("group_count", launch_count(gb, pass, s));
+        GEAR_RUN("group_ids", launch_counted_pass(gb, pass, views, plan_args, failed, s, pass + 1 == passes && pass >= plan_behind ? end : nullptr));
         if (pass + 1 == plan_behind) {
           GEAR_HIP(lane.enter(s));
-          GEAR_RUN("accum_plan", launch_segments_count(gb, plan_args, plan_behind, failed, s));
+          GEAR_RUN("accum_plan", launch_segments_count(gb, plan_args, plan_behind, failed, s, pass + 1 == passes ? end : nullptr));
         }
       }
     } else {
       GEAR_RUN("group_ids", launch_check(gb, b->img_off, occ_view, B, b->nnz, failed, out->status, s));
       for (int pass = 0; pass < group_passes(gb); ++pass) GEAR_RUN("group_ids", launch_radix_pass(gb, pass, failed, s));
       if (long_rows) GEAR_HIP(lane.enter(s));
-      GEAR_RUN("accum_plan", launch_segments(gb, &plan_args, failed, s));
+      GEAR_RUN("accum_plan", launch_segments(gb, &plan_args, failed, s, end));
     }
-    if (!group_here) GEAR_HIP(long_rows ? lane.mark() : lane.mark_checked());
+    if (!group_here) GEAR_HIP(long_rows ? lane.mark(true) : lane.mark_checked(true));
   }
 
   // Until its first kernel that changes caller state (the first SGD on a hidden layer's weights), the
@@ -846,9 +858,10 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
       // the same way in both forms.
       if (long_dx) {
         GEAR_RUN("dgrad_gemm_emb", launch_gemm_nt(dt, ws + lay.delta[0], ws + lay.wct[0], B, E2, lay.out_dim[0], EPI_DX,
-                                                  nullptr, dx_dfv, dx_emb, E2, nullptr, nullptr, nullptr, s));
+                                                  nullptr, dx_dfv, dx_emb, E2, nullptr, nullptr, nullptr, s, false, nullptr, false,
+                                                  lane.fork_by()));
         if (gear_status st = links_left()) return st;
-        GEAR_HIP(lane.fork());
+        GEAR_HIP(lane.fork(true));
         {
           hipStream_t s = helper;
           GEAR_RUN("small_sums", launch_param_update(nullptr, 0, 1, columns, n_columns, loss, nullptr, nullptr, opt, failed, s));
@@ -858,12 +871,12 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
         GEAR_RUN(kDgrad[0], launch_gemm_nt(dt, ws + lay.delta[0],
                                            ws + lay.wct[0] + (size_t)E2 * lay.out_dim[0] * lay.act_bytes, B, F - E2,
                                            lay.out_dim[0], EPI_DX, nullptr, dx_dfv, dx_emb, 0, nullptr, nullptr, nullptr, s, false, nullptr,
-                                           wt_tiles_from[0] == E2));
+                                           wt_tiles_from[0] == E2, lane.fork_by()));
       } else {
         const bool takes = gemm_nt_carries(dt, B, F, lay.out_dim[0]);
         GEAR_RUN(kDgrad[0], launch_gemm_nt(dt, ws + lay.delta[0], ws + lay.wct[0], B, F, lay.out_dim[0], EPI_DX,
                                            nullptr, dx_dfv, dx_emb, E2, nullptr, nullptr, nullptr, s, false,
-                                           takes ? passenger() : nullptr, wt_tiles_from[0] == 0));
+                                           takes ? passenger() : nullptr, wt_tiles_from[0] == 0, lane.fork_by()));
         if (gear_status st = links_left()) return st;
       }
     }
@@ -879,18 +892,20 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   // Behind blocks of views the grouping may still be at work: the products fill that time, and the bookkeeping follows them
   // on the caller's stream.
   const bool books_here = one_stream || by_rows;
-  if (!by_rows) GEAR_HIP(lane.fork());
+  const bool ends_here = !out->dbg_img_unique && !out->dbg_img_segoff && !out->dbg_img_perm && !out->dbg_n_img_unique;   // with the last update
+  if (!by_rows) GEAR_HIP(lane.fork(true));
   auto bookkeeping = [&](hipStream_t s) -> gear_status {
     if (!divided && !books_here) GEAR_RUN("embedding_update", launch_embedding_update(emb, false, failed, s));
     BlockSums riding;
     if (as_rows) riding = block_sums_of(rows, lay, *b, ws);
     GEAR_RUN("accumulate", launch_accumulate(*cfg, gb.p[2], plan, dx_dfv, grad_accum, M, out->ready_ids, out->ready_grads,
-                                             divided ? nullptr : &emb, !books_here, as_rows ? &riding : nullptr, failed, s));
+                                             divided ? nullptr : &emb, !books_here, as_rows ? &riding : nullptr, failed, s,
+                                             books_here ? nullptr : lane.mark_by()));
     return GEAR_OK;
   };
   if (!beside && !long_rows) {
     if (gear_status st = bookkeeping(helper)) return st;
-    GEAR_HIP(lane.mark());
+    GEAR_HIP(lane.mark(true));
   }
   // SGD on the hidden layers' weights: split-K wgrad.  With the last of them go the small sums, unless they are done.
   // All layers go out as one launch, in as many ranges of the batch as their partials have room for; a model whose
@@ -933,7 +948,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
     // workgroups get onto the device as the bookkeeping's leave room and are done before it is, so the
     // step ends with the bookkeeping and the join.
     if (first == 0 && long_rows) {
-      if (group_here) GEAR_HIP(lane.mark());
+      if (group_here) GEAR_HIP(lane.mark(false));
       GEAR_HIP(lane.wait(true));
       if (gear_status st = bookkeeping(s)) return st;
     } else if (first == 0) {
@@ -942,7 +957,9 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
     first += n;
     const bool sums_too = first == n_wp && !divided;   // else the helper stream has done them
     GEAR_RUN("param_update", launch_param_update(sp, n, splits, columns, sums_too ? n_columns : 0, sums_too ? loss : LossSum{},
-                                                 sums_too && books_here ? &emb : nullptr, local_sort ? out->n_ready : nullptr, opt, failed, s));
+                                                 sums_too && books_here ? &emb : nullptr, local_sort ? out->n_ready : nullptr, opt, failed, s,
+                                                 first == n_wp && ends_here ? lane.done_by() : nullptr));
+    if (first == n_wp && ends_here) lane.done_left();
   }
   if (!by_rows) GEAR_HIP(lane.wait(true));  // the step ends on the caller's stream
   if (out->dbg_img_unique && b->nnz > 0)

@@ -1,6 +1,7 @@
 // Internal declarations shared by the libgear translation units (gfx950 only).
 #pragma once
 
+#include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 #include <stddef.h>
 #include <stdint.h>
@@ -285,6 +286,16 @@ constexpr int kLossBlocks = 2048;    // most workgroups (and partial sums) of th
 // ------------------------------------------------------------------------------------------------
 // kernel launchers (each defined next to its kernel)
 // ------------------------------------------------------------------------------------------------
+// `stop` (may be NULL) is an event that the launch itself leaves when it ends.  Recorded behind the launch, an event is a packet
+// of its own, which what follows on the stream waits for.
+inline hipError_t leave(hipEvent_t stop, hipStream_t s) { return stop ? hipEventRecord(stop, s) : hipSuccess; }   // no launch to leave it
+template <typename Kernel, typename... Args>
+inline void launch_leaving(hipEvent_t stop, Kernel kernel, dim3 grid, int threads, size_t lds, hipStream_t s, const Args &...args) {
+  if (stop)
+    hipExtLaunchKernelGGL(kernel, grid, dim3((unsigned)threads), (uint32_t)lds, s, nullptr, stop, 0, args...);
+  else
+    hipLaunchKernelGGL(kernel, grid, dim3((unsigned)threads), (uint32_t)lds, s, args...);
+}
 hipError_t launch_fill_normal(void *dst, int dtype, int64_t n_elems, uint64_t seed, uint32_t stream_id,
                               float std, hipStream_t s);
 hipError_t launch_fill_zero(void *dst, size_t bytes, hipStream_t s);
@@ -307,9 +318,16 @@ struct CastJob {
   int tiles_from;
 };
 hipError_t launch_clear(const ZeroList &zero, hipStream_t s);
-// (status NULL: the outputs are cleared elsewhere)
+struct FirstCounts {
+  GroupBatch gb;
+  ViewCheck views;
+  int first_block[kMaxProblems + 1];   // of each list, then of the views
+};
+FirstCounts first_counts(const GroupBatch &gb, const ViewCheck &views);
+void counted_zero_list(const GroupBatch &gb, ZeroList *z);
+// `first` (may be NULL; packed weights only): and what the first passes over lists in counted tiles need, the counts and the views
 hipError_t launch_begin(int32_t *status, int32_t *failed, int32_t *n_ready, float *loss, const ZeroList &zero, int dtype, const CastJob *jobs,
-                        int count, bool packed, hipStream_t s);
+                        int count, bool packed, const FirstCounts *first, hipStream_t s, hipEvent_t stop);
 void group_zero_list(const GroupBatch &gb, ZeroList *z);
 CheckTask check_task(const GroupBatch &gb, const int32_t *img_off, int32_t *occ_view, int B, int nnz, int32_t *failed,
                      int32_t *status);
@@ -324,14 +342,11 @@ hipError_t launch_radix_pass(const GroupBatch &gb, int pass, const int32_t *fail
 // unique ids and their offsets go (of `cap` ids at most); 0: they do not
 int counted_passes(int bits, int n, int cap, int widest);
 int counted_lds_bytes(int digit_bits);
-struct StepOutputs {      // cleared at the start of a step
-  int32_t *status, *failed, *n_ready;
-  float *loss;
-};
-hipError_t launch_count(const GroupBatch &gb, int pass, const StepOutputs &out, const ViewCheck &views, hipStream_t s);   // the first one clears the outputs
-hipError_t launch_counted_pass(const GroupBatch &gb, int pass, const ViewCheck &views, const PlanArgs &args, int32_t *failed, hipStream_t s);
-hipError_t launch_segments_count(const GroupBatch &gb, const PlanArgs &args, int next, int32_t *failed, hipStream_t s);
-hipError_t launch_segments(const GroupBatch &gb, const PlanArgs *args, int32_t *failed, hipStream_t s);
+hipError_t launch_count(const GroupBatch &gb, int pass, hipStream_t s);   // the first passes' counts are the prologue's
+hipError_t launch_counted_pass(const GroupBatch &gb, int pass, const ViewCheck &views, const PlanArgs &args, int32_t *failed, hipStream_t s,
+                               hipEvent_t stop);
+hipError_t launch_segments_count(const GroupBatch &gb, const PlanArgs &args, int next, int32_t *failed, hipStream_t s, hipEvent_t stop);
+hipError_t launch_segments(const GroupBatch &gb, const PlanArgs *args, int32_t *failed, hipStream_t s, hipEvent_t stop = nullptr);
 // distinct ids of a grouped list whose cache entry is older than `expiry`, ascending
 // words (four images each) of the byte map over all images that the expiry filter marks, and tiles
 // of kSortTile words
@@ -360,7 +375,7 @@ enum GemmEpilogue {
 hipError_t launch_gemm_nt(int dtype, const void *A, const void *B, int M, int N, int K, int epilogue,
                           const float *bias, const void *aux, void *out, int split, float *colpart,
                           uint8_t *relu_bits, const int32_t *status, hipStream_t s, bool coarse = false,
-                          const SideTask *side = nullptr, bool tiles = false);
+                          const SideTask *side = nullptr, bool tiles = false, hipEvent_t stop = nullptr);
 // whether such a product without a SideTask takes B in the operand order of the large tiles (`tiles`)
 bool gemm_nt_takes_tiles(int dtype, int M, int N, int K, int epilogue);
 bool gemm_nt_carries(int dtype, int M, int N, int K);   // whether a bias + ReLU or dLoss/dx product of this shape takes a SideTask
@@ -408,11 +423,11 @@ constexpr int kMaxColumnSums = GEAR_MAX_LAYERS + 2;
 struct EmbeddingWork;
 hipError_t launch_param_update(const SplitkProblem *p, int count, int splits, const ColumnSum *c, int n_columns,
                                const LossSum &loss, const EmbeddingWork *emb, int32_t *n_ready, const Optim &opt,
-                               const int32_t *status, hipStream_t s);
+                               const int32_t *status, hipStream_t s, hipEvent_t stop = nullptr);
 // the same products on tiles of moderate size (gemm_tile.hip)
 hipError_t launch_gemm_nt_tile(int dtype, const void *A, const void *B, int M, int N, int K, int epilogue,
                                const float *bias, const void *aux, void *out, int split, float *colpart,
-                               uint8_t *relu_bits, const int32_t *status, hipStream_t s, bool coarse, const SideTask *side);
+                               uint8_t *relu_bits, const int32_t *status, hipStream_t s, bool coarse, const SideTask *side, hipEvent_t stop);
 int nt_tile_colsum_parts(int dtype, int M, int N, bool coarse);
 hipError_t launch_gemm_tn_tile(int dtype, const TnProblem *p, int count, int K, int splits, const int32_t *status,
                                hipStream_t s, const int32_t *k_dev);
@@ -473,7 +488,7 @@ struct BlockSums {
 hipError_t launch_accumulate(const gear_config &cfg, const GroupProblem &img, const AccumPlan &plan,
                              const void *dx_dfv, float *grad_accum, int32_t M, int32_t *ready_ids,
                              float *ready_grads, const EmbeddingWork *emb, bool level2, const BlockSums *sums, const int32_t *status,
-                             hipStream_t s);
+                             hipStream_t s, hipEvent_t stop);
 
 // with level 1 and the counters, beside `count` weight-gradient products on tiles of moderate size
 hipError_t launch_accumulate_wgrad(const gear_config &cfg, const GroupProblem &img, const AccumPlan &plan, const void *dx_dfv,

@@ -600,18 +600,18 @@ bool gemm_nt_carries(int dtype, int M, int N, int K) { return !nt_fills(dtype, M
 
 hipError_t launch_gemm_nt(int dtype, const void *A, const void *B, int M, int N, int K, int epi, const float *bias,
                           const void *aux, void *out, int split, float *colpart, uint8_t *relu_bits,
-                          const int32_t *status, hipStream_t s, bool coarse, const SideTask *side, bool tiles) {
-  if (M <= 0 || N <= 0) return hipSuccess;
+                          const int32_t *status, hipStream_t s, bool coarse, const SideTask *side, bool tiles, hipEvent_t stop) {
+  if (M <= 0 || N <= 0) return leave(stop, s);
   if (tiles && (side || !gemm_nt_takes_tiles(dtype, M, N, K, epi))) return hipErrorInvalidValue;
   if (epi == EPI_MASK_BITS && dtype != GEAR_BF16) return hipErrorInvalidValue;
   const bool narrow = N <= NtNarrow::BN && (epi == EPI_DX || epi == EPI_F32);
   if (side ? !nt_fills(dtype, M, N, K, narrow) : !nt_dma(dtype, M, N, K, narrow))
-    return launch_gemm_nt_tile(dtype, A, B, M, N, K, epi, bias, aux, out, split, colpart, relu_bits, status, s, coarse, side);
+    return launch_gemm_nt_tile(dtype, A, B, M, N, K, epi, bias, aux, out, split, colpart, relu_bits, status, s, coarse, side, stop);
   if (side) return hipErrorInvalidValue;
   const dim3 grid(((M + DM - 1) / DM) * (narrow ? 1 : (N + DN - 1) / DN));
 #define GEAR_DMA(E, ...)                                                                                              \
-  hipLaunchKernelGGL((k_gemm_nt_dma<E, __VA_ARGS__>), grid, dim3(DTHREADS), 0, s, (const bf16_t *)A, (const bf16_t *)B, M, N, K, \
-                     bias, (const bf16_t *)aux, out, split, colpart, relu_bits, status)
+  launch_leaving(stop, k_gemm_nt_dma<E, __VA_ARGS__>, grid, DTHREADS, 0, s, (const bf16_t *)A, (const bf16_t *)B, M, N, K, bias, \
+                 (const bf16_t *)aux, out, split, colpart, relu_bits, status)
   if (tiles) {
     if (epi == EPI_BIAS_RELU)
       GEAR_DMA(EPI_BIAS_RELU, NtWide, true);

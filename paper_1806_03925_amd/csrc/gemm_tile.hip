@@ -407,31 +407,31 @@ long long tiles_of(int M, int N, int bm, int bn) { return (long long)((M + bm - 
 
 template <int EPI, typename C>
 hipError_t run_nt(const void *A, const void *B, int M, int N, int K, const float *bias, const void *aux, void *out, int split,
-                  float *colpart, uint8_t *relu_bits, const int32_t *status, hipStream_t s, const SideTask *side) {
+                  float *colpart, uint8_t *relu_bits, const int32_t *status, hipStream_t s, const SideTask *side, hipEvent_t stop) {
   using T = typename C::T;
   const unsigned tiles = (unsigned)tiles_of(M, N, C::BM, C::BN);
   if constexpr (EPI == EPI_BIAS_RELU || EPI == EPI_DX) {
     if (side) {
-      hipLaunchKernelGGL((k_gemm_nt_tile<EPI, C, true>), dim3(tiles + side->blocks), dim3(kSortBlock), 0, s, (const T *)A,
-                         (const T *)B, M, N, K, bias, (const T *)aux, out, split, colpart, relu_bits, status, *side);
+      launch_leaving(stop, k_gemm_nt_tile<EPI, C, true>, dim3(tiles + side->blocks), kSortBlock, 0, s, (const T *)A, (const T *)B, M, N, K,
+                     bias, (const T *)aux, out, split, colpart, relu_bits, status, *side);
       return hipGetLastError();
     }
   }
   if (side) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((k_gemm_nt_tile<EPI, C>), dim3(tiles), dim3(C::THREADS), 0, s, (const T *)A, (const T *)B, M, N, K, bias,
-                     (const T *)aux, out, split, colpart, relu_bits, status, NoTask{});
+  launch_leaving(stop, k_gemm_nt_tile<EPI, C>, dim3(tiles), C::THREADS, 0, s, (const T *)A, (const T *)B, M, N, K, bias, (const T *)aux,
+                 out, split, colpart, relu_bits, status, NoTask{});
   return hipGetLastError();
 }
 
 template <typename C>
 hipError_t run_nt_any(const void *A, const void *B, int M, int N, int K, int epi, const float *bias, const void *aux, void *out,
-                      int split, float *colpart, uint8_t *relu_bits, const int32_t *status, hipStream_t s, const SideTask *side) {
-#define GEAR_NT(E) run_nt<E, C>(A, B, M, N, K, bias, aux, out, split, colpart, relu_bits, status, s, side)
+                      int split, float *colpart, uint8_t *relu_bits, const int32_t *status, hipStream_t s, const SideTask *side, hipEvent_t stop) {
+#define GEAR_NT(E) run_nt<E, C>(A, B, M, N, K, bias, aux, out, split, colpart, relu_bits, status, s, side, stop)
   switch (epi) {
     case EPI_BIAS_RELU: return GEAR_NT(EPI_BIAS_RELU);
     case EPI_MASK: return GEAR_NT(EPI_MASK);
     case EPI_DX: return GEAR_NT(EPI_DX);
-    case EPI_F32: return run_nt<EPI_F32, std::conditional_t<std::is_same_v<C, F32Big>, F32Pair, C>>(A, B, M, N, K, bias, aux, out, split, colpart, relu_bits, status, s, side);
+    case EPI_F32: return run_nt<EPI_F32, std::conditional_t<std::is_same_v<C, F32Big>, F32Pair, C>>(A, B, M, N, K, bias, aux, out, split, colpart, relu_bits, status, s, side, stop);
     case EPI_MASK_BITS:
       if constexpr (sizeof(typename C::T) == 2) return GEAR_NT(EPI_MASK_BITS);
   }
@@ -487,9 +487,9 @@ int nt_tile_colsum_parts(int dtype, int M, int N, bool coarse) {
 
 hipError_t launch_gemm_nt_tile(int dtype, const void *A, const void *B, int M, int N, int K, int epi, const float *bias,
                                const void *aux, void *out, int split, float *colpart, uint8_t *relu_bits,
-                               const int32_t *status, hipStream_t s, bool coarse, const SideTask *side) {
+                               const int32_t *status, hipStream_t s, bool coarse, const SideTask *side, hipEvent_t stop) {
   const NtShape shape = nt_shape(dtype, M, N, coarse, epi);
-#define GEAR_NT(C) run_nt_any<C>(A, B, M, N, K, epi, bias, aux, out, split, colpart, relu_bits, status, s, side)
+#define GEAR_NT(C) run_nt_any<C>(A, B, M, N, K, epi, bias, aux, out, split, colpart, relu_bits, status, s, side, stop)
   if (dtype == GEAR_BF16) return shape == kWide ? GEAR_NT(Bf16Mid) : shape == kTall ? GEAR_NT(Bf16Tall) : GEAR_NT(Bf16Small);
   return shape == kWide ? GEAR_NT(F32Big) : GEAR_NT(F32Small);
 #undef GEAR_NT

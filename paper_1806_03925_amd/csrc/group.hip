@@ -237,27 +237,7 @@ __global__ void __launch_bounds__(kSortBlock) k_radix_pass(GroupBatch gb, int pa
 
 // 96 registers in the passes and the segments: five waves' worth, which find a place beside four of a block's 96 on a SIMD whatever
 // was there before (with 128 the first pass waited 40 us for one to end).
-// The first of these launches of a step clears what the segments publish in, and the step's outputs.
-__global__ void __launch_bounds__(kSortBlock) k_count(GroupBatch gb, int pass, StepOutputs out, ViewCheck views) {
-  if ((int)blockIdx.y == gb.count) {
-    // the views of the occurrences; a list that is no list is noted by the next launch, since this one clears the word for it
-    for (int i = blockIdx.x * kSortBlock + threadIdx.x; i < views.B; i += gridDim.x * kSortBlock) {
-      int32_t lo, hi;
-      if (view_ok(views, i, lo, hi))
-        for (int j = lo; j < hi; ++j) views.occ_view[j] = i;
-    }
-    if (blockIdx.x != 0) return;
-    const int words = 3 * (radix_tiles(gb.p[gb.count - 1].n) - 1);
-    for (int i = threadIdx.x; i < words; i += kSortBlock) gb.seg_state[i] = 0u;
-    if (threadIdx.x == 0) {
-      gb.tickets[kTickets - 1] = 0;
-      *out.status = 0;
-      *out.failed = 0;
-      *out.n_ready = 0;
-      *out.loss = 0.0f;
-    }
-    return;
-  }
+__global__ void __launch_bounds__(kSortBlock) k_count(GroupBatch gb, int pass) {
   const GroupProblem &p = gb.p[blockIdx.y];
   if (pass >= p.passes || (int)blockIdx.x >= radix_tiles(p.n)) return;
   __builtin_amdgcn_s_setprio(3);
@@ -350,26 +330,54 @@ static int most_tiles(const GroupBatch &gb, int pass) {
   return tiles;
 }
 
-hipError_t launch_count(const GroupBatch &gb, int pass, const StepOutputs &out, const ViewCheck &views, hipStream_t s) {
+static int counted_digits_ok(const GroupBatch &gb) {
   for (int i = 0; i < gb.count; ++i)
-    if (gb.p[i].digit_bits > kCountedDigitBits) return hipErrorInvalidValue;   // counted_pass
+    if (gb.p[i].digit_bits > kCountedDigitBits) return 0;   // counted_pass
+  return 1;
+}
+
+FirstCounts first_counts(const GroupBatch &gb, const ViewCheck &views) {
+  FirstCounts f;
+  f.gb = gb;
+  f.views = views;
+  int blocks = 0;
+  for (int i = 0; i < kMaxProblems; ++i) {
+    f.first_block[i] = blocks;
+    if (i < gb.count) blocks += radix_tiles(gb.p[i].n);
+  }
+  f.first_block[kMaxProblems] = blocks;
+  return f;
+}
+
+// what the segments publish in
+void counted_zero_list(const GroupBatch &gb, ZeroList *z) {
+  z->count = 1;
+  z->p[0] = (uint32_t *)(gb.tickets + kTickets - 1);
+  z->words[0] = 1;
+  const int64_t words = 3 * ((int64_t)radix_tiles(gb.p[gb.count - 1].n) - 1);
+  if (words > 0) z->p[1] = gb.seg_state, z->words[z->count++] = words;
+}
+
+hipError_t launch_count(const GroupBatch &gb, int pass, hipStream_t s) {
+  if (!counted_digits_ok(gb)) return hipErrorInvalidValue;
   const int tiles = most_tiles(gb, pass);
-  if (tiles == 0 && pass > 0) return hipSuccess;
-  hipLaunchKernelGGL(k_count, dim3(tiles < 1 ? 1 : tiles, gb.count + (pass == 0 ? 1 : 0)), dim3(kSortBlock),
-                     widest_radix(gb) * sizeof(int), s, gb, pass, out, views);
+  if (tiles == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_count, dim3(tiles, gb.count), dim3(kSortBlock), widest_radix(gb) * sizeof(int), s, gb, pass);
   return hipGetLastError();
 }
 
-hipError_t launch_counted_pass(const GroupBatch &gb, int pass, const ViewCheck &views, const PlanArgs &args, int32_t *failed, hipStream_t s) {
+hipError_t launch_counted_pass(const GroupBatch &gb, int pass, const ViewCheck &views, const PlanArgs &args, int32_t *failed, hipStream_t s,
+                               hipEvent_t stop) {
+  if (!counted_digits_ok(gb)) return hipErrorInvalidValue;
   const int tiles = most_tiles(gb, pass);
-  if (tiles == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_counted_pass, dim3(tiles, gb.count + (pass == 0 ? 1 : 0)), dim3(kSortBlock), radix_lds_bytes(gb), s, gb, pass,
-                     views, args, failed);
+  if (tiles == 0) return leave(stop, s);
+  launch_leaving(stop, k_counted_pass, dim3(tiles, gb.count + (pass == 0 ? 1 : 0)), kSortBlock, radix_lds_bytes(gb), s, gb, pass, views,
+                 args, failed);
   return hipGetLastError();
 }
 
 // the plan of the last list, and the counts of the others' pass `next` where they have one
-hipError_t launch_segments_count(const GroupBatch &gb, const PlanArgs &args, int next, int32_t *failed, hipStream_t s) {
+hipError_t launch_segments_count(const GroupBatch &gb, const PlanArgs &args, int next, int32_t *failed, hipStream_t s, hipEvent_t stop) {
   int tiles = radix_tiles(gb.p[gb.count - 1].n), others = 0;
   if (tiles < 1) tiles = 1;
   for (int i = 0; i + 1 < gb.count; ++i)
@@ -377,12 +385,12 @@ hipError_t launch_segments_count(const GroupBatch &gb, const PlanArgs &args, int
       others = gb.count - 1;
       if (radix_tiles(gb.p[i].n) > tiles) tiles = radix_tiles(gb.p[i].n);
     }
-  hipLaunchKernelGGL(k_segments_count, dim3(tiles, 1 + others), dim3(kSortBlock), widest_radix(gb) * sizeof(int), s, gb, args, next, failed);
+  launch_leaving(stop, k_segments_count, dim3(tiles, 1 + others), kSortBlock, widest_radix(gb) * sizeof(int), s, gb, args, next, failed);
   return hipGetLastError();
 }
 
 // segments of the last list; with `args` also the plan of the accumulation
-hipError_t launch_segments(const GroupBatch &gb, const PlanArgs *args, int32_t *failed, hipStream_t s) {
+hipError_t launch_segments(const GroupBatch &gb, const PlanArgs *args, int32_t *failed, hipStream_t s, hipEvent_t stop) {
   const int tiles = (int)(((int64_t)gb.p[gb.count - 1].n + kSortTile - 1) / kSortTile);
   // Beside the large products of a long step: few registers (96 instead of 116, of which 14 spill, 60 bytes of scratch), so
   // that a workgroup fits on a product's CU.  The list's length decides, not the products: a long list beside products of
@@ -391,11 +399,11 @@ hipError_t launch_segments(const GroupBatch &gb, const PlanArgs *args, int32_t *
   // room.
   const dim3 grid(tiles < 1 ? 1 : tiles);
   if (!args)
-    hipLaunchKernelGGL((k_segments<false, false>), grid, dim3(kSortBlock), 0, s, gb, PlanArgs{}, failed);
+    launch_leaving(stop, k_segments<false, false>, grid, kSortBlock, 0, s, gb, PlanArgs{}, failed);
   else if (gb.p[gb.count - 1].n > kLongList)
-    hipLaunchKernelGGL((k_segments<true, true>), grid, dim3(kSortBlock), 0, s, gb, *args, failed);
+    launch_leaving(stop, k_segments<true, true>, grid, kSortBlock, 0, s, gb, *args, failed);
   else
-    hipLaunchKernelGGL((k_segments<true, false>), grid, dim3(kSortBlock), 0, s, gb, *args, failed);
+    launch_leaving(stop, k_segments<true, false>, grid, kSortBlock, 0, s, gb, *args, failed);
   return hipGetLastError();
 }
 

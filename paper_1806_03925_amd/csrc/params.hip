@@ -151,7 +151,7 @@ __global__ void __launch_bounds__(256) k_param_update(ParamArgs args, std::condi
 
 hipError_t launch_param_update(const SplitkProblem *p, int count, int splits, const ColumnSum *c, int n_columns,
                                const LossSum &loss, const EmbeddingWork *emb, int32_t *n_ready, const Optim &opt,
-                               const int32_t *status, hipStream_t s) {
+                               const int32_t *status, hipStream_t s, hipEvent_t stop) {
   if (count < 0 || count > GEAR_MAX_LAYERS || splits < 1 || n_columns < 0 || n_columns > kMaxColumnSums)
     return hipErrorInvalidValue;
   ParamArgs args;
@@ -178,11 +178,11 @@ hipError_t launch_param_update(const SplitkProblem *p, int count, int splits, co
     SpanWork spans;
     spans.w = *emb;
     spans.blocks = (embedding_chunks(*emb) + 256 / kWave - 1) / (256 / kWave);
-    hipLaunchKernelGGL(k_param_update<true>, dim3(blocks + 2 * spans.blocks), dim3(256), 0, s, args, spans, opt, status);
+    launch_leaving(stop, k_param_update<true>, dim3(blocks + 2 * spans.blocks), 256, 0, s, args, spans, opt, status);
     return hipGetLastError();
   }
-  if (blocks == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_param_update<false>, dim3(blocks), dim3(256), 0, s, args, NoSpans{}, opt, status);
+  if (blocks == 0) return leave(stop, s);
+  launch_leaving(stop, k_param_update<false>, dim3(blocks), 256, 0, s, args, NoSpans{}, opt, status);
   return hipGetLastError();
 }
 

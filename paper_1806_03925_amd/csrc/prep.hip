@@ -1,6 +1,7 @@
 // Step prologue, one launch: reset the per-step outputs, clear the words that the sorts count in, and make the operand
-// copies of the weights.
-#include "gear_internal.hpp"
+// copies of the weights.  Ahead of sorts in counted tiles also the counts of their first passes, which a launch of its own on the
+// other stream had before: that one began 5 us into the step, behind an event of its own, and now the first pass does.
+#include "group_device.hpp"
 
 namespace gear {
 namespace {
@@ -8,7 +9,7 @@ namespace {
 // wc = W as MLP operands [rows x cols], wct = its transpose [cols x rows]; both from the fp32 master, row-major or `packed`.
 // One launch serves all layers: a workgroup owns a 32 x 32 tile of one of them; those behind the tiles clear words.
 struct BeginArgs {
-  int count, cast_blocks;
+  int count, cast_blocks, clear_blocks;
   CastJob job[GEAR_MAX_LAYERS];
   int first_block[GEAR_MAX_LAYERS];
   ZeroList zero;
@@ -60,28 +61,51 @@ __device__ __forceinline__ void put_tiles(bf16_t *dst, int K, int row0, int r, i
   *reinterpret_cast<uint4 *>(dst + (size_t)row0 * K + (k0 / 16 + piece / 2) * 512 + ((piece & 1) * 32 + r) * 8) = make_uint4(w[0], w[1], w[2], w[3]);
 }
 
-template <typename T, bool PACKED>
-__global__ void __launch_bounds__(256) k_begin(BeginArgs args, int32_t *status, int32_t *failed, int32_t *n_ready, float *loss) {
-  if (blockIdx.x == 0 && threadIdx.x == 0 && status) {
+struct NoCounts {};
+template <typename T, bool PACKED, bool COUNT>
+__global__ void __launch_bounds__(256) k_begin(BeginArgs args, std::conditional_t<COUNT, FirstCounts, NoCounts> first, int32_t *status,
+                                               int32_t *failed, int32_t *n_ready, float *loss) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
     *status = 0;
     *failed = 0;
     *n_ready = 0;
     *loss = 0.0f;
   }
-  if ((int)blockIdx.x >= args.cast_blocks) {
-    clear_words(args.zero, (int64_t)(blockIdx.x - args.cast_blocks) * 256 + threadIdx.x,
-                (int64_t)(gridDim.x - args.cast_blocks) * 256);
+  int block = blockIdx.x;
+  if constexpr (COUNT) {   // ahead of the rest: they are the longest
+    extern __shared__ int hist[];
+    static_assert(kSortBlock == 256, "one size of workgroup");
+    const int counts = first.first_block[kMaxProblems], views = (first.views.B + 255) / 256;
+    if (block < counts) {
+      int list = 0;
+      for (int i = 1; i < kMaxProblems; ++i)
+        if (block >= first.first_block[i]) list = i;
+      return count_tile(first.gb.p[list], 0, block - first.first_block[list], hist);
+    }
+    block -= counts;
+    if (block < views) {
+      // the views of the occurrences; a list that is no list is noted by the next launch, since this one clears the word for it
+      const int i = block * 256 + threadIdx.x;
+      int32_t lo, hi;
+      if (i < first.views.B && view_ok(first.views, i, lo, hi))
+        for (int j = lo; j < hi; ++j) first.views.occ_view[j] = i;
+      return;
+    }
+    block -= views;
+  }
+  if (block >= args.cast_blocks) {
+    clear_words(args.zero, (int64_t)(block - args.cast_blocks) * 256 + threadIdx.x, (int64_t)args.clear_blocks * 256);
     return;
   }
   __shared__ float tile[32][33];
   int which = 0;
   for (int i = 1; i < args.count; ++i)
-    if ((int)blockIdx.x >= args.first_block[i]) which = i;
+    if (block >= args.first_block[i]) which = i;
   const int rows = args.job[which].rows, cols = args.job[which].cols;
   const float *__restrict__ w = args.job[which].w;
   T *__restrict__ wc = static_cast<T *>(args.job[which].wc);
   T *__restrict__ wct = static_cast<T *>(args.job[which].wct);
-  const int local = blockIdx.x - args.first_block[which], col_tiles = (cols + 31) / 32;
+  const int local = block - args.first_block[which], col_tiles = (cols + 31) / 32;
   const int c0 = (local % col_tiles) * 32, r0 = (local / col_tiles) * 32;
   const bool tiles = !PACKED && args.job[which].tiles, tiles_t = !PACKED && c0 >= args.job[which].tiles_from;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8
@@ -133,8 +157,8 @@ hipError_t launch_clear(const ZeroList &zero, hipStream_t s) {
 }
 
 hipError_t launch_begin(int32_t *status, int32_t *failed, int32_t *n_ready, float *loss, const ZeroList &zero, int dtype, const CastJob *jobs,
-                        int count, bool packed, hipStream_t s) {
-  if (count < 0 || count > GEAR_MAX_LAYERS) return hipErrorInvalidValue;
+                        int count, bool packed, const FirstCounts *first, hipStream_t s, hipEvent_t stop) {
+  if (count < 0 || count > GEAR_MAX_LAYERS || (first && !packed)) return hipErrorInvalidValue;
   BeginArgs args;
   args.count = count;
   args.zero = zero;
@@ -147,18 +171,29 @@ hipError_t launch_begin(int32_t *status, int32_t *failed, int32_t *n_ready, floa
     args.first_block[i] = args.cast_blocks;
     if (i < count) args.cast_blocks += ((jobs[i].cols + 31) / 32) * ((jobs[i].rows + 31) / 32);
   }
-  const dim3 grid((unsigned)(args.cast_blocks + clear_blocks(zero)));
-#define GEAR_BEGIN(T, P) hipLaunchKernelGGL((k_begin<T, P>), grid, dim3(256), 0, s, args, status, failed, n_ready, loss)
+  args.clear_blocks = clear_blocks(zero);
+  int blocks = args.cast_blocks + args.clear_blocks;
+  size_t lds = 0;
+  if (first) {
+    blocks += first->first_block[kMaxProblems] + (first->views.B + 255) / 256;
+    for (int i = 0; i < first->gb.count; ++i) lds = max(lds, sizeof(int) << first->gb.p[i].digit_bits);
+  }
+#define GEAR_BEGIN(T, P, C, FIRST) \
+  launch_leaving(stop, k_begin<T, P, C>, dim3((unsigned)blocks), 256, lds, s, args, FIRST, status, failed, n_ready, loss)
   if (dtype == GEAR_BF16) {
-    if (packed)
-      GEAR_BEGIN(bf16_t, true);
+    if (first)
+      GEAR_BEGIN(bf16_t, true, true, *first);
+    else if (packed)
+      GEAR_BEGIN(bf16_t, true, false, NoCounts{});
     else
-      GEAR_BEGIN(bf16_t, false);
+      GEAR_BEGIN(bf16_t, false, false, NoCounts{});
   } else {
-    if (packed)
-      GEAR_BEGIN(float, true);
+    if (first)
+      GEAR_BEGIN(float, true, true, *first);
+    else if (packed)
+      GEAR_BEGIN(float, true, false, NoCounts{});
     else
-      GEAR_BEGIN(float, false);
+      GEAR_BEGIN(float, false, false, NoCounts{});
   }
 #undef GEAR_BEGIN
   return hipGetLastError();
