@@ -87,10 +87,10 @@ __device__ __forceinline__ void round4(float (&)[4], float) {}
 
 // acc[j][i] += W[16 (tile0 + j) .. + 15][0 .. K) (a + 16 i rows)^T: lane (q, r) ends with columns 16 (tile0 + j) + 4 q .. + 3 of row
 // 16 i + r.  `w` is in operand order, `act` the lane's place in the first activation row.  AHEAD k-steps of weights are in
-// flight: an L2 latency is one to two k-steps of products.
-template <typename T, int MT, int NT, int AHEAD>
+// flight: an L2 latency is one to two k-steps of products.  `meet`: called once, when the first of them are.
+template <typename T, int MT, int NT, int AHEAD, typename Meet>
 __device__ __forceinline__ void rows_product(f32x4_v (&acc)[NT][MT], const unsigned char *act, int stride, const void *w, int N,
-                                             int K, int tile0, int q, int r) {
+                                             int K, int tile0, int q, int r, Meet meet) {
   constexpr int ES = (int)sizeof(T), SK = Step<T>::K;
   const int steps = K / SK, step_bytes = 64 * N;   // all rows' 64 bytes of a k-step lie together
   // a step's place is a scalar offset, a lane's 32 bits: with 64-bit addresses per lane and tile the registers would not do
@@ -121,6 +121,7 @@ __device__ __forceinline__ void rows_product(f32x4_v (&acc)[NT][MT], const unsig
 #pragma unroll
     for (int d = 0; d < AHEAD; ++d) weights(wf[d], d);
   }
+  meet();
   int s0 = 0;
   for (; s0 + AHEAD <= steps; s0 += AHEAD) {
 #pragma unroll
@@ -159,10 +160,10 @@ __device__ __forceinline__ void rows_product(f32x4_v (&acc)[NT][MT], const unsig
 
 enum RowsEpi { ROWS_FORWARD, ROWS_BACK, ROWS_DX };
 
-template <typename T, int MT, int NT, int EPI>
+template <typename T, int MT, int NT, int EPI, typename Meet>
 __device__ __forceinline__ void rows_tiles_of(const RowsArgs &p, unsigned char *lds, const RowsBuf &in, const RowsBuf &out,
                                               const void *w, int N, int K, const float *bias, T *global, int row0, int tile0,
-                                              int lane) {
+                                              int lane, Meet meet) {
   constexpr int AHEAD = MT == 1 ? 4 : 2;
   const int q = lane >> 4, r = lane & 15;
   float b[NT][4];
@@ -181,7 +182,7 @@ __device__ __forceinline__ void rows_tiles_of(const RowsArgs &p, unsigned char *
     for (int i = 0; i < MT; ++i)
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[j][i][e] = 0.0f;
-  rows_product<T, MT, NT, AHEAD>(acc, lds + in.at + r * in.stride + q * 16, in.stride, w, N, K, tile0, q, r);
+  rows_product<T, MT, NT, AHEAD>(acc, lds + in.at + r * in.stride + q * 16, in.stride, w, N, K, tile0, q, r, meet);
 #pragma unroll
   for (int j = 0; j < NT; ++j) {
     const int n = 16 * (tile0 + j) + 4 * q;
@@ -224,20 +225,27 @@ __device__ __forceinline__ void rows_tiles_of(const RowsArgs &p, unsigned char *
 
 // One layer's product by the whole workgroup: the first N / 16 % 8 of eight shares have a column tile more (shares w and w + 4
 // are on one SIMD, so those of 36 tiles have nine each).  The workgroups of an XCD start with different shares, so that its
-// L2 is not asked for the same lines by all of them at once.
-template <typename T, int MT, int EPI>
+// L2 is not asked for the same lines by all of them at once.  `meet`: what has to come between the launch's earlier phases and the
+// first read of `in`, by every wavefront once; its first weights are on their way meanwhile.
+template <typename T, int MT, int EPI, typename Meet>
 __device__ __forceinline__ void rows_layer(const RowsArgs &p, unsigned char *lds, const RowsBuf &in, const RowsBuf &out, const void *w,
-                                           int N, int K, const float *bias, T *global, int row0, int wave, int lane) {
+                                           int N, int K, const float *bias, T *global, int row0, int wave, int lane, Meet meet) {
   const int tiles = (N + 15) / 16, least = tiles / kRowsWaves, more = tiles % kRowsWaves;
   const int share = (wave + blockIdx.x / kXcds) % kRowsWaves;
   int count = least + (share < more ? 1 : 0), tile = share * least + min(share, more);
   constexpr int MOST = MT == 4 ? (EPI == ROWS_FORWARD ? 4 : 5) : 3;   // column tiles at a time: registers
+  bool met = false;
+  auto meet_once = [&]() {
+    if (!met) meet();
+    met = true;
+  };
+  if (count == 0) meet();
   while (count > 0) {
     const int parts = (count + MOST - 1) / MOST, n = (count + parts - 1) / parts;
     switch (n) {
 #define GEAR_TILES(NT)                                                                                          \
   case NT:                                                                                                      \
-    if constexpr (NT <= MOST) rows_tiles_of<T, MT, NT, EPI>(p, lds, in, out, w, N, K, bias, global, row0, tile, lane); \
+    if constexpr (NT <= MOST) rows_tiles_of<T, MT, NT, EPI>(p, lds, in, out, w, N, K, bias, global, row0, tile, lane, meet_once); \
     break;
       GEAR_TILES(1)
       GEAR_TILES(2)
@@ -522,16 +530,19 @@ __global__ void __launch_bounds__(kRowsThreads, MT == 4 ? 2 : MT == 2 && sizeof(
 
   rows_gather<T, R>(p, lds, local.failed, local.plan.status, row0, wave, lane);
   zero_pad<T, R>(lds, p.x_buf, p.F, tid);
-  __syncthreads();
-  const RowsBuf *in = &p.x_buf;
+  // A layer's activations are whole in LDS behind the barrier that begins the next phase.
+  auto whole = [&](int l) {
+    __syncthreads();
+    if constexpr (sizeof(T) == 2)
+      if (l >= 0) copy_out<R>(lds, p.layer[l].buf, p.layer[l].out, static_cast<bf16_t *>(p.layer[l].h), row0, p.B, wave, lane);
+  };
   for (int l = 0; l + 1 < p.L; ++l) {
     const RowsLayer &a = p.layer[l];
-    rows_layer<T, MT, ROWS_FORWARD>(p, lds, *in, a.buf, a.w, a.out, a.in, a.bias, static_cast<T *>(a.h), row0, wave, lane);
+    rows_layer<T, MT, ROWS_FORWARD>(p, lds, l == 0 ? p.x_buf : p.layer[l - 1].buf, a.buf, a.w, a.out, a.in, a.bias, static_cast<T *>(a.h), row0,
+                                    wave, lane, [&]() { whole(l - 1); });
     zero_pad<T, R>(lds, a.buf, a.out, tid);
-    __syncthreads();
-    if constexpr (sizeof(T) == 2) copy_out<R>(lds, a.buf, a.out, static_cast<bf16_t *>(a.h), row0, p.B, wave, lane);
-    in = &a.buf;
   }
+  whole(p.L - 2);
   const RowsLayer &last = p.layer[p.L - 2];
   rows_logit<T, R>(p, lds, last.buf, s_w, y, b0, s_dz, s_red, row0, wave, lane);
   __syncthreads();
@@ -544,16 +555,16 @@ __global__ void __launch_bounds__(kRowsThreads, MT == 4 ? 2 : MT == 2 && sizeof(
   }
   rows_columns<T, R, true>(p, lds, last.buf, p.H, static_cast<T *>(last.delta), last.colsum + (size_t)block * p.H,
                            p.part_w + (size_t)block * p.H, s_w, s_dz, scratch, row0, tid);
-  __syncthreads();
+  // The deltas are whole behind the barrier in there, and behind the one in the loop, ahead of which the scratch is read.
+  const auto nothing = []() {};
   for (int l = p.L - 2; l > 0; --l) {
     const RowsLayer &a = p.layer[l], &below = p.layer[l - 1];
-    rows_layer<T, MT, ROWS_BACK>(p, lds, a.buf, below.buf, a.wt, a.in, a.out, nullptr, static_cast<T *>(below.delta), row0, wave, lane);
+    rows_layer<T, MT, ROWS_BACK>(p, lds, a.buf, below.buf, a.wt, a.in, a.out, nullptr, static_cast<T *>(below.delta), row0, wave, lane, nothing);
     __syncthreads();
     rows_columns<T, R, false>(p, lds, below.buf, a.in, static_cast<T *>(below.delta), below.colsum + (size_t)block * a.in, nullptr,
                               nullptr, nullptr, scratch, row0, tid);
-    __syncthreads();   // the scratch is used again
   }
-  rows_layer<T, MT, ROWS_DX>(p, lds, p.layer[0].buf, p.layer[0].buf, p.layer[0].wt, p.F, p.layer[0].out, nullptr, nullptr, row0, wave, lane);
+  rows_layer<T, MT, ROWS_DX>(p, lds, p.layer[0].buf, p.layer[0].buf, p.layer[0].wt, p.F, p.layer[0].out, nullptr, nullptr, row0, wave, lane, nothing);
 }
 
 template <typename T, int MT> hipError_t run_rows(const RowsArgs &a, const LocalTask &local, const RowsPlan &plan, hipStream_t s) {
