@@ -50,7 +50,7 @@ k_accumulate(AccumPlan plan, const GT *__restrict__ dx, int D, float *__restrict
     block -= emb.sum_blocks;
     blocks -= emb.sum_blocks;
   }
-  accumulate_units<GT, AT>(plan, dx, D, accum, M, ready_ids, ready_grads, block, blocks, threadIdx.x, blockDim.x);
+  accumulate_units<GT, AT, false>(plan, LocalState{}, dx, D, accum, M, ready_ids, ready_grads, block, blocks, threadIdx.x, blockDim.x);
 }
 
 // dfv_cache[ids[r]] = rows[r]; one wavefront per row, 16-byte pieces
@@ -93,7 +93,7 @@ hipError_t launch_accumulate(const gear_config &cfg, const GroupProblem &img, co
     work.sum_blocks = sums ? (int)((block_sums_threads(*sums) + threads - 1) / threads) : 0;
     blocks += 2 * work.blocks + work.count_blocks + work.sum_blocks;
   }
-  if (sums && (!emb || level2 || plan.row_at)) return hipErrorInvalidValue;
+  if ((sums && (!emb || level2 || plan.row_at)) || plan.local.parts) return hipErrorInvalidValue;
 #define GEAR_ACC(T, R, AT, EMB, SUMS)                                                                                            \
   launch_leaving(stop, k_accumulate<T, R, AT>, dim3(blocks), threads, 0, s, plan, (const T *)dx_dfv, D, grad_accum, M, ready_ids, \
                  ready_grads, EMB, SUMS, status)

@@ -645,6 +645,9 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   // 192 -> 128, 10 000 views 97 / 110; 96 -> 64 fp32, 16 384 106 / 127.  The sums are 1 to 4 of it.
   const bool by_rows = planned && (is_short || !out->one_stream), as_rows = planned && !by_rows;
   const bool local_sort = by_rows && is_short, long_rows = by_rows && !is_short;
+  const bool beside = local_sort && !first_choice.large && one_group;   // accumulation and weight gradients are one launch
+  const bool no_prologue = beside && rows.direct;
+  rows.direct = no_prologue;
   // Every tile reads the counts of all, so very long lists go back to tiles that look back (us a step, look back / counted, of
   // 64-view blocks: 576 -> 512 -> 256 bf16, 327 000 images of 16 384 views 221 / 229; 192 -> 128, 290 000 of 20 000 167 / 170, 785 000 of
   // 16 384 262 / 317.  Below: 239 000 of 8000 149 / 137, 158 000 of 4000 views of 576 -> 512 -> 256 152 / 155, 59 000 of 2000 99 / 93, 54 000 of
@@ -695,6 +698,9 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   plan.row_scale = (float *)(ws + lay.row_scale);
   plan.n_units = (int32_t *)(ws + lay.n_units);
   plan.row_at = local_sort ? gb.p[2].perm : nullptr;
+  plan.local = no_prologue ? local_result(rows, gb, b->nnz, out->ready_cap) : LocalResult{};
+  LocalOutputs local_out = {};
+  if (local_sort) local_out = LocalOutputs{plan.local, out->status, out->n_ready, out->loss};
   const PlanArgs plan_args = {plan, occ_view, b->img_off, counts, M, out->ready_cap, out->n_ready, out->status};
   // Not carried: what depends only on ids and counters (the check of the ids, the grouping, the accumulation plan) runs on
   // the helper stream while the main stream gathers and runs the forward pass.  The
@@ -732,7 +738,8 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
       group_zero_list(gb, &zero);
     FirstCounts first;
     if (counted) first = first_counts(gb, views);
-    GEAR_RUN(counted ? "group_count" : "begin",
+    if (!no_prologue)
+      GEAR_RUN(counted ? "group_count" : "begin",
              launch_begin(out->status, failed, out->n_ready, out->loss, zero, dt, jobs, n_jobs, by_rows, counted ? &first : nullptr, s, lane.fork_by()));
   }
   if (!carried && !local_sort) GEAR_HIP(lane.fork(true));
@@ -763,7 +770,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   void *dx_dfv = ws + lay.dx_dfv;
   if (by_rows) {
     LocalTask local = {};
-    if (local_sort) local = local_task(rows, gb, plan_args, failed);
+    if (local_sort) local = local_task(rows, gb, plan_args, views, failed);
     hipStream_t caller = s;
     {
       hipStream_t s = group_here ? helper : caller;
@@ -864,7 +871,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
         GEAR_HIP(lane.fork(true));
         {
           hipStream_t s = helper;
-          GEAR_RUN("small_sums", launch_param_update(nullptr, 0, 1, columns, n_columns, loss, nullptr, nullptr, opt, failed, s));
+          GEAR_RUN("small_sums", launch_param_update(nullptr, 0, 1, columns, n_columns, loss, nullptr, LocalOutputs{}, opt, failed, s));
           GEAR_RUN("embedding_update", launch_embedding_update(emb, true, failed, s));
         }
         divided = true;
@@ -888,7 +895,6 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   // they hold their CUs before the bookkeeping's many small workgroups arrive and fill what is
   // left; a product arriving later would wait until all of those have been placed.
   // In blocks of views the two are one launch where the products go on small tiles in one group.
-  const bool beside = local_sort && !first_choice.large && one_group;
   // Behind blocks of views the grouping may still be at work: the products fill that time, and the bookkeeping follows them
   // on the caller's stream.
   const bool books_here = one_stream || by_rows;
@@ -957,18 +963,21 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
     first += n;
     const bool sums_too = first == n_wp && !divided;   // else the helper stream has done them
     GEAR_RUN("param_update", launch_param_update(sp, n, splits, columns, sums_too ? n_columns : 0, sums_too ? loss : LossSum{},
-                                                 sums_too && books_here ? &emb : nullptr, local_sort ? out->n_ready : nullptr, opt, failed, s,
+                                                 sums_too && books_here ? &emb : nullptr, local_out, opt, failed, s,
                                                  first == n_wp && ends_here ? lane.done_by() : nullptr));
     if (first == n_wp && ends_here) lane.done_left();
   }
   if (!by_rows) GEAR_HIP(lane.wait(true));  // the step ends on the caller's stream
-  if (out->dbg_img_unique && b->nnz > 0)
+  if (no_prologue && !ends_here)
+    GEAR_RUN("grouping_out", launch_unique(plan.local, gb.p[2].unique, gb.p[2].segoff, b->nnz, out->dbg_img_unique, out->dbg_img_segoff,
+                                           out->dbg_n_img_unique, s));
+  if (!no_prologue && out->dbg_img_unique && b->nnz > 0)
     GEAR_HIP(hipMemcpyAsync(out->dbg_img_unique, gb.p[2].unique, (size_t)b->nnz * 4, hipMemcpyDeviceToDevice, s));
-  if (out->dbg_img_segoff)
+  if (!no_prologue && out->dbg_img_segoff)
     GEAR_HIP(hipMemcpyAsync(out->dbg_img_segoff, gb.p[2].segoff, ((size_t)b->nnz + 1) * 4, hipMemcpyDeviceToDevice, s));
   if (out->dbg_img_perm && b->nnz > 0)
     GEAR_HIP(hipMemcpyAsync(out->dbg_img_perm, gb.p[2].perm, (size_t)b->nnz * 4, hipMemcpyDeviceToDevice, s));
-  if (out->dbg_n_img_unique)
+  if (!no_prologue && out->dbg_n_img_unique)
     GEAR_HIP(hipMemcpyAsync(out->dbg_n_img_unique, gb.p[2].n_unique, 4, hipMemcpyDeviceToDevice, s));
   return GEAR_OK;
 }
@@ -1082,7 +1091,7 @@ gear_status gear_gemm(int32_t dtype, int32_t form, const void *A, const void *B,
     const Optim minus = {-1.0f, 0.0f, 0.0f, 0.0f, 1.0f, 0};   // out = 0 - (-1) * sum of the partials
     const Moments none = {nullptr, nullptr};
     const SplitkProblem sum = {partial, (float *)out, none, (int64_t)M * N};
-    GEAR_HIP(launch_param_update(&sum, 1, splits, nullptr, 0, LossSum{}, nullptr, nullptr, minus, status, s));
+    GEAR_HIP(launch_param_update(&sum, 1, splits, nullptr, 0, LossSum{}, nullptr, LocalOutputs{}, minus, status, s));
   } else {
     return GEAR_ERR_INVALID;
   }

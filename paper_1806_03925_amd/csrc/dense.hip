@@ -150,7 +150,7 @@ gear_status dense_backward(const gear_dense_config *cfg, const float *raw, float
   const Optim sgd = {lr, 0.0f, 0.0f, 0.0f, 1.0f, 0};
   const Moments none = {nullptr, nullptr};
   const SplitkProblem sum = {partial, wd, none, (int64_t)cfg->dfv_dim * cfg->raw_dim};
-  DENSE_HIP(launch_param_update(&sum, 1, splits, nullptr, 0, LossSum{}, nullptr, nullptr, sgd, status, s));
+  DENSE_HIP(launch_param_update(&sum, 1, splits, nullptr, 0, LossSum{}, nullptr, LocalOutputs{}, sgd, status, s));
   return GEAR_OK;
 }
 }  // namespace

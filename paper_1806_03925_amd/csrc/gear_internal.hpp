@@ -187,12 +187,29 @@ struct UnitDesc {         // one workgroup's share of the accumulation (32 bytes
   int32_t pad;
 };
 
+// What the workgroups that sort short lists in LDS (local_group.hpp) leave where a step has no prologue: none of them looks at what another
+// one does, so that nothing has to be cleared ahead of their launch.  Who reads their plan adds up what the parts of the images count
+// (local_parts.hpp).
+struct PartCounts {
+  int32_t below;          // ids of the list in lower parts: the part's units begin at that place
+  int32_t heads, units, emits;
+};
+constexpr int kMaxParts = 32;
+constexpr int kCodeGroup = 64;
+struct LocalResult {
+  PartCounts *parts;      // [n_parts], 16-byte aligned; NULL: not so
+  uint8_t *codes;         // [n_codes up to a whole group, 64-byte aligned] whether a workgroup has found ids or offsets that are wrong
+  int parts_log2, n_parts, n_codes;   // of the parts, which are a power of two
+  int ready_cap;          // -1: more emissions than there is room for cannot be
+};
+
 struct AccumPlan {
   UnitDesc *units;       // [nnz]
   int32_t *row_view;     // [nnz] view that owns the occurrence at each sorted position
   float *row_scale;      // [nnz] 1 / (images of that view): backward of the mean
   const int32_t *row_at; // [nnz] where the two are by position in the batch: that of each sorted one (else NULL)
   int32_t *n_units;      // [1]
+  LocalResult local;     // with it units lie part by part, their slots count from the part's first emission, and n_units is not there
 };
 
 // ---- tasks of the grouping (group.hip) ----
@@ -241,11 +258,16 @@ struct LocalList {
 struct LocalTask {
   LocalList list[kMaxProblems];          // segments are made of the last one
   PlanArgs plan;
+  ViewCheck views;
   int32_t *unique, *segoff, *n_unique;   // of the last list; the first two may be NULL
-  uint32_t *state;                       // [parts][3] what the parts of the last list publish
+  // where the step has a prologue, which clears them: what the parts of the last list publish ([parts][3]), and their ticket
+  uint32_t *state;
   int32_t *ticket, *failed;
   int blocks, room;                      // workgroups; items that LDS has room for
 };
+// the distinct ids and their segments from where the parts have left them to where one after the other belongs (each may be NULL)
+hipError_t launch_unique(const LocalResult &local, const int32_t *unique, const int32_t *segoff, int n, int32_t *out_unique, int32_t *out_segoff,
+                         int32_t *out_n, hipStream_t s);
 
 // ------------------------------------------------------------------------------------------------
 // workspace layout (byte offsets from a 256-byte aligned base)
@@ -418,11 +440,16 @@ struct LossSum {   // *loss = (sum of the partial sums) / B; parts = 0: not want
   int parts, B;
 };
 constexpr int kMaxColumnSums = GEAR_MAX_LAYERS + 2;
-// all of that in one launch, and level 2 of an embedding update (may be NULL); n_ready (may be NULL) is cleared if the step
-// has failed
+// n_ready (may be NULL) is cleared if the step has failed; with local.parts, all outputs are written here.
+struct LocalOutputs {
+  LocalResult local;
+  int32_t *status, *n_ready;
+  float *loss;
+};
+// all of that in one launch, and level 2 of an embedding update (may be NULL)
 struct EmbeddingWork;
 hipError_t launch_param_update(const SplitkProblem *p, int count, int splits, const ColumnSum *c, int n_columns,
-                               const LossSum &loss, const EmbeddingWork *emb, int32_t *n_ready, const Optim &opt,
+                               const LossSum &loss, const EmbeddingWork *emb, const LocalOutputs &local, const Optim &opt,
                                const int32_t *status, hipStream_t s, hipEvent_t stop = nullptr);
 // the same products on tiles of moderate size (gemm_tile.hip)
 hipError_t launch_gemm_nt_tile(int dtype, const void *A, const void *B, int M, int N, int K, int epilogue,

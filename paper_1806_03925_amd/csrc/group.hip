@@ -146,6 +146,33 @@ hipError_t launch_stamp(int32_t *stamp, int64_t n_images, const int32_t *ids, in
   return hipGetLastError();
 }
 
+namespace {
+// by one workgroup: a copy for callers who look at the grouping itself
+__global__ void __launch_bounds__(256) k_unique(LocalResult local, const int32_t *unique, const int32_t *segoff, int n, int32_t *out_unique,
+                                                int32_t *out_segoff, int32_t *out_n) {
+  int at = 0;
+  for (int part = 0; part < local.n_parts; ++part) {
+    const PartCounts c = local.parts[part];
+    for (int i = threadIdx.x; i < c.heads; i += 256) {
+      if (out_unique) out_unique[at + i] = unique[c.below + i];
+      if (out_segoff) out_segoff[at + i] = segoff[c.below + i];
+    }
+    at += c.heads;
+  }
+  if (threadIdx.x == 0) {
+    if (out_segoff) out_segoff[at] = n;
+    if (out_n) *out_n = at;
+  }
+}
+}  // namespace
+
+hipError_t launch_unique(const LocalResult &local, const int32_t *unique, const int32_t *segoff, int n, int32_t *out_unique, int32_t *out_segoff,
+                         int32_t *out_n, hipStream_t s) {
+  if ((out_unique && !unique) || (out_segoff && !segoff)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_unique, dim3(1), dim3(256), 0, s, local, unique, segoff, n, out_unique, out_segoff, out_n);
+  return hipGetLastError();
+}
+
 // What the grouping counts in has to be zero first.
 void group_zero_list(const GroupBatch &gb, ZeroList *z) {
   z->count = 0;

@@ -192,15 +192,14 @@ __device__ __forceinline__ bool local_popular(const LocalList &p, uint32_t *item
 // The part's ids, in order, into items[0 .. m).  Returns m; *below = ids of the list in lower ranges.
 // A thread owns `per` consecutive positions, a multiple of four: it counts its own, and writes them when it knows where.
 // Loads go out in batches whose addresses are clamped instead of branched around: the ids are cold.
-__device__ __forceinline__ int local_select(const LocalTask &t, const LocalList &p, int part, uint32_t *items,
-                                            unsigned long long *smem, int *below) {
+__device__ __forceinline__ int local_select(const LocalList &p, int part, uint32_t *items, unsigned long long *smem, int *below, bool *bad_ids) {
   constexpr int U = 5;   // quadruples of ids in flight
   const int tid = threadIdx.x, n = p.n, low_bits = p.bits - p.parts_log2;
   const int per = (n + 4 * kLocalThreads - 1) / (4 * kLocalThreads) * 4, p0 = min(n, tid * per), p1 = min(n, p0 + per);
   const int quads = ((uintptr_t)p.keys_in & 15u) == 0 ? n & ~3 : 0;   // positions that are read four at a time
   const int q1 = min(p1, quads), rest = max(p0, quads);
   unsigned mine = 0, lower = 0;
-  bool bad = false;
+  bool bad = *bad_ids;
   auto count = [&](int32_t key) {
     const int range = (int)((uint32_t)key >> low_bits);
     bad |= key < 0 || (int64_t)key >= p.range;
@@ -217,11 +216,11 @@ __device__ __forceinline__ int local_select(const LocalTask &t, const LocalList 
         if (i + 4 * k < per && p0 + i + 4 * k < q1) count(key[k].x), count(key[k].y), count(key[k].z), count(key[k].w);
     }
   GEAR_ROLLED for (int q = rest; q < p1; ++q) count(p.keys_in[q]);
-  if (bad) flag(t.failed, t.plan.status, GEAR_ERR_RANGE);
-  unsigned long long all;
-  int at = (int)(uint32_t)local_scan((unsigned long long)mine | (unsigned long long)lower << 32, &all, smem);
+  unsigned long long all;   // a list has less than 65 536 ids
+  int at = (int)(uint32_t)local_scan((unsigned long long)mine | (unsigned long long)lower << 32 | (unsigned long long)(bad ? 1 : 0) << 48, &all, smem);
   const int m = (int)(uint32_t)all;
-  *below = (int)(all >> 32);
+  *below = (int)(all >> 32) & 0xffff;
+  *bad_ids = (all >> 48) != 0ull;
   auto keep = [&](int32_t key, int q) {
     if ((int)((uint32_t)key >> low_bits) == part) {
       items[at] = ((uint32_t)key & ((1u << low_bits) - 1u)) << p.value_bits | (uint32_t)q;
@@ -248,8 +247,8 @@ __device__ __forceinline__ int local_select(const LocalTask &t, const LocalList 
 
 // Segments of the part's ids and the plan of the accumulation (group_device.hpp has the rules): a thread owns `per`
 // consecutive positions, at most 64.  cnt: room for the counters of the items' images.
-// FITS: the counters too are in LDS.
-template <bool FITS>
+// FITS: the counters too are in LDS.  PARTS: the part leaves what it counts to those who read the plan.
+template <bool FITS, bool PARTS>
 __device__ __forceinline__ void local_plan(const LocalTask &t, const LocalList &p, int part, const uint32_t *items, int32_t *cnt, int m,
                                            int below, unsigned long long *smem, int (*edge)[kLocalWaves], int *s_base) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -321,28 +320,34 @@ __device__ __forceinline__ void local_plan(const LocalTask &t, const LocalList &
   unsigned long long all;
   const unsigned long long before = local_scan((unsigned long long)__popcll(heads) | (unsigned long long)__popcll(units) << 21 |
                                                    (unsigned long long)__popcll(emits) << 42, &all, smem);
-  // What the parts below count: each publishes its own before it looks, and parts are numbered by a ticket, so those below
-  // are running.  Whether ids are bad or not: a part does not know what another finds.
   constexpr int kMask = (1 << 21) - 1;
-  if (tid < 3) publish(t.state + 3 * part + tid, 1u + (uint32_t)((all >> (21 * tid)) & kMask));
-  if (wave == 0) {
-    int v[3] = {0, 0, 0};
-    if (lane < part)
+  int h = (int)(before & kMask), u = (int)((before >> 21) & kMask), e = (int)(before >> 42);
+  if constexpr (PARTS) {
+    if (tid == 0) plan.local.parts[part] = PartCounts{below, (int)(all & kMask), (int)((all >> 21) & kMask), (int)(all >> 42)};
+    h += below, u += below;
+  } else {
+    // What the parts below count: each publishes its own before it looks, and parts are numbered by a ticket, so those below
+    // are running.  Whether ids are bad or not: a part does not know what another finds.
+    if (tid < 3) publish(t.state + 3 * part + tid, 1u + (uint32_t)((all >> (21 * tid)) & kMask));
+    if (wave == 0) {
+      int v[3] = {0, 0, 0};
+      if (lane < part)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          uint32_t w;
+          while ((w = published(t.state + 3 * lane + c)) == 0u) __builtin_amdgcn_s_sleep(2);
+          v[c] = (int)w - 1;
+        }
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
-        uint32_t w;
-        while ((w = published(t.state + 3 * lane + c)) == 0u) __builtin_amdgcn_s_sleep(2);
-        v[c] = (int)w - 1;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) v[c] += __shfl_xor(v[c], off, kWave);
+        if (lane == 0) s_base[c] = v[c];
       }
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) v[c] += __shfl_xor(v[c], off, kWave);
-      if (lane == 0) s_base[c] = v[c];
     }
+    __syncthreads();
+    h += s_base[0], u += s_base[1], e += s_base[2];
   }
-  __syncthreads();
-  int h = s_base[0] + (int)(before & kMask), u = s_base[1] + (int)((before >> 21) & kMask), e = s_base[2] + (int)(before >> 42);
   seg = seg0;
   GEAR_ROLLED for (int i0 = 0; i0 < mine; i0 += U) {
     int c[U];
@@ -376,7 +381,7 @@ __device__ __forceinline__ void local_plan(const LocalTask &t, const LocalList &
       e += (emits >> i) & 1ull ? 1 : 0;
     }
   }
-  if (part == (1 << p.parts_log2) - 1 && tid == 0) {
+  if (!PARTS && part == (1 << p.parts_log2) - 1 && tid == 0) {
     const int n_heads = s_base[0] + (int)(all & kMask), n_emits = s_base[2] + (int)(all >> 42);
     *t.n_unique = n_heads;
     if (t.unique) t.segoff[n_heads] = p.n;
@@ -388,7 +393,7 @@ __device__ __forceinline__ void local_plan(const LocalTask &t, const LocalList &
 }
 
 // the part's place in the sorted list, and what hangs on the images
-template <bool FITS>
+template <bool FITS, bool PARTS>
 __device__ __forceinline__ void local_finish(const LocalTask &t, const LocalList &p, bool last, bool placed, int part, const uint32_t *sorted,
                                              uint32_t *spare, int m, int below, unsigned long long *smem,
                                              int (*edge)[kLocalWaves], int *s_base) {
@@ -398,12 +403,12 @@ __device__ __forceinline__ void local_finish(const LocalTask &t, const LocalList
     if (!last) p.sorted_keys[below + q] = high | (int)(item >> p.value_bits);   // the images' are in the plan
     if (!placed) p.perm[below + q] = (int)(item & ((1u << p.value_bits) - 1u));
   }
-  if (last) local_plan<FITS>(t, p, part, sorted, reinterpret_cast<int32_t *>(spare), m, below, smem, edge, s_base);
+  if (last) local_plan<FITS, PARTS>(t, p, part, sorted, reinterpret_cast<int32_t *>(spare), m, below, smem, edge, s_base);
 }
 
 // Two sets of the part's items are in LDS (INSIDE), or one is and the other in the workspace: a part is that long only where
 // one image is very popular.
-template <bool INSIDE>
+template <bool INSIDE, bool PARTS>
 __device__ __forceinline__ void local_sorted(const LocalTask &t, const LocalList &p, bool last, bool placed, int part, uint32_t *items, uint16_t *count,
                                              int m, int below, unsigned long long *smem, int (*edge)[kLocalWaves], int *s_base) {
   const int bits = p.bits - p.parts_log2, passes = placed ? 0 : (bits + kLocalDigitBits - 1) / kLocalDigitBits;
@@ -422,39 +427,53 @@ __device__ __forceinline__ void local_sorted(const LocalTask &t, const LocalList
     }
   }
   if constexpr (INSIDE)
-    local_finish<true>(t, p, last, placed, part, items + a, items + (m - a), m, below, smem, edge, s_base);
+    local_finish<true, PARTS>(t, p, last, placed, part, items + a, items + (m - a), m, below, smem, edge, s_base);
   else
-    local_finish<false>(t, p, last, placed, part, items, nullptr, m, below, smem, edge, s_base);
+    local_finish<false, PARTS>(t, p, last, placed, part, items, nullptr, m, below, smem, edge, s_base);
 }
 
 // Workgroup `block` of t.blocks, with kLocalThreads threads.  lds: kLocalWaves * kLocalRadix counts and t.room items.
-__device__ __forceinline__ void local_group(const LocalTask &t, int block, unsigned char *lds) {
+template <bool PARTS> __device__ __forceinline__ void local_group(const LocalTask &t, int block, unsigned char *lds) {
   __shared__ unsigned long long smem[kLocalWaves];
   __shared__ int edge[2][kLocalWaves], s_base[3], s_part;
   // by selection and not by an index, with which the arguments would be copied to memory
   static_assert(kMaxProblems == 3, "users, URLs, images");
   const int first = 1 << t.list[0].parts_log2, second = first + (1 << t.list[1].parts_log2);
   const bool last = block >= second;
+  const int word = block;
   LocalList p = t.list[0];
   if (last)
     p = t.list[2], block -= second;
   else if (block >= first)
     p = t.list[1], block -= first;
   int part = block;
-  if (last) {
+  if (!PARTS && last) {
     if (threadIdx.x == 0) s_part = draw_ticket(t.ticket);
     __syncthreads();
     part = s_part;
   }
+  bool bad = false;
+  if (word < first) {   // the offsets with the first list
+    int32_t lo, hi;
+    GEAR_ROLLED for (int i = word * kLocalThreads + threadIdx.x; i < t.views.B; i += first * kLocalThreads)
+      bad |= !view_ok(t.views, i, lo, hi);
+  }
   uint32_t *items = reinterpret_cast<uint32_t *>(lds + kLocalWaves * kLocalRadix * sizeof(uint16_t));
   uint16_t *count = reinterpret_cast<uint16_t *>(lds);
   int below;
-  const int m = local_select(t, p, part, items, smem, &below);
+  const int m = local_select(p, part, items, smem, &below, &bad);
+  if constexpr (PARTS) {
+    const LocalResult &result = t.plan.plan.local;
+    if (threadIdx.x == 0) result.codes[word] = bad ? 1 : 0;
+    if (word == 0 && (int)threadIdx.x < (kCodeGroup - t.blocks % kCodeGroup) % kCodeGroup) result.codes[t.blocks + threadIdx.x] = 0;
+  } else {
+    if (bad && threadIdx.x == 0) flag(t.failed, t.plan.status, GEAR_ERR_RANGE);
+  }
   const bool placed = m >= kPopularLeast && local_popular(p, items, count, m, below, t.room, smem);
   if (2 * m <= t.room)
-    local_sorted<true>(t, p, last, placed, part, items, count, m, below, smem, edge, s_base);
+    local_sorted<true, PARTS>(t, p, last, placed, part, items, count, m, below, smem, edge, s_base);
   else
-    local_sorted<false>(t, p, last, placed, part, items, count, m, below, smem, edge, s_base);
+    local_sorted<false, PARTS>(t, p, last, placed, part, items, count, m, below, smem, edge, s_base);
 }
 
 }  // namespace

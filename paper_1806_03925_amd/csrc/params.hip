@@ -101,7 +101,7 @@ struct ParamArgs {
   int first_column_block[kMaxColumnSums];
   int columns_at, loss_at;      // first workgroup of the column sums, and the loss's
   LossSum loss;
-  int32_t *n_ready;             // cleared by a step that has failed: its lists do not know of each other
+  LocalOutputs local;
 };
 struct SpanWork {
   EmbeddingWork w;
@@ -112,8 +112,17 @@ struct NoSpans {};
 template <bool SPANS>
 __global__ void __launch_bounds__(256) k_param_update(ParamArgs args, std::conditional_t<SPANS, SpanWork, NoSpans> spans,
                                                       Optim opt, const int32_t *__restrict__ status) {
-  if (*status != 0) {
-    if (blockIdx.x == 0 && threadIdx.x == 0 && args.n_ready) *args.n_ready = 0;
+  if (args.local.local.parts) {
+    const LocalState local = local_state(args.local.local, 0);
+    const int emits = blockIdx.x == 0 ? emits_of(args.local.local, args.local.local.n_parts) : 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      *args.local.status = local.code;
+      *args.local.n_ready = local.code ? 0 : emits;
+      if (local.code) *args.local.loss = 0.0f;
+    }
+    if (local.code) return;
+  } else if (*status != 0) {
+    if (blockIdx.x == 0 && threadIdx.x == 0 && args.local.n_ready) *args.local.n_ready = 0;
     return;
   }
   int block = blockIdx.x;
@@ -150,7 +159,7 @@ __global__ void __launch_bounds__(256) k_param_update(ParamArgs args, std::condi
 }  // namespace
 
 hipError_t launch_param_update(const SplitkProblem *p, int count, int splits, const ColumnSum *c, int n_columns,
-                               const LossSum &loss, const EmbeddingWork *emb, int32_t *n_ready, const Optim &opt,
+                               const LossSum &loss, const EmbeddingWork *emb, const LocalOutputs &local, const Optim &opt,
                                const int32_t *status, hipStream_t s, hipEvent_t stop) {
   if (count < 0 || count > GEAR_MAX_LAYERS || splits < 1 || n_columns < 0 || n_columns > kMaxColumnSums)
     return hipErrorInvalidValue;
@@ -159,7 +168,7 @@ hipError_t launch_param_update(const SplitkProblem *p, int count, int splits, co
   args.n_columns = n_columns;
   args.splits = splits;
   args.loss = loss;
-  args.n_ready = n_ready;
+  args.local = local;
   int blocks = 0;
   for (int i = 0; i < GEAR_MAX_LAYERS; ++i) {
     args.p[i] = i < count ? p[i] : SplitkProblem{nullptr, nullptr, Moments{nullptr, nullptr}, 0};

@@ -201,7 +201,84 @@ __device__ __forceinline__ void rows_product(f32x4_v (&acc)[NT][MT], const unsig
 
 enum RowsEpi { ROWS_FORWARD, ROWS_BACK, ROWS_DX };
 
-template <typename T, int MT, int NT, int EPI, typename Meet>
+// The same from the fp32 weights themselves, row-major, sixteen views: forward W [N x K], of which a lane has four neighbouring k, and
+// the four lanes of a row exchange them; backward W [K x N], four words of four rows.  No launch has to lay them out first.
+template <int NT, int AHEAD, bool BACK, typename Meet>
+__device__ __forceinline__ void rows_product_direct(f32x4_v (&acc)[NT][1], const unsigned char *act, const void *w, int N, int K, int tile0,
+                                                    int q, int r, Meet meet) {
+  constexpr int SK = Step<float>::K;
+  const int steps = K / SK;
+  const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(w), 0, N * K * 4, 0x00020000);
+  int lane_at[NT];
+#pragma unroll
+  for (int j = 0; j < NT; ++j) {
+    const int n = min(16 * (tile0 + j) + r, N - 1);   // the missing rows of a last tile repeat its last one and are not stored
+    lane_at[j] = BACK ? (q * N + n) * 4 : (n * K + 4 * q) * 4;
+  }
+  u32x4_v wf[AHEAD][NT];
+  auto weights = [&](u32x4_v (&to)[NT], int s) {
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+      if constexpr (BACK) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) to[j][e] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, lane_at[j], min(SK * s + 4 * e, K - 4) * N * 4, 0);
+      } else {
+        to[j] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane_at[j], s * SK * 4, 0);
+      }
+    }
+  };
+  auto products = [&](u32x4_v (&wt)[NT], int s) {
+    const u32x4_v at = *reinterpret_cast<const u32x4_v *>(act + s * 64);
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+      if constexpr (!BACK) {   // lane q has k = 4 q + e, and is to have q + 4 e
+        auto swap16 = [&](int a, int b) {
+          const auto t = __builtin_amdgcn_permlane16_swap(wt[j][a], wt[j][b], false, false);
+          wt[j][a] = t[0], wt[j][b] = t[1];
+        };
+        auto swap32 = [&](int a, int b) {
+          const auto t = __builtin_amdgcn_permlane32_swap(wt[j][a], wt[j][b], false, false);
+          wt[j][a] = t[0], wt[j][b] = t[1];
+        };
+        swap16(0, 1), swap16(2, 3), swap32(0, 2), swap32(1, 3);
+      }
+      Step<float>::mma(acc[j][0], wt[j], at);
+    }
+  };
+#pragma unroll
+  for (int d = 0; d < AHEAD; ++d)
+    if (d < steps) weights(wf[d], d);
+  meet();
+  int s0 = 0;
+  for (; s0 + AHEAD <= steps; s0 += AHEAD) {
+#pragma unroll
+    for (int d = 0; d < AHEAD; ++d) {
+      products(wf[d], s0 + d);
+      weights(wf[d], min(s0 + d + AHEAD, steps - 1));
+      __builtin_amdgcn_sched_barrier(0);   // registers
+    }
+  }
+#pragma unroll
+  for (int d = 0; d < AHEAD - 1; ++d)
+    if (s0 + d < steps) products(wf[d], s0 + d);
+  if (K % SK) {   // eight more, zero beyond them (LDS rows are padded with zeros): of a lane's four the first two, or those of two lanes
+    u32x4_v last[NT];
+    if constexpr (BACK) {
+      weights(last, steps);
+#pragma unroll
+      for (int j = 0; j < NT; ++j) last[j][2] = last[j][3] = 0u;
+    } else {
+#pragma unroll
+      for (int j = 0; j < NT; ++j) {
+        last[j] = u32x4_v{0u, 0u, 0u, 0u};
+        if (q < 2) last[j] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane_at[j], steps * SK * 4, 0);
+      }
+    }
+    products(last, steps);
+  }
+}
+
+template <typename T, int MT, bool DIRECT, int NT, int EPI, typename Meet>
 __device__ __forceinline__ void rows_tiles_of(const RowsArgs &p, unsigned char *lds, const RowsBuf &in, const RowsBuf &out,
                                               const void *w, int N, int K, const float *bias, T *global, int row0, int tile0,
                                               int lane, Meet meet) {
@@ -223,7 +300,11 @@ __device__ __forceinline__ void rows_tiles_of(const RowsArgs &p, unsigned char *
     for (int i = 0; i < MT; ++i)
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[j][i][e] = 0.0f;
-  rows_product<T, MT, NT, AHEAD>(acc, lds + in.at + r * in.stride + q * 16, in.stride, w, N, K, tile0, q, r, meet);
+  const unsigned char *act = lds + in.at + r * in.stride + q * 16;
+  if constexpr (DIRECT)
+    rows_product_direct<NT, AHEAD, EPI != ROWS_FORWARD>(acc, act, w, N, K, tile0, q, r, meet);
+  else
+    rows_product<T, MT, NT, AHEAD>(acc, act, in.stride, w, N, K, tile0, q, r, meet);
 #pragma unroll
   for (int j = 0; j < NT; ++j) {
     const int n = 16 * (tile0 + j) + 4 * q;
@@ -268,7 +349,7 @@ __device__ __forceinline__ void rows_tiles_of(const RowsArgs &p, unsigned char *
 // are on one SIMD, so those of 36 tiles have nine each).  The workgroups of an XCD start with different shares, so that its
 // L2 is not asked for the same lines by all of them at once.  `meet`: what has to come between the launch's earlier phases and the
 // first read of `in`, by every wavefront once; its first weights are on their way meanwhile.
-template <typename T, int MT, int EPI, typename Meet>
+template <typename T, int MT, bool DIRECT, int EPI, typename Meet>
 __device__ __forceinline__ void rows_layer(const RowsArgs &p, unsigned char *lds, const RowsBuf &in, const RowsBuf &out, const void *w,
                                            int N, int K, const float *bias, T *global, int row0, int wave, int lane, Meet meet) {
   const int tiles = (N + 15) / 16, least = tiles / kRowsWaves, more = tiles % kRowsWaves;
@@ -286,7 +367,7 @@ __device__ __forceinline__ void rows_layer(const RowsArgs &p, unsigned char *lds
     switch (n) {
 #define GEAR_TILES(NT)                                                                                          \
   case NT:                                                                                                      \
-    if constexpr (NT <= MOST) rows_tiles_of<T, MT, NT, EPI>(p, lds, in, out, w, N, K, bias, global, row0, tile, lane, meet_once); \
+    if constexpr (NT <= MOST) rows_tiles_of<T, MT, DIRECT, NT, EPI>(p, lds, in, out, w, N, K, bias, global, row0, tile, lane, meet_once); \
     break;
       GEAR_TILES(1)
       GEAR_TILES(2)
@@ -403,17 +484,12 @@ __device__ __forceinline__ void gather_embeddings(const RowsArgs &p, unsigned ch
 }
 
 template <typename T, int R>
-__device__ __forceinline__ void rows_gather(const RowsArgs &p, unsigned char *lds, int32_t *failed, int32_t *status, int row0, int wave, int lane) {
+__device__ __forceinline__ void rows_gather(const RowsArgs &p, unsigned char *lds, bool local, int row0, int wave, int lane) {
   constexpr int PER = R / kRowsWaves, VIEWS = R == 64 ? 4 : 2;
   const int first = wave * PER;
   // bounds of the wavefront's lists, clamped like every id: the check of the ids may still be running (gather.hip)
   const int at = min(row0 + first + min(lane, PER), p.B);
-  const int raw = p.img_off[at], off = min(max(raw, 0), p.nnz);
-  if (failed) {   // the check of the offsets, unless it is made elsewhere
-    const int next = __shfl_down(raw, 1, kWave), view = row0 + first + lane;
-    if (lane < PER && view < p.B && (raw < 0 || raw > next || next > p.nnz || (view == 0 && raw != 0) || (view == p.B - 1 && next != p.nnz)))
-      flag(failed, status, GEAR_ERR_RANGE);
-  }
+  const int off = min(max(p.img_off[at], 0), p.nnz);
   if (p.emb_bf16)
     gather_embeddings<T, bf16_t, R>(p, lds, row0, first, lane);
   else
@@ -429,7 +505,7 @@ __device__ __forceinline__ void rows_gather(const RowsArgs &p, unsigned char *ld
     }
 #pragma unroll
     for (int u = 0; u < VIEWS; ++u)
-      for (int j = lane; failed && j < n[u]; j += kWave) {
+      for (int j = lane; local && j < n[u]; j += kWave) {
         p.occ_view[lo[u] + j] = row0 + first + u0 + u;
         p.occ_scale[lo[u] + j] = 1.0f / (float)n[u];
       }
@@ -559,11 +635,11 @@ __device__ __forceinline__ void rows_columns(const RowsArgs &p, unsigned char *l
 // The first local.blocks workgroups group the ids.  Two workgroups of up to 32 views share a CU (kHalf below), so they have half
 // the registers; those of 64 have the CU to themselves but for the sorts of a long step, which take 96 registers
 // beside 191 (group.hip).  In fp32 with 32 views, a form of long steps only, 96 leave room for them too (hotkey 175.5 us a step, with 108 180).
-template <typename T, int MT>
+template <typename T, int MT, bool DIRECT>
 __global__ void __launch_bounds__(kRowsThreads, MT == 4 ? 2 : MT == 2 && sizeof(T) == 4 ? 5 : 4) k_rows(RowsArgs p, LocalTask local) {
   constexpr int R = 16 * MT;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-  if ((int)blockIdx.x < local.blocks) return local_group(local, blockIdx.x, lds);
+  if ((int)blockIdx.x < local.blocks) return local_group<DIRECT>(local, blockIdx.x, lds);
   __shared__ float s_dz[R], s_red[kRowsWaves][2];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int block = blockIdx.x - local.blocks, row0 = block * R;
@@ -573,7 +649,7 @@ __global__ void __launch_bounds__(kRowsThreads, MT == 4 ? 2 : MT == 2 && sizeof(
   const int my_view = row0 + wave * (R / kRowsWaves) + lane;
   const float b0 = p.b_last[0], y = lane < R / kRowsWaves && my_view < p.B ? p.label[my_view] : 0.0f;
 
-  rows_gather<T, R>(p, lds, local.failed, local.plan.status, row0, wave, lane);
+  rows_gather<T, R>(p, lds, local.blocks > 0, row0, wave, lane);
   zero_pad<T, R>(lds, p.x_buf, p.F, tid);
   // A layer's activations are whole in LDS behind the barrier that begins the next phase.
   auto whole = [&](int l) {
@@ -583,7 +659,7 @@ __global__ void __launch_bounds__(kRowsThreads, MT == 4 ? 2 : MT == 2 && sizeof(
   };
   for (int l = 0; l + 1 < p.L; ++l) {
     const RowsLayer &a = p.layer[l];
-    rows_layer<T, MT, ROWS_FORWARD>(p, lds, l == 0 ? p.x_buf : p.layer[l - 1].buf, a.buf, a.w, a.out, a.in, a.bias, static_cast<T *>(a.h), row0,
+    rows_layer<T, MT, DIRECT, ROWS_FORWARD>(p, lds, l == 0 ? p.x_buf : p.layer[l - 1].buf, a.buf, a.w, a.out, a.in, a.bias, static_cast<T *>(a.h), row0,
                                     wave, lane, [&]() { whole(l - 1); });
     zero_pad<T, R>(lds, a.buf, a.out, tid);
   }
@@ -604,16 +680,16 @@ __global__ void __launch_bounds__(kRowsThreads, MT == 4 ? 2 : MT == 2 && sizeof(
   const auto nothing = []() {};
   for (int l = p.L - 2; l > 0; --l) {
     const RowsLayer &a = p.layer[l], &below = p.layer[l - 1];
-    rows_layer<T, MT, ROWS_BACK>(p, lds, a.buf, below.buf, a.wt, a.in, a.out, nullptr, static_cast<T *>(below.delta), row0, wave, lane, nothing);
+    rows_layer<T, MT, DIRECT, ROWS_BACK>(p, lds, a.buf, below.buf, a.wt, a.in, a.out, nullptr, static_cast<T *>(below.delta), row0, wave, lane, nothing);
     __syncthreads();
     rows_columns<T, R, false>(p, lds, below.buf, a.in, static_cast<T *>(below.delta), below.colsum + (size_t)block * a.in, nullptr,
                               nullptr, nullptr, scratch, row0, tid);
   }
-  rows_layer<T, MT, ROWS_DX>(p, lds, p.layer[0].buf, p.layer[0].buf, p.layer[0].wt, p.F, p.layer[0].out, nullptr, nullptr, row0, wave, lane, nothing);
+  rows_layer<T, MT, DIRECT, ROWS_DX>(p, lds, p.layer[0].buf, p.layer[0].buf, p.layer[0].wt, p.F, p.layer[0].out, nullptr, nullptr, row0, wave, lane, nothing);
 }
 
-template <typename T, int MT> hipError_t run_rows(const RowsArgs &a, const LocalTask &local, const RowsPlan &plan, hipStream_t s) {
-  hipLaunchKernelGGL((k_rows<T, MT>), dim3((unsigned)(local.blocks + plan.blocks)), dim3(kRowsThreads), plan.lds, s, a, local);
+template <typename T, int MT, bool DIRECT = false> hipError_t run_rows(const RowsArgs &a, const LocalTask &local, const RowsPlan &plan, hipStream_t s) {
+  hipLaunchKernelGGL((k_rows<T, MT, DIRECT>), dim3((unsigned)(local.blocks + plan.blocks)), dim3(kRowsThreads), plan.lds, s, a, local);
   return hipGetLastError();
 }
 
@@ -644,8 +720,15 @@ long long place_buffers(const Layout &lay, int dtype, int rows, RowsArgs *a) {
 
 }  // namespace
 
+constexpr int kStateSpan = 3 * kMaxParts;   // words of three per part, then a ticket
+// Bytes of weights (once forward, once backward) up to which fp32 blocks read them as they are and a step goes without its prologue, a launch
+// of 4 us: read row by row they are 64 bytes of a line at a time forward and words backward, so that every block pays for more of
+// them.  us a step, with the prologue / without: 96 -> 64 (49 KB) 512 views 30.3 / 26.1, 2000 34.9 / 28.9, 6000 44.4 / 41.0; 96 -> 128
+// (98 KB) 512 views 31.7 / 27.1, 6000 47.0 / 43.5; 96 -> 128 -> 64 (164 KB) 512 32.2 / 31.7, 4000 42.4 / 41.7; 320 -> 64 (164 KB) 1000
+// 37.3 / 34.1, 4000 57.2 / 53.6.  Beyond: 288 -> 64 -> 64 (180 KB) 1000 33.7 / 34.1; 1056 -> 24 (203 KB) 1000 51.4 / 52.3; 320 -> 256 -> 128
+// 4096 74.8 / 78.1; and with more than a block a CU 288 -> 64 (147 KB) 5000 44.6 / 47.3, 288 -> 256 61.0 / 71.0.
+constexpr double kDirectBytes = 170e3, kDirectBytesLong = 100e3;   // up to 4096 views, beyond
 constexpr int kLocalPart = 1024;   // ids of a part, where they are spread evenly (2048: a step of 4096 views 1.5 us longer)
-constexpr int kStateSpan = 96;     // words of three per part, then a ticket
 
 // A step whose ids are sorted in launches of their own (api.hip), on two streams.  Lines by measurement (us a step; blocks of
 // views against layer by layer; three images a view unless it says otherwise):
@@ -677,6 +760,7 @@ bool plan_long(const Layout &lay, int dt, int B, int nnz, double stream, size_t 
   if (bf16 ? stream > 1.5e6 + 420.0 * B : stream > 1e6 || B < (stream > 2e5 ? 14336 : 12288)) return false;
   const bool two_loads = lay.L > 3 && row_bytes > kWave * 16;
   RowsArgs a;
+  plan->direct = false;
   plan->rows = bf16 && B > 8192 ? 64 : 32;
   if (plan->rows == 64 && B <= 12288 && (two_loads || place_buffers(lay, dt, 64, &a) + 1024 > 160 * 1024)) plan->rows = 32;
   const long long lds = place_buffers(lay, dt, plan->rows, &a);
@@ -739,11 +823,12 @@ bool plan_rows(const gear_config &cfg, const Layout &lay, int B, int nnz, bool l
     log2 = bits + plan->value_bits[i] - 32;
     if (log2 < 0) log2 = 0;
     while (log2 < bits && n > kLocalPart << log2) ++log2;
-    if (log2 > (last ? 5 : 7)) return false;   // the parts of the last list look at one another's words, a lane each
+    if ((1 << log2) > (last ? kMaxParts : 128)) return false;   // those of the last list are read by a lane each
     if (n > most) most = n;
   }
   const int counts = kLocalWaves * kLocalRadix * 2;
   plan->rows = dt == GEAR_BF16 && B > 4096 ? 32 : 16;
+  plan->direct = dt == GEAR_F32 && stream <= (B <= 4096 ? kDirectBytes : kDirectBytesLong);
   RowsArgs a;
   long long lds = place_buffers(lay, dt, plan->rows, &a);
   // room for two sets of the longest list's ids, as far as that leaves room for a second workgroup on the CU
@@ -790,7 +875,20 @@ BlockSums block_sums_of(const RowsPlan &plan, const Layout &lay, const gear_batc
   return w;
 }
 
-LocalTask local_task(const RowsPlan &plan, const GroupBatch &gb, const PlanArgs &args, int32_t *failed) {
+// The parts' counts and the codes lie where the sorts of longer steps publish and count: 768 bytes and more.
+LocalResult local_result(const RowsPlan &plan, const GroupBatch &gb, int nnz, int ready_cap) {
+  LocalResult r;
+  r.parts = (PartCounts *)gb.seg_state;
+  r.codes = (uint8_t *)gb.p[0].state;
+  r.parts_log2 = plan.parts_log2[kMaxProblems - 1];
+  r.n_parts = 1 << r.parts_log2;
+  r.n_codes = 0;
+  for (int i = 0; i < kMaxProblems; ++i) r.n_codes += 1 << plan.parts_log2[i];
+  r.ready_cap = ready_cap < nnz ? ready_cap : -1;   // an emission has an occurrence of its own
+  return r;
+}
+
+LocalTask local_task(const RowsPlan &plan, const GroupBatch &gb, const PlanArgs &args, const ViewCheck &views, int32_t *failed) {
   LocalTask t;
   t.blocks = 0;
   t.room = plan.room;
@@ -802,6 +900,7 @@ LocalTask local_task(const RowsPlan &plan, const GroupBatch &gb, const PlanArgs 
   }
   const GroupProblem &img = gb.p[kMaxProblems - 1];
   t.plan = args;
+  t.views = views;
   t.unique = img.unique, t.segoff = img.segoff, t.n_unique = img.n_unique;
   t.state = gb.seg_state;
   t.ticket = (int32_t *)gb.seg_state + kStateSpan;
@@ -846,6 +945,7 @@ hipError_t launch_rows(const gear_config &cfg, const Layout &lay, const RowsPlan
   for (int l = 0; l + 1 < L; ++l) {
     RowsLayer &r = a.layer[l];
     r.w = ws + lay.wc[l], r.wt = ws + lay.wct[l];
+    if (plan.direct) r.w = r.wt = t.mlp_params + lay.w_off[l];
     r.bias = t.mlp_params + lay.b_off[l];
     r.h = ws + lay.h[l], r.delta = ws + lay.delta[l];
     r.in = lay.in_dim[l], r.out = lay.out_dim[l];
@@ -858,7 +958,7 @@ hipError_t launch_rows(const gear_config &cfg, const Layout &lay, const RowsPlan
     if (rows == 16) return run_rows<bf16_t, 1>(a, local, plan, s);
   } else {
     if (rows == 32) return run_rows<float, 2>(a, local, plan, s);
-    if (rows == 16) return run_rows<float, 1>(a, local, plan, s);
+    if (rows == 16) return plan.direct ? run_rows<float, 1, true>(a, local, plan, s) : run_rows<float, 1>(a, local, plan, s);
   }
   return hipErrorInvalidValue;
 }

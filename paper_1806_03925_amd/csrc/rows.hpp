@@ -45,6 +45,7 @@ __host__ __device__ inline int rows_split(int rows, int owners) {
 
 // How a step goes about it: decided by sizes alone.
 struct RowsPlan {
+  bool direct;                         // the blocks read the weights as they are, and the step has no prologue
   int rows, blocks;                    // views of a block; blocks of the batch
   int lds, room;                       // bytes of LDS; items of the sorts in them
   int digit_bits;                      // of the sorts that run beside
@@ -57,7 +58,8 @@ struct RowsPlan {
 bool plan_rows(const gear_config &cfg, const Layout &lay, int B, int nnz, bool local, RowsPlan *plan);
 LogitSums rows_sums(const RowsPlan &plan, const float *partials, int H);
 BlockSums block_sums_of(const RowsPlan &plan, const Layout &lay, const gear_batch &b, char *ws);   // the same sums, from the launches of the layers
-LocalTask local_task(const RowsPlan &plan, const GroupBatch &gb, const PlanArgs &args, int32_t *failed);
+LocalResult local_result(const RowsPlan &plan, const GroupBatch &gb, int nnz, int ready_cap);
+LocalTask local_task(const RowsPlan &plan, const GroupBatch &gb, const PlanArgs &args, const ViewCheck &views, int32_t *failed);
 void local_zero_list(const GroupBatch &gb, ZeroList *z);
 hipError_t launch_rows(const gear_config &cfg, const Layout &lay, const RowsPlan &plan, const gear_batch &b, const gear_tables &t,
                        const void *dfv_cache, char *ws, const LocalTask &local, hipStream_t s);

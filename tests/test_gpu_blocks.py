@@ -448,3 +448,96 @@ def test_rows_beyond_the_batch_take_part_in_no_sum(dtype):
     assert (h > 0).any()
     grad = ((torch.sigmoid(z) - torch.from_numpy(batch.label)) / B) @ h
     assert ((before - w2[0]).double().cpu() - 0.5 * grad).abs().max() <= 1e-5 * float(grad.abs().max() + before.abs().max())
+
+
+def outputs(st):
+    n = int(st.n_ready.item())
+    return [t.clone() for t in (st.loss, st.n_ready, st.ready_ids[:n], st.ready_grads[:n], st.grad_accum, st.counts, st.user_emb,
+                                st.url_emb, st.mlp_params)]
+
+
+@pytest.mark.parametrize("batch,layers,d,D,prologue", [
+    (64, (24, 1), 8, 40, False), (1_000, (72, 40, 1), 24, 72, False),    # widths that neither a tile nor a k-step divides
+    (4_096, (80, 1), 8, 248, False), (4_096, (88, 1), 8, 248, True),      # 168 960 bytes of weights, 185 856
+    (4_100, (56, 1), 8, 200, False), (4_100, (64, 1), 8, 200, True),      # 96 768, 110 592
+])
+def test_blocks_that_read_the_weights_as_they_are(batch, layers, d, D, prologue):
+    """On either side of the lines.  The same views with three times as many behind them go another way (their ids do not fit in LDS), with the
+    weights copied: the same logits, and dLoss/dx exactly a quarter."""
+    import paper_1806_03925_amd as g
+    from gear_inputs import PageViewSource
+    from gear_inputs.pageviews import PageViewBatch
+    wl = wl_of("f32", 4 * batch, layers, d, D, max_images=2, n_images=500)
+    full = PageViewSource(wl).batch(0)
+    if full.nnz <= 19_200:   # a longer list: more images to the last view
+        more = np.random.default_rng(batch).integers(0, wl.n_images, 19_201 - full.nnz).astype(np.int32)
+        full = PageViewBatch(user_id=full.user_id, url_id=full.url_id, img_id=np.concatenate([full.img_id, more]), label=full.label,
+                             img_off=np.concatenate([full.img_off[:-1], [19_201]]).astype(np.int32))
+    part = PageViewBatch(user_id=full.user_id[:batch], url_id=full.url_id[:batch], img_off=full.img_off[:batch + 1],
+                         img_id=full.img_id[:full.img_off[batch]], label=full.label[:batch])
+    states = []
+    for b in (part, full):
+        st = g.GearState(g.config_for(wl.scaled(max_images=max(2, -(-full.nnz // full.B)))))
+        g.gear_init_tables(st)
+        g.gear_fill_normal(st.dfv_cache, wl.n_images, wl.dfv_dim, wl.seed, 3, wl.dfv_std)
+        names = launches_of(st, g.DeviceBatch.from_host(b), wl.M, 0.1)
+        assert int(st.status.item()) == 0
+        assert (form_of_launches(names) == "blocks") == (b is part)
+        if b is part:
+            assert ("begin" in names) == prologue
+        states.append(st)
+    assert torch.equal(states[1].region("logits", full.B)[:batch], states[0].region("logits", batch))
+    assert torch.equal(4.0 * states[1].region("dx", full.B)[:batch], states[0].region("dx", batch))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])   # without a prologue, with one
+@pytest.mark.parametrize("what", ["user", "url", "image", "first offset", "last offset", "room"])
+def test_a_step_that_fails_among_others(dtype, what):
+    """Several parts of every list.  It leaves everything as it was, and the steps ahead of it and behind it give what they give without it;
+    a ready list of exactly the length needed is enough."""
+    import paper_1806_03925_amd as g
+    from gear_inputs import PageViewSource
+    wl = wl_of(dtype, 2_500, (16, 1), 8, 8, M=2, n_images=3_000)
+    src = PageViewSource(wl)
+    results = []
+    for failing in (False, True):
+        probe = g.GearState(g.config_for(wl))
+        g.gear_init_tables(probe)
+        room = 0
+        for t in range(2):
+            g.gear_step(probe, g.DeviceBatch.from_host(src.batch(t)), wl.M, 0.1)
+            torch.cuda.synchronize()
+            room = max(room, int(probe.n_ready.item()))
+        st = g.GearState(g.config_for(wl), ready_cap=room)
+        g.gear_init_tables(st)
+        g.gear_step(st, g.DeviceBatch.from_host(src.batch(0)), wl.M, 0.1)
+        torch.cuda.synchronize()
+        assert int(st.status.item()) == 0
+        if failing:
+            bad = src.batch(7)
+            if what == "user":
+                bad.user_id[-1] = wl.n_users
+            elif what == "url":
+                bad.url_id[0] = -1
+            elif what == "image":
+                bad.img_id[3] = wl.n_images
+            elif what == "first offset":
+                bad.img_off[0] = 1
+            elif what == "last offset":
+                bad.img_off[-1] -= 1
+            else:
+                bad.img_off = np.arange(0, 4 * bad.B + 1, 4, dtype=np.int32)   # more occurrences, so more groups that close
+                bad.img_id = np.repeat(np.arange(wl.n_images, dtype=np.int32), 4)[:4 * bad.B]
+                assert 2 * bad.B - 1 > room
+            before = [t.clone() for t in (st.user_emb, st.url_emb, st.mlp_params, st.grad_accum, st.counts)]
+            g.gear_step(st, g.DeviceBatch.from_host(bad), wl.M, 0.1)
+            torch.cuda.synchronize()
+            assert int(st.status.item()) == (g.GEAR_ERR_CAPACITY if what == "room" else g.GEAR_ERR_RANGE)
+            assert int(st.n_ready.item()) == 0 and float(st.loss.item()) == 0.0
+            for a, b in zip(before, (st.user_emb, st.url_emb, st.mlp_params, st.grad_accum, st.counts)):
+                assert torch.equal(a, b)
+        names = launches_of(st, g.DeviceBatch.from_host(src.batch(1)), wl.M, 0.1)
+        assert int(st.status.item()) == 0 and form_of_launches(names) == "blocks" and ("begin" in names) == (dtype == "bf16")
+        results.append(outputs(st))
+    for a, b in zip(*results):
+        assert torch.equal(a, b)
