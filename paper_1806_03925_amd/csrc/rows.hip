@@ -728,6 +728,10 @@ constexpr int kStateSpan = 3 * kMaxParts;   // words of three per part, then a t
 // 37.3 / 34.1, 4000 57.2 / 53.6.  Beyond: 288 -> 64 -> 64 (180 KB) 1000 33.7 / 34.1; 1056 -> 24 (203 KB) 1000 51.4 / 52.3; 320 -> 256 -> 128
 // 4096 74.8 / 78.1; and with more than a block a CU 288 -> 64 (147 KB) 5000 44.6 / 47.3, 288 -> 256 61.0 / 71.0.
 constexpr double kDirectBytes = 170e3, kDirectBytesLong = 100e3;   // up to 4096 views, beyond
+// And of all occurrences' gradients: where the accumulation is long, units that are found part by part, some parts with few, keep it longer
+// (with the prologue / without, D = 256, 320 -> 64: 9000 occurrences, 9 MB, M = 2 44.8 / 42.0, M = 16 43.1 / 38.7; 18 000, 18 MB, M = 2
+// 62.2 / 63.3, M = 16 57.1 / 54.1, of skewed ids in 21 of 32 parts 65.5 / 69.3; D = 64, 18 000, 4.6 MB 43.4 / 39.5).
+constexpr double kDirectGradients = 12e6;
 constexpr int kLocalPart = 1024;   // ids of a part, where they are spread evenly (2048: a step of 4096 views 1.5 us longer)
 
 // A step whose ids are sorted in launches of their own (api.hip), on two streams.  Lines by measurement (us a step; blocks of
@@ -828,7 +832,7 @@ bool plan_rows(const gear_config &cfg, const Layout &lay, int B, int nnz, bool l
   }
   const int counts = kLocalWaves * kLocalRadix * 2;
   plan->rows = dt == GEAR_BF16 && B > 4096 ? 32 : 16;
-  plan->direct = dt == GEAR_F32 && stream <= (B <= 4096 ? kDirectBytes : kDirectBytesLong);
+  plan->direct = dt == GEAR_F32 && stream <= (B <= 4096 ? kDirectBytes : kDirectBytesLong) && 4.0 * nnz * cfg.dfv_dim <= kDirectGradients;
   RowsArgs a;
   long long lds = place_buffers(lay, dt, plan->rows, &a);
   // room for two sets of the longest list's ids, as far as that leaves room for a second workgroup on the CU
