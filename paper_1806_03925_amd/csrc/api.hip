@@ -927,7 +927,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
       ++n;
     }
     if (n == 0) return GEAR_ERR_CAPACITY;  // cannot happen: the region holds one range of the widest layer
-    int splits = gemm_tn_splits(dt, wp + first, n, B, choice.large);
+    int splits = gemm_tn_splits(dt, wp + first, n, B, choice.large, !beside);
     // Beside the accumulation two thirds as many: the CUs are not theirs alone, and every range is partials to write and to
     // add (us a step, all / two thirds / half: 4096 views 82.2 / 80.4 / 80.4, 5000 64.3 / 63.5 / 65.4).
     if (beside) splits = (2 * splits + 2) / 3;

@@ -419,7 +419,8 @@ struct TnChoice {
   bool large;
 };
 TnChoice gemm_tn_choice(int dtype, const TnProblem *p, int count, int K);
-int gemm_tn_splits(int dtype, const TnProblem *p, int count, int K, bool large);
+// pairs: of workgroups that walk two halves of a range (in a launch of their own and of known length, gemm_tile.hip)
+int gemm_tn_splits(int dtype, const TnProblem *p, int count, int K, bool large, bool pairs);
 // w_i <- update(w_i, sum_z partial_i[z]) for the results of such a launch
 struct SplitkProblem {
   const float *partial;
@@ -458,7 +459,7 @@ hipError_t launch_gemm_nt_tile(int dtype, const void *A, const void *B, int M, i
 int nt_tile_colsum_parts(int dtype, int M, int N, bool coarse);
 hipError_t launch_gemm_tn_tile(int dtype, const TnProblem *p, int count, int K, int splits, const int32_t *status,
                                hipStream_t s, const int32_t *k_dev);
-int tn_tile_splits(int dtype, const TnProblem *p, int count, int K);
+int tn_tile_splits(int dtype, const TnProblem *p, int count, int K, bool pairs);
 long long tn_tile_rows(int dtype, const TnProblem *p, int count, int K);   // that a CU walks, two ranges at a time
 
 hipError_t launch_logit_loss(int dtype, const void *h, const void *wc_last, const float *bias_last, const float *label,

@@ -669,8 +669,8 @@ TnChoice gemm_tn_choice(int dtype, const TnProblem *p, int count, int K) {
   return TnChoice{count, false};
 }
 
-int gemm_tn_splits(int dtype, const TnProblem *p, int count, int K, bool large) {
-  if (!large) return tn_tile_splits(dtype, p, count, K);
+int gemm_tn_splits(int dtype, const TnProblem *p, int count, int K, bool large, bool pairs) {
+  if (!large) return tn_tile_splits(dtype, p, count, K, pairs);
   int tiles = 0;
   for (int i = 0; i < count; ++i) tiles += tn_dma_tiles(p[i]);
   return tn_dma_splits(tiles, K);

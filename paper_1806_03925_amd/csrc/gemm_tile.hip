@@ -393,6 +393,19 @@ k_gemm_tn_tile(TnTileArgs args, int K, int splits, const int32_t *__restrict__ s
   tn_tile<C>(args, K, splits, k_dev, xcd_remap(blockIdx.x, gridDim.x), lds);
 }
 
+// bf16: what the ranges leave is written, read again and added by the parameter update, so two workgroups of a CU that would walk
+// neighbouring ranges of one tile are one of twice the wavefronts instead, which leaves one partial: of 576 -> 512 -> 256 15 MB and not 31
+// (us a step, 16 384 views 153.1 / 149.3, with Adam 158.4 / 154.1, 10 001 127.3 / 125.4).  Where whole ranges of pairs leave more of the CUs
+// out than those of single ones do, they are not taken (26 tiles, 234 of 256 against 494 of 512: 184.9 / 186.9), nor in fp32, whose 64 x 64
+// tiles leave little (16 384 views 157.3 / 158.0).
+template <typename C>
+__global__ void __launch_bounds__(2 * C::THREADS)
+k_gemm_tn_pair(TnTileArgs args, int K, int splits, const int32_t *__restrict__ status, const int32_t *__restrict__ k_dev) {
+  if (status && *status != 0) return;
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * C::STAGES * C::STAGE_BYTES];
+  tn_tile<C, true>(args, K, splits, k_dev, xcd_remap(blockIdx.x, gridDim.x), lds);
+}
+
 // ---- tile shapes -----------------------------------------------------------------------------------------
 using F32Small = NtTile<float, 1, 1, 2, 2, 4>;      //  64 x  64, 64 KB
 using F32Big = NtTile<float, 2, 2, 2, 2, 3>;        // 128 x 128, 96 KB
@@ -474,7 +487,10 @@ hipError_t run_tn(const TnProblem *p, int count, int K, int splits, const int32_
   TnTileArgs args;
   static_assert(C::BM == C::BN, "square tiles");
   (void)tn_tile_args(p, count, C::BM, &args);
-  hipLaunchKernelGGL((k_gemm_tn_tile<C>), dim3((unsigned)(args.tiles * splits)), dim3(C::THREADS), 0, s, args, K, splits, status, k_dev);
+  if (sizeof(typename C::T) == 2 && !k_dev && args.tiles * splits <= 256)
+    hipLaunchKernelGGL((k_gemm_tn_pair<C>), dim3((unsigned)(args.tiles * splits)), dim3(2 * C::THREADS), 0, s, args, K, splits, status, k_dev);
+  else
+    hipLaunchKernelGGL((k_gemm_tn_tile<C>), dim3((unsigned)(args.tiles * splits)), dim3(C::THREADS), 0, s, args, K, splits, status, k_dev);
   return hipGetLastError();
 }
 
@@ -502,17 +518,21 @@ static long long tn_tiles(int dtype, const TnProblem *p, int count) {
   return tiles;
 }
 
-// Ranges of the inner length: two workgroups for every CU, as long as each keeps at least 64 rows.
-int tn_tile_splits(int dtype, const TnProblem *p, int count, int K) {
+// Ranges of the inner length: `slots` for all CUs, as long as each keeps at least 64 rows.
+static int tn_splits(int dtype, const TnProblem *p, int count, int K, int slots) {
   const long long tiles = tn_tiles(dtype, p, count);
-  long long s = tiles > 0 ? 512 / tiles : 1;
+  long long s = tiles > 0 ? slots / tiles : 1;
   if (s > K / 64) s = K / 64;
   if (s > 64) s = 64;
   return s < 1 ? 1 : (int)s;
 }
+int tn_tile_splits(int dtype, const TnProblem *p, int count, int K, bool pairs) {
+  const int all = tn_splits(dtype, p, count, K, 512), half = tn_splits(dtype, p, count, K, 256);
+  return pairs && dtype == GEAR_BF16 && 200 * half >= 97 * all ? half : all;
+}
 
 long long tn_tile_rows(int dtype, const TnProblem *p, int count, int K) {
-  const int splits = tn_tile_splits(dtype, p, count, K);
+  const int splits = tn_splits(dtype, p, count, K, 512);
   return (tn_tiles(dtype, p, count) * splits + 511) / 512 * ((K + splits - 1) / splits);
 }
 

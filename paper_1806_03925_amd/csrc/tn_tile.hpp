@@ -168,7 +168,9 @@ inline int tn_tile_args(const TnProblem *p, int count, int edge, TnTileArgs *arg
 // `work`: one of k-ranges x (all tiles of all problems).  k_dev (may be NULL): the real inner length, at most K, only
 // known on the device; the ranges are then cut there, and one beyond the end leaves zeros.
 // lds: C::STAGES * C::STAGE_BYTES, aligned to 1024.
-template <typename C>
+// PAIR: 512 threads and twice the LDS; either half of the wavefronts walks one half of the range, and the first adds the second's result
+// to its own.
+template <typename C, bool PAIR = false>
 __device__ __forceinline__ void tn_tile(const TnTileArgs &args, int K, int splits, const int32_t *__restrict__ k_dev, int work,
                                         unsigned char *lds) {
   using T = typename C::T;
@@ -182,10 +184,21 @@ __device__ __forceinline__ void tn_tile(const TnTileArgs &args, int K, int split
   const int M = q.M, N = q.N, tile = tile_all - args.first_tile[which];
   const int n_tiles = (N + C::BN - 1) / C::BN;
   const int m0 = (tile / n_tiles) * C::BM, n0 = (tile % n_tiles) * C::BN;
-  const int k_begin = z * k_chunk, k_end = min(K, k_begin + k_chunk);
+  int k_begin = z * k_chunk, k_end = min(K, k_begin + k_chunk);
 
   const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wave = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) & (C::WAVES - 1));
+  const int half = PAIR ? __builtin_amdgcn_readfirstlane(threadIdx.x / C::THREADS) : 0;
+  int rounds = k_end > k_begin ? (k_end - k_begin + C::KD - 1) / C::KD : 0;   // of the longer half
+  if constexpr (PAIR) {
+    lds += half * C::STAGES * C::STAGE_BYTES;
+    rounds = (rounds + 1) / 2;
+    const int middle = min(k_end, k_begin + rounds * C::KD);
+    if (half == 0)
+      k_end = middle;
+    else
+      k_begin = middle;
+  }
   const int wm = wave >> 1, wn = wave & 1;
   constexpr int VEC = 16 / (int)sizeof(T);
   // a DMA instruction copies four k-rows; LDS slot lane % 16 of k-row lane / 16 receives this piece of the row
@@ -229,8 +242,8 @@ __device__ __forceinline__ void tn_tile(const TnTileArgs &args, int K, int split
     a_addr[0] = lds_base + at + (uint32_t)wm * 128u;
     b_addr[0] = lds_base + C::OPERAND_BYTES + at + (uint32_t)wn * 128u;
   } else {
-    const int j = lane & 15, half = (lane >> 4) & 1, g = lane >> 5;
-    const uint32_t at = (uint32_t)(8 * g + (j >> 2)) * C::ROW + 32u * half + 8u * (j & 3);
+    const int j = lane & 15, h = (lane >> 4) & 1, g = lane >> 5;
+    const uint32_t at = (uint32_t)(8 * g + (j >> 2)) * C::ROW + 32u * h + 8u * (j & 3);
 #pragma unroll
     for (int i = 0; i < C::WTM; ++i) a_addr[i] = lds_base + at + (uint32_t)(((wm * C::WTM + i) ^ (j >> 2)) << 6);
 #pragma unroll
@@ -238,13 +251,36 @@ __device__ __forceinline__ void tn_tile(const TnTileArgs &args, int K, int split
       b_addr[i] = lds_base + C::OPERAND_BYTES + at + (uint32_t)(((wn * C::WTN + i) ^ (j >> 2)) << 6);
   }
   int stage = 0, fill = C::STAGES - 1;
-  for (int t = 0; t < nk; ++t) {
-    wait_stages<2 * C::DMA, C::STAGES - 2>(nk - 1 - t);
+  for (int t = 0; t < rounds; ++t) {
+    if (!PAIR || t < nk) wait_stages<2 * C::DMA, C::STAGES - 2>(nk - 1 - t);
     block_barrier();
+    if (PAIR && t >= nk) break;   // the second half's last round, if it has one less; no barrier of the first half's is behind it
     if (t + C::STAGES - 1 < nk) issue(t + C::STAGES - 1, fill);
     mma_stage_rows<C>(acc, a_addr, b_addr, (uint32_t)stage * C::STAGE_BYTES);
     stage = stage + 1 == C::STAGES ? 0 : stage + 1;
     fill = fill + 1 == C::STAGES ? 0 : fill + 1;
+  }
+  if constexpr (PAIR) {
+    static_assert(C::WTM * C::WTN * 16 * C::THREADS * 4 <= C::STAGES * C::STAGE_BYTES, "a half's result fits in its stages");
+    block_barrier();   // all reads of the stages are done
+    float *other = reinterpret_cast<float *>(half == 0 ? lds + C::STAGES * C::STAGE_BYTES : lds) + threadIdx.x % C::THREADS;
+    if (half == 1) {
+#pragma unroll
+      for (int i = 0; i < C::WTM; ++i)
+#pragma unroll
+        for (int j = 0; j < C::WTN; ++j)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) other[((i * C::WTN + j) * 16 + e) * C::THREADS] = acc[i][j][e];
+      wait_lgkm<0>();
+    }
+    block_barrier();
+    if (half == 1) return;
+#pragma unroll
+    for (int i = 0; i < C::WTM; ++i)
+#pragma unroll
+      for (int j = 0; j < C::WTN; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[i][j][e] += other[((i * C::WTN + j) * 16 + e) * C::THREADS];
   }
   float *dst = q.partial + (size_t)z * M * N;
   const int c = lane & 31, g = lane >> 5;

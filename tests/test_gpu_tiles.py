@@ -138,3 +138,18 @@ def test_weights_in_the_order_of_large_tiles(batch, layers, d, D):
                              img_id=full.img_id[:full.img_off[B]], label=full.label[:B]))
     assert torch.equal(whole.region("logits", batch)[:B], part.region("logits", B))
     assert torch.equal(4.0 * whole.region("dx", batch)[:B].float(), part.region("dx", B).float())
+
+
+@pytest.mark.parametrize("M,N,K,splits", [
+    (8, 8, 32, 1), (8, 8, 33, 1), (136, 264, 65, 1), (128, 128, 64, 2),      # one round, a half that has none, halves of unlike length
+    (136, 40, 1_000, 3), (520, 72, 4_099, 25), (256, 256, 4_096, 64),        # tiles and ranges that nothing divides; 256 workgroups
+    (256, 264, 4_096, 64),                                                    # and more: single ones
+])
+def test_weight_gradients_by_two_halves_of_a_range(M, N, K, splits):
+    """bf16 values of few bits, so that all sums are exact."""
+    import paper_1806_03925_amd as g
+    gen = torch.Generator(device="cuda").manual_seed(K)
+    a = torch.randint(-4, 5, (K, M), device="cuda", generator=gen).bfloat16()
+    b = torch.randint(-4, 5, (K, N), device="cuda", generator=gen).bfloat16()
+    out = g.gear_gemm(a, b, 1, splits=splits)
+    assert torch.equal(out.double().cpu(), a.double().cpu().T @ b.double().cpu())
