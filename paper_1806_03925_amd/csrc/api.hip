@@ -616,7 +616,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   const bool is_short = (long long)2 * B + b->nnz < kOneStreamIds && macs * (dt == GEAR_BF16 ? 1 : 4) < kOneStreamMacs;
   // In blocks of views: the whole network in one launch (rows.hip), of a short step with the grouping of the ids in its first
   // workgroups.  A longer one has the grouping on the other stream, by tiles that are counted ahead of every pass
-  // (group_device.hpp), from the start of the step on, so that it is done when the weight gradients are, and the bookkeeping
+  // (group_device.hpp), from the prologue on, which counts the first pass, so that it is done when the weight gradients are, and the bookkeeping
   // follows those on the caller's (accumulation beside weight gradients, in one launch or on two streams, took as long as one
   // behind the other, and the wait for the blocks 10 us more).  us a step, tiles that look back / counted: 16 384 views of 576 ->
   // 512 -> 256 bf16, 106 000 ids, 170 / 158; of 320 -> 256 fp32, 172 000 ids, 178 / 166.

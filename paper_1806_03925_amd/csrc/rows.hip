@@ -7,15 +7,17 @@
 //
 // Layer by layer a short step is a chain of eight to twelve dependent launches of 4 to 16 us, each of which pays its ramp,
 // the latency of its first operands and the links of the grouping it carries.  Here the chain is four launches: the prologue,
-// this one, accumulation beside weight gradients (accum_wgrad.hip) and the parameter update.  us a step, layer by layer / so,
-// 512 views fp32 51 / 31, 4096 views of 320 -> 256 -> 128 fp32 104 / 74, 5000 of 288 -> 256 fp32 79 / 62, 1000 of 336 ->
-// 320 -> 72 -> 64 bf16 86 / 44.  What bounds it: 4096 views in fp32 take 29 us here, of which the matrix instructions need
-// 12 and the gather 4; the rest is the first fetch of each layer's weights (cold in every XCD's L2), the waits between
-// phases and, in the smallest steps, the fetch of instructions (about 0.5 us a KB of code that runs once).
+// this one, accumulation beside weight gradients (accum_wgrad.hip) and the parameter update; small fp32 networks need no prologue
+// (kDirectBytes).  us a step, layer by layer / so, 512 views fp32 51 / 25, 4096 views of 320 -> 256 -> 128 fp32 104 / 73, 5000 of 288 ->
+// 256 fp32 79 / 59, 1000 of 336 -> 320 -> 72 -> 64 bf16 86 / 41.  What bounds it: a chain of phases.  4096 views in fp32 take 28 us here:
+// gather 5, products 6, 4, 3 and 5.5 (the matrix instructions 12 of them), logit layer 1, its columns 1.3, the sums of delta 1; 512 views
+// of 96 -> 64 take 9: 3.5, 1.5 and 1, logit 1, columns 1.3.  Run a second time in the same launch a block of the latter is 1 us shorter, so
+// neither the fetch of instructions nor that of cold weights is what is left.
 //
 // The weights come straight from memory (every XCD's L2 holds them) into the registers of the one wavefront that owns
 // those columns: they are laid out in operand order ahead of the step (prep.hip), so that a wavefront's load is 1 KB in one
-// piece.  Each weight is read once per workgroup.
+// piece.  Each weight is read once per workgroup: 1.7 MB for 64 views of 576 -> 512 -> 256, at half of the 64 bytes a clock that a CU gets from
+// L2, is what bounds the products of the larger networks (touching all of them ahead of the gather made no difference).
 //
 // Every product adds k in ascending order, in steps of the 16 x 16 matrix instructions, which gives the bits of the
 // 32 x 32 ones of the other product kernels: a hidden unit next to zero takes the same branch in either form of a step.
