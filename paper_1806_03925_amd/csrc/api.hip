@@ -700,7 +700,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   plan.row_at = local_sort ? gb.p[2].perm : nullptr;
   plan.local = no_prologue ? local_result(rows, gb, b->nnz, out->ready_cap) : LocalResult{};
   LocalOutputs local_out = {};
-  if (local_sort) local_out = LocalOutputs{plan.local, out->status, out->n_ready, out->loss};
+  if (local_sort) local_out = LocalOutputs{plan.local, out->status, out->n_ready};
   const PlanArgs plan_args = {plan, occ_view, b->img_off, counts, M, out->ready_cap, out->n_ready, out->status};
   // Not carried: what depends only on ids and counters (the check of the ids, the grouping, the accumulation plan) runs on
   // the helper stream while the main stream gathers and runs the forward pass.  The
@@ -770,7 +770,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
   void *dx_dfv = ws + lay.dx_dfv;
   if (by_rows) {
     LocalTask local = {};
-    if (local_sort) local = local_task(rows, gb, plan_args, views, failed);
+    if (local_sort) local = local_task(rows, gb, plan_args, views, failed, out->loss);
     hipStream_t caller = s;
     {
       hipStream_t s = group_here ? helper : caller;

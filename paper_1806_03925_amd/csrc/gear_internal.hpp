@@ -263,6 +263,7 @@ struct LocalTask {
   // where the step has a prologue, which clears them: what the parts of the last list publish ([parts][3]), and their ticket
   uint32_t *state;
   int32_t *ticket, *failed;
+  float *loss;                           // where it has none the first workgroup clears the step's outputs: this, and the plan's
   int blocks, room;                      // workgroups; items that LDS has room for
 };
 // the distinct ids and their segments from where the parts have left them to where one after the other belongs (each may be NULL)
@@ -441,11 +442,11 @@ struct LossSum {   // *loss = (sum of the partial sums) / B; parts = 0: not want
   int parts, B;
 };
 constexpr int kMaxColumnSums = GEAR_MAX_LAYERS + 2;
-// n_ready (may be NULL) is cleared if the step has failed; with local.parts, all outputs are written here.
+// n_ready (may be NULL) is cleared if the step has failed; with local.parts, it and what has gone wrong are written here, and the status
+// word is left alone otherwise: what another call has reported there meanwhile stays.
 struct LocalOutputs {
   LocalResult local;
   int32_t *status, *n_ready;
-  float *loss;
 };
 // all of that in one launch, and level 2 of an embedding update (may be NULL)
 struct EmbeddingWork;

@@ -441,6 +441,12 @@ template <bool PARTS> __device__ __forceinline__ void local_group(const LocalTas
   const int first = 1 << t.list[0].parts_log2, second = first + (1 << t.list[1].parts_log2);
   const bool last = block >= second;
   const int word = block;
+  // Past the L2, from which they would be written back when the launch ends, over what another call has reported meanwhile.
+  if (PARTS && block == 0 && threadIdx.x == 0) {
+    __hip_atomic_store(t.plan.status, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(t.plan.n_ready, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(t.loss, 0.0f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
   LocalList p = t.list[0];
   if (last)
     p = t.list[2], block -= second;

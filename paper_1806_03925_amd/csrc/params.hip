@@ -116,9 +116,10 @@ __global__ void __launch_bounds__(256) k_param_update(ParamArgs args, std::condi
     const LocalState local = local_state(args.local.local, 0);
     const int emits = blockIdx.x == 0 ? emits_of(args.local.local, args.local.local.n_parts) : 0;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
-      *args.local.status = local.code;
-      *args.local.n_ready = local.code ? 0 : emits;
-      if (local.code) *args.local.loss = 0.0f;
+      if (local.code)
+        atomicCAS(args.local.status, 0, local.code);
+      else
+        *args.local.n_ready = emits;
     }
     if (local.code) return;
   } else if (*status != 0) {

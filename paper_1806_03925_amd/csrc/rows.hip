@@ -894,7 +894,7 @@ LocalResult local_result(const RowsPlan &plan, const GroupBatch &gb, int nnz, in
   return r;
 }
 
-LocalTask local_task(const RowsPlan &plan, const GroupBatch &gb, const PlanArgs &args, const ViewCheck &views, int32_t *failed) {
+LocalTask local_task(const RowsPlan &plan, const GroupBatch &gb, const PlanArgs &args, const ViewCheck &views, int32_t *failed, float *loss) {
   LocalTask t;
   t.blocks = 0;
   t.room = plan.room;
@@ -911,6 +911,7 @@ LocalTask local_task(const RowsPlan &plan, const GroupBatch &gb, const PlanArgs 
   t.state = gb.seg_state;
   t.ticket = (int32_t *)gb.seg_state + kStateSpan;
   t.failed = failed;
+  t.loss = loss;
   return t;
 }
 

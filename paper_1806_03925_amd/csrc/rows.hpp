@@ -59,7 +59,7 @@ bool plan_rows(const gear_config &cfg, const Layout &lay, int B, int nnz, bool l
 LogitSums rows_sums(const RowsPlan &plan, const float *partials, int H);
 BlockSums block_sums_of(const RowsPlan &plan, const Layout &lay, const gear_batch &b, char *ws);   // the same sums, from the launches of the layers
 LocalResult local_result(const RowsPlan &plan, const GroupBatch &gb, int nnz, int ready_cap);
-LocalTask local_task(const RowsPlan &plan, const GroupBatch &gb, const PlanArgs &args, const ViewCheck &views, int32_t *failed);
+LocalTask local_task(const RowsPlan &plan, const GroupBatch &gb, const PlanArgs &args, const ViewCheck &views, int32_t *failed, float *loss);
 void local_zero_list(const GroupBatch &gb, ZeroList *z);
 hipError_t launch_rows(const gear_config &cfg, const Layout &lay, const RowsPlan &plan, const gear_batch &b, const gear_tables &t,
                        const void *dfv_cache, char *ws, const LocalTask &local, hipStream_t s);

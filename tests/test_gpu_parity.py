@@ -970,6 +970,32 @@ def test_a_step_that_fails_part_way_still_joins_the_helper_stream(name):
     pair.step(PageViewSource(wl).batch(0), wl.lr, f"{name} after failed enqueues")
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])   # without a prologue, with one
+def test_a_step_that_fails_part_way_does_not_show_the_outputs_of_the_last_one(dtype):
+    """Whatever reads a step's outputs on the device must not take the length of the last step's list for this one's: what is
+    there behind the launches that were enqueued is this step's, or nothing."""
+    wl = get_workload("tiny").scaled(emb_dtype=dtype, dfv_dtype=dtype, mlp_dtype=dtype, M=1)
+    cfg = g.config_for(wl)
+    st = g.GearState(cfg)
+    g.gear_init_tables(st)
+    src = PageViewSource(wl)
+    dev = g.DeviceBatch.from_host(src.batch(0))
+    names = launches_of(st, dev, wl.M, wl.lr)
+    assert names == ["begin"] * (dtype == "bf16") + ["view_blocks", "accumulate_wgrad", "param_update"]
+    try:
+        for nth in range(2, len(names) + 1):
+            st.status.fill_(77), st.n_ready.fill_(12_345), st.loss.fill_(9.0)
+            g.gear_debug_fail_launch(nth)
+            with pytest.raises(g.GearError):
+                g.gear_step(st, dev, wl.M, wl.lr)
+            torch.cuda.synchronize()
+            assert int(st.status.item()) == 0 and float(st.loss.item()) == 0.0, nth
+            # with a prologue the launch that sorts the ids writes the length; without one the last launch does
+            assert int(st.n_ready.item()) == (dev.nnz if dtype == "bf16" and nth > 2 else 0), nth
+    finally:
+        g.gear_debug_fail_launch(0)
+
+
 def test_host_checked_arguments():
     wl = get_workload("tiny")
     cfg, st, _ = make_pair(wl)

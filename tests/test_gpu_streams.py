@@ -3,7 +3,7 @@ import numpy as np
 import pytest
 import torch
 
-from step_forms import form_of
+from step_forms import form_of, form_of_launches, launches_of
 
 pytestmark = pytest.mark.gpu
 
@@ -89,6 +89,50 @@ def test_a_step_does_not_read_the_status_word_that_others_write(name, batch, cha
     assert int(results[0][1].item()) > 0
     for a, b in zip(*results):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])   # without a prologue, with one
+def test_what_others_report_while_a_step_runs_stays(dtype):
+    """A step clears its status word when it starts and not again: refreshes on another stream that report a bad id from before the
+    middle of it on are still seen behind it.  All images are one and no group closes, so that the accumulation is one chain of
+    19 000 rows, many times as long as all that comes ahead of it."""
+    import paper_1806_03925_amd as g
+    from gear_inputs import get_workload
+    from gear_inputs.pageviews import PageViewBatch
+    B, nnz = 100, 19_000
+    wl = get_workload("tiny").scaled(batch=B, layers=(16, 1), emb_dim=8, dfv_dim=8, emb_dtype=dtype, dfv_dtype=dtype, mlp_dtype=dtype,
+                                     n_users=1_000, n_urls=1_000, n_images=2_000, max_images=190, M=1 << 20)
+    st = g.GearState(g.config_for(wl))
+    g.gear_init_tables(st)
+    rng = np.random.default_rng(0)
+    dev = g.DeviceBatch.from_host(PageViewBatch(
+        user_id=rng.integers(0, 1_000, B).astype(np.int32), url_id=rng.integers(0, 1_000, B).astype(np.int32),
+        img_off=(190 * np.arange(B + 1)).astype(np.int32), img_id=np.full(nnz, 7, dtype=np.int32), label=np.zeros(B, dtype=np.float32)))
+    names = launches_of(st, dev, wl.M, 0.1)
+    assert form_of_launches(names) == "blocks" and ("begin" in names) == (dtype == "bf16")
+    other = g.GearState(g.make_config(16, 16, 16, 8, 8, (8, 1), max_batch=1, max_nnz=64))
+    other.status = st.status
+    bad, rows = torch.full((64,), 16, dtype=torch.int32, device="cuda"), torch.zeros((64, 8), device="cuda")
+    begin, reported, end = (torch.cuda.Event(enable_timing=True) for _ in range(3))
+    for _ in range(8):   # another stream each time: one that shares a queue of the device with the step's runs behind it
+        beside = torch.cuda.Stream()
+        torch.cuda.synchronize()
+        begin.record()
+        beside.wait_event(begin)
+        g.gear_step(st, dev, wl.M, 0.1)
+        end.record()
+        with torch.cuda.stream(beside):
+            for _ in range(60):
+                g.gear_refresh_dfv(other, bad, rows)
+            reported.record()
+        torch.cuda.synchronize()
+        at, whole = begin.elapsed_time(reported), begin.elapsed_time(end)
+        print(f"{dtype}: reported until {at:.3f} of {whole:.3f} ms", flush=True)
+        if 0.2 < at < 0.8 * whole:
+            break
+    else:
+        pytest.fail("no refresh ran beside the step")
+    assert int(st.status.item()) == g.GEAR_ERR_RANGE
 
 
 # views of the bf16 workload: in blocks on one stream (13 000 ids), with the grouping on the helper stream, in counted tiles (58 000)
