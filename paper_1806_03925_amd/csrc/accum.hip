@@ -50,7 +50,7 @@ k_accumulate(AccumPlan plan, const GT *__restrict__ dx, int D, float *__restrict
     block -= emb.sum_blocks;
     blocks -= emb.sum_blocks;
   }
-  accumulate_units<GT, AT, false>(plan, LocalState{}, dx, D, accum, M, ready_ids, ready_grads, block, blocks, threadIdx.x, blockDim.x);
+  accumulate_units<GT, AT, false>(plan, LocalState{}, dx, D, accum, nullptr, M, ready_ids, ready_grads, block, blocks, threadIdx.x, blockDim.x);
 }
 
 // dfv_cache[ids[r]] = rows[r]; one wavefront per row, 16-byte pieces

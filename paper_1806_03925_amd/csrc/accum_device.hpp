@@ -120,29 +120,36 @@ __device__ __forceinline__ void add_rows_at(float (&acc)[Cols<GT>::N], const Acc
 }
 
 // The units u, u + stride, ..., one after the other, by `threads` threads of which this is number t.  AT: the lists were sorted in LDS;
-// PARTS: the plan lies in parts, and these are the units of one.
+// PARTS: the plan lies in parts, and the counters of the images go with their first units (as in count_images, which has one thread for each
+// of them and would have to look for its part).
 template <typename GT, bool AT, bool PARTS>
 __device__ __forceinline__ void accumulate_units(const AccumPlan &plan, const LocalState &local, const GT *__restrict__ dx, int D, float *__restrict__ accum,
-                                                 int M, int32_t *__restrict__ ready_ids, float *__restrict__ ready_grads, int u,
-                                                 int stride, int t, int threads) {
+                                                 int32_t *__restrict__ counts, int M, int32_t *__restrict__ ready_ids,
+                                                 float *__restrict__ ready_grads, int u, int stride, int t, int threads) {
   constexpr int N = Cols<GT>::N;
-  const int n_units = PARTS ? local.units : *plan.n_units, first = PARTS ? local.below : 0;
-  int emitted = -1;   // emissions of lower parts
-  auto unit = [&](int i) { return plan.units[first + i]; };
+  const int n_units = PARTS ? local.units : *plan.n_units;
+  int slot = 0, slot_next = 0;   // emissions of lower parts
+  auto unit = [&](int i, int &below) {
+    if constexpr (PARTS) {
+      const int part = part_of_unit(local, i);
+      below = __builtin_amdgcn_readlane(local.slot, part);
+      i += __builtin_amdgcn_readlane(local.place, part);
+    }
+    return plan.units[i];
+  };
   const int DC = D / N;
   const float fM = (float)M;
   if (u >= n_units) return;
-  UnitDesc d = unit(u);
+  UnitDesc d = unit(u, slot);
   while (true) {
     const int u_next = u + stride;
     UnitDesc d_next = d;
-    if (u_next < n_units) d_next = unit(u_next);  // in flight while this unit is summed
+    if (u_next < n_units) d_next = unit(u_next, slot_next);  // in flight while this unit is summed
     float *arow = accum + (size_t)d.image * D;
-    if constexpr (PARTS)
-      if (d.q0 != d.s0 || d.s1 - d.s0 >= M - d.phase) {   // the unit emits
-        if (emitted < 0) emitted = emits_of(plan.local, local.part);
-        d.slot += emitted;
-      }
+    if constexpr (PARTS) {
+      d.slot += slot;
+      if (t == 0 && d.q0 == d.s0) counts[d.image] = d.collected;
+    }
     for (int cg = t; cg < DC; cg += threads) {
       const GT *col = dx + N * cg;
       auto add = [&](float (&to)[N], int qa, int qb) {
@@ -192,6 +199,7 @@ __device__ __forceinline__ void accumulate_units(const AccumPlan &plan, const Lo
     if (u_next >= n_units) break;
     u = u_next;
     d = d_next;
+    slot = slot_next;
   }
 }
 
@@ -220,10 +228,7 @@ __device__ __forceinline__ bool chunks_ride(const AccumPlan &plan, const RideWor
   }
   block -= 2 * emb.blocks;
   if (block >= emb.count_blocks) return false;
-  if (plan.local.parts)
-    count_images(plan, block, emb.w.counts, threadIdx.x, blockDim.x);   // a workgroup for each part
-  else
-    count_images(plan, -1, emb.w.counts, block * blockDim.x + threadIdx.x, emb.count_blocks * blockDim.x);
+  count_images(plan, emb.w.counts, block * blockDim.x + threadIdx.x, emb.count_blocks * blockDim.x);
   return true;
 }
 

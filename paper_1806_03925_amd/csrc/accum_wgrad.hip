@@ -29,20 +29,18 @@ k_accumulate_wgrad(AccumPlan plan, const GT *__restrict__ dx, int D, float *__re
   if (block < w.tn_blocks) return tn_tile<C>(w.tn, w.K, w.splits, nullptr, xcd_remap(block, w.tn_blocks), lds);   // into the workspace only
   block -= w.tn_blocks;
   blocks -= w.tn_blocks;
-  const int rides = 2 * w.ride.blocks + w.ride.count_blocks;
-  int turn = block - rides, stride = blocks - rides;   // of the units; of those of one part
   LocalState local = {};
-  if constexpr (PARTS) {   // the units' workgroups are a multiple of the parts, and those of a part on all XCDs
-    const int log2 = plan.local.parts_log2;
-    local = local_state(plan.local, turn < 0 ? 0 : (turn + (turn >> log2)) & (plan.local.n_parts - 1));
+  if constexpr (PARTS) {
+    local = local_state(plan.local, true);
     if (local.code != 0) return;
-    turn >>= log2, stride >>= log2;
   } else {
     if (*status != 0) return;
   }
   if (chunks_ride(plan, w.ride, block)) return;
+  block -= 2 * w.ride.blocks + w.ride.count_blocks;
+  blocks -= 2 * w.ride.blocks + w.ride.count_blocks;
   const int side = 256 / w.unit_threads, which = __builtin_amdgcn_readfirstlane((int)threadIdx.x / w.unit_threads);
-  accumulate_units<GT, true, PARTS>(plan, local, dx, D, accum, M, ready_ids, ready_grads, turn * side + which, stride * side,
+  accumulate_units<GT, true, PARTS>(plan, local, dx, D, accum, w.ride.w.counts, M, ready_ids, ready_grads, block * side + which, blocks * side,
                                     (int)threadIdx.x - which * w.unit_threads, w.unit_threads);
 }
 
@@ -60,7 +58,7 @@ hipError_t launch_accumulate_wgrad(const gear_config &cfg, const GroupProblem &i
   w.ride.blocks = (int)(((long long)embedding_chunks(emb) * w.ride.lanes + threads - 1) / threads);
   w.ride.count_blocks = (img.n + 4 * threads - 1) / (4 * threads);
   if (w.ride.count_blocks > 256) w.ride.count_blocks = 256;
-  if (plan.local.parts) w.ride.count_blocks = plan.local.n_parts;
+  if (plan.local.parts) w.ride.count_blocks = 0;   // the units do
   w.ride.sum_blocks = 0;
   w.K = K;
   w.splits = splits;
@@ -72,7 +70,6 @@ hipError_t launch_accumulate_wgrad(const gear_config &cfg, const GroupProblem &i
   const int side = threads / w.unit_threads;
   int units = (img.n + side - 1) / side;
   if (units > 32768) units = 32768;
-  if (plan.local.parts) units = (units + plan.local.n_parts - 1) / plan.local.n_parts * plan.local.n_parts;
   const dim3 grid((unsigned)(w.tn_blocks + 2 * w.ride.blocks + w.ride.count_blocks + units));
   if (bf16 && plan.local.parts) return hipErrorInvalidValue;
   if (bf16)

@@ -143,11 +143,11 @@ __device__ __forceinline__ void embedding_chunk(const EmbeddingTable &t, int tid
 }
 
 // counts[image] += occurrences of the image in this step (Section 1, third point), by the image's first unit; thread `at`
-// of `stride`.  part: of a plan that lies in parts, else -1
-__device__ __forceinline__ void count_images(const AccumPlan &plan, int part, int32_t *__restrict__ counts, int at, int stride) {
-  const int n = part < 0 ? *plan.n_units : plan.local.parts[part].units, first = part < 0 ? 0 : plan.local.parts[part].below;
+// of `stride`
+__device__ __forceinline__ void count_images(const AccumPlan &plan, int32_t *__restrict__ counts, int at, int stride) {
+  const int n = *plan.n_units;
   for (int u = at; u < n; u += stride) {
-    const UnitDesc d = plan.units[first + u];
+    const UnitDesc d = plan.units[u];
     if (d.q0 == d.s0) counts[d.image] = d.collected;
   }
 }

@@ -199,7 +199,7 @@ constexpr int kCodeGroup = 64;
 struct LocalResult {
   PartCounts *parts;      // [n_parts], 16-byte aligned; NULL: not so
   uint8_t *codes;         // [n_codes up to a whole group, 64-byte aligned] whether a workgroup has found ids or offsets that are wrong
-  int parts_log2, n_parts, n_codes;   // of the parts, which are a power of two
+  int n_parts, n_codes;
   int ready_cap;          // -1: more emissions than there is room for cannot be
 };
 

@@ -113,13 +113,12 @@ template <bool SPANS>
 __global__ void __launch_bounds__(256) k_param_update(ParamArgs args, std::conditional_t<SPANS, SpanWork, NoSpans> spans,
                                                       Optim opt, const int32_t *__restrict__ status) {
   if (args.local.local.parts) {
-    const LocalState local = local_state(args.local.local, 0);
-    const int emits = blockIdx.x == 0 ? emits_of(args.local.local, args.local.local.n_parts) : 0;
+    const LocalState local = local_state(args.local.local, blockIdx.x == 0);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
       if (local.code)
         atomicCAS(args.local.status, 0, local.code);
       else
-        *args.local.n_ready = emits;
+        *args.local.n_ready = local.emits;
     }
     if (local.code) return;
   } else if (*status != 0) {

@@ -730,9 +730,11 @@ constexpr int kStateSpan = 3 * kMaxParts;   // words of three per part, then a t
 // 37.3 / 34.1, 4000 57.2 / 53.6.  Beyond: 288 -> 64 -> 64 (180 KB) 1000 33.7 / 34.1; 1056 -> 24 (203 KB) 1000 51.4 / 52.3; 320 -> 256 -> 128
 // 4096 74.8 / 78.1; and with more than a block a CU 288 -> 64 (147 KB) 5000 44.6 / 47.3, 288 -> 256 61.0 / 71.0.
 constexpr double kDirectBytes = 170e3, kDirectBytesLong = 100e3;   // up to 4096 views, beyond
-// And of all occurrences' gradients: where the accumulation is long, units that are found part by part, some parts with few, keep it longer
-// (with the prologue / without, D = 256, 320 -> 64: 9000 occurrences, 9 MB, M = 2 44.8 / 42.0, M = 16 43.1 / 38.7; 18 000, 18 MB, M = 2
-// 62.2 / 63.3, M = 16 57.1 / 54.1, of skewed ids in 21 of 32 parts 65.5 / 69.3; D = 64, 18 000, 4.6 MB 43.4 / 39.5).
+// And of all occurrences' gradients: where the accumulation is long, what every one of its wavefronts does to find its units
+// (local_parts.hpp) keeps it longer.  With the prologue / without, M = 2, however the ids are spread unless it says so: 320 -> 64, 11 500
+// occurrences, 12 MB, 3000 views 50.1 / 46.1, 500 44.2 / 42.5; 528 -> 32, 5500, 11 MB, 2000 views 47.2 / 46.7, Zipf 1.1 55.6 / 50.6; 784 -> 24,
+// 3900, 12 MB, 500 views 54.1 / 54.5, Zipf 1.1 48.5 / 47.4; a few steps with wider rows lose 1.  Beyond: 320 -> 64, 18 000, 18 MB, 3000
+// views 53.9 / 50.6, 500 50.9 / 52.0; 400 -> 48, 28 MB, 4096 views 71.3 / 73.2; 576 -> 32, 37 MB, 2000 views 69.2 / 72.1.
 constexpr double kDirectGradients = 12e6;
 constexpr int kLocalPart = 1024;   // ids of a part, where they are spread evenly (2048: a step of 4096 views 1.5 us longer)
 
@@ -886,8 +888,7 @@ LocalResult local_result(const RowsPlan &plan, const GroupBatch &gb, int nnz, in
   LocalResult r;
   r.parts = (PartCounts *)gb.seg_state;
   r.codes = (uint8_t *)gb.p[0].state;
-  r.parts_log2 = plan.parts_log2[kMaxProblems - 1];
-  r.n_parts = 1 << r.parts_log2;
+  r.n_parts = 1 << plan.parts_log2[kMaxProblems - 1];
   r.n_codes = 0;
   for (int i = 0; i < kMaxProblems; ++i) r.n_codes += 1 << plan.parts_log2[i];
   r.ready_cap = ready_cap < nnz ? ready_cap : -1;   // an emission has an occurrence of its own

@@ -26,7 +26,7 @@ __global__ void __launch_bounds__(256) k_embedding_chunks(EmbeddingWork w, int l
   if (*status != 0) return;
   const int tid = blockIdx.x * blockDim.x + threadIdx.x;
   if (blockIdx.y == 2)
-    count_images(w.plan, -1, w.counts, tid, gridDim.x * blockDim.x);
+    count_images(w.plan, w.counts, tid, gridDim.x * blockDim.x);
   else
     embedding_chunk<ET, 8>(w.table[blockIdx.y], tid, w.dx, 2 * w.d, w.d, lanes, w.opt);
 }

@@ -490,6 +490,57 @@ def test_blocks_that_read_the_weights_as_they_are(batch, layers, d, D, prologue)
     assert torch.equal(4.0 * states[1].region("dx", full.B)[:batch], states[0].region("dx", batch))
 
 
+@pytest.mark.parametrize("M,D", [(2, 64), (4, 72), (3, 264), (4, 520)])   # workers of a wavefront, of two, of four
+@pytest.mark.parametrize("first", [0, 32_768, (1 << 20) - 4_100])
+def test_units_that_are_all_in_one_part(M, D, first):
+    """Of a list of a power of two ids' range: the first, the second and the last of the parts, and one image of the part in the middle."""
+    from gear_inputs.pageviews import PageViewBatch
+    B, nnz, n_images = 1_000, 5_700, 1 << 20
+    wl = wl_of("f32", B, (16, 1), 8, D, n_images=n_images, max_images=6, M=M)
+    pair = beside_the_oracle(wl)
+    rng = np.random.default_rng(M)
+    for step in range(2):
+        ids = first + rng.permutation(4_100)[rng.integers(0, 3_000, nnz)]
+        ids[:: 50] = n_images // 2 + 1
+        off = np.sort(rng.integers(0, nnz + 1, B - 1))
+        batch = PageViewBatch(user_id=rng.integers(0, wl.n_users, B).astype(np.int32), url_id=rng.integers(0, wl.n_urls, B).astype(np.int32),
+                              img_off=np.concatenate([[0], off, [nnz]]).astype(np.int32), img_id=ids.astype(np.int32),
+                              label=(rng.random(B) < 0.3).astype(np.float32))
+        assert in_blocks(pair, batch, f"{M} {D} from {first}, step {step}")
+    pair.check_state(f"{M} {D} from {first}")
+
+
+def test_units_are_shared_out_whatever_a_part_holds():
+    """19 000 images in one part of the list take the accumulation no longer than 19 000 in all of them (three times as long with a share of the
+    workers for every part)."""
+    import paper_1806_03925_amd as g
+    from gear_inputs.pageviews import PageViewBatch
+    B, nnz, n_images = 4_000, 19_000, 1 << 20
+    wl = wl_of("f32", B, (64, 1), 16, 64, n_images=n_images, max_images=5, M=4)
+    rng = np.random.default_rng(0)
+    some = rng.permutation(20_000)[:nnz]
+    times = []
+    for ids in (some, some * (n_images // 20_000)):
+        st = g.GearState(g.config_for(wl))
+        g.gear_init_tables(st)
+        dev = g.DeviceBatch.from_host(PageViewBatch(
+            user_id=rng.integers(0, wl.n_users, B).astype(np.int32), url_id=rng.integers(0, wl.n_urls, B).astype(np.int32),
+            img_off=(nnz * np.arange(B + 1) // B).astype(np.int32), img_id=ids.astype(np.int32), label=np.zeros(B, dtype=np.float32)))
+        assert launches_of(st, dev, wl.M, 0.0) == ["view_blocks", "accumulate_wgrad", "param_update"]
+        took = []
+        for _ in range(11):
+            st.profile = g.GearProfile()
+            g.gear_step(st, dev, wl.M, 0.0)
+            torch.cuda.synchronize()
+            took.append(dict(st.profile.spans())["accumulate_wgrad"])
+            st.profile.close()
+            st.profile = None
+        assert int(st.status.item()) == 0
+        times.append(sorted(took)[5])
+    print(f"accumulation: one part {times[0]:.4f}, all {times[1]:.4f} ms", flush=True)
+    assert times[0] < 2.0 * times[1]
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])   # without a prologue, with one
 @pytest.mark.parametrize("what", ["user", "url", "image", "first offset", "last offset", "room"])
 def test_a_step_that_fails_among_others(dtype, what):
