@@ -927,7 +927,8 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
       ++n;
     }
     if (n == 0) return GEAR_ERR_CAPACITY;  // cannot happen: the region holds one range of the widest layer
-    int splits = gemm_tn_splits(dt, wp + first, n, B, choice.large, !beside);
+    bool pairs = !beside;
+    int splits = gemm_tn_splits(dt, wp + first, n, B, choice.large, &pairs);
     // Beside the accumulation two thirds as many: the CUs are not theirs alone, and every range is partials to write and to
     // add (us a step, all / two thirds / half: 4096 views 82.2 / 80.4 / 80.4, 5000 64.3 / 63.5 / 65.4).
     if (beside) splits = (2 * splits + 2) / 3;
@@ -947,7 +948,7 @@ gear_status gear_step_adam(const gear_config *cfg, const gear_batch *b, gear_tab
     } else {
       hipStream_t caller = s;
       hipStream_t s = group_here ? helper : caller;
-      GEAR_RUN("wgrad_gemm", launch_gemm_tn(dt, wp + first, n, B, splits, choice.large, nullptr, s));
+      GEAR_RUN("wgrad_gemm", launch_gemm_tn(dt, wp + first, n, B, splits, choice.large, pairs, nullptr, s));
     }
     // The sums of the partials and the SGD change caller state, so the status word has to be final: the
     // stream waits for the helper's first part (long done by now), not for the bookkeeping.  Their
@@ -1086,7 +1087,7 @@ gear_status gear_gemm(int32_t dtype, int32_t form, const void *A, const void *B,
   } else if (form == 1) {
     if (M % vec || N % vec || splits < 1 || splits > 64 || !partial) return GEAR_ERR_INVALID;
     const TnProblem one = {A, B, partial, M, N};
-    GEAR_HIP(launch_gemm_tn(dtype, &one, 1, K, splits, gemm_tn_choice(dtype, &one, 1, K).large, status, s));
+    GEAR_HIP(launch_gemm_tn(dtype, &one, 1, K, splits, gemm_tn_choice(dtype, &one, 1, K).large, true, status, s));
     GEAR_HIP(launch_fill_zero(out, (size_t)M * N * sizeof(float), s));
     const Optim minus = {-1.0f, 0.0f, 0.0f, 0.0f, 1.0f, 0};   // out = 0 - (-1) * sum of the partials
     const Moments none = {nullptr, nullptr};

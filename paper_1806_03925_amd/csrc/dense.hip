@@ -146,7 +146,7 @@ gear_status dense_backward(const gear_dense_config *cfg, const float *raw, float
   int splits = n_dev ? lay.splits : (n_ready + 255) / 256;
   if (splits > lay.splits) splits = lay.splits;
   const TnProblem dw = {ready_grads, rows, partial, cfg->dfv_dim, cfg->raw_dim};
-  DENSE_HIP(launch_gemm_tn(GEAR_F32, &dw, 1, n_ready, splits, false, status, s, n_dev));
+  DENSE_HIP(launch_gemm_tn(GEAR_F32, &dw, 1, n_ready, splits, false, false, status, s, n_dev));
   const Optim sgd = {lr, 0.0f, 0.0f, 0.0f, 1.0f, 0};
   const Moments none = {nullptr, nullptr};
   const SplitkProblem sum = {partial, wd, none, (int64_t)cfg->dfv_dim * cfg->raw_dim};

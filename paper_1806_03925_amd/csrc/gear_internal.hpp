@@ -412,7 +412,7 @@ struct TnProblem {
   int M, N;
 };
 // `large`: on 256 x 256 tiles (bf16, K a multiple of 32 and no k_dev), as gemm_tn_choice says.
-hipError_t launch_gemm_tn(int dtype, const TnProblem *p, int count, int K, int splits, bool large, const int32_t *status,
+hipError_t launch_gemm_tn(int dtype, const TnProblem *p, int count, int K, int splits, bool large, bool pairs, const int32_t *status,
                           hipStream_t s, const int32_t *k_dev = nullptr);
 // how to go about several of them (looks at M and N only): the first `layers` in one launch, on which tiles, in how many ranges
 struct TnChoice {
@@ -420,8 +420,9 @@ struct TnChoice {
   bool large;
 };
 TnChoice gemm_tn_choice(int dtype, const TnProblem *p, int count, int K);
-// pairs: of workgroups that walk two halves of a range (in a launch of their own and of known length, gemm_tile.hip)
-int gemm_tn_splits(int dtype, const TnProblem *p, int count, int K, bool large, bool pairs);
+// *pairs: whether it may be of workgroups that walk two halves of a range (in a launch of their own and of known length, gemm_tile.hip);
+// then whether it is
+int gemm_tn_splits(int dtype, const TnProblem *p, int count, int K, bool large, bool *pairs);
 // w_i <- update(w_i, sum_z partial_i[z]) for the results of such a launch
 struct SplitkProblem {
   const float *partial;
@@ -458,9 +459,9 @@ hipError_t launch_gemm_nt_tile(int dtype, const void *A, const void *B, int M, i
                                const float *bias, const void *aux, void *out, int split, float *colpart,
                                uint8_t *relu_bits, const int32_t *status, hipStream_t s, bool coarse, const SideTask *side, hipEvent_t stop);
 int nt_tile_colsum_parts(int dtype, int M, int N, bool coarse);
-hipError_t launch_gemm_tn_tile(int dtype, const TnProblem *p, int count, int K, int splits, const int32_t *status,
+hipError_t launch_gemm_tn_tile(int dtype, const TnProblem *p, int count, int K, int splits, bool pairs, const int32_t *status,
                                hipStream_t s, const int32_t *k_dev);
-int tn_tile_splits(int dtype, const TnProblem *p, int count, int K, bool pairs);
+int tn_tile_splits(int dtype, const TnProblem *p, int count, int K, bool *pairs);
 long long tn_tile_rows(int dtype, const TnProblem *p, int count, int K);   // that a CU walks, two ranges at a time
 
 hipError_t launch_logit_loss(int dtype, const void *h, const void *wc_last, const float *bias_last, const float *label,

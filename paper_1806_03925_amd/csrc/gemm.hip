@@ -650,7 +650,7 @@ hipError_t launch_gemm_nt(int dtype, const void *A, const void *B, int M, int N,
 // images a view: 1024-256 over 12288 views 254 / 254, 24576 424 / 449; 1024 over 16384 253 / 253, 24576 357 / 373, 32736
 // 416 / 442; 512-512-512 over 20000 289 / 283, 32736 355 / 353; 512-256 over 32736 265 / 263.  From 32768 rows on up to 128
 // tiles are the larger kernel's (512-256 over 65536 views 441 / 445, 1024-256 857 / 953, 320-72 531 / 546; a layer of 256
-// columns 227 / 222).
+// columns 227 / 222).  (All with single workgroups on 128 x 128; pairs of them, gemm_tile.hip, save 2 to 6 of a step.)
 TnChoice gemm_tn_choice(int dtype, const TnProblem *p, int count, int K) {
   if (dtype == GEAR_BF16 && K % DK == 0) {
     long long cost = min(2200, 20000000 / K);   // in half rows of the smaller kernel, 9 ns; a launch more is 1100
@@ -669,19 +669,20 @@ TnChoice gemm_tn_choice(int dtype, const TnProblem *p, int count, int K) {
   return TnChoice{count, false};
 }
 
-int gemm_tn_splits(int dtype, const TnProblem *p, int count, int K, bool large, bool pairs) {
+int gemm_tn_splits(int dtype, const TnProblem *p, int count, int K, bool large, bool *pairs) {
   if (!large) return tn_tile_splits(dtype, p, count, K, pairs);
+  *pairs = false;
   int tiles = 0;
   for (int i = 0; i < count; ++i) tiles += tn_dma_tiles(p[i]);
   return tn_dma_splits(tiles, K);
 }
 
-hipError_t launch_gemm_tn(int dtype, const TnProblem *p, int count, int K, int splits, bool large, const int32_t *status,
+hipError_t launch_gemm_tn(int dtype, const TnProblem *p, int count, int K, int splits, bool large, bool pairs, const int32_t *status,
                           hipStream_t s, const int32_t *k_dev) {
   if (count < 1 || count > GEAR_MAX_LAYERS || splits < 1) return hipErrorInvalidValue;
   for (int i = 0; i < count; ++i)
     if (p[i].M < 4 || p[i].N < 4 || !p[i].A || !p[i].B || !p[i].partial) return hipErrorInvalidValue;
-  if (!large) return launch_gemm_tn_tile(dtype, p, count, K, splits, status, s, k_dev);
+  if (!large) return launch_gemm_tn_tile(dtype, p, count, K, splits, pairs, status, s, k_dev);
   if (k_dev || dtype != GEAR_BF16 || K % DK != 0) return hipErrorInvalidValue;
   TnBatchArgs args;
   args.count = count;

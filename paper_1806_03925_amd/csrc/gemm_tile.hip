@@ -394,10 +394,13 @@ k_gemm_tn_tile(TnTileArgs args, int K, int splits, const int32_t *__restrict__ s
 }
 
 // bf16: what the ranges leave is written, read again and added by the parameter update, so two workgroups of a CU that would walk
-// neighbouring ranges of one tile are one of twice the wavefronts instead, which leaves one partial: of 576 -> 512 -> 256 15 MB and not 31
-// (us a step, 16 384 views 153.1 / 149.3, with Adam 158.4 / 154.1, 10 001 127.3 / 125.4).  Where whole ranges of pairs leave more of the CUs
-// out than those of single ones do, they are not taken (26 tiles, 234 of 256 against 494 of 512: 184.9 / 186.9), nor in fp32, whose 64 x 64
-// tiles leave little (16 384 views 157.3 / 158.0).
+// neighbouring ranges of one tile are one of twice the wavefronts instead, which leaves one partial: of 576 -> 512 -> 256 15 MB and not 31.
+// us a step, single / pairs, in blocks: 16 384 views 153.1 / 149.3, with Adam 158.4 / 154.1, 10 001 127.3 / 125.4; layer by layer on two
+// streams, with the accumulation beside them: 8193 of 1024 -> 256 168.3 / 164.5, 12 000 of 704 -> 640 -> 128 212.6 / 209.5, 16 384 of 1024 ->
+// 1024 304.6 / 298.5, 32 736 of 576 -> 512 -> 256 327.6 / 321.3; on one, 2000 of 576 -> 512 -> 256 108.5 / 106.7.  Where whole ranges of pairs
+// leave more of the CUs out than those of single ones do, they are not taken (26 tiles, 234 of 256 against 494 of 512: 184.9 / 186.9), nor
+// where there are as many ranges either way, so that no partial is left out (a range has 64 rows at least, and there are 64 at most: 600
+// views of 320 -> 256 91.6 / 92.1, 1500 of 128 -> 64 82.7 / 83.4, 16 384 of 128 -> 128 134.0 / 135.1, wider ones the same), nor in fp32, whose 64 x 64 tiles leave little (16 384 views 157.3 / 158.0).
 template <typename C>
 __global__ void __launch_bounds__(2 * C::THREADS)
 k_gemm_tn_pair(TnTileArgs args, int K, int splits, const int32_t *__restrict__ status, const int32_t *__restrict__ k_dev) {
@@ -483,11 +486,11 @@ NtShape nt_shape(int dtype, int M, int N, bool coarse, int epi = EPI_MASK) {
 }
 
 template <typename C>
-hipError_t run_tn(const TnProblem *p, int count, int K, int splits, const int32_t *status, hipStream_t s, const int32_t *k_dev) {
+hipError_t run_tn(const TnProblem *p, int count, int K, int splits, bool pairs, const int32_t *status, hipStream_t s, const int32_t *k_dev) {
   TnTileArgs args;
   static_assert(C::BM == C::BN, "square tiles");
   (void)tn_tile_args(p, count, C::BM, &args);
-  if (sizeof(typename C::T) == 2 && !k_dev && args.tiles * splits <= 256)
+  if (pairs && sizeof(typename C::T) == 2 && !k_dev && args.tiles * splits <= 256)
     hipLaunchKernelGGL((k_gemm_tn_pair<C>), dim3((unsigned)(args.tiles * splits)), dim3(2 * C::THREADS), 0, s, args, K, splits, status, k_dev);
   else
     hipLaunchKernelGGL((k_gemm_tn_tile<C>), dim3((unsigned)(args.tiles * splits)), dim3(C::THREADS), 0, s, args, K, splits, status, k_dev);
@@ -526,9 +529,10 @@ static int tn_splits(int dtype, const TnProblem *p, int count, int K, int slots)
   if (s > 64) s = 64;
   return s < 1 ? 1 : (int)s;
 }
-int tn_tile_splits(int dtype, const TnProblem *p, int count, int K, bool pairs) {
+int tn_tile_splits(int dtype, const TnProblem *p, int count, int K, bool *pairs) {
   const int all = tn_splits(dtype, p, count, K, 512), half = tn_splits(dtype, p, count, K, 256);
-  return pairs && dtype == GEAR_BF16 && 200 * half >= 97 * all ? half : all;
+  *pairs = *pairs && dtype == GEAR_BF16 && half < all && 200 * half >= 97 * all;
+  return *pairs ? half : all;
 }
 
 long long tn_tile_rows(int dtype, const TnProblem *p, int count, int K) {
@@ -536,10 +540,10 @@ long long tn_tile_rows(int dtype, const TnProblem *p, int count, int K) {
   return (tn_tiles(dtype, p, count) * splits + 511) / 512 * ((K + splits - 1) / splits);
 }
 
-hipError_t launch_gemm_tn_tile(int dtype, const TnProblem *p, int count, int K, int splits, const int32_t *status, hipStream_t s,
+hipError_t launch_gemm_tn_tile(int dtype, const TnProblem *p, int count, int K, int splits, bool pairs, const int32_t *status, hipStream_t s,
                                const int32_t *k_dev) {
-  return dtype == GEAR_BF16 ? run_tn<TnBf16>(p, count, K, splits, status, s, k_dev)
-                            : run_tn<TnF32>(p, count, K, splits, status, s, k_dev);
+  return dtype == GEAR_BF16 ? run_tn<TnBf16>(p, count, K, splits, pairs, status, s, k_dev)
+                            : run_tn<TnF32>(p, count, K, splits, pairs, status, s, k_dev);
 }
 
 }  // namespace gear
