@@ -17,14 +17,23 @@ def wl_of(dtype, batch, layers, d, D, **kw):
                                        mlp_dtype=dtype, **kw)
 
 
-def in_blocks(pair, batch, what):
+def launches_beside_the_oracle(pair, batch, what):
     import paper_1806_03925_amd as g
     pair.st.profile = g.GearProfile()
     pair.step(batch, pair.wl.lr, what)
     names = [name for name, _ in pair.st.profile.spans()]
     pair.st.profile.close()
     pair.st.profile = None
-    return "view_blocks" in names
+    return names
+
+
+def in_blocks(pair, batch, what):
+    return "view_blocks" in launches_beside_the_oracle(pair, batch, what)
+
+
+# Short steps in blocks without a prologue, whose parts of the image list do not look at one another, and with one, whose parts wait for the
+# counts of those below: 3 KB of weights, 188 KB.  Both with more LDS for the ids than for the activations.
+PROLOGUE = {(16, 1): False, (128, 160, 1): True}
 
 
 @pytest.mark.parametrize("dtype,batch,layers,d,D", [
@@ -44,6 +53,7 @@ def test_blocks_at_the_edges_of_tiles(dtype, batch, layers, d, D):
     pair.check_state(f"{dtype} {batch} {layers}")
 
 
+@pytest.mark.parametrize("layers", list(PROLOGUE))
 @pytest.mark.parametrize("n_images,nnz,popular,blocks", [
     (2_000, 0, 0.0, True), (1, 1_024, 1.0, True),
     (2_000, 1_024, 0.0, True), (2_000, 1_025, 0.0, True),   # one part, two
@@ -53,11 +63,11 @@ def test_blocks_at_the_edges_of_tiles(dtype, batch, layers, d, D):
     (70_000, 19_199, 0.97, True),
     (2_000, 19_201, 0.1, False),                             # too long a list
 ])
-def test_lists_at_the_edges_of_parts(n_images, nnz, popular, blocks):
+def test_lists_at_the_edges_of_parts(n_images, nnz, popular, blocks, layers):
     """`popular`: the share of the occurrences that are one image, the last of all."""
     from gear_inputs.pageviews import PageViewBatch
     B = 2_560
-    wl = wl_of("f32", B, (16, 1), 8, 8, n_images=n_images, max_images=max(1, -(-nnz // B)), M=3)
+    wl = wl_of("f32", B, layers, 8, 8, n_images=n_images, max_images=max(1, -(-nnz // B)), M=3)
     pair = beside_the_oracle(wl)
     rng = np.random.default_rng(nnz)
     off = np.sort(rng.integers(0, nnz + 1, B - 1)) if nnz else np.zeros(B - 1, dtype=np.int64)
@@ -67,10 +77,12 @@ def test_lists_at_the_edges_of_parts(n_images, nnz, popular, blocks):
                           img_off=np.concatenate([[0], off, [nnz]]).astype(np.int32), img_id=ids.astype(np.int32),
                           label=(rng.random(B) < 0.3).astype(np.float32))
     for step in range(2):
-        assert in_blocks(pair, batch, f"{nnz} ids, {popular} popular, step {step}") == blocks
-    pair.check_state(f"{nnz} ids, {popular} popular")
+        names = launches_beside_the_oracle(pair, batch, f"{nnz} ids, {popular} popular, {layers}, step {step}")
+        assert ("view_blocks" in names) == blocks and ("begin" in names) == (PROLOGUE[layers] or not blocks)
+    pair.check_state(f"{nnz} ids, {popular} popular, {layers}")
 
 
+@pytest.mark.parametrize("layers", list(PROLOGUE))
 @pytest.mark.parametrize("n_images,nnz,shares", [
     (2_000, 19_200, {1_000: 0.6}), (2_000, 19_200, {0: 0.7}),       # one pass over the others
     (2_000, 9_000, {1_000: 0.6, 999: 0.2, 1_001: 0.2}),             # neighbours on both sides, in the same part
@@ -79,11 +91,11 @@ def test_lists_at_the_edges_of_parts(n_images, nnz, popular, blocks):
     (1 << 16, 19_100, {40_000: 0.9}), (1 << 22, 19_100, {4_000_000: 0.9}),   # two passes, three
     (2_000, 4_099, {7: 1.0}), (2_000, 2_048, {1_999: 1.0}), (2_000, 2_047, {1_999: 1.0}),   # the smallest part that is looked at
 ])
-def test_lists_that_are_mostly_one_id(n_images, nnz, shares):
+def test_lists_that_are_mostly_one_id(n_images, nnz, shares, layers):
     """Parts that set a popular id aside; the same for users, of whom one has most of the views."""
     from gear_inputs.pageviews import PageViewBatch
     B = 6_001
-    wl = wl_of("f32", B, (16, 1), 8, 8, n_images=n_images, n_users=5_000, max_images=4, M=7)
+    wl = wl_of("f32", B, layers, 8, 8, n_images=n_images, n_users=5_000, max_images=4, M=7)
     pair = beside_the_oracle(wl)
     rng = np.random.default_rng(nnz)
     for step in range(2):
@@ -98,8 +110,9 @@ def test_lists_that_are_mostly_one_id(n_images, nnz, shares):
         batch = PageViewBatch(user_id=users.astype(np.int32), url_id=rng.integers(0, wl.n_urls, B).astype(np.int32),
                               img_off=np.concatenate([[0], off, [nnz]]).astype(np.int32), img_id=ids.astype(np.int32),
                               label=(rng.random(B) < 0.3).astype(np.float32))
-        assert in_blocks(pair, batch, f"{nnz} ids, {shares}, step {step}")
-    pair.check_state(f"{nnz} ids, {shares}")
+        names = launches_beside_the_oracle(pair, batch, f"{nnz} ids, {shares}, {layers}, step {step}")
+        assert form_of_launches(names) == "blocks" and ("begin" in names) == PROLOGUE[layers]
+    pair.check_state(f"{nnz} ids, {shares}, {layers}")
 
 
 @pytest.mark.parametrize("dtype,batch,images", [
@@ -329,11 +342,12 @@ def test_blocks_of_hardly_any_image(nnz):
         assert torch.equal(a, b)
 
 
-def test_ids_at_any_address():
+@pytest.mark.parametrize("layers", list(PROLOGUE))
+def test_ids_at_any_address(layers):
     """Ids are read sixteen bytes at a time where their list begins at such an address, one by one elsewhere."""
     import paper_1806_03925_amd as g
     from gear_inputs import PageViewSource
-    wl = wl_of("f32", 700, (16, 1), 8, 8)
+    wl = wl_of("f32", 700, layers, 8, 8)
     results = []
     for shift in (0, 1, 3):
         st = g.GearState(g.config_for(wl))
@@ -345,20 +359,20 @@ def test_ids_at_any_address():
             moved = torch.empty(ids.numel() + shift, dtype=ids.dtype, device="cuda")[shift:]
             moved.copy_(ids)
             setattr(dev, name, moved)
-        g.gear_step(st, dev, wl.M, 0.1)
-        torch.cuda.synchronize()
-        assert int(st.status.item()) == 0
+        names = launches_of(st, dev, wl.M, 0.1)
+        assert int(st.status.item()) == 0 and form_of_launches(names) == "blocks" and ("begin" in names) == PROLOGUE[layers]
         results.append([t.clone() for t in (st.loss, st.n_ready, st.grad_accum, st.counts, st.user_emb, st.url_emb, st.mlp_params)])
     for other in results[1:]:
         assert all(torch.equal(a, b) for a, b in zip(results[0], other))
 
 
+@pytest.mark.parametrize("layers", list(PROLOGUE))
 @pytest.mark.parametrize("what", ["user", "image", "offset"])
-def test_a_bad_id_or_offset_leaves_everything_as_it_was(what):
+def test_a_bad_id_or_offset_leaves_everything_as_it_was(what, layers):
     """Whichever workgroup finds it, the others do not know: no table, counter or ready list may show a trace of the step."""
     import paper_1806_03925_amd as g
     from gear_inputs import PageViewSource
-    wl = wl_of("f32", 300, (16, 1), 8, 8, M=1)
+    wl = wl_of("f32", 300, layers, 8, 8, M=1)
     st = g.GearState(g.config_for(wl))
     g.gear_init_tables(st)
     batch = PageViewSource(wl).batch(0)
@@ -369,8 +383,8 @@ def test_a_bad_id_or_offset_leaves_everything_as_it_was(what):
     else:
         batch.img_off[100] = batch.img_off[102] + 1
     before = [t.clone() for t in (st.user_emb, st.url_emb, st.mlp_params, st.grad_accum, st.counts)]
-    g.gear_step(st, g.DeviceBatch.from_host(batch), wl.M, 0.1)
-    torch.cuda.synchronize()
+    names = launches_of(st, g.DeviceBatch.from_host(batch), wl.M, 0.1)
+    assert form_of_launches(names) == "blocks" and ("begin" in names) == PROLOGUE[layers]
     assert int(st.status.item()) == g.GEAR_ERR_RANGE and int(st.n_ready.item()) == 0
     for a, b in zip(before, (st.user_emb, st.url_emb, st.mlp_params, st.grad_accum, st.counts)):
         assert torch.equal(a, b)
