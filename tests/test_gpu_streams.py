@@ -183,6 +183,43 @@ def test_steps_on_streams_of_their_own_share_a_store_in_the_order_they_were_issu
         assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])   # without a prologue, with one
+def test_a_step_that_stops_part_way_keeps_its_place_in_the_order(dtype):
+    """The last launch of a short step leaves the event by which steps on other streams know their place behind it.  Where that launch, or an
+    earlier one, is not enqueued, what the step has done to the store so far still happens ahead of the next step's."""
+    import paper_1806_03925_amd as g
+    results = []
+    for apart in (False, True):
+        states = [state_of("tiny", 512, emb_dtype=dtype, dfv_dtype=dtype, mlp_dtype=dtype) for _ in range(2)]
+        (wl, first, src), (_, second, _) = states
+        second.grad_accum, second.counts = first.grad_accum, first.counts
+        dev = [g.DeviceBatch.from_host(src.batch(t, batch=512)) for t in range(10)]
+        streams = [torch.cuda.Stream() if apart else torch.cuda.current_stream() for _ in states]
+        torch.cuda.synchronize()
+        names = launches_of(first, dev[8], wl.M, 0.1)
+        assert names == ["begin"] * (dtype == "bf16") + ["view_blocks", "accumulate_wgrad", "param_update"]
+        assert launches_of(second, dev[9], wl.M, 0.1) == names
+        lists = []
+        for nth in range(1, len(names) + 1):
+            print(f"{dtype} apart {apart}, without launch {nth}", flush=True)
+            with torch.cuda.stream(streams[0]):
+                torch.cuda._sleep(3_000_000)
+                g.gear_debug_fail_launch(nth)
+                try:
+                    with pytest.raises(g.GearError):
+                        g.gear_step(first, dev[2 * nth - 2], wl.M, 0.1)
+                finally:
+                    g.gear_debug_fail_launch(0)
+            with torch.cuda.stream(streams[1]):
+                g.gear_step(second, dev[2 * nth - 1], wl.M, 0.1)
+            torch.cuda.synchronize()
+            assert int(second.status.item()) == 0
+            lists += outputs(second)
+        results.append(lists)
+    for a, b in zip(*results):
+        assert torch.equal(a, b)
+
+
 # on one stream, in blocks and layer by layer with the sums of blocks; on two, the fork to the helper ahead of all launches and behind the first
 @pytest.mark.parametrize("views,one", [(SHORT, False), (LONG, True), (LONG, False), (BACK, False), (HERE, False)])
 def test_a_step_recorded_into_a_graph_between_steps_on_other_streams(views, one):
