@@ -376,8 +376,9 @@ class LaneScope {
   LaneScope(const LaneScope &) = delete;
   LaneScope &operator=(const LaneScope &) = delete;
   // The step takes its place behind the last one.  Of two long steps the helper stream keeps the order by itself; behind or
-  // ahead of a short one it takes an event.  (A short step pays 2 us for one recorded behind it: 49.7 -> 51.8, 78.6 -> 80.5 and
-  // 104.9 -> 106.6 us on the three smallest workloads in an earlier form; 0.3 us left by its last launch itself, done_by.)
+  // ahead of a short one it takes an event.  (In an earlier form a short step paid 2 us for one recorded behind it, 49.7 -> 51.8, 78.6 ->
+  // 80.5 and 104.9 -> 106.6 us on the three smallest workloads, and for one left by its last launch itself 0.3 us where the device was the
+  // slower side and 4 us where the host was.  Now the latter is the cheaper one on either side: done_by.)
   // A step that is being captured has the place its graph is launched in; it leaves the events of the others alone.
   // `on`: the stream that first looks at the store; what the step gives to its streams before this call, or to others than this
   // one, runs beside the steps ahead of it (us for a step of each of two programs on streams of their own, with the whole step
@@ -393,9 +394,11 @@ class LaneScope {
   }
   // The launches that an event is to come behind leave it themselves where they can: what follows on the stream then waits for no
   // event's packet (us between the ends of a launch and the start of the next one on its stream, with the packet / without: 8 to 10 / 3;
-  // from a launch on one stream to one on the other that waits for it 10 to 12 / 6 to 8; a step of 512 views 31.3 / 30.1, of 16 384
-  // bf16 159 / 154, the counts of its first passes in the prologue included).  Not while they are being captured.  `left`: the launch
-  // ahead was given the event.
+  // from a launch on one stream to one on the other that waits for it 10 to 12 / 6 to 8).  us a step, all events recorded / left: 512 views
+  // 26.4 / 25.4, 4096 fp32 74.3 / 72.7, 16 384 fp32 164.4 / 159.6, bf16 151.5 / 149.4, 65 536 936.5 / 930.6.  The host issues a step of 512
+  // views in 18.6 / 18.2 us (23.5 / 22.7 on a slower core), of 16 384 in 70 / 64 (85 / 90), and one that is waited for takes 47 / 46 and
+  // 173 / 174; first passes on a new state differ by no more than two of one build (58 / 57, 230 / 241, 1112 / 1104).  Not while they are
+  // being captured.  `left`: the launch ahead was given the event.
   hipEvent_t fork_by() const { return side_ && !captured_ ? side_->fork : nullptr; }
   hipEvent_t mark_by() const { return side_ && !captured_ ? join_ : nullptr; }
   hipEvent_t mark_checked_by() const { return side_ && !captured_ ? side_->checked : nullptr; }

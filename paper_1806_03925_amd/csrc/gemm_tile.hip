@@ -395,12 +395,14 @@ k_gemm_tn_tile(TnTileArgs args, int K, int splits, const int32_t *__restrict__ s
 
 // bf16: what the ranges leave is written, read again and added by the parameter update, so two workgroups of a CU that would walk
 // neighbouring ranges of one tile are one of twice the wavefronts instead, which leaves one partial: of 576 -> 512 -> 256 15 MB and not 31.
-// us a step, single / pairs, in blocks: 16 384 views 153.1 / 149.3, with Adam 158.4 / 154.1, 10 001 127.3 / 125.4; layer by layer on two
+// us a step, single / pairs, in blocks: 16 384 views 153.4 / 150.0, with Adam 158.5 / 154.9, 10 001 127.4 / 125.6 (on the same batch
+// over and over, whose rows are in the caches, 138.8 / 138.5, 142.7 / 141.0, 118.3 / 117.3); layer by layer on two
 // streams, with the accumulation beside them: 8193 of 1024 -> 256 168.3 / 164.5, 12 000 of 704 -> 640 -> 128 212.6 / 209.5, 16 384 of 1024 ->
 // 1024 304.6 / 298.5, 32 736 of 576 -> 512 -> 256 327.6 / 321.3; on one, 2000 of 576 -> 512 -> 256 108.5 / 106.7.  Where whole ranges of pairs
 // leave more of the CUs out than those of single ones do, they are not taken (26 tiles, 234 of 256 against 494 of 512: 184.9 / 186.9), nor
 // where there are as many ranges either way, so that no partial is left out (a range has 64 rows at least, and there are 64 at most: 600
-// views of 320 -> 256 91.6 / 92.1, 1500 of 128 -> 64 82.7 / 83.4, 16 384 of 128 -> 128 134.0 / 135.1, wider ones the same), nor in fp32, whose 64 x 64 tiles leave little (16 384 views 157.3 / 158.0).
+// views of 320 -> 256 91.6 / 92.1, 1500 of 128 -> 64 82.7 / 83.4, 16 384 of 128 -> 128 134.0 / 135.1, wider ones the same), nor in fp32, whose
+// 64 x 64 tiles leave little (16 384 views 157.3 / 158.0).
 template <typename C>
 __global__ void __launch_bounds__(2 * C::THREADS)
 k_gemm_tn_pair(TnTileArgs args, int K, int splits, const int32_t *__restrict__ status, const int32_t *__restrict__ k_dev) {

@@ -728,7 +728,8 @@ constexpr int kStateSpan = 3 * kMaxParts;   // words of three per part, then a t
 // them.  us a step, with the prologue / without: 96 -> 64 (49 KB) 512 views 30.3 / 26.1, 2000 34.9 / 28.9, 6000 44.4 / 41.0; 96 -> 128
 // (98 KB) 512 views 31.7 / 27.1, 6000 47.0 / 43.5; 96 -> 128 -> 64 (164 KB) 512 32.2 / 31.7, 4000 42.4 / 41.7; 320 -> 64 (164 KB) 1000
 // 37.3 / 34.1, 4000 57.2 / 53.6.  Beyond: 288 -> 64 -> 64 (180 KB) 1000 33.7 / 34.1; 1056 -> 24 (203 KB) 1000 51.4 / 52.3; 320 -> 256 -> 128
-// 4096 74.8 / 78.1; and with more than a block a CU 288 -> 64 (147 KB) 5000 44.6 / 47.3, 288 -> 256 61.0 / 71.0.
+// 4096 74.8 / 78.1; and with more than a block a CU 288 -> 64 (147 KB) 5000 44.6 / 47.3, 288 -> 256 61.0 / 71.0.  bf16 blocks keep the
+// prologue, which rounds the weights once for all: every block would read twice the bytes and round them itself (not tried).
 constexpr double kDirectBytes = 170e3, kDirectBytesLong = 100e3;   // up to 4096 views, beyond
 // And of all occurrences' gradients: where the accumulation is long, what every one of its wavefronts does to find its units
 // (local_parts.hpp) keeps it longer.  With the prologue / without, M = 2, however the ids are spread unless it says so: 320 -> 64, 11 500
@@ -807,7 +808,7 @@ bool plan_long(const Layout &lay, int dt, int B, int nnz, double stream, size_t 
 //   20 000 ids in one a CU: 134 against 102).
 // - A list of at most kLocalMost ids, in as many parts as an item's 32 bits ask for: a longer one whose ids are most of them
 //   one image would not fit in its part's LDS (19 000 ids, 96 -> 64 fp32: 30 % of them one image 57 / 74, 60 % 65 / 73, all 76 /
-//   71; 320 -> 256 fp32: 70 / 86, 75 / 86, 87 / 84; Zipf 1.5 80 / 103; 25 000 ids of Zipf 1.5 in an earlier form 109 / 88).
+//   71, without a prologue 4 to 5 less; 320 -> 256 fp32: 70 / 86, 75 / 86, 87 / 84; Zipf 1.5 80 / 103; 25 000 ids of Zipf 1.5 in an earlier form 109 / 88).
 bool plan_rows(const gear_config &cfg, const Layout &lay, int B, int nnz, bool local, RowsPlan *plan) {
   const int dt = cfg.mlp_dtype, es = (int)dtype_bytes(dt);
   double stream = 0.0;
